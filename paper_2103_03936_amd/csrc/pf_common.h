@@ -98,6 +98,42 @@ struct TimingScope {
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
+// The plans of the last few layer shapes a thread has called: a call asks for its plan two or three times (workspace
+// query, checks, launch), and a training loop calls the same dozens of layers again and again.  A slot is replaced by
+// the next shape that hashes to it.
+template <class KEY, class PLAN>
+struct PlanCache {
+    static constexpr int SLOTS = 64;
+    struct Slot {
+        bool used = false;
+        KEY key;
+        PLAN plan;
+    } slot[SLOTS];
+    template <class MAKE>
+    const PLAN &get(const KEY &k, MAKE make)
+    {
+        uint64_t h = 1469598103934665603ULL;
+        for (i64 v : k.v) h = (h ^ (uint64_t)v) * 1099511628211ULL;
+        Slot &s = slot[(h >> 32) % SLOTS];
+        if (!s.used || !(s.key == k)) {
+            s.plan = make();
+            s.key = k;
+            s.used = true;
+        }
+        return s.plan;
+    }
+};
+template <int N>
+struct PlanKey {
+    i64 v[N];
+    bool operator==(const PlanKey &o) const
+    {
+        for (int i = 0; i < N; ++i)
+            if (v[i] != o.v[i]) return false;
+        return true;
+    }
+};
+
 // Bump allocator over the caller's workspace.
 struct Workspace {
     char *base;
@@ -119,11 +155,14 @@ struct Workspace {
 
 // Launch `kernel` on `stream`, bracketed by timing events when enabled.  Evaluates to a
 // pf_status in `status_var` (PF_OK or PF_ERR_LAUNCH).
-#define PF_LAUNCH(status_var, name, kernel, grid, block, stream, ...)                    \
+#define PF_LAUNCH(status_var, name, kernel, grid, block, stream, ...) \
+    PF_LAUNCH_LDS(status_var, name, kernel, grid, block, 0, stream, __VA_ARGS__)
+// (the same with `lds` bytes of LDS sized at launch)
+#define PF_LAUNCH_LDS(status_var, name, kernel, grid, block, lds, stream, ...)            \
     do {                                                                                  \
         if ((status_var) == PF_OK) {                                                      \
             pf::TimingScope pf_ts_(name, stream);                                         \
-            hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);              \
+            hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);            \
             hipError_t pf_e_ = hipGetLastError();                                         \
             if (pf_e_ != hipSuccess) (status_var) = pf::set_hip_error(pf_e_);             \
         }                                                                                 \

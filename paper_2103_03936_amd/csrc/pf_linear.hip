@@ -5,6 +5,7 @@
 #include "pf_linear_chain.h"
 #include "pf_skinny.h"
 #include "pf_linear_small.h"
+#include "pf_tile_host.h"
 #include "pf_conv_wgrad.h"
 #include <mutex>
 #include "pf_gemm.h"
@@ -133,11 +134,15 @@ struct LinearPlan {
     int wg_cols;           // columns per workgroup of that kernel
     bool skinny;           // fp32 with at most 128 rows: the weight-streaming kernels of the LSTM cell
     size_t n_part_sk;      // their slice sums, floats
+    bool tiles;            // every dimension holds a 16-byte piece: the tiled products of pf_tile.h
+    TilePlan t_T, t_dT, t_Y; // ... their tile shapes and splits
+    TileGroup t_grads;     // ... dX, dU and dV in one launch
+    size_t n_part_T, n_part_g; // ... partial sums, floats
     bool small;            // fp32 with at most 128 rows and dimensions in whole tiles: two launches per direction
     size_t n_small;        // slices of the rank-r intermediate(s) between them, floats
 };
 
-static LinearPlan plan_linear(const pf_linear_desc *d)
+static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
     LinearPlan p;
     p.ks_dU = choose_ksplit(d->out, d->r, d->M);
@@ -165,6 +170,25 @@ static LinearPlan plan_linear(const pf_linear_desc *d)
         p.n_part_sk = f > b ? f : b;
         const size_t fwd = align_up(p.n_T * sizeof(float)) + align_up(p.n_part_sk * sizeof(float));
         const size_t bwd = 2 * align_up(p.n_T * sizeof(float)) + align_up(p.n_part_sk * sizeof(float));
+        if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
+        if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
+    }
+    const i64 piece = d->dtype == PF_BF16 ? 8 : 4;
+    p.tiles = d->M > 0 && d->in >= piece && d->out >= piece && d->r >= piece;
+    p.n_part_T = p.n_part_g = 0;
+    if (p.tiles) {
+        const i64 M = d->M, in = d->in, out = d->out, r = d->r;
+        p.t_T = plan_tiles(d->dtype, M, r, in, 16);
+        p.t_Y = plan_tiles(d->dtype, M, out, r, 1);
+        p.t_dT = plan_tiles(d->dtype, M, r, out, 16);
+        const TileNeed need[3] = {{M, in, r, false}, {out, r, M, true}, {in, r, M, true}};
+        p.t_grads = plan_tile_group(d->dtype, need, 3);
+        const int ks = p.t_T.ksplit > p.t_dT.ksplit ? p.t_T.ksplit : p.t_dT.ksplit;
+        p.n_part_T = ks > 1 ? (size_t)(ks * M * r) : 0;
+        p.n_part_g = (size_t)(p.t_grads.ksplit[1] * (out * r + out) + p.t_grads.ksplit[2] * in * r) + 128;
+        const size_t el = d->dtype == PF_BF16 ? 2 : 4;
+        const size_t fwd = align_up(p.n_T * el) + align_up(p.n_part_T * 4);
+        const size_t bwd = 2 * align_up(p.n_T * el) + align_up((p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g) * 4) + 512;
         if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
         if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
     }
@@ -207,6 +231,12 @@ static LinearPlan plan_linear(const pf_linear_desc *d)
         if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
     }
     return p;
+}
+
+static const LinearPlan &plan_linear(const pf_linear_desc *d)
+{
+    static thread_local PlanCache<PlanKey<6>, LinearPlan> cache;
+    return cache.get(PlanKey<6>{{d->M, d->in, d->out, d->r, d->dtype, d->has_bias}}, [&] { return make_linear_plan(d); });
 }
 
 // ------------------------------------------------------------- any-shape
@@ -282,6 +312,115 @@ static int linear_bwd_generic(const pf_linear_desc *d, const T *X, const T *V, c
         if (st != PF_OK) return st;
     }
     if (d->has_bias && dbias) st = launch_colsum<T>(s, dY, part, dbias, M, out, out, accumulate);
+    return st;
+}
+
+// ---------------------------------------------------- any shape of at least a 16-byte piece
+// T = A B (A [M][K], B [K][r]) in the call's element type, through partial sums when the product has too few tiles for
+// the chip.
+template <typename T>
+static int tiles_intermediate(hipStream_t s, const char *name, const TilePlan &t, int M, int r, int K, const T *A,
+                              const T *B, T *out, float *part)
+{
+    const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32;
+    TileArgs a = {};
+    TileProb p = tile_prob(TILE_NN, M, r, K, A, K, B, r, out, r);
+    const bool split = t.ksplit > 1;
+    if (split) {
+        p.o.C = part;
+        p.o.f32 = 1;
+        p.o.split_stride = (i64)M * r;
+    }
+    tile_add(a, t.shape, dt, p, t.ksplit);
+    int st = launch_tiles_linear(s, name, dt, t.shape, a);
+    if (st != PF_OK || !split) return st;
+    SplitSumArgs ss = {};
+    split_sum_add(ss, SplitSum{part, (float *)out, (i64)M * r, (i64)M * r, a.p[0].ksplit, 0, nullptr, 0, sizeof(T) == 2});
+    return launch_split_sums(s, ss);
+}
+
+// Two launches: T = X V, then Y = act(T U^T + bias + residual) with the epilogue on the tile.
+template <typename T>
+static int linear_fwd_tiles(const pf_linear_desc *d, const LinearPlan &p, const T *X, const T *V, const T *U,
+                            const T *bias, T *Y, T *T_save, Workspace &ws, hipStream_t s, const LinEpilogue &ep)
+{
+    const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
+    T *Tws = ws.take<T>(p.n_T);
+    float *part = ws.take<float>(p.n_part_T);
+    T *Tt = T_save ? T_save : Tws;
+    int st = tiles_intermediate<T>(s, "linear_T=X*V", p.t_T, M, r, in, X, V, Tt, part);
+    if (st != PF_OK) return st;
+    TileArgs a = {};
+    TileProb q = tile_prob(TILE_NT, M, out, r, Tt, r, U, r, Y, out);
+    q.o.bias = d->has_bias ? bias : nullptr;
+    q.o.add = ep.add;
+    q.o.relu = ep.relu;
+    if (ep.used) *ep.used = true;
+    tile_add(a, p.t_Y.shape, d->dtype, q, 1);
+    return launch_tiles_linear(s, "linear_Y=T*Ut", d->dtype, p.t_Y.shape, a);
+}
+
+// Two or three launches: dT = dY U (T = X V again when it was not kept), then dX, dU, dV and the bias gradient side by
+// side, then the sums over their splits where the rows were split.
+template <typename T>
+static int linear_bwd_tiles(const pf_linear_desc *d, const LinearPlan &p, const T *X, const T *V, const T *U, const T *dY,
+                            const T *T_saved, T *dX, float *dU, float *dV, float *dbias, int accumulate, Workspace &ws,
+                            hipStream_t s, const LinEpilogue &ep)
+{
+    const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
+    T *Tws = ws.take<T>(p.n_T), *dT = ws.take<T>(p.n_T);
+    float *part = ws.take<float>(p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g);
+    int st = PF_OK;
+    if (dU && !T_saved) {
+        st = tiles_intermediate<T>(s, "linear_T=X*V", p.t_T, M, r, in, X, V, Tws, part);
+        if (st != PF_OK) return st;
+    }
+    if (dX || dV) {
+        st = tiles_intermediate<T>(s, "linear_dT=dY*U", p.t_dT, M, r, out, dY, U, dT, part);
+        if (st != PF_OK) return st;
+    }
+    const TileShape sh = p.t_grads.shape;
+    const bool want_db = d->has_bias && dbias;
+    TileArgs a = {};
+    SplitSumArgs ss = {};
+    if (dX) {
+        TileProb q = tile_prob(TILE_NT, M, in, r, dT, r, V, r, dX, in);
+        q.o.add = ep.add;
+        q.o.mask = ep.mask;
+        if (ep.used) *ep.used = true;
+        tile_add(a, sh, d->dtype, q, 1);
+    }
+    const auto grad = [&](const T *A, int m, const T *B, float *dst, int ks, float *sums) {
+        TileProb q = tile_prob(TILE_TN, m, r, M, A, m, B, r, dst, r);
+        q.o.f32 = 1;
+        q.o.accumulate = accumulate;
+        q.o.sums = sums;
+        float *psum = part;
+        if (ks > 1) {
+            q.o.accumulate = 0;
+            q.o.C = part;
+            q.o.split_stride = (i64)m * r;
+            part += (i64)ks * m * r;
+            if (sums) {
+                psum = part;
+                q.o.sums = psum;
+                q.o.sums_stride = m;
+                part += (i64)ks * m;
+            }
+            part += (64 - (part - (float *)nullptr) % 64) % 64; // the next partial sums start 256-byte aligned
+        }
+        tile_add(a, sh, d->dtype, q, ks);
+        if (ks > 1) {
+            const int n = a.p[a.n - 1].ksplit;
+            split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, (i64)m * r, (i64)m * r, n, accumulate, nullptr, 0, 0});
+            if (sums) split_sum_add(ss, SplitSum{psum, sums, m, m, n, accumulate, nullptr, 0, 0});
+        }
+    };
+    if (dU) grad(dY, out, T_saved ? T_saved : Tws, dU, p.t_grads.ksplit[1], want_db ? dbias : nullptr);
+    if (dV) grad(X, in, dT, dV, p.t_grads.ksplit[2], nullptr);
+    st = launch_tiles_linear(s, "linear_dX,dU,dV", d->dtype, sh, a);
+    if (st == PF_OK) st = launch_split_sums(s, ss);
+    if (st == PF_OK && want_db && !dU) st = launch_colsum<T>(s, dY, part, dbias, M, out, out, accumulate);
     return st;
 }
 
@@ -642,24 +781,32 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (!V || !U || (d->has_bias && !bias)) return PF_ERR_NULL;
     if (d->M > 0 && (!X || !Y)) return PF_ERR_NULL;
     if (any_misaligned({X, V, U, bias, Y, T_save}, align)) return PF_ERR_UNSUPPORTED;
-    const size_t need = plan_linear(d).fwd_bytes;
+    const LinearPlan p = plan_linear(d);
+    const size_t need = p.fwd_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     if (d->M == 0) return PF_OK;
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    if (d->dtype == PF_F32 && plan_linear(d).small)
-        return linear_fwd_small(d, plan_linear(d), (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.small)
+        return linear_fwd_small(d, p, (const float *)X, (const float *)V, (const float *)U,
                                 (const float *)bias, (float *)Y, (float *)T_save, ws, s);
-    if (d->dtype == PF_F32 && plan_linear(d).skinny)
-        return linear_fwd_skinny(d, plan_linear(d), (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.skinny)
+        return linear_fwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)bias, (float *)Y, (float *)T_save, ws, s);
+    if (d->dtype == PF_F32 && p.tiles)
+        return linear_fwd_tiles<float>(d, p, (const float *)X, (const float *)V, (const float *)U,
+                                       (const float *)bias, (float *)Y, (float *)T_save, ws, s, ep ? *ep : LinEpilogue{});
     if (d->dtype == PF_F32)
         return linear_fwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)bias,
                                          (float *)Y, (float *)T_save, ws, s);
-    if (plan_linear(d).fused)
+    if (p.fused)
         return linear_fwd_fused(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)bias,
                                 (bf16_t *)Y, (bf16_t *)T_save, ws, s, ep ? *ep : LinEpilogue{});
+    if (p.tiles)
+        return linear_fwd_tiles<bf16_t>(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+                                        (const bf16_t *)bias, (bf16_t *)Y, (bf16_t *)T_save, ws, s,
+                                        ep ? *ep : LinEpilogue{});
     return linear_fwd_generic<bf16_t>(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
                                       (const bf16_t *)bias, (bf16_t *)Y, (bf16_t *)T_save, ws, s);
 }
@@ -673,28 +820,36 @@ int pf::linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (!V || !U) return PF_ERR_NULL;
     if (d->M > 0 && (!X || !dY)) return PF_ERR_NULL;
     if (any_misaligned({X, V, U, dY, T_saved, dX}, align) || any_misaligned({dU, dV, dbias}, 4)) return PF_ERR_UNSUPPORTED;
-    const size_t need = plan_linear(d).bwd_bytes;
+    const LinearPlan p = plan_linear(d);
+    const size_t need = p.bwd_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    if (d->dtype == PF_F32 && plan_linear(d).small)
-        return linear_bwd_small(d, plan_linear(d), (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.small)
+        return linear_bwd_small(d, p, (const float *)X, (const float *)V, (const float *)U,
                                 (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                 (float *)dbias, accumulate, ws, s);
-    if (d->dtype == PF_F32 && plan_linear(d).skinny)
-        return linear_bwd_skinny(d, plan_linear(d), (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.skinny)
+        return linear_bwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                  (float *)dbias, accumulate, ws, s);
+    if (d->dtype == PF_F32 && p.tiles)
+        return linear_bwd_tiles<float>(d, p, (const float *)X, (const float *)V, (const float *)U,
+                                       (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
+                                       (float *)dbias, accumulate, ws, s, ep ? *ep : LinEpilogue{});
     if (d->dtype == PF_F32)
         return linear_bwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
                                          (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                          (float *)dbias, accumulate, ws, s);
-    const LinearPlan p = plan_linear(d);
     if (p.fused && dX && d->M > 0)
         return linear_bwd_fused(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
                                 (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias,
                                 accumulate, ws, s, ep ? *ep : LinEpilogue{});
+    if (p.tiles)
+        return linear_bwd_tiles<bf16_t>(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
+                                        (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias,
+                                        accumulate, ws, s, ep ? *ep : LinEpilogue{});
     return linear_bwd_generic<bf16_t>(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
                                       (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
                                       (float *)dV, (float *)dbias, accumulate, ws, s);

@@ -1,0 +1,696 @@
+// Tiled matrix products for any shape, the device side: C(m,n) = sum_k A(m,k) B(k,n) on one BM x BN tile.
+//
+// Operands reach LDS in 16-byte pieces that keep the direction they have in memory: along k ("KC": tile rows of BK
+// elements) or along the row / column index ("MC": one tile row per k).  MC tiles of bf16 are read with the
+// transposing LDS read, MC tiles of float one element per lane, so neither needs a transposed copy.  A piece may start
+// at any element (rows of odd length): the load is then an unaligned 16-byte load, which costs the memory pipeline
+// about three aligned ones and is still four times cheaper than eight element loads.  Edges never branch per element: the
+// address of a piece that would leave its row is pulled back inside the row and the piece is shifted into place when
+// it is written to LDS; what lies past K is written as zero, what lies past M or N is never stored.
+//
+// The pieces of NS chunks of the contraction are in flight in registers while one of two LDS buffers is multiplied
+// and the other is filled: one barrier per chunk.  A chunk is 64 (bf16) or 32 (float) deep, so that a workgroup has
+// 16 to 64 KB outstanding: with few workgroups per compute unit it is the latency of the loads, not their number, that
+// bounds these products.  float sums every chunk on its own before adding it to the total (the rounding error then
+// grows with K / 32).
+#pragma once
+
+#include "pf_common.h"
+
+namespace pf {
+
+template <typename CT>
+struct TileEl;
+template <>
+struct TileEl<bf16_t> {
+    typedef uint16_t elem;
+    static constexpr int V = 8, BK = 64, PAD = 8;
+};
+template <>
+struct TileEl<float> {
+    typedef float elem;
+    static constexpr int V = 4, BK = 32, PAD = 4;
+};
+
+// BM x BN tile, WM x WN wavefronts over it; the 4 / (WM WN) wavefronts that share a block split the contraction
+template <int BM_, int BN_, int WM_, int WN_, int NS_>
+struct TileCfg {
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, WK = 4 / (WM_ * WN_);
+};
+
+constexpr int TILE_THREADS = 256;
+
+// ------------------------------------------------------------------ 16-byte pieces
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+
+__device__ __forceinline__ uint4 ldg16(const void *p)
+{
+    const u32x4_any v = *(const u32x4_any *)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void stg16(void *p, uint4 v)
+{
+    u32x4_any w;
+    w.x = v.x, w.y = v.y, w.z = v.z, w.w = v.w;
+    *(u32x4_any *)p = w;
+}
+
+// element e of the result is element e + s of r (0 where that is outside the piece)
+template <int EB>
+__device__ __forceinline__ uint4 piece_shift(uint4 r, int s)
+{
+    const int b = 8 * EB * s; // bits
+    if (b == 0) return r;
+    uint64_t lo = (uint64_t)r.y << 32 | r.x, hi = (uint64_t)r.w << 32 | r.z, l = 0, h = 0;
+    if (b > 0) {
+        if (b < 64) {
+            l = lo >> b | hi << (64 - b);
+            h = hi >> b;
+        } else if (b == 64) {
+            l = hi;
+        } else if (b < 128) {
+            l = hi >> (b - 64);
+        }
+    } else {
+        const int c = -b;
+        if (c < 64) {
+            h = hi << c | lo >> (64 - c);
+            l = lo << c;
+        } else if (c == 64) {
+            h = lo;
+        } else if (c < 128) {
+            h = lo << (c - 64);
+        }
+    }
+    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+
+__device__ __forceinline__ int bit_all(uint32_t m, int b) { return ((int)(m << (31 - b))) >> 31; } // 0 or -1
+
+// keep element e where bit e of m is set
+template <int V>
+__device__ __forceinline__ uint4 piece_mask(uint4 r, uint32_t m)
+{
+    if (V == 4) {
+        return make_uint4(r.x & bit_all(m, 0), r.y & bit_all(m, 1), r.z & bit_all(m, 2), r.w & bit_all(m, 3));
+    } else {
+        const auto two = [&](int b) {
+            return ((uint32_t)bit_all(m, b) & 0xffffu) | ((uint32_t)bit_all(m, b + 1) & 0xffff0000u);
+        };
+        return make_uint4(r.x & two(0), r.y & two(2), r.z & two(4), r.w & two(6));
+    }
+}
+
+template <typename CT>
+__device__ __forceinline__ void piece_floats(uint4 r, float *f)
+{
+    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+    if (sizeof(CT) == 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(w[e]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            f[2 * e] = __uint_as_float(w[e] << 16);
+            f[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u);
+        }
+    }
+}
+template <typename CT>
+__device__ __forceinline__ uint4 floats_piece(const float *f)
+{
+    if (sizeof(CT) == 4)
+        return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]), __float_as_uint(f[3]));
+    return make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]),
+                      pack_bf16x2(f[6], f[7]));
+}
+
+// ------------------------------------------------------------------ operand loaders
+// A loader owns CH pieces of a tile per thread.  load() issues the loads of the next chunk, store() writes the oldest
+// outstanding chunk to LDS; both walk the same sequence of chunks.  XF floats travel with a chunk's pieces (row
+// scales).  SUM (weight gradients) adds up what passes.
+
+// Matrix stored [rows][K] with k contiguous, leading dimension ld
+template <typename CT, int ROWS, bool SUM = false>
+struct LoadKC {
+    typedef typename TileEl<CT>::elem elem;
+    static constexpr bool KC = true;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V,
+                         CH = ROWS * CPR / TILE_THREADS, LDS = ROWS * PITCH, XF = 1;
+    const elem *rp[CH];
+    int K, kc, row, kl, ks;
+    float sum[SUM ? CH : 1];
+
+    __device__ __forceinline__ void init(const void *p, i64 ld, int rows, int K_, int row0, int kbeg, int tid)
+    {
+        K = K_;
+        kc = (tid % CPR) * V;
+        row = tid / CPR;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = min(row0 + row + i * (TILE_THREADS / CPR), rows - 1);
+            rp[i] = (const elem *)p + (i64)r * ld;
+            if (SUM) sum[i] = 0.f;
+        }
+        kl = ks = kbeg;
+    }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    {
+        const int k = min(kl + kc, K - V);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) r[i] = ldg16(rp[i] + k);
+        kl += BK;
+    }
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    {
+        const bool tail = ks + BK > K;
+        const int s = ks + kc - min(ks + kc, K - V);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            uint4 v = r[i];
+            if (tail) v = piece_shift<sizeof(elem)>(v, s);
+            *(uint4 *)&lds[(row + i * (TILE_THREADS / CPR)) * PITCH + kc] = v;
+            if (SUM) {
+                float f[8];
+                piece_floats<CT>(v, f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) sum[i] += f[e];
+            }
+        }
+        ks += BK;
+    }
+    // row sums to out[row0 + ..] (all threads; CPR neighbouring lanes hold the shares of a row)
+    template <class PUT>
+    __device__ __forceinline__ void put_sums(float *, int, PUT put)
+    {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            float v = sum[SUM ? i : 0];
+#pragma unroll
+            for (int d = 1; d < CPR; d <<= 1) v += __shfl_xor(v, d, 64);
+            if (kc == 0) put(row + i * (TILE_THREADS / CPR), v);
+        }
+    }
+};
+
+// Matrix stored [K][cols] with the row / column index contiguous; kscale (nullable): row k is multiplied by kscale[k]
+template <typename CT, int ROWS, bool SUM = false, bool SCALE = false>
+struct LoadMC {
+    typedef typename TileEl<CT>::elem elem;
+    static constexpr bool KC = false;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V,
+                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = SCALE ? CH : 1;
+    const elem *p;
+    const float *kscale;
+    i64 ld;
+    int K, mc, shift, krow, kl, ks;
+    float sum[SUM ? V : 1];
+
+    __device__ __forceinline__ void init(const void *p_, i64 ld_, int cols, int K_, int col0, int kbeg, int tid,
+                                         const float *kscale_ = nullptr)
+    {
+        K = K_;
+        ld = ld_;
+        mc = (tid % CPR) * V;
+        krow = tid / CPR;
+        const int m = min(col0 + mc, cols - V);
+        shift = col0 + mc - m;
+        p = (const elem *)p_ + m;
+        kscale = kscale_;
+        kl = ks = kbeg;
+        if (SUM) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) sum[SUM ? e : 0] = 0.f;
+        }
+    }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int k = min(kl + krow + i * KSTEP, K - 1);
+            r[i] = ldg16(p + (i64)k * ld);
+            if (SCALE) x[SCALE ? i : 0] = kscale ? kscale[k] : 1.f;
+        }
+        kl += BK;
+    }
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    {
+        const bool tail = ks + BK > K;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            uint4 v = r[i];
+            const int k = ks + krow + i * KSTEP;
+            if (shift) v = piece_shift<sizeof(elem)>(v, shift);
+            if (tail && k >= K) v = make_uint4(0, 0, 0, 0);
+            if (SCALE && kscale) {
+                const float s = x[SCALE ? i : 0];
+                float f[8];
+                piece_floats<CT>(v, f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) f[e] *= s;
+                v = floats_piece<CT>(f);
+            }
+            *(uint4 *)&lds[(krow + i * KSTEP) * PITCH + mc] = v;
+            if (SUM) {
+                float f[8];
+                piece_floats<CT>(v, f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) sum[SUM ? e : 0] += f[e];
+            }
+        }
+        ks += BK;
+    }
+    // column sums: the KSTEP threads that share columns meet in LDS (KSTEP * ROWS floats), added in a fixed order
+    template <class PUT>
+    __device__ __forceinline__ void put_sums(float *red, int tid, PUT put)
+    {
+#pragma unroll
+        for (int e = 0; e < V; ++e) red[krow * ROWS + mc + e] = sum[SUM ? e : 0];
+        __syncthreads();
+        if (tid < ROWS) {
+            float v = 0.f;
+#pragma unroll
+            for (int q = 0; q < KSTEP; ++q) v += red[q * ROWS + tid];
+            put(tid, v);
+        }
+    }
+};
+
+// ------------------------------------------------------------------ convolution operands
+constexpr int TILE_MAX_TAPS = 25;
+
+// An activation tensor [N][CH][plane] seen through a filter's taps over a grid of pixels gH x gW per image:
+// (channel, tap, pixel (y, x)) is the element (y s + dy[tap], x s + dx[tap]) of the channel's H x W plane, or zero
+// outside it.  Pixels of an image are padded to whole 16-byte pieces: pixel index = image * HC * V + position.
+// Without stride, and with gW == W, the pixels of a piece are neighbours in memory whatever the tap, so a piece is
+// one 16-byte load at an element offset plus a mask of the elements that lie in the plane.
+struct PixView {
+    const void *p;
+    i64 total; // elements of the tensor
+    int N, CH, H, W, gH, gW, s, HC, ntap;
+    signed char dy[TILE_MAX_TAPS], dx[TILE_MAX_TAPS];
+};
+
+// (mask of the elements of the piece at position pos that the tap finds inside the plane)
+template <int V>
+__device__ __forceinline__ uint32_t pix_mask(const PixView &g, int pos, int tap)
+{
+    uint32_t m = 0;
+    int y = pos / g.gW, x = pos - y * g.gW;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        const int iy = y * g.s + g.dy[tap], ix = x * g.s + g.dx[tap];
+        if (y < g.gH && iy >= 0 && iy < g.H && ix >= 0 && ix < g.W) m |= 1u << e;
+        if (++x == g.gW) x = 0, ++y;
+    }
+    return m;
+}
+
+// B operand (k = (channel, tap), n = pixel): one tile row per k, pixels contiguous.  Tables in LDS: offset of every tap,
+// mask of every (tap, piece of the tile).
+template <typename CT, int ROWS, bool GATHER>
+struct LoadPixMC {
+    typedef typename TileEl<CT>::elem elem;
+    static constexpr bool KC = false;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V,
+                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = 1;
+    static constexpr int TAB = 4 * TILE_MAX_TAPS + TILE_MAX_TAPS * CPR; // bytes of tables
+    const elem *p;
+    const int *toff;
+    const unsigned char *tmask;
+    i64 plane0, last; // element of channel 0 at the piece's position; last element address a piece may start at
+    int HW, ntap, K, mc, col, krow, kl, ks, inc_c, inc_t;
+    bool masked;
+    int lc[CH], lt[CH], sc[CH], st[CH]; // (channel, tap) of the rows to load / to store next
+    int pixoff[GATHER ? V : 1];
+
+    // tab: TAB bytes of LDS; ends with a barrier
+    __device__ __forceinline__ void init(const PixView &g, int n0, int kbeg, int tid, unsigned char *tab)
+    {
+        p = (const elem *)g.p;
+        HW = g.H * g.W;
+        ntap = g.ntap;
+        K = g.CH * g.ntap;
+        col = tid % CPR;
+        mc = col * V;
+        krow = tid / CPR;
+        masked = g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER;
+        int *to = (int *)tab;
+        unsigned char *tm = tab + 4 * TILE_MAX_TAPS;
+        if (tid < g.ntap) to[tid] = g.dy[tid] * g.W + g.dx[tid];
+        for (int j = tid; j < g.ntap * CPR; j += TILE_THREADS) {
+            const int t = j / CPR, c = n0 / V + j % CPR;
+            tm[j] = (unsigned char)pix_mask<V>(g, c % g.HC * V, t);
+        }
+        const int cidx = n0 / V + col, img = min(cidx / g.HC, g.N - 1), pos = cidx % g.HC * V;
+        plane0 = (i64)img * g.CH * HW;
+        if (GATHER) {
+            int y = pos / g.gW, x = pos - y * g.gW;
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                pixoff[GATHER ? e : 0] = y * g.s * g.W + x * g.s;
+                if (++x == g.gW) x = 0, ++y;
+            }
+        } else {
+            plane0 += pos;
+        }
+        last = g.total - V;
+        inc_c = BK / g.ntap;
+        inc_t = BK - inc_c * g.ntap;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int k = kbeg + krow + i * KSTEP;
+            lc[i] = sc[i] = k / g.ntap;
+            lt[i] = st[i] = k - lc[i] * g.ntap;
+        }
+        kl = ks = kbeg;
+        toff = to;
+        tmask = tm;
+        __syncthreads();
+    }
+    __device__ __forceinline__ void step(int &c, int &t)
+    {
+        c += inc_c;
+        t += inc_t;
+        if (t >= ntap) t -= ntap, ++c;
+    }
+    __device__ __forceinline__ i64 addr(int c, int t) const { return plane0 + (i64)c * HW + toff[t]; }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if (GATHER) {
+                const bool in = kl + krow + i * KSTEP < K;
+                const elem *q = p + (in ? addr(lc[i], lt[i]) : plane0);
+                const uint32_t m = in ? tmask[lt[i] * CPR + col] : 0u;
+                elem v[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? q[pixoff[GATHER ? e : 0]] : elem(0);
+                r[i] = *(const uint4 *)v;
+            } else {
+                i64 a = addr(lc[i], lt[i]);
+                a = a < 0 ? 0 : a > last ? last : a;
+                r[i] = ldg16(p + a);
+            }
+            step(lc[i], lt[i]);
+        }
+        kl += BK;
+    }
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    {
+        const bool tail = ks + BK > K;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            uint4 v = r[i];
+            if (!GATHER) {
+                const i64 a = addr(sc[i], st[i]);
+                if (a < 0) v = piece_shift<sizeof(elem)>(v, (int)a);
+                else if (a > last) v = piece_shift<sizeof(elem)>(v, (int)(a - last < V ? a - last : V));
+                if (masked) v = piece_mask<V>(v, tmask[st[i] * CPR + col]);
+                if (tail && ks + krow + i * KSTEP >= K) v = make_uint4(0, 0, 0, 0);
+            }
+            *(uint4 *)&lds[(krow + i * KSTEP) * PITCH + mc] = v;
+            step(sc[i], st[i]);
+        }
+        ks += BK;
+    }
+};
+
+// Weight gradients: row = (channel, tap), k = pixel.  The contraction runs over the pieces of whole images
+// [img0, img1).  Tables in LDS: mask of every (tap, piece of a plane), with stride also the offset of every pixel.
+template <typename CT, int ROWS, bool GATHER, bool SUM = false>
+struct LoadPixKC {
+    typedef typename TileEl<CT>::elem elem;
+    static constexpr bool KC = true;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V,
+                         CH = ROWS * CPR / TILE_THREADS, LDS = ROWS * PITCH, XF = 1;
+    const elem *p;
+    const unsigned char *tmask;
+    const int *pix;
+    i64 image, last;
+    int HC, N, img1, kc, row, limg, lpc, simg, spc;
+    bool masked;
+    i64 ro[CH];
+    int tap[CH];
+    float sum[SUM ? CH : 1];
+
+    static __host__ __device__ int table_bytes(const PixView &g)
+    {
+        return (g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER ? (g.ntap * g.HC + 15) / 16 * 16 : 0) +
+               (GATHER ? 4 * V * g.HC : 0);
+    }
+    // tab: table_bytes() of LDS; the caller's barrier follows
+    __device__ __forceinline__ void init(const PixView &g, int row0, int img0, int img1_, int tid, unsigned char *tab)
+    {
+        p = (const elem *)g.p;
+        HC = g.HC;
+        N = g.N;
+        img1 = img1_;
+        kc = (tid % CPR) * V;
+        row = tid / CPR;
+        masked = g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER;
+        const int HW = g.H * g.W;
+        image = (i64)g.CH * HW;
+        last = g.total - V;
+        tmask = tab;
+        pix = (const int *)(tab + (g.ntap * g.HC + 15) / 16 * 16);
+        if (masked)
+            for (int j = tid; j < g.ntap * HC; j += TILE_THREADS)
+                tab[j] = (unsigned char)pix_mask<V>(g, j % HC * V, j / HC);
+        if (GATHER)
+            for (int j = tid; j < HC * V; j += TILE_THREADS)
+                ((int *)pix)[j] = (j / g.gW) * g.s * g.W + (j % g.gW) * g.s;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int r = min(row0 + row + i * (TILE_THREADS / CPR), g.CH * g.ntap - 1);
+            const int c = r / g.ntap;
+            tap[i] = r - c * g.ntap;
+            ro[i] = (i64)c * HW + g.dy[tap[i]] * g.W + g.dx[tap[i]];
+            if (SUM) sum[i] = 0.f;
+        }
+        limg = img0;
+        lpc = tid % CPR;
+        wrap(limg, lpc);
+        simg = limg;
+        spc = lpc;
+    }
+    __device__ __forceinline__ void wrap(int &img, int &pc)
+    {
+        while (pc >= HC) pc -= HC, ++img;
+    }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    {
+        const i64 b = (i64)min(limg, N - 1) * image;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if (GATHER) {
+                const uint32_t m = limg < img1 ? tmask[tap[i] * HC + lpc] : 0u;
+                const elem *q = p + b + ro[i];
+                elem v[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? q[pix[lpc * V + e]] : elem(0);
+                r[i] = *(const uint4 *)v;
+            } else {
+                i64 a = b + ro[i] + lpc * V;
+                a = a < 0 ? 0 : a > last ? last : a;
+                r[i] = ldg16(p + a);
+            }
+        }
+        lpc += CPR;
+        wrap(limg, lpc);
+    }
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    {
+        const i64 b = (i64)min(simg, N - 1) * image;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            uint4 v = r[i];
+            if (!GATHER) {
+                const i64 a = b + ro[i] + spc * V;
+                if (a < 0) v = piece_shift<sizeof(elem)>(v, (int)a);
+                else if (a > last) v = piece_shift<sizeof(elem)>(v, (int)(a - last < V ? a - last : V));
+                if (masked) v = piece_mask<V>(v, tmask[tap[i] * HC + spc]);
+                if (simg >= img1) v = make_uint4(0, 0, 0, 0);
+            }
+            *(uint4 *)&lds[(row + i * (TILE_THREADS / CPR)) * PITCH + kc] = v;
+            if (SUM) {
+                float f[8];
+                piece_floats<CT>(v, f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) sum[SUM ? i : 0] += f[e];
+            }
+        }
+        spc += CPR;
+        wrap(simg, spc);
+    }
+    template <class PUT>
+    __device__ __forceinline__ void put_sums(float *, int, PUT put)
+    {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            float v = sum[SUM ? i : 0];
+#pragma unroll
+            for (int d = 1; d < CPR; d <<= 1) v += __shfl_xor(v, d, 64);
+            if (kc == 0) put(row + i * (TILE_THREADS / CPR), v);
+        }
+    }
+};
+
+// ------------------------------------------------------------------ fragments
+// 8 (bf16) or 4 (float) values of row / column c0 + lane % 32 at k = step * 16 (8) + (lane / 32) * 8 (4) ..
+template <bool KC, int PITCH>
+__device__ __forceinline__ bf16x8_t tile_frag(const uint16_t *lds, int c0, int step, int lane)
+{
+    if (KC) return *(const bf16x8_t *)&lds[(c0 + (lane & 31)) * PITCH + step * 16 + (lane >> 5) * 8];
+    return lds_frag_tr(lds, PITCH, step * 16, c0, lane);
+}
+template <bool KC, int PITCH>
+__device__ __forceinline__ f32x4_t tile_frag(const float *lds, int c0, int step, int lane)
+{
+    if (KC) return *(const f32x4_t *)&lds[(c0 + (lane & 31)) * PITCH + step * 8 + (lane >> 5) * 4];
+    const float *q = &lds[(step * 8 + (lane >> 5) * 4) * PITCH + c0 + (lane & 31)];
+    f32x4_t f = {q[0], q[PITCH], q[2 * PITCH], q[3 * PITCH]};
+    return f;
+}
+
+// ------------------------------------------------------------------ the product
+template <typename CT, class CFG, class LA, class LB>
+struct TileSize {
+    static constexpr int loop = 2 * (LA::LDS + LB::LDS) * (int)sizeof(typename TileEl<CT>::elem);
+    static constexpr int cpitch = CFG::BN + 4;
+    static constexpr int out = CFG::WK * CFG::BM * cpitch * 4;
+    static constexpr int bytes = loop > out ? loop : out;
+};
+
+// nch chunks; the sums end up in smem as WK tiles [BM][BN + 4] of floats (ends with a barrier)
+template <typename CT, class CFG, class LA, class LB>
+__device__ __forceinline__ void tile_product(LA &la, LB &lb, int nch, unsigned char *smem, int tid)
+{
+    typedef typename TileEl<CT>::elem elem;
+    constexpr int NS = CFG::NS, MI = CFG::BM / 32 / CFG::WM, NI = CFG::BN / 32 / CFG::WN;
+    constexpr int STEPS = 4 / CFG::WK; // a chunk has four steps
+    static_assert(NS % 2 == 0, "the LDS buffer of a stage is its parity");
+    elem *As[2], *Bs[2];
+    As[0] = (elem *)smem;
+    As[1] = As[0] + LA::LDS;
+    Bs[0] = As[1] + LA::LDS;
+    Bs[1] = Bs[0] + LB::LDS;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int wk = wave / (CFG::WM * CFG::WN), wm = wave / CFG::WN % CFG::WM, wn = wave % CFG::WN;
+    uint4 ra[NS][LA::CH], rb[NS][LB::CH];
+    float xa[NS][LA::XF], xb[NS][LB::XF];
+    f32x16_t acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    if (nch > 0) { // (an empty contraction reads nothing)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            la.load(ra[s], xa[s]);
+            lb.load(rb[s], xb[s]);
+        }
+        la.store(As[0], ra[0], xa[0]);
+        lb.store(Bs[0], rb[0], xb[0]);
+        la.load(ra[0], xa[0]);
+        lb.load(rb[0], xb[0]);
+    }
+    __syncthreads();
+    for (int c = 0; c < nch; c += NS) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (c + s < nch) {
+                const int cur = s & 1, nx = (s + 1) % NS;
+                if (c + s + 1 < nch) {
+                    la.store(As[cur ^ 1], ra[nx], xa[nx]);
+                    lb.store(Bs[cur ^ 1], rb[nx], xb[nx]);
+                    la.load(ra[nx], xa[nx]);
+                    lb.load(rb[nx], xb[nx]);
+                }
+                if constexpr (sizeof(elem) == 2) {
+#pragma unroll
+                    for (int q = 0; q < STEPS; ++q) {
+                        const int step = wk * STEPS + q;
+                        bf16x8_t a[MI], b[NI];
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+                            a[i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, step, lane);
+#pragma unroll
+                        for (int j = 0; j < NI; ++j)
+                            b[j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, step, lane);
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+#pragma unroll
+                            for (int j = 0; j < NI; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+                    }
+                } else {
+                    f32x4_t a[STEPS][MI], b[STEPS][NI];
+#pragma unroll
+                    for (int q = 0; q < STEPS; ++q) {
+#pragma unroll
+                        for (int i = 0; i < MI; ++i)
+                            a[q][i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, wk * STEPS + q, lane);
+#pragma unroll
+                        for (int j = 0; j < NI; ++j)
+                            b[q][j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, wk * STEPS + q, lane);
+                    }
+#pragma unroll
+                    for (int i = 0; i < MI; ++i)
+#pragma unroll
+                        for (int j = 0; j < NI; ++j) {
+                            f32x16_t t;
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) t[v] = 0.f;
+#pragma unroll
+                            for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i][e], b[q][j][e], t, 0, 0, 0);
+#pragma unroll
+                            for (int v = 0; v < 16; ++v) acc[i][j][v] += t[v];
+                        }
+                }
+                __syncthreads();
+            }
+        }
+    }
+    float *Cs = (float *)smem + wk * CFG::BM * (CFG::BN + 4);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int m = (wm * MI + i) * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
+                Cs[m * (CFG::BN + 4) + (wn * NI + j) * 32 + (lane & 31)] = acc[i][j][v];
+            }
+    __syncthreads();
+}
+
+// out(m, n, v[V]) for every piece of V neighbouring columns of the tile, in tile coordinates
+template <typename CT, class CFG, class OUT>
+__device__ __forceinline__ void tile_pieces(const unsigned char *smem, int tid, OUT out)
+{
+    constexpr int V = TileEl<CT>::V, CPR = CFG::BN / V, P = CFG::BN + 4;
+    const float *Cs = (const float *)smem;
+#pragma unroll 2
+    for (int q = tid; q < CFG::BM * CPR; q += TILE_THREADS) {
+        const int m = q / CPR, n = q % CPR * V;
+        float v[V];
+#pragma unroll
+        for (int e = 0; e < V; e += 4) {
+            f32x4_t t = *(const f32x4_t *)&Cs[m * P + n + e];
+#pragma unroll
+            for (int w = 1; w < CFG::WK; ++w) t += *(const f32x4_t *)&Cs[(w * CFG::BM + m) * P + n + e];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[e + x] = t[x];
+        }
+        out(m, n, v);
+    }
+}
+
+} // namespace pf

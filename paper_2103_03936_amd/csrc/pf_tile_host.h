@@ -1,0 +1,101 @@
+// Tiled matrix products for any shape, the host side: problem lists, the choice of tile and split, launches.
+#pragma once
+
+#include "pf_tile.h"
+
+namespace pf {
+
+// Where a tile goes.  float32: C[split][m][n] (a partial sum per split of the contraction) or, unsplit, a gradient that
+// is written or added to.  Otherwise elements of the call's type, row-major, or (HC > 0) planes [image][m][pixel] with
+// the column index counting padded pixels as PixView does.
+struct TileOut {
+    void *C;
+    i64 ld;
+    int f32, accumulate;
+    i64 split_stride;
+    float *sums; // sums over k of the left operand's rows, [split][m]: gradients of a bias or a shift
+    i64 sums_stride;
+    const void *bias;           // per column, the call's element type
+    const float *scale, *shift; // per row
+    const void *add, *mask;     // like C: added before the ReLU / the output is kept where mask > 0
+    int relu;
+    int N, CH, HC, HW, gW; // images, channels, pieces per image, pixels per image, pixels per row (planes)
+    int s, ph, pw, H, W;   // s > 1: pixel (y, x) is element (y s + ph, x s + pw) of an H x W plane
+};
+
+enum TileType {
+    TILE_NN,   // A [M][K], B [K][N]
+    TILE_NT,   // A [M][K], B [N][K]
+    TILE_TN,   // A [K][M], B [K][N]
+    TILE_CONV, // A [M][K], B a PixView (k = (channel, tap))
+    TILE_CONVG,// the same with stride
+    TILE_CONVT,// A [K][M] with a scale per k, B a PixView
+    TILE_WG,   // A and B PixViews, k = pixel
+    TILE_WGG,  // the same, B with stride
+    TILE_PACK, // filters [q][c][tap] -> [c][q][selected tap]
+};
+
+struct TileProb {
+    int type, M, N, K;
+    int tm, tn, ksplit, kper, block0; // kper: chunk-aligned extent of a split (images for TILE_WG)
+    const void *A, *B;
+    i64 lda, ldb;
+    const float *ascale;
+    PixView pa, pb;
+    TileOut o;
+};
+
+constexpr int TILE_MAX_PROBS = 6;
+struct TileArgs {
+    int n, blocks;
+    TileProb p[TILE_MAX_PROBS];
+};
+
+// Tile shapes a launch can use.
+enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x128, TS_COUNT };
+
+// One product: add it to a launch.  ksplit <= 0 asks for the split that plan_tiles chose.
+TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc);
+
+struct TilePlan {
+    TileShape shape;
+    int ksplit;
+    double cost; // cycles
+};
+// The tile shape and k-split that should finish first, at most max_split ways.
+TilePlan plan_tiles(int dtype, i64 M, i64 N, i64 K, int max_split);
+
+// Several products in one launch (one tile shape); those marked may split their contraction.
+struct TileNeed {
+    i64 M, N, K;
+    bool split;
+};
+struct TileGroup {
+    TileShape shape;
+    int ksplit[4];
+    double cost;
+};
+TileGroup plan_tile_group(int dtype, const TileNeed *need, int n);
+
+void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &p, int ksplit);
+int launch_tiles_linear(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a);
+int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a);
+
+// dst (+)= sum over splits of src[split], optionally times rscale[index / rlen]; bf16: dst holds bf16 (no accumulation)
+struct SplitSum {
+    const float *src;
+    float *dst;
+    i64 count, stride;
+    int splits, accumulate;
+    const float *rscale;
+    i64 rlen;
+    int bf16;
+};
+struct SplitSumArgs {
+    int n, blocks[5];
+    SplitSum s[4];
+};
+void split_sum_add(SplitSumArgs &a, const SplitSum &s);
+int launch_split_sums(hipStream_t s, const SplitSumArgs &a);
+
+} // namespace pf
