@@ -5,6 +5,7 @@
 #include "pf_conv_chain.h"
 #include "pf_conv_wgrad.h"
 #include "pf_epilogue.h"
+#include "pf_tile_host.h"
 
 namespace pf {
 
@@ -135,6 +136,15 @@ static int check_conv_desc(const pf_conv_desc *d, ConvGeom *g)
     return PF_OK;
 }
 
+// What the kernels apply as they store their output (all optional): forward scale / shift / residual / ReLU,
+// backward the gradient arriving over a skip connection and the mask of a ReLU input.
+struct ConvEpilogue {
+    const float *scale, *shift;
+    const void *add, *mask;
+    int relu;
+    float *dshift; // backward, tiled products only: sums of dZ per channel
+};
+
 struct ConvPlan {
     int ks_dVp, ks_dUk;
     size_t n_T, n_part, fwd_bytes, bwd_bytes;
@@ -144,10 +154,74 @@ struct ConvPlan {
     int wg_groups2, wg_ipg2; // the same for the 1x1 stage
     size_t n_w1, n_w2;       // packed weight elements, forward direction
     size_t n_w1b, n_w2b;     // packed weight elements, backward direction
+    bool tiles;              // the tiled products of pf_tile.h take the shape
+    bool gather;             // ... and read the k x k stage's input with stride
+    TileShape sh_T, sh_Y, sh_dT, sh_g; // ... the tile shapes of their launches
+    int ks_tU, ks_tV;        // ... image splits of the two filter gradients
+    size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     size_t saved_bytes;      // the backward direction's packed weights when the forward call saves them
 };
 
-static ConvPlan plan_conv(const ConvGeom &g, int dtype)
+// Which filter taps reach the input pixels (s y + a) of one phase of a strided convolution's input gradient, and the
+// row of dT each of them reads relative to y: y s + a + p = i + s (row), i.e. row = y + (a + p - i) / s.
+static int phase_taps(const ConvGeom &g, int a, int *tap, int *off)
+{
+    int n = 0;
+    for (int i = 0; i < g.k; ++i)
+        if ((a + g.p - i) % g.s == 0) {
+            tap[n] = i;
+            off[n++] = (a + g.p - i) / g.s;
+        }
+    return n;
+}
+
+// The convolution on the tiled products (pf_tile.h): every extent holds a 16-byte piece, the filter fits the tap
+// table, and the grids of forward and backward have the row length of the planes they read (always for unit stride
+// with same padding; for stride s when no input pixel lies beyond s * output extent).
+static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
+{
+    const int V = dtype == PF_BF16 ? 8 : 4, kk = g.k * g.k, HW = g.Ho * g.Wo;
+    const i64 big = 1LL << 30;
+    p.tiles = false;
+    if (g.N < 1 || kk > TILE_MAX_TAPS || g.C < 1 || (i64)g.C * kk < V || g.r < V || g.Cout < 1) return;
+    const i64 planes = (i64)g.N * HW;
+    if (planes * g.r < V || planes * g.Cout < V || (i64)g.N * g.C * g.H * g.W < V) return;
+    const int HC = (HW + V - 1) / V, HCin = (g.H * g.W + V - 1) / V;
+    if ((i64)g.N * HC * V > big || (i64)g.N * HCin * V > big) return;
+    const bool same = g.s == 1 && g.Ho == g.H && g.Wo == g.W;
+    // gather: the k x k stage reads X by element offsets; backward needs one grid of Ho x Wo pixels per phase
+    if (!same && !(g.s > 1 && (g.H + g.s - 1) / g.s <= g.Ho && (g.W + g.s - 1) / g.s <= g.Wo && g.s <= 2)) return;
+    p.gather = !same;
+    const int tab = 2 * ((kk * HC + 15) / 16 * 16 + (p.gather ? 4 * V * HC : 0));
+    if (tab > 20 * 1024) return;
+    p.tiles = true;
+    const i64 npx = (i64)g.N * HC * V, npin = (i64)g.N * HCin * V;
+    p.sh_T = g.r <= 32 ? TS_32x128 : TS_64;
+    p.sh_Y = g.Cout <= 32 ? TS_32x128 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
+    p.sh_dT = p.sh_T;
+    p.sh_g = TS_64;
+    (void)npin;
+    // both filter gradients in one launch: about two workgroups per compute unit, each at least two chunks long
+    const i64 tU = ((g.r + 63) / 64) * (((i64)g.C * kk + 63) / 64), tV = ((g.Cout + 63) / 64) * ((g.r + 63) / 64);
+    const i64 want = 512;
+    const auto split = [&](i64 tiles, i64 floats) {
+        i64 ks = (want + tiles - 1) / tiles;
+        const i64 chunks = (i64)g.N * HC * V / (dtype == PF_BF16 ? 64 : 32);
+        if (ks > chunks / 2) ks = chunks / 2;
+        if (ks > g.N) ks = g.N;
+        if (ks > 32) ks = 32;
+        while (ks > 1 && ks * floats > (4 << 20)) --ks;
+        if (ks < 1) ks = 1;
+        const i64 per = (g.N + ks - 1) / ks;
+        return (int)((g.N + per - 1) / per);
+    };
+    p.ks_tU = split(tU, (i64)g.r * g.C * kk);
+    p.ks_tV = split(tV, (i64)g.Cout * (g.r + 1));
+    p.n_pack = kk > 1 ? (size_t)g.r * g.C * kk : 0;
+    p.n_part_t = (size_t)p.ks_tU * g.r * g.C * kk + (size_t)p.ks_tV * ((size_t)g.Cout * g.r + g.Cout) + 192;
+}
+
+static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
 {
     ConvPlan p;
     p.chain = dtype == PF_BF16 && chain_supported(g.C, g.Cout, g.r, g.H, g.W, g.k, g.s, g.p);
@@ -212,7 +286,19 @@ static ConvPlan plan_conv(const ConvGeom &g, int dtype)
         if (f > p.fwd_bytes) p.fwd_bytes = f;
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
+    plan_conv_tiles(g, dtype, p);
+    if (p.tiles) {
+        const size_t el = dtype == PF_BF16 ? 2 : 4;
+        const size_t b = 2 * align_up(p.n_T * el) + 4 * align_up(p.n_pack * el) + align_up(p.n_part_t * 4);
+        if (b > p.bwd_bytes) p.bwd_bytes = b;
+    }
     return p;
+}
+
+static const ConvPlan &plan_conv(const ConvGeom &g, int dtype)
+{
+    static thread_local PlanCache<PlanKey<10>, ConvPlan> cache;
+    return cache.get(PlanKey<10>{{g.N, g.C, g.H, g.W, g.Cout, g.r, g.k, g.s, g.p, dtype}}, [&] { return make_conv_plan(g, dtype); });
 }
 
 // ------------------------------------------------------------- any-shape
@@ -291,15 +377,172 @@ static int conv_bwd_generic(const ConvGeom &g, const ConvPlan &p, const T *X, co
     return conv_wgrads<T, float, float>(g, p, X, dY, Tws, dTws, dUk, dVp, accumulate, part, s);
 }
 
-// ----------------------------------------------------- fused small-image path (bf16)
-// What the chain kernel applies as it stores its output (all optional): forward scale / shift / residual / ReLU,
-// backward the gradient arriving over a skip connection and the mask of a ReLU input.
-struct ConvEpilogue {
-    const float *scale, *shift;
-    const void *add, *mask;
-    int relu;
-};
+// ------------------------------------------------------------- any shape of at least a 16-byte piece
+// T [n][pixel] etc. as the right operand of a product: every channel through one tap, or through all k x k.
+static PixView pix_view(const ConvGeom &g, int dtype, const void *p, int CH, int H, int W, int gH, int gW)
+{
+    const int V = dtype == PF_BF16 ? 8 : 4;
+    PixView v = {};
+    v.p = p;
+    v.total = (i64)g.N * CH * H * W;
+    v.N = g.N, v.CH = CH, v.H = H, v.W = W, v.gH = gH, v.gW = gW;
+    v.s = 1;
+    v.HC = (gH * gW + V - 1) / V;
+    v.ntap = 1;
+    return v;
+}
+static PixView conv_input_view(const ConvGeom &g, int dtype, const void *X)
+{
+    PixView v = pix_view(g, dtype, X, g.C, g.H, g.W, g.Ho, g.Wo);
+    v.s = g.s;
+    v.ntap = g.k * g.k;
+    for (int t = 0; t < v.ntap; ++t) {
+        v.dy[t] = (signed char)(t / g.k - g.p);
+        v.dx[t] = (signed char)(t % g.k - g.p);
+    }
+    return v;
+}
+static void out_planes(TileOut &o, const PixView &v, int CH)
+{
+    o.N = v.N, o.CH = CH, o.HC = v.HC, o.HW = v.gH * v.gW, o.gW = v.gW;
+    o.s = 1;
+}
 
+template <typename T>
+static int conv_T_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, T *out, hipStream_t s)
+{
+    const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32, K = g.C * g.k * g.k;
+    const PixView v = conv_input_view(g, dt, X);
+    TileArgs a = {};
+    TileProb q = tile_prob(p.gather ? TILE_CONVG : TILE_CONV, g.r, g.N * v.HC * (16 / (int)sizeof(T)), K, Uk, K, nullptr, 0,
+                           out, 0);
+    q.pb = v;
+    out_planes(q.o, v, g.r);
+    tile_add(a, p.sh_T, dt, q, 1);
+    return launch_tiles_conv(s, "conv_T=Uk*X", dt, p.sh_T, a);
+}
+
+// Two launches: T = Uk * X (an implicit product over (channel, tap), the order in which the filters lie in memory), then
+// Y = act(scale (Vp T) + shift + residual) with the epilogue on the tile.
+template <typename T>
+static int conv_fwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, const T *Vp, T *Y, T *T_save,
+                          Workspace &ws, hipStream_t s, const ConvEpilogue &ep)
+{
+    const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32;
+    T *Tt = T_save ? T_save : ws.take<T>(p.n_T);
+    int st = conv_T_tiles<T>(g, p, X, Uk, Tt, s);
+    if (st != PF_OK) return st;
+    TileArgs a = {};
+    const PixView v = pix_view(g, dt, Tt, g.r, g.Ho, g.Wo, g.Ho, g.Wo);
+    TileProb q = tile_prob(TILE_CONV, g.Cout, g.N * v.HC * (16 / (int)sizeof(T)), g.r, Vp, g.r, nullptr, 0, Y, 0);
+    q.pb = v;
+    out_planes(q.o, v, g.Cout);
+    q.o.scale = ep.scale;
+    q.o.shift = ep.shift;
+    q.o.add = ep.add;
+    q.o.relu = ep.relu;
+    tile_add(a, p.sh_Y, dt, q, 1);
+    return launch_tiles_conv(s, "conv_Y=Vp*T", dt, p.sh_Y, a);
+}
+
+// Three launches: dT = (scale Vp)^T dZ, with the filters re-ordered for the next launch in extra workgroups; then dX, dUk,
+// dVp and the shift gradient side by side; then the sums over the image groups of the filter gradients.  With stride s,
+// dX is s^2 products, one per phase of the input pixels, each over the taps that reach it.
+template <typename T>
+static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, const T *Vp, const T *dY,
+                          const T *T_saved, T *dX, float *dUk, float *dVp, int accumulate, Workspace &ws, hipStream_t s,
+                          const ConvEpilogue &ep)
+{
+    const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32, V = 16 / (int)sizeof(T), kk = g.k * g.k;
+    T *Tws = ws.take<T>(p.n_T), *dT = ws.take<T>(p.n_T), *pack[4];
+    for (int i = 0; i < 4; ++i) pack[i] = ws.take<T>(p.n_pack);
+    float *part = ws.take<float>(p.n_part_t);
+    int st = PF_OK;
+    if (dVp && !T_saved) {
+        st = conv_T_tiles<T>(g, p, X, Uk, Tws, s);
+        if (st != PF_OK) return st;
+    }
+    const PixView vdY = pix_view(g, dt, dY, g.Cout, g.Ho, g.Wo, g.Ho, g.Wo);
+    const PixView vdT = pix_view(g, dt, dT, g.r, g.Ho, g.Wo, g.Ho, g.Wo);
+    const PixView vT = pix_view(g, dt, T_saved ? T_saved : Tws, g.r, g.Ho, g.Wo, g.Ho, g.Wo);
+    const int npx = g.N * vdT.HC * V, phases = g.s * g.s;
+    TileArgs a = {}, b = {};
+    if (dX || dUk) {
+        TileProb q = tile_prob(TILE_CONVT, g.r, npx, g.Cout, Vp, g.r, nullptr, 0, dT, 0);
+        q.pb = vdY;
+        q.ascale = ep.scale;
+        out_planes(q.o, vdT, g.r);
+        tile_add(a, p.sh_dT, dt, q, 1);
+    }
+    if (dX) {
+        for (int f = 0; f < phases; ++f) {
+            int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
+            const int ni = phase_taps(g, f / g.s, ti, oi), nj = phase_taps(g, f % g.s, tj, oj), nt = ni * nj;
+            const T *W = Uk;
+            i64 ldw = 0;
+            PixView v = vdT;
+            TileProb pk = tile_prob(TILE_PACK, g.C, g.r, 0, Uk, 0, nullptr, 0, pack[f], 0);
+            for (int t = 0; t < nt; ++t) {
+                v.dy[t] = (signed char)oi[t / nj];
+                v.dx[t] = (signed char)oj[t % nj];
+                pk.pb.dy[t] = (signed char)(ti[t / nj] * g.k + tj[t % nj]);
+            }
+            v.ntap = nt > 0 ? nt : 1;
+            if (kk > 1 && nt > 0) {
+                pk.pb.ntap = nt;
+                pk.kper = kk;
+                tile_add(a, p.sh_dT, dt, pk, 1);
+                W = pack[f];
+            }
+            TileProb q = kk > 1 ? tile_prob(TILE_CONV, g.C, npx, g.r * nt, W, g.r * nt, nullptr, 0, dX, 0)
+                                : tile_prob(TILE_CONVT, g.C, npx, nt > 0 ? g.r : 0, Uk, g.C, nullptr, 0, dX, 0);
+            (void)ldw;
+            q.pb = v;
+            out_planes(q.o, vdT, g.C);
+            q.o.add = ep.add;
+            q.o.mask = ep.mask;
+            if (g.s > 1) {
+                q.o.s = g.s;
+                q.o.ph = f / g.s;
+                q.o.pw = f % g.s;
+                q.o.H = g.H;
+                q.o.W = g.W;
+            }
+            tile_add(b, p.sh_g, dt, q, 1);
+        }
+    }
+    st = launch_tiles_conv(s, "conv_dT=Vpt*dY", dt, p.sh_dT, a);
+    if (st != PF_OK) return st;
+    SplitSumArgs ss = {};
+    const auto grad = [&](const PixView &pa, const PixView &pb, int type, int m, int n, float *dst, int ks, float *sums,
+                          const float *rscale) {
+        TileProb q = tile_prob(type, m, n, 0, nullptr, 0, nullptr, 0, part, n);
+        q.pa = pa;
+        q.pb = pb;
+        q.o.f32 = 1;
+        q.o.split_stride = (i64)m * n;
+        float *ps = part + (i64)ks * m * n;
+        part = ps;
+        if (sums) {
+            q.o.sums = ps;
+            q.o.sums_stride = m;
+            part += (i64)ks * m;
+        }
+        part += (64 - ((uintptr_t)part / 4) % 64) % 64;
+        tile_add(b, p.sh_g, dt, q, ks);
+        const int got = b.p[b.n - 1].ksplit;
+        split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, (i64)m * n, (i64)m * n, got, accumulate, rscale, n, 0});
+        if (sums) split_sum_add(ss, SplitSum{ps, sums, m, m, got, accumulate, nullptr, 0, 0});
+    };
+    if (dUk)
+        grad(vdT, conv_input_view(g, dt, X), p.gather ? TILE_WGG : TILE_WG, g.r, g.C * kk, dUk, p.ks_tU, nullptr, nullptr);
+    if (dVp || ep.dshift) grad(vdY, vT, TILE_WG, g.Cout, g.r, dVp, p.ks_tV, ep.dshift, ep.scale);
+    st = launch_tiles_conv(s, "conv_dX,dUk,dVp", dt, p.sh_g, b);
+    if (st != PF_OK) return st;
+    return launch_split_sums(s, ss);
+}
+
+// ----------------------------------------------------- fused small-image path (bf16)
 static int conv_fwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X, const bf16_t *Uk, const bf16_t *Vp,
                           bf16_t *Y, bf16_t *T_save, void *W_save, Workspace &ws, hipStream_t s, const ConvEpilogue &ep)
 {
@@ -515,14 +758,18 @@ int pf_dense_conv_bwd(const pf_conv_desc *d, const void *X, const void *Wd, cons
 
 } // extern "C"
 
-// Does the backward call for this descriptor run on the chain kernels, which fold a batch-norm scale into their
-// weight re-ordering and into the sum of the filter gradients?  (Otherwise the caller scales beforehand.)
-bool pf::conv_bwd_takes_scale(const pf_conv_desc *d, bool want_dX)
+// What the backward call for this descriptor does by itself: fold a batch-norm scale into the filters and the sum of
+// their gradients (chain kernels and tiled products), and form the shift gradient (tiled products).  Otherwise the
+// caller scales beforehand and sums afterwards.
+void pf::conv_bwd_takes(const pf_conv_desc *d, bool want_dX, bool *scale, bool *dshift)
 {
+    *scale = *dshift = false;
     ConvGeom g;
-    if (check_conv_desc(d, &g) != PF_OK || d->dtype != PF_BF16 || g.N == 0 || !want_dX) return false;
+    if (check_conv_desc(d, &g) != PF_OK || g.N == 0) return;
     const ConvPlan p = plan_conv(g, d->dtype);
-    return p.chain && p.wgrad;
+    const bool chain = d->dtype == PF_BF16 && p.chain && want_dX;
+    *scale = chain ? p.wgrad : p.tiles;
+    *dshift = !chain && p.tiles;
 }
 
 // ------------------------------------------------ entry points with an epilogue
@@ -543,6 +790,15 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     if (g.N == 0) return PF_OK;
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
+    const ConvEpilogue all = {scale, shift, residual, nullptr, act == PF_ACT_RELU ? 1 : 0, nullptr};
+    if (p.tiles && !(d->dtype == PF_BF16 && p.chain)) {
+        *fused = true;
+        if (d->dtype == PF_F32)
+            return conv_fwd_tiles<float>(g, p, (const float *)X, (const float *)Uk, (const float *)Vp, (float *)Y,
+                                         (float *)T_save, ws, s, all);
+        return conv_fwd_tiles<bf16_t>(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (bf16_t *)Y,
+                                      (bf16_t *)T_save, ws, s, all);
+    }
     if (d->dtype == PF_F32)
         return conv_fwd_generic<float>(g, (const float *)X, (const float *)Uk, (const float *)Vp, (float *)Y,
                                        (float *)T_save, ws, s);
@@ -551,7 +807,7 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         // the kernel applies the epilogue as it stores (its float4 loads of scale and shift need 16-byte alignment)
         ConvEpilogue ep = {};
         if (!any_misaligned({scale, shift}, 16)) {
-            ep = ConvEpilogue{scale, shift, residual, nullptr, act == PF_ACT_RELU ? 1 : 0};
+            ep = all;
             *fused = true;
         }
         return conv_fwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (bf16_t *)Y,
@@ -564,7 +820,7 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
 int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, const void *Vp, const float *scale,
                           const void *dY, const void *T_saved, const void *W_saved, const void *dX_add, int x_is_relu,
                           void *dX, void *dUk, void *dVp, int accumulate, void *workspace, size_t workspace_bytes,
-                          void *stream, bool *fused)
+                          void *stream, bool *fused, float *dshift)
 {
     ConvGeom g;
     int st = check_conv_desc(d, &g);
@@ -584,6 +840,17 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         }
         return st;
     }
+    if (p.tiles && !(d->dtype == PF_BF16 && p.chain && dX)) {
+        *fused = true;
+        const ConvEpilogue ep = {scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift};
+        if (d->dtype == PF_F32)
+            return conv_bwd_tiles<float>(g, p, (const float *)X, (const float *)Uk, (const float *)Vp, (const float *)dY,
+                                         (const float *)T_saved, (float *)dX, (float *)dUk, (float *)dVp, accumulate, ws, s,
+                                         ep);
+        return conv_bwd_tiles<bf16_t>(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY,
+                                      (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dUk, (float *)dVp, accumulate, ws, s,
+                                      ep);
+    }
     if (d->dtype == PF_F32)
         return conv_bwd_generic<float>(g, p, (const float *)X, (const float *)Uk, (const float *)Vp, (const float *)dY,
                                        (const float *)T_saved, (float *)dX, (float *)dUk, (float *)dVp, accumulate, ws,
@@ -593,7 +860,7 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         *fused = true; // the kernel adds the skip gradient and masks as it stores dX
         return conv_bwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY,
                               (const bf16_t *)T_saved, p.saved_bytes ? W_saved : nullptr, (bf16_t *)dX, (float *)dUk,
-                              (float *)dVp, accumulate, ws, s, ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0});
+                              (float *)dVp, accumulate, ws, s, ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, nullptr});
     }
     return conv_bwd_generic<bf16_t>(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp,
                                     (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dUk,

@@ -283,9 +283,11 @@ int pf_lowrank_conv_bwd_ep(const pf_conv_desc *d, const void *X, const void *Uk,
     void *dVp_used = dVp;
     float *raw = nullptr;
     int st = PF_OK;
-    // the chain kernels fold the scale into their own weight re-ordering and gradient sum; any other path runs on
+    // the fast paths fold the scale into their own filters and gradient sums; the element-wise one runs on
     // a scaled copy of the 1x1 filters and finishes dVp afterwards
-    const bool in_kernel = scale && conv_bwd_takes_scale(d, dX != nullptr);
+    bool takes_scale, takes_dshift;
+    conv_bwd_takes(d, dX != nullptr, &takes_scale, &takes_dshift);
+    const bool in_kernel = scale && takes_scale;
     const bool scaled = !in_kernel && scale && Vp && d->Cout > 0 && d->r > 0 && d->N > 0;
     if (scaled) {
         // dT = Vp^T (scale dZ) = (scale Vp)^T dZ: the backward kernels run on a scaled copy of the 1x1 filters,
@@ -316,7 +318,8 @@ int pf_lowrank_conv_bwd_ep(const pf_conv_desc *d, const void *X, const void *Uk,
     }
     bool fused = false;
     st = conv_bwd_entry_ep(d, X, Uk, Vp_used, in_kernel ? (const float *)scale : nullptr, dZ, T_saved, W_saved, dX_add,
-                           x_is_relu, dX, dUk, dVp_used, accumulate, workspace, workspace_bytes, stream, &fused);
+                           x_is_relu, dX, dUk, dVp_used, accumulate, workspace, workspace_bytes, stream, &fused,
+                           takes_dshift ? (float *)dshift : nullptr);
     if (st != PF_OK) return st;
     const i64 Ho = (d->H + 2 * (i64)d->pad - d->k) / d->stride + 1, Wo = (d->W + 2 * (i64)d->pad - d->k) / d->stride + 1;
     if (scaled && dVp) {
@@ -325,7 +328,7 @@ int pf_lowrank_conv_bwd_ep(const pf_conv_desc *d, const void *X, const void *Uk,
                   (const float *)raw, (const float *)scale, (float *)dVp, n, (int)d->r, accumulate);
         if (st != PF_OK) return st;
     }
-    if (dshift) {
+    if (dshift && !takes_dshift) {
         if (d->N == 0) {
             if (!accumulate) st = launch_zero_f32(s, (float *)dshift, d->Cout);
         } else if (d->dtype == PF_F32) {

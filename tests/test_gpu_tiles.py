@@ -3,6 +3,7 @@ edges, rows of odd length (unaligned pieces, the last piece of a row pulled back
 every tile shape; convolutions whose pixels do not fill their pieces, planes smaller than a piece, stride."""
 import pytest
 
+import test_gpu_conv
 import test_gpu_linear
 
 pytestmark = pytest.mark.gpu
@@ -17,8 +18,25 @@ LINEAR = [
     (2050, 1032, 1160, 264),  # large tiles with ragged edges
 ]
 
+CONV = [
+    # N, C, H, W, Cout, r, k, stride, pad
+    (3, 9, 7, 5, 17, 10, 3, 2, 1),
+    (5, 24, 7, 7, 20, 8, 1, 2, 0),    # three of the four phases of dX are reached by no tap
+    (9, 40, 2, 2, 33, 12, 3, 1, 1),
+    (5, 16, 1, 1, 16, 8, 3, 1, 1),
+    (2, 10, 17, 16, 21, 9, 5, 1, 2),
+    (3, 130, 14, 14, 136, 40, 3, 1, 1),
+    (70, 64, 8, 8, 200, 36, 3, 2, 1),  # image groups of the filter gradients of unequal length
+]
+
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", LINEAR)
 def test_linear(shape, dtype):
     test_gpu_linear._run(*shape, dtype=dtype, bias=True, saved_T=shape[0] != 257, seed=21)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", CONV)
+def test_conv(shape, dtype):
+    test_gpu_conv._run(shape, dtype, saved_T=shape[0] != 5, seed=22)
