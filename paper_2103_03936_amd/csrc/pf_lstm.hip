@@ -3,6 +3,7 @@
 // the any-shape path composes the guarded tile GEMM with two pointwise kernels.
 #include "pf_gemm.h"
 #include "pf_skinny.h"
+#include "pf_tile_host.h"
 
 namespace pf {
 
@@ -225,10 +226,6 @@ static int lstm_bwd_generic(const pf_lstm_desc *d, const float *x, const float *
 }
 
 
-// ------------------------------------------------------------------ small-batch path (B <= 32)
-// Seven launches per cell instead of two dozen: every product streams its factor once from all compute
-// units (pf_skinny.h); slice sums ride along with the gate arithmetic and with the gradient updates.
-
 // z = bias + sum of the pre-activation slices, then the gate arithmetic of eq. (2)
 // (zadd, nullable: pre-activations computed elsewhere, [B x 4h] -- the hoisted input path of a sequence)
 __global__ __launch_bounds__(256) void lstm_slices_pointwise_fwd_kernel(const float *P, int nslices, i64 pcount,
@@ -262,6 +259,161 @@ __global__ __launch_bounds__(256) void lstm_slices_pointwise_fwd_kernel(const fl
     c_out[idx] = c;
     h_out[idx] = og * tanhf(c);
 }
+
+// ------------------------------------------------------------------ any batch, every extent at least four floats
+// The products of a step on the tiled kernels (pf_tile.h), both paths (and the four gate blocks) side by side: forward
+// T; z as two slices; gates.  Backward gate derivatives; dT; dx and dh_prev; all parameter gradients.  A launch whose
+// products are too small for the chip splits their contraction and one more launch adds the partial sums.
+struct LstmTilePlan {
+    TileGroup T, z, dT, dxh, grads;
+    size_t n_T, n_dT, n_dxh, fwd_bytes, bwd_bytes; // partial sums, floats
+};
+static bool lstm_tiles_ok(const pf_lstm_desc *d) { return d->B > 0 && d->d_in >= 4 && d->h >= 4 && d->r >= 4; }
+
+static LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
+{
+    LstmTilePlan p;
+    const i64 B = d->B, h = d->h, r = d->r, G = d->groups, gr = G * r, din = d->d_in;
+    const TileNeed T[2] = {{B, gr, din, true}, {B, gr, h, true}};
+    p.T = plan_tile_group(PF_F32, T, 2);
+    const TileNeed z[2] = {{B, 4 * h, r, false}, {B, 4 * h, r, false}};
+    p.z = plan_tile_group(PF_F32, z, 2);
+    const TileNeed dT[2] = {{B, gr, G == 4 ? h : 4 * h, true}, {B, gr, G == 4 ? h : 4 * h, true}};
+    p.dT = plan_tile_group(PF_F32, dT, 2);
+    const TileNeed dxh[2] = {{B, din, gr, true}, {B, h, gr, true}};
+    p.dxh = plan_tile_group(PF_F32, dxh, 2);
+    const TileNeed gd[4] = {{4 * h, r, B, false}, {4 * h, r, B, false}, {din, gr, B, false}, {h, gr, B, false}};
+    p.grads = plan_tile_group(PF_F32, gd, 4);
+    p.n_T = (size_t)((p.T.ksplit[0] + p.T.ksplit[1]) * B * gr) + 64;
+    p.n_dT = (size_t)((p.dT.ksplit[0] + p.dT.ksplit[1]) * B * gr) + 64;
+    p.n_dxh = (size_t)(p.dxh.ksplit[0] * B * din + p.dxh.ksplit[1] * B * h) + 64;
+    const size_t nz = (size_t)(B * 4 * h);
+    p.fwd_bytes = align_up(p.n_T * 4) + align_up(2 * nz * 4);
+    p.bwd_bytes = align_up(nz * 4) + 2 * align_up((size_t)(B * gr) * 4) + align_up((p.n_dT > p.n_dxh ? p.n_dT : p.n_dxh) * 4);
+    return p;
+}
+static const LstmTilePlan &plan_lstm_tiles(const pf_lstm_desc *d)
+{
+    static thread_local PlanCache<PlanKey<5>, LstmTilePlan> cache;
+    return cache.get(PlanKey<5>{{d->B, d->d_in, d->h, d->r, d->groups}}, [&] { return make_lstm_tile_plan(d); });
+}
+
+// Adds a product whose result is needed in full: straight to `out`, or through partial sums taken from `part`.
+static void add_split(TileArgs &a, SplitSumArgs &ss, const TileGroup &g, int i, TileProb q, float *out, i64 count, float *&part)
+{
+    const int ks = g.ksplit[i];
+    q.o.f32 = 1;
+    q.o.C = out;
+    if (ks > 1) {
+        q.o.C = part;
+        q.o.split_stride = count;
+    }
+    tile_add(a, g.shape, PF_F32, q, ks);
+    if (ks > 1) {
+        split_sum_add(ss, SplitSum{part, out, count, count, a.p[a.n - 1].ksplit, 0, nullptr, 0, 0});
+        part += (ks * count + 3) / 4 * 4;
+    }
+}
+
+static int lstm_fwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_prev, const float *c_prev, const float *Vx,
+                          const float *Ux, const float *Vh, const float *Uh, const float *bias, float *h_out, float *c_out,
+                          float *gates, float *Tx, float *Th, Workspace &ws, hipStream_t s)
+{
+    const int B = (int)d->B, din = (int)d->d_in, h = (int)d->h, r = (int)d->r, G = d->groups, gr = G * r;
+    const LstmTilePlan p = plan_lstm_tiles(d);
+    float *part = ws.take<float>(p.n_T), *z = ws.take<float>((size_t)2 * B * 4 * h);
+    TileArgs a = {};
+    SplitSumArgs ss = {};
+    add_split(a, ss, p.T, 0, tile_prob(TILE_NN, B, gr, din, x, din, Vx, gr, nullptr, gr), Tx, (i64)B * gr, part);
+    add_split(a, ss, p.T, 1, tile_prob(TILE_NN, B, gr, h, h_prev, h, Vh, gr, nullptr, gr), Th, (i64)B * gr, part);
+    int st = launch_tiles_linear(s, "lstm_T=[x*Vx|h*Vh]", PF_F32, p.T.shape, a);
+    if (st == PF_OK) st = launch_split_sums(s, ss);
+    if (st != PF_OK) return st;
+    TileArgs b = {};
+    for (int path = 0; path < 2; ++path) {
+        TileProb q = tile_prob(TILE_NT, B, G == 4 ? h : 4 * h, r, path ? Th : Tx, gr, path ? Uh : Ux, r,
+                               z + (i64)path * B * 4 * h, 4 * (i64)h);
+        q.o.f32 = 1;
+        if (G == 4) {
+            q.nb = 4;
+            q.sa = r;
+            q.sb = (i64)h * r;
+            q.sc = h;
+        }
+        tile_add(b, p.z.shape, PF_F32, q, 1);
+    }
+    st = launch_tiles_linear(s, "lstm_z=[Tx|Th]*[Ux|Uh]t", PF_F32, p.z.shape, b);
+    if (st != PF_OK) return st;
+    PF_LAUNCH(st, "lstm_pointwise_fwd", lstm_slices_pointwise_fwd_kernel, dim3((unsigned)(((i64)B * h + 255) / 256)), dim3(256),
+              s, z, 2, (i64)B * 4 * h, d->has_bias ? bias : nullptr, (const float *)nullptr, c_prev, h_out, c_out, gates, B, h);
+    return st;
+}
+
+static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_prev, const float *c_prev,
+                          const float *c_out, const float *gates, const float *Tx, const float *Th, const float *Vx,
+                          const float *Ux, const float *Vh, const float *Uh, const float *dh, const float *dc_next,
+                          float *dx, float *dh_prev, float *dc_prev, float *dVx, float *dUx, float *dVh, float *dUh,
+                          float *dbias, int accumulate, Workspace &ws, hipStream_t s)
+{
+    const int B = (int)d->B, din = (int)d->d_in, h = (int)d->h, r = (int)d->r, G = d->groups, gr = G * r;
+    const LstmTilePlan p = plan_lstm_tiles(d);
+    float *dz = ws.take<float>((size_t)B * 4 * h);
+    float *dTx = ws.take<float>((size_t)B * gr), *dTh = ws.take<float>((size_t)B * gr);
+    float *part0 = ws.take<float>(p.n_dT > p.n_dxh ? p.n_dT : p.n_dxh), *part = part0;
+    int st = PF_OK;
+    PF_LAUNCH(st, "lstm_pointwise_bwd", lstm_pointwise_bwd_kernel, dim3((unsigned)(((i64)B * h + 255) / 256)), dim3(256), s,
+              gates, c_prev, c_out, dh, dc_next, dz, dc_prev, B, h);
+    if (st != PF_OK) return st;
+    TileArgs a = {};
+    SplitSumArgs ss = {};
+    for (int path = 0; path < 2; ++path) { // dT = dz U: over all 4h columns, or per gate block
+        TileProb q = tile_prob(TILE_NN, B, r, G == 4 ? h : 4 * h, dz, 4 * (i64)h, path ? Uh : Ux, r, nullptr, gr);
+        if (G == 4) {
+            q.nb = 4;
+            q.sa = h;
+            q.sb = (i64)h * r;
+            q.sc = r;
+        }
+        add_split(a, ss, p.dT, path, q, path ? dTh : dTx, (i64)B * gr, part);
+    }
+    st = launch_tiles_linear(s, "lstm_dT=dz*[Ux|Uh]", PF_F32, p.dT.shape, a);
+    if (st == PF_OK) st = launch_split_sums(s, ss);
+    if (st != PF_OK) return st;
+    TileArgs b = {};
+    SplitSumArgs sb = {};
+    part = part0;
+    if (dx) add_split(b, sb, p.dxh, 0, tile_prob(TILE_NT, B, din, gr, dTx, gr, Vx, gr, nullptr, din), dx, (i64)B * din, part);
+    add_split(b, sb, p.dxh, 1, tile_prob(TILE_NT, B, h, gr, dTh, gr, Vh, gr, nullptr, h), dh_prev, (i64)B * h, part);
+    st = launch_tiles_linear(s, "lstm_dxh=[dTx*Vxt|dTh*Vht]", PF_F32, p.dxh.shape, b);
+    if (st == PF_OK) st = launch_split_sums(s, sb);
+    if (st != PF_OK) return st;
+    TileArgs c = {};
+    const auto grad = [&](const float *A, i64 lda, int m, const float *Bm, i64 ldb, int n, float *out, float *sums) {
+        TileProb q = tile_prob(TILE_TN, m, n, B, A, lda, Bm, ldb, out, n);
+        q.o.f32 = 1;
+        q.o.accumulate = accumulate;
+        q.o.sums = sums;
+        return q;
+    };
+    for (int path = 0; path < 2; ++path) {
+        TileProb q = grad(dz, 4 * (i64)h, G == 4 ? h : 4 * h, path ? Th : Tx, gr, r, path ? dUh : dUx, path ? nullptr : dbias);
+        if (G == 4) {
+            q.nb = 4;
+            q.sa = h;
+            q.sb = r;
+            q.sc = (i64)h * r;
+            q.ssums = h;
+        }
+        tile_add(c, p.grads.shape, PF_F32, q, 1);
+    }
+    tile_add(c, p.grads.shape, PF_F32, grad(x, din, din, dTx, gr, gr, dVx, nullptr), 1);
+    tile_add(c, p.grads.shape, PF_F32, grad(h_prev, h, h, dTh, gr, gr, dVh, nullptr), 1);
+    return launch_tiles_linear(s, "lstm_grads", PF_F32, p.grads.shape, c);
+}
+
+// ------------------------------------------------------------------ small-batch path (B <= 32)
+// Seven launches per cell instead of two dozen: every product streams its factor once from all compute
+// units (pf_skinny.h); slice sums ride along with the gate arithmetic and with the gradient updates.
 
 // (every extent of the sliced products must hold one 16-byte load: see launch_skinny_gemm)
 static bool lstm_skinny_ok(const pf_lstm_desc *d)
@@ -468,13 +620,17 @@ extern "C" {
 size_t pf_lowrank_lstm_cell_fwd_workspace_bytes(const pf_lstm_desc *d)
 {
     if (check_lstm_desc(d) != PF_OK) return 0;
-    return lstm_skinny_ok(d) ? plan_lstm_skinny(d).fwd_bytes : plan_lstm(d).fwd_bytes;
+    return lstm_skinny_ok(d)  ? plan_lstm_skinny(d).fwd_bytes
+           : lstm_tiles_ok(d) ? plan_lstm_tiles(d).fwd_bytes
+                              : plan_lstm(d).fwd_bytes;
 }
 
 size_t pf_lowrank_lstm_cell_bwd_workspace_bytes(const pf_lstm_desc *d)
 {
     if (check_lstm_desc(d) != PF_OK) return 0;
-    return lstm_skinny_ok(d) ? plan_lstm_skinny(d).bwd_bytes : plan_lstm(d).bwd_bytes;
+    return lstm_skinny_ok(d)  ? plan_lstm_skinny(d).bwd_bytes
+           : lstm_tiles_ok(d) ? plan_lstm_tiles(d).bwd_bytes
+                              : plan_lstm(d).bwd_bytes;
 }
 
 int pf_lowrank_lstm_cell_fwd(const pf_lstm_desc *d, const void *x, const void *h_prev, const void *c_prev,
@@ -499,6 +655,11 @@ int pf_lowrank_lstm_cell_fwd(const pf_lstm_desc *d, const void *x, const void *h
                                (const float *)Ux, (const float *)Vh, (const float *)Uh, (const float *)bias,
                                (float *)h_out, (float *)c_out, (float *)gates_save, (float *)Tx_save, (float *)Th_save,
                                ws, (hipStream_t)stream);
+    if (lstm_tiles_ok(d))
+        return lstm_fwd_tiles(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)Vx,
+                              (const float *)Ux, (const float *)Vh, (const float *)Uh, (const float *)bias, (float *)h_out,
+                              (float *)c_out, (float *)gates_save, (float *)Tx_save, (float *)Th_save, ws,
+                              (hipStream_t)stream);
     return lstm_fwd_generic(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)Vx,
                             (const float *)Ux, (const float *)Vh, (const float *)Uh, (const float *)bias,
                             (float *)h_out, (float *)c_out, (float *)gates_save, (float *)Tx_save, (float *)Th_save, ws,
@@ -533,6 +694,13 @@ int pf_lowrank_lstm_cell_bwd(const pf_lstm_desc *d, const void *x, const void *h
                                (const float *)Uh, (const float *)dh, (const float *)dc_next, (float *)dx,
                                (float *)dh_prev, (float *)dc_prev, (float *)dVx, (float *)dUx, (float *)dVh,
                                (float *)dUh, (float *)dbias, accumulate, ws, (hipStream_t)stream);
+    if (lstm_tiles_ok(d))
+        return lstm_bwd_tiles(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)c_out,
+                              (const float *)gates_saved, (const float *)Tx_saved, (const float *)Th_saved,
+                              (const float *)Vx, (const float *)Ux, (const float *)Vh, (const float *)Uh,
+                              (const float *)dh, (const float *)dc_next, (float *)dx, (float *)dh_prev,
+                              (float *)dc_prev, (float *)dVx, (float *)dUx, (float *)dVh, (float *)dUh, (float *)dbias,
+                              accumulate, ws, (hipStream_t)stream);
     return lstm_bwd_generic(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)c_out,
                             (const float *)gates_saved, (const float *)Tx_saved, (const float *)Th_saved,
                             (const float *)Vx, (const float *)Ux, (const float *)Vh, (const float *)Uh,

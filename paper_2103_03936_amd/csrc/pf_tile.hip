@@ -15,13 +15,13 @@ __device__ __forceinline__ int die_order(int b, int n)
 
 // One 16-byte piece of the output: V neighbouring columns n .. n + V - 1 of row m (n a multiple of V).
 template <typename CT, int V>
-__device__ __forceinline__ void put_piece(const TileProb &p, int ks, int m, int n, float *v)
+__device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int m, int n, float *v)
 {
     typedef typename TileEl<CT>::elem elem;
     const TileOut &o = p.o;
     if (m >= p.M || n >= p.N) return;
     if (o.f32) {
-        float *c = (float *)o.C + ks * o.split_stride + (i64)m * o.ld + n;
+        float *c = (float *)o.C + ks * o.split_stride + zb * p.sc + (i64)m * o.ld + n;
         const int nv = min(V, p.N - n);
         if (nv == V && !o.accumulate) {
 #pragma unroll
@@ -46,7 +46,7 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int m, int 
             at = ((i64)img * o.CH + m) * o.HW + pos;
         }
     } else {
-        at = (i64)m * o.ld + n;
+        at = zb * p.sc + (i64)m * o.ld + n;
         nv = min(V, p.N - n);
     }
     elem *c = (elem *)o.C;
@@ -114,14 +114,14 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int m, int 
 }
 
 template <typename CT, class CFG, class LA, class LB>
-__device__ __forceinline__ void finish(const TileProb &p, int ks, int m0, int n0, LA &la, bool sums, unsigned char *smem,
+__device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, LA &la, bool sums, unsigned char *smem,
                                        int tid)
 {
     constexpr int V = TileEl<CT>::V;
-    tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, m0 + m, n0 + n, v); });
+    tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, zb, m0 + m, n0 + n, v); });
     if (sums) {
         __syncthreads();
-        float *out = p.o.sums + ks * p.o.sums_stride;
+        float *out = p.o.sums + ks * p.o.sums_stride + zb * p.ssums;
         const bool acc = p.o.accumulate != 0;
         la.put_sums((float *)smem, tid, [&](int m, float v) {
             if (m0 + m < p.M) out[m0 + m] = acc ? out[m0 + m] + v : v;
@@ -141,7 +141,7 @@ __device__ __forceinline__ const TileArgs &tile_args(const TileArgs &a)
 }
 
 struct TileAt {
-    int prob, ks, m0, n0;
+    int prob, ks, zb, m0, n0;
 };
 template <class CFG>
 __device__ __forceinline__ TileAt find_tile(const TileArgs &a)
@@ -154,8 +154,9 @@ __device__ __forceinline__ TileAt find_tile(const TileArgs &a)
         if (i < a.n && b >= a.p[i].block0) t.prob = i;
     const TileProb &p = a.p[t.prob];
     const int l = b - p.block0, per = p.tm * p.tn;
-    t.ks = l / per;
-    const int q = l - t.ks * per, tm = q / p.tn;
+    const int zk = l / per, q = l - zk * per, tm = q / p.tn;
+    t.zb = zk / p.ksplit;
+    t.ks = zk - t.zb * p.ksplit;
     t.m0 = tm * CFG::BM;
     t.n0 = (q - tm * p.tn) * CFG::BN;
     return t;
@@ -178,31 +179,33 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_v
     const TileAt t = find_tile<CFG>(a);
     const TileProb &p = a.p[t.prob];
     const int kbeg = t.ks * p.kper, kend = min(p.K, kbeg + p.kper), nch = (kend - kbeg + BK - 1) / BK;
+    typedef typename TileEl<CT>::elem elem;
+    const elem *A = (const elem *)p.A + t.zb * p.sa, *B = (const elem *)p.B + t.zb * p.sb;
     if (p.type == TILE_NT) {
         AK la;
         BKC lb;
-        la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid);
-        lb.init(p.B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
         tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
-            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.m0 + m, t.n0 + n, v);
+            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);
         });
     } else if (p.type == TILE_NN) {
         AK la;
         BMC lb;
-        la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid);
-        lb.init(p.B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
         tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
-            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.m0 + m, t.n0 + n, v);
+            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);
         });
     } else {
         AM la;
         BMC lb;
-        la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid);
-        lb.init(p.B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
-        finish<CT, CFG, AM, BMC>(p, t.ks, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
+        finish<CT, CFG, AM, BMC>(p, t.ks, t.zb, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
     }
 }
 
@@ -246,7 +249,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
     const int tid = threadIdx.x;
     const TileAt t = find_tile<CFG>(a);
     const TileProb &p = a.p[t.prob];
-    const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.m0 + m, t.n0 + n, v); };
+    const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v); };
     const int nch = (p.K + BK - 1) / BK; // (not TILE_WG)
     if (p.type == TILE_CONV || (GATHER && p.type == TILE_CONVG)) {
         AK la;
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
             __syncthreads();
             tile_product<CT, CFG>(la, lb, n, smem, tid);
         }
-        finish<CT, CFG, AW, BW>(p, t.ks, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
+        finish<CT, CFG, AW, BW>(p, t.ks, t.zb, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
     }
 }
 
@@ -303,6 +306,7 @@ TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const 
     TileProb p = {};
     p.type = type;
     p.M = M, p.N = N, p.K = K;
+    p.nb = 1;
     p.A = A, p.lda = lda;
     p.B = B, p.ldb = ldb;
     p.o.C = C, p.o.ld = ldc;
@@ -392,7 +396,7 @@ void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ks
         p.ksplit = p.K > 0 ? (p.K + p.kper - 1) / p.kper : 1;
     }
     p.block0 = a.blocks;
-    a.blocks += p.tm * p.tn * p.ksplit;
+    a.blocks += p.tm * p.tn * p.ksplit * p.nb;
 }
 
 template <typename CT, class CFG>

@@ -40,6 +40,8 @@ struct TileProb {
     int tm, tn, ksplit, kper, block0; // kper: chunk-aligned extent of a split (images for TILE_WG)
     const void *A, *B;
     i64 lda, ldb;
+    int nb;                // TILE_NN / NT / TN: products of the same shape, operands and output apart by
+    i64 sa, sb, sc, ssums; // sa, sb, sc elements (and ssums row sums)
     const float *ascale;
     PixView pa, pb;
     TileOut o;

@@ -5,6 +5,7 @@ import pytest
 
 import test_gpu_conv
 import test_gpu_linear
+import test_gpu_lstm
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +41,9 @@ def test_linear(shape, dtype):
 @pytest.mark.parametrize("shape", CONV)
 def test_conv(shape, dtype):
     test_gpu_conv._run(shape, dtype, saved_T=shape[0] != 5, seed=22)
+
+
+@pytest.mark.parametrize("groups", [1, 4])
+@pytest.mark.parametrize("shape", [(33, 9, 5, 4), (70, 41, 38, 9), (130, 700, 644, 161)])
+def test_lstm_cell(shape, groups):
+    test_gpu_lstm._cell(*shape, groups, seed=23)
