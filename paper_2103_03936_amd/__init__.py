@@ -3,8 +3,9 @@
 Argument marshalling only: every function takes torch tensors that live on the
 GPU, passes their device pointers and torch's current HIP stream through the
 C ABI declared in include/pufferfish.h, and returns the output tensors.  torch
-is used for device memory and streams; nothing here computes.  There is no
-CPU fallback: importing without the built library, or calling with CPU
+is used for device memory and streams; nothing here computes.  The layers' calls
+are marshalled natively (csrc/pf_binding.cpp), the rest through ctypes.  There is
+no CPU fallback: importing without the built library, or calling with CPU
 tensors, raises.
 """
 import ctypes
@@ -14,6 +15,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libpufferfish.so")
+BINDING_PATH = os.path.join(_HERE, "_binding.so")
 
 PF_F32, PF_BF16 = 0, 1
 PF_NCHW, PF_NHWC = 0, 1
@@ -83,12 +85,15 @@ EXPORTS = [
     "pf_timing_enable", "pf_timing_collect", "pf_timing_entry", "pf_timing_reset",
 ]
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(
-        f"{LIB_PATH} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()'); "
-        "there is no fallback path")
+for _p in (LIB_PATH, BINDING_PATH):
+    if not os.path.exists(_p):
+        raise ImportError(f"{_p} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()'); "
+                          "there is no fallback path")
 
 lib = ctypes.CDLL(LIB_PATH)
+from . import _binding as _native  # noqa: E402  (it links against the library just loaded)
+
+_native.set_errors(PfError, torch.OutOfMemoryError)
 lib.pf_status_string.restype = ctypes.c_char_p
 for _n in EXPORTS:
     if _n.endswith("_bytes"):  # (size_t results)
@@ -157,38 +162,13 @@ def _linear_desc(X, U, bias_flag):
 
 def pf_lowrank_linear_fwd(X, V, U, bias=None, save_T=True):
     """Y = (X V) U^T + bias.  Returns (Y, T) with T = X V saved for backward (None if not saved)."""
-    d = _linear_desc(X, U, bias is not None)
-    dt = X.dtype
-    Y = torch.empty((d.M, d.n_out), dtype=dt, device=X.device)
-    T = torch.empty((d.M, d.r), dtype=dt, device=X.device) if save_T else None
-    n = lib.pf_lowrank_linear_fwd_workspace_bytes(ctypes.byref(d))
-    ws = _workspace(n, X.device)
-    _check(lib.pf_lowrank_linear_fwd(ctypes.byref(d), _ptr(X, dt), _ptr(V, dt), _ptr(U, dt), _ptr(bias, dt),
-                                     _ptr(Y), _ptr(T), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-           "pf_lowrank_linear_fwd")
-    return Y, T
+    return _native.linear_fwd(X, V, U, bias, None, 0, save_T, False)
 
 
 def pf_lowrank_linear_bwd(X, V, U, dY, T_saved=None, need_dX=True, has_bias=False, grads=None):
     """Returns (dX, dU, dV, dbias); dU, dV, dbias are float32.  If `grads` = (dU, dV, dbias) is given the
     parameter gradients are accumulated into those tensors."""
-    d = _linear_desc(X, U, has_bias)
-    dt = X.dtype
-    dX = torch.empty_like(X) if need_dX else None
-    accumulate = grads is not None
-    if grads is None:
-        dU = torch.empty((d.n_out, d.r), dtype=torch.float32, device=X.device)
-        dV = torch.empty((d.n_in, d.r), dtype=torch.float32, device=X.device)
-        db = torch.empty((d.n_out,), dtype=torch.float32, device=X.device) if has_bias else None
-    else:
-        dU, dV, db = grads
-    n = lib.pf_lowrank_linear_bwd_workspace_bytes(ctypes.byref(d))
-    ws = _workspace(n, X.device)
-    _check(lib.pf_lowrank_linear_bwd(ctypes.byref(d), _ptr(X, dt), _ptr(V, dt), _ptr(U, dt), _ptr(dY, dt),
-                                     _ptr(T_saved, dt), _ptr(dX), _ptr(dU, torch.float32), _ptr(dV, torch.float32),
-                                     _ptr(db, torch.float32), ctypes.c_int(1 if accumulate else 0), _ptr(ws),
-                                     ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_linear_bwd")
-    return dX, dU, dV, db
+    return _native.linear_bwd(X, V, U, dY, T_saved, None, False, need_dX, has_bias, grads, False)
 
 
 def pf_lowrank_linear_bwd_static(X, V, U, dY, T_saved, dX, dU, dV, dbias=None, accumulate=False):
@@ -206,79 +186,25 @@ def pf_lowrank_linear_bwd_static(X, V, U, dY, T_saved, dX, dU, dV, dbias=None, a
 
 def pf_lowrank_linear_fwd_ep(X, V, U, bias=None, residual=None, act="none", save_T=True):
     """Y = act((X V) U^T + bias + residual); returns (Y, T)."""
-    d = _linear_desc(X, U, bias is not None)
-    dt = X.dtype
-    Y = torch.empty((d.M, d.n_out), dtype=dt, device=X.device)
-    T = torch.empty((d.M, d.r), dtype=dt, device=X.device) if save_T else None
-    ws = _workspace(lib.pf_lowrank_linear_fwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_linear_fwd_ep(ctypes.byref(d), _ptr(X, dt), _ptr(V, dt), _ptr(U, dt), _ptr(bias, dt),
-                                        _ptr(residual, dt), ctypes.c_int(_ACT[act]), _ptr(Y), _ptr(T), _ptr(ws),
-                                        ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_linear_fwd_ep")
-    return Y, T
+    return _native.linear_fwd(X, V, U, bias, residual, _ACT[act], save_T, True)
 
 
 def pf_lowrank_linear_bwd_ep(X, V, U, dZ, T_saved=None, dX_add=None, x_is_relu=False, need_dX=True, has_bias=False,
                              grads=None):
     """From dZ = dL/d(pre-activation): (dX, dU, dV, dbias) with dX = (dZ U V^T + dX_add) * [X > 0 if x_is_relu]."""
-    d = _linear_desc(X, U, has_bias)
-    dt, f32 = X.dtype, torch.float32
-    dX = torch.empty_like(X) if need_dX else None
-    accumulate = grads is not None
-    if grads is None:
-        dU = torch.empty((d.n_out, d.r), dtype=f32, device=X.device)
-        dV = torch.empty((d.n_in, d.r), dtype=f32, device=X.device)
-        db = torch.empty((d.n_out,), dtype=f32, device=X.device) if has_bias else None
-    else:
-        dU, dV, db = grads
-    ws = _workspace(lib.pf_lowrank_linear_bwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_linear_bwd_ep(ctypes.byref(d), _ptr(X, dt), _ptr(V, dt), _ptr(U, dt), _ptr(dZ, dt),
-                                        _ptr(T_saved, dt), _ptr(dX_add, dt), ctypes.c_int(1 if x_is_relu else 0),
-                                        _ptr(dX), _ptr(dU, f32), _ptr(dV, f32), _ptr(db, f32),
-                                        ctypes.c_int(1 if accumulate else 0), _ptr(ws), ctypes.c_size_t(ws.numel()),
-                                        _stream()), "pf_lowrank_linear_bwd_ep")
-    return dX, dU, dV, db
-
-
-def _shared_desc(X, U, bias_flag):
-    M, n_in = X.shape
-    G, n_out, r = U.shape
-    return pf_linear_shared_desc(M, n_in, n_out, r, G, _dtype_code(X), 1 if bias_flag else 0)
+    return _native.linear_bwd(X, V, U, dZ, T_saved, dX_add, x_is_relu, need_dX, has_bias, grads, True)
 
 
 def pf_lowrank_linear_shared_fwd(X, V, U, bias=None, save_T=True):
     """G projections of one input (Q, K, V of attention): X[M,in], V[G,in,r], U[G,out,r], bias[G,out] -> (Y[G,M,out],
     T[G,M,r])."""
-    d = _shared_desc(X, U, bias is not None)
-    dt = X.dtype
-    Y = torch.empty((d.groups, d.M, d.n_out), dtype=dt, device=X.device)
-    T = torch.empty((d.groups, d.M, d.r), dtype=dt, device=X.device) if save_T else None
-    ws = _workspace(lib.pf_lowrank_linear_shared_fwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_linear_shared_fwd(ctypes.byref(d), _ptr(X), _ptr(V, dt), _ptr(U, dt), _ptr(bias, dt), _ptr(Y),
-                                            _ptr(T), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-           "pf_lowrank_linear_shared_fwd")
-    return Y, T
+    return _native.shared_fwd(X, V, U, bias, save_T)
 
 
 def pf_lowrank_linear_shared_bwd(X, V, U, dY, T_saved=None, need_dX=True, has_bias=False, grads=None):
     """dY[G,M,out] -> (dX[M,in] summed over the projections, dU[G,out,r], dV[G,in,r], dbias[G,out]); the parameter
     gradients are float32 and accumulate into `grads` = (dU, dV, dbias) when given."""
-    d = _shared_desc(X, U, has_bias)
-    dt = X.dtype
-    f32 = torch.float32
-    dX = torch.empty_like(X) if need_dX else None
-    accumulate = grads is not None
-    if grads is None:
-        dU = torch.empty(U.shape, dtype=f32, device=X.device)
-        dV = torch.empty(V.shape, dtype=f32, device=X.device)
-        db = torch.empty((d.groups, d.n_out), dtype=f32, device=X.device) if has_bias else None
-    else:
-        dU, dV, db = grads
-    ws = _workspace(lib.pf_lowrank_linear_shared_bwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_linear_shared_bwd(ctypes.byref(d), _ptr(X, dt), _ptr(V, dt), _ptr(U, dt), _ptr(dY, dt),
-                                            _ptr(T_saved, dt), _ptr(dX), _ptr(dU, f32), _ptr(dV, f32), _ptr(db, f32),
-                                            ctypes.c_int(1 if accumulate else 0), _ptr(ws),
-                                            ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_linear_shared_bwd")
-    return dX, dU, dV, db
+    return _native.shared_bwd(X, V, U, dY, T_saved, need_dX, has_bias, grads)
 
 
 def pf_dense_linear_fwd(X, W, bias=None):
@@ -308,12 +234,6 @@ def pf_dense_linear_bwd(X, W, dY, has_bias=False):
 
 # -------------------------------------------------------------------- conv
 
-def _conv_desc(X, Uk, Vp, stride, pad):
-    N, C, H, W = X.shape
-    r, _, k, _ = Uk.shape
-    return pf_conv_desc(N, C, H, W, Vp.shape[0], r, k, stride, pad, PF_NCHW, _dtype_code(X), PF_F32)
-
-
 def conv_out_hw(d):
     return (d.H + 2 * d.pad - d.k) // d.stride + 1, (d.W + 2 * d.pad - d.k) // d.stride + 1
 
@@ -321,79 +241,27 @@ def conv_out_hw(d):
 def pf_lowrank_conv_fwd(X, Uk, Vp, stride=1, pad=0, save_T=True, save_W=False):
     """Thin k x k conv (Uk[r,C,k,k]) then 1x1 conv (Vp[Cout,r]).  Returns (Y, T), or (Y, T, W) with
     save_W: W holds the factors as the backward kernels read them (None when they read them in place)."""
-    d = _conv_desc(X, Uk, Vp, stride, pad)
-    Ho, Wo = conv_out_hw(d)
-    dt = X.dtype
-    Y = torch.empty((d.N, d.Cout, Ho, Wo), dtype=dt, device=X.device)
-    T = torch.empty((d.N, d.r, Ho, Wo), dtype=dt, device=X.device) if save_T else None
-    nW = lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(d)) if save_W else 0
-    Wsv = torch.empty((nW,), dtype=torch.uint8, device=X.device) if nW else None
-    ws = _workspace(lib.pf_lowrank_conv_fwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_conv_fwd(ctypes.byref(d), _ptr(X), _ptr(Uk, dt), _ptr(Vp, dt), _ptr(Y), _ptr(T),
-                                   _ptr(Wsv), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-           "pf_lowrank_conv_fwd")
-    return (Y, T, Wsv) if save_W else (Y, T)
+    return _native.conv_fwd(X, Uk, Vp, None, None, None, 0, stride, pad, save_T, save_W, False)
 
 
 def pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=None, stride=1, pad=0, need_dX=True, grads=None, W_saved=None):
     """Returns (dX, dUk, dVp); dUk, dVp are float32 (accumulated into `grads` = (dUk, dVp) if given)."""
-    d = _conv_desc(X, Uk, Vp, stride, pad)
-    dt = X.dtype
-    dX = torch.empty_like(X) if need_dX else None
-    accumulate = grads is not None
-    if grads is None:
-        dUk = torch.empty(Uk.shape, dtype=torch.float32, device=X.device)
-        dVp = torch.empty(Vp.shape, dtype=torch.float32, device=X.device)
-    else:
-        dUk, dVp = grads
-    ws = _workspace(lib.pf_lowrank_conv_bwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_conv_bwd(ctypes.byref(d), _ptr(X), _ptr(Uk, dt), _ptr(Vp, dt), _ptr(dY, dt),
-                                   _ptr(T_saved, dt), _ptr(W_saved), _ptr(dX), _ptr(dUk, torch.float32),
-                                   _ptr(dVp, torch.float32), ctypes.c_int(1 if accumulate else 0), _ptr(ws),
-                                   ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_conv_bwd")
-    return dX, dUk, dVp
+    return _native.conv_bwd(X, Uk, Vp, None, dY, T_saved, stride, pad, None, False, need_dX, False, grads, W_saved, False)
 
 
 def pf_lowrank_conv_fwd_ep(X, Uk, Vp, scale=None, shift=None, residual=None, act="none", stride=1, pad=0, save_T=True,
                            save_W=False):
     """Y = act(scale[o] (Vp * (Uk * X)) + shift[o] + residual); scale, shift float32 [Cout].  Returns (Y, T) or
     (Y, T, W_save)."""
-    d = _conv_desc(X, Uk, Vp, stride, pad)
-    dt, f32 = X.dtype, torch.float32
-    Ho, Wo = conv_out_hw(d)
-    Y = torch.empty((d.N, d.Cout, Ho, Wo), dtype=dt, device=X.device)
-    T = torch.empty((d.N, d.r, Ho, Wo), dtype=dt, device=X.device) if save_T else None
-    nW = lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(d)) if save_W else 0
-    Wsv = torch.empty((nW,), dtype=torch.uint8, device=X.device) if nW else None
-    ws = _workspace(lib.pf_lowrank_conv_fwd_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_conv_fwd_ep(ctypes.byref(d), _ptr(X), _ptr(Uk, dt), _ptr(Vp, dt), _ptr(scale, f32),
-                                      _ptr(shift, f32), _ptr(residual, dt), ctypes.c_int(_ACT[act]), _ptr(Y), _ptr(T),
-                                      _ptr(Wsv), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-           "pf_lowrank_conv_fwd_ep")
-    return (Y, T, Wsv) if save_W else (Y, T)
+    return _native.conv_fwd(X, Uk, Vp, scale, shift, residual, _ACT[act], stride, pad, save_T, save_W, True)
 
 
 def pf_lowrank_conv_bwd_ep(X, Uk, Vp, scale, dZ, T_saved=None, stride=1, pad=0, dX_add=None, x_is_relu=False,
                            need_dX=True, need_dshift=True, grads=None, W_saved=None):
     """From dZ = dL/d(pre-activation): (dX, dUk, dVp, dshift), dX = (conv^T(dT) + dX_add) * [X > 0 if x_is_relu];
     `grads` = (dUk, dVp, dshift) accumulates."""
-    d = _conv_desc(X, Uk, Vp, stride, pad)
-    dt, f32 = X.dtype, torch.float32
-    dX = torch.empty_like(X) if need_dX else None
-    accumulate = grads is not None
-    if grads is None:
-        dUk = torch.empty(Uk.shape, dtype=f32, device=X.device)
-        dVp = torch.empty(Vp.shape, dtype=f32, device=X.device)
-        dsh = torch.empty((d.Cout,), dtype=f32, device=X.device) if need_dshift else None
-    else:
-        dUk, dVp, dsh = grads
-    ws = _workspace(lib.pf_lowrank_conv_bwd_ep_workspace_bytes(ctypes.byref(d)), X.device)
-    _check(lib.pf_lowrank_conv_bwd_ep(ctypes.byref(d), _ptr(X), _ptr(Uk, dt), _ptr(Vp, dt), _ptr(scale, f32),
-                                      _ptr(dZ, dt), _ptr(T_saved, dt), _ptr(W_saved), _ptr(dX_add, dt),
-                                      ctypes.c_int(1 if x_is_relu else 0), _ptr(dX), _ptr(dUk, f32), _ptr(dVp, f32),
-                                      _ptr(dsh, f32), ctypes.c_int(1 if accumulate else 0), _ptr(ws),
-                                      ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_conv_bwd_ep")
-    return dX, dUk, dVp, dsh
+    return _native.conv_bwd(X, Uk, Vp, scale, dZ, T_saved, stride, pad, dX_add, x_is_relu, need_dX, need_dshift, grads,
+                            W_saved, True)
 
 
 def pf_dense_conv_fwd(X, Wd, stride=1, pad=0):
@@ -423,52 +291,16 @@ def pf_dense_conv_bwd(X, Wd, dY, stride=1, pad=0):
 
 # -------------------------------------------------------------------- LSTM
 
-def _lstm_desc(x, h_prev, Ux, groups, has_bias):
-    B, d_in = x.shape
-    return pf_lstm_desc(B, d_in, h_prev.shape[1], Ux.shape[1], groups, _dtype_code(x), 1 if has_bias else 0)
-
-
 def pf_lowrank_lstm_cell_fwd(x, h_prev, c_prev, Vx, Ux, Vh, Uh, bias=None, groups=1):
     """One factorized LSTM step.  Returns (h, c, gates, Tx, Th); the last three are saved for backward."""
-    d = _lstm_desc(x, h_prev, Ux, groups, bias is not None)
-    f32 = torch.float32
-    dev = x.device
-    h_out = torch.empty((d.B, d.h), dtype=f32, device=dev)
-    c_out = torch.empty((d.B, d.h), dtype=f32, device=dev)
-    gates = torch.empty((d.B, 4 * d.h), dtype=f32, device=dev)
-    Tx = torch.empty((d.B, groups * d.r), dtype=f32, device=dev)
-    Th = torch.empty((d.B, groups * d.r), dtype=f32, device=dev)
-    ws = _workspace(lib.pf_lowrank_lstm_cell_fwd_workspace_bytes(ctypes.byref(d)), dev)
-    _check(lib.pf_lowrank_lstm_cell_fwd(ctypes.byref(d), _ptr(x, f32), _ptr(h_prev, f32), _ptr(c_prev, f32),
-                                        _ptr(Vx, f32), _ptr(Ux, f32), _ptr(Vh, f32), _ptr(Uh, f32), _ptr(bias, f32),
-                                        _ptr(h_out), _ptr(c_out), _ptr(gates), _ptr(Tx), _ptr(Th), _ptr(ws),
-                                        ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_lstm_cell_fwd")
-    return h_out, c_out, gates, Tx, Th
+    return _native.cell_fwd(x, h_prev, c_prev, Vx, Ux, Vh, Uh, bias, groups)
 
 
 def pf_lowrank_lstm_cell_bwd(x, h_prev, c_prev, c_out, gates, Tx, Th, Vx, Ux, Vh, Uh, dh, dc_next=None, groups=1,
                              need_dx=True, grads=None):
     """One BPTT step.  Returns (dx, dh_prev, dc_prev, grads) with grads = dict(dVx, dUx, dVh, dUh, dbias) in
     float32; if `grads` is given the parameter gradients are accumulated into it."""
-    d = _lstm_desc(x, h_prev, Ux, groups, True)
-    f32 = torch.float32
-    dev = x.device
-    dx = torch.empty_like(x) if need_dx else None
-    dh_prev = torch.empty_like(h_prev)
-    dc_prev = torch.empty_like(c_prev)
-    accumulate = grads is not None
-    if grads is None:
-        grads = dict(dVx=torch.empty_like(Vx), dUx=torch.empty_like(Ux), dVh=torch.empty_like(Vh),
-                     dUh=torch.empty_like(Uh), dbias=torch.empty((4 * d.h,), dtype=f32, device=dev))
-    ws = _workspace(lib.pf_lowrank_lstm_cell_bwd_workspace_bytes(ctypes.byref(d)), dev)
-    _check(lib.pf_lowrank_lstm_cell_bwd(
-        ctypes.byref(d), _ptr(x, f32), _ptr(h_prev, f32), _ptr(c_prev, f32), _ptr(c_out, f32), _ptr(gates, f32),
-        _ptr(Tx, f32), _ptr(Th, f32), _ptr(Vx, f32), _ptr(Ux, f32), _ptr(Vh, f32), _ptr(Uh, f32), _ptr(dh, f32),
-        _ptr(dc_next, f32), _ptr(dx), _ptr(dh_prev), _ptr(dc_prev), _ptr(grads["dVx"], f32), _ptr(grads["dUx"], f32),
-        _ptr(grads["dVh"], f32), _ptr(grads["dUh"], f32), _ptr(grads["dbias"], f32),
-        ctypes.c_int(1 if accumulate else 0), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-        "pf_lowrank_lstm_cell_bwd")
-    return dx, dh_prev, dc_prev, grads
+    return _native.cell_bwd(x, h_prev, c_prev, c_out, gates, Tx, Th, Vx, Ux, Vh, Uh, dh, dc_next, groups, need_dx, grads)
 
 
 def _lstm_seq_desc(x, h0, Ux, groups, has_bias):
@@ -519,36 +351,10 @@ def pf_lowrank_lstm_seq_bwd(x, h0, c0, h_all, c_all, gates_all, Tx_all, Th_all, 
     return dx_all, dh0, dc0, grads
 
 
-def _ptr_array(ts, dtype=None):
-    """A host array of device pointers, one per layer (None: a NULL array)."""
-    if ts is None:
-        return None
-    return (ctypes.c_void_p * len(ts))(*[_ptr(t, dtype).value for t in ts])
-
-
-def _lstm_stack_desc(x, h0, Ux, groups, has_bias):
-    T, B, d_in = x.shape
-    return pf_lstm_stack_desc(T, B, d_in, h0[0].shape[1], Ux[0].shape[1], groups, len(Ux), _dtype_code(x),
-                              1 if has_bias else 0)
-
-
 def pf_lowrank_lstm_stack_fwd(x, h0, c0, Vx, Ux, Vh, Uh, bias=None, groups=1):
     """A stack of factorized LSTM layers over a sequence x[T,B,d]; h0, c0, Vx, Ux, Vh, Uh, bias are lists with one
     tensor per layer.  Returns lists (h_all, c_all, gates_all, Tx_all, Th_all), one tensor per layer."""
-    d = _lstm_stack_desc(x, h0, Ux, groups, bias is not None)
-    f32 = torch.float32
-    dev = x.device
-    L = d.layers
-    new = lambda n: [torch.empty((d.T, d.B, n), dtype=f32, device=dev) for _ in range(L)]
-    h_all, c_all, gates_all = new(d.h), new(d.h), new(4 * d.h)
-    Tx_all, Th_all = new(groups * d.r), new(groups * d.r)
-    ws = _workspace(lib.pf_lowrank_lstm_stack_fwd_workspace_bytes(ctypes.byref(d)), dev)
-    _check(lib.pf_lowrank_lstm_stack_fwd(
-        ctypes.byref(d), _ptr(x, f32), _ptr_array(h0, f32), _ptr_array(c0, f32), _ptr_array(Vx, f32),
-        _ptr_array(Ux, f32), _ptr_array(Vh, f32), _ptr_array(Uh, f32), _ptr_array(bias, f32), _ptr_array(h_all),
-        _ptr_array(c_all), _ptr_array(gates_all), _ptr_array(Tx_all), _ptr_array(Th_all), _ptr(ws),
-        ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_lstm_stack_fwd")
-    return h_all, c_all, gates_all, Tx_all, Th_all
+    return _native.stack_fwd(x, h0, c0, Vx, Ux, Vh, Uh, bias, groups)
 
 
 def pf_lowrank_lstm_stack_bwd(x, h0, c0, h_all, c_all, gates_all, Tx_all, Th_all, Vx, Ux, Vh, Uh, dh_top, dhT=None,
@@ -556,28 +362,8 @@ def pf_lowrank_lstm_stack_bwd(x, h0, c0, h_all, c_all, gates_all, Tx_all, Th_all
     """Back-propagation through time and depth.  dh_top[T,B,h] arrives at the last layer; dhT, dcT: optional
     lists (entries may be None).  Returns (dx_all, dh0, dc0, grads) with dh0, dc0 lists and grads a list of dicts
     per layer; if `grads` is given the parameter gradients are accumulated into it."""
-    d = _lstm_stack_desc(x, h0, Ux, groups, True)
-    f32 = torch.float32
-    dev = x.device
-    L = d.layers
-    dx_all = torch.empty_like(x) if need_dx else None
-    dh0 = [torch.empty_like(t) for t in h0]
-    dc0 = [torch.empty_like(t) for t in c0]
-    accumulate = grads is not None
-    if grads is None:
-        grads = [dict(dVx=torch.empty_like(Vx[l]), dUx=torch.empty_like(Ux[l]), dVh=torch.empty_like(Vh[l]),
-                      dUh=torch.empty_like(Uh[l]), dbias=torch.empty((4 * d.h,), dtype=f32, device=dev))
-                 for l in range(L)]
-    col = lambda k: _ptr_array([g[k] for g in grads], f32)
-    ws = _workspace(lib.pf_lowrank_lstm_stack_bwd_workspace_bytes(ctypes.byref(d)), dev)
-    _check(lib.pf_lowrank_lstm_stack_bwd(
-        ctypes.byref(d), _ptr(x, f32), _ptr_array(h0, f32), _ptr_array(c0, f32), _ptr_array(h_all, f32),
-        _ptr_array(c_all, f32), _ptr_array(gates_all, f32), _ptr_array(Tx_all, f32), _ptr_array(Th_all, f32),
-        _ptr_array(Vx, f32), _ptr_array(Ux, f32), _ptr_array(Vh, f32), _ptr_array(Uh, f32), _ptr(dh_top, f32),
-        _ptr_array(dhT, f32), _ptr_array(dcT, f32), _ptr(dx_all), _ptr_array(dh0), _ptr_array(dc0), col("dVx"),
-        col("dUx"), col("dVh"), col("dUh"), col("dbias"), ctypes.c_int(1 if accumulate else 0), _ptr(ws),
-        ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_lstm_stack_bwd")
-    return dx_all, dh0, dc0, grads
+    return _native.stack_bwd(x, h0, c0, h_all, c_all, gates_all, Tx_all, Th_all, Vx, Ux, Vh, Uh, dh_top, dhT, dcT, groups,
+                             need_dx, grads)
 
 
 def pf_svd_split(W, r, return_info=False):

@@ -1,12 +1,14 @@
-"""Compile the HIP sources under csrc/ for gfx950 into libpufferfish.so (in-tree)."""
+"""Compile the HIP sources under csrc/ for gfx950 into libpufferfish.so and the Python binding (in-tree)."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpufferfish.so")
+BINDING = os.path.join(HERE, "_binding.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -46,7 +48,21 @@ def build(verbose=False, jobs=8):
     if failed:
         raise RuntimeError("hipcc failed")
     subprocess.check_call([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
+    build_binding()
     return LIB
+
+
+def build_binding():
+    """csrc/pf_binding.cpp (host code only) -> _binding.so, linked against torch and libpufferfish.so."""
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    subprocess.check_call(
+        ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+         "-I" + os.path.join(tdir, "include"), "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+         "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "pf_binding.cpp"), "-o", BINDING,
+         "-L" + os.path.join(tdir, "lib"), "-L" + HERE, "-lpufferfish", "-ltorch_python", "-ltorch_cpu", "-ltorch_hip",
+         "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"])
+    return BINDING
 
 
 if __name__ == "__main__":

@@ -1,0 +1,74 @@
+// The tiled products' kernels, plain matrices (one translation unit per element type).
+#pragma once
+
+#include "pf_tile_put.h"
+
+namespace pf {
+
+template <typename CT, class CFG>
+__global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_value)
+{
+    const TileArgs &a = tile_args(by_value);
+    constexpr int BM = CFG::BM, BN = CFG::BN, BK = TileEl<CT>::BK;
+    typedef LoadKC<CT, BM> AK;
+    typedef LoadMC<CT, BM, true> AM;
+    typedef LoadKC<CT, BN> BKC;
+    typedef LoadMC<CT, BN> BMC;
+    constexpr int s1 = TileSize<CT, CFG, AK, BKC>::bytes, s2 = TileSize<CT, CFG, AK, BMC>::bytes,
+                  s3 = TileSize<CT, CFG, AM, BMC>::bytes;
+    constexpr int bytes = s1 > s2 ? (s1 > s3 ? s1 : s3) : (s2 > s3 ? s2 : s3);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[bytes];
+    const int tid = threadIdx.x;
+    const TileAt t = find_tile<CFG>(a);
+    const TileProb &p = a.p[t.prob];
+    const int kbeg = t.ks * p.kper, kend = min(p.K, kbeg + p.kper), nch = (kend - kbeg + BK - 1) / BK;
+    typedef typename TileEl<CT>::elem elem;
+    const elem *A = (const elem *)p.A + t.zb * p.sa, *B = (const elem *)p.B + t.zb * p.sb;
+    if (p.type == TILE_NT) {
+        AK la;
+        BKC lb;
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
+            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);
+        });
+    } else if (p.type == TILE_NN) {
+        AK la;
+        BMC lb;
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
+            put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);
+        });
+    } else {
+        AM la;
+        BMC lb;
+        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        finish<CT, CFG, AM, BMC>(p, t.ks, t.zb, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
+    }
+}
+
+template <typename CT, class CFG>
+static int launch_linear(hipStream_t s, const char *name, const TileArgs &a)
+{
+    int st = PF_OK;
+    PF_LAUNCH(st, name, (tile_linear_kernel<CT, CFG>), dim3(a.blocks), dim3(TILE_THREADS), s, a);
+    return st;
+}
+template <typename CT>
+int launch_linear_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a)
+{
+    switch (shape) {
+    case TS_32: return launch_linear<CT, TileCfg<32, 32, 1, 1, 4>>(s, name, a);
+    case TS_64: return launch_linear<CT, TileCfg<64, 64, 2, 2, 4>>(s, name, a);
+    case TS_128x64: return launch_linear<CT, TileCfg<128, 64, 2, 2, 2>>(s, name, a);
+    case TS_128: return launch_linear<CT, TileCfg<128, 128, 2, 2, 2>>(s, name, a);
+    default: return PF_ERR_UNSUPPORTED;
+    }
+}
+
+} // namespace pf

@@ -1,0 +1,166 @@
+// What the tiled products' kernels share: finding a workgroup's tile, and storing it.  One launch runs a
+// list of problems: a workgroup finds its problem, its tile and its share of the contraction from its index.
+#pragma once
+
+#include "pf_tile_host.h"
+
+namespace pf {
+
+// Workgroups are dealt to the eight dies in turn: give every die a run of consecutive tiles, which share operands
+// in its L2.
+__device__ __forceinline__ int die_order(int b, int n)
+{
+    const int q = n >> 3, r = n & 7, x = b & 7;
+    return x * q + min(x, r) + (b >> 3);
+}
+
+// One 16-byte piece of the output: V neighbouring columns n .. n + V - 1 of row m (n a multiple of V).
+template <typename CT, int V>
+__device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int m, int n, float *v)
+{
+    typedef typename TileEl<CT>::elem elem;
+    const TileOut &o = p.o;
+    if (m >= p.M || n >= p.N) return;
+    if (o.f32) {
+        float *c = (float *)o.C + ks * o.split_stride + zb * p.sc + (i64)m * o.ld + n;
+        const int nv = min(V, p.N - n);
+        if (nv == V && !o.accumulate) {
+#pragma unroll
+            for (int e = 0; e < V; e += 4) stg16(c + e, floats_piece<float>(v + e));
+        } else {
+            for (int e = 0; e < V; ++e)
+                if (e < nv) c[e] = o.accumulate ? c[e] + v[e] : v[e];
+        }
+        return;
+    }
+    i64 at;
+    int nv;
+    int pos = 0;
+    if (o.HC > 0) {
+        const int cn = n / V, img = cn / o.HC;
+        pos = (cn - img * o.HC) * V;
+        nv = min(V, o.HW - pos);
+        if (img >= o.N) return;
+        if (o.s > 1) {
+            at = ((i64)img * o.CH + m) * ((i64)o.H * o.W);
+        } else {
+            at = ((i64)img * o.CH + m) * o.HW + pos;
+        }
+    } else {
+        at = zb * p.sc + (i64)m * o.ld + n;
+        nv = min(V, p.N - n);
+    }
+    elem *c = (elem *)o.C;
+    const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask, *bias = (const elem *)o.bias;
+    const float sc = o.scale ? o.scale[m] : 1.f, sh = o.shift ? o.shift[m] : 0.f;
+    if (o.scale || o.shift) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) v[e] = v[e] * sc + sh;
+    }
+    if (nv == V && !(o.s > 1)) {
+        float f[8];
+        if (bias) {
+            piece_floats<CT>(ldg16(bias + n), f);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] += f[e];
+        }
+        if (add) {
+            piece_floats<CT>(ldg16(add + at), f);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] += f[e];
+        }
+        if (o.relu) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = fmaxf(v[e], 0.f);
+        }
+        if (mask) {
+            piece_floats<CT>(ldg16(mask + at), f);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = f[e] > 0.f ? v[e] : 0.f;
+        }
+        stg16(c + at, floats_piece<CT>(v));
+        return;
+    }
+    int y = 0, x = 0;
+    if (o.s > 1) y = pos / o.gW, x = pos - y * o.gW;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        if (e < nv) {
+            i64 i = at + e;
+            bool in = true;
+            if (o.s > 1) {
+                const int yy = y * o.s + o.ph, xx = x * o.s + o.pw;
+                in = yy < o.H && xx < o.W;
+                i = at + (i64)yy * o.W + xx;
+                if (++x == o.gW) x = 0, ++y;
+            }
+            if (in) {
+                union {
+                    uint32_t w[4];
+                    elem e[V];
+                } u;
+                float t = v[e];
+                if (bias) t += sizeof(elem) == 4 ? ((const float *)bias)[n + e] : bf16_bits_to_float((uint16_t)bias[n + e]);
+                if (add) t += sizeof(elem) == 4 ? ((const float *)add)[i] : bf16_bits_to_float((uint16_t)add[i]);
+                if (o.relu) t = fmaxf(t, 0.f);
+                if (mask)
+                    t = (sizeof(elem) == 4 ? ((const float *)mask)[i] : bf16_bits_to_float((uint16_t)mask[i])) > 0.f ? t
+                                                                                                                   : 0.f;
+                if (sizeof(elem) == 4) u.w[0] = __float_as_uint(t);
+                else u.w[0] = float_to_bf16_bits(t);
+                c[i] = u.e[0];
+            }
+        }
+    }
+}
+
+template <typename CT, class CFG, class LA, class LB>
+__device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, LA &la, bool sums, unsigned char *smem,
+                                       int tid)
+{
+    constexpr int V = TileEl<CT>::V;
+    tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, zb, m0 + m, n0 + n, v); });
+    if (sums) {
+        __syncthreads();
+        float *out = p.o.sums + ks * p.o.sums_stride + zb * p.ssums;
+        const bool acc = p.o.accumulate != 0;
+        la.put_sums((float *)smem, tid, [&](int m, float v) {
+            if (m0 + m < p.M) out[m0 + m] = acc ? out[m0 + m] + v : v;
+        });
+    }
+}
+
+// The argument block where the launch put it.  (Indexed by problem and, for the taps, by lane, the by-value parameter
+// would be copied to scratch memory by every thread.)
+__device__ __forceinline__ const TileArgs &tile_args(const TileArgs &a)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *(const TileArgs *)(const __attribute__((address_space(4))) TileArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+#else
+    return a;
+#endif
+}
+
+struct TileAt {
+    int prob, ks, zb, m0, n0;
+};
+template <class CFG>
+__device__ __forceinline__ TileAt find_tile(const TileArgs &a)
+{
+    TileAt t;
+    const int b = die_order(blockIdx.x, a.blocks);
+    t.prob = 0;
+#pragma unroll
+    for (int i = 1; i < TILE_MAX_PROBS; ++i)
+        if (i < a.n && b >= a.p[i].block0) t.prob = i;
+    const TileProb &p = a.p[t.prob];
+    const int l = b - p.block0, per = p.tm * p.tn;
+    const int zk = l / per, q = l - zk * per, tm = q / p.tn;
+    t.zb = zk / p.ksplit;
+    t.ks = zk - t.zb * p.ksplit;
+    t.m0 = tm * CFG::BM;
+    t.n0 = (q - tm * p.tn) * CFG::BN;
+    return t;
+}
+
+} // namespace pf
