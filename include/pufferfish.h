@@ -451,8 +451,9 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x,
 /* PF_ERR_SHAPE / PF_ERR_UNSUPPORTED).  For a convolution unroll        */
 /* W[c_out, c_in, k, k] to [c_in k^2, c_out] first (Section 2.2).       */
 /* Sweeps stop once a whole sweep found every column pair orthogonal to */
-/* min(m,n)-independent rounding level (max(m,n) * 2^-52 relative); at  */
-/* most 24 sweeps run.  The call is asynchronous, so convergence cannot */
+/* 2^-36 (or max(m,n) * 2^-52, if that is more) relative, which leaves  */
+/* the float factors exact to their last bit; at most 24 sweeps run.    */
+/* The call is asynchronous, so convergence cannot                      */
 /* come back in the status: info (nullable, DEVICE int[2]) receives     */
 /* info[0] = sweeps that ran, info[1] = rotations applied in the last   */
 /* of them -- 0 means converged; anything else means the 24 sweeps did  */

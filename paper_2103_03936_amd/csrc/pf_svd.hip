@@ -1,107 +1,542 @@
 // Truncated-SVD factor initialisation (Algorithm 1: W ~ U V^T with U = Ut_r S_r^(1/2), V = Vt_r S_r^(1/2)):
-// one-sided Jacobi (Hestenes) in double precision.
+// preconditioned one-sided Jacobi in double precision, eight columns at a time.
 //
-// The matrix with fewer columns is taken (A = W or W^T, rows >= cols) and stored column-major, so that a column is
-// contiguous.  A sweep orthogonalises every pair of columns once; pairs that share no column commute, so the
-// cols (cols - 1) / 2 pairs of a sweep are dealt into cols - 1 rounds of cols / 2 disjoint pairs (round-robin
-// tournament) and a round is one launch with a workgroup per pair: three dot products over the two columns, the
-// plane rotation that zeroes their inner product, applied to the columns of A and of the accumulated right
-// vectors Q.  When no pair of a sweep needed a rotation the remaining launches return at once.  Then
-// singular values = column norms, sorted by counting, and the r largest triplets are scaled and written out.
+// The matrix with fewer columns is taken (A = W or W^T, rows >= cols) and stored column-major.  One-sided Jacobi
+// orthogonalises every pair of columns once per sweep; on A itself a sweep moves rows x cols numbers cols times and
+// eight or more sweeps follow.  So it first runs on something smaller that has the same right singular vectors:
+//   G = A^T A + shift I,  G = L L^T,  one-sided Jacobi on the cols x cols matrix L: L W = V S  (columns of V orthonormal,
+//   no rotations accumulated: the normalised columns themselves are the eigenvectors of G),
+//   B = A V: columns orthogonal to about eps kappa^2.
+// V is a preconditioner only.  Then the one-sided Jacobi runs on B with V carried along, to the same threshold as it
+// would on A: when a check of all pairs finds them orthogonal (well-conditioned matrices) nothing is left to do, otherwise
+// sweeps follow until one finds nothing to rotate, so singular values far below the largest come out as exactly as
+// without the preconditioner.  The shift (rounding level of G) keeps L defined for any matrix.
+// Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
+//
+// A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
+// every column of one block against every column of the other (in a sweep's first round also within the blocks) found on
+// that 16 x 16 matrix in LDS by one wavefront and applied to the rows, one row per thread.  Pairs of blocks are dealt into rounds by round-robin; the rounds of all sweeps run in ONE cooperative
+// kernel with a grid barrier between them, because the number of sweeps is known on the device only: a launch per
+// round has to be enqueued for the most sweeps that may be needed, at 2.8 us each (2048 x 512: 12264 launches, 84 ms).
+// A barrier's wait is bounded: after about a second without the others a workgroup gives up and reports no convergence.
 #include "pf_gemm.h"
 
 namespace pf {
 
 constexpr int SVD_MAX_SWEEPS = 24;
-// A pair counts as orthogonal when |a_p . a_q| <= tol |a_p| |a_q|.  The inner product of two columns of `rows`
-// doubles carries rounding noise of about rows * 2^-53 relative to |a_p| |a_q|, so a tighter threshold never stops
-// the sweeps; rows * 2^-52 still leaves the fp32 factors exact to their last bit.
+constexpr int SVD_NT = 512;  // threads of the cooperative kernels
+constexpr int SVD_B = 8;     // columns per block
+typedef __attribute__((ext_vector_type(4))) double f64x4_t;
+typedef __attribute__((ext_vector_type(2))) double f64x2_t;
+
+// A pair counts as orthogonal when |a_p . a_q| <= tol |a_p| |a_q|.  The factors are float (2^-24): 2^-36 leaves their last
+// bit exact, and is far above the rounding noise of an inner product of doubles, which a threshold must not go below
+// (rows * 2^-53) and which the preconditioner reaches for matrices that are not ill-conditioned.
 static double svd_tolerance(int rows)
 {
     const double t = (double)rows * 2.220446049250313e-16;
-    return t < 1e-15 ? 1e-15 : t;
+    return t < 1.4551915228366852e-11 ? 1.4551915228366852e-11 : t;
 }
+// That of the preconditioner, whose columns become V: rounding level.
+static double svd_tolerance_v(int rows) { return (double)(rows < 64 ? 64 : rows) * 2.220446049250313e-16; }
 
-__global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *At, double *Qt, int n, int nr, int nc,
+// Device-side state of a call
+struct SvdCtrl {
+    unsigned arrived[2]; // grid barriers of the two cooperative kernels
+    unsigned failed;     // a barrier's wait ran out
+    unsigned violations; // pairs of B that are not orthogonal after the preconditioner
+    unsigned rot[2][SVD_MAX_SWEEPS + 1]; // block pairs rotated per sweep, of L and of B
+    unsigned sweeps;     // sweeps over the pairs of B, the check included
+    unsigned last;       // block pairs rotated in the last of them
+};
+
+__global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *At, SvdCtrl *ctrl, int n, int nr, int nc, int ld,
                                                         int transposed)
 {
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < (int)(sizeof(SvdCtrl) / 4); i += 256) ((unsigned *)ctrl)[i] = 0u;
     const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;
-    if (idx < (i64)nc * nr) {
-        const int j = (int)(idx / nr), i = (int)(idx % nr);
-        At[idx] = (double)(transposed ? W[(i64)j * n + i] : W[(i64)i * n + j]);
-    }
-    if (idx < (i64)nc * nc) Qt[idx] = (idx / nc == idx % nc) ? 1.0 : 0.0;
+    if (idx >= (i64)nc * ld) return;
+    const int j = (int)(idx / ld), i = (int)(idx % ld);
+    At[idx] = i >= nr ? 0.0 : (double)(transposed ? W[(i64)j * n + i] : W[(i64)i * n + j]);
 }
 
-__global__ __launch_bounds__(256) void svd_round_kernel(double *At, double *Qt, int nr, int nc, int npad, int round,
-                                                         int sweep, unsigned *rot, double tol)
+// Lane l of a wavefront holds column c0 + l % 16 of a column-major matrix at rows r0 + 2 (l / 16) + {0, 1}: fragments of
+// two 16x16x4 MFMAs, for the left and for the right operand alike.  Columns >= nc and rows >= nr read as zero.
+__device__ __forceinline__ f64x2_t svd_frag(const double *M, int ld, int col, int nc, int row, int nr)
 {
-    if (sweep > 0 && rot[sweep - 1] == 0u) return; // the sweep before found every pair orthogonal
-    const int k = blockIdx.x, m1 = npad - 1, tid = threadIdx.x;
-    int p = k == 0 ? m1 : (round + k) % m1, q = k == 0 ? round % m1 : (round - k + m1) % m1;
-    if (p >= nc || q >= nc) return; // the padding player sits this round out
-    if (p > q) {
-        const int t = p;
-        p = q;
-        q = t;
+    f64x2_t v = {0.0, 0.0};
+    if (col < nc && row < nr) {
+        v = *(const f64x2_t *)(M + (i64)col * ld + row);
+        if (row + 1 >= nr) v[1] = 0.0;
     }
-    double *ap = At + (i64)p * nr, *aq = At + (i64)q * nr;
-    double alpha = 0.0, beta = 0.0, gamma = 0.0;
-    for (int i = tid; i < nr; i += 256) {
-        const double va = ap[i], vb = aq[i];
-        alpha += va * va;
-        beta += vb * vb;
-        gamma += va * vb;
+    return v;
+}
+
+// C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows
+__global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc)
+{
+    const int ti = blockIdx.x, tj = blockIdx.y;
+    if (tj > ti) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    f64x4_t acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
+    for (int r = 8 * wave; r < nr; r += 32) {
+        f64x2_t x[2], y[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            x[a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 2 * g, nr);
+            y[a] = svd_frag(M, ld, 32 * tj + 16 * a + c, nc, r + 2 * g, nr);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][0], y[b][0], acc[a][b], 0, 0, 0);
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][1], y[b][1], acc[a][b], 0, 0, 0);
+            }
     }
-    __shared__ double red[3][256];
-    __shared__ double cs[2];
-    __shared__ int rotate;
-    red[0][tid] = alpha;
-    red[1][tid] = beta;
-    red[2][tid] = gamma;
+    __shared__ double part[4][32][33];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[wave][16 * a + g + 4 * v][16 * b + c] = acc[a][b][v];
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) { // fixed tree: the same sums every run
-        if (tid < s) {
-            red[0][tid] += red[0][tid + s];
-            red[1][tid] += red[1][tid + s];
-            red[2][tid] += red[2][tid + s];
+    for (int e = tid; e < 1024; e += 256) {
+        const int i = e >> 5, j = e & 31, gi = 32 * ti + i, gj = 32 * tj + j;
+        const double s = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
+        if (gi < nc && gj < nc && (ti != tj || i >= j)) {
+            C[(i64)gj * ldc + gi] = s;
+            C[(i64)gi * ldc + gj] = s;
+        }
+    }
+}
+
+// counts the pairs of columns whose Gram entry says that they are not orthogonal
+__global__ __launch_bounds__(256) void svd_check_kernel(const double *G, SvdCtrl *ctrl, int nc, int ld, double tol)
+{
+    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;
+    bool bad = false;
+    if (idx < (i64)nc * nc) {
+        const int i = (int)(idx % nc), j = (int)(idx / nc);
+        if (i > j) {
+            const double g = G[(i64)j * ld + i];
+            bad = g != 0.0 && !(fabs(g) <= tol * sqrt(G[(i64)j * ld + j] * G[(i64)i * ld + i]));
+        }
+    }
+    if (bad) atomicAdd(&ctrl->violations, 1u);
+}
+
+// B[:, j] = A V[:, j] in rows 0 .. of BV, V itself below: 64 x 64 tiles, a wavefront 32 columns x 32 rows.  V = the
+// normalised columns of L.
+__global__ __launch_bounds__(256) void svd_apply_kernel(const double *At, const double *L, double *BV, int nr, int nc, int ld,
+                                                         int ldl, int ldb)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const int j0 = blockIdx.y * 64 + (wave >> 1) * 32, i0 = blockIdx.x * 64 + (wave & 1) * 32;
+    f64x4_t acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
+    for (int k = 0; k < nc; k += 8) {
+        f64x2_t x[2], y[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+            x[a] = svd_frag(L, ldl, j0 + 16 * a + c, nc, k + 2 * g, nc);
+            const int row = i0 + 16 * a + c, kk = k + 2 * g;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) y[a][e] = row < nr && kk + e < nc ? At[(i64)(kk + e) * ld + row] : 0.0;
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][0], y[b][0], acc[a][b], 0, 0, 0);
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][1], y[b][1], acc[a][b], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int j = j0 + 16 * a + g + 4 * v, i = i0 + 16 * b + c;
+                if (j < nc && i < nr) BV[(i64)j * ldb + i] = acc[a][b][v];
+            }
+}
+
+// L[:, j] /= |L[:, j]|, also into the V part of BV (rows v0 ..)
+__global__ __launch_bounds__(256) void svd_normalise_kernel(double *L, double *BV, int nc, int ldl, int ldb, int v0)
+{
+    double *a = L + (i64)blockIdx.x * ldl, *b = BV + (i64)blockIdx.x * ldb;
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < nc; i += 256) acc += a[i] * a[i];
+    __shared__ double red[256];
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    const double n = sqrt(red[0]), inv = n > 0.0 ? 1.0 / n : 0.0;
+    for (int i = threadIdx.x; i < nc; i += 256) {
+        a[i] *= inv;
+        b[v0 + i] = a[i];
+    }
+    // (the padding row between the two parts, and the one below)
+    if (threadIdx.x == 0) {
+        for (int i = v0 + nc; i < ldb; ++i) b[i] = 0.0;
+    }
+}
+
+// ------------------------------------------------------------------ grid barrier
+// Every workgroup of a cooperative launch is resident, so all of them arrive.  The wait is bounded all the same;
+// false: some workgroup gave up, and everyone leaves.
+__device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *failed, unsigned &generation, unsigned nwg)
+{
+    __shared__ int ok;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence(); // what this workgroup wrote is visible before it arrives
+        generation += nwg;
+        __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int good = 0;
+        for (int spin = 0; spin < 4000000; ++spin) {
+            if ((int)(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - generation) >= 0) {
+                good = 1;
+                break;
+            }
+            if ((spin & 255) == 255 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        if (!good) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence(); // and what the others wrote before they arrived is read afresh
+        ok = good;
+    }
+    __syncthreads();
+    return ok != 0;
+}
+
+// ------------------------------------------------------------------ one pair of blocks
+// Rounds of eight disjoint pairs of the 16 columns.  Rounds 0 .. 7 pair every column of the first block with one of the
+// second; rounds 8 .. 14 the columns within the blocks, four pairs in each (round-robin of eight).
+__host__ __device__ constexpr int svd_in_block(int t, int q, bool second)
+{
+    return second ? (q == 0 ? 7 : (t + q) % 7) : (q == 0 ? t % 7 : (t - q + 7) % 7);
+}
+__host__ __device__ constexpr int svd_inner_lo(int t, int q)
+{
+    if (t < 8) return q;
+    const int a = svd_in_block(t - 8, q & 3, false), b = svd_in_block(t - 8, q & 3, true);
+    return (q >> 2) * 8 + (a < b ? a : b);
+}
+__host__ __device__ constexpr int svd_inner_hi(int t, int q)
+{
+    if (t < 8) return 8 + ((q + t) & 7);
+    const int a = svd_in_block(t - 8, q & 3, false), b = svd_in_block(t - 8, q & 3, true);
+    return (q >> 2) * 8 + (a < b ? b : a);
+}
+
+struct SvdShared {
+    double part[SVD_NT / 64][16][17];
+    double g[16][17];
+    f64x2_t cs[120];
+    int any[4];
+};
+
+// The rotation that takes gamma out of [[alpha, gamma], [gamma, beta]].  The angle needs no more than float precision (what
+// it leaves of gamma is 1e-7 of it); c is refined so that c^2 + s^2 = 1 to the last bit.
+__device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2)
+{
+    f64x2_t r = {1.0, 0.0};
+    if (!(gamma * gamma > tol2 * (alpha * beta))) return r;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const int e = -__builtin_amdgcn_frexp_exp(alpha + beta);
+    const float d = (float)__builtin_amdgcn_ldexp(beta - alpha, e), g = (float)__builtin_amdgcn_ldexp(2.0 * gamma, e);
+    const float z = d * __builtin_amdgcn_rcpf(g), az = fabsf(z);
+    const float ta = az > 1e18f ? 0.5f * __builtin_amdgcn_rcpf(az) : __builtin_amdgcn_rcpf(az + __builtin_amdgcn_sqrtf(1.f + z * z));
+    const double t = (double)copysignf(ta, z), w = 1.0 + t * t;
+    double c = (double)__builtin_amdgcn_rsqf((float)w);
+#else
+    const double z = (beta - alpha) / (2.0 * gamma), t = (z >= 0.0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z)), w = 1.0 + t * t;
+    double c = 1.0 / sqrt(w);
+#endif
+    c = c * (1.5 - 0.5 * w * c * c); // Newton: 23 -> 45 bits
+    c = c * (1.5 - 0.5 * w * c * c);
+    r[0] = c;
+    r[1] = c * t;
+    return r;
+}
+
+template <int T, int END>
+__device__ __forceinline__ void svd_rotate_row(const f64x2_t *cs, double (&x)[16])
+{
+    if constexpr (T < END) {
+        asm volatile("" ::: "memory"); // (the rotations are read round by round, not all kept in registers)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            constexpr int t = T;
+            const int lo = svd_inner_lo(t, q), hi = svd_inner_hi(t, q);
+            const f64x2_t r = cs[8 * t + q];
+            const double u = x[lo], v = x[hi];
+            x[lo] = r[0] * u - r[1] * v;
+            x[hi] = r[1] * u + r[0] * v;
+        }
+        svd_rotate_row<T + 1, END>(cs, x);
+    }
+}
+
+// Blocks p and q of M (columns 8 p .., 8 q ..): every column of one against every column of the other, with `within` also
+// the pairs inside the blocks.  Inner products over rows [0, nr), rotations applied to rows [0, rows).  Returns 0: nothing
+// to rotate, 1: rotated, 2: rotated, and some pair was farther from orthogonal than SVD_SMALL.
+constexpr double SVD_SMALL = 3e-8; // rotations this small leave their square: orthogonal to rounding level
+__device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr, int rows, int p, int q, bool within, double tol,
+                                              SvdShared &sh)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    constexpr int NW = SVD_NT / 64;
+    const auto column = [&](int k) { return (k < SVD_B ? SVD_B * p : SVD_B * q - SVD_B) + k; };
+    // Gram matrix, rows dealt to the wavefronts eight at a time, eight pieces in flight; the rows that this thread will
+    // rotate come along
+    double x[16];
+    const auto fetch = [&](int row) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int cc = column(k);
+            x[k] = cc < nc && row < rows ? M[(i64)cc * ld + row] : 0.0;
+        }
+    };
+    f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
+    const int col = column(c);
+    for (int r = 8 * wave; r < nr; r += 8 * NW * 8) {
+        f64x2_t y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = svd_frag(M, ld, col, nc, r + 8 * NW * u + 2 * g, nr);
+        if (r < 8 * NW) fetch(tid);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u][0], y[u][0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u][1], y[u][1], acc, 0, 0, 0);
+        }
+    }
+    if (8 * wave >= nr) fetch(tid); // (fewer rows than wavefronts)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sh.part[wave][g + 4 * v][c] = acc[v];
+    __syncthreads();
+    const double tol2 = tol * tol;
+    if (tid < 256) { // entry (i, j), and whether the pair needs a rotation
+        const int i = tid >> 4, j = tid & 15;
+        double y = 0.0, a = 0.0, b = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            y += sh.part[w][i][j];
+            a += sh.part[w][i][i];
+            b += sh.part[w][j][j];
+        }
+        sh.g[i][j] = y;
+        const bool pair = i > j && (within || (i >= 8 && j < 8));
+        const bool some = pair && y * y > tol2 * (a * b), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
+        const bool anyone = __any(some), anylarge = __any(large);
+        if (lane == 0) sh.any[wave] = anylarge ? 2 : anyone ? 1 : 0;
+    }
+    __syncthreads();
+    const int any = max(max(sh.any[0], sh.any[1]), max(sh.any[2], sh.any[3]));
+    if (!any) return 0;
+    if (wave == 0) {
+        // lane (a, b) owns the four entries where row pair a meets column pair b
+        const int a = lane >> 3, b = lane & 7, rounds = within ? 15 : 8;
+        for (int t = 0; t < rounds; ++t) {
+            const int i0 = svd_inner_lo(t, a), i1 = svd_inner_hi(t, a), j0 = svd_inner_lo(t, b), j1 = svd_inner_hi(t, b);
+            const double g00 = sh.g[i0][j0], g01 = sh.g[i0][j1], g10 = sh.g[i1][j0], g11 = sh.g[i1][j1];
+            const f64x2_t rb = svd_rotation(sh.g[j0][j0], sh.g[j1][j1], sh.g[j0][j1], tol2);
+            f64x2_t ra; // that of row pair a: lane (0, a) has it
+            ra[0] = __shfl(rb[0], a, 64);
+            ra[1] = __shfl(rb[1], a, 64);
+            if (a == 0) sh.cs[8 * t + b] = rb;
+            const double h00 = ra[0] * g00 - ra[1] * g10, h10 = ra[1] * g00 + ra[0] * g10;
+            const double h01 = ra[0] * g01 - ra[1] * g11, h11 = ra[1] * g01 + ra[0] * g11;
+            __builtin_amdgcn_wave_barrier(); // (all lanes have read before any writes)
+            sh.g[i0][j0] = rb[0] * h00 - rb[1] * h01;
+            sh.g[i0][j1] = rb[1] * h00 + rb[0] * h01;
+            sh.g[i1][j0] = rb[0] * h10 - rb[1] * h11;
+            sh.g[i1][j1] = rb[1] * h10 + rb[0] * h11;
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    for (int row = tid; row < rows; row += SVD_NT) {
+        if (row != tid) fetch(row);
+        svd_rotate_row<0, 8>(sh.cs, x);
+        if (within) svd_rotate_row<8, 15>(sh.cs, x);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int cc = column(k);
+            if (cc < nc) M[(i64)cc * ld + row] = x[k];
+        }
+    }
+    return any;
+}
+
+// Sweeps until one rotates nothing -- or, with `quick`, nothing but small angles -- or the cap.  Returns false when a barrier
+// gave up.
+__device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, unsigned *arrived,
+                                           unsigned &generation, unsigned *rot, bool quick, SvdCtrl *ctrl, SvdShared &sh,
+                                           int *ran)
+{
+    const int nbl = ((nc + SVD_B - 1) / SVD_B + 1) / 2 * 2, m1 = nbl - 1;
+    int sweep = 0;
+    for (; sweep < SVD_MAX_SWEEPS; ++sweep) {
+        for (int round = 0; round < m1; ++round) {
+            for (int k = blockIdx.x; k < nbl / 2; k += gridDim.x) {
+                int p = k == 0 ? m1 : (round + k) % m1, q = k == 0 ? round % m1 : (round - k + m1) % m1;
+                if (p > q) {
+                    const int t = p;
+                    p = q;
+                    q = t;
+                }
+                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, sh);
+                if (did > (quick ? 1 : 0) && threadIdx.x == 0)
+                    __hip_atomic_fetch_add(&rot[sweep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __syncthreads(); // (the LDS tables are used again)
+            }
+            if (!svd_grid_barrier(arrived, &ctrl->failed, generation, gridDim.x)) return false;
+        }
+        if (__hip_atomic_load(&rot[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+            ++sweep;
+            break;
+        }
+    }
+    *ran = sweep;
+    return true;
+}
+
+// G (overwritten) -> L with G + shift I = L L^T, sixteen columns at a time; then one-sided Jacobi on L.
+__global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel,
+                                                                   double tol)
+{
+    __shared__ SvdShared sh;
+    __shared__ double d[16][17];
+    __shared__ double shift_s;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+    const unsigned nwg = gridDim.x;
+    unsigned generation = 0;
+    // the shift: rounding level of the largest diagonal entry (read by every workgroup before anyone changes G)
+    {
+        double m = 0.0;
+        for (int i = tid; i < nc; i += SVD_NT) m = fmax(m, G[(i64)i * ld + i]);
+        double *red = &sh.part[0][0][0];
+        red[tid] = m;
+        __syncthreads();
+        if (tid == 0) {
+            for (int i = 1; i < SVD_NT; ++i) m = fmax(m, red[i]);
+            shift_s = m > 0.0 ? rel * m : 1.0;
         }
         __syncthreads();
     }
-    if (tid == 0) {
-        alpha = red[0][0];
-        beta = red[1][0];
-        gamma = red[2][0];
-        int doit = !(fabs(gamma) <= tol * sqrt(alpha * beta) || gamma == 0.0);
-        if (doit) {
-            const double zeta = (beta - alpha) / (2.0 * gamma);
-            const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-            const double c = 1.0 / sqrt(1.0 + t * t);
-            cs[0] = c;
-            cs[1] = c * t;
-            atomicAdd(&rot[sweep], 1u);
+    const double shift = shift_s;
+    if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
+    for (int p0 = 0; p0 < nc; p0 += 16) {
+        const int w = min(16, nc - p0);
+        // the diagonal block, by every workgroup
+        if (tid < 256) {
+            const int i = tid & 15, j = tid >> 4;
+            d[i][j] = i < w && j < w ? G[(i64)(p0 + j) * ld + p0 + i] + (i == j ? shift : 0.0) : (i == j ? 1.0 : 0.0);
         }
-        rotate = doit;
+        __syncthreads();
+        for (int k = 0; k < 16; ++k) {
+            const int i = tid & 15, j = tid >> 4;
+            const double piv = d[k][k], s = piv > 0.0 ? 1.0 / sqrt(piv) : 0.0;
+            double u = 0.0;
+            if (tid < 256 && i >= j && j > k) u = d[i][j] - (d[i][k] * s) * (d[j][k] * s);
+            double col = 0.0;
+            if (tid < 256 && j == k && i >= k) col = d[i][k] * s;
+            __syncthreads();
+            if (tid < 256 && i >= j && j > k) d[i][j] = u;
+            if (tid < 256 && j == k && i >= k) d[i][k] = col;
+            __syncthreads();
+        }
+        // rows below: X = G[rows, block] d^-T, one row per thread over all workgroups
+        for (i64 r = p0 + (i64)blockIdx.x * SVD_NT + tid; r < nc; r += (i64)nwg * SVD_NT) {
+            double x[16];
+            if (r < p0 + w) {
+                for (int j = 0; j < w; ++j) L[(i64)(p0 + j) * ld + r] = r - p0 >= j ? d[r - p0][j] : 0.0;
+            } else {
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    asm volatile("" ::: "memory"); // (row j of d is read now, not all of d kept in registers)
+                    double v = j < w ? G[(i64)(p0 + j) * ld + r] : 0.0;
+#pragma unroll
+                    for (int k = 0; k < j; ++k) v -= x[k] * d[j][k];
+                    const double piv = d[j][j];
+                    x[j] = piv > 0.0 ? v / piv : 0.0;
+                    if (j < w) L[(i64)(p0 + j) * ld + r] = x[j];
+                }
+            }
+        }
+        for (i64 e = (i64)blockIdx.x * SVD_NT + tid; e < (i64)p0 * w; e += (i64)nwg * SVD_NT)
+            L[(p0 + e / p0) * ld + e % p0] = 0.0; // above the diagonal block
+        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
+        // trailing blocks: G_ij -= X_i X_j^T, one 16 x 16 tile per wavefront
+        const int n0 = p0 + 16, nt = n0 < nc ? (nc - n0 + 15) / 16 : 0;
+        for (i64 t = (i64)blockIdx.x * (SVD_NT / 64) + wave; t < (i64)nt * nt; t += (i64)nwg * (SVD_NT / 64)) {
+            const int ti = (int)(t / nt), tj = (int)(t % nt);
+            if (tj > ti) continue;
+            const int gi = n0 + 16 * ti, gj = n0 + 16 * tj;
+            f64x4_t acc;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = gi + g + 4 * v, j = gj + c;
+                acc[v] = i < nc && j < nc ? G[(i64)j * ld + i] : 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int kc = p0 + 4 * k + g;
+                const double a = kc < nc && gi + c < nc ? L[(i64)kc * ld + gi + c] : 0.0;
+                const double b = kc < nc && gj + c < nc ? L[(i64)kc * ld + gj + c] : 0.0;
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a, b, acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = gi + g + 4 * v, j = gj + c;
+                if (i < nc && j < nc) G[(i64)j * ld + i] = acc[v];
+            }
+        }
+        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
     }
-    __syncthreads();
-    if (!rotate) return;
-    const double c = cs[0], s = cs[1];
-    for (int i = tid; i < nr; i += 256) {
-        const double va = ap[i], vb = aq[i];
-        ap[i] = c * va - s * vb;
-        aq[i] = s * va + c * vb;
-    }
-    double *qp = Qt + (i64)p * nc, *qq = Qt + (i64)q * nc;
-    for (int i = tid; i < nc; i += 256) {
-        const double va = qp[i], vb = qq[i];
-        qp[i] = c * va - s * vb;
-        qq[i] = s * va + c * vb;
+    int ran = 0;
+    (void)svd_sweeps(L, ld, nc, nc, nc, tol, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
+}
+
+// One-sided Jacobi on B with V carried along, when the check found pairs to rotate.
+__global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, SvdCtrl *ctrl, int nr, int nc, int rows, int ld, double tol)
+{
+    __shared__ SvdShared sh;
+    unsigned generation = 0;
+    int ran = 0;
+    bool ok = ctrl->failed == 0u;
+    if (ok && ctrl->violations != 0u)
+        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, &ctrl->arrived[1], generation, ctrl->rot[1], false, ctrl, sh, &ran);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        // (a check that found nothing counts as one clean sweep)
+        ctrl->sweeps = ok ? (ran > 0 ? ran : 1) : SVD_MAX_SWEEPS;
+        ctrl->last = ok ? (ran > 0 ? ctrl->rot[1][ran - 1] : 0u) : 1u;
     }
 }
 
-__global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double *sig, int nr)
+__global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double *sig, int nr, int ld)
 {
-    const double *a = At + (i64)blockIdx.x * nr;
+    const double *a = At + (i64)blockIdx.x * ld;
     double acc = 0.0;
     for (int i = threadIdx.x; i < nr; i += 256) acc += a[i] * a[i];
     __shared__ double red[256];
@@ -125,21 +560,14 @@ __global__ __launch_bounds__(256) void svd_rank_kernel(const double *sig, int *r
     rank[j] = k;
 }
 
-// column j of A (= sigma_j x left vector) and of Q (right vector) -> column rank[j] of the balanced factors
-__global__ __launch_bounds__(256) void svd_emit_kernel(const double *At, const double *Qt, const double *sig,
-                                                        const int *rank, float *U, float *V, float *sigma_out, int nr,
-                                                        int nc, int r, int transposed, const unsigned *rot, int *info)
+// column j of B (= sigma_j x left vector) and of V (right vector, from row v0 on) -> column rank[j] of the balanced factors
+__global__ __launch_bounds__(256) void svd_emit_kernel(const double *BV, const double *sig, const int *rank, float *U, float *V,
+                                                        float *sigma_out, int nr, int nc, int v0, int ld, int r,
+                                                        int transposed, const SvdCtrl *ctrl, int *info)
 {
     if (info && blockIdx.x == 0 && threadIdx.x == 0) {
-        // sweeps that ran (the first one that rotated nothing ends them) and rotations of the last one
-        int ran = SVD_MAX_SWEEPS;
-        for (int sw = 0; sw < SVD_MAX_SWEEPS; ++sw)
-            if (rot[sw] == 0u) {
-                ran = sw + 1;
-                break;
-            }
-        info[0] = nc > 1 ? ran : 0;
-        info[1] = nc > 1 ? (int)rot[ran - 1] : 0;
+        info[0] = nc > 1 ? (int)ctrl->sweeps : 0;
+        info[1] = nc > 1 ? (int)ctrl->last : 0;
     }
     const int j = blockIdx.x, k = rank[j];
     const double s = sig[j];
@@ -147,14 +575,14 @@ __global__ __launch_bounds__(256) void svd_emit_kernel(const double *At, const d
     if (k >= r) return;
     const double rs = sqrt(s), inv = s > 0.0 ? rs / s : 0.0;
     float *left = transposed ? V : U, *right = transposed ? U : V;
-    const double *a = At + (i64)j * nr, *qv = Qt + (i64)j * nc;
+    const double *a = BV + (i64)j * ld, *qv = a + v0;
     for (int i = threadIdx.x; i < nr; i += 256) left[(i64)i * r + k] = (float)(a[i] * inv);
     for (int i = threadIdx.x; i < nc; i += 256) right[(i64)i * r + k] = (float)(qv[i] * rs);
 }
 
 struct SvdPlan {
-    int nr, nc, npad, transposed;
-    size_t n_At, n_Qt, bytes;
+    int nr, nc, transposed, lda, ldn, ldb; // leading dimensions are even: columns are read two rows at a time
+    size_t n_At, n_G, n_BV, bytes;
 };
 static int plan_svd(const pf_svd_desc *d, SvdPlan *p)
 {
@@ -166,12 +594,25 @@ static int plan_svd(const pf_svd_desc *d, SvdPlan *p)
     p->transposed = d->m < d->n;
     p->nr = (int)mx;
     p->nc = (int)mn;
-    p->npad = (p->nc + 1) / 2 * 2;
-    p->n_At = (size_t)mn * mx;
-    p->n_Qt = (size_t)mn * mn;
-    p->bytes = align_up(p->n_At * 8) + align_up(p->n_Qt * 8) + align_up((size_t)mn * 8) + align_up((size_t)mn * 4) +
-               align_up(64 * 4);
+    p->lda = (p->nr + 1) / 2 * 2;
+    p->ldn = (p->nc + 1) / 2 * 2;
+    p->ldb = p->lda + p->ldn;
+    p->n_At = (size_t)p->nc * p->lda;
+    p->n_G = (size_t)p->nc * p->ldn;
+    p->n_BV = (size_t)p->nc * p->ldb;
+    p->bytes = align_up(p->n_At * 8) + 2 * align_up(p->n_G * 8) + align_up(p->n_BV * 8) + align_up((size_t)mn * 8) +
+               align_up((size_t)mn * 4) + align_up(sizeof(SvdCtrl));
     return PF_OK;
+}
+
+// A launch whose workgroups are all resident (they wait for one another)
+template <class... ARGS>
+static int launch_cooperative(hipStream_t s, const char *name, void (*kernel)(ARGS...), int blocks, ARGS... args)
+{
+    TimingScope ts(name, s);
+    void *list[] = {(void *)&args...};
+    const hipError_t e = hipLaunchCooperativeKernel((const void *)kernel, dim3(blocks), dim3(SVD_NT), list, 0, s);
+    return e == hipSuccess ? PF_OK : set_hip_error(e);
 }
 
 } // namespace pf
@@ -198,25 +639,35 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V, void *si
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    double *At = ws.take<double>(p.n_At), *Qt = ws.take<double>(p.n_Qt), *sig = ws.take<double>(p.nc);
+    double *At = ws.take<double>(p.n_At), *G = ws.take<double>(p.n_G), *L = ws.take<double>(p.n_G);
+    double *BV = ws.take<double>(p.n_BV), *sig = ws.take<double>(p.nc);
     int *rank = ws.take<int>(p.nc);
-    unsigned *rot = ws.take<unsigned>(64);
-    st = launch_zero_f32(s, (float *)rot, 64);
-    if (st != PF_OK) return st;
-    const i64 cells = (i64)p.nc * p.nr;
-    PF_LAUNCH(st, "svd_init", svd_init_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), s, (const float *)W, At,
-              Qt, (int)d->n, p.nr, p.nc, p.transposed);
-    if (p.nc > 1) {
-        for (int sweep = 0; sweep < SVD_MAX_SWEEPS && st == PF_OK; ++sweep)
-            for (int round = 0; round < p.npad - 1 && st == PF_OK; ++round)
-                PF_LAUNCH(st, "svd_jacobi_round", svd_round_kernel, dim3(p.npad / 2), dim3(256), s, At, Qt, p.nr, p.nc,
-                          p.npad, round, sweep, rot, svd_tolerance(p.nr));
-    }
-    PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(p.nc), dim3(256), s, (const double *)At, sig, p.nr);
-    PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((p.nc + 255) / 256), dim3(256), s, (const double *)sig, rank, p.nc);
-    PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(p.nc), dim3(256), s, (const double *)At, (const double *)Qt,
-              (const double *)sig, (const int *)rank, (float *)U, (float *)V, (float *)sigma, p.nr, p.nc, (int)d->r,
-              p.transposed, (const unsigned *)rot, (int *)info);
+    SvdCtrl *ctrl = ws.take<SvdCtrl>(1);
+    const int nc = p.nc, nr = p.nr;
+    const i64 cells = (i64)nc * p.lda;
+    PF_LAUNCH(st, "svd_init", svd_init_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), s, (const float *)W, At, ctrl,
+              (int)d->n, nr, nc, p.lda, p.transposed);
+    const dim3 gram((nc + 31) / 32, (nc + 31) / 32);
+    PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn);
+    // one workgroup per pair of blocks (at least eight for the factorization), all of them resident
+    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2;
+    const int nwg = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
+    if (st == PF_OK)
+        st = launch_cooperative(s, "svd_precondition", svd_precondition_kernel, nwg, G, L, ctrl, nc, p.ldn,
+                                16.0 * 2.220446049250313e-16 * (nc + 16), svd_tolerance_v(nc));
+    PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda);
+    PF_LAUNCH(st, "svd_apply", svd_apply_kernel, dim3((p.lda + 63) / 64, (nc + 63) / 64), dim3(256), s, (const double *)At,
+              (const double *)L, BV, p.lda, nc, p.lda, p.ldn, p.ldb);
+    PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn);
+    PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3((unsigned)(((i64)nc * nc + 255) / 256)), dim3(256), s, (const double *)G,
+              ctrl, nc, p.ldn, svd_tolerance(nr));
+    if (st == PF_OK)
+        st = launch_cooperative(s, "svd_finish", svd_finish_kernel, nwg, BV, ctrl, nr, nc, p.ldb, p.ldb, svd_tolerance(nr));
+    PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, nr, p.ldb);
+    PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 255) / 256), dim3(256), s, (const double *)sig, rank, nc);
+    PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(nc), dim3(256), s, (const double *)BV, (const double *)sig,
+              (const int *)rank, (float *)U, (float *)V, (float *)sigma, nr, nc, p.lda, p.ldb, (int)d->r, p.transposed,
+              (const SvdCtrl *)ctrl, (int *)info);
     return st;
 }
 
