@@ -104,7 +104,7 @@ void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ks
         p.ksplit = p.K > 0 ? (p.K + p.kper - 1) / p.kper : 1;
     }
     p.block0 = a.blocks;
-    a.blocks += p.tm * p.tn * p.ksplit * p.nb;
+    a.blocks += (p.tm * p.tn * p.ksplit * p.nb + 7) / 8 * 8;
 }
 
 template <typename CT>

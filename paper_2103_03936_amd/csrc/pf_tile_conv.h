@@ -44,6 +44,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_tables[];
     const int tid = threadIdx.x;
     const TileAt t = find_tile<CFG>(a);
+    if (!t.live) return;
     const TileProb &p = a.p[t.prob];
     const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v); };
     const int nch = (p.K + BK - 1) / BK; // (not TILE_WG)
@@ -68,8 +69,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
         tile_pieces<CT, CFG>(smem, tid, put);
     } else if (p.type == TILE_PACK) {
-        const int l = die_order(blockIdx.x, a.blocks) - p.block0;
-        pack_filters<CT>(p, l, tid);
+        pack_filters<CT>(p, t.index, tid);
     } else {
         const int img0 = t.ks * p.kper, img1 = min(p.pa.N, img0 + p.kper);
         const int pieces = (img1 - img0) * p.pa.HC, n = (pieces + BK / TileEl<CT>::V - 1) / (BK / TileEl<CT>::V);

@@ -20,6 +20,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_v
     __shared__ __attribute__((aligned(16))) unsigned char smem[bytes];
     const int tid = threadIdx.x;
     const TileAt t = find_tile<CFG>(a);
+    if (!t.live) return;
     const TileProb &p = a.p[t.prob];
     const int kbeg = t.ks * p.kper, kend = min(p.K, kbeg + p.kper), nch = (kend - kbeg + BK - 1) / BK;
     typedef typename TileEl<CT>::elem elem;

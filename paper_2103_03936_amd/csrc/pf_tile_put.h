@@ -6,14 +6,6 @@
 
 namespace pf {
 
-// Workgroups are dealt to the eight dies in turn: give every die a run of consecutive tiles, which share operands
-// in its L2.
-__device__ __forceinline__ int die_order(int b, int n)
-{
-    const int q = n >> 3, r = n & 7, x = b & 7;
-    return x * q + min(x, r) + (b >> 3);
-}
-
 // One 16-byte piece of the output: V neighbouring columns n .. n + V - 1 of row m (n a multiple of V).
 template <typename CT, int V>
 __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int m, int n, float *v)
@@ -142,20 +134,25 @@ __device__ __forceinline__ const TileArgs &tile_args(const TileArgs &a)
 }
 
 struct TileAt {
-    int prob, ks, zb, m0, n0;
+    int prob, index, ks, zb, m0, n0;
+    bool live; // (not one of the workgroups that fill up a problem)
 };
 template <class CFG>
 __device__ __forceinline__ TileAt find_tile(const TileArgs &a)
 {
     TileAt t;
-    const int b = die_order(blockIdx.x, a.blocks);
+    // Workgroups are dealt to the eight dies in turn: every die gets a run of a problem's consecutive tiles, which share
+    // operands in its L2, and its share of every problem (a problem's workgroups are padded to a multiple of eight).
+    const int b = blockIdx.x;
     t.prob = 0;
 #pragma unroll
     for (int i = 1; i < TILE_MAX_PROBS; ++i)
         if (i < a.n && b >= a.p[i].block0) t.prob = i;
     const TileProb &p = a.p[t.prob];
-    const int l = b - p.block0, per = p.tm * p.tn;
-    const int zk = l / per, q = l - zk * per, tm = q / p.tn;
+    const int n = p.tm * p.tn * p.ksplit * p.nb, w = b - p.block0;
+    t.index = (w & 7) * ((n + 7) >> 3) + (w >> 3);
+    t.live = t.index < n;
+    const int per = p.tm * p.tn, zk = t.index / per, q = t.index - zk * per, tm = q / p.tn;
     t.zb = zk / p.ksplit;
     t.ks = zk - t.zb * p.ksplit;
     t.m0 = tm * CFG::BM;
