@@ -186,18 +186,21 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     if (g.N < 1 || kk > TILE_MAX_TAPS || g.C < 1 || (i64)g.C * kk < V || g.r < V || g.Cout < 1) return;
     const i64 planes = (i64)g.N * HW;
     if (planes * g.r < V || planes * g.Cout < V || (i64)g.N * g.C * g.H * g.W < V) return;
+    // (32-bit byte offsets, a row of channels past the end included)
+    const i64 lim = (1LL << 31) / (16 / V) - (1 << 20), over = 400LL * (HW > g.H * g.W ? HW : g.H * g.W);
+    if (planes * g.r + over > lim || planes * g.Cout + over > lim || (i64)g.N * g.C * g.H * g.W + over > lim) return;
     const int HC = (HW + V - 1) / V, HCin = (g.H * g.W + V - 1) / V;
     if ((i64)g.N * HC * V > big || (i64)g.N * HCin * V > big) return;
     const bool same = g.s == 1 && g.Ho == g.H && g.Wo == g.W;
     // gather: the k x k stage reads X by element offsets; backward needs one grid of Ho x Wo pixels per phase
     if (!same && !(g.s > 1 && (g.H + g.s - 1) / g.s <= g.Ho && (g.W + g.s - 1) / g.s <= g.Wo && g.s <= 2)) return;
     p.gather = !same;
-    const int tab = 2 * ((kk * HC + 15) / 16 * 16 + (p.gather ? 4 * V * HC : 0));
-    if (tab > 20 * 1024) return;
+    const int tab = 2 * (4096 + (kk * HC + 15) / 16 * 16 + (p.gather ? 4 * V * HC : 0));
+    if (tab > 28 * 1024) return;
     p.tiles = true;
     const i64 npx = (i64)g.N * HC * V, npin = (i64)g.N * HCin * V;
-    p.sh_T = g.r <= 32 ? TS_32x128 : TS_64;
-    p.sh_Y = g.Cout <= 32 ? TS_32x128 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
+    p.sh_T = g.r <= 32 ? TS_32x64 : TS_64;
+    p.sh_Y = g.Cout <= 32 ? TS_32x64 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
     p.sh_dT = p.sh_T;
     p.sh_g = TS_64;
     (void)npin;

@@ -86,21 +86,27 @@ __device__ __forceinline__ uint4 piece_shift(uint4 r, int s)
     return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
 }
 
-__device__ __forceinline__ int bit_all(uint32_t m, int b) { return ((int)(m << (31 - b))) >> 31; } // 0 or -1
-
-// keep element e where bit e of m is set
+// Masks of a piece's elements are bytes (bit e: keep element e); a table in LDS holds the piece-wide mask of every byte.
 template <int V>
-__device__ __forceinline__ uint4 piece_mask(uint4 r, uint32_t m)
-{
-    if (V == 4) {
-        return make_uint4(r.x & bit_all(m, 0), r.y & bit_all(m, 1), r.z & bit_all(m, 2), r.w & bit_all(m, 3));
-    } else {
-        const auto two = [&](int b) {
-            return ((uint32_t)bit_all(m, b) & 0xffffu) | ((uint32_t)bit_all(m, b + 1) & 0xffff0000u);
-        };
-        return make_uint4(r.x & two(0), r.y & two(2), r.z & two(4), r.w & two(6));
+struct MaskTable {
+    static constexpr int N = 1 << V, BYTES = 16 * N;
+    static __device__ __forceinline__ void build(unsigned char *tab, int tid)
+    {
+        if (tid < N) {
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                w[e] = V == 4 ? (tid >> e & 1 ? 0xffffffffu : 0u)
+                              : (tid >> (2 * e) & 1 ? 0xffffu : 0u) | (tid >> (2 * e + 1) & 1 ? 0xffff0000u : 0u);
+            ((uint4 *)tab)[tid] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
     }
-}
+    static __device__ __forceinline__ uint4 apply(const unsigned char *tab, uint32_t m, uint4 r)
+    {
+        const uint4 k = ((const uint4 *)tab)[m];
+        return make_uint4(r.x & k.x, r.y & k.y, r.z & k.z, r.w & k.w);
+    }
+};
 
 template <typename CT>
 __device__ __forceinline__ void piece_floats(uint4 r, float *f)
@@ -128,8 +134,8 @@ __device__ __forceinline__ uint4 floats_piece(const float *f)
 
 // ------------------------------------------------------------------ operand loaders
 // A loader owns CH pieces of a tile per thread.  load() issues the loads of the next chunk, store() writes the oldest
-// outstanding chunk to LDS; both walk the same sequence of chunks.  XF floats travel with a chunk's pieces (row
-// scales).  SUM (weight gradients) adds up what passes.
+// outstanding chunk to LDS; both walk the same sequence of chunks.  XF words travel with a chunk's pieces (row
+// scales, taps).  SUM (weight gradients) adds up what passes.
 
 // Matrix stored [rows][K] with k contiguous, leading dimension ld
 template <typename CT, int ROWS, bool SUM = false>
@@ -155,14 +161,14 @@ struct LoadKC {
         }
         kl = ks = kbeg;
     }
-    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
     {
         const int k = min(kl + kc, K - V);
 #pragma unroll
         for (int i = 0; i < CH; ++i) r[i] = ldg16(rp[i] + k);
         kl += BK;
     }
-    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
         const bool tail = ks + BK > K;
         const int s = ks + kc - min(ks + kc, K - V);
@@ -224,17 +230,17 @@ struct LoadMC {
             for (int e = 0; e < V; ++e) sum[SUM ? e : 0] = 0.f;
         }
     }
-    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
     {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int k = min(kl + krow + i * KSTEP, K - 1);
             r[i] = ldg16(p + (i64)k * ld);
-            if (SCALE) x[SCALE ? i : 0] = kscale ? kscale[k] : 1.f;
+            if (SCALE) x[SCALE ? i : 0] = kscale ? __float_as_int(kscale[k]) : 0;
         }
         kl += BK;
     }
-    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
         const bool tail = ks + BK > K;
 #pragma unroll
@@ -244,7 +250,7 @@ struct LoadMC {
             if (shift) v = piece_shift<sizeof(elem)>(v, shift);
             if (tail && k >= K) v = make_uint4(0, 0, 0, 0);
             if (SCALE && kscale) {
-                const float s = x[SCALE ? i : 0];
+                const float s = __int_as_float(x[SCALE ? i : 0]);
                 float f[8];
                 piece_floats<CT>(v, f);
 #pragma unroll
@@ -307,6 +313,14 @@ __device__ __forceinline__ uint32_t pix_mask(const PixView &g, int pos, int tap)
     return m;
 }
 
+// A 16-byte piece at element `off` of a tensor, off pulled back inside [0, last] (what is missing is shifted in later).
+// 32-bit byte offsets from a uniform base: the address of a load is one register.
+template <typename elem>
+__device__ __forceinline__ uint4 ldg16_at(const elem *p, int off)
+{
+    return ldg16((const char *)p + (uint32_t)(off * (int)sizeof(elem)));
+}
+
 // B operand (k = (channel, tap), n = pixel): one tile row per k, pixels contiguous.  Tables in LDS: offset of every tap,
 // mask of every (tap, piece of the tile).
 template <typename CT, int ROWS, bool GATHER>
@@ -314,21 +328,25 @@ struct LoadPixMC {
     typedef typename TileEl<CT>::elem elem;
     static constexpr bool KC = false;
     static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V,
-                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = 1;
-    static constexpr int TAB = 4 * TILE_MAX_TAPS + TILE_MAX_TAPS * CPR; // bytes of tables
+                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = CH;
+    static constexpr int TAPS = (TILE_MAX_TAPS + 3) / 4 * 16; // bytes of the offset table
+    static constexpr int TAB = MaskTable<V>::BYTES + TAPS + TILE_MAX_TAPS * CPR;
     const elem *p;
-    const int *toff;
-    const unsigned char *tmask;
-    i64 plane0, last; // element of channel 0 at the piece's position; last element address a piece may start at
+    const unsigned char *tab;
+    int pos0, last; // element of channel 0 at the piece's position; last element a piece may start at
     int HW, ntap, K, mc, col, krow, kl, ks, inc_c, inc_t;
     bool masked;
-    int lc[CH], lt[CH], sc[CH], st[CH]; // (channel, tap) of the rows to load / to store next
+    int lc[CH], lt[CH]; // (first element of the channel, tap) of the rows to load next
     int pixoff[GATHER ? V : 1];
 
+    __device__ __forceinline__ int toff(int t) const { return ((const int *)(tab + MaskTable<V>::BYTES))[t]; }
+    __device__ __forceinline__ uint32_t tmask(int t) const { return tab[MaskTable<V>::BYTES + TAPS + t * CPR + col]; }
+
     // tab: TAB bytes of LDS; ends with a barrier
-    __device__ __forceinline__ void init(const PixView &g, int n0, int kbeg, int tid, unsigned char *tab)
+    __device__ __forceinline__ void init(const PixView &g, int n0, int kbeg, int tid, unsigned char *tab_)
     {
         p = (const elem *)g.p;
+        tab = tab_;
         HW = g.H * g.W;
         ntap = g.ntap;
         K = g.CH * g.ntap;
@@ -336,15 +354,16 @@ struct LoadPixMC {
         mc = col * V;
         krow = tid / CPR;
         masked = g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER;
-        int *to = (int *)tab;
-        unsigned char *tm = tab + 4 * TILE_MAX_TAPS;
-        if (tid < g.ntap) to[tid] = g.dy[tid] * g.W + g.dx[tid];
-        for (int j = tid; j < g.ntap * CPR; j += TILE_THREADS) {
-            const int t = j / CPR, c = n0 / V + j % CPR;
-            tm[j] = (unsigned char)pix_mask<V>(g, c % g.HC * V, t);
+        if (tid < g.ntap) ((int *)(tab_ + MaskTable<V>::BYTES))[tid] = g.dy[tid] * g.W + g.dx[tid];
+        if (masked) {
+            MaskTable<V>::build(tab_, tid);
+            for (int j = tid; j < g.ntap * CPR; j += TILE_THREADS) {
+                const int t = j / CPR, c = n0 / V + j % CPR;
+                tab_[MaskTable<V>::BYTES + TAPS + j] = (unsigned char)pix_mask<V>(g, c % g.HC * V, t);
+            }
         }
         const int cidx = n0 / V + col, img = min(cidx / g.HC, g.N - 1), pos = cidx % g.HC * V;
-        plane0 = (i64)img * g.CH * HW;
+        pos0 = img * g.CH * HW;
         if (GATHER) {
             int y = pos / g.gW, x = pos - y * g.gW;
 #pragma unroll
@@ -353,65 +372,61 @@ struct LoadPixMC {
                 if (++x == g.gW) x = 0, ++y;
             }
         } else {
-            plane0 += pos;
+            pos0 += pos;
         }
-        last = g.total - V;
+        last = (int)g.total - V;
         inc_c = BK / g.ntap;
         inc_t = BK - inc_c * g.ntap;
+        inc_c *= HW;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const int k = kbeg + krow + i * KSTEP;
-            lc[i] = sc[i] = k / g.ntap;
-            lt[i] = st[i] = k - lc[i] * g.ntap;
+            const int k = kbeg + krow + i * KSTEP, c = k / g.ntap;
+            lc[i] = c * HW;
+            lt[i] = k - c * g.ntap;
         }
         kl = ks = kbeg;
-        toff = to;
-        tmask = tm;
         __syncthreads();
     }
-    __device__ __forceinline__ void step(int &c, int &t)
-    {
-        c += inc_c;
-        t += inc_t;
-        if (t >= ntap) t -= ntap, ++c;
-    }
-    __device__ __forceinline__ i64 addr(int c, int t) const { return plane0 + (i64)c * HW + toff[t]; }
-    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
     {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
+            const int off = pos0 + lc[i] + toff(lt[i]);
             if (GATHER) {
-                const bool in = kl + krow + i * KSTEP < K;
-                const elem *q = p + (in ? addr(lc[i], lt[i]) : plane0);
-                const uint32_t m = in ? tmask[lt[i] * CPR + col] : 0u;
+                const uint32_t m = kl + krow + i * KSTEP < K ? tmask(lt[i]) : 0u;
                 elem v[V];
 #pragma unroll
-                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? q[pixoff[GATHER ? e : 0]] : elem(0);
+                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? p[off + pixoff[GATHER ? e : 0]] : elem(0);
                 r[i] = *(const uint4 *)v;
+                x[i] = 0;
             } else {
-                i64 a = addr(lc[i], lt[i]);
-                a = a < 0 ? 0 : a > last ? last : a;
-                r[i] = ldg16(p + a);
+                const int a = min(max(off, 0), last);
+                r[i] = ldg16_at(p, a);
+                // the tap, and how far the piece was pulled back (rows past K: anything, they become zero)
+                x[i] = (min(max(off - a, -V), V) + V) << 8 | lt[i];
             }
-            step(lc[i], lt[i]);
+            lc[i] += inc_c;
+            lt[i] += inc_t;
+            if (lt[i] >= ntap) {
+                lt[i] -= ntap;
+                lc[i] += HW;
+            }
         }
         kl += BK;
     }
-    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
         const bool tail = ks + BK > K;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
             if (!GATHER) {
-                const i64 a = addr(sc[i], st[i]);
-                if (a < 0) v = piece_shift<sizeof(elem)>(v, (int)a);
-                else if (a > last) v = piece_shift<sizeof(elem)>(v, (int)(a - last < V ? a - last : V));
-                if (masked) v = piece_mask<V>(v, tmask[st[i] * CPR + col]);
+                const int s = (x[i] >> 8) - V;
+                if (s != 0) v = piece_shift<sizeof(elem)>(v, s);
+                if (masked) v = MaskTable<V>::apply(tab, tmask(x[i] & 255), v);
                 if (tail && ks + krow + i * KSTEP >= K) v = make_uint4(0, 0, 0, 0);
             }
             *(uint4 *)&lds[(krow + i * KSTEP) * PITCH + mc] = v;
-            step(sc[i], st[i]);
         }
         ks += BK;
     }
@@ -426,18 +441,16 @@ struct LoadPixKC {
     static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V,
                          CH = ROWS * CPR / TILE_THREADS, LDS = ROWS * PITCH, XF = 1;
     const elem *p;
-    const unsigned char *tmask;
+    const unsigned char *lut, *tmask;
     const int *pix;
-    i64 image, last;
-    int HC, N, img1, kc, row, limg, lpc, simg, spc;
+    int image, last, HC, N, img1, kc, row, limg, lpc, simg, spc;
     bool masked;
-    i64 ro[CH];
-    int tap[CH];
+    int ro[CH], tap[CH]; // offset of the row's channel and tap; first mask of the tap
     float sum[SUM ? CH : 1];
 
     static __host__ __device__ int table_bytes(const PixView &g)
     {
-        return (g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER ? (g.ntap * g.HC + 15) / 16 * 16 : 0) +
+        return (g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER ? MaskTable<V>::BYTES + (g.ntap * g.HC + 15) / 16 * 16 : 0) +
                (GATHER ? 4 * V * g.HC : 0);
     }
     // tab: table_bytes() of LDS; the caller's barrier follows
@@ -451,22 +464,25 @@ struct LoadPixKC {
         row = tid / CPR;
         masked = g.ntap > 1 || g.gH * g.gW % V != 0 || GATHER;
         const int HW = g.H * g.W;
-        image = (i64)g.CH * HW;
-        last = g.total - V;
-        tmask = tab;
-        pix = (const int *)(tab + (g.ntap * g.HC + 15) / 16 * 16);
-        if (masked)
+        image = g.CH * HW;
+        last = (int)g.total - V;
+        lut = tab;
+        tmask = tab + MaskTable<V>::BYTES;
+        pix = (const int *)(tmask + (g.ntap * g.HC + 15) / 16 * 16);
+        if (masked) {
+            MaskTable<V>::build(tab, tid);
             for (int j = tid; j < g.ntap * HC; j += TILE_THREADS)
-                tab[j] = (unsigned char)pix_mask<V>(g, j % HC * V, j / HC);
+                tab[MaskTable<V>::BYTES + j] = (unsigned char)pix_mask<V>(g, j % HC * V, j / HC);
+        }
         if (GATHER)
             for (int j = tid; j < HC * V; j += TILE_THREADS)
                 ((int *)pix)[j] = (j / g.gW) * g.s * g.W + (j % g.gW) * g.s;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int r = min(row0 + row + i * (TILE_THREADS / CPR), g.CH * g.ntap - 1);
-            const int c = r / g.ntap;
-            tap[i] = r - c * g.ntap;
-            ro[i] = (i64)c * HW + g.dy[tap[i]] * g.W + g.dx[tap[i]];
+            const int c = r / g.ntap, t = r - c * g.ntap;
+            tap[i] = t * HC;
+            ro[i] = c * HW + g.dy[t] * g.W + g.dx[t];
             if (SUM) sum[i] = 0.f;
         }
         limg = img0;
@@ -479,38 +495,34 @@ struct LoadPixKC {
     {
         while (pc >= HC) pc -= HC, ++img;
     }
-    __device__ __forceinline__ void load(uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
     {
-        const i64 b = (i64)min(limg, N - 1) * image;
+        const int b = min(limg, N - 1) * image + (GATHER ? 0 : lpc * V);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             if (GATHER) {
-                const uint32_t m = limg < img1 ? tmask[tap[i] * HC + lpc] : 0u;
-                const elem *q = p + b + ro[i];
+                const uint32_t m = limg < img1 ? tmask[tap[i] + lpc] : 0u;
                 elem v[V];
 #pragma unroll
-                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? q[pix[lpc * V + e]] : elem(0);
+                for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? p[b + ro[i] + pix[lpc * V + e]] : elem(0);
                 r[i] = *(const uint4 *)v;
             } else {
-                i64 a = b + ro[i] + lpc * V;
-                a = a < 0 ? 0 : a > last ? last : a;
-                r[i] = ldg16(p + a);
+                r[i] = ldg16_at(p, min(max(b + ro[i], 0), last));
             }
         }
         lpc += CPR;
         wrap(limg, lpc);
     }
-    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], float (&x)[XF])
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
-        const i64 b = (i64)min(simg, N - 1) * image;
+        const int b = min(simg, N - 1) * image + spc * V;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
             if (!GATHER) {
-                const i64 a = b + ro[i] + spc * V;
-                if (a < 0) v = piece_shift<sizeof(elem)>(v, (int)a);
-                else if (a > last) v = piece_shift<sizeof(elem)>(v, (int)(a - last < V ? a - last : V));
-                if (masked) v = piece_mask<V>(v, tmask[tap[i] * HC + spc]);
+                const int off = b + ro[i], s = off - min(max(off, 0), last);
+                if (s != 0) v = piece_shift<sizeof(elem)>(v, min(max(s, -V), V));
+                if (masked) v = MaskTable<V>::apply(lut, tmask[tap[i] + spc], v);
                 if (simg >= img1) v = make_uint4(0, 0, 0, 0);
             }
             *(uint4 *)&lds[(row + i * (TILE_THREADS / CPR)) * PITCH + kc] = v;
@@ -579,7 +591,7 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, int nch, unsigned c
     const int lane = tid & 63, wave = tid >> 6;
     const int wk = wave / (CFG::WM * CFG::WN), wm = wave / CFG::WN % CFG::WM, wn = wave % CFG::WN;
     uint4 ra[NS][LA::CH], rb[NS][LB::CH];
-    float xa[NS][LA::XF], xb[NS][LB::XF];
+    int xa[NS][LA::XF], xb[NS][LB::XF];
     f32x16_t acc[MI][NI];
 #pragma unroll
     for (int i = 0; i < MI; ++i)

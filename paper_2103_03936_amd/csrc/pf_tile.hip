@@ -7,7 +7,7 @@ namespace pf {
 struct ShapeInfo {
     int bm, bn;
 };
-static const ShapeInfo SHAPES[TS_COUNT] = {{32, 32}, {64, 64}, {128, 64}, {128, 128}, {32, 128}};
+static const ShapeInfo SHAPES[TS_COUNT] = {{32, 32}, {64, 64}, {128, 64}, {128, 128}, {32, 64}};
 
 TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc)
 {

@@ -117,7 +117,7 @@ template <typename CT>
 int launch_conv_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a)
 {
     switch (shape) {
-    case TS_32x128: return launch_conv<CT, TileCfg<32, 128, 1, 4, 4>>(s, name, a);
+    case TS_32x64: return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>>(s, name, a);
     case TS_64: return launch_conv<CT, TileCfg<64, 64, 2, 2, 4>>(s, name, a);
     case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>>(s, name, a);
     default: return PF_ERR_UNSUPPORTED;

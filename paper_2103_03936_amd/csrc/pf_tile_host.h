@@ -54,7 +54,7 @@ struct TileArgs {
 };
 
 // Tile shapes a launch can use.
-enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x128, TS_COUNT };
+enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x64, TS_COUNT };
 
 // One product: add it to a launch.  ksplit <= 0 asks for the split that plan_tiles chose.
 TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc);
