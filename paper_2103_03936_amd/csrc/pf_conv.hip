@@ -156,7 +156,7 @@ struct ConvPlan {
     size_t n_w1b, n_w2b;     // packed weight elements, backward direction
     bool tiles;              // the tiled products of pf_tile.h take the shape
     bool gather;             // ... and read the k x k stage's input with stride
-    TileShape sh_T, sh_Y, sh_dT, sh_g; // ... the tile shapes of their launches
+    TileShape sh_T, sh_Y, sh_dT, sh_g, sh_w; // ... the tile shapes of their launches
     int ks_tU, ks_tV;        // ... image splits of the two filter gradients
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     size_t saved_bytes;      // the backward direction's packed weights when the forward call saves them
@@ -204,15 +204,19 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.sh_dT = p.sh_T;
     p.sh_g = TS_64;
     (void)npin;
-    // both filter gradients in one launch: about two workgroups per compute unit, each at least two chunks long
-    const i64 tU = ((g.r + 63) / 64) * (((i64)g.C * kk + 63) / 64), tV = ((g.Cout + 63) / 64) * ((g.r + 63) / 64);
+    p.sh_w = g.r <= 32 ? TS_32x128 : TS_64;
+    // both filter gradients in one launch: about two workgroups per compute unit, each at least four chunks long.  With at most 32
+    // filters the gradients of both stages have the rank as their rows (dVp is formed transposed).
+    const bool low = p.sh_w == TS_32x128;
+    const i64 tU = low ? ((i64)g.C * kk + 127) / 128 : ((g.r + 63) / 64) * (((i64)g.C * kk + 63) / 64);
+    const i64 tV = low ? (g.Cout + 127) / 128 : ((g.Cout + 63) / 64) * ((g.r + 63) / 64);
     const i64 want = 512;
     const auto split = [&](i64 tiles, i64 floats) {
         i64 ks = (want + tiles - 1) / tiles;
         const i64 chunks = (i64)g.N * HC * V / (dtype == PF_BF16 ? 64 : 32);
-        if (ks > chunks / 2) ks = chunks / 2;
+        if (ks > chunks / 4) ks = chunks / 4;
         if (ks > g.N) ks = g.N;
-        if (ks > 32) ks = 32;
+        if (ks > 64) ks = 64;
         while (ks > 1 && ks * floats > (4 << 20)) --ks;
         if (ks < 1) ks = 1;
         const i64 per = (g.N + ks - 1) / ks;
@@ -221,7 +225,7 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.ks_tU = split(tU, (i64)g.r * g.C * kk);
     p.ks_tV = split(tV, (i64)g.Cout * (g.r + 1));
     p.n_pack = kk > 1 ? (size_t)g.r * g.C * kk : 0;
-    p.n_part_t = (size_t)p.ks_tU * g.r * g.C * kk + (size_t)p.ks_tV * ((size_t)g.Cout * g.r + g.Cout) + 192;
+    p.n_part_t = (size_t)p.ks_tU * g.r * g.C * kk + (size_t)p.ks_tV * ((size_t)g.Cout * g.r + g.Cout) + 320;
 }
 
 static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
@@ -422,7 +426,7 @@ static int conv_T_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const 
     q.pb = v;
     out_planes(q.o, v, g.r);
     tile_add(a, p.sh_T, dt, q, 1);
-    return launch_tiles_conv(s, "conv_T=Uk*X", dt, p.sh_T, a);
+    return launch_tiles_conv(s, "conv_T=Uk*X", dt, p.sh_T, TS_64, a);
 }
 
 // Two launches: T = Uk * X (an implicit product over (channel, tap), the order in which the filters lie in memory), then
@@ -445,7 +449,7 @@ static int conv_fwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
     q.o.add = ep.add;
     q.o.relu = ep.relu;
     tile_add(a, p.sh_Y, dt, q, 1);
-    return launch_tiles_conv(s, "conv_Y=Vp*T", dt, p.sh_Y, a);
+    return launch_tiles_conv(s, "conv_Y=Vp*T", dt, p.sh_Y, TS_64, a);
 }
 
 // Three launches: dT = (scale Vp)^T dZ, with the filters re-ordered for the next launch in extra workgroups; then dX, dUk,
@@ -514,33 +518,40 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
             tile_add(b, p.sh_g, dt, q, 1);
         }
     }
-    st = launch_tiles_conv(s, "conv_dT=Vpt*dY", dt, p.sh_dT, a);
+    st = launch_tiles_conv(s, "conv_dT=Vpt*dY", dt, p.sh_dT, TS_64, a);
     if (st != PF_OK) return st;
     SplitSumArgs ss = {};
+    // [m][n] over the pixels (`transposed`: the result is wanted as [n][m]); sums: those of pa's rows, transposed: of pb's
     const auto grad = [&](const PixView &pa, const PixView &pb, int type, int m, int n, float *dst, int ks, float *sums,
-                          const float *rscale) {
+                          const float *rscale, bool transposed) {
         TileProb q = tile_prob(type, m, n, 0, nullptr, 0, nullptr, 0, part, n);
         q.pa = pa;
         q.pb = pb;
         q.o.f32 = 1;
         q.o.split_stride = (i64)m * n;
+        const int nsum = transposed ? n : m;
         float *ps = part + (i64)ks * m * n;
+        ps += (64 - ((uintptr_t)ps / 4) % 64) % 64;
         part = ps;
         if (sums) {
             q.o.sums = ps;
-            q.o.sums_stride = m;
-            part += (i64)ks * m;
+            q.o.sums_stride = nsum;
+            part += (i64)ks * nsum;
         }
         part += (64 - ((uintptr_t)part / 4) % 64) % 64;
-        tile_add(b, p.sh_g, dt, q, ks);
+        tile_add(b, p.sh_w, dt, q, ks);
         const int got = b.p[b.n - 1].ksplit;
-        split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, (i64)m * n, (i64)m * n, got, accumulate, rscale, n, 0});
-        if (sums) split_sum_add(ss, SplitSum{ps, sums, m, m, got, accumulate, nullptr, 0, 0});
+        split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, (i64)m * n, (i64)m * n, got, accumulate, rscale,
+                                   transposed ? m : n, 0, m, transposed ? n : 0});
+        if (sums) split_sum_add(ss, SplitSum{ps, sums, nsum, nsum, got, accumulate, nullptr, 0, 0});
     };
     if (dUk)
-        grad(vdT, conv_input_view(g, dt, X), p.gather ? TILE_WGG : TILE_WG, g.r, g.C * kk, dUk, p.ks_tU, nullptr, nullptr);
-    if (dVp || ep.dshift) grad(vdY, vT, TILE_WG, g.Cout, g.r, dVp, p.ks_tV, ep.dshift, ep.scale);
-    st = launch_tiles_conv(s, "conv_dX,dUk,dVp", dt, p.sh_g, b);
+        grad(vdT, conv_input_view(g, dt, X), p.gather ? TILE_WGG : TILE_WG, g.r, g.C * kk, dUk, p.ks_tU, nullptr, nullptr, false);
+    if ((dVp || ep.dshift) && p.sh_w == TS_32x128)
+        grad(vT, vdY, TILE_WGT, g.r, g.Cout, dVp, p.ks_tV, ep.dshift, ep.scale, true);
+    else if (dVp || ep.dshift)
+        grad(vdY, vT, TILE_WG, g.Cout, g.r, dVp, p.ks_tV, ep.dshift, ep.scale, false);
+    st = launch_tiles_conv(s, "conv_dX,dUk,dVp", dt, p.sh_g, p.sh_w, b);
     if (st != PF_OK) return st;
     return launch_split_sums(s, ss);
 }

@@ -7,7 +7,7 @@ namespace pf {
 struct ShapeInfo {
     int bm, bn;
 };
-static const ShapeInfo SHAPES[TS_COUNT] = {{32, 32}, {64, 64}, {128, 64}, {128, 128}, {32, 64}};
+static const ShapeInfo SHAPES[TS_COUNT] = {{32, 32}, {64, 64}, {128, 64}, {128, 128}, {32, 64}, {32, 128}};
 
 TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc)
 {
@@ -91,7 +91,7 @@ void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ks
     p.tm = (p.M + SHAPES[shape].bm - 1) / SHAPES[shape].bm;
     p.tn = (p.N + SHAPES[shape].bn - 1) / SHAPES[shape].bn;
     p.ksplit = ksplit < 1 ? 1 : ksplit;
-    if (p.type == TILE_WG || p.type == TILE_WGG) {
+    if (p.type == TILE_WG || p.type == TILE_WGG || p.type == TILE_WGT) {
         p.kper = (p.pa.N + p.ksplit - 1) / p.ksplit;
         p.ksplit = (p.pa.N + p.kper - 1) / p.kper;
     } else if (p.type == TILE_PACK) {
@@ -110,7 +110,7 @@ void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ks
 template <typename CT>
 int launch_linear_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a);
 template <typename CT>
-int launch_conv_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a);
+int launch_conv_t(hipStream_t s, const char *name, TileShape shape, TileShape wg, const TileArgs &a);
 
 int launch_tiles_linear(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a)
 {
@@ -118,60 +118,69 @@ int launch_tiles_linear(hipStream_t s, const char *name, int dtype, TileShape sh
     return dtype == PF_F32 ? launch_linear_t<float>(s, name, shape, a) : launch_linear_t<bf16_t>(s, name, shape, a);
 }
 
-int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a)
+int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, TileShape wg, const TileArgs &a)
 {
     if (a.blocks <= 0) return PF_OK;
-    return dtype == PF_F32 ? launch_conv_t<float>(s, name, shape, a) : launch_conv_t<bf16_t>(s, name, shape, a);
+    return dtype == PF_F32 ? launch_conv_t<float>(s, name, shape, wg, a) : launch_conv_t<bf16_t>(s, name, shape, wg, a);
 }
 
 // ------------------------------------------------------------------ sums over splits
-// Four outputs per thread where the arrays allow 16-byte accesses, up to eight splits in flight, added in order.
+// 64 groups of four neighbouring outputs per workgroup; the splits are dealt to four threads per group, eight in flight
+// each, and the four sums are added in a fixed order.
 template <bool VEC>
-__device__ __forceinline__ void split_sum(const SplitSum &q, i64 i)
+__device__ __forceinline__ f32x4_t split_share(const SplitSum &q, i64 i, int part)
 {
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    const float *p = q.src + i;
-    for (int s = 0; s < q.splits; s += 8) {
+    const int per = (q.splits + 3) / 4, end = min(q.splits, (part + 1) * per);
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    for (int s = part * per; s < end; s += 8) {
         f32x4_t t[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const float *r = p + (i64)min(s + u, q.splits - 1) * q.stride;
-            if (VEC) t[u] = *(const f32x4_t *)r;
-            else t[u][0] = *r;
+            const float *r = q.src + i + (i64)min(s + u, q.splits - 1) * q.stride;
+            if (VEC) {
+                t[u] = *(const f32x4_t *)r;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[u][e] = r[i + e < q.count ? e : 0];
+            }
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            if (s + u < q.splits) {
-#pragma unroll
-                for (int e = 0; e < (VEC ? 4 : 1); ++e) v[e] += t[u][e];
-            }
+            if (s + u < end) v += t[u];
     }
-#pragma unroll
-    for (int e = 0; e < (VEC ? 4 : 1); ++e) {
-        float w = v[e];
-        if (q.rscale) w *= q.rscale[(i + e) / q.rlen];
-        if (q.bf16) ((uint16_t *)q.dst)[i + e] = float_to_bf16_bits(w);
-        else q.dst[i + e] = q.accumulate ? q.dst[i + e] + w : w;
-    }
+    return v;
 }
 
 __global__ __launch_bounds__(256) void split_sums_kernel(SplitSumArgs a)
 {
+    __shared__ f32x4_t share[3][64];
     int k = 0;
 #pragma unroll
     for (int i = 1; i < 4; ++i)
         if (i < a.n && (int)blockIdx.x >= a.blocks[i]) k = i;
     const SplitSum &q = a.s[k];
-    const i64 b = blockIdx.x - a.blocks[k];
-    if (q.count % 4 == 0 && q.stride % 4 == 0) { // (the partial sums start 256-byte aligned)
-        const i64 i = (b * 256 + threadIdx.x) * 4;
-        if (i < q.count) split_sum<true>(q, i);
-    } else {
+    const int part = threadIdx.x >> 6, o = threadIdx.x & 63;
+    const i64 i = ((i64)(blockIdx.x - a.blocks[k]) * 64 + o) * 4;
+    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+    if (i < q.count) // (the partial sums start 256-byte aligned)
+        v = q.count % 4 == 0 && q.stride % 4 == 0 ? split_share<true>(q, i, part) : split_share<false>(q, i, part);
+    if (part > 0) share[part - 1][o] = v;
+    __syncthreads();
+    if (part > 0) return;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const i64 i = (b * 4 + u) * 256 + threadIdx.x;
-            if (i < q.count) split_sum<false>(q, i);
+    for (int u = 0; u < 3; ++u) v += share[u][o];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (i + e >= q.count) return;
+        i64 at = i + e;
+        if (q.tn > 0) {
+            const i64 m = at / q.tn;
+            at = (at - m * q.tn) * q.tm + m;
         }
+        float w = v[e];
+        if (q.rscale) w *= q.rscale[at / q.rlen];
+        if (q.bf16) ((uint16_t *)q.dst)[at] = float_to_bf16_bits(w);
+        else q.dst[at] = q.accumulate ? q.dst[at] + w : w;
     }
 }
 
@@ -179,7 +188,7 @@ void split_sum_add(SplitSumArgs &a, const SplitSum &s)
 {
     if (!s.dst || s.count <= 0) return;
     a.s[a.n] = s;
-    a.blocks[a.n + 1] = a.blocks[a.n] + (int)((s.count + 1023) / 1024);
+    a.blocks[a.n + 1] = a.blocks[a.n] + (int)((s.count + 255) / 256);
     ++a.n;
 }
 

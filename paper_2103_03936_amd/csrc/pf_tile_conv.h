@@ -25,7 +25,8 @@ __device__ __forceinline__ void pack_filters(const TileProb &p, int block, int t
     }
 }
 
-template <typename CT, class CFG, bool GATHER>
+// WG: the launch has weight gradients (tiles of CFGW).  Launches without run kernels without their registers.
+template <typename CT, class CFG, class CFGW, bool GATHER, bool WG>
 __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_value)
 {
     const TileArgs &a = tile_args(by_value);
@@ -34,12 +35,14 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
     typedef LoadMC<CT, BM, false, true> AS;
     typedef LoadPixMC<CT, BN, false> BP;
     typedef LoadPixMC<CT, BN, true> BPG;
-    typedef LoadPixKC<CT, BM, false, true> AW;
-    typedef LoadPixKC<CT, BN, false> BW;
-    typedef LoadPixKC<CT, BN, true> BWG;
+    typedef LoadPixKC<CT, CFGW::BM, false, true> AW;
+    typedef LoadPixKC<CT, CFGW::BM, false> AWT;
+    typedef LoadPixKC<CT, CFGW::BN, false> BW;
+    typedef LoadPixKC<CT, CFGW::BN, false, true> BWT;
+    typedef LoadPixKC<CT, CFGW::BN, true> BWG;
     constexpr int s1 = TileSize<CT, CFG, AK, BP>::bytes, s2 = TileSize<CT, CFG, AS, BP>::bytes,
-                  s3 = TileSize<CT, CFG, AW, BW>::bytes;
-    constexpr int bytes = s1 > s2 ? (s1 > s3 ? s1 : s3) : (s2 > s3 ? s2 : s3);
+                  s3 = TileSize<CT, CFGW, AW, BW>::bytes;
+    constexpr int s12 = s1 > s2 ? s1 : s2, bytes = WG && s3 > s12 ? s3 : s12;
     __shared__ __attribute__((aligned(16))) unsigned char smem[bytes];
     extern __shared__ __attribute__((aligned(16))) unsigned char tile_tables[];
     const int tid = threadIdx.x;
@@ -70,56 +73,73 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
         tile_pieces<CT, CFG>(smem, tid, put);
     } else if (p.type == TILE_PACK) {
         pack_filters<CT>(p, t.index, tid);
-    } else {
-        const int img0 = t.ks * p.kper, img1 = min(p.pa.N, img0 + p.kper);
+    } else if constexpr (WG) {
+        const TileAt u = find_tile<CFGW>(a);
+        const int img0 = u.ks * p.kper, img1 = min(p.pa.N, img0 + p.kper);
         const int pieces = (img1 - img0) * p.pa.HC, n = (pieces + BK / TileEl<CT>::V - 1) / (BK / TileEl<CT>::V);
-        AW la;
         unsigned char *tb = tile_tables + (AW::table_bytes(p.pa) + 15) / 16 * 16;
-        la.init(p.pa, t.m0, img0, img1, tid, tile_tables);
-        if (GATHER && p.type == TILE_WGG) {
-            BWG lb;
-            lb.init(p.pb, t.n0, img0, img1, tid, tb);
+        if (p.type == TILE_WGT) {
+            AWT la;
+            BWT lb;
+            la.init(p.pa, u.m0, img0, img1, tid, tile_tables);
+            lb.init(p.pb, u.n0, img0, img1, tid, tb);
             __syncthreads();
-            tile_product<CT, CFG>(la, lb, n, smem, tid);
+            tile_product<CT, CFGW>(la, lb, n, smem, tid);
+            finish<CT, CFGW, BWT>(p, u.ks, u.zb, u.m0, u.n0, lb, u.n0, p.N, p.o.sums && u.m0 == 0, smem, tid);
         } else {
-            BW lb;
-            lb.init(p.pb, t.n0, img0, img1, tid, tb);
-            __syncthreads();
-            tile_product<CT, CFG>(la, lb, n, smem, tid);
+            AW la;
+            la.init(p.pa, u.m0, img0, img1, tid, tile_tables);
+            if (GATHER && p.type == TILE_WGG) {
+                BWG lb;
+                lb.init(p.pb, u.n0, img0, img1, tid, tb);
+                __syncthreads();
+                tile_product<CT, CFGW>(la, lb, n, smem, tid);
+            } else {
+                BW lb;
+                lb.init(p.pb, u.n0, img0, img1, tid, tb);
+                __syncthreads();
+                tile_product<CT, CFGW>(la, lb, n, smem, tid);
+            }
+            finish<CT, CFGW, AW>(p, u.ks, u.zb, u.m0, u.n0, la, u.m0, p.M, p.o.sums && u.n0 == 0, smem, tid);
         }
-        finish<CT, CFG, AW, BW>(p, t.ks, t.zb, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
     }
 }
 
-template <typename CT, class CFG>
+template <typename CT, class CFG, class CFGW>
 static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
 {
     typedef LoadPixMC<CT, CFG::BN, false> BP;
     int st = PF_OK, tab = 0;
-    bool gather = false;
+    bool gather = false, wg = false;
     for (int i = 0; i < a.n; ++i) {
         const TileProb &p = a.p[i];
         int b = BP::TAB;
-        if (p.type == TILE_WG) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, false>::table_bytes(p.pb);
+        if (p.type == TILE_WG || p.type == TILE_WGT) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, false>::table_bytes(p.pb);
         if (p.type == TILE_WGG) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, true>::table_bytes(p.pb);
         if (b > tab) tab = b;
+        wg = wg || p.type == TILE_WG || p.type == TILE_WGG || p.type == TILE_WGT;
         gather = gather || p.type == TILE_CONVG || p.type == TILE_WGG;
     }
     tab = (tab + 15) / 16 * 16;
-    if (gather) {
-        PF_LAUNCH_LDS(st, name, (tile_conv_kernel<CT, CFG, true>), dim3(a.blocks), dim3(TILE_THREADS), tab, s, a);
-    } else {
-        PF_LAUNCH_LDS(st, name, (tile_conv_kernel<CT, CFG, false>), dim3(a.blocks), dim3(TILE_THREADS), tab, s, a);
-    }
+#define PF_TILE_CONV(G, W)                                                                                              \
+    if (gather == G && wg == W)                                                                                         \
+        PF_LAUNCH_LDS(st, name, (tile_conv_kernel<CT, CFG, CFGW, G, W>), dim3(a.blocks), dim3(TILE_THREADS), tab, s, a);
+    PF_TILE_CONV(false, false)
+    PF_TILE_CONV(false, true)
+    PF_TILE_CONV(true, false)
+    PF_TILE_CONV(true, true)
+#undef PF_TILE_CONV
     return st;
 }
 template <typename CT>
-int launch_conv_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a)
+int launch_conv_t(hipStream_t s, const char *name, TileShape shape, TileShape wg, const TileArgs &a)
 {
+    typedef TileCfg<64, 64, 2, 2, 4> S64;
+    typedef TileCfg<32, 128, 1, 4, 4> W32;
     switch (shape) {
-    case TS_32x64: return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>>(s, name, a);
-    case TS_64: return launch_conv<CT, TileCfg<64, 64, 2, 2, 4>>(s, name, a);
-    case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>>(s, name, a);
+    case TS_32x64: return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, W32>(s, name, a); // (forward, or at most 32 channels)
+    case TS_64: return wg == TS_32x128 ? launch_conv<CT, S64, W32>(s, name, a) : launch_conv<CT, S64, S64>(s, name, a);
+    case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>, S64>(s, name, a);
     default: return PF_ERR_UNSUPPORTED;
     }
 }

@@ -1,5 +1,5 @@
 #include "pf_tile_conv.h"
 
 namespace pf {
-template int launch_conv_t<float>(hipStream_t, const char *, TileShape, const TileArgs &);
+template int launch_conv_t<float>(hipStream_t, const char *, TileShape, TileShape, const TileArgs &);
 }

@@ -32,6 +32,7 @@ enum TileType {
     TILE_CONVT,// A [K][M] with a scale per k, B a PixView
     TILE_WG,   // A and B PixViews, k = pixel
     TILE_WGG,  // the same, B with stride
+    TILE_WGT,  // TILE_WG whose row sums are those of the right operand
     TILE_PACK, // filters [q][c][tap] -> [c][q][selected tap]
 };
 
@@ -54,7 +55,7 @@ struct TileArgs {
 };
 
 // Tile shapes a launch can use.
-enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x64, TS_COUNT };
+enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x64, TS_32x128, TS_COUNT };
 
 // One product: add it to a launch.  ksplit <= 0 asks for the split that plan_tiles chose.
 TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc);
@@ -81,7 +82,8 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n);
 
 void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &p, int ksplit);
 int launch_tiles_linear(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a);
-int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a);
+// (`wg`: the shape of the weight gradients' tiles, pixels being summed over)
+int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, TileShape wg, const TileArgs &a);
 
 // dst (+)= sum over splits of src[split], optionally times rscale[index / rlen]; bf16: dst holds bf16 (no accumulation)
 struct SplitSum {
@@ -92,6 +94,7 @@ struct SplitSum {
     const float *rscale;
     i64 rlen;
     int bf16;
+    int tm, tn; // tn > 0: src is [tm][tn], dst its transpose (rscale per row of dst)
 };
 struct SplitSumArgs {
     int n, blocks[5];

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_v
         la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
         lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
-        finish<CT, CFG, AM, BMC>(p, t.ks, t.zb, t.m0, t.n0, la, p.o.sums && t.n0 == 0, smem, tid);
+        finish<CT, CFG, AM>(p, t.ks, t.zb, t.m0, t.n0, la, t.m0, p.M, p.o.sums && t.n0 == 0, smem, tid);
     }
 }
 

@@ -106,9 +106,10 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
     }
 }
 
-template <typename CT, class CFG, class LA, class LB>
-__device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, LA &la, bool sums, unsigned char *smem,
-                                       int tid)
+// Stores a tile and, from the loader that added them up, row sums r0 .. of at most nr.
+template <typename CT, class CFG, class L>
+__device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, L &l, int r0, int nr, bool sums,
+                                       unsigned char *smem, int tid)
 {
     constexpr int V = TileEl<CT>::V;
     tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, zb, m0 + m, n0 + n, v); });
@@ -116,8 +117,8 @@ __device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0
         __syncthreads();
         float *out = p.o.sums + ks * p.o.sums_stride + zb * p.ssums;
         const bool acc = p.o.accumulate != 0;
-        la.put_sums((float *)smem, tid, [&](int m, float v) {
-            if (m0 + m < p.M) out[m0 + m] = acc ? out[m0 + m] + v : v;
+        l.put_sums((float *)smem, tid, [&](int r, float v) {
+            if (r0 + r < nr) out[r0 + r] = acc ? out[r0 + r] + v : v;
         });
     }
 }
