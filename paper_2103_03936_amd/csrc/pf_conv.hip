@@ -157,7 +157,9 @@ struct ConvPlan {
     bool tiles;              // the tiled products of pf_tile.h take the shape
     bool gather;             // ... and read the k x k stage's input with stride
     TileShape sh_T, sh_Y, sh_dT, sh_g, sh_w; // ... the tile shapes of their launches
+    int ks_T, ks_dT;         // ... splits of the products that give T and dT
     int ks_tU, ks_tV;        // ... image splits of the two filter gradients
+    size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     size_t saved_bytes;      // the backward direction's packed weights when the forward call saves them
 };
@@ -202,6 +204,18 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.sh_T = g.r <= 32 ? TS_32x64 : TS_64;
     p.sh_Y = g.Cout <= 32 ? TS_32x64 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
     p.sh_dT = p.sh_T;
+    // T and dT: too few tiles for the chip split their contraction (at least four chunks each)
+    const auto split_k = [&](i64 K) {
+        const i64 bm = g.r <= 32 ? 32 : 64, tiles = (g.r + bm - 1) / bm * ((npx + 63) / 64), chunks = (K + 8 * V - 1) / (8 * V);
+        i64 ks = tiles >= 200 ? 1 : 384 / tiles;
+        if (ks > chunks / 4) ks = chunks / 4;
+        if (ks > 16) ks = 16;
+        return (int)(ks < 1 ? 1 : ks);
+    };
+    p.ks_T = split_k((i64)g.C * kk);
+    p.ks_dT = split_k(g.Cout);
+    const size_t part_T = (size_t)(p.ks_T > p.ks_dT ? p.ks_T : p.ks_dT) * g.r * npx;
+    p.n_part_T = p.ks_T > 1 || p.ks_dT > 1 ? part_T : 0;
     p.sh_g = TS_64;
     (void)npin;
     p.sh_w = g.r <= 32 ? TS_32x128 : TS_64;
@@ -232,6 +246,12 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
 {
     ConvPlan p;
     p.chain = dtype == PF_BF16 && chain_supported(g.C, g.Cout, g.r, g.H, g.W, g.k, g.s, g.p);
+    // One workgroup per image, 64 pixel columns whatever the image has: the tiled products are faster where most of the
+    // columns would be empty (4 x 4 images, 512 channels, rank 128, 3x3: 62 against 100 us at batch 4, 130 against 139 at
+    // 256) and where a few images would have to stream megabytes of filters through a few compute units (7 x 7 images,
+    // the same filters: 67 against 90 us at batch 4, 77 against 92 at 16, equal at 32).
+    plan_conv_tiles(g, dtype, p);
+    if (p.tiles && (g.H * g.W < 32 || (g.k == 3 && g.r > 64 && g.N < 32))) p.chain = false;
     p.n_w1 = chain_w1_elems(g.C, g.r, g.k);
     p.n_w2 = chain_w2_elems(g.Cout, g.r, 1);
     p.n_w1b = chain_w1_elems(g.Cout, g.r, 1);
@@ -293,10 +313,12 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
         if (f > p.fwd_bytes) p.fwd_bytes = f;
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
-    plan_conv_tiles(g, dtype, p);
     if (p.tiles) {
         const size_t el = dtype == PF_BF16 ? 2 : 4;
-        const size_t b = 2 * align_up(p.n_T * el) + 4 * align_up(p.n_pack * el) + align_up(p.n_part_t * 4);
+        const size_t f = align_up(p.n_T * el) + align_up(p.n_part_T * 4);
+        const size_t b = 2 * align_up(p.n_T * el) + 4 * align_up(p.n_pack * el) +
+                         align_up((p.n_part_t > p.n_part_T ? p.n_part_t : p.n_part_T) * 4);
+        if (f > p.fwd_bytes) p.fwd_bytes = f;
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
     return p;
@@ -415,18 +437,41 @@ static void out_planes(TileOut &o, const PixView &v, int CH)
     o.s = 1;
 }
 
+// The rank-r intermediate from one product (and what else is in the launch), through partial sums when it is split.
 template <typename T>
-static int conv_T_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, T *out, hipStream_t s)
+static int conv_mid_tiles(hipStream_t s, const char *name, const ConvGeom &g, TileShape shape, TileArgs &a, TileProb q, const PixView &v,
+                          int ks, T *out, float *part)
+{
+    const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32, V = 16 / (int)sizeof(T);
+    if (ks > 1) {
+        q.o.C = part;
+        q.o.f32 = 1;
+        q.o.ld = q.N;
+        q.o.split_stride = (i64)g.r * q.N;
+    } else {
+        q.o.C = out;
+        out_planes(q.o, v, g.r);
+    }
+    tile_add(a, shape, dt, q, ks);
+    const int got = a.p[a.n - 1].ksplit;
+    int st = launch_tiles_conv(s, name, dt, shape, TS_64, a);
+    if (st != PF_OK || ks <= 1) return st;
+    SplitSumArgs ss = {};
+    split_sum_add(ss, SplitSum{part, (float *)out, (i64)g.r * q.N, (i64)g.r * q.N, got, 0, nullptr, 0, sizeof(T) == 2, g.r, 0,
+                               v.HC * V, v.gH * v.gW});
+    return launch_split_sums(s, ss);
+}
+
+template <typename T>
+static int conv_T_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, T *out, float *part, hipStream_t s)
 {
     const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32, K = g.C * g.k * g.k;
     const PixView v = conv_input_view(g, dt, X);
     TileArgs a = {};
     TileProb q = tile_prob(p.gather ? TILE_CONVG : TILE_CONV, g.r, g.N * v.HC * (16 / (int)sizeof(T)), K, Uk, K, nullptr, 0,
-                           out, 0);
+                           nullptr, 0);
     q.pb = v;
-    out_planes(q.o, v, g.r);
-    tile_add(a, p.sh_T, dt, q, 1);
-    return launch_tiles_conv(s, "conv_T=Uk*X", dt, p.sh_T, TS_64, a);
+    return conv_mid_tiles<T>(s, "conv_T=Uk*X", g, p.sh_T, a, q, v, p.ks_T, out, part);
 }
 
 // Two launches: T = Uk * X (an implicit product over (channel, tap), the order in which the filters lie in memory), then
@@ -436,8 +481,8 @@ static int conv_fwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
                           Workspace &ws, hipStream_t s, const ConvEpilogue &ep)
 {
     const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32;
-    T *Tt = T_save ? T_save : ws.take<T>(p.n_T);
-    int st = conv_T_tiles<T>(g, p, X, Uk, Tt, s);
+    T *Tws = ws.take<T>(p.n_T), *Tt = T_save ? T_save : Tws;
+    int st = conv_T_tiles<T>(g, p, X, Uk, Tt, ws.take<float>(p.n_part_T), s);
     if (st != PF_OK) return st;
     TileArgs a = {};
     const PixView v = pix_view(g, dt, Tt, g.r, g.Ho, g.Wo, g.Ho, g.Wo);
@@ -463,10 +508,10 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
     const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32, V = 16 / (int)sizeof(T), kk = g.k * g.k;
     T *Tws = ws.take<T>(p.n_T), *dT = ws.take<T>(p.n_T), *pack[4];
     for (int i = 0; i < 4; ++i) pack[i] = ws.take<T>(p.n_pack);
-    float *part = ws.take<float>(p.n_part_t);
+    float *part = ws.take<float>(p.n_part_t > p.n_part_T ? p.n_part_t : p.n_part_T);
     int st = PF_OK;
     if (dVp && !T_saved) {
-        st = conv_T_tiles<T>(g, p, X, Uk, Tws, s);
+        st = conv_T_tiles<T>(g, p, X, Uk, Tws, part, s);
         if (st != PF_OK) return st;
     }
     const PixView vdY = pix_view(g, dt, dY, g.Cout, g.Ho, g.Wo, g.Ho, g.Wo);
@@ -474,13 +519,6 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
     const PixView vT = pix_view(g, dt, T_saved ? T_saved : Tws, g.r, g.Ho, g.Wo, g.Ho, g.Wo);
     const int npx = g.N * vdT.HC * V, phases = g.s * g.s;
     TileArgs a = {}, b = {};
-    if (dX || dUk) {
-        TileProb q = tile_prob(TILE_CONVT, g.r, npx, g.Cout, Vp, g.r, nullptr, 0, dT, 0);
-        q.pb = vdY;
-        q.ascale = ep.scale;
-        out_planes(q.o, vdT, g.r);
-        tile_add(a, p.sh_dT, dt, q, 1);
-    }
     if (dX) {
         for (int f = 0; f < phases; ++f) {
             int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
@@ -518,8 +556,13 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
             tile_add(b, p.sh_g, dt, q, 1);
         }
     }
-    st = launch_tiles_conv(s, "conv_dT=Vpt*dY", dt, p.sh_dT, TS_64, a);
-    if (st != PF_OK) return st;
+    if (dX || dUk) {
+        TileProb q = tile_prob(TILE_CONVT, g.r, npx, g.Cout, Vp, g.r, nullptr, 0, nullptr, 0);
+        q.pb = vdY;
+        q.ascale = ep.scale;
+        st = conv_mid_tiles<T>(s, "conv_dT=Vpt*dY", g, p.sh_dT, a, q, vdT, p.ks_dT, dT, part);
+        if (st != PF_OK) return st;
+    }
     SplitSumArgs ss = {};
     // [m][n] over the pixels (`transposed`: the result is wanted as [n][m]); sums: those of pa's rows, transposed: of pb's
     const auto grad = [&](const PixView &pa, const PixView &pb, int type, int m, int n, float *dst, int ks, float *sums,

@@ -173,7 +173,11 @@ __global__ __launch_bounds__(256) void split_sums_kernel(SplitSumArgs a)
     for (int e = 0; e < 4; ++e) {
         if (i + e >= q.count) return;
         i64 at = i + e;
-        if (q.tn > 0) {
+        if (q.np > 0) {
+            const i64 per = q.count / q.tm, m = at / per, n = at - m * per, img = n / q.np, pos = n - img * q.np;
+            if (pos >= q.hw) continue;
+            at = (img * q.tm + m) * q.hw + pos;
+        } else if (q.tn > 0) {
             const i64 m = at / q.tn;
             at = (at - m * q.tn) * q.tm + m;
         }

@@ -50,25 +50,25 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_val
     if (!t.live) return;
     const TileProb &p = a.p[t.prob];
     const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v); };
-    const int nch = (p.K + BK - 1) / BK; // (not TILE_WG)
+    const int kbeg = t.ks * p.kper, nch = (min(p.K, kbeg + p.kper) - kbeg + BK - 1) / BK; // (not TILE_WG)
     if (p.type == TILE_CONV || (GATHER && p.type == TILE_CONVG)) {
         AK la;
-        la.init(p.A, p.lda, p.M, p.K, t.m0, 0, tid);
+        la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid);
         if (GATHER && p.type == TILE_CONVG) {
             BPG lb;
-            lb.init(p.pb, t.n0, 0, tid, tile_tables);
+            lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
             tile_product<CT, CFG>(la, lb, nch, smem, tid);
         } else {
             BP lb;
-            lb.init(p.pb, t.n0, 0, tid, tile_tables);
+            lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
             tile_product<CT, CFG>(la, lb, nch, smem, tid);
         }
         tile_pieces<CT, CFG>(smem, tid, put);
     } else if (p.type == TILE_CONVT) {
         AS la;
         BP lb;
-        la.init(p.A, p.lda, p.M, p.K, t.m0, 0, tid, p.ascale);
-        lb.init(p.pb, t.n0, 0, tid, tile_tables);
+        la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid, p.ascale);
+        lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
         tile_pieces<CT, CFG>(smem, tid, put);
     } else if (p.type == TILE_PACK) {

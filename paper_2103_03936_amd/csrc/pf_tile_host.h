@@ -95,6 +95,7 @@ struct SplitSum {
     i64 rlen;
     int bf16;
     int tm, tn; // tn > 0: src is [tm][tn], dst its transpose (rscale per row of dst)
+    int np, hw; // np > 0: src is [tm][images][np], dst the planes [image][tm][hw], hw <= np
 };
 struct SplitSumArgs {
     int n, blocks[5];
