@@ -123,24 +123,65 @@ int linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, cons
                      size_t workspace_bytes, void *stream, int align, const LinEpilogue *ep = nullptr);
 
 // ---------------------------------------------------------- workspace plan
+// The tiled products' part of a plan, for G layers of this shape that share their input (side by side in every launch).
+struct LinearTiles {
+    bool ok;               // every dimension holds a 16-byte piece
+    TilePlan T, dT, Y;     // tile shapes and splits of the intermediates and the output
+    TileGroup grads;       // dX, dU and dV in one launch
+    size_t n_mid, n_part_T, n_part_g, fwd_bytes, bwd_bytes; // elements of T, partial sums (floats)
+};
+static LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
+{
+    LinearTiles p = {};
+    const i64 piece = d->dtype == PF_BF16 ? 8 : 4;
+    p.ok = d->M > 0 && d->in >= piece && d->out >= piece && d->r >= piece && (G == 1 || d->r % piece == 0);
+    if (!p.ok) return p;
+    const i64 M = d->M, in = d->in, out = d->out, r = d->r;
+    p.T = plan_tiles(d->dtype, M, G * r, in, 16);
+    p.Y = plan_tiles(d->dtype, M, G * out, r, 1);
+    p.dT = plan_tiles(d->dtype, M, G * r, out, 16);
+    const TileNeed need[3] = {{M, in, G * r, false}, {G * out, r, M, true}, {in, G * r, M, true}};
+    p.grads = plan_tile_group(d->dtype, need, 3);
+    const int ks = p.T.ksplit > p.dT.ksplit ? p.T.ksplit : p.dT.ksplit;
+    p.n_mid = (size_t)(G * M * r);
+    p.n_part_T = ks > 1 ? (size_t)(ks * G * M * r) : 0;
+    p.n_part_g = (size_t)(G * (p.grads.ksplit[1] * (out * r + out) + p.grads.ksplit[2] * in * r)) + 192;
+    const size_t el = d->dtype == PF_BF16 ? 2 : 4;
+    p.fwd_bytes = align_up(p.n_mid * el) + align_up(p.n_part_T * 4);
+    p.bwd_bytes = 2 * align_up(p.n_mid * el) + align_up((p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g) * 4);
+    return p;
+}
+
 struct LinearPlan {
     int ks_dU, ks_dV;
     size_t fwd_bytes, bwd_bytes;
     size_t n_T, n_dT, n_part;
     bool fused;         // bf16 and shapes the fused chain / factor-gradient kernels take
+    bool chain_fwd, chain_bwd; // ... and sizes where they are the faster ones
     bool chain2;        // ... and the rank the 32-row chain kernel is built for: no weight re-ordering pass
     size_t n_colsum;    // per-tile column sums of dY (bias gradient), floats
     int wg_groups, wg_ipg; // row-tile groups of the factor-gradient kernel and tiles per group
     int wg_cols;           // columns per workgroup of that kernel
     bool skinny;           // fp32 with at most 128 rows: the weight-streaming kernels of the LSTM cell
     size_t n_part_sk;      // their slice sums, floats
-    bool tiles;            // every dimension holds a 16-byte piece: the tiled products of pf_tile.h
-    TilePlan t_T, t_dT, t_Y; // ... their tile shapes and splits
-    TileGroup t_grads;     // ... dX, dU and dV in one launch
-    size_t n_part_T, n_part_g; // ... partial sums, floats
+    LinearTiles t;         // the tiled products of pf_tile.h
     bool small;            // fp32 with at most 128 rows and dimensions in whole tiles: two launches per direction
     size_t n_small;        // slices of the rank-r intermediate(s) between them, floats
 };
+
+// Chain kernel or tiled products?  A workgroup of the chain kernel takes 32 rows through the whole layer one after the
+// other, about 5 us per 1024 of `width` (in + out) however few rows there are; the tiled products
+// spread few rows over the chip but move the intermediates through memory.  Measured (us, chain / tiled):
+//   forward, 512 -> 512:   7.3 / 10.6 at 64 rows,  7.8 / 13.6 at 2048
+//   forward, 512 -> 2048: 14.1 / 10.6 at 64 rows, 14.4 / 13.7 at 512, 15.9 / 17.8 at 2048
+//   training, encoder layer d = 512 (backward on either): 250 / 150 at 300 rows, 285 / 245 at 3000, 305 / 294 at 4096,
+//   327 / 342 at 6000; d = 256, rank 64: 272 / 154 at 3000, 310 / 245 at 8192, a 1024 -> 1024 layer 82 / 128 at 16384
+static bool chain_fwd_pays(i64 M, i64 width, i64 r)
+{
+    if (r != 128) return M >= 10000;
+    return 10 * M >= 7 * (width - 1024);
+}
+static bool chain_bwd_pays(i64 M, i64 r) { return M >= (r == 128 ? 4608 : 10000); }
 
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
@@ -156,6 +197,8 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.fwd_bytes = align_up(p.n_T * sizeof(float));
     p.bwd_bytes = align_up(p.n_T * sizeof(float)) + align_up(p.n_dT * sizeof(float)) + align_up(p.n_part * sizeof(float));
     p.fused = d->dtype == PF_BF16 && linear_chain_supported(d->in, d->out, d->r);
+    p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in + d->out, d->r);
+    p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->r);
     p.skinny = d->dtype == PF_F32 && d->M > 0 && d->M <= 4 * SK_MAX_ROWS && d->in >= 4 && d->out >= 4 &&
                d->r >= 4;
     p.n_part_sk = 0;
@@ -173,25 +216,9 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
         if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
         if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
     }
-    const i64 piece = d->dtype == PF_BF16 ? 8 : 4;
-    p.tiles = d->M > 0 && d->in >= piece && d->out >= piece && d->r >= piece;
-    p.n_part_T = p.n_part_g = 0;
-    if (p.tiles) {
-        const i64 M = d->M, in = d->in, out = d->out, r = d->r;
-        p.t_T = plan_tiles(d->dtype, M, r, in, 16);
-        p.t_Y = plan_tiles(d->dtype, M, out, r, 1);
-        p.t_dT = plan_tiles(d->dtype, M, r, out, 16);
-        const TileNeed need[3] = {{M, in, r, false}, {out, r, M, true}, {in, r, M, true}};
-        p.t_grads = plan_tile_group(d->dtype, need, 3);
-        const int ks = p.t_T.ksplit > p.t_dT.ksplit ? p.t_T.ksplit : p.t_dT.ksplit;
-        p.n_part_T = ks > 1 ? (size_t)(ks * M * r) : 0;
-        p.n_part_g = (size_t)(p.t_grads.ksplit[1] * (out * r + out) + p.t_grads.ksplit[2] * in * r) + 128;
-        const size_t el = d->dtype == PF_BF16 ? 2 : 4;
-        const size_t fwd = align_up(p.n_T * el) + align_up(p.n_part_T * 4);
-        const size_t bwd = 2 * align_up(p.n_T * el) + align_up((p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g) * 4) + 512;
-        if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
-        if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
-    }
+    p.t = make_linear_tiles(d, 1);
+    if (p.t.fwd_bytes > p.fwd_bytes) p.fwd_bytes = p.t.fwd_bytes;
+    if (p.t.bwd_bytes > p.bwd_bytes) p.bwd_bytes = p.t.bwd_bytes;
     p.small = d->dtype == PF_F32 && linear_small_supported(d->M, d->in, d->out, d->r);
     p.n_small = p.small ? (size_t)(8 * d->M * d->r) : 0; // at most eight slices per intermediate
     if (p.small) {
@@ -316,111 +343,142 @@ static int linear_bwd_generic(const pf_linear_desc *d, const T *X, const T *V, c
 }
 
 // ---------------------------------------------------- any shape of at least a 16-byte piece
-// T = A B (A [M][K], B [K][r]) in the call's element type, through partial sums when the product has too few tiles for
-// the chip.
+// T = A B_g (A [M][K], B_g [K][r]) for G layers, in the call's element type: T_g at out + g * sout with leading dimension
+// ldo; through partial sums when the products have too few tiles for the chip.  A steps by sa from layer to layer.
 template <typename T>
-static int tiles_intermediate(hipStream_t s, const char *name, const TilePlan &t, int M, int r, int K, const T *A,
-                              const T *B, T *out, float *part)
+static int tiles_mid(hipStream_t s, const char *name, const TilePlan &t, int G, int M, int r, int K, const T *A, i64 sa,
+                     const T *B, T *out, i64 ldo, i64 sout, float *part)
 {
     const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32;
     TileArgs a = {};
-    TileProb p = tile_prob(TILE_NN, M, r, K, A, K, B, r, out, r);
+    TileProb p = tile_prob(TILE_NN, M, r, K, A, K, B, r, out, ldo);
+    p.nb = G;
+    p.sa = sa;
+    p.sb = (i64)K * r;
+    p.sc = sout;
     const bool split = t.ksplit > 1;
     if (split) {
         p.o.C = part;
         p.o.f32 = 1;
-        p.o.split_stride = (i64)M * r;
+        p.o.split_stride = (i64)G * M * r;
     }
     tile_add(a, t.shape, dt, p, t.ksplit);
     int st = launch_tiles_linear(s, name, dt, t.shape, a);
     if (st != PF_OK || !split) return st;
     SplitSumArgs ss = {};
-    split_sum_add(ss, SplitSum{part, (float *)out, (i64)M * r, (i64)M * r, a.p[0].ksplit, 0, nullptr, 0, sizeof(T) == 2});
+    const i64 n = (i64)G * M * r;
+    split_sum_add(ss, SplitSum{part, (float *)out, n, n, a.p[0].ksplit, 0, nullptr, 0, sizeof(T) == 2});
     return launch_split_sums(s, ss);
 }
 
-// Two launches: T = X V, then Y = act(T U^T + bias + residual) with the epilogue on the tile.
+// Two launches: T_g = X V_g, then Y_g = act(T_g U_g^T + bias_g + residual) with the epilogue on the tile.
 template <typename T>
-static int linear_fwd_tiles(const pf_linear_desc *d, const LinearPlan &p, const T *X, const T *V, const T *U,
+static int linear_fwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G, const T *X, const T *V, const T *U,
                             const T *bias, T *Y, T *T_save, Workspace &ws, hipStream_t s, const LinEpilogue &ep)
 {
     const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
-    T *Tws = ws.take<T>(p.n_T);
+    T *Tws = ws.take<T>(p.n_mid);
     float *part = ws.take<float>(p.n_part_T);
     T *Tt = T_save ? T_save : Tws;
-    int st = tiles_intermediate<T>(s, "linear_T=X*V", p.t_T, M, r, in, X, V, Tt, part);
+    int st = tiles_mid<T>(s, "linear_T=X*V", p.T, G, M, r, in, X, 0, V, Tt, r, (i64)M * r, part);
     if (st != PF_OK) return st;
     TileArgs a = {};
     TileProb q = tile_prob(TILE_NT, M, out, r, Tt, r, U, r, Y, out);
+    q.nb = G;
+    q.sa = (i64)M * r;
+    q.sb = (i64)out * r;
+    q.sc = (i64)M * out;
+    q.sbias = out;
     q.o.bias = d->has_bias ? bias : nullptr;
     q.o.add = ep.add;
     q.o.relu = ep.relu;
     if (ep.used) *ep.used = true;
-    tile_add(a, p.t_Y.shape, d->dtype, q, 1);
-    return launch_tiles_linear(s, "linear_Y=T*Ut", d->dtype, p.t_Y.shape, a);
+    tile_add(a, p.Y.shape, d->dtype, q, 1);
+    return launch_tiles_linear(s, "linear_Y=T*Ut", d->dtype, p.Y.shape, a);
 }
 
-// Two or three launches: dT = dY U (T = X V again when it was not kept), then dX, dU, dV and the bias gradient side by
-// side, then the sums over their splits where the rows were split.
+// Two or three launches: dT_g = dY_g U_g (T_g = X V_g again when it was not kept), then dX = sum_g dT_g V_g^T, dU_g, dV_g
+// and the bias gradients side by side, then the sums over their splits where the rows were split.  The dT_g of several
+// layers lie side by side in one [M][G r] matrix, so that dX is one product with a contraction of G r.
 template <typename T>
-static int linear_bwd_tiles(const pf_linear_desc *d, const LinearPlan &p, const T *X, const T *V, const T *U, const T *dY,
-                            const T *T_saved, T *dX, float *dU, float *dV, float *dbias, int accumulate, Workspace &ws,
-                            hipStream_t s, const LinEpilogue &ep)
+static int linear_bwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G, const T *X, const T *V, const T *U,
+                            const T *dY, const T *T_saved, T *dX, float *dU, float *dV, float *dbias, int accumulate,
+                            Workspace &ws, hipStream_t s, const LinEpilogue &ep)
 {
     const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
-    T *Tws = ws.take<T>(p.n_T), *dT = ws.take<T>(p.n_T);
+    T *Tws = ws.take<T>(p.n_mid), *dT = ws.take<T>(p.n_mid);
     float *part = ws.take<float>(p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g);
     int st = PF_OK;
     if (dU && !T_saved) {
-        st = tiles_intermediate<T>(s, "linear_T=X*V", p.t_T, M, r, in, X, V, Tws, part);
+        st = tiles_mid<T>(s, "linear_T=X*V", p.T, G, M, r, in, X, 0, V, Tws, r, (i64)M * r, part);
         if (st != PF_OK) return st;
     }
+    // (split, the partial sums of the layers are [G][M][r] like their sum)
+    const bool side = G > 1 && p.dT.ksplit == 1;
+    const i64 ldd = side ? (i64)G * r : r, sd = side ? r : (i64)M * r;
     if (dX || dV) {
-        st = tiles_intermediate<T>(s, "linear_dT=dY*U", p.t_dT, M, r, out, dY, U, dT, part);
+        st = tiles_mid<T>(s, "linear_dT=dY*U", p.dT, G, M, r, out, dY, (i64)M * out, U, dT, ldd, sd, part);
         if (st != PF_OK) return st;
     }
-    const TileShape sh = p.t_grads.shape;
+    const TileShape sh = p.grads.shape;
     const bool want_db = d->has_bias && dbias;
     TileArgs a = {};
     SplitSumArgs ss = {};
     if (dX) {
-        TileProb q = tile_prob(TILE_NT, M, in, r, dT, r, V, r, dX, in);
+        TileProb q = tile_prob(TILE_NT, M, in, G * r, dT, side ? ldd : r, V, r, dX, in);
+        if (G > 1) {
+            q.bseg = r;
+            q.bjump = (i64)in * r;
+        }
+        if (G > 1 && !side) {
+            q.aseg = r;
+            q.ajump = (i64)M * r;
+        }
         q.o.add = ep.add;
         q.o.mask = ep.mask;
         if (ep.used) *ep.used = true;
         tile_add(a, sh, d->dtype, q, 1);
     }
-    const auto grad = [&](const T *A, int m, const T *B, float *dst, int ks, float *sums) {
-        TileProb q = tile_prob(TILE_TN, m, r, M, A, m, B, r, dst, r);
+    const auto grad = [&](const T *A, i64 sa, int m, const T *B, i64 ldb, i64 sb, float *dst, int ks, float *sums) {
+        TileProb q = tile_prob(TILE_TN, m, r, M, A, m, B, ldb, dst, r);
+        q.nb = G;
+        q.sa = sa;
+        q.sb = sb;
+        q.sc = (i64)m * r;
+        q.ssums = m;
         q.o.f32 = 1;
         q.o.accumulate = accumulate;
         q.o.sums = sums;
         float *psum = part;
+        const i64 n = (i64)G * m * r, nsum = (i64)G * m;
         if (ks > 1) {
             q.o.accumulate = 0;
             q.o.C = part;
-            q.o.split_stride = (i64)m * r;
-            part += (i64)ks * m * r;
+            q.o.split_stride = n;
+            part += ks * n;
+            part += (64 - ((uintptr_t)part / 4) % 64) % 64; // partial sums start 256-byte aligned
             if (sums) {
                 psum = part;
                 q.o.sums = psum;
-                q.o.sums_stride = m;
-                part += (i64)ks * m;
+                q.o.sums_stride = nsum;
+                part += ks * nsum;
+                part += (64 - ((uintptr_t)part / 4) % 64) % 64;
             }
-            part += (64 - (part - (float *)nullptr) % 64) % 64; // the next partial sums start 256-byte aligned
         }
         tile_add(a, sh, d->dtype, q, ks);
         if (ks > 1) {
-            const int n = a.p[a.n - 1].ksplit;
-            split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, (i64)m * r, (i64)m * r, n, accumulate, nullptr, 0, 0});
-            if (sums) split_sum_add(ss, SplitSum{psum, sums, m, m, n, accumulate, nullptr, 0, 0});
+            const int got = a.p[a.n - 1].ksplit;
+            split_sum_add(ss, SplitSum{(const float *)q.o.C, dst, n, n, got, accumulate, nullptr, 0, 0});
+            if (sums) split_sum_add(ss, SplitSum{psum, sums, nsum, nsum, got, accumulate, nullptr, 0, 0});
         }
     };
-    if (dU) grad(dY, out, T_saved ? T_saved : Tws, dU, p.t_grads.ksplit[1], want_db ? dbias : nullptr);
-    if (dV) grad(X, in, dT, dV, p.t_grads.ksplit[2], nullptr);
+    if (dU)
+        grad(dY, (i64)M * out, out, T_saved ? T_saved : Tws, r, (i64)M * r, dU, p.grads.ksplit[1], want_db ? dbias : nullptr);
+    if (dV) grad(X, 0, in, dT, ldd, sd, dV, p.grads.ksplit[2], nullptr);
     st = launch_tiles_linear(s, "linear_dX,dU,dV", d->dtype, sh, a);
     if (st == PF_OK) st = launch_split_sums(s, ss);
-    if (st == PF_OK && want_db && !dU) st = launch_colsum<T>(s, dY, part, dbias, M, out, out, accumulate);
+    for (int g = 0; st == PF_OK && want_db && !dU && g < G; ++g)
+        st = launch_colsum<T>(s, dY + (i64)g * M * out, part, dbias + (i64)g * out, M, out, out, accumulate);
     return st;
 }
 
@@ -708,6 +766,7 @@ struct SharedPlan {
     pf_linear_desc one; // one of the G layers
     LinearPlan p;
     bool fused_fwd, fused_bwd; // the groups run inside one launch of the chain kernel
+    LinearTiles t;             // otherwise side by side on the tiled products
     size_t n_colsum, fwd_bytes, bwd_bytes;
 };
 
@@ -723,22 +782,32 @@ static int check_shared_desc(const pf_linear_shared_desc *d, pf_linear_desc *one
     return PF_OK;
 }
 
-static SharedPlan plan_shared(const pf_linear_shared_desc *d, const pf_linear_desc &one)
+static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_linear_desc &one)
 {
     SharedPlan sp;
     sp.one = one;
     sp.p = plan_linear(&one);
     const int G = d->groups;
     const bool bf = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1;
-    sp.fused_fwd = bf && linear_chain2_multi_supported(d->n_in, d->n_out, d->r, G, false);
-    sp.fused_bwd = bf && linear_chain2_multi_supported(d->n_out, d->n_in, d->r, G, true);
+    sp.fused_fwd = bf && sp.p.chain_fwd && linear_chain2_multi_supported(d->n_in, d->n_out, d->r, G, false);
+    sp.fused_bwd = bf && sp.p.chain_bwd && linear_chain2_multi_supported(d->n_out, d->n_in, d->r, G, true);
     sp.n_colsum = (size_t)(2 * ((d->M + LC_ROWS - 1) / LC_ROWS)) * d->n_out;
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
     // one layer's workspace, then: dT and (recomputed) T of all groups, their column sums, one more dX
     sp.bwd_bytes = sp.p.bwd_bytes + 2 * align_up((size_t)G * sp.p.n_T * 2) + align_up((size_t)G * sp.n_colsum * 4) +
                    align_up((size_t)(d->M * d->n_in) * el);
+    sp.t = make_linear_tiles(&one, G);
+    if (sp.t.fwd_bytes > sp.fwd_bytes) sp.fwd_bytes = sp.t.fwd_bytes;
+    if (sp.t.bwd_bytes > sp.bwd_bytes) sp.bwd_bytes = sp.t.bwd_bytes;
     return sp;
+}
+
+static const SharedPlan &plan_shared(const pf_linear_shared_desc *d, const pf_linear_desc &one)
+{
+    static thread_local PlanCache<PlanKey<7>, SharedPlan> cache;
+    return cache.get(PlanKey<7>{{d->M, d->n_in, d->n_out, d->r, d->groups, d->dtype, d->has_bias}},
+                     [&] { return make_shared_plan(d, one); });
 }
 
 // Alignment a layer's slice of the stacked operands is held to: 16 bytes where the 16-byte-load kernels may run
@@ -794,17 +863,17 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (d->dtype == PF_F32 && p.skinny)
         return linear_fwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)bias, (float *)Y, (float *)T_save, ws, s);
-    if (d->dtype == PF_F32 && p.tiles)
-        return linear_fwd_tiles<float>(d, p, (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.t.ok)
+        return linear_fwd_tiles<float>(d, p.t, 1, (const float *)X, (const float *)V, (const float *)U,
                                        (const float *)bias, (float *)Y, (float *)T_save, ws, s, ep ? *ep : LinEpilogue{});
     if (d->dtype == PF_F32)
         return linear_fwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)bias,
                                          (float *)Y, (float *)T_save, ws, s);
-    if (p.fused)
+    if (p.chain_fwd)
         return linear_fwd_fused(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)bias,
                                 (bf16_t *)Y, (bf16_t *)T_save, ws, s, ep ? *ep : LinEpilogue{});
-    if (p.tiles)
-        return linear_fwd_tiles<bf16_t>(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+    if (p.t.ok)
+        return linear_fwd_tiles<bf16_t>(d, p.t, 1, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
                                         (const bf16_t *)bias, (bf16_t *)Y, (bf16_t *)T_save, ws, s,
                                         ep ? *ep : LinEpilogue{});
     return linear_fwd_generic<bf16_t>(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
@@ -834,20 +903,20 @@ int pf::linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
         return linear_bwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                  (float *)dbias, accumulate, ws, s);
-    if (d->dtype == PF_F32 && p.tiles)
-        return linear_bwd_tiles<float>(d, p, (const float *)X, (const float *)V, (const float *)U,
+    if (d->dtype == PF_F32 && p.t.ok)
+        return linear_bwd_tiles<float>(d, p.t, 1, (const float *)X, (const float *)V, (const float *)U,
                                        (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                        (float *)dbias, accumulate, ws, s, ep ? *ep : LinEpilogue{});
     if (d->dtype == PF_F32)
         return linear_bwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
                                          (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                          (float *)dbias, accumulate, ws, s);
-    if (p.fused && dX && d->M > 0)
+    if (p.chain_bwd && dX)
         return linear_bwd_fused(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
                                 (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias,
                                 accumulate, ws, s, ep ? *ep : LinEpilogue{});
-    if (p.tiles)
-        return linear_bwd_tiles<bf16_t>(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
+    if (p.t.ok)
+        return linear_bwd_tiles<bf16_t>(d, p.t, 1, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
                                         (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias,
                                         accumulate, ws, s, ep ? *ep : LinEpilogue{});
     return linear_bwd_generic<bf16_t>(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
@@ -1018,6 +1087,14 @@ int pf_lowrank_linear_shared_fwd(const pf_linear_shared_desc *d, const void *X, 
         c.gs_mid = M * r;
         return launch_linear_chain2(s, "linear_shared_fwd_fused", c);
     }
+    if (sp.t.ok) {
+        Workspace ws(workspace, workspace_bytes);
+        if (d->dtype == PF_F32)
+            return linear_fwd_tiles<float>(&one, sp.t, d->groups, (const float *)X, (const float *)V, (const float *)U,
+                                           (const float *)bias, (float *)Y, (float *)T_save, ws, s, LinEpilogue{});
+        return linear_fwd_tiles<bf16_t>(&one, sp.t, d->groups, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+                                        (const bf16_t *)bias, (bf16_t *)Y, (bf16_t *)T_save, ws, s, LinEpilogue{});
+    }
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     for (int g = 0; g < d->groups && st == PF_OK; ++g)
         st = linear_fwd_entry(&one, X, (const char *)V + g * in * r * el, (const char *)U + g * out * r * el,
@@ -1044,6 +1121,16 @@ int pf_lowrank_linear_shared_bwd(const pf_linear_shared_desc *d, const void *X, 
     const i64 M = d->M, in = d->n_in, out = d->n_out, r = d->r;
     const int G = d->groups;
     if (!(sp.fused_bwd && dX)) {
+        if (sp.t.ok) {
+            Workspace ws(workspace, workspace_bytes);
+            if (d->dtype == PF_F32)
+                return linear_bwd_tiles<float>(&one, sp.t, G, (const float *)X, (const float *)V, (const float *)U,
+                                               (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU,
+                                               (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
+            return linear_bwd_tiles<bf16_t>(&one, sp.t, G, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+                                            (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
+                                            (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
+        }
         if (d->dtype == PF_F32)
             return shared_bwd_loop<float>(d, sp, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
                                           (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,

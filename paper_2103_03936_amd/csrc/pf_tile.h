@@ -137,8 +137,9 @@ __device__ __forceinline__ uint4 floats_piece(const float *f)
 // outstanding chunk to LDS; both walk the same sequence of chunks.  XF words travel with a chunk's pieces (row
 // scales, taps).  SUM (weight gradients) adds up what passes.
 
-// Matrix stored [rows][K] with k contiguous, leading dimension ld
-template <typename CT, int ROWS, bool SUM = false>
+// Matrix stored [rows][K] with k contiguous, leading dimension ld; SEG: k comes in segments of `seg` (whole pieces), each a
+// matrix of its own that starts `jump` elements after the one before
+template <typename CT, int ROWS, bool SUM = false, bool SEG = false>
 struct LoadKC {
     typedef typename TileEl<CT>::elem elem;
     static constexpr bool KC = true;
@@ -146,6 +147,8 @@ struct LoadKC {
                          CH = ROWS * CPR / TILE_THREADS, LDS = ROWS * PITCH, XF = 1;
     const elem *rp[CH];
     int K, kc, row, kl, ks;
+    int seg = 0;
+    i64 jump = 0;
     float sum[SUM ? CH : 1];
 
     __device__ __forceinline__ void init(const void *p, i64 ld, int rows, int K_, int row0, int kbeg, int tid)
@@ -164,8 +167,9 @@ struct LoadKC {
     __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
     {
         const int k = min(kl + kc, K - V);
+        const i64 at = SEG && seg > 0 ? k + (k / seg) * (jump - seg) : k;
 #pragma unroll
-        for (int i = 0; i < CH; ++i) r[i] = ldg16(rp[i] + k);
+        for (int i = 0; i < CH; ++i) r[i] = ldg16(rp[i] + at);
         kl += BK;
     }
     __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])

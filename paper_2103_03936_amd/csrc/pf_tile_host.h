@@ -42,7 +42,10 @@ struct TileProb {
     const void *A, *B;
     i64 lda, ldb;
     int nb;                // TILE_NN / NT / TN: products of the same shape, operands and output apart by
-    i64 sa, sb, sc, ssums; // sa, sb, sc elements (and ssums row sums)
+    i64 sa, sb, sc, ssums; // sa, sb, sc elements (and ssums row sums), a bias by sbias
+    i64 sbias;
+    int aseg, bseg;        // TILE_NT: an operand comes in segments of this many contraction indices (0: one), each a matrix
+    i64 ajump, bjump;      // of its own, this many elements after the one before
     const float *ascale;
     PixView pa, pb;
     TileOut o;

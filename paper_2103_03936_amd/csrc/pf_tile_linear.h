@@ -11,8 +11,9 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_v
     const TileArgs &a = tile_args(by_value);
     constexpr int BM = CFG::BM, BN = CFG::BN, BK = TileEl<CT>::BK;
     typedef LoadKC<CT, BM> AK;
+    typedef LoadKC<CT, BM, false, true> AKS;
     typedef LoadMC<CT, BM, true> AM;
-    typedef LoadKC<CT, BN> BKC;
+    typedef LoadKC<CT, BN, false, true> BKC;
     typedef LoadMC<CT, BN> BMC;
     constexpr int s1 = TileSize<CT, CFG, AK, BKC>::bytes, s2 = TileSize<CT, CFG, AK, BMC>::bytes,
                   s3 = TileSize<CT, CFG, AM, BMC>::bytes;
@@ -26,10 +27,14 @@ __global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_v
     typedef typename TileEl<CT>::elem elem;
     const elem *A = (const elem *)p.A + t.zb * p.sa, *B = (const elem *)p.B + t.zb * p.sb;
     if (p.type == TILE_NT) {
-        AK la;
+        AKS la;
         BKC lb;
         la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
         lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+        la.seg = p.aseg;
+        la.jump = p.ajump;
+        lb.seg = p.bseg;
+        lb.jump = p.bjump;
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
         tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
             put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);

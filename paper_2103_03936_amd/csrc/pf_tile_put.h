@@ -43,7 +43,7 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
         nv = min(V, p.N - n);
     }
     elem *c = (elem *)o.C;
-    const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask, *bias = (const elem *)o.bias;
+    const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask, *bias = o.bias ? (const elem *)o.bias + zb * p.sbias : nullptr;
     const float sc = o.scale ? o.scale[m] : 1.f, sh = o.shift ? o.shift[m] : 0.f;
     if (o.scale || o.shift) {
 #pragma unroll

@@ -5,6 +5,7 @@ import pytest
 
 import test_gpu_conv
 import test_gpu_linear
+import test_gpu_linear_shared
 import test_gpu_lstm
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,10 @@ def test_conv(shape, dtype):
 @pytest.mark.parametrize("shape", [(33, 9, 5, 4), (70, 41, 38, 9), (130, 700, 644, 161)])
 def test_lstm_cell(shape, groups):
     test_gpu_lstm._cell(*shape, groups, seed=23)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4)])
+def test_linear_shared(shape, dtype):
+    """The middle one splits the contraction of dT, whose layers then lie one after the other instead of side by side."""
+    test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=shape[0] != 700, seed=24)
