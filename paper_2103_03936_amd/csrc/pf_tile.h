@@ -9,7 +9,10 @@
 // it is written to LDS; what lies past K is written as zero, what lies past M or N is never stored.
 //
 // The pieces of NS chunks of the contraction are in flight in registers while one of two LDS buffers is multiplied
-// and the other is filled: one barrier per chunk.  A chunk is 64 (bf16) or 32 (float) deep, so that a workgroup has
+// and the other is filled: one barrier per chunk.  The main loop has no condition on its loads (a load past the last
+// chunk repeats a valid address), and the last chunks have a copy of their own: with a load that may or may not have
+// been issued the compiler can only wait for all of them (8192 x 2048 x 512, bf16, 128 x 128 tiles: 45 -> 33 us, 510
+// TFLOP/s; the fragments' LDS traffic, 96 KB per chunk at 128 bytes per clock, is then what bounds them).  A chunk is 64 (bf16) or 32 (float) deep, so that a workgroup has
 // 16 to 64 KB outstanding: with few workgroups per compute unit it is the latency of the loads, not their number, that
 // bounds these products.  float sums every chunk on its own before adding it to the total (the rounding error then
 // grows with K / 32).
@@ -36,6 +39,11 @@ struct TileEl<float> {
 template <int BM_, int BN_, int WM_, int WN_, int NS_>
 struct TileCfg {
     static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, WK = 4 / (WM_ * WN_);
+    // Wavefronts per SIMD that a kernel of plain products is compiled for: the registers would allow fewer if the compiler
+    // had its way (float, 64 x 64: one workgroup per compute unit -> three, 8192 x 1024 x 256 60 -> 49 us, 88 TFLOP/s)
+    template <typename CT>
+    static constexpr int OCC = sizeof(CT) == 2 ? (BM_ * BN_ <= 64 * 64 ? 4 : 2)
+                                               : (BM_ * BN_ <= 32 * 32 ? 3 : BM_ * BN_ <= 64 * 128 ? 2 : 1);
 };
 
 constexpr int TILE_THREADS = 256;
@@ -60,30 +68,19 @@ __device__ __forceinline__ void stg16(void *p, uint4 v)
 template <int EB>
 __device__ __forceinline__ uint4 piece_shift(uint4 r, int s)
 {
-    const int b = 8 * EB * s; // bits
-    if (b == 0) return r;
-    uint64_t lo = (uint64_t)r.y << 32 | r.x, hi = (uint64_t)r.w << 32 | r.z, l = 0, h = 0;
-    if (b > 0) {
-        if (b < 64) {
-            l = lo >> b | hi << (64 - b);
-            h = hi >> b;
-        } else if (b == 64) {
-            l = hi;
-        } else if (b < 128) {
-            l = hi >> (b - 64);
-        }
-    } else {
-        const int c = -b;
-        if (c < 64) {
-            h = hi << c | lo >> (64 - c);
-            l = lo << c;
-        } else if (c == 64) {
-            h = lo;
-        } else if (c < 128) {
-            h = lo << (c - 64);
-        }
-    }
-    return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+    // towards the front by s >= 0; a shift to the back is one to the front of the piece with four zero words before it
+    const int b = 8 * EB * s + (s < 0 ? 128 : 0); // bits
+    const bool back = s < 0;
+    const uint32_t w0 = back ? 0u : r.x, w1 = back ? 0u : r.y, w2 = back ? 0u : r.z, w3 = back ? 0u : r.w;
+    const uint32_t w4 = back ? r.x : 0u, w5 = back ? r.y : 0u, w6 = back ? r.z : 0u, w7 = back ? r.w : 0u;
+    if (b >= 128 || b < 0) return make_uint4(0, 0, 0, 0);
+    const bool q1 = b & 32, q2 = b & 64;
+    const uint32_t a0 = q2 ? w2 : w0, a1 = q2 ? w3 : w1, a2 = q2 ? w4 : w2, a3 = q2 ? w5 : w3, a4 = q2 ? w6 : w4,
+                   a5 = q2 ? w7 : w5;
+    const uint32_t c0 = q1 ? a1 : a0, c1 = q1 ? a2 : a1, c2 = q1 ? a3 : a2, c3 = q1 ? a4 : a3, c4 = q1 ? a5 : a4;
+    const int f = b & 31;
+    return make_uint4((uint32_t)((((uint64_t)c1 << 32) | c0) >> f), (uint32_t)((((uint64_t)c2 << 32) | c1) >> f),
+                      (uint32_t)((((uint64_t)c3 << 32) | c2) >> f), (uint32_t)((((uint64_t)c4 << 32) | c3) >> f));
 }
 
 // Masks of a piece's elements are bytes (bit e: keep element e); a table in LDS holds the piece-wide mask of every byte.
@@ -172,9 +169,10 @@ struct LoadKC {
         for (int i = 0; i < CH; ++i) r[i] = ldg16(rp[i] + at);
         kl += BK;
     }
+    template <bool EDGE>
     __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
-        const bool tail = ks + BK > K;
+        const bool tail = EDGE && ks + BK > K;
         const int s = ks + kc - min(ks + kc, K - V);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
@@ -244,9 +242,10 @@ struct LoadMC {
         }
         kl += BK;
     }
+    template <bool EDGE>
     __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
-        const bool tail = ks + BK > K;
+        const bool tail = EDGE && ks + BK > K;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
@@ -418,9 +417,10 @@ struct LoadPixMC {
         }
         kl += BK;
     }
+    template <bool EDGE>
     __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
-        const bool tail = ks + BK > K;
+        const bool tail = EDGE && ks + BK > K;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
@@ -517,6 +517,7 @@ struct LoadPixKC {
         lpc += CPR;
         wrap(limg, lpc);
     }
+    template <bool EDGE>
     __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
     {
         const int b = min(simg, N - 1) * image + spc * V;
@@ -527,7 +528,7 @@ struct LoadPixKC {
                 const int off = b + ro[i], s = off - min(max(off, 0), last);
                 if (s != 0) v = piece_shift<sizeof(elem)>(v, min(max(s, -V), V));
                 if (masked) v = MaskTable<V>::apply(lut, tmask[tap[i] + spc], v);
-                if (simg >= img1) v = make_uint4(0, 0, 0, 0);
+                if (EDGE && simg >= img1) v = make_uint4(0, 0, 0, 0);
             }
             *(uint4 *)&lds[(row + i * (TILE_THREADS / CPR)) * PITCH + kc] = v;
             if (SUM) {
@@ -603,77 +604,101 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, int nch, unsigned c
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    if (nch > 0) { // (an empty contraction reads nothing)
+    auto load = [&](int st) __attribute__((always_inline)) {
+        la.load(ra[st], xa[st]);
+        lb.load(rb[st], xb[st]);
+    };
+    auto compute = [&](int cur) __attribute__((always_inline)) {
+        if constexpr (sizeof(elem) == 2) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            la.load(ra[s], xa[s]);
-            lb.load(rb[s], xb[s]);
+            for (int q = 0; q < STEPS; ++q) {
+                const int step = wk * STEPS + q;
+                bf16x8_t a[MI], b[NI];
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+                    a[i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, step, lane);
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    b[j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, step, lane);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+            }
+        } else {
+            f32x4_t a[STEPS][MI], b[STEPS][NI];
+#pragma unroll
+            for (int q = 0; q < STEPS; ++q) {
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+                    a[q][i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, wk * STEPS + q, lane);
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    b[q][j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, wk * STEPS + q, lane);
+            }
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    f32x16_t t;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) t[v] = 0.f;
+#pragma unroll
+                    for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            t = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i][e], b[q][j][e], t, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] += t[v];
+                }
         }
-        la.store(As[0], ra[0], xa[0]);
-        lb.store(Bs[0], rb[0], xb[0]);
-        la.load(ra[0], xa[0]);
-        lb.load(rb[0], xb[0]);
+    };
+#define TILE_STORE(EDGE, st)                                      \
+    {                                                             \
+        la.template store<EDGE>(As[(st) & 1], ra[(st) % NS], xa[(st) % NS]); \
+        lb.template store<EDGE>(Bs[(st) & 1], rb[(st) % NS], xb[(st) % NS]); \
     }
-    __syncthreads();
-    for (int c = 0; c < nch; c += NS) {
+    if (nch > NS) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) load(s);
+        TILE_STORE(false, 0)
+        load(0);
+        __syncthreads();
+        int c = 0;
+        for (; c + NS + 1 < nch; c += NS) {
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                TILE_STORE(false, s + 1)
+                load((s + 1) % NS); // (past the last chunk in the last round: read, never used)
+                compute(s & 1);
+                __syncthreads();
+            }
+        }
+#pragma unroll
+        for (int s = 0; s <= NS; ++s) {
+            if (c + s < nch) {
+                if (s < NS && c + s + 1 < nch) TILE_STORE(true, s + 1)
+                compute(s & 1);
+                __syncthreads();
+            }
+        }
+    } else { // (an empty contraction reads nothing)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (s < nch) load(s);
+        if (nch > 0) TILE_STORE(true, 0)
+        __syncthreads();
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if (c + s < nch) {
-                const int cur = s & 1, nx = (s + 1) % NS;
-                if (c + s + 1 < nch) {
-                    la.store(As[cur ^ 1], ra[nx], xa[nx]);
-                    lb.store(Bs[cur ^ 1], rb[nx], xb[nx]);
-                    la.load(ra[nx], xa[nx]);
-                    lb.load(rb[nx], xb[nx]);
-                }
-                if constexpr (sizeof(elem) == 2) {
-#pragma unroll
-                    for (int q = 0; q < STEPS; ++q) {
-                        const int step = wk * STEPS + q;
-                        bf16x8_t a[MI], b[NI];
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-                            a[i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, step, lane);
-#pragma unroll
-                        for (int j = 0; j < NI; ++j)
-                            b[j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, step, lane);
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-#pragma unroll
-                            for (int j = 0; j < NI; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-                    }
-                } else {
-                    f32x4_t a[STEPS][MI], b[STEPS][NI];
-#pragma unroll
-                    for (int q = 0; q < STEPS; ++q) {
-#pragma unroll
-                        for (int i = 0; i < MI; ++i)
-                            a[q][i] = tile_frag<LA::KC, LA::PITCH>(As[cur], (wm * MI + i) * 32, wk * STEPS + q, lane);
-#pragma unroll
-                        for (int j = 0; j < NI; ++j)
-                            b[q][j] = tile_frag<LB::KC, LB::PITCH>(Bs[cur], (wn * NI + j) * 32, wk * STEPS + q, lane);
-                    }
-#pragma unroll
-                    for (int i = 0; i < MI; ++i)
-#pragma unroll
-                        for (int j = 0; j < NI; ++j) {
-                            f32x16_t t;
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) t[v] = 0.f;
-#pragma unroll
-                            for (int q = 0; q < STEPS; ++q)
-#pragma unroll
-                                for (int e = 0; e < 4; ++e)
-                                    t = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q][i][e], b[q][j][e], t, 0, 0, 0);
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) acc[i][j][v] += t[v];
-                        }
-                }
+            if (s < nch) {
+                if (s + 1 < NS && s + 1 < nch) TILE_STORE(true, s + 1)
+                compute(s & 1);
                 __syncthreads();
             }
         }
     }
+#undef TILE_STORE
     float *Cs = (float *)smem + wk * CFG::BM * (CFG::BN + 4);
 #pragma unroll
     for (int i = 0; i < MI; ++i)

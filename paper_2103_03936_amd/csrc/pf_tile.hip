@@ -1,4 +1,6 @@
 // Tiled matrix products for any shape (pf_tile.h): the choice of tile shape and split, and the sums over splits.
+#include <math.h>
+
 #include "pf_tile_host.h"
 
 namespace pf {
@@ -21,21 +23,19 @@ TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const 
     return p;
 }
 
-// A chunk costs a compute unit `work` cycles (its matrix instructions, or the LDS traffic of its fragments) when several
-// workgroups keep it busy, and at least `lat` (the next chunk's loads, the LDS round trip, the barrier) when one is
-// alone; every split costs a partial sum to write and to read, and the first of them one more launch.
+// Clocks of a compute unit, measured over products of 2000 to 16000 rows and contractions of 256 to 4096: `work` is what a
+// chunk of the contraction costs a compute unit that several workgroups keep busy (the LDS traffic of the fragments for
+// bf16, the matrix instructions for float), `tile` what a tile costs besides (finding it, the first loads, the store),
+// `one` how long a chunk takes a workgroup that is alone.  Every split costs a partial sum to write and to read, and the
+// first of them one more launch.
 struct ChunkCost {
-    double work, one;
+    double work, tile, one;
 };
 static ChunkCost chunk_cost(bool bf, TileShape sh)
 {
-    const double bm = SHAPES[sh].bm, bn = SHAPES[sh].bn;
-    const double mma = (bm / 32) * (bn / 32) * (bf ? 4 * 32 : 16 * 64) / 4.0;
-    const double wm = bm == 32 ? 1 : 2, wn = bn == 32 ? 1 : 2;
-    const double lds = bm * wn + bn * wm + bm + bn;
-    const double lat = bf ? 350 : 300;
-    const double work = mma > lds ? mma : lds;
-    return ChunkCost{work, work > lat ? work : lat};
+    static const ChunkCost costs[2][4] = {{{469, 910, 400}, {1608, 1100, 1200}, {3440, 2140, 2600}, {6120, 20000, 5500}},
+                                          {{282, 260, 380}, {600, 1000, 650}, {1000, 4800, 1100}, {1850, 8000, 1850}}};
+    return costs[bf][sh];
 }
 
 TilePlan plan_tiles(int dtype, i64 M, i64 N, i64 K, int max_split)
@@ -56,7 +56,7 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
         const i64 bm = SHAPES[sh].bm, bn = SHAPES[sh].bn;
         for (int most = 2; most <= (1 << 20); most *= 2) { // chunks a workgroup of a split product may have
             TileGroup g = {sh, {1, 1, 1, 1}, 0};
-            double total = 0, longest = 0, part = 0;
+            double total = 0, longest = 0, part = 0, count = 0;
             bool any = false, last = true;
             for (int i = 0; i < n; ++i) {
                 const i64 tiles = ((need[i].M + bm - 1) / bm) * ((need[i].N + bn - 1) / bn);
@@ -72,10 +72,12 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
                 }
                 if (need[i].split && chunks > most) last = false;
                 g.ksplit[i] = (int)ks;
-                total += (double)tiles * ks * (per * cc.work + 500 + bm * bn / 32.0);
-                if (per * cc.one > longest) longest = per * cc.one;
+                total += (double)tiles * ks * (per * cc.work + cc.tile);
+                count += (double)tiles * ks;
+                if (per * cc.one + cc.tile > longest) longest = per * cc.one + cc.tile;
             }
-            g.cost = (total / 256 > longest ? total / 256 : longest) + 3000 + (any ? 6000 + part / 2000 : 0);
+            const double each = count > 0 ? ceil(count / 256) * (total / count) : 0; // the fullest compute unit's share
+            g.cost = (each > longest ? each : longest) + 3000 + (any ? 6000 + part / 2000 : 0);
             if (g.cost < best.cost) best = g;
             if (last) break;
         }

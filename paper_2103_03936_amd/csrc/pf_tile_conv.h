@@ -27,7 +27,8 @@ __device__ __forceinline__ void pack_filters(const TileProb &p, int block, int t
 
 // WG: the launch has weight gradients (tiles of CFGW).  Launches without run kernels without their registers.
 template <typename CT, class CFG, class CFGW, bool GATHER, bool WG>
-__global__ __launch_bounds__(TILE_THREADS) void tile_conv_kernel(TileArgs by_value)
+__global__ __launch_bounds__(TILE_THREADS, sizeof(CT) == 2 && CFG::BM * CFG::BN <= 64 * 64 ? 3 : 2) void
+tile_conv_kernel(TileArgs by_value)
 {
     const TileArgs &a = tile_args(by_value);
     constexpr int BM = CFG::BM, BN = CFG::BN, BK = TileEl<CT>::BK;
@@ -134,8 +135,8 @@ static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
 template <typename CT>
 int launch_conv_t(hipStream_t s, const char *name, TileShape shape, TileShape wg, const TileArgs &a)
 {
-    typedef TileCfg<64, 64, 2, 2, 4> S64;
-    typedef TileCfg<32, 128, 1, 4, 4> W32;
+    typedef TileCfg<64, 64, 2, 2, 2> S64;
+    typedef TileCfg<32, 128, 1, 4, 2> W32;
     switch (shape) {
     case TS_32x64: return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, W32>(s, name, a); // (forward, or at most 32 channels)
     case TS_64: return wg == TS_32x128 ? launch_conv<CT, S64, W32>(s, name, a) : launch_conv<CT, S64, S64>(s, name, a);

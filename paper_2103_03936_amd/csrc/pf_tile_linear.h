@@ -6,7 +6,7 @@
 namespace pf {
 
 template <typename CT, class CFG>
-__global__ __launch_bounds__(TILE_THREADS) void tile_linear_kernel(TileArgs by_value)
+__global__ __launch_bounds__(TILE_THREADS, CFG::template OCC<CT>) void tile_linear_kernel(TileArgs by_value)
 {
     const TileArgs &a = tile_args(by_value);
     constexpr int BM = CFG::BM, BN = CFG::BN, BK = TileEl<CT>::BK;
@@ -70,7 +70,7 @@ int launch_linear_t(hipStream_t s, const char *name, TileShape shape, const Tile
 {
     switch (shape) {
     case TS_32: return launch_linear<CT, TileCfg<32, 32, 1, 1, 4>>(s, name, a);
-    case TS_64: return launch_linear<CT, TileCfg<64, 64, 2, 2, 4>>(s, name, a);
+    case TS_64: return launch_linear<CT, TileCfg<64, 64, 2, 2, 2>>(s, name, a);
     case TS_128x64: return launch_linear<CT, TileCfg<128, 64, 2, 2, 2>>(s, name, a);
     case TS_128: return launch_linear<CT, TileCfg<128, 128, 2, 2, 2>>(s, name, a);
     default: return PF_ERR_UNSUPPORTED;
