@@ -13,13 +13,20 @@
 // (lstm_zgates_kernel, lstm_dhgates_kernel): three launches per slot.  All parameter gradients are formed once per
 // layer over all T B rows after the backward wavefront.  The factors are copied once per call into the order the
 // kernels read them in.  A single layer over a sequence (pf_lowrank_lstm_seq_*) is a stack of one layer.
+//
+// Where the registers of the chip hold all factors, the whole recurrence is one launch per direction instead
+// (pf_lstm_persist.hip); the schedule below is for single steps and for what is too wide for that.
+#include <algorithm>
 #include <vector>
 
 #include "pf_gemm.h"
+#include "pf_lstm_persist.h"
 #include "pf_skinny.h"
 #include "pf_common.h"
 
 namespace pf {
+
+LstmRecurrence lstm_recurrence = {};
 
 constexpr int ST_MAX_LAYERS = 4;
 constexpr int ST_RANK_MMA_ROWS = 128; // T B from which the weight gradients go to the matrix unit
@@ -841,8 +848,23 @@ static int stack_fwd_slot(const StackGeom &g, const StackPtrs &p, const StackPac
     return st;
 }
 
+// ---- the recurrence in one launch, where the device can hold it ----
+static LstmGeom run_geom(const StackGeom &g) { return LstmGeom{g.T, g.B, g.h, g.r, g.G, g.gr, g.L}; }
+static void run_layers(const StackGeom &g, const StackPtrs &p, LstmRunLayer *out)
+{
+    for (int l = 0; l < g.L; ++l) {
+        LstmRunLayer &y = out[l];
+        y = LstmRunLayer{};
+        y.Vx = p.Vx[l], y.Ux = p.Ux[l], y.Vh = p.Vh[l], y.Uh = p.Uh[l];
+        y.bias = g.has_bias ? p.bias[l] : nullptr;
+        y.h0 = p.h0[l], y.c0 = p.c0[l];
+        y.h_all = p.h_all[l], y.c_all = p.c_all[l], y.gates = p.gates_all[l];
+        y.Tx = p.Tx_all[l], y.Th = p.Th_all[l];
+    }
+}
+
 struct StackPlan {
-    size_t n_zx0, n_part, n_part2, n_dT, n_dz, n_pack_f, n_pack_b, fwd_bytes, bwd_bytes;
+    size_t n_zx0, n_part, n_part2, n_dT, n_dz, n_pack_f, n_pack_b, n_run_f, n_run_b, fwd_bytes, bwd_bytes;
 };
 
 // per-layer tensors of the backward pass
@@ -1072,9 +1094,16 @@ static int plan_stack(const StackGeom &g, StackPlan *out)
     p.n_pack_f = stack_pack(g, none, false, nullptr, nullptr, true, nullptr, nullptr);
     p.n_pack_b = stack_pack(g, none, true, nullptr, nullptr, true, nullptr, nullptr);
     p.fwd_bytes = align_up(p.n_zx0 * sizeof(float)) + align_up(p.n_part * sizeof(float)) + align_up(p.n_pack_f * sizeof(float));
-    p.bwd_bytes = (size_t)g.L * (align_up(p.n_dz * sizeof(float)) + 2 * align_up(p.n_dT * sizeof(float))) +
-                  align_up(p.n_part * sizeof(float)) + align_up(p.n_part2 * sizeof(float)) +
+    const size_t kept = (size_t)g.L * (align_up(p.n_dz * sizeof(float)) + 2 * align_up(p.n_dT * sizeof(float)));
+    p.bwd_bytes = kept + align_up(p.n_part * sizeof(float)) + align_up(p.n_part2 * sizeof(float)) +
                   align_up(p.n_pack_b * sizeof(float));
+    // (the one-launch recurrence: its exchange buffers instead of slices and copied factors)
+    if (lstm_recurrence.run) {
+        p.n_run_f = lstm_recurrence.floats(run_geom(g), false);
+        p.n_run_b = lstm_recurrence.floats(run_geom(g), true);
+        p.fwd_bytes = std::max(p.fwd_bytes, align_up(p.n_part * sizeof(float)) + align_up(p.n_run_f * sizeof(float)));
+        p.bwd_bytes = std::max(p.bwd_bytes, kept + align_up(p.n_part * sizeof(float)) + align_up(p.n_run_b * sizeof(float)));
+    }
     *out = p;
     return PF_OK;
 }
@@ -1144,6 +1173,18 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
+    const i64 Mt = (i64)g.T * g.B;
+    const int h = g.h, r = g.r, gr = g.gr;
+    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), false)) {
+        float *part = ws.take<float>(pl.n_part), *run = ws.take<float>(pl.n_run_f);
+        if (!ws.ok()) return PF_ERR_WORKSPACE;
+        st = st_tall(s, "lstm_stack_Tx0=X*Vx", false, Mt, (const float *)x, g.din, p.Vx[0], gr, g.din, gr, p.Tx_all[0], gr,
+                     nullptr, part);
+        if (st != PF_OK) return st;
+        LstmRunLayer layers[ST_MAX_LAYERS];
+        run_layers(g, p, layers);
+        return lstm_recurrence.run(run_geom(g), layers, nullptr, false, run, s);
+    }
     float *zx0 = ws.take<float>(pl.n_zx0);
     float *part = ws.take<float>(pl.n_part);
     float *packed = ws.take<float>(pl.n_pack_f);
@@ -1151,8 +1192,6 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     StackPacked pk = {};
     stack_pack(g, p, false, packed, &pk, false, s, &st);
     if (st != PF_OK) return st;
-    const i64 Mt = (i64)g.T * g.B;
-    const int h = g.h, r = g.r, gr = g.gr;
     // the input path of the first layer for every time step at once
     st = st_tall(s, "lstm_stack_Tx0=X*Vx", false, Mt, (const float *)x, g.din, p.Vx[0], gr, g.din, gr, p.Tx_all[0], gr,
                  nullptr, part);
@@ -1247,16 +1286,30 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x, const 
         b.dTx_all[l] = ws.take<float>(pl.n_dT);
     }
     float *part = ws.take<float>(pl.n_part);
-    float *part2 = ws.take<float>(pl.n_part2);
-    float *packed = ws.take<float>(pl.n_pack_b);
-    if (!ws.ok()) return PF_ERR_WORKSPACE;
-    StackPacked pk = {};
-    stack_pack(g, p, true, packed, &pk, false, s, &st);
-    if (st != PF_OK) return st;
-    StackCarry carry = {};
-    for (int u = 0; u < T + L - 1 + (pk.fused_z ? 1 : 0) && st == PF_OK; ++u) // fused: one more slot for the first layer's dh0
-        st = stack_bwd_slot(g, p, pk, b, (const float *)dh_top, u, part, pl.n_part, part2, pl.n_part2, carry, false, s,
-                            nullptr, nullptr);
+    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), true)) {
+        float *run = ws.take<float>(pl.n_run_b);
+        if (!ws.ok()) return PF_ERR_WORKSPACE;
+        LstmRunLayer layers[ST_MAX_LAYERS];
+        run_layers(g, p, layers);
+        for (int l = 0; l < L; ++l) {
+            LstmRunLayer &y = layers[l];
+            y.dhT = b.dhT[l], y.dcT = b.dcT[l];
+            y.dh0 = b.dh0[l], y.dc0 = b.dc0[l];
+            y.dz = b.dz_all[l], y.dTh = b.dTh_all[l], y.dTx = b.dTx_all[l];
+        }
+        st = lstm_recurrence.run(run_geom(g), layers, (const float *)dh_top, true, run, s);
+    } else {
+        float *part2 = ws.take<float>(pl.n_part2);
+        float *packed = ws.take<float>(pl.n_pack_b);
+        if (!ws.ok()) return PF_ERR_WORKSPACE;
+        StackPacked pk = {};
+        stack_pack(g, p, true, packed, &pk, false, s, &st);
+        if (st != PF_OK) return st;
+        StackCarry carry = {};
+        for (int u = 0; u < T + L - 1 + (pk.fused_z ? 1 : 0) && st == PF_OK; ++u) // fused: one more slot for the first layer's dh0
+            st = stack_bwd_slot(g, p, pk, b, (const float *)dh_top, u, part, pl.n_part, part2, pl.n_part2, carry, false, s,
+                                nullptr, nullptr);
+    }
     if (st != PF_OK) return st;
     // the input path of the first layer for all steps at once
     const i64 Mt = (i64)T * B;

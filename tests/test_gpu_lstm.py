@@ -507,3 +507,17 @@ def test_layer_stack_long_sequences_edges(shape):
     import paper_2103_03936_amd as pf
     T, B, d, h, r, L, G = shape
     _check_stack_case(pf, T, B, d, h, r, L, G, True, 77, f"long stack edge {shape}")
+
+
+@pytest.mark.parametrize("groups", [1, 4])
+@pytest.mark.parametrize("shape", [(3, 4, 24, 31, 7, 1), (2, 5, 16, 33, 8, 2), (3, 8, 40, 64, 32, 3), (2, 12, 20, 97, 33, 2),
+                                   (2, 13, 16, 96, 31, 1), (2, 21, 12, 65, 12, 2), (2, 32, 12, 40, 10, 2), (1, 3, 8, 4, 4, 2),
+                                   (2, 9, 16, 1040, 9, 3), (2, 20, 16, 1040, 9, 3), (2, 32, 16, 1100, 5, 2),
+                                   (2, 2, 16, 1536, 384, 1), (2, 2, 16, 1540, 20, 1), (2, 6, 16, 700, 129, 2)])
+def test_layer_stack_resident_factors_edges(shape, groups):
+    """The recurrence with its factors kept in registers, at its edges: every number of row blocks (batch 4, 8, 12, 20,
+    32), widths and ranks around its groups of 32 indices, one to three slices and column tiles, the largest width and
+    rank, and just past what it takes (the schedule of launches)."""
+    import paper_2103_03936_amd as pf
+    T, B, d, h, r, L = shape
+    _check_stack_case(pf, T, B, d, h, r, L, groups, True, 91, f"resident factors {shape} groups {groups}")
