@@ -18,6 +18,7 @@
 // group tells eight copies of the group flags, and everybody polls one of the copies: 1.9 us over 256 workgroups, where
 // polling one flag per workgroup took 4.6 us (all pollers hit the same few memory channels).
 #include "pf_lstm_persist.h"
+#include "pf_lstm_persist_index.h"
 
 #include <atomic>
 
@@ -349,21 +350,19 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
     const bool in1 = wg < a.n1, in2 = wg < a.n2;
     // the initial states and the first layer's Tx into the lanes' order
     if (in2) {
-        const int nh = hp * 4 * RB, nx = G * rp * 4 * RB;
-        for (i64 e = (i64)wg * LP_NT + tid; e < (i64)L * nh + (i64)T * nx; e += (i64)a.n2 * LP_NT) {
-            const bool state = e < (i64)L * nh;
-            const int n = state ? nh : nx, at = (int)(state ? e : e - (i64)L * nh), which = at / n, o = at - which * n;
+        // (the few states by the last workgroups, which have one element less of the other)
+        for (LpWalk at(hp * 4 * RB, (a.n2 - 1 - wg) * LP_NT + tid, a.n2 * LP_NT); at.row < L; at.next()) {
             int k, m;
-            lp_element<RB>(o, k, m);
-            m = min(m, B - 1);
-            if (state) {
-                const float v = a.l[which].h0[(i64)m * h + min(k, h - 1)];
-                lp_share(lp_xh(a, which, 0) + o, k < h ? v : 0.f);
-            } else {
-                const int q = k / rp, cc = k - q * rp;
-                const float v = a.l[0].Tx[((i64)which * B + m) * gr + q * r + min(cc, r - 1)];
-                lp_share(lp_xt(a, 0, 1, which) + o, cc < r ? v : 0.f);
-            }
+            lp_element<RB>(at.o, k, m);
+            const float v = a.l[at.row].h0[(i64)min(m, B - 1) * h + min(k, h - 1)];
+            lp_share(lp_xh(a, at.row, 0) + at.o, k < h ? v : 0.f);
+        }
+        for (LpWalk at(G * rp * 4 * RB, wg * LP_NT + tid, a.n2 * LP_NT); at.row < T; at.next()) {
+            int k, m;
+            lp_element<RB>(at.o, k, m);
+            const int q = k / rp, cc = k - q * rp;
+            const float v = a.l[0].Tx[((i64)at.row * B + min(m, B - 1)) * gr + q * r + min(cc, r - 1)];
+            lp_share(lp_xt(a, 0, 1, at.row) + at.o, cc < r ? v : 0.f);
         }
         sync.arrive(1, a.n2, 1u);
     }
@@ -618,8 +617,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     }
     if (SL > 1 && in1) { // (these workgroups have waited for the last dT)
         const int nx = rp * 4 * RB;
-        for (int e = wg * LP_NT + tid; e < (2 * L - 1) * T * nx; e += a.n1 * LP_NT) {
-            const int at = e / nx, o = e - at * nx, pr = at / T, t = at - pr * T, l = lp_layer(pr), path = lp_path(pr);
+        for (LpWalk at(nx, wg * LP_NT + tid, a.n1 * LP_NT); at.row < (2 * L - 1) * T; at.next()) {
+            const int o = at.o, pr = at.row / T, t = at.row - pr * T, l = lp_layer(pr), path = lp_path(pr);
             int k, m;
             lp_element<RB>(o, k, m);
             if (k >= r || m >= B) continue;

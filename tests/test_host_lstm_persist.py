@@ -1,0 +1,39 @@
+"""Index arithmetic of the one-launch LSTM recurrence without a GPU (tests/emulation/lstm_persist_host.cpp)."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    if not (os.path.exists(HIPCC) or shutil.which(HIPCC)):
+        pytest.skip("hipcc not found")
+    out = str(tmp_path_factory.mktemp("emu") / "liblstm_persist_host.so")
+    cmd = [HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared",
+           "-I", os.path.join(ROOT, "paper_2103_03936_amd", "csrc"),
+           os.path.join(ROOT, "tests", "emulation", "lstm_persist_host.cpp"), "-o", out]
+    subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
+    return ctypes.CDLL(out)
+
+
+@pytest.mark.parametrize("n,workgroups,rows", [
+    (4 * 384 * 20, 256, 69906),   # forward, a pair per gate: 32 bits end inside
+    (384 * 32, 24, 5 * 34953),    # backward, three layers, sums over slices
+    (384 * 32, 24, 5 * 34952),
+    (32 * 4, 8, 3 * 7),           # a step is many rows
+    (128, 1, 1),
+])
+def test_walk_visits_every_element_once(emu, n, workgroups, rows):
+    """Thread `first` of `step` visits first, first + step, ... below rows * n, also beyond 32 bits."""
+    step, total = 512 * workgroups, rows * n
+    count, last = ctypes.c_longlong(), ctypes.c_longlong()
+    for first in {0, 1, step // 2 + 5, step - 1}:
+        assert emu.emu_walk(n, first, step, rows, ctypes.byref(count), ctypes.byref(last))
+        want = len(range(first, total, step))
+        assert (count.value, last.value) == (want, first + (want - 1) * step if want else -1)
