@@ -389,6 +389,10 @@ int pf_lowrank_lstm_seq_bwd(const pf_lstm_seq_desc *d, const void *x,
 /* Per-layer tensors are passed as HOST arrays of `layers` DEVICE       */
 /* pointers (the arrays are read during the call only); shapes per      */
 /* layer as for the sequence entry points.                              */
+/* Where the factors fit the chip's registers the workgroups of one     */
+/* cooperative launch run all steps and wait for one another.  The waits */
+/* are bounded; should one ever run out (the call has returned by then, */
+/* so no status can say so), every output not yet written is NaN.       */
 /* ------------------------------------------------------------------ */
 typedef struct {
     int64_t T, B, d_in, h, r;

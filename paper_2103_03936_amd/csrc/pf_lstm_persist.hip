@@ -17,7 +17,6 @@
 // The barrier between phases: workgroups count arrivals in eight groups (an atomic each on a line of its own), the last of a
 // group tells eight copies of the group flags, and everybody polls one of the copies: 1.9 us over 256 workgroups, where
 // polling one flag per workgroup took 4.6 us (all pollers hit the same few memory channels).
-#include "pf_lstm_persist.h"
 #include "pf_lstm_persist_index.h"
 
 #include <atomic>
@@ -25,24 +24,6 @@
 namespace pf {
 
 int launch_zero_f32(hipStream_t s, float *p, i64 n);
-
-constexpr int LP_MAX_LAYERS = 4;
-constexpr int LP_NT = 512, LP_WAVES = 8; // threads
-constexpr int LP_GROUPS = 8;             // of workgroups in a barrier
-constexpr int LP_BAR = 2 * LP_GROUPS * 64; // words of one: a line per group counter, then the copies of the flags
-constexpr int LP_SYNC = 2 * LP_BAR + 64;   // both barriers, the word of a failed wait
-
-struct LpArgs {
-    LstmRunLayer l[LP_MAX_LAYERS];
-    const float *dh_top;
-    float *xh, *xt; // exchanged: h (forward; step t at t + 1, the initial state at 0) or dz (backward); T or dT
-    unsigned *sync;
-    i64 xh_step, xt_step; // floats from one step's copy to the next
-    int T, B, h, r, G, gr, L;
-    int hp, rp;           // h and r up to whole groups of 32 contraction indices
-    int n1, n2, nwg;      // tasks (one per workgroup) of the two phases of a slot
-    int nt1;              // 8-column tiles of a T / dT task
-};
 
 // The argument block where the launch put it (indexed by layer, the by-value copy would go to scratch memory).
 __device__ __forceinline__ const LpArgs &lp_args(const LpArgs &a)
@@ -84,8 +65,9 @@ struct LpSync {
                 __hip_atomic_store(flags + threadIdx.x * 64 + g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // All workgroups of a cooperative launch are resident, so all of them arrive; the wait is bounded all the same, and
-    // everyone leaves when one gives up.
+    // All workgroups of a cooperative launch are resident, so all of them arrive; the wait is bounded all the same (by polls, of
+    // about a microsecond each: a process that is suspended does not count), and everyone leaves when one gives up, with NaN in
+    // what it has not written.
     __device__ __forceinline__ bool wait(int b, unsigned epoch)
     {
         if (threadIdx.x < 64) {
@@ -114,10 +96,6 @@ struct LpSync {
         return all;
     }
 };
-
-// Workgroups go to the dies in turn.  Those of one die get neighbouring tasks: they read the same activations and, where a row of
-// the factors is shared by column tiles, the same lines.  (n workgroups take part: a multiple of LP_GROUPS; some have no task)
-__device__ __forceinline__ int lp_task(int wg, int n) { return (wg % LP_GROUPS) * (n / LP_GROUPS) + wg / LP_GROUPS; }
 
 // ------------------------------------------------------------------ a wavefront's product
 // Exchanged matrices [4 RB rows][K]: groups of 32 indices, in each the row blocks, in each 16 index pairs of four rows: lane
@@ -286,15 +264,6 @@ __device__ __forceinline__ float lp_sum(const float *red, int nt, int m, int c)
     return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
 }
 
-// product p of the 2 L - 1 of a slot: layer (p + 1) / 2, its hidden path (p = 0 or odd) or input path
-__device__ __forceinline__ int lp_layer(int p) { return (p + 1) >> 1; }
-__device__ __forceinline__ int lp_path(int p) { return p > 0 && !(p & 1); }
-__device__ __forceinline__ float *lp_xt(const LpArgs &a, int l, int path, int t)
-{
-    return a.xt + ((i64)(2 * l + path) * a.T + t) * a.xt_step;
-}
-__device__ __forceinline__ float *lp_xh(const LpArgs &a, int l, int slot) { return a.xh + ((i64)l * (a.T + 1) + slot) * a.xh_step; }
-
 // element o of an exchanged matrix: row m, index k
 template <int RB>
 __device__ __forceinline__ void lp_element(int o, int &k, int &m)
@@ -366,11 +335,10 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
         }
         sync.arrive(1, a.n2, 1u);
     }
-    // phase 1: product tpr, columns tcol .. tcol + tncol - 1; groups tg0 .. of h
-    const int per_block = (G * rp / 8 + a.nt1 - 1) / a.nt1, task1 = lp_task(wg, a.n1);
-    const bool has1 = in1 && task1 < (2 * L - 1) * per_block;
-    const int tpr = has1 ? task1 / per_block : 0, tl = lp_layer(tpr), tpath = lp_path(tpr);
-    const int tcol = has1 ? (task1 - tpr * per_block) * 8 * a.nt1 : 0, tncol = min(8 * a.nt1, G * rp - tcol);
+    // phase 1: columns tcol .. tcol + tncol - 1 of a product; groups tg0 .. of h
+    const LpColumns cols = lp_columns(a, wg, a.n1, G * rp, 8, 1);
+    const bool has1 = cols.has;
+    const int tl = cols.l, tpath = cols.path, tcol = cols.col, tncol = cols.n;
     const int tper = (hp / 32 + LP_WAVES - 1) / LP_WAVES, tg0 = w * tper, tng = has1 ? min(tper, hp / 32 - tg0) : 0;
     float wt[TN][TKG][4];
     {
@@ -382,9 +350,9 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
         });
     }
     // phase 2: units u0 .. of layer zl
-    const int UT = (hp + U - 1) / U, task2 = lp_task(wg, a.n2);
-    const bool has2 = in2 && task2 < L * UT;
-    const int zl = has2 ? task2 / UT : 0, u0 = has2 ? (task2 - zl * UT) * U : 0, zx = w >> 2, zgroups = rp / 32;
+    const LpUnits units = lp_units(a, wg, a.n2, U);
+    const bool has2 = units.has;
+    const int zl = units.l, u0 = units.u0, zx = w >> 2, zgroups = rp / 32;
     const int zper = G4 ? zgroups : (zgroups + 3) / 4, zg0 = (G4 ? (w & 3) * zgroups : (w & 3) * zper);
     const int zng = !has2 ? 0 : G4 ? zgroups : min(zper, zgroups - zg0);
     float wz[NT][KG][8];
@@ -408,9 +376,11 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
 #pragma unroll
         for (int g = 0; g < 4; ++g) pb[g] = a.l[zl].bias ? a.l[zl].bias[(i64)g * h + un] : 0.f;
     }
-    for (int slot = 0; slot < T + L - 1; ++slot) {
+    int slot = 0;
+    bool lost = false; // a wait gave up
+    for (; slot < T + L - 1; ++slot) {
         if (in1) {
-            if (!sync.wait(1, slot + 1)) return;
+            if ((lost = !sync.wait(1, slot + 1))) break;
             const int t = slot - tl;
             if (has1 && t >= 0 && t < T) {
                 f32x4_t acc[TN][RB];
@@ -424,7 +394,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
         }
         if (in2) {
             const int t = slot - zl;
-            if (!sync.wait(0, slot + 1)) return;
+            if ((lost = !sync.wait(0, slot + 1))) break;
             float gv[4] = {}, cv = 0.f, hv = 0.f;
             const bool active = has2 && t >= 0 && t < T;
             if (active) {
@@ -464,6 +434,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
             }
         }
     }
+    if (lost) lp_void_fwd(a, cols, units, slot, tid);
 }
 
 // ------------------------------------------------------------------ backward
@@ -486,9 +457,9 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     LpSync sync = {a.sync, wg, &ok};
     const bool in1 = wg < a.n1, in2 = wg < a.n2;
     // phase 1: units u0 .. of layer zl
-    const int UT = (hp + 16 * NT - 1) / (16 * NT), task1 = lp_task(wg, a.n1);
-    const bool has1 = in1 && task1 < L * UT;
-    const int zl = has1 ? task1 / UT : 0, u0 = has1 ? (task1 - zl * UT) * 16 * NT : 0;
+    const LpUnits units = lp_units(a, wg, a.n1, 16 * NT);
+    const bool has1 = units.has;
+    const int zl = units.l, u0 = units.u0;
     const bool two = zl + 1 < L;
     const int zx = two ? w >> 2 : 0, zgroups = G * rp / 32, parts = two ? 4 : 8, zper = (zgroups + parts - 1) / parts;
     const int zg0 = (w & (parts - 1)) * zper, zng = has1 ? min(zper, zgroups - zg0) : 0;
@@ -504,12 +475,10 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
             },
             [&](int g) __attribute__((always_inline)) { return r - (G4 ? 32 * g % rp : 32 * g); });
     }
-    // phase 2: product tpr (of gate tq, or slice tq of the contraction), columns tcol .. ; groups tg0 .. of dz
-    constexpr int TB = G4 ? 4 : SL;
-    const int per_block = (rp / TW + a.nt1 - 1) / a.nt1, task2 = lp_task(wg, a.n2);
-    const bool has2 = in2 && task2 < (2 * L - 1) * TB * per_block;
-    const int tb = has2 ? task2 / per_block : 0, tq = tb % TB, tpr = tb / TB, tl = lp_layer(tpr), tpath = lp_path(tpr);
-    const int tcol = has2 ? (task2 - tb * per_block) * TW * a.nt1 : 0, tncol = min(TW * a.nt1, rp - tcol);
+    // phase 2: columns tcol .. of a product (of gate tq, or slice tq of the contraction); groups tg0 .. of dz
+    const LpColumns cols = lp_columns(a, wg, a.n2, rp, TW, G4 ? 4 : SL);
+    const bool has2 = cols.has;
+    const int tq = cols.q, tl = cols.l, tpath = cols.path, tcol = cols.col, tncol = cols.n;
     const int tgroups = (G4 ? hp : 4 * hp) / 32, tslice = (tgroups + SL - 1) / SL, tper = (tslice + LP_WAVES - 1) / LP_WAVES;
     const int ts0 = G4 ? 0 : tq * tslice, tg0 = ts0 + w * tper;
     const int tng = has2 ? min(tper, min(ts0 + tslice, tgroups) - tg0) : 0;
@@ -525,7 +494,9 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     float dcs[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) dcs[it] = 0.f;
-    for (int u = 0; u < T + L; ++u) {
+    int u = 0;
+    bool lost = false; // a wait gave up
+    for (; u < T + L; ++u) {
         if (in1) {
             const LstmRunLayer &y = a.l[zl];
             const int t = T - 1 - (u - (L - 1 - zl));
@@ -552,7 +523,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                     if (t == T - 1) dcs[it] = in && y.dcT ? y.dcT[idx] : 0.f;
                 }
             }
-            if (u > 0 && !sync.wait(1, u)) return;
+            if (u > 0 && (lost = !sync.wait(1, u))) break;
             if (active) {
                 f32x4_t acc[NT][RB];
                 lp_zero(acc);
@@ -602,7 +573,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
         }
         if (in2 && u + 1 < T + L) {
             const int t = T - 1 - (u - (L - 1 - tl));
-            if (!sync.wait(0, u + 1)) return;
+            if ((lost = !sync.wait(0, u + 1))) break;
             if (has2 && t >= 0 && t < T) {
                 f32x4_t acc[TN][RB];
                 lp_zero(acc);
@@ -614,6 +585,10 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
             }
             sync.arrive(1, a.n2, u + 1);
         }
+    }
+    if (lost) {
+        lp_void_bwd(a, cols, units, u, SL, RB, wg, tid);
+        return;
     }
     if (SL > 1 && in1) { // (these workgroups have waited for the last dT)
         const int nx = rp * 4 * RB;
@@ -647,62 +622,6 @@ static int lp_cus()
     return n;
 }
 
-static int lp_row_blocks(int B) { return B <= 4 ? 1 : B <= 8 ? 2 : B <= 12 ? 3 : B <= 20 ? 5 : 8; }
-
-struct LpPlan {
-    int RB, NT, SL, nt1, n1, n2, nwg, hp, rp; // NT 0: the registers of the chip do not hold the factors
-    i64 xh_step, xt_step;
-    size_t floats;
-};
-// One task per workgroup and phase, the smallest tiles that come out at no more tasks than compute units.  The bounds are the
-// kernels': groups of 32 contraction indices per wavefront, tiles, and what fits beside the accumulators of RB row blocks.
-static LpPlan lp_plan(const LstmGeom &g, bool bwd, int cus)
-{
-    LpPlan p = {};
-    p.RB = lp_row_blocks(g.B);
-    p.hp = (g.h + 31) & ~31;
-    p.rp = (g.r + 31) & ~31;
-    p.xh_step = (i64)(bwd ? 4 : 1) * p.hp * 4 * p.RB;
-    p.xt_step = (i64)(bwd && g.G == 1 ? 3 : 1) * g.G * p.rp * 4 * p.RB;
-    p.floats = (size_t)p.xh_step * g.L * (g.T + 1) + (size_t)p.xt_step * 2 * g.L * g.T + LP_SYNC;
-    if (p.hp > 1536 || p.rp > 384 || (g.G != 1 && p.RB == 8)) return p;
-    const int products = 2 * g.L - 1;
-    int tasks = 0;
-    p.SL = p.nt1 = 1;
-    if (bwd && g.G == 1) {
-        // dT = dz U contracts 4 h: tiles of 16 columns, up to three slices (the readers add them up; one slice of 8 columns per
-        // workgroup read three times the activations: 9 instead of 5 us at 1500 units)
-        const int groups = p.hp / 8, cols = p.rp / 16;
-        for (p.SL = 3; p.SL > 1; --p.SL)
-            if (products * cols * p.SL <= cus && groups >= LP_WAVES * p.SL) break;
-        tasks = products * cols * p.SL;
-        const int per_wave = ((groups + p.SL - 1) / p.SL + LP_WAVES - 1) / LP_WAVES;
-        if (tasks > cus || per_wave > (p.SL == 3 ? 8 : 12)) return p;
-    } else {
-        const int blocks = products * (bwd ? g.G : 1), cols = (bwd ? 1 : g.G) * p.rp / 8, most = g.G == 1 ? 1 : 3;
-        for (p.nt1 = 1;; ++p.nt1) {
-            tasks = blocks * ((cols + p.nt1 - 1) / p.nt1);
-            if (tasks <= cus) break;
-            if (p.nt1 == most) return p;
-        }
-    }
-    int units = 0, most = g.G != 1 ? 1 : bwd ? (p.RB == 8 ? 1 : 2) : p.RB == 8 ? 2 : p.RB == 5 ? 3 : 5, NT = 1;
-    for (; NT <= most; ++NT) {
-        const int U = bwd || g.G != 1 ? 16 * NT : 4 * NT;
-        units = g.L * ((p.hp + U - 1) / U);
-        if (units <= cus) break;
-    }
-    if (units > cus) return p;
-    p.NT = NT == 4 ? 5 : NT;
-    if (p.NT == 5) units = g.L * ((p.hp + 19) / 20);
-    units = (units + LP_GROUPS - 1) / LP_GROUPS * LP_GROUPS; // (the barrier's groups are even)
-    tasks = (tasks + LP_GROUPS - 1) / LP_GROUPS * LP_GROUPS;
-    p.n1 = bwd ? units : tasks;
-    p.n2 = bwd ? tasks : units;
-    p.nwg = p.n1 > p.n2 ? p.n1 : p.n2;
-    if (p.nwg > cus) p.NT = 0;
-    return p;
-}
 // (sizes do not depend on the device: a workspace may be asked for before one is chosen)
 static size_t lp_floats(const LstmGeom &g, bool bwd) { return lp_plan(g, bwd, 256).floats; }
 static bool lp_fits(const LstmGeom &g, bool bwd)
@@ -750,17 +669,8 @@ static LpKernel lp_kernel(const LpPlan &p, int G, bool bwd)
 static int lp_run(const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, bool bwd, float *ws, hipStream_t s)
 {
     const LpPlan p = lp_plan(g, bwd, lp_cus());
-    LpArgs a = {};
-    for (int q = 0; q < g.L; ++q) a.l[q] = l[q];
-    a.dh_top = dh_top;
-    a.xh = ws;
-    a.xt = a.xh + p.xh_step * g.L * (g.T + 1);
-    a.sync = (unsigned *)(a.xt + p.xt_step * 2 * g.L * g.T);
-    a.xh_step = p.xh_step;
-    a.xt_step = p.xt_step;
-    a.T = g.T, a.B = g.B, a.h = g.h, a.r = g.r, a.G = g.G, a.gr = g.gr, a.L = g.L;
-    a.hp = p.hp, a.rp = p.rp;
-    a.n1 = p.n1, a.n2 = p.n2, a.nwg = p.nwg, a.nt1 = p.nt1;
+    LpArgs a;
+    lp_fill(a, p, g, l, dh_top, ws);
     int st = launch_zero_f32(s, (float *)a.sync, LP_SYNC);
     if (st != PF_OK) return st;
     return lp_launch(lp_kernel(p, g.G, bwd), a, bwd, s);

@@ -1,9 +1,74 @@
-// Index arithmetic of the one-launch LSTM recurrence (pf_lstm_persist.hip), for device and host.
+// The one-launch LSTM recurrence (pf_lstm_persist.hip): plan, arguments, and which workgroup has what.  Host and device.
 #pragma once
 
 #include "pf_lstm_persist.h"
 
 namespace pf {
+
+constexpr int LP_MAX_LAYERS = 4;
+constexpr int LP_NT = 512, LP_WAVES = 8; // threads
+constexpr int LP_GROUPS = 8;             // of workgroups in a barrier
+constexpr int LP_BAR = 2 * LP_GROUPS * 64; // words of one: a line per group counter, then the copies of the flags
+constexpr int LP_SYNC = 2 * LP_BAR + 64;   // both barriers, the word of a failed wait
+
+struct LpArgs {
+    LstmRunLayer l[LP_MAX_LAYERS];
+    const float *dh_top;
+    float *xh, *xt; // exchanged: h (forward; step t at t + 1, the initial state at 0) or dz (backward); T or dT
+    unsigned *sync;
+    i64 xh_step, xt_step; // floats from one step's copy to the next
+    int T, B, h, r, G, gr, L;
+    int hp, rp;           // h and r up to whole groups of 32 contraction indices
+    int n1, n2, nwg;      // tasks (one per workgroup) of the two phases of a slot
+    int nt1;              // 8-column tiles of a T / dT task
+};
+
+// ------------------------------------------------------------------ tasks
+// Workgroups go to the dies in turn.  Those of one die get neighbouring tasks: they read the same activations and, where a row of
+// the factors is shared by column tiles, the same lines.  (n workgroups take part: a multiple of LP_GROUPS; some have no task)
+__host__ __device__ __forceinline__ int lp_task(int wg, int n) { return (wg % LP_GROUPS) * (n / LP_GROUPS) + wg / LP_GROUPS; }
+
+// product p of the 2 L - 1 of a slot: layer (p + 1) / 2, its hidden path (p = 0 or odd) or input path
+__host__ __device__ __forceinline__ int lp_layer(int p) { return (p + 1) >> 1; }
+__host__ __device__ __forceinline__ int lp_path(int p) { return p > 0 && !(p & 1); }
+__host__ __device__ __forceinline__ float *lp_xt(const LpArgs &a, int l, int path, int t)
+{
+    return a.xt + ((i64)(2 * l + path) * a.T + t) * a.xt_step;
+}
+__host__ __device__ __forceinline__ float *lp_xh(const LpArgs &a, int l, int slot) { return a.xh + ((i64)l * (a.T + 1) + slot) * a.xh_step; }
+
+// A workgroup's units u0 .. u0 + n - 1 of layer l (n workgroups of U units each take part; !has: none for this one)
+struct LpUnits {
+    bool has;
+    int l, u0, n;
+};
+__host__ __device__ __forceinline__ LpUnits lp_units(const LpArgs &a, int wg, int parts, int U)
+{
+    LpUnits t;
+    const int per_layer = (a.hp + U - 1) / U, task = lp_task(wg, parts);
+    t.has = wg < parts && task < a.L * per_layer;
+    t.l = t.has ? task / per_layer : 0;
+    t.u0 = t.has ? (task - t.l * per_layer) * U : 0;
+    t.n = U;
+    return t;
+}
+// Its columns col .. col + n - 1 of T (or dT) of product p: of `cols` columns, in tiles of TW, block q of the product's `blocks`
+struct LpColumns {
+    bool has;
+    int p, q, l, path, col, n;
+};
+__host__ __device__ __forceinline__ LpColumns lp_columns(const LpArgs &a, int wg, int parts, int cols, int TW, int blocks)
+{
+    LpColumns t;
+    const int per_block = (cols / TW + a.nt1 - 1) / a.nt1, task = lp_task(wg, parts);
+    t.has = wg < parts && task < (2 * a.L - 1) * blocks * per_block;
+    const int b = t.has ? task / per_block : 0;
+    t.p = b / blocks, t.q = b - t.p * blocks;
+    t.l = lp_layer(t.p), t.path = lp_path(t.p);
+    t.col = t.has ? (task - b * per_block) * TW * a.nt1 : 0;
+    t.n = TW * a.nt1 < cols - t.col ? TW * a.nt1 : cols - t.col;
+    return t;
+}
 
 // Walks the elements first, first + step, ... of a list of rows of n elements each; row and o are the current element's row
 // and place in it.  All steps' rows together have more elements than 32 bits count (three layers of rank 384, batch 32: from
@@ -23,5 +88,135 @@ struct LpWalk {
         if (o >= n) o -= n, ++row;
     }
 };
+
+// ------------------------------------------------------------------ a wait that gave up
+// A workgroup that leaves the launch early writes NaN over what it has not written: its own outputs of the steps from the
+// current one on, and no one else's.  (Every wait that succeeded had all its data, so what was written before is right.)
+__host__ __device__ inline float lp_nan() { return __builtin_nanf(""); }
+
+__host__ __device__ inline void lp_void_columns(const LpArgs &a, float *out, int col, int n, int t0, int t1, int tid)
+{
+    for (int t = t0; t < t1; ++t)
+        for (int e = tid; e < a.B * n; e += LP_NT) {
+            const int m = e / n, c = col + e - m * n, q = c / a.rp, cc = c - q * a.rp;
+            if (q < a.G && cc < a.r) out[((i64)t * a.B + m) * a.gr + q * a.r + cc] = lp_nan();
+        }
+}
+// forward, in slot `slot`
+__host__ __device__ inline void lp_void_fwd(const LpArgs &a, const LpColumns &c, const LpUnits &z, int slot, int tid)
+{
+    if (c.has) lp_void_columns(a, c.path ? a.l[c.l].Tx : a.l[c.l].Th, c.col, c.n, slot > c.l ? slot - c.l : 0, a.T, tid);
+    if (!z.has) return;
+    const LstmRunLayer &y = a.l[z.l];
+    for (int t = slot > z.l ? slot - z.l : 0; t < a.T; ++t)
+        for (int e = tid; e < a.B * z.n; e += LP_NT) {
+            const int m = e / z.n, un = z.u0 + e - m * z.n;
+            if (un >= a.h) continue;
+            const i64 row = (i64)t * a.B + m;
+            y.h_all[row * a.h + un] = y.c_all[row * a.h + un] = lp_nan();
+            for (int q = 0; q < 4; ++q) y.gates[(row * 4 + q) * a.h + un] = lp_nan();
+        }
+}
+// backward, in slot `u`; with SL > 1 slices of dT it is their sums at the end that are written, RB row blocks wide
+__host__ __device__ inline void lp_void_bwd(const LpArgs &a, const LpColumns &c, const LpUnits &z, int u, int SL, int RB, int wg, int tid)
+{
+    // steps that a layer has left: all below
+    const auto left = [&](int l) {
+        const int t1 = a.T - (u - (a.L - 1 - l));
+        return t1 < a.T ? t1 : a.T;
+    };
+    if (c.has && SL == 1)
+        lp_void_columns(a, c.path ? a.l[c.l].dTx : a.l[c.l].dTh, (a.G != 1 ? c.q * a.rp : 0) + c.col, c.n, 0, left(c.l), tid);
+    if (wg < a.n1 && SL > 1) {
+        const int per = a.rp * 4 * RB; // (this workgroup's share of the sums, in any order)
+        for (LpWalk at(per, wg * LP_NT + tid, a.n1 * LP_NT); at.row < (2 * a.L - 1) * a.T; at.next()) {
+            const int pr = at.row / a.T, t = at.row - pr * a.T, l = lp_layer(pr), k = at.o / (4 * RB), m = at.o - k * (4 * RB);
+            if (k < a.r && m < a.B) (lp_path(pr) ? a.l[l].dTx : a.l[l].dTh)[((i64)t * a.B + m) * a.gr + k] = lp_nan();
+        }
+    }
+    if (!z.has || left(z.l) < 0) return;
+    const LstmRunLayer &y = a.l[z.l];
+    for (int t = -1; t < left(z.l); ++t)
+        for (int e = tid; e < a.B * z.n; e += LP_NT) {
+            const int m = e / z.n, un = z.u0 + e - m * z.n;
+            if (un >= a.h) continue;
+            if (t < 0) y.dh0[(i64)m * a.h + un] = y.dc0[(i64)m * a.h + un] = lp_nan();
+            else
+                for (int q = 0; q < 4; ++q) y.dz[(((i64)t * a.B + m) * 4 + q) * a.h + un] = lp_nan();
+        }
+}
+
+// ------------------------------------------------------------------ plan
+static int lp_row_blocks(int B) { return B <= 4 ? 1 : B <= 8 ? 2 : B <= 12 ? 3 : B <= 20 ? 5 : 8; }
+
+struct LpPlan {
+    int RB, NT, SL, nt1, n1, n2, nwg, hp, rp; // NT 0: the registers of the chip do not hold the factors
+    i64 xh_step, xt_step;
+    size_t floats;
+};
+// One task per workgroup and phase, the smallest tiles that come out at no more tasks than compute units.  The bounds are the
+// kernels': groups of 32 contraction indices per wavefront, tiles, and what fits beside the accumulators of RB row blocks.
+static LpPlan lp_plan(const LstmGeom &g, bool bwd, int cus)
+{
+    LpPlan p = {};
+    p.RB = lp_row_blocks(g.B);
+    p.hp = (g.h + 31) & ~31;
+    p.rp = (g.r + 31) & ~31;
+    p.xh_step = (i64)(bwd ? 4 : 1) * p.hp * 4 * p.RB;
+    p.xt_step = (i64)(bwd && g.G == 1 ? 3 : 1) * g.G * p.rp * 4 * p.RB;
+    p.floats = (size_t)p.xh_step * g.L * (g.T + 1) + (size_t)p.xt_step * 2 * g.L * g.T + LP_SYNC;
+    if (p.hp > 1536 || p.rp > 384 || (g.G != 1 && p.RB == 8)) return p;
+    const int products = 2 * g.L - 1;
+    int tasks = 0;
+    p.SL = p.nt1 = 1;
+    if (bwd && g.G == 1) {
+        // dT = dz U contracts 4 h: tiles of 16 columns, up to three slices (the readers add them up; one slice of 8 columns per
+        // workgroup read three times the activations: 9 instead of 5 us at 1500 units)
+        const int groups = p.hp / 8, cols = p.rp / 16;
+        for (p.SL = 3; p.SL > 1; --p.SL)
+            if (products * cols * p.SL <= cus && groups >= LP_WAVES * p.SL) break;
+        tasks = products * cols * p.SL;
+        const int per_wave = ((groups + p.SL - 1) / p.SL + LP_WAVES - 1) / LP_WAVES;
+        if (tasks > cus || per_wave > (p.SL == 3 ? 8 : 12)) return p;
+    } else {
+        const int blocks = products * (bwd ? g.G : 1), cols = (bwd ? 1 : g.G) * p.rp / 8, most = g.G == 1 ? 1 : 3;
+        for (p.nt1 = 1;; ++p.nt1) {
+            tasks = blocks * ((cols + p.nt1 - 1) / p.nt1);
+            if (tasks <= cus) break;
+            if (p.nt1 == most) return p;
+        }
+    }
+    int units = 0, most = g.G != 1 ? 1 : bwd ? (p.RB == 8 ? 1 : 2) : p.RB == 8 ? 2 : p.RB == 5 ? 3 : 5, NT = 1;
+    for (; NT <= most; ++NT) {
+        const int U = bwd || g.G != 1 ? 16 * NT : 4 * NT;
+        units = g.L * ((p.hp + U - 1) / U);
+        if (units <= cus) break;
+    }
+    if (units > cus) return p;
+    p.NT = NT == 4 ? 5 : NT;
+    if (p.NT == 5) units = g.L * ((p.hp + 19) / 20);
+    units = (units + LP_GROUPS - 1) / LP_GROUPS * LP_GROUPS; // (the barrier's groups are even)
+    tasks = (tasks + LP_GROUPS - 1) / LP_GROUPS * LP_GROUPS;
+    p.n1 = bwd ? units : tasks;
+    p.n2 = bwd ? tasks : units;
+    p.nwg = p.n1 > p.n2 ? p.n1 : p.n2;
+    if (p.nwg > cus) p.NT = 0;
+    return p;
+}
+
+static void lp_fill(LpArgs &a, const LpPlan &p, const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, float *ws)
+{
+    a = {};
+    for (int q = 0; q < g.L; ++q) a.l[q] = l[q];
+    a.dh_top = dh_top;
+    a.xh = ws;
+    a.xt = a.xh + p.xh_step * g.L * (g.T + 1);
+    a.sync = (unsigned *)(a.xt + p.xt_step * 2 * g.L * g.T);
+    a.xh_step = p.xh_step;
+    a.xt_step = p.xt_step;
+    a.T = g.T, a.B = g.B, a.h = g.h, a.r = g.r, a.G = g.G, a.gr = g.gr, a.L = g.L;
+    a.hp = p.hp, a.rp = p.rp;
+    a.n1 = p.n1, a.n2 = p.n2, a.nwg = p.nwg, a.nt1 = p.nt1;
+}
 
 } // namespace pf

@@ -37,3 +37,15 @@ def test_walk_visits_every_element_once(emu, n, workgroups, rows):
         assert emu.emu_walk(n, first, step, rows, ctypes.byref(count), ctypes.byref(last))
         want = len(range(first, total, step))
         assert (count.value, last.value) == (want, first + (want - 1) * step if want else -1)
+
+
+@pytest.mark.parametrize("T,B,h,r,groups,layers", [
+    (4, 3, 40, 12, 1, 2), (3, 20, 260, 65, 1, 3), (5, 7, 33, 9, 4, 2), (3, 20, 500, 125, 4, 1), (4, 32, 640, 33, 1, 1),
+    (3, 9, 1500, 375, 1, 2),
+])
+@pytest.mark.parametrize("bwd", [0, 1])
+def test_workgroups_that_give_up_leave_nan(emu, T, B, h, r, groups, layers, bwd):
+    """A wait that gives up returns no status: what its workgroups have not written yet is NaN, whatever the slot, and what
+    they wrote before stays."""
+    for slot in {0, 1, layers, T - 1, T + layers - 2}:
+        assert emu.emu_void(T, B, h, r, groups, layers, bwd, slot) == 0, slot
