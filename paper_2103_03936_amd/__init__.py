@@ -386,13 +386,13 @@ def pf_svd_split(W, r, return_info=False):
     return (U, V, sigma, info) if return_info else (U, V, sigma)
 
 
-def pf_svd_split_conv(Wd, r):
-    """A dense filter bank Wd[c_out, c_in, k, k] -> (Uk[r, c_in, k, k], Vp[c_out, r]) (Section 2.2: unroll to
-    [c_in k^2, c_out], factor, fold the left factor back into r thin filters)."""
+def pf_svd_split_conv(Wd, r, return_info=False):
+    """A dense filter bank Wd[c_out, c_in, k, k] -> (Uk[r, c_in, k, k], Vp[c_out, r], sigma) (Section 2.2: unroll to
+    [c_in k^2, c_out], factor, fold the left factor back into r thin filters), with return_info also pf_svd_split's."""
     co, ci, k, _ = Wd.shape
     Wu = Wd.reshape(co, ci * k * k).t().contiguous()  # [c_in k^2, c_out], row index c k^2 + i k + j
-    U, V, sigma = pf_svd_split(Wu, r)
-    return U.t().contiguous().reshape(r, ci, k, k), V.contiguous(), sigma
+    U, V, *rest = pf_svd_split(Wu, r, return_info)
+    return U.t().contiguous().reshape(r, ci, k, k), V.contiguous(), *rest
 
 
 # ------------------------------------------------------------------ timing

@@ -18,12 +18,13 @@
 // that 16 x 16 matrix in LDS by one wavefront and applied to the rows, one row per thread.  Pairs of blocks are dealt into rounds by round-robin; the rounds of all sweeps run in ONE cooperative
 // kernel with a grid barrier between them, because the number of sweeps is known on the device only: a launch per
 // round has to be enqueued for the most sweeps that may be needed, at 2.8 us each (2048 x 512: 12264 launches, 84 ms).
-// A barrier's wait is bounded: after about a second without the others a workgroup gives up and reports no convergence.
+// A barrier's wait is bounded: after about a second without the others a workgroup gives up; the call then reports no
+// convergence and its outputs are NaN.
 #include "pf_gemm.h"
+#include "pf_svd_pair.h"
 
 namespace pf {
 
-constexpr int SVD_MAX_SWEEPS = 24;
 constexpr int SVD_NT = 512;  // threads of the cooperative kernels
 constexpr int SVD_B = 8;     // columns per block
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
@@ -39,16 +40,6 @@ static double svd_tolerance(int rows)
 }
 // That of the preconditioner, whose columns become V: rounding level.
 static double svd_tolerance_v(int rows) { return (double)(rows < 64 ? 64 : rows) * 2.220446049250313e-16; }
-
-// Device-side state of a call
-struct SvdCtrl {
-    unsigned arrived[2]; // grid barriers of the two cooperative kernels
-    unsigned failed;     // a barrier's wait ran out
-    unsigned violations; // pairs of B that are not orthogonal after the preconditioner
-    unsigned rot[2][SVD_MAX_SWEEPS + 1]; // block pairs rotated per sweep, of L and of B
-    unsigned sweeps;     // sweeps over the pairs of B, the check included
-    unsigned last;       // block pairs rotated in the last of them
-};
 
 __global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *At, SvdCtrl *ctrl, int n, int nr, int nc, int ld,
                                                         int transposed)
@@ -565,15 +556,16 @@ __global__ __launch_bounds__(256) void svd_emit_kernel(const double *BV, const d
                                                         float *sigma_out, int nr, int nc, int v0, int ld, int r,
                                                         int transposed, const SvdCtrl *ctrl, int *info)
 {
+    const SvdOutcome done = svd_outcome(*ctrl, nc);
     if (info && blockIdx.x == 0 && threadIdx.x == 0) {
-        info[0] = nc > 1 ? (int)ctrl->sweeps : 0;
-        info[1] = nc > 1 ? (int)ctrl->last : 0;
+        info[0] = done.sweeps;
+        info[1] = done.last;
     }
-    const int j = blockIdx.x, k = rank[j];
-    const double s = sig[j];
+    const int j = blockIdx.x, k = done.lost ? j : rank[j];
+    const double s = done.lost ? __builtin_nan("") : sig[j];
     if (threadIdx.x == 0 && sigma_out) sigma_out[k] = (float)s;
     if (k >= r) return;
-    const double rs = sqrt(s), inv = s > 0.0 ? rs / s : 0.0;
+    const double rs = sqrt(s), inv = done.lost ? s : s > 0.0 ? rs / s : 0.0;
     float *left = transposed ? V : U, *right = transposed ? U : V;
     const double *a = BV + (i64)j * ld, *qv = a + v0;
     for (int i = threadIdx.x; i < nr; i += 256) left[(i64)i * r + k] = (float)(a[i] * inv);

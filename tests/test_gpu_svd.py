@@ -104,3 +104,13 @@ def test_deterministic():
     b = pf.pf_svd_split(W, 12)
     for u, v in zip(a, b):
         assert torch.equal(u, v)
+
+
+def test_conv_info():
+    """The filter bank's call hands out the convergence report too."""
+    import paper_2103_03936_amd as pf
+    Wd = to_gpu(_matrix(12, 8 * 9, 21).reshape(12, 8, 3, 3))
+    plain = pf.pf_svd_split_conv(Wd, 4)
+    *same, info = pf.pf_svd_split_conv(Wd, 4, return_info=True)
+    assert len(plain) == 3 and all(torch.equal(a, b) for a, b in zip(plain, same))
+    assert 1 <= int(info[0]) <= 24 and int(info[1]) == 0
