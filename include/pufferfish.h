@@ -461,7 +461,8 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x,
 /* come back in the status: info (nullable, DEVICE int[2]) receives     */
 /* info[0] = sweeps that ran, info[1] = rotations applied in the last   */
 /* of them -- 0 means converged; anything else means the 24 sweeps did  */
-/* not suffice and the factors are approximate.  (The workgroups wait   */
+/* not suffice and the factors are approximate, or that W holds NaN or  */
+/* infinity, which then show in the outputs.  (The workgroups wait      */
 /* for one another in bounded waits; should one ever run out, all       */
 /* outputs are NaN and info[1] is not 0.)                               */
 /* ------------------------------------------------------------------ */

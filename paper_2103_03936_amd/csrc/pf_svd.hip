@@ -28,7 +28,6 @@ namespace pf {
 constexpr int SVD_NT = 512;  // threads of the cooperative kernels
 constexpr int SVD_B = 8;     // columns per block
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
-typedef __attribute__((ext_vector_type(2))) double f64x2_t;
 
 // A pair counts as orthogonal when |a_p . a_q| <= tol |a_p| |a_q|.  The factors are float (2^-24): 2^-36 leaves their last
 // bit exact, and is far above the rounding noise of an inner product of doubles, which a threshold must not go below
@@ -118,8 +117,7 @@ __global__ __launch_bounds__(256) void svd_check_kernel(const double *G, SvdCtrl
     if (idx < (i64)nc * nc) {
         const int i = (int)(idx % nc), j = (int)(idx / nc);
         if (i > j) {
-            const double g = G[(i64)j * ld + i];
-            bad = g != 0.0 && !(fabs(g) <= tol * sqrt(G[(i64)j * ld + j] * G[(i64)i * ld + i]));
+            bad = !svd_orthogonal(G[(i64)j * ld + j], G[(i64)i * ld + i], G[(i64)j * ld + i], tol * tol);
         }
     }
     if (bad) atomicAdd(&ctrl->violations, 1u);
@@ -246,30 +244,6 @@ struct SvdShared {
     int any[4];
 };
 
-// The rotation that takes gamma out of [[alpha, gamma], [gamma, beta]].  The angle needs no more than float precision (what
-// it leaves of gamma is 1e-7 of it); c is refined so that c^2 + s^2 = 1 to the last bit.
-__device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2)
-{
-    f64x2_t r = {1.0, 0.0};
-    if (!(gamma * gamma > tol2 * (alpha * beta))) return r;
-#if defined(__HIP_DEVICE_COMPILE__)
-    const int e = -__builtin_amdgcn_frexp_exp(alpha + beta);
-    const float d = (float)__builtin_amdgcn_ldexp(beta - alpha, e), g = (float)__builtin_amdgcn_ldexp(2.0 * gamma, e);
-    const float z = d * __builtin_amdgcn_rcpf(g), az = fabsf(z);
-    const float ta = az > 1e18f ? 0.5f * __builtin_amdgcn_rcpf(az) : __builtin_amdgcn_rcpf(az + __builtin_amdgcn_sqrtf(1.f + z * z));
-    const double t = (double)copysignf(ta, z), w = 1.0 + t * t;
-    double c = (double)__builtin_amdgcn_rsqf((float)w);
-#else
-    const double z = (beta - alpha) / (2.0 * gamma), t = (z >= 0.0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z)), w = 1.0 + t * t;
-    double c = 1.0 / sqrt(w);
-#endif
-    c = c * (1.5 - 0.5 * w * c * c); // Newton: 23 -> 45 bits
-    c = c * (1.5 - 0.5 * w * c * c);
-    r[0] = c;
-    r[1] = c * t;
-    return r;
-}
-
 template <int T, int END>
 __device__ __forceinline__ void svd_rotate_row(const f64x2_t *cs, double (&x)[16])
 {
@@ -337,7 +311,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
         }
         sh.g[i][j] = y;
         const bool pair = i > j && (within || (i >= 8 && j < 8));
-        const bool some = pair && y * y > tol2 * (a * b), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
+        const bool some = pair && !svd_orthogonal(a, b, y, tol2), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
         const bool anyone = __any(some), anylarge = __any(large);
         if (lane == 0) sh.any[wave] = anylarge ? 2 : anyone ? 1 : 0;
     }
@@ -525,7 +499,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, SvdCtrl 
     }
 }
 
-__global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double *sig, int nr, int ld)
+__global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double *sig, SvdCtrl *ctrl, int nr, int ld)
 {
     const double *a = At + (i64)blockIdx.x * ld;
     double acc = 0.0;
@@ -537,17 +511,20 @@ __global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) sig[blockIdx.x] = sqrt(red[0]);
+    if (threadIdx.x == 0) {
+        sig[blockIdx.x] = sqrt(red[0]);
+        if (!(red[0] < __builtin_huge_val())) ctrl->broken = 1u; // (also a matrix of one column, which has no pairs)
+    }
 }
 
-// position of column j in descending order of singular value (ties: lower index first)
+// position of column j in descending order of singular value (ties: lower index first; NaN before all others)
 __global__ __launch_bounds__(256) void svd_rank_kernel(const double *sig, int *rank, int nc)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= nc) return;
     const double s = sig[j];
     int k = 0;
-    for (int i = 0; i < nc; ++i) k += (sig[i] > s || (sig[i] == s && i < j)) ? 1 : 0;
+    for (int i = 0; i < nc; ++i) k += svd_before(sig[i], i, s, j) ? 1 : 0;
     rank[j] = k;
 }
 
@@ -655,7 +632,7 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V, void *si
               ctrl, nc, p.ldn, svd_tolerance(nr));
     if (st == PF_OK)
         st = launch_cooperative(s, "svd_finish", svd_finish_kernel, nwg, BV, ctrl, nr, nc, p.ldb, p.ldb, svd_tolerance(nr));
-    PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, nr, p.ldb);
+    PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, ctrl, nr, p.ldb);
     PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 255) / 256), dim3(256), s, (const double *)sig, rank, nc);
     PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(nc), dim3(256), s, (const double *)BV, (const double *)sig,
               (const int *)rank, (float *)U, (float *)V, (float *)sigma, nr, nc, p.lda, p.ldb, (int)d->r, p.transposed,

@@ -5,10 +5,12 @@
 using namespace pf;
 
 extern "C" {
-void emu_outcome(unsigned failed, unsigned sweeps, unsigned last, int nc, int *out)
+int emu_orthogonal(double alpha, double beta, double gamma, double tol) { return svd_orthogonal(alpha, beta, gamma, tol * tol); }
+int emu_before(double a, int i, double b, int j) { return svd_before(a, i, b, j); }
+void emu_outcome(unsigned failed, unsigned broken, unsigned sweeps, unsigned last, int nc, int *out)
 {
     SvdCtrl c = {};
-    c.failed = failed, c.sweeps = sweeps, c.last = last;
+    c.failed = failed, c.broken = broken, c.sweeps = sweeps, c.last = last;
     const SvdOutcome o = svd_outcome(c, nc);
     out[0] = o.sweeps, out[1] = o.last, out[2] = o.lost;
 }

@@ -114,3 +114,15 @@ def test_conv_info():
     *same, info = pf.pf_svd_split_conv(Wd, 4, return_info=True)
     assert len(plain) == 3 and all(torch.equal(a, b) for a, b in zip(plain, same))
     assert 1 <= int(info[0]) <= 24 and int(info[1]) == 0
+
+
+@pytest.mark.parametrize("shape", [(40, 1), (30, 24), (17, 70), (300, 130)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_not_finite_is_reported(shape, value):
+    """A matrix with one element that is not finite: info says so, and so do the factors."""
+    import paper_2103_03936_amd as pf
+    W = _matrix(*shape, seed=31)
+    W[shape[0] // 2, shape[1] // 3] = value
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), 1, return_info=True)
+    assert int(info[1]) != 0
+    assert not (torch.isfinite(U).all() and torch.isfinite(V).all() and torch.isfinite(sigma).all())

@@ -19,14 +19,44 @@ def emu(tmp_path_factory):
            "-I", os.path.join(ROOT, "paper_2103_03936_amd", "csrc"),
            os.path.join(ROOT, "tests", "emulation", "svd_host.cpp"), "-o", out]
     subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
-    return ctypes.CDLL(out)
+    lib, d = ctypes.CDLL(out), ctypes.c_double
+    lib.emu_orthogonal.argtypes = [d, d, d, d]
+    lib.emu_before.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
+    return lib
 
 
 def test_a_wait_that_gave_up_is_never_reported_as_converged(emu):
     out = (ctypes.c_int * 3)()
     for sweeps, last in ((0, 0), (5, 0), (24, 3)):
         for nc in (1, 2, 300):
-            emu.emu_outcome(1, sweeps, last, nc, out)
+            emu.emu_outcome(1, 0, sweeps, last, nc, out)
             assert out[1] != 0 and out[2] == 1
-            emu.emu_outcome(0, sweeps, last, nc, out)
+            emu.emu_outcome(0, 0, sweeps, last, nc, out)
             assert list(out) == ([sweeps, last, 0] if nc > 1 else [0, 0, 0])
+
+
+def test_not_finite_is_not_orthogonal(emu):
+    inf, nan = float("inf"), float("nan")
+    for a, b, g in ((nan, 1, 1e-20), (1, nan, 0), (1, 1, nan), (nan, nan, nan), (inf, 1, inf), (inf, inf, inf), (1, 1, -inf),
+                    (inf, 0, 0)):
+        assert not emu.emu_orthogonal(a, b, g, 1e-13), (a, b, g)
+    for a, b, g in ((1, 1, 0), (0, 0, 0), (1e80, 1e-80, 1e-14), (2.0, 0.0, 0.0)):
+        assert emu.emu_orthogonal(a, b, g, 1e-13), (a, b, g)
+    assert not emu.emu_orthogonal(4, 4, 1e-12, 1e-13)
+
+
+def test_a_singular_value_that_is_not_finite_is_never_reported_as_converged(emu):
+    out = (ctypes.c_int * 3)()
+    for nc, want in ((1, [0, 1, 0]), (300, [3, 1, 0])):
+        emu.emu_outcome(0, 1, 3, 0, nc, out)
+        assert list(out) == want
+
+
+def test_every_column_has_a_place(emu):
+    """The order of the singular values is total, NaN included: no two columns share a place, none is left unwritten."""
+    nan = float("nan")
+    for v in ([3.0, nan, 5.0, nan, 5.0, 0.0, float("inf")], [nan] * 4, [1.0, 1.0, 0.0, 0.0]):
+        rank = [sum(emu.emu_before(v[i], i, v[j], j) for i in range(len(v))) for j in range(len(v))]
+        assert sorted(rank) == list(range(len(v)))
+        finite = [v[rank.index(k)] for k in range(len(v)) if v[rank.index(k)] == v[rank.index(k)]]
+        assert finite == sorted(finite, reverse=True)
