@@ -3,6 +3,8 @@
 
 #include "pf_common.h"
 
+#include <math.h>
+
 namespace pf {
 
 constexpr int SVD_MAX_SWEEPS = 24;
@@ -10,13 +12,13 @@ typedef __attribute__((ext_vector_type(2))) double f64x2_t;
 
 // Device-side state of a call
 struct SvdCtrl {
-    unsigned arrived[2]; // grid barriers of the two cooperative kernels
-    unsigned failed;     // a barrier's wait ran out
-    unsigned broken;     // a singular value is not finite: the matrix was not
-    unsigned violations; // pairs of B that are not orthogonal after the preconditioner
-    unsigned rot[2][SVD_MAX_SWEEPS + 1]; // block pairs rotated per sweep, of L and of B
-    unsigned sweeps;     // sweeps over the pairs of B, the check included
-    unsigned last;       // block pairs rotated in the last of them
+    unsigned arrived[3];    // grid barriers of the three cooperative launches
+    unsigned failed;        // a barrier's wait ran out
+    unsigned broken;        // a singular value is not finite: the matrix was not
+    unsigned violations[2]; // pairs of B that are not orthogonal after the preconditioner, and after the first sweep
+    unsigned rot[3][SVD_MAX_SWEEPS + 1]; // pairs rotated per sweep: of L (in pairs of blocks with a large angle), of B first, of B then
+    unsigned sweeps;        // sweeps over the pairs of B, a check that found nothing included
+    unsigned last;          // pairs rotated in the last of them
 };
 
 // What a call reports: sweeps, rotations of the last one, and whether its outputs are worth nothing because a barrier's wait
@@ -49,25 +51,45 @@ __host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double bet
     return g2 <= tol2 * (alpha * beta) && g2 < __builtin_huge_val();
 }
 
-// The rotation that takes gamma out of [[alpha, gamma], [gamma, beta]].  The angle needs no more than float precision (what
-// it leaves of gamma is 1e-7 of it); c is refined so that c^2 + s^2 = 1 to the last bit.
+// 1 / sqrt(q) and 1 / q to a few units of the last place: a float approximation (23 bits) and two Newton steps in double.
+__host__ __device__ __forceinline__ double svd_rsqrt(double q)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = (double)__builtin_amdgcn_rsqf((float)q);
+#else
+    double y = (double)(1.0f / sqrtf((float)q));
+#endif
+    y = y * (1.5 - 0.5 * q * y * y);
+    return y * (1.5 - 0.5 * q * y * y);
+}
+__host__ __device__ __forceinline__ double svd_rcp(double q)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double y = (double)__builtin_amdgcn_rcpf((float)q);
+#else
+    double y = (double)(1.0f / (float)q);
+#endif
+    y = y * (2.0 - q * y);
+    return y * (2.0 - q * y);
+}
+
+// The rotation (c, s) that takes gamma out of [[alpha, gamma], [gamma, beta]], all in double: s / c = t solves
+// t^2 + 2 z t - 1 = 0, z = (beta - alpha) / (2 gamma), |t| <= 1.  With d = beta - alpha and g = 2 gamma that is
+// t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that alpha + beta is near 1: the arguments of the two approximations are then
+// in float's range (at least the threshold's square), while t itself may be as small as it is.
 __host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2)
 {
     f64x2_t r = {1.0, 0.0};
     if (svd_orthogonal(alpha, beta, gamma, tol2)) return r;
 #if defined(__HIP_DEVICE_COMPILE__)
     const int e = -__builtin_amdgcn_frexp_exp(alpha + beta);
-    const float d = (float)__builtin_amdgcn_ldexp(beta - alpha, e), g = (float)__builtin_amdgcn_ldexp(2.0 * gamma, e);
-    const float z = d * __builtin_amdgcn_rcpf(g), az = fabsf(z);
-    const float ta = az > 1e18f ? 0.5f * __builtin_amdgcn_rcpf(az) : __builtin_amdgcn_rcpf(az + __builtin_amdgcn_sqrtf(1.f + z * z));
-    const double t = (double)copysignf(ta, z), w = 1.0 + t * t;
-    double c = (double)__builtin_amdgcn_rsqf((float)w);
+    const double d = __builtin_amdgcn_ldexp(beta - alpha, e), g = __builtin_amdgcn_ldexp(2.0 * gamma, e);
 #else
-    const double z = (beta - alpha) / (2.0 * gamma), t = (z >= 0.0 ? 1.0 : -1.0) / (fabs(z) + sqrt(1.0 + z * z)), w = 1.0 + t * t;
-    double c = 1.0 / sqrt(w);
+    int e;
+    (void)frexp(alpha + beta, &e);
+    const double d = ldexp(beta - alpha, -e), g = ldexp(2.0 * gamma, -e);
 #endif
-    c = c * (1.5 - 0.5 * w * c * c); // Newton: 23 -> 45 bits
-    c = c * (1.5 - 0.5 * w * c * c);
+    const double q = d * d + g * g, n = fabs(d) + q * svd_rsqrt(q), t = (d < 0.0 ? -g : g) * svd_rcp(n), c = svd_rsqrt(1.0 + t * t);
     r[0] = c;
     r[1] = c * t;
     return r;

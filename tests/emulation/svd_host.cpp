@@ -6,6 +6,11 @@ using namespace pf;
 
 extern "C" {
 int emu_orthogonal(double alpha, double beta, double gamma, double tol) { return svd_orthogonal(alpha, beta, gamma, tol * tol); }
+void emu_rotation(double alpha, double beta, double gamma, double *cs)
+{
+    const f64x2_t r = svd_rotation(alpha, beta, gamma, 0.0);
+    cs[0] = r[0], cs[1] = r[1];
+}
 int emu_before(double a, int i, double b, int j) { return svd_before(a, i, b, j); }
 void emu_outcome(unsigned failed, unsigned broken, unsigned sweeps, unsigned last, int nc, int *out)
 {

@@ -126,3 +126,25 @@ def test_not_finite_is_reported(shape, value):
     U, V, sigma, info = pf.pf_svd_split(to_gpu(W), 1, return_info=True)
     assert int(info[1]) != 0
     assert not (torch.isfinite(U).all() and torch.isfinite(V).all() and torch.isfinite(sigma).all())
+
+
+@pytest.mark.parametrize("m,n,big", [(256, 64, 400.0), (256, 64, 1000.0), (600, 200, 300.0)])
+def test_close_singular_values_are_separated(m, n, big):
+    """Singular values a relative 1e-6 apart under a few large ones: the vectors themselves, up to sign.  Columns orthogonal to
+    t = max(m, n) 2^-52 are mixed by t / (2 d) at most for values a relative d apart, the factors round by 2^-24, and the
+    float64 reference is off by 2^-52 sigma_1 / (sigma d)."""
+    import paper_2103_03936_amd as pf
+    top = n // 8
+    s = np.concatenate([big * np.linspace(2, 1, top), 1 + 1e-6 * np.arange(n - top, 0, -1)])
+    q1, _ = np.linalg.qr(_matrix(m, n, 41).astype(np.float64))
+    q2, _ = np.linalg.qr(_matrix(n, n, 42).astype(np.float64))
+    W = ((q1 * s) @ q2.T).astype(np.float32)
+    U, V, _, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+    assert int(info[1]) == 0
+    u, sv, vt = np.linalg.svd(W.astype(np.float64), full_matrices=False)
+    d = np.min(-np.diff(sv) / sv[1:])
+    bound = 2.0 ** -24 + 2.0 ** -52 * (m / (2 * d) + sv[0] / (sv[-1] * d))
+    for got, ref in ((U, u), (V, vt.T)):
+        got, ref = got.double().cpu().numpy(), ref * np.sqrt(sv)
+        err = np.abs(got * np.sign((got * ref).sum(0)) - ref).max(0) / np.abs(ref).max(0)
+        assert err.max() <= bound, (err.max(), bound)

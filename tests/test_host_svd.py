@@ -21,6 +21,7 @@ def emu(tmp_path_factory):
     subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
     lib, d = ctypes.CDLL(out), ctypes.c_double
     lib.emu_orthogonal.argtypes = [d, d, d, d]
+    lib.emu_rotation.argtypes = [d, d, d, ctypes.c_void_p]
     lib.emu_before.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
     return lib
 
@@ -60,3 +61,17 @@ def test_every_column_has_a_place(emu):
         assert sorted(rank) == list(range(len(v)))
         finite = [v[rank.index(k)] for k in range(len(v)) if v[rank.index(k)] == v[rank.index(k)]]
         assert finite == sorted(finite, reverse=True)
+
+
+def test_rotation_is_exact_to_double(emu):
+    """(c, s) takes gamma out to the rounding of doubles, also between columns whose norms are 1e30 apart or equal."""
+    from fractions import Fraction as F
+    cs = (ctypes.c_double * 2)()
+    for alpha, beta, rel in ((3.0, 2.0, 0.5), (2.0, 3.0, -0.5), (1.0, 1.0, 1e-13), (1.0, 1.0 + 2 ** -40, -1e-12), (1.0, 1e-60, 1e-13),
+                             (1e-60, 1e60, 0.9), (5e70, 4e70, -1e-9), (1.0, 1.0, -1.0 + 2 ** -50)):
+        gamma = rel * alpha ** 0.5 * beta ** 0.5
+        emu.emu_rotation(alpha, beta, gamma, cs)
+        c, s, a, b, g = (F(v) for v in (cs[0], cs[1], alpha, beta, gamma))
+        assert abs(float(c * c + s * s - 1)) <= 8 * 2.0 ** -53
+        # columns p, q -> c p - s q, s p + c q: their inner product, relative to what it was
+        assert abs(float((c * s * (a - b) + (c * c - s * s) * g) / g)) <= 16 * 2.0 ** -53, (alpha, beta, gamma)
