@@ -87,9 +87,8 @@ def test_lstm_cell_graph_replay():
 @pytest.mark.parametrize("T", [5, 9])
 @pytest.mark.parametrize("groups", [1, 4])
 def test_lstm_stack_graph_replay(groups, T):
-    """Two stacked layers over a short sequence (groups = 1: the fused pre-activation + gate kernel and the packed
-    factors; groups = 4: the unfused launches), forward and backward in one graph.  T = 9 gives 180 rows, from
-    where the weight gradients are summed on the matrix unit."""
+    """Two stacked layers over a short sequence (the recurrence in one cooperative launch per direction), forward and
+    backward in one graph.  T = 9 gives 180 rows, from where the weight gradients are summed on the matrix unit."""
     import paper_2103_03936_amd as pf
     B, d, h, r, L = 20, 72, 80, 20, 2
 
@@ -112,3 +111,46 @@ def test_lstm_stack_graph_replay(groups, T):
                 gr[1]["dbias"])
 
     _replay_matches_eager(make, run, ("h_top", "c_0", "dx", "dh0_0", "dc0_1", "dVx_0", "dUh_0", "dUx_1", "dVh_1", "dbias_1"))
+
+
+@pytest.mark.parametrize("shape", [(300, 130), (90, 64)])
+def test_svd_graph_replay(shape):
+    """The SVD's cooperative launches (their number of sweeps is found on the device) in a graph; the second matrix is
+    ill-conditioned in two of the replays, which then need other sweeps than the one that was captured."""
+    import paper_2103_03936_amd as pf
+
+    def make(seed):
+        W = workloads.Stream(workloads.SEED_BASE + 960 + seed, "f32").normal(shape).astype("float32")
+        return {"W": to_gpu(W) * torch.logspace(0, -2 * seed, shape[1], device="cuda")}
+
+    def run(g):
+        return pf.pf_svd_split(g["W"], 20, return_info=True)
+
+    _replay_matches_eager(make, run, ("U", "V", "sigma", "info"))
+
+
+@pytest.mark.parametrize("B,h,r,groups", [(24, 40, 12, 4), (20, 48, 400, 1), (9, 1540, 24, 1)])
+def test_lstm_stack_launches_graph_replay(B, h, r, groups):
+    """What the one-launch recurrence does not take (a pair per gate above batch 20, rank above 384, more than 1536 units): the
+    schedule of launches per step."""
+    import paper_2103_03936_amd as pf
+    T, d, L = 4, 36, 2
+
+    def make(seed):
+        s = workloads.Stream(workloads.SEED_BASE + 720 + seed, "f32")
+        out = {"x": to_gpu(s.normal((T, B, d))), "dh_top": to_gpu(s.normal((T, B, h)))}
+        for l in range(L):
+            a = workloads.lstm_cell_inputs(B, d if l == 0 else h, h, r, groups=groups, seed=10 * seed + l)
+            for k in ("h_prev", "c_prev", "Vx", "Ux", "Vh", "Uh", "bias"):
+                out[f"{k}{l}"] = to_gpu(a[k])
+        return out
+
+    def run(g):
+        col = lambda k: [g[f"{k}{l}"] for l in range(L)]
+        f = [col(k) for k in ("Vx", "Ux", "Vh", "Uh")]
+        saved = pf.pf_lowrank_lstm_stack_fwd(g["x"], col("h_prev"), col("c_prev"), *f, col("bias"), groups)
+        dx, dh0, dc0, gr = pf.pf_lowrank_lstm_stack_bwd(g["x"], col("h_prev"), col("c_prev"), *saved, *f, g["dh_top"], None,
+                                                        None, groups)
+        return saved[0][L - 1], dx, dh0[0], dc0[1], gr[0]["dVx"], gr[0]["dVh"], gr[1]["dUx"], gr[1]["dbias"]
+
+    _replay_matches_eager(make, run, ("h_top", "dx", "dh0_0", "dc0_1", "dVx_0", "dVh_0", "dUx_1", "dbias_1"))
