@@ -152,23 +152,34 @@ PyObject *entry(PyObject *, PyObject *const *a, Py_ssize_t n)
     return nullptr;
 }
 
-// parameter gradients: new tensors, or those of a given tuple (accumulated into)
+// An owned reference
+struct Ref {
+    PyObject *o;
+    explicit Ref(PyObject *owned = nullptr) : o(owned) {}
+    Ref(const Ref &) = delete;
+    Ref(Ref &&r) : o(r.o) { r.o = nullptr; }
+    ~Ref() { Py_XDECREF(o); }
+};
+
+// parameter gradients: new tensors, or those of a given sequence of n (accumulated into; None: not wanted)
 struct Grads {
+    Ref items; // a list or tuple, which keeps them
     PyObject *g[3] = {nullptr, nullptr, nullptr};
     Out o[3];
     void *p[3] = {nullptr, nullptr, nullptr};
     bool given;
-    explicit Grads(PyObject *grads) : given(grads != Py_None)
+    Grads(PyObject *grads, int n) : given(grads != Py_None)
     {
         if (!given) return;
-        PyObject *s = PySequence_Fast(grads, "grads must be a sequence");
-        if (!s) throw Fail{nullptr, ""};
-        for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(s) && i < 3; ++i) {
-            g[i] = PySequence_Fast_GET_ITEM(s, i); // (kept alive by the caller's sequence)
+        items.o = PySequence_Fast(grads, "grads must be a sequence");
+        if (!items.o) throw Fail{nullptr, ""};
+        const Py_ssize_t have = PySequence_Fast_GET_SIZE(items.o);
+        if (have != n)
+            throw Fail{PyExc_ValueError, "grads must hold " + std::to_string(n) + " entries, not " + std::to_string(have)};
+        for (int i = 0; i < n; ++i) {
+            g[i] = PySequence_Fast_GET_ITEM(items.o, i);
+            p[i] = ptr(g[i], F32);
         }
-        Py_DECREF(s);
-        for (int i = 0; i < 3; ++i)
-            if (g[i]) p[i] = ptr(g[i], F32);
     }
     void make(int i, at::IntArrayRef size, const at::Device &dev)
     {
@@ -224,7 +235,7 @@ PyObject *linear_bwd(PyObject *const *a)
     const auto dev = X.device();
     Out dX;
     if (truth(a[7])) dX = Out(X.sizes(), dt, dev);
-    Grads g(a[9]);
+    Grads g(a[9], 3);
     if (!g.given) {
         g.make(0, {d.out, d.r}, dev);
         g.make(1, {d.in, d.r}, dev);
@@ -283,7 +294,7 @@ PyObject *shared_bwd(PyObject *const *a)
     const auto dev = X.device();
     Out dX;
     if (truth(a[5])) dX = Out(X.sizes(), dt, dev);
-    Grads g(a[7]);
+    Grads g(a[7], 3);
     if (!g.given) {
         g.make(0, U.sizes(), dev);
         g.make(1, V.sizes(), dev);
@@ -353,7 +364,7 @@ PyObject *conv_bwd(PyObject *const *a)
     const bool ep = truth(a[14]);
     Out dX;
     if (truth(a[10])) dX = Out(X.sizes(), dt, dev);
-    Grads g(a[12]);
+    Grads g(a[12], ep ? 3 : 2);
     if (!g.given) {
         g.make(0, Uk.sizes(), dev);
         g.make(1, Vp.sizes(), dev);
@@ -379,44 +390,32 @@ const char *const GRAD_NAMES[5] = {"dVx", "dUx", "dVh", "dUh", "dbias"};
 
 // The five parameter gradients of a layer: a given dict's tensors, or new ones in a new dict
 struct LstmGrads {
-    PyObject *dict = nullptr; // owned
+    Ref dict, items[5];
     void *p[5];
     LstmGrads(PyObject *given, const Tensor &Vx, const Tensor &Ux, const Tensor &Vh, const Tensor &Uh, int64_t h)
     {
         if (given != Py_None) {
-            dict = borrowed(given);
+            dict.o = borrowed(given);
             for (int i = 0; i < 5; ++i) {
-                PyObject *o = PyMapping_GetItemString(given, GRAD_NAMES[i]);
-                if (!o) throw Fail{nullptr, ""};
-                Py_DECREF(o); // (the mapping keeps it)
-                p[i] = ptr(o, F32);
+                items[i].o = PyMapping_GetItemString(given, GRAD_NAMES[i]);
+                if (!items[i].o) throw Fail{nullptr, ""};
+                p[i] = ptr(items[i].o, F32);
             }
             return;
         }
-        dict = PyDict_New();
+        dict.o = PyDict_New();
         const at::IntArrayRef sizes[4] = {Vx.sizes(), Ux.sizes(), Vh.sizes(), Uh.sizes()};
         for (int i = 0; i < 5; ++i) {
             const int64_t nb[1] = {4 * h};
             Out o(i < 4 ? sizes[i] : at::IntArrayRef(nb), F32, Vx.device());
             p[i] = o.p;
             PyObject *t = o.give();
-            PyDict_SetItemString(dict, GRAD_NAMES[i], t);
+            PyDict_SetItemString(dict.o, GRAD_NAMES[i], t);
             Py_DECREF(t);
         }
     }
-    LstmGrads(const LstmGrads &) = delete;
-    LstmGrads(LstmGrads &&o) : dict(o.dict)
-    {
-        for (int i = 0; i < 5; ++i) p[i] = o.p[i];
-        o.dict = nullptr;
-    }
-    ~LstmGrads() { Py_XDECREF(dict); }
-    PyObject *give()
-    {
-        PyObject *d = dict;
-        dict = nullptr;
-        return d;
-    }
+    LstmGrads(LstmGrads &&) = default;
+    PyObject *give() { return std::exchange(dict.o, nullptr); }
 };
 
 pf_lstm_desc cell_desc(const Tensor &x, const Tensor &h, const Tensor &Ux, long groups, bool bias)
@@ -567,13 +566,9 @@ PyObject *stack_bwd(PyObject *const *a)
     std::vector<LstmGrads> gr;
     gr.reserve(d.layers);
     for (int l = 0; l < d.layers; ++l) {
-        PyObject *given = Py_None;
-        if (a[17] != Py_None) {
-            given = PySequence_GetItem(a[17], l);
-            if (!given) throw Fail{nullptr, ""};
-            Py_DECREF(given); // (the sequence keeps it)
-        }
-        gr.emplace_back(given, Vx.at(l), Ux.at(l), Vh.at(l), Uh.at(l), d.h);
+        Ref given(a[17] != Py_None ? PySequence_GetItem(a[17], l) : borrowed(Py_None));
+        if (!given.o) throw Fail{nullptr, ""};
+        gr.emplace_back(given.o, Vx.at(l), Ux.at(l), Vh.at(l), Uh.at(l), d.h);
     }
     std::vector<void *> gp[5];
     for (int i = 0; i < 5; ++i)

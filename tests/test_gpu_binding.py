@@ -1,0 +1,43 @@
+"""The Python boundary: what it refuses, and that it keeps what it was given."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _linear(M=8, n_in=16, n_out=24, r=8):
+    g = torch.Generator(device="cuda").manual_seed(1)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    return n(M, n_in), n(n_in, r), n(n_out, r), n(M, n_out)
+
+
+def _zeros(*shapes):
+    return [torch.zeros(s, device="cuda") for s in shapes]
+
+
+@pytest.mark.parametrize("entries", [0, 1, 2, 4])
+def test_grads_of_the_wrong_length_are_refused(entries):
+    """Neither is a gradient left out nor an extra entry ignored."""
+    import paper_2103_03936_amd as pf
+    X, V, U, dY = _linear()
+    grads = _zeros((24, 8), (16, 8), (24,), (24,))[:entries]
+    for call in (pf.pf_lowrank_linear_bwd, pf.pf_lowrank_linear_bwd_ep):
+        with pytest.raises(ValueError):
+            call(X, V, U, dY, has_bias=True, grads=grads)
+    with pytest.raises(ValueError):
+        pf.pf_lowrank_linear_shared_bwd(X, V[None].contiguous(), U[None].contiguous(), dY[None].contiguous(), grads=grads)
+    Xc, Uk, Vp, dZ = torch.ones(2, 4, 6, 6, device="cuda"), *_zeros((4, 4, 3, 3), (8, 4)), torch.ones(2, 8, 6, 6, device="cuda")
+    with pytest.raises(ValueError):
+        pf.pf_lowrank_conv_bwd_ep(Xc, Uk, Vp, None, dZ, pad=1, grads=grads)
+    grads = _zeros((4, 4, 3, 3), (8, 4), (8,), (8,))[:3 if entries == 2 else entries]
+    with pytest.raises(ValueError):
+        pf.pf_lowrank_conv_bwd(Xc, Uk, Vp, dZ, pad=1, grads=grads)
+
+
+def test_grads_from_an_iterator():
+    """Entries that nothing else keeps alive, and one that is not wanted."""
+    import paper_2103_03936_amd as pf
+    X, V, U, dY = _linear()
+    _, dU, dV, db = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True)
+    _, gU, gV, none = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True, grads=(z for z in [*_zeros((24, 8), (16, 8)), None]))
+    assert torch.equal(gU, dU) and torch.equal(gV, dV) and none is None and db is not None
