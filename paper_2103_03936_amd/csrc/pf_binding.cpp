@@ -94,12 +94,13 @@ void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
 // A reusable byte buffer per (device, stream): calls enqueued on one stream are ordered, so they may share scratch
 // memory; calls on different streams get different buffers.  It grows and never shrinks; one that is outgrown is kept
-// alive rather than freed, so that graphs captured through these calls stay valid when a later call needs more.
+// alive rather than freed, so that graphs captured through these calls stay valid when a later call needs more.  Every call
+// of the package takes it from here, those that Python marshals through lend().
 struct Space {
     void *p;
     size_t n;
 };
-Space workspace(size_t bytes, const at::Device &dev)
+const Tensor &scratch(size_t bytes, const at::Device &dev)
 {
     static std::mutex lock;
     static auto &buffers = *new std::map<std::pair<int, void *>, Tensor>; // (never destroyed: the allocator may be gone)
@@ -111,6 +112,11 @@ Space workspace(size_t bytes, const at::Device &dev)
         if (t.defined()) retired.push_back(t);
         t = Tensor(at::detail::empty_cuda({(int64_t)(bytes < 256 ? 256 : bytes)}, at::kByte, dev, std::nullopt));
     }
+    return t;
+}
+Space workspace(size_t bytes, const at::Device &dev)
+{
+    const Tensor &t = scratch(bytes, dev);
     return Space{t.data_ptr(), (size_t)t.numel()};
 }
 
@@ -591,6 +597,9 @@ PyObject *stack_bwd(PyObject *const *a)
     return tuple({dx.give(), dh0.give(), dc0.give(), grads});
 }
 
+// bytes, a tensor on the device: the scratch buffer of the current stream
+PyObject *lend(PyObject *const *a) { return THPVariable_Wrap(scratch((size_t)integer(a[0]), tensor(a[1]).device())); }
+
 // The exceptions to raise: PfError, torch.OutOfMemoryError
 PyObject *set_errors(PyObject *, PyObject *args)
 {
@@ -612,6 +621,7 @@ PyMethodDef methods[] = {CALL(linear_fwd, 8),
                          CALL(cell_bwd, 16),
                          CALL(stack_fwd, 9),
                          CALL(stack_bwd, 18),
+                         CALL(lend, 2),
                          {"set_errors", set_errors, METH_VARARGS, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

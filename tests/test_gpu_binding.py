@@ -41,3 +41,16 @@ def test_grads_from_an_iterator():
     _, dU, dV, db = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True)
     _, gU, gV, none = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True, grads=(z for z in [*_zeros((24, 8), (16, 8)), None]))
     assert torch.equal(gU, dU) and torch.equal(gV, dV) and none is None and db is not None
+
+
+def test_one_scratch_buffer_per_stream():
+    """A call marshalled in Python (the SVD) and a native one share their stream's buffer."""
+    import paper_2103_03936_amd as pf
+    X, V, U, dY = _linear(64, 512, 512, 128)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        pf.pf_svd_split(torch.randn(300, 128, device="cuda"), 8)
+        torch.cuda.synchronize()
+        before = torch.cuda.memory_allocated()
+        pf.pf_lowrank_linear_bwd(X, V, U, dY)
+        torch.cuda.synchronize()
+        assert torch.cuda.memory_allocated() == before
