@@ -132,10 +132,19 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
-def _workspace(nbytes, like):
-    """The scratch buffer of torch's current stream on the device of `like`, at least nbytes: the one that the natively
-    marshalled calls use."""
-    return _native.lend(nbytes, like)
+class _workspace:
+    """with _workspace(nbytes, like) as ws: the scratch buffer of torch's current stream on the device of `like`, at least
+    nbytes.  It is the one that the natively marshalled calls use; other threads' calls on the stream wait meanwhile."""
+
+    def __init__(self, nbytes, like):
+        self.args = nbytes, like
+
+    def __enter__(self):
+        self.key, buf = _native.lend(*self.args)
+        return buf
+
+    def __exit__(self, *_):
+        _native.give_back(self.key)
 
 
 # ------------------------------------------------------------------ linear
@@ -198,9 +207,9 @@ def pf_dense_linear_fwd(X, W, bias=None):
     n_out = W.shape[0]
     d = pf_linear_desc(M, n_in, n_out, 1, _dtype_code(X), PF_F32, 1 if bias is not None else 0)
     Y = torch.empty((M, n_out), dtype=X.dtype, device=X.device)
-    ws = _workspace(256, X)
-    _check(lib.pf_dense_linear_fwd(ctypes.byref(d), _ptr(X), _ptr(W, X.dtype), _ptr(bias, X.dtype), _ptr(Y),
-                                   _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()), "pf_dense_linear_fwd")
+    with _workspace(256, X) as ws:
+        _check(lib.pf_dense_linear_fwd(ctypes.byref(d), _ptr(X), _ptr(W, X.dtype), _ptr(bias, X.dtype), _ptr(Y),
+                                       _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()), "pf_dense_linear_fwd")
     return Y
 
 
@@ -211,10 +220,10 @@ def pf_dense_linear_bwd(X, W, dY, has_bias=False):
     dX = torch.empty_like(X)
     dW = torch.empty((n_out, n_in), dtype=torch.float32, device=X.device)
     db = torch.empty((n_out,), dtype=torch.float32, device=X.device) if has_bias else None
-    ws = _workspace(lib.pf_dense_linear_workspace_bytes(ctypes.byref(d)), X)
-    _check(lib.pf_dense_linear_bwd(ctypes.byref(d), _ptr(X), _ptr(W, X.dtype), _ptr(dY, X.dtype), _ptr(dX),
-                                   _ptr(dW), _ptr(db), ctypes.c_int(0), _ptr(ws), ctypes.c_size_t(ws.numel()),
-                                   _stream()), "pf_dense_linear_bwd")
+    with _workspace(lib.pf_dense_linear_workspace_bytes(ctypes.byref(d)), X) as ws:
+        _check(lib.pf_dense_linear_bwd(ctypes.byref(d), _ptr(X), _ptr(W, X.dtype), _ptr(dY, X.dtype), _ptr(dX),
+                                       _ptr(dW), _ptr(db), ctypes.c_int(0), _ptr(ws), ctypes.c_size_t(ws.numel()),
+                                       _stream()), "pf_dense_linear_bwd")
     return dX, dW, db
 
 
@@ -256,9 +265,9 @@ def pf_dense_conv_fwd(X, Wd, stride=1, pad=0):
     d = pf_conv_desc(N, C, H, W, Cout, 1, k, stride, pad, PF_NCHW, _dtype_code(X), PF_F32)
     Ho, Wo = conv_out_hw(d)
     Y = torch.empty((N, Cout, Ho, Wo), dtype=X.dtype, device=X.device)
-    ws = _workspace(lib.pf_dense_conv_workspace_bytes(ctypes.byref(d)), X)
-    _check(lib.pf_dense_conv_fwd(ctypes.byref(d), _ptr(X), _ptr(Wd, X.dtype), _ptr(Y), _ptr(ws),
-                                 ctypes.c_size_t(ws.numel()), _stream()), "pf_dense_conv_fwd")
+    with _workspace(lib.pf_dense_conv_workspace_bytes(ctypes.byref(d)), X) as ws:
+        _check(lib.pf_dense_conv_fwd(ctypes.byref(d), _ptr(X), _ptr(Wd, X.dtype), _ptr(Y), _ptr(ws),
+                                     ctypes.c_size_t(ws.numel()), _stream()), "pf_dense_conv_fwd")
     return Y
 
 
@@ -268,10 +277,10 @@ def pf_dense_conv_bwd(X, Wd, dY, stride=1, pad=0):
     d = pf_conv_desc(N, C, H, W, Cout, 1, k, stride, pad, PF_NCHW, _dtype_code(X), PF_F32)
     dX = torch.empty_like(X)
     dW = torch.empty(Wd.shape, dtype=torch.float32, device=X.device)
-    ws = _workspace(lib.pf_dense_conv_workspace_bytes(ctypes.byref(d)), X)
-    _check(lib.pf_dense_conv_bwd(ctypes.byref(d), _ptr(X), _ptr(Wd, X.dtype), _ptr(dY, X.dtype), _ptr(dX), _ptr(dW),
-                                 ctypes.c_int(0), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
-           "pf_dense_conv_bwd")
+    with _workspace(lib.pf_dense_conv_workspace_bytes(ctypes.byref(d)), X) as ws:
+        _check(lib.pf_dense_conv_bwd(ctypes.byref(d), _ptr(X), _ptr(Wd, X.dtype), _ptr(dY, X.dtype), _ptr(dX), _ptr(dW),
+                                     ctypes.c_int(0), _ptr(ws), ctypes.c_size_t(ws.numel()), _stream()),
+               "pf_dense_conv_bwd")
     return dX, dW
 
 
@@ -304,11 +313,11 @@ def pf_lowrank_lstm_seq_fwd(x, h0, c0, Vx, Ux, Vh, Uh, bias=None, groups=1):
     gates_all = torch.empty((d.T, d.B, 4 * d.h), dtype=f32, device=dev)
     Tx_all = torch.empty((d.T, d.B, groups * d.r), dtype=f32, device=dev)
     Th_all = torch.empty((d.T, d.B, groups * d.r), dtype=f32, device=dev)
-    ws = _workspace(lib.pf_lowrank_lstm_seq_fwd_workspace_bytes(ctypes.byref(d)), x)
-    _check(lib.pf_lowrank_lstm_seq_fwd(ctypes.byref(d), _ptr(x, f32), _ptr(h0, f32), _ptr(c0, f32), _ptr(Vx, f32),
-                                       _ptr(Ux, f32), _ptr(Vh, f32), _ptr(Uh, f32), _ptr(bias, f32), _ptr(h_all),
-                                       _ptr(c_all), _ptr(gates_all), _ptr(Tx_all), _ptr(Th_all), _ptr(ws),
-                                       ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_lstm_seq_fwd")
+    with _workspace(lib.pf_lowrank_lstm_seq_fwd_workspace_bytes(ctypes.byref(d)), x) as ws:
+        _check(lib.pf_lowrank_lstm_seq_fwd(ctypes.byref(d), _ptr(x, f32), _ptr(h0, f32), _ptr(c0, f32), _ptr(Vx, f32),
+                                           _ptr(Ux, f32), _ptr(Vh, f32), _ptr(Uh, f32), _ptr(bias, f32), _ptr(h_all),
+                                           _ptr(c_all), _ptr(gates_all), _ptr(Tx_all), _ptr(Th_all), _ptr(ws),
+                                           ctypes.c_size_t(ws.numel()), _stream()), "pf_lowrank_lstm_seq_fwd")
     return h_all, c_all, gates_all, Tx_all, Th_all
 
 
@@ -326,14 +335,14 @@ def pf_lowrank_lstm_seq_bwd(x, h0, c0, h_all, c_all, gates_all, Tx_all, Th_all, 
     if grads is None:
         grads = dict(dVx=torch.empty_like(Vx), dUx=torch.empty_like(Ux), dVh=torch.empty_like(Vh),
                      dUh=torch.empty_like(Uh), dbias=torch.empty((4 * d.h,), dtype=f32, device=dev))
-    ws = _workspace(lib.pf_lowrank_lstm_seq_bwd_workspace_bytes(ctypes.byref(d)), x)
-    _check(lib.pf_lowrank_lstm_seq_bwd(
-        ctypes.byref(d), _ptr(x, f32), _ptr(h0, f32), _ptr(c0, f32), _ptr(h_all, f32), _ptr(c_all, f32),
-        _ptr(gates_all, f32), _ptr(Tx_all, f32), _ptr(Th_all, f32), _ptr(Vx, f32), _ptr(Ux, f32), _ptr(Vh, f32),
-        _ptr(Uh, f32), _ptr(dh_all, f32), _ptr(dhT, f32), _ptr(dcT, f32), _ptr(dx_all), _ptr(dh0), _ptr(dc0),
-        _ptr(grads["dVx"], f32), _ptr(grads["dUx"], f32), _ptr(grads["dVh"], f32), _ptr(grads["dUh"], f32),
-        _ptr(grads["dbias"], f32), ctypes.c_int(1 if accumulate else 0), _ptr(ws), ctypes.c_size_t(ws.numel()),
-        _stream()), "pf_lowrank_lstm_seq_bwd")
+    with _workspace(lib.pf_lowrank_lstm_seq_bwd_workspace_bytes(ctypes.byref(d)), x) as ws:
+        _check(lib.pf_lowrank_lstm_seq_bwd(
+            ctypes.byref(d), _ptr(x, f32), _ptr(h0, f32), _ptr(c0, f32), _ptr(h_all, f32), _ptr(c_all, f32),
+            _ptr(gates_all, f32), _ptr(Tx_all, f32), _ptr(Th_all, f32), _ptr(Vx, f32), _ptr(Ux, f32), _ptr(Vh, f32),
+            _ptr(Uh, f32), _ptr(dh_all, f32), _ptr(dhT, f32), _ptr(dcT, f32), _ptr(dx_all), _ptr(dh0), _ptr(dc0),
+            _ptr(grads["dVx"], f32), _ptr(grads["dUx"], f32), _ptr(grads["dVh"], f32), _ptr(grads["dUh"], f32),
+            _ptr(grads["dbias"], f32), ctypes.c_int(1 if accumulate else 0), _ptr(ws), ctypes.c_size_t(ws.numel()),
+            _stream()), "pf_lowrank_lstm_seq_bwd")
     return dx_all, dh0, dc0, grads
 
 
@@ -366,9 +375,9 @@ def pf_svd_split(W, r, return_info=False):
     V = torch.empty((n, r), dtype=torch.float32, device=dev)
     sigma = torch.empty((min(m, n),), dtype=torch.float32, device=dev)
     info = torch.empty((2,), dtype=torch.int32, device=dev) if return_info else None
-    ws = _workspace(lib.pf_svd_split_workspace_bytes(ctypes.byref(d)), W)
-    _check(lib.pf_svd_split(ctypes.byref(d), _ptr(W), _ptr(U), _ptr(V), _ptr(sigma), _ptr(info), _ptr(ws),
-                            ctypes.c_size_t(ws.numel()), _stream()), "pf_svd_split")
+    with _workspace(lib.pf_svd_split_workspace_bytes(ctypes.byref(d)), W) as ws:
+        _check(lib.pf_svd_split(ctypes.byref(d), _ptr(W), _ptr(U), _ptr(V), _ptr(sigma), _ptr(info), _ptr(ws),
+                                ctypes.c_size_t(ws.numel()), _stream()), "pf_svd_split")
     return (U, V, sigma, info) if return_info else (U, V, sigma)
 
 

@@ -92,39 +92,63 @@ PyObject *give_or(Out &o, PyObject *given) { return given ? borrowed(given) : o.
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
-// A reusable byte buffer per (device, stream): calls enqueued on one stream are ordered, so they may share scratch
-// memory; calls on different streams get different buffers.  It grows and never shrinks; one that is outgrown is kept
-// alive rather than freed, so that graphs captured through these calls stay valid when a later call needs more.  Every call
-// of the package takes it from here, those that Python marshals through lend().
-struct Space {
-    void *p;
-    size_t n;
-};
-const Tensor &scratch(size_t bytes, const at::Device &dev)
-{
-    static std::mutex lock;
-    static auto &buffers = *new std::map<std::pair<int, void *>, Tensor>; // (never destroyed: the allocator may be gone)
-    static auto &retired = *new std::vector<Tensor>;
-    if (!dev.is_cuda()) fail("tensors must live on the GPU; there is no CPU path");
-    std::lock_guard<std::mutex> hold(lock);
-    Tensor &t = buffers[{dev.index(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream()}];
-    if (!t.defined() || (size_t)t.numel() < bytes) {
-        if (t.defined()) retired.push_back(t);
-        t = Tensor(at::detail::empty_cuda({(int64_t)(bytes < 256 ? 256 : bytes)}, at::kByte, dev, std::nullopt));
-    }
-    return t;
-}
-Space workspace(size_t bytes, const at::Device &dev)
-{
-    const Tensor &t = scratch(bytes, dev);
-    return Space{t.data_ptr(), (size_t)t.numel()};
-}
-
 void check(int status, const char *what)
 {
     if (status != PF_OK)
         fail(std::string(what) + ": status " + std::to_string(status) + " (" + pf_status_string(status) + "), hip error " +
              std::to_string(pf_last_hip_error()));
+}
+
+// A reusable byte buffer per (device, stream): calls enqueued on one stream are ordered, so they may share scratch
+// memory; calls on different streams get different buffers.  It grows and never shrinks; one that is outgrown is kept
+// alive rather than freed, so that graphs captured through these calls stay valid when a later call needs more.  Every call
+// of the package takes it from here, those that Python marshals through lend(), and holds it until its launches are
+// enqueued: of two threads' calls on one stream the second's launches follow the first's.
+struct Space {
+    void *p;
+    size_t n;
+};
+struct Scratch {
+    std::recursive_mutex busy; // (recursive: a finalizer may run a call while its thread has the buffer lent)
+    Tensor t;
+    std::vector<Tensor> retired;
+    Space get(size_t bytes, const at::Device &dev)
+    {
+        if (!t.defined() || (size_t)t.numel() < bytes) {
+            if (t.defined()) retired.push_back(t);
+            t = Tensor(at::detail::empty_cuda({(int64_t)(bytes < 256 ? 256 : bytes)}, at::kByte, dev, std::nullopt));
+        }
+        return Space{t.data_ptr(), (size_t)t.numel()};
+    }
+};
+Scratch &scratch(const at::Device &dev)
+{
+    static std::mutex lock;
+    static auto &all = *new std::map<std::pair<int, void *>, Scratch>; // (never destroyed: the allocator may be gone)
+    std::lock_guard<std::mutex> hold(lock);
+    return all[{dev.index(), (void *)c10::hip::getCurrentHIPStream(dev.index()).stream()}];
+}
+
+// The interpreter runs other threads meanwhile
+struct NoGil {
+    PyThreadState *state = PyEval_SaveThread();
+    NoGil() {}
+    NoGil(const NoGil &) = delete;
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+// f(scratch memory): the call into the library, which touches no Python object
+template <class F>
+void call(const char *what, size_t bytes, const at::Device &dev, F f)
+{
+    if (!dev.is_cuda()) fail("tensors must live on the GPU; there is no CPU path");
+    int status;
+    {
+        NoGil released;
+        Scratch &s = scratch(dev);
+        std::lock_guard<std::recursive_mutex> hold(s.busy);
+        status = f(s.get(bytes, dev));
+    }
+    check(status, what);
 }
 bool truth(PyObject *o)
 {
@@ -220,15 +244,16 @@ PyObject *linear_fwd(PyObject *const *a)
     const auto dev = X.device();
     Out Y({d.M, d.out}, dt, dev), T;
     if (truth(a[6])) T = Out({d.M, d.r}, dt, dev);
-    const Space ws = workspace(pf_lowrank_linear_fwd_workspace_bytes(&d), dev);
+    void *const p[5] = {ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt)}, *const st = stream();
+    const size_t need = pf_lowrank_linear_fwd_workspace_bytes(&d);
+    const int act = (int)integer(a[5]);
     if (truth(a[7]))
-        check(pf_lowrank_linear_fwd_ep(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt),
-                                       (int)integer(a[5]), Y.p, T.p, ws.p, ws.n, stream()),
-              "pf_lowrank_linear_fwd_ep");
+        call("pf_lowrank_linear_fwd_ep", need, dev, [&](Space ws) {
+            return pf_lowrank_linear_fwd_ep(&d, p[0], p[1], p[2], p[3], p[4], act, Y.p, T.p, ws.p, ws.n, st);
+        });
     else
-        check(pf_lowrank_linear_fwd(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), Y.p, T.p, ws.p, ws.n,
-                                    stream()),
-              "pf_lowrank_linear_fwd");
+        call("pf_lowrank_linear_fwd", need, dev,
+             [&](Space ws) { return pf_lowrank_linear_fwd(&d, p[0], p[1], p[2], p[3], Y.p, T.p, ws.p, ws.n, st); });
     return tuple({Y.give(), T.give()});
 }
 
@@ -247,16 +272,17 @@ PyObject *linear_bwd(PyObject *const *a)
         g.make(1, {d.in, d.r}, dev);
         if (d.has_bias) g.make(2, {d.out}, dev);
     }
-    const Space ws = workspace(pf_lowrank_linear_bwd_workspace_bytes(&d), dev);
+    void *const p[6] = {ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt), ptr(a[5], dt)}, *const st = stream();
+    const size_t need = pf_lowrank_linear_bwd_workspace_bytes(&d);
+    const bool relu = truth(a[6]);
     if (truth(a[10]))
-        check(pf_lowrank_linear_bwd_ep(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt),
-                                       ptr(a[5], dt), truth(a[6]), dX.p, g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n,
-                                       stream()),
-              "pf_lowrank_linear_bwd_ep");
+        call("pf_lowrank_linear_bwd_ep", need, dev, [&](Space ws) {
+            return pf_lowrank_linear_bwd_ep(&d, p[0], p[1], p[2], p[3], p[4], p[5], relu, dX.p, g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n, st);
+        });
     else
-        check(pf_lowrank_linear_bwd(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt), dX.p,
-                                    g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n, stream()),
-              "pf_lowrank_linear_bwd");
+        call("pf_lowrank_linear_bwd", need, dev, [&](Space ws) {
+            return pf_lowrank_linear_bwd(&d, p[0], p[1], p[2], p[3], p[4], dX.p, g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n, st);
+        });
     return tuple({dX.give(), g.give(0), g.give(1), g.give(2)});
 }
 
@@ -284,10 +310,9 @@ PyObject *shared_fwd(PyObject *const *a)
     const auto dev = X.device();
     Out Y({d.groups, d.M, d.n_out}, dt, dev), T;
     if (truth(a[4])) T = Out({d.groups, d.M, d.r}, dt, dev);
-    const Space ws = workspace(pf_lowrank_linear_shared_fwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_linear_shared_fwd(&d, ptr(a[0]), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), Y.p, T.p, ws.p, ws.n,
-                                       stream()),
-          "pf_lowrank_linear_shared_fwd");
+    void *const p[4] = {ptr(a[0]), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt)}, *const st = stream();
+    call("pf_lowrank_linear_shared_fwd", pf_lowrank_linear_shared_fwd_workspace_bytes(&d), dev,
+         [&](Space ws) { return pf_lowrank_linear_shared_fwd(&d, p[0], p[1], p[2], p[3], Y.p, T.p, ws.p, ws.n, st); });
     return tuple({Y.give(), T.give()});
 }
 
@@ -306,10 +331,10 @@ PyObject *shared_bwd(PyObject *const *a)
         g.make(1, V.sizes(), dev);
         if (d.has_bias) g.make(2, {d.groups, d.n_out}, dev);
     }
-    const Space ws = workspace(pf_lowrank_linear_shared_bwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_linear_shared_bwd(&d, ptr(a[0]), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt), dX.p,
-                                       g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n, stream()),
-          "pf_lowrank_linear_shared_bwd");
+    void *const p[5] = {ptr(a[0]), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], dt), ptr(a[4], dt)}, *const st = stream();
+    call("pf_lowrank_linear_shared_bwd", pf_lowrank_linear_shared_bwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_linear_shared_bwd(&d, p[0], p[1], p[2], p[3], p[4], dX.p, g.p[0], g.p[1], g.p[2], g.given, ws.p, ws.n, st);
+    });
     return tuple({dX.give(), g.give(0), g.give(1), g.give(2)});
 }
 
@@ -349,14 +374,16 @@ PyObject *conv_fwd(PyObject *const *a)
     if (truth(a[9])) T = Out({d.N, d.r, Ho, Wo}, dt, dev);
     const size_t nW = save_W ? pf_lowrank_conv_saved_weights_bytes(&d) : 0;
     if (nW) W = Out({(int64_t)nW}, at::kByte, dev);
-    const Space ws = workspace(pf_lowrank_conv_fwd_workspace_bytes(&d), dev);
+    void *const p[6] = {ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], F32), ptr(a[4], F32), ptr(a[5], dt)}, *const st = stream();
+    const size_t need = pf_lowrank_conv_fwd_workspace_bytes(&d);
+    const int act = (int)integer(a[6]);
     if (truth(a[11]))
-        check(pf_lowrank_conv_fwd_ep(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], F32), ptr(a[4], F32),
-                                     ptr(a[5], dt), (int)integer(a[6]), Y.p, T.p, W.p, ws.p, ws.n, stream()),
-              "pf_lowrank_conv_fwd_ep");
+        call("pf_lowrank_conv_fwd_ep", need, dev, [&](Space ws) {
+            return pf_lowrank_conv_fwd_ep(&d, p[0], p[1], p[2], p[3], p[4], p[5], act, Y.p, T.p, W.p, ws.p, ws.n, st);
+        });
     else
-        check(pf_lowrank_conv_fwd(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), Y.p, T.p, W.p, ws.p, ws.n, stream()),
-              "pf_lowrank_conv_fwd");
+        call("pf_lowrank_conv_fwd", need, dev,
+             [&](Space ws) { return pf_lowrank_conv_fwd(&d, p[0], p[1], p[2], Y.p, T.p, W.p, ws.p, ws.n, st); });
     return save_W ? tuple({Y.give(), T.give(), W.give()}) : tuple({Y.give(), T.give()});
 }
 
@@ -376,18 +403,19 @@ PyObject *conv_bwd(PyObject *const *a)
         g.make(1, Vp.sizes(), dev);
         if (ep && truth(a[11])) g.make(2, {d.Cout}, dev);
     }
+    void *const p[6] = {ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[4], dt), ptr(a[5], dt), ptr(a[13])}, *const st = stream();
     if (ep) {
-        const Space ws = workspace(pf_lowrank_conv_bwd_ep_workspace_bytes(&d), dev);
-        check(pf_lowrank_conv_bwd_ep(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[3], F32), ptr(a[4], dt),
-                                     ptr(a[5], dt), ptr(a[13]), ptr(a[8], dt), truth(a[9]), dX.p, g.p[0], g.p[1], g.p[2],
-                                     g.given, ws.p, ws.n, stream()),
-              "pf_lowrank_conv_bwd_ep");
+        void *const scale = ptr(a[3], F32), *const add = ptr(a[8], dt);
+        const bool relu = truth(a[9]);
+        call("pf_lowrank_conv_bwd_ep", pf_lowrank_conv_bwd_ep_workspace_bytes(&d), dev, [&](Space ws) {
+            return pf_lowrank_conv_bwd_ep(&d, p[0], p[1], p[2], scale, p[3], p[4], p[5], add, relu, dX.p, g.p[0], g.p[1], g.p[2], g.given,
+                                          ws.p, ws.n, st);
+        });
         return tuple({dX.give(), g.give(0), g.give(1), g.give(2)});
     }
-    const Space ws = workspace(pf_lowrank_conv_bwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_conv_bwd(&d, ptr(a[0], dt), ptr(a[1], dt), ptr(a[2], dt), ptr(a[4], dt), ptr(a[5], dt), ptr(a[13]),
-                              dX.p, g.p[0], g.p[1], g.given, ws.p, ws.n, stream()),
-          "pf_lowrank_conv_bwd");
+    call("pf_lowrank_conv_bwd", pf_lowrank_conv_bwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_conv_bwd(&d, p[0], p[1], p[2], p[3], p[4], p[5], dX.p, g.p[0], g.p[1], g.given, ws.p, ws.n, st);
+    });
     return tuple({dX.give(), g.give(0), g.give(1)});
 }
 
@@ -447,11 +475,11 @@ PyObject *cell_fwd(PyObject *const *a)
     const int64_t gr = d.groups * d.r;
     Out h({d.B, d.h}, F32, dev), c({d.B, d.h}, F32, dev), g({d.B, 4 * d.h}, F32, dev), Tx({d.B, gr}, F32, dev),
         Th({d.B, gr}, F32, dev);
-    const Space ws = workspace(pf_lowrank_lstm_cell_fwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_lstm_cell_fwd(&d, ptr(a[0], F32), ptr(a[1], F32), ptr(a[2], F32), ptr(a[3], F32), ptr(a[4], F32),
-                                   ptr(a[5], F32), ptr(a[6], F32), ptr(a[7], F32), h.p, c.p, g.p, Tx.p, Th.p, ws.p, ws.n,
-                                   stream()),
-          "pf_lowrank_lstm_cell_fwd");
+    void *p[8], *const st = stream();
+    for (int i = 0; i < 8; ++i) p[i] = ptr(a[i], F32);
+    call("pf_lowrank_lstm_cell_fwd", pf_lowrank_lstm_cell_fwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_lstm_cell_fwd(&d, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], h.p, c.p, g.p, Tx.p, Th.p, ws.p, ws.n, st);
+    });
     return tuple({h.give(), c.give(), g.give(), Tx.give(), Th.give()});
 }
 
@@ -464,18 +492,20 @@ PyObject *cell_bwd(PyObject *const *a)
     Out dx, dh(hp.sizes(), F32, dev), dc(tensor(a[2]).sizes(), F32, dev);
     if (truth(a[14])) dx = Out(x.sizes(), F32, dev);
     LstmGrads g(a[15], tensor(a[7]), tensor(a[8]), tensor(a[9]), tensor(a[10]), d.h);
-    const Space ws = workspace(pf_lowrank_lstm_cell_bwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_lstm_cell_bwd(&d, ptr(a[0], F32), ptr(a[1], F32), ptr(a[2], F32), ptr(a[3], F32), ptr(a[4], F32),
-                                   ptr(a[5], F32), ptr(a[6], F32), ptr(a[7], F32), ptr(a[8], F32), ptr(a[9], F32),
-                                   ptr(a[10], F32), ptr(a[11], F32), ptr(a[12], F32), dx.p, dh.p, dc.p, g.p[0], g.p[1],
-                                   g.p[2], g.p[3], g.p[4], a[15] != Py_None, ws.p, ws.n, stream()),
-          "pf_lowrank_lstm_cell_bwd");
+    void *p[13], *const st = stream();
+    for (int i = 0; i < 13; ++i) p[i] = ptr(a[i], F32);
+    const bool given = a[15] != Py_None;
+    call("pf_lowrank_lstm_cell_bwd", pf_lowrank_lstm_cell_bwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_lstm_cell_bwd(&d, p[0], p[1], p[2], p[3], p[4], p[5], p[6], p[7], p[8], p[9], p[10], p[11], p[12], dx.p, dh.p,
+                                        dc.p, g.p[0], g.p[1], g.p[2], g.p[3], g.p[4], given, ws.p, ws.n, st);
+    });
     return tuple({dx.give(), dh.give(), dc.give(), g.give()});
 }
 
 // A list with one tensor (or None) per layer and the host array of its pointers
 struct Layers {
     PyObject *seq = nullptr;
+    std::vector<Tensor> keep; // (another thread may change the list during the call)
     std::vector<void *> p;
     bool present;
     explicit Layers(PyObject *o, at::ScalarType want = F32) : present(o != Py_None)
@@ -483,7 +513,11 @@ struct Layers {
         if (!present) return;
         seq = PySequence_Fast(o, "expected a list with one tensor per layer");
         if (!seq) throw Fail{nullptr, ""};
-        for (Py_ssize_t i = 0; i < size(); ++i) p.push_back(ptr(PySequence_Fast_GET_ITEM(seq, i), want));
+        for (Py_ssize_t i = 0; i < size(); ++i) {
+            PyObject *t = PySequence_Fast_GET_ITEM(seq, i);
+            p.push_back(ptr(t, want));
+            if (t != Py_None) keep.push_back(tensor(t));
+        }
     }
     Layers(const Layers &) = delete;
     ~Layers() { Py_XDECREF(seq); }
@@ -546,12 +580,13 @@ PyObject *stack_fwd(PyObject *const *a)
     Outs o[5];
     for (int i = 0; i < 5; ++i)
         for (int l = 0; l < d.layers; ++l) o[i].add({d.T, d.B, n[i]}, dev);
-    const Space ws = workspace(pf_lowrank_lstm_stack_fwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_lstm_stack_fwd(&d, ptr(a[0], F32), h0.arr<const void *>(), c0.arr<const void *>(),
-                                    Vx.arr<const void *>(), Ux.arr<const void *>(), Vh.arr<const void *>(),
-                                    Uh.arr<const void *>(), bias.arr<const void *>(), o[0].p.data(), o[1].p.data(),
-                                    o[2].p.data(), o[3].p.data(), o[4].p.data(), ws.p, ws.n, stream()),
-          "pf_lowrank_lstm_stack_fwd");
+    void *const px = ptr(a[0], F32), *const st = stream();
+    call("pf_lowrank_lstm_stack_fwd", pf_lowrank_lstm_stack_fwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_lstm_stack_fwd(&d, px, h0.arr<const void *>(), c0.arr<const void *>(), Vx.arr<const void *>(),
+                                         Ux.arr<const void *>(), Vh.arr<const void *>(), Uh.arr<const void *>(),
+                                         bias.arr<const void *>(), o[0].p.data(), o[1].p.data(), o[2].p.data(), o[3].p.data(),
+                                         o[4].p.data(), ws.p, ws.n, st);
+    });
     return tuple({o[0].give(), o[1].give(), o[2].give(), o[3].give(), o[4].give()});
 }
 
@@ -579,14 +614,15 @@ PyObject *stack_bwd(PyObject *const *a)
     std::vector<void *> gp[5];
     for (int i = 0; i < 5; ++i)
         for (int l = 0; l < d.layers; ++l) gp[i].push_back(gr[l].p[i]);
-    const Space ws = workspace(pf_lowrank_lstm_stack_bwd_workspace_bytes(&d), dev);
-    check(pf_lowrank_lstm_stack_bwd(
-              &d, ptr(a[0], F32), h0.arr<const void *>(), c0.arr<const void *>(), h.arr<const void *>(),
-              c.arr<const void *>(), g.arr<const void *>(), Tx.arr<const void *>(), Th.arr<const void *>(),
-              Vx.arr<const void *>(), Ux.arr<const void *>(), Vh.arr<const void *>(), Uh.arr<const void *>(),
-              ptr(a[12], F32), dhT.arr<const void *>(), dcT.arr<const void *>(), dx.p, dh0.p.data(), dc0.p.data(),
-              gp[0].data(), gp[1].data(), gp[2].data(), gp[3].data(), gp[4].data(), a[17] != Py_None, ws.p, ws.n, stream()),
-          "pf_lowrank_lstm_stack_bwd");
+    void *const px = ptr(a[0], F32), *const pdh = ptr(a[12], F32), *const st = stream();
+    const bool given = a[17] != Py_None;
+    call("pf_lowrank_lstm_stack_bwd", pf_lowrank_lstm_stack_bwd_workspace_bytes(&d), dev, [&](Space ws) {
+        return pf_lowrank_lstm_stack_bwd(&d, px, h0.arr<const void *>(), c0.arr<const void *>(), h.arr<const void *>(),
+                                         c.arr<const void *>(), g.arr<const void *>(), Tx.arr<const void *>(), Th.arr<const void *>(),
+                                         Vx.arr<const void *>(), Ux.arr<const void *>(), Vh.arr<const void *>(), Uh.arr<const void *>(),
+                                         pdh, dhT.arr<const void *>(), dcT.arr<const void *>(), dx.p, dh0.p.data(), dc0.p.data(),
+                                         gp[0].data(), gp[1].data(), gp[2].data(), gp[3].data(), gp[4].data(), given, ws.p, ws.n, st);
+    });
     PyObject *grads = a[17];
     if (grads == Py_None) {
         grads = PyList_New(d.layers);
@@ -597,8 +633,31 @@ PyObject *stack_bwd(PyObject *const *a)
     return tuple({dx.give(), dh0.give(), dc0.give(), grads});
 }
 
-// bytes, a tensor on the device: the scratch buffer of the current stream
-PyObject *lend(PyObject *const *a) { return THPVariable_Wrap(scratch((size_t)integer(a[0]), tensor(a[1]).device())); }
+// bytes, a tensor on the device: the scratch buffer of the current stream, held by this thread until it gives it back
+PyObject *lend(PyObject *const *a)
+{
+    const size_t bytes = (size_t)integer(a[0]);
+    const auto dev = tensor(a[1]).device();
+    if (!dev.is_cuda()) fail("tensors must live on the GPU; there is no CPU path");
+    Scratch *s;
+    {
+        NoGil released;
+        s = &scratch(dev);
+        s->busy.lock();
+    }
+    try {
+        s->get(bytes, dev);
+    } catch (...) {
+        s->busy.unlock();
+        throw;
+    }
+    return tuple({PyLong_FromVoidPtr(s), THPVariable_Wrap(s->t)});
+}
+PyObject *give_back(PyObject *const *a)
+{
+    ((Scratch *)PyLong_AsVoidPtr(a[0]))->busy.unlock();
+    Py_RETURN_NONE;
+}
 
 // The exceptions to raise: PfError, torch.OutOfMemoryError
 PyObject *set_errors(PyObject *, PyObject *args)
@@ -622,6 +681,7 @@ PyMethodDef methods[] = {CALL(linear_fwd, 8),
                          CALL(stack_fwd, 9),
                          CALL(stack_bwd, 18),
                          CALL(lend, 2),
+                         CALL(give_back, 1),
                          {"set_errors", set_errors, METH_VARARGS, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -54,3 +54,55 @@ def test_one_scratch_buffer_per_stream():
         pf.pf_lowrank_linear_bwd(X, V, U, dY)
         torch.cuda.synchronize()
         assert torch.cuda.memory_allocated() == before
+
+
+def test_a_call_waits_for_its_streams_buffer_without_the_interpreter():
+    """While another thread has the stream's scratch buffer a call waits, and Python goes on meanwhile; on another stream it
+    does not wait."""
+    import threading
+    import paper_2103_03936_amd as pf
+    X, V, U, dY = _linear(64, 512, 512, 128)
+    stream = torch.cuda.current_stream()
+    pf.pf_lowrank_linear_bwd(X, V, U, dY)
+    done = threading.Event()
+
+    def call():
+        with torch.cuda.stream(stream):
+            pf.pf_lowrank_linear_bwd(X, V, U, dY)
+        done.set()
+
+    thread = threading.Thread(target=call)
+    with pf._workspace(256, X):
+        thread.start()
+        assert not done.wait(0.2)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            pf.pf_lowrank_linear_bwd(X, V, U, dY)
+    assert done.wait(60)
+    thread.join()
+
+
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_threads(own_stream):
+    """Four threads' calls, on one stream (which share its scratch buffer) and on their own, give what one thread gets."""
+    import threading
+    import paper_2103_03936_amd as pf
+    shapes = [(64, 512, 512, 128), (300, 200, 100, 30), (129, 65, 127, 33), (1000, 130, 72, 17)]
+    inputs = [_linear(*s) for s in shapes]
+    want = [pf.pf_lowrank_linear_bwd(*a, has_bias=True) for a in inputs]
+    torch.cuda.synchronize()
+    main, wrong = torch.cuda.current_stream(), []
+
+    def work(i):
+        s = torch.cuda.Stream() if own_stream else main
+        with torch.cuda.stream(s):
+            for _ in range(100):
+                got = pf.pf_lowrank_linear_bwd(*inputs[i], has_bias=True)
+            s.synchronize()
+            wrong.extend(k for k, (g, w) in enumerate(zip(got, want[i])) if not torch.equal(g, w))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
