@@ -16,7 +16,7 @@ struct LstmRunLayer {
     float *dh0, *dc0, *dz, *dTh, *dTx;
 };
 struct LstmRecurrence {
-    size_t (*floats)(const LstmGeom &g, bool bwd); // workspace
+    size_t (*floats)(const LstmGeom &g, bool bwd); // workspace (0: no device takes the call)
     bool (*fits)(const LstmGeom &g, bool bwd);     // this device can hold the launch's workgroups at once
     // ws: 256-byte aligned; dh_top: gradient of the top layer's outputs, backward only
     int (*run)(const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, bool bwd, float *ws, hipStream_t s);

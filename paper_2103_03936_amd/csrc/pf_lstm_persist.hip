@@ -607,7 +607,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
 }
 
 // ------------------------------------------------------------------ host side
-// compute units of the current device, 0 if it cannot run cooperative launches
+constexpr int LP_MOST_CUS = 256;
+// compute units of the current device that a launch may use, 0 if it cannot run cooperative launches
 static int lp_cus()
 {
     static std::atomic<int> known[16]; // (0: not asked yet)
@@ -617,18 +618,22 @@ static int lp_cus()
         return known[dev].load(std::memory_order_relaxed) - 1;
     int n = 0, coop = 0;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
+    if (n > LP_MOST_CUS) n = LP_MOST_CUS;
     if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) n = 0;
     if (dev >= 0 && dev < 16) known[dev].store(n + 1, std::memory_order_relaxed);
     return n;
 }
 
-// (sizes do not depend on the device: a workspace may be asked for before one is chosen)
-static size_t lp_floats(const LstmGeom &g, bool bwd) { return lp_plan(g, bwd, 256).floats; }
+// Whether the largest device could take the call, and what it needs there: sizes do not depend on the device (a workspace may be
+// asked for before one is chosen).  A single step uses the factors once: 125 us as launches, 160 here (1216 units, batch 28).
+static size_t lp_floats(const LstmGeom &g, bool bwd)
+{
+    const LpPlan p = lp_plan(g, bwd, LP_MOST_CUS);
+    return g.T + g.L < 3 || p.NT == 0 ? 0 : p.floats;
+}
 static bool lp_fits(const LstmGeom &g, bool bwd)
 {
-    if (g.T + g.L < 3) return false; // a single step uses the factors once: 125 us as launches, 160 here (1216 units, batch 28)
-    const int cus = lp_cus();
-    return cus > 0 && lp_plan(g, bwd, cus).NT > 0;
+    return lp_floats(g, bwd) > 0 && lp_plan(g, bwd, lp_cus()).NT > 0;
 }
 
 static int lp_launch(void (*kernel)(LpArgs), const LpArgs &a, bool bwd, hipStream_t s)

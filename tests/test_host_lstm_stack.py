@@ -170,3 +170,15 @@ def test_a_workspace_one_byte_short_is_refused(emu):
     st = emu.pf_lowrank_lstm_stack_fwd(ctypes.byref(desc), ctypes.c_void_p(256), *args, _p(ws), ctypes.c_size_t(need - 1),
                                        None)
     assert st == 4
+
+
+@pytest.mark.parametrize("T,B,h,r,groups,L", [(35, 20, 1540, 24, 1, 1), (35, 20, 64, 400, 1, 2), (35, 24, 64, 16, 4, 2),
+                                              (1, 28, 1216, 300, 1, 1), (70, 32, 256, 64, 4, 1)])
+def test_workspace_holds_the_schedule_that_runs(emu, T, B, h, r, groups, L):
+    """Where the one-launch recurrence does not take a call, its exchange buffers are not part of the workspace: the library
+    asks for what the schedule of launches alone (all that the emulation has) asks for."""
+    from paper_2103_03936_amd import lib
+    d = _Desc(T, B, h, h, r, groups, L, 0, 1)
+    for name in ("pf_lowrank_lstm_stack_fwd_workspace_bytes", "pf_lowrank_lstm_stack_bwd_workspace_bytes"):
+        need = getattr(emu, name)(ctypes.byref(d))
+        assert need > 0 and getattr(lib, name)(ctypes.byref(d)) == need, name
