@@ -11,9 +11,9 @@ __global__ __launch_bounds__(TILE_THREADS, CFG::template OCC<CT>) void tile_line
     const TileArgs &a = tile_args(by_value);
     constexpr int BM = CFG::BM, BN = CFG::BN, BK = TileEl<CT>::BK;
     typedef LoadKC<CT, BM> AK;
-    typedef LoadKC<CT, BM, false, true> AKS;
+    typedef LoadKC<CT, BM, true> AKS;
     typedef LoadMC<CT, BM, true> AM;
-    typedef LoadKC<CT, BN, false, true> BKC;
+    typedef LoadKC<CT, BN, true> BKC;
     typedef LoadMC<CT, BN> BMC;
     constexpr int s1 = TileSize<CT, CFG, AK, BKC>::bytes, s2 = TileSize<CT, CFG, AK, BMC>::bytes,
                   s3 = TileSize<CT, CFG, AM, BMC>::bytes;

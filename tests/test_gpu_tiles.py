@@ -55,3 +55,16 @@ def test_lstm_cell(shape, groups):
 def test_linear_shared(shape, dtype):
     """The middle one splits the contraction of dT, whose layers then lie one after the other instead of side by side."""
     test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=shape[0] != 700, seed=24)
+
+
+def test_bias_gradient_of_many_rows():
+    """Float sums over 16384 rows of zero mean, unsplit.  Chains of n additions of such terms are off by about 2^-24 sqrt(n / 6)
+    of the sum, rms: 2^-22 for runs of at most 96 rows, which the thousands of one thread's single chain would miss."""
+    import torch
+    import paper_2103_03936_amd as pf
+    g = torch.Generator(device="cuda").manual_seed(5)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    X, V, U, dY = n(16384, 1024), n(1024, 250) * 0.05, n(1000, 250) * 0.05, n(16384, 1000)
+    db = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True)[3].double()
+    want = dY.double().sum(0)
+    assert float((db - want).norm() / want.norm()) <= 2.0 ** -22
