@@ -200,7 +200,7 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     const int tab = 2 * (4096 + (kk * HC + 15) / 16 * 16 + (p.gather ? 4 * V * HC : 0));
     if (tab > 28 * 1024) return;
     p.tiles = true;
-    const i64 npx = (i64)g.N * HC * V, npin = (i64)g.N * HCin * V;
+    const i64 npx = (i64)g.N * HC * V;
     p.sh_T = g.r <= 32 ? TS_32x64 : TS_64;
     p.sh_Y = g.Cout <= 32 ? TS_32x64 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
     p.sh_dT = p.sh_T;
@@ -217,7 +217,6 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     const size_t part_T = (size_t)(p.ks_T > p.ks_dT ? p.ks_T : p.ks_dT) * g.r * npx;
     p.n_part_T = p.ks_T > 1 || p.ks_dT > 1 ? part_T : 0;
     p.sh_g = TS_64;
-    (void)npin;
     p.sh_w = g.r <= 32 ? TS_32x128 : TS_64;
     // both filter gradients in one launch: about two workgroups per compute unit, each at least four chunks long.  With at most 32
     // filters the gradients of both stages have the rank as their rows (dVp is formed transposed).
@@ -524,7 +523,6 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
             int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
             const int ni = phase_taps(g, f / g.s, ti, oi), nj = phase_taps(g, f % g.s, tj, oj), nt = ni * nj;
             const T *W = Uk;
-            i64 ldw = 0;
             PixView v = vdT;
             TileProb pk = tile_prob(TILE_PACK, g.C, g.r, 0, Uk, 0, nullptr, 0, pack[f], 0);
             for (int t = 0; t < nt; ++t) {
@@ -541,7 +539,6 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
             }
             TileProb q = kk > 1 ? tile_prob(TILE_CONV, g.C, npx, g.r * nt, W, g.r * nt, nullptr, 0, dX, 0)
                                 : tile_prob(TILE_CONVT, g.C, npx, nt > 0 ? g.r : 0, Uk, g.C, nullptr, 0, dX, 0);
-            (void)ldw;
             q.pb = v;
             out_planes(q.o, vdT, g.C);
             q.o.add = ep.add;
