@@ -245,12 +245,14 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
 {
     ConvPlan p;
     p.chain = dtype == PF_BF16 && chain_supported(g.C, g.Cout, g.r, g.H, g.W, g.k, g.s, g.p);
-    // One workgroup per image, 64 pixel columns whatever the image has: the tiled products are faster where most of the
-    // columns would be empty (4 x 4 images, 512 channels, rank 128, 3x3: 62 against 100 us at batch 4, 130 against 139 at
-    // 256) and where a few images would have to stream megabytes of filters through a few compute units (7 x 7 images,
-    // the same filters: 67 against 90 us at batch 4, 77 against 92 at 16, equal at 32).
+    // One workgroup per image, 64 pixel columns whatever the image has: of 3x3 layers the tiled products are faster where most
+    // of the columns would be empty (4 x 4 images, 512 channels, forward and backward together, tiled against chain: rank 128
+    // 51 against 76 us at batch 4, 86 against 97 at 128, equal at 256; rank 64 45 against 50 and 66 against 69) and where a few
+    // images would have to stream megabytes of filters through a few compute units (7 x 7 images, rank 128: 57 against 66 us
+    // at batch 4, 67 against 70 at 16, 83 against 74 at 32).  Of 1x1 layers they never are (4 x 4 images: 37 against 36 us at
+    // batch 4, 59 against 49 at 256; 7 x 7, 2048 -> 512: 49 against 48 and 182 against 77).
     plan_conv_tiles(g, dtype, p);
-    if (p.tiles && (g.H * g.W < 32 || (g.k == 3 && g.r > 64 && g.N < 32))) p.chain = false;
+    if (p.tiles && g.k == 3 && (g.H * g.W < 32 || (g.r > 64 && g.N < 32))) p.chain = false;
     p.n_w1 = chain_w1_elems(g.C, g.r, g.k);
     p.n_w2 = chain_w2_elems(g.Cout, g.r, 1);
     p.n_w1b = chain_w1_elems(g.Cout, g.r, 1);
