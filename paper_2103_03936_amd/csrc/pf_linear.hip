@@ -169,19 +169,38 @@ struct LinearPlan {
     size_t n_small;        // slices of the rank-r intermediate(s) between them, floats
 };
 
-// Chain kernel or tiled products?  A workgroup of the chain kernel takes 32 rows through the whole layer one after the
-// other, about 5 us per 1024 of `width` (in + out) however few rows there are; the tiled products
-// spread few rows over the chip but move the intermediates through memory.  Measured (us, chain / tiled):
-//   forward, 512 -> 512:   7.3 / 10.6 at 64 rows,  7.8 / 13.6 at 2048
-//   forward, 512 -> 2048: 14.1 / 10.6 at 64 rows, 14.4 / 13.7 at 512, 15.9 / 17.8 at 2048
-//   training, encoder layer d = 512 (backward on either): 250 / 150 at 300 rows, 285 / 245 at 3000, 305 / 294 at 4096,
-//   327 / 342 at 6000; d = 256, rank 64: 272 / 154 at 3000, 310 / 245 at 8192, a 1024 -> 1024 layer 82 / 128 at 16384
-static bool chain_fwd_pays(i64 M, i64 width, i64 r)
+// Chain kernel or tiled products?  A workgroup of the chain kernel takes 32 rows through the whole layer, one stage after the
+// other, so 8192 rows are one round of the chip whose length is the layer's width, however few rows there are; the
+// tiled products spread few rows over the chip but move the intermediates through memory.  Measured with calls on one stream
+// (us, chain / tiled), rank 128:
+//   forward:  512 -> 512    8 / 10 at 64 rows,   8 / 12 at 4000,  9 / 14 at 8192,  16 / 20 at 16384
+//             512 -> 2048  13 / 10              15 / 17           18 / 27           32 / 43
+//            1024 -> 1024  13 / 11              14 / 14           17 / 22           31 / 32
+//            2048 -> 512   16 / 12              19 / 17           20 / 22           38 / 31
+//            4096 -> 512   26 / 13              32 / 25           33 / 32           62 / 44
+//   backward: 512 -> 512   16 /  9              26 / 23           28 / 30           42 / 38
+//             512 -> 2048  32 / 12              44 / 34           53 / 46           91 / 73
+//            1024 -> 512   18 / 10              28 / 27           33 / 37           51 / 56
+//            2048 -> 512   22 / 10              34 / 39           42 / 55           69 / 94
+//            2048 -> 2048  38 / 12              54 / 56           67 / 82          116 / 106
+//   three 512 -> 512 layers that share their input: forward 8 / 10 at 64 rows, 26 / 27 at 8192, 50 / 45 at 16384; backward
+//   53 / 16, 88 / 51, 135 / 87
+// and rank 64 (whose factors are re-ordered first): 1024 -> 256 forward 12 / 10, 13 / 13, 14 / 13, 16 / 17, at 32768 rows 29 / 25;
+// backward 23 / 9, 33 / 24, 35 / 27, 42 / 39, 62 / 74.
+static bool chain_fwd_pays(i64 M, i64 in, i64 out, i64 r)
 {
-    if (r != 128) return M >= 10000;
-    return 10 * M >= 7 * (width - 1024);
+    if (r != 128) return M >= 10000 && M <= 16384;
+    if (M > 8192) return in <= 512;
+    return in + out <= 1536 || (M >= 4096 && in <= 2048);
 }
-static bool chain_bwd_pays(i64 M, i64 r) { return M >= (r == 128 ? 4608 : 10000); }
+static bool chain_bwd_pays(i64 M, i64 in, i64 out, i64 r)
+{
+    if (r != 128) return in > out && M >= 24000;
+    if (in > out) return in >= 768 && M >= 4096;
+    return in == out && M >= 5000 && M <= 10000;
+}
+// (several layers that share their input; backward, their dX is one tiled product over all ranks)
+static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 512 || (in <= 1024 && M <= 4096)); }
 
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
@@ -197,8 +216,8 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.fwd_bytes = align_up(p.n_T * sizeof(float));
     p.bwd_bytes = align_up(p.n_T * sizeof(float)) + align_up(p.n_dT * sizeof(float)) + align_up(p.n_part * sizeof(float));
     p.fused = d->dtype == PF_BF16 && linear_chain_supported(d->in, d->out, d->r);
-    p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in + d->out, d->r);
-    p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->r);
+    p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in, d->out, d->r);
+    p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->in, d->out, d->r);
     p.skinny = d->dtype == PF_F32 && d->M > 0 && d->M <= 4 * SK_MAX_ROWS && d->in >= 4 && d->out >= 4 &&
                d->r >= 4;
     p.n_part_sk = 0;
@@ -765,9 +784,9 @@ static int launch_add_into(hipStream_t s, T *dst, const T *src, i64 count)
 struct SharedPlan {
     pf_linear_desc one; // one of the G layers
     LinearPlan p;
-    bool fused_fwd, fused_bwd; // the groups run inside one launch of the chain kernel
-    LinearTiles t;             // otherwise side by side on the tiled products
-    size_t n_colsum, fwd_bytes, bwd_bytes;
+    bool fused_fwd; // the groups run inside one launch of the chain kernel
+    LinearTiles t;  // otherwise, and backward, side by side on the tiled products
+    size_t fwd_bytes, bwd_bytes;
 };
 
 static int check_shared_desc(const pf_linear_shared_desc *d, pf_linear_desc *one)
@@ -788,15 +807,11 @@ static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_line
     sp.one = one;
     sp.p = plan_linear(&one);
     const int G = d->groups;
-    const bool bf = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1;
-    sp.fused_fwd = bf && sp.p.chain_fwd && linear_chain2_multi_supported(d->n_in, d->n_out, d->r, G, false);
-    sp.fused_bwd = bf && sp.p.chain_bwd && linear_chain2_multi_supported(d->n_out, d->n_in, d->r, G, true);
-    sp.n_colsum = (size_t)(2 * ((d->M + LC_ROWS - 1) / LC_ROWS)) * d->n_out;
+    sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS && chain_shared_fwd_pays(d->M, d->n_in);
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
-    // one layer's workspace, then: dT and (recomputed) T of all groups, their column sums, one more dX
-    sp.bwd_bytes = sp.p.bwd_bytes + 2 * align_up((size_t)G * sp.p.n_T * 2) + align_up((size_t)G * sp.n_colsum * 4) +
-                   align_up((size_t)(d->M * d->n_in) * el);
+    // one layer's workspace, then one more dX (layer by layer)
+    sp.bwd_bytes = sp.p.bwd_bytes + align_up((size_t)(d->M * d->n_in) * el);
     sp.t = make_linear_tiles(&one, G);
     if (sp.t.fwd_bytes > sp.fwd_bytes) sp.fwd_bytes = sp.t.fwd_bytes;
     if (sp.t.bwd_bytes > sp.bwd_bytes) sp.bwd_bytes = sp.t.bwd_bytes;
@@ -1118,63 +1133,24 @@ int pf_lowrank_linear_shared_bwd(const pf_linear_shared_desc *d, const void *X, 
     if (!workspace || workspace_bytes < sp.bwd_bytes) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     hipStream_t s = (hipStream_t)stream;
-    const i64 M = d->M, in = d->n_in, out = d->n_out, r = d->r;
     const int G = d->groups;
-    if (!(sp.fused_bwd && dX)) {
-        if (sp.t.ok) {
-            Workspace ws(workspace, workspace_bytes);
-            if (d->dtype == PF_F32)
-                return linear_bwd_tiles<float>(&one, sp.t, G, (const float *)X, (const float *)V, (const float *)U,
-                                               (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU,
-                                               (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
-            return linear_bwd_tiles<bf16_t>(&one, sp.t, G, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
-                                            (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
-                                            (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
-        }
+    if (sp.t.ok) {
+        Workspace ws(workspace, workspace_bytes);
         if (d->dtype == PF_F32)
-            return shared_bwd_loop<float>(d, sp, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
-                                          (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
-                                          (float *)dbias, accumulate, workspace, workspace_bytes, s);
-        return shared_bwd_loop<bf16_t>(d, sp, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
-                                       (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
-                                       (float *)dV, (float *)dbias, accumulate, workspace, workspace_bytes, s);
+            return linear_bwd_tiles<float>(&one, sp.t, G, (const float *)X, (const float *)V, (const float *)U,
+                                           (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU,
+                                           (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
+        return linear_bwd_tiles<bf16_t>(&one, sp.t, G, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+                                        (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
+                                        (float *)dV, (float *)dbias, accumulate, ws, s, LinEpilogue{});
     }
-    // fused: every group's dT = dY_g U_g and the sum dX = sum_g dT_g V_g^T in one launch, then the factor
-    // gradients layer by layer
-    Workspace ws(workspace, workspace_bytes);
-    const size_t grads = (size_t)sp.p.wg_groups * r * (in + out);
-    float *part = ws.take<float>(grads > sp.p.n_part ? grads : sp.p.n_part);
-    bf16_t *dT16 = ws.take<bf16_t>((size_t)G * sp.p.n_T);
-    bf16_t *T16 = ws.take<bf16_t>((size_t)G * sp.p.n_T);
-    float *colsum = ws.take<float>((size_t)G * sp.n_colsum);
-    const bool want_db = d->has_bias && dbias;
-    const bf16_t *Xb = (const bf16_t *)X, *Vb = (const bf16_t *)V, *Ub = (const bf16_t *)U, *dYb = (const bf16_t *)dY;
-    const bf16_t *Tb = (const bf16_t *)T_saved;
-    if (dU && !Tb) { // T was not saved: recompute it
-        for (int g = 0; g < G && st == PF_OK; ++g)
-            st = launch_gemm_generic<bf16_t, true, false>(
-                "linear_T=X*V", s, GemmShape{(int)M, (int)r, (int)in, 1, 1}, OpA_RowMajor<bf16_t>{Xb, (int)in, 0},
-                OpB_KN<bf16_t>{Vb + g * in * r, (int)r, 0, 0},
-                EpiRowMajor<bf16_t, bf16_t>{T16 + g * M * r, nullptr, (int)r, nullptr, 0});
-        if (st != PF_OK) return st;
-        Tb = T16;
-    }
-    LinChainArgs c{(const uint16_t *)dYb, (const uint16_t *)Ub, (const uint16_t *)Vb, nullptr, (uint16_t *)dX,
-                   (uint16_t *)dT16, want_db ? colsum : nullptr, M, (int)out, (int)in};
-    c.groups = G;
-    c.sum_out = 1;
-    c.gs_in = M * out;
-    c.gs_W1 = out * r;
-    c.gs_W2 = in * r;
-    c.gs_mid = M * r;
-    c.gs_colsum = (i64)sp.n_colsum;
-    st = launch_linear_chain2(s, "linear_shared_bwd_data_fused", c);
-    for (int g = 0; g < G && st == PF_OK; ++g)
-        st = linear_wgrads_fused(&one, sp.p, Xb, dYb + g * M * out, Tb ? Tb + g * M * r : nullptr, dT16 + g * M * r,
-                                 dU ? (float *)dU + g * out * r : nullptr, dV ? (float *)dV + g * in * r : nullptr,
-                                 dbias ? (float *)dbias + g * out : nullptr, want_db ? colsum + g * sp.n_colsum : nullptr,
-                                 accumulate, part, s);
-    return st;
+    if (d->dtype == PF_F32)
+        return shared_bwd_loop<float>(d, sp, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
+                                      (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
+                                      (float *)dbias, accumulate, workspace, workspace_bytes, s);
+    return shared_bwd_loop<bf16_t>(d, sp, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U,
+                                   (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU,
+                                   (float *)dV, (float *)dbias, accumulate, workspace, workspace_bytes, s);
 }
 
 } // extern "C"

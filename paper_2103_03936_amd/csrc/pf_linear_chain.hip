@@ -33,11 +33,9 @@ __device__ __forceinline__ bf16x8_t lc_as_bf16x8(u32x4_t v) { return __builtin_b
 
 // NP: pairs of output blocks per wavefront (C2 / 256) when it is one of 1, 2, 4, 8 -- then stage 2 is fully
 // unrolled and its W2 fragments are fetched two pairs ahead, the first two during stage 1; NP == 0: any C2.
-// MODE 0: one layer.  MODE 1: the groups of LinChainArgs run one after the other in the same workgroup (same
-// rows), each with its own output.  MODE 2: the same, but the groups' stage-2 products are summed into one output.
-// EP: the epilogue members of the arguments are honoured (MODE 0 only; a separate instantiation, so that the plain
-// layer does not carry their registers).
-template <int NP, int MODE = 0, bool EP = false>
+// EP: the epilogue members of the arguments are honoured (a separate instantiation, so that the plain layer does not
+// carry their registers).  blockIdx.y: the group.
+template <int NP, bool EP = false>
 __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args)
 {
     __shared__ __attribute__((aligned(16))) uint16_t Xs[2][LC_ROWS * LC_XP];
@@ -64,22 +62,9 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
     // ---- copy roles: thread -> (row or k, 16-byte column) of a chunk
     const int cr = tid >> 4, co = tid & 15; // 16 threads per 128-element row; 16 rows per pass
 
-    constexpr bool MULTI = MODE != 0, summing = MODE == 2;
-    const int G = MULTI ? args.groups : 1;
-    constexpr int NSUM = summing ? NP : 1;
-    static_assert(!summing || NP == 1 || NP == 2, "the sums of all output blocks stay in registers");
-    f32x16_t ysum[NSUM][2]; // stage-2 sums over the groups (summing only)
-#pragma unroll
-    for (int i = 0; i < NSUM; ++i)
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) ysum[i][bi][v] = 0.f;
-
-    for (int gi = 0; gi < G; ++gi) {
     LinChainArgs a = args;
-    const int group = MULTI ? gi : (int)blockIdx.y; // (MODE 0: groups of few rows run side by side)
-    if (MULTI || group > 0) {
+    const int group = blockIdx.y;
+    if (group > 0) {
         a.in += group * args.gs_in;
         a.W1 += group * args.gs_W1;
         a.W2 += group * args.gs_W2;
@@ -87,7 +72,6 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
         a.out += group * args.gs_out;
         if (a.mid_save) a.mid_save += group * args.gs_mid;
         if (a.colsum) a.colsum += group * args.gs_colsum;
-        if (MULTI && gi > 0) __syncthreads(); // the LDS tiles of the previous group are free
     }
     const uint16_t *xsrc[2];
 #pragma unroll
@@ -249,7 +233,7 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
     write_x(x0, 0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) write_v(v0, 0, i);
-    if (!MULTI && nch == 4) {
+    if (nch == 4) {
         // The common short contraction (512), spelled out: every chunk is requested exactly once, and the stage-2
         // operands follow in the last two chunks, when nothing else is left to ask for.
         load_x(x2, 2);
@@ -397,7 +381,7 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) y[bi][v] = summing ? ysum[g < NSUM ? g : 0][bi][v] : 0.f;
+            for (int v = 0; v < 16; ++v) y[bi][v] = 0.f;
         if (held) epi_operands();
         mma_block(u, 0, y[0], [&](int ks) __attribute__((always_inline)) {
             write_u(u, 1, ks);
@@ -412,23 +396,16 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
             if (gf >= 0) load_u1(uf, gf, 1, ks);
             if (held) epi_slot(8 + ks);
         });
-        if (summing && gi + 1 < G) { // (uniform) not the last group: keep the sums, nothing leaves yet
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi) ysum[g < NSUM ? g : 0][bi] = y[bi];
-            return;
-        }
 #pragma unroll
         for (int bi = 0; bi < 2; ++bi) yp[bi] = y[bi];
         obp = ob0;
-        if (summing) flush(); // (the sums over the groups take the registers a held pair would need)
     };
 #pragma unroll
     for (int j = 0; j < 8; ++j) write_u(ur[0], 0, j);
     if (NP > 0) {
 #pragma unroll
         for (int g = 0; g < NP; ++g)
-            pair(ur[g % 3], ur[(g + 1 < NP ? g + 1 : g) % 3], ur[(g + 2) % 3], g + 2 < NP ? g + 2 : -1, g,
-                 g > 0 && !summing);
+            pair(ur[g % 3], ur[(g + 1 < NP ? g + 1 : g) % 3], ur[(g + 2) % 3], g + 2 < NP ? g + 2 : -1, g, g > 0);
     } else { // any number of pairs: one pair ahead, requests past the end repeat the last pair
         for (int g = 0; 2 * g < obw; g += 2) {
             pair(ur[0], ur[1], ur[2], -1, g, g > 0);
@@ -437,14 +414,7 @@ __global__ __launch_bounds__(256, 1) void linear_chain2_kernel(LinChainArgs args
             load_u(ur[1], g + 3);
         }
     }
-    if (!summing) flush();
-    } // groups
-}
-
-bool linear_chain2_multi_supported(i64 n_in, i64 n_out, i64 r, int groups, bool sum_out)
-{
-    if (!linear_chain2_supported(n_in, n_out, r) || groups < 1 || groups > LC_MAX_GROUPS) return false;
-    return !sum_out || n_out == 256 || n_out == 512;
+    flush();
 }
 
 bool linear_chain2_supported(i64 n_in, i64 n_out, i64 r)
@@ -460,36 +430,16 @@ int launch_linear_chain2(hipStream_t s, const char *name, const LinChainArgs &a)
     if (!linear_chain2_supported(a.C1, a.C2, LC_R)) return PF_ERR_UNSUPPORTED;
     const i64 tiles = (a.rows + LC_ROWS - 1) / LC_ROWS;
     if (tiles > 0x7fffffffLL) return PF_ERR_SHAPE;
-    // Groups with outputs of their own: one after the other in a workgroup, which then reads the rows once, where the rows
-    // alone fill the chip; side by side where they do not (three 512 -> 512 projections of 64 rows: 8 us instead of 37).
-    const bool side_by_side = a.groups > 1 && !a.sum_out && tiles < 256;
-    const dim3 grid((unsigned)tiles, side_by_side ? a.groups : 1), block(256);
-    if (a.groups > 1 && !linear_chain2_multi_supported(a.C1, a.C2, LC_R, a.groups, a.sum_out != 0)) return PF_ERR_UNSUPPORTED;
-    if (a.groups > 1 && !side_by_side) {
-        if (a.sum_out) {
-            if (a.C2 == 256) {
-                PF_LAUNCH(st, name, (linear_chain2_kernel<1, 2>), grid, block, s, a);
-            } else {
-                PF_LAUNCH(st, name, (linear_chain2_kernel<2, 2>), grid, block, s, a);
-            }
-            return st;
-        }
-        switch (a.C2 / 256) {
-        case 1: PF_LAUNCH(st, name, (linear_chain2_kernel<1, 1>), grid, block, s, a); break;
-        case 2: PF_LAUNCH(st, name, (linear_chain2_kernel<2, 1>), grid, block, s, a); break;
-        case 4: PF_LAUNCH(st, name, (linear_chain2_kernel<4, 1>), grid, block, s, a); break;
-        case 8: PF_LAUNCH(st, name, (linear_chain2_kernel<8, 1>), grid, block, s, a); break;
-        default: PF_LAUNCH(st, name, (linear_chain2_kernel<0, 1>), grid, block, s, a); break;
-        }
-        return st;
-    }
+    const int groups = a.groups > 1 ? a.groups : 1;
+    if (groups > LC_MAX_GROUPS) return PF_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)tiles, groups), block(256);
     if (a.ep_add || a.ep_mask || a.ep_relu) {
         switch (a.C2 / 256) {
-        case 1: PF_LAUNCH(st, name, (linear_chain2_kernel<1, 0, true>), grid, block, s, a); break;
-        case 2: PF_LAUNCH(st, name, (linear_chain2_kernel<2, 0, true>), grid, block, s, a); break;
-        case 4: PF_LAUNCH(st, name, (linear_chain2_kernel<4, 0, true>), grid, block, s, a); break;
-        case 8: PF_LAUNCH(st, name, (linear_chain2_kernel<8, 0, true>), grid, block, s, a); break;
-        default: PF_LAUNCH(st, name, (linear_chain2_kernel<0, 0, true>), grid, block, s, a); break;
+        case 1: PF_LAUNCH(st, name, (linear_chain2_kernel<1, true>), grid, block, s, a); break;
+        case 2: PF_LAUNCH(st, name, (linear_chain2_kernel<2, true>), grid, block, s, a); break;
+        case 4: PF_LAUNCH(st, name, (linear_chain2_kernel<4, true>), grid, block, s, a); break;
+        case 8: PF_LAUNCH(st, name, (linear_chain2_kernel<8, true>), grid, block, s, a); break;
+        default: PF_LAUNCH(st, name, (linear_chain2_kernel<0, true>), grid, block, s, a); break;
         }
         return st;
     }

@@ -68,3 +68,52 @@ def test_bias_gradient_of_many_rows():
     db = pf.pf_lowrank_linear_bwd(X, V, U, dY, has_bias=True)[3].double()
     want = dY.double().sum(0)
     assert float((db - want).norm() / want.norm()) <= 2.0 ** -22
+
+
+def _rel(got, want):
+    return float((got.double() - want).norm() / want.norm())
+
+
+# Where one layer or several go from the chain kernel to the tiled products or back.  bf16: the rank-r intermediate and the
+# output are rounded (2^-9 / sqrt(3) rms each, and what the first carries into the second): 2^-9 sqrt(3) bounds them together.
+ROUNDED = 2.0 ** -9 * 3 ** 0.5
+
+
+@pytest.mark.parametrize("M,n_in,n_out,r", [
+    (4095, 512, 2048, 128), (4096, 512, 2048, 128), (8192, 512, 256, 128), (8193, 512, 256, 128), (8193, 768, 256, 128),
+    (4096, 1024, 512, 128), (4999, 256, 256, 128), (5000, 256, 256, 128), (10001, 256, 256, 128), (10000, 256, 256, 64),
+    (16385, 256, 256, 64), (24000, 512, 256, 64)])
+def test_linear_routes(M, n_in, n_out, r):
+    import torch
+    import paper_2103_03936_amd as pf
+    g = torch.Generator(device="cuda").manual_seed(M)
+    n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    X, V, U, dY, b = n(M, n_in), n(n_in, r, std=n_in ** -0.5), n(n_out, r, std=r ** -0.5), n(M, n_out), n(n_out)
+    Y, T = pf.pf_lowrank_linear_fwd(X, V, U, b)
+    dX, dU, dV, db = pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T, has_bias=True)
+    x, v, u, dy = (t.double() for t in (X, V, U, dY))
+    t, dt = x @ v, dy @ u
+    for name, got, want in (("Y", Y, t @ u.t() + b.double()), ("T", T, t), ("dX", dX, dt @ v.t()), ("dU", dU, dy.t() @ t),
+                            ("dV", dV, x.t() @ dt), ("db", db, dy.sum(0))):
+        assert _rel(got, want) <= ROUNDED, name
+
+
+@pytest.mark.parametrize("G,M,n_in,n_out", [(3, 8192, 256, 512), (3, 8193, 256, 512), (2, 4096, 1024, 256), (2, 4097, 1024, 256),
+                                            (8, 33, 512, 256), (9, 33, 512, 256)])
+def test_linear_shared_routes(G, M, n_in, n_out):
+    import torch
+    import paper_2103_03936_amd as pf
+    r, g = 128, torch.Generator(device="cuda").manual_seed(M + G)
+    n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    X, V, U, dY, b = n(M, n_in), n(G, n_in, r, std=n_in ** -0.5), n(G, n_out, r, std=r ** -0.5), n(G, M, n_out), n(G, n_out)
+    Y, T = pf.pf_lowrank_linear_shared_fwd(X, V, U, b)
+    dX, dU, dV, db = pf.pf_lowrank_linear_shared_bwd(X, V, U, dY, T_saved=T, has_bias=True)
+    x, total = X.double(), 0
+    for k in range(G):
+        v, u, dy = (t[k].double() for t in (V, U, dY))
+        t, dt = x @ v, dy @ u
+        total = total + dt @ v.t()
+        for name, got, want in (("Y", Y, t @ u.t() + b[k].double()), ("T", T, t), ("dU", dU, dy.t() @ t), ("dV", dV, x.t() @ dt),
+                                ("db", db, dy.sum(0))):
+            assert _rel(got[k], want) <= ROUNDED, name
+    assert _rel(dX, total) <= ROUNDED
