@@ -246,6 +246,7 @@ class LinearWorkload:
             add("linear_dX=dT*Vt", 2.0 * M * r * i, s * (i * r + M * i) + 4 * M * r)
             add("linear_dU=dYt*T", 2.0 * M * r * o, s * (M * o + M * r) + 4 * o * r)
             add("linear_dV=Xt*dT", 2.0 * M * r * i, s * M * i + 4 * (M * r + i * r))
+            add("linear_dX,dU,dV", 2.0 * M * r * (2 * i + o), s * (2 * M * r + i * r + M * i + M * o + M * i) + 4 * r * (i + o))
             # fp32 with few rows: slices of the rank-r intermediate, then every product that reads their sum
             add("linear_T_slices", 2.0 * M * r * i, s * (M * i + i * r + M * r))
             add("linear_Y=T*Ut+b", 2.0 * M * r * o, s * (M * r + o * r + M * o + M * r))
@@ -255,12 +256,10 @@ class LinearWorkload:
             add("linear_fwd_fused", 2.0 * M * r * (i + o), s * (M * i + M * o + M * r + r * (i + o)))
             add("linear_bwd_data_fused", 2.0 * M * r * (i + o), s * (M * o + M * i + M * r + r * (i + o)))
             add("linear_wgrad_pair", 2.0 * M * r * (i + o), s * (M * i + M * o + 2 * M * r) + 4 * r * (i + o))
-        if self.shared:  # one launch for all the projections of the shared input: X and dX move once
+        if self.shared:  # one launch for all the projections of the shared input: X moves once
             i, o, r = self.layers[self.shared[0]]
             G = len(self.shared)
             add("linear_shared_fwd_fused", 2.0 * G * M * r * (i + o), s * (M * i + G * (M * o + M * r + r * (i + o))))
-            add("linear_shared_bwd_data_fused", 2.0 * G * M * r * (i + o),
-                s * (M * i + G * (M * o + M * r + r * (i + o))))
         return out
 
     def algorithmic_bytes(self):
@@ -405,25 +404,19 @@ class LstmWorkload:
         B, d, h, r, g = c["B"], c["d"], c["h"], c["r"], self.groups
         gr, cells = g * r, c["T"] * c["layers"]
         if self.stack or self.seq:
-            # one call per direction for the whole stack, or (sequence entry points) per layer: a slot holds every
-            # layer of the call that has a step on its diagonal
+            # one call per direction for the whole stack, or (sequence entry points) per layer
             Mt, L = c["T"] * B, c["layers"]
             calls, lay = (1, L) if self.stack else (L, 1)
-            slots = calls * (c["T"] + lay - 1)
-            up = (lay - 1) * c["T"] * calls  # layer-to-layer products that ride in the slots
+            up = (lay - 1) * c["T"] * calls  # layer-to-layer products
             prods = cells + up
+            factors = L * (4 * h * r * 2 + gr * h) + (lay - 1) * calls * gr * h  # of the recurrence: all but the first Vx
             ws = {
-                "lstm_stack_T": (2.0 * B * gr * h * prods, 4 * (gr * h + B * h + B * gr) * prods, slots),
-                "lstm_stack_z": (2.0 * B * 4 * h * r * prods, 4 * (4 * h * r + B * gr + 2 * B * 4 * h) * prods, slots),
-                # pre-activations of both paths and the gates in one launch (one factor pair per path)
-                "lstm_stack_z_gates": (2.0 * B * 4 * h * r * 2 * cells,
-                                       4 * ((4 * h * r + B * gr) * 2 * cells + (B * 4 * h + 3 * B * h) * cells), slots),
-                "lstm_stack_dT": (2.0 * B * 4 * h * r * prods, 4 * (4 * h * r + B * 4 * h + B * gr) * prods, slots),
-                "lstm_stack_dh": (2.0 * B * gr * h * prods, 4 * (gr * h + B * gr + B * h) * prods, slots),
-                # dh from both products and the gate derivatives in one launch (one factor pair per path)
-                "lstm_stack_dh_gates": (2.0 * B * gr * h * prods,
-                                        4 * ((gr * h + B * gr) * prods + (B * 4 * h * 2 + 5 * B * h) * cells),
-                                        slots + calls),
+                # the recurrence of every call in one launch per direction: factors once, what is kept for backward, the
+                # exchanged activations not counted
+                "lstm_run_fwd": (2.0 * B * gr * h * prods + 2.0 * B * 4 * h * r * 2 * cells,
+                                 4 * (factors + Mt * L * (6 * h + 2 * gr)), calls),
+                "lstm_run_bwd": (2.0 * B * (gr * h + 4 * h * r) * prods,
+                                 4 * (factors + Mt * (L * (4 * h + h + 4 * h + 2 * gr) + h)), calls),
                 "lstm_stack_grads": (2.0 * Mt * (8 * h * r + gr * (d + h)) * L,
                                      4 * ((8 * h * r + gr * (d + h) + 4 * h) + Mt * (4 * h + 2 * gr + d + h)) * L,
                                      L if Mt >= 128 else 2 * L),  # one launch per layer from 128 rows on
@@ -442,9 +435,7 @@ class LstmWorkload:
     def algorithmic_bytes(self):
         w = self.kernel_work()
         if self.stack or self.seq:
-            names = (("lstm_stack_T", "lstm_stack_z_gates", "lstm_stack_dT", "lstm_stack_dh_gates", "lstm_stack_grads")
-                     if self.groups == 1 else ("lstm_stack_T", "lstm_stack_z", "lstm_stack_dT", "lstm_stack_dh", "lstm_stack_grads"))
-            return sum(w[k][1] for k in names)
+            return sum(w[k][1] for k in ("lstm_run_fwd", "lstm_run_bwd", "lstm_stack_grads"))
         return sum(v[1] for v in w.values())
 
     def cpu_baseline(self, oracle, workloads, cells=8):
@@ -790,7 +781,8 @@ def run_workload(args, torch, pf, workloads, name, lstm_groups=1):
     # per-kernel durations, HIP events around every launch on the launch stream
     pf.timing_reset()
     pf.timing_enable(True)
-    for i in range(max(args.steps, 20)):
+    timed_steps = max(args.steps, 20)
+    for i in range(timed_steps):
         wl.step(pf, sets[i % len(sets)])
     torch.cuda.synchronize()
     pf.timing_enable(False)
@@ -799,10 +791,11 @@ def run_workload(args, torch, pf, workloads, name, lstm_groups=1):
     work = wl.kernel_work()
     roofline = None
     if kernels:
-        dom = next((k for k in kernels if k in work), next(iter(kernels)))  # the costliest kernel that has a work model
+        # the costliest kernel whose work is known: that of every layer, so all of them must have launched it
+        dom = next((k for k in kernels if k in work and kernels[k]["launches"] == work[k][2] * timed_steps), next(iter(kernels)))
         roofline = {"kernel": dom, "bound": "mfma", "achieved": None, "peak": peak, "unit": "TFLOP/s", "frac": None,
                     "traffic": None, "avg_us": kernels[dom]["avg_us"]}
-        if dom in work:
+        if dom in work and kernels[dom]["launches"] == work[dom][2] * timed_steps:
             kflops, kbytes, per_step = work[dom]
             step_s = kernels[dom]["avg_us"] * 1e-6 * per_step  # time this kernel takes per step, all layers
             bound = "mfma" if kflops / kbytes >= peak * 1e12 / (HBM_GBS * 1e9) else "hbm"
@@ -936,12 +929,26 @@ def main():
         "warmup": args.warmup, "ms_per_step": head["ms_per_step"], "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": head["dtype"], "data": "synthetic",
     }
-    out.update({k: v for k, v in head.items() if k not in out})
-    brief = lambda r: {k: r[k] for k in ("config", "dtype", "ms_per_step", "value", "unit", "timing", "frac_of_mfma_peak",
-                                         "arithmetic_intensity", "attainable_TFLOPs", "frac_of_min_peak_ai_bw",
-                                         "eager_ms_per_step", "roofline", "cpu_baseline", "dense_layer_vendor_library",
-                                         "unfused_vendor_library", "separate_epilogues", "kernels")}
-    out["workloads"] = [brief(head)] + [brief(r) for r in others]
+    # One short line on stdout (a reader may keep only the last few kilobytes); everything measured goes to stderr.
+    def brief(r):
+        roof = r["roofline"] or {}
+        legs = (("vs_dense_vendor_library", "dense_layer_vendor_library", "speedup_of_factorized"),
+                ("vs_unfused_vendor_library", "unfused_vendor_library", "speedup_of_fused"),
+                ("vs_separate_epilogues", "separate_epilogues", "speedup_of_fused_epilogues"))
+        b = {"workload": r["config"].get("workload"), "dtype": r["dtype"], "ms_per_step": r["ms_per_step"], "value": r["value"],
+             "frac_of_mfma_peak": r["frac_of_mfma_peak"], "eager_ms_per_step": r["eager_ms_per_step"],
+             "roofline": {k: roof.get(k) for k in ("kernel", "bound", "achieved", "unit", "frac", "traffic")}}
+        if "groups" in r["config"]:
+            b["groups"] = r["config"]["groups"]
+        b.update({name: (r.get(leg) or {}).get(key) for name, leg, key in legs if (r.get(leg) or {}).get(key)})
+        return {k: float(f"{v:.5g}") if isinstance(v, float) else v for k, v in b.items()}
+
+    full = dict(out, **{k: v for k, v in head.items() if k not in out}, workloads=[head] + others)
+    print(json.dumps(full), file=sys.stderr, flush=True)
+    out.update({k: head[k] for k in ("config", "frac_of_mfma_peak", "frac_of_min_peak_ai_bw", "launch", "roofline")})
+    cpu = head["cpu_baseline"]
+    out["cpu_baseline"] = {k: v for k, v in cpu.items() if not isinstance(v, (dict, list))} if cpu else None
+    out["workloads"] = [brief(r) for r in [head] + others]
     print(json.dumps(out))
 
 
