@@ -63,7 +63,8 @@ def test_parity_with_weights_saved_by_forward(shape, dtype):
 
 
 # shapes the fused small-image kernels take in bfloat16 (channels a multiple of 256, rank 64 or 128, images of at
-# most 8 x 8): 8 x 8 and 7 x 7 have their own instantiations, every other height and width shares one
+# most 8 x 8): 8 x 8 and 7 x 7 have their own instantiations, every other height and width shares one.  (3x3 layers of fewer
+# than 32 pixels, and of rank 128 at batches below 32, run on the tiled products.)
 FUSED_SHAPES = [
     (9, 256, 8, 8, 256, 64, 3, 1, 1),
     (5, 512, 7, 7, 256, 128, 3, 1, 1),
@@ -78,6 +79,10 @@ FUSED_SHAPES = [
     (45, 1024, 7, 7, 256, 128, 1, 1, 0),
     (11, 768, 7, 7, 256, 64, 1, 1, 0),   # 7 x 7 planes copied flat, rank 64, three rounds of 256 channels
     (3, 256, 8, 8, 768, 64, 1, 1, 0),
+    (5, 256, 6, 6, 256, 64, 3, 1, 1),
+    (32, 256, 5, 7, 256, 128, 3, 1, 1),
+    (33, 512, 8, 8, 256, 128, 3, 1, 1),
+    (35, 256, 7, 7, 512, 128, 3, 1, 1),
 ]
 
 

@@ -118,7 +118,8 @@ def test_basic_block(shape, dtype):
     _basic_block(*shape, dtype, seed=70)
 
 
-@pytest.mark.parametrize("shape", [(9, 256, 8, 8, 64, 3), (5, 512, 7, 7, 128, 3), (6, 256, 7, 7, 128, 1)])
+@pytest.mark.parametrize("shape", [(9, 256, 8, 8, 64, 3), (5, 512, 7, 7, 128, 3), (6, 256, 7, 7, 128, 1), (33, 256, 7, 7, 128, 3),
+                                   (34, 256, 6, 6, 128, 3), (3, 256, 6, 7, 64, 3)])
 def test_basic_block_fused_shapes(shape):
     _basic_block(*shape, "bf16", seed=80)
 

@@ -19,11 +19,11 @@ SHAPES = [
     (64, 512, 512, 128),   # VGG-19 fc17/fc18
     (70, 33, 31, 33),      # rank above min(in, out)
     (100, 130, 260, 129),  # fp32: four row blocks on the streaming kernels, every extent ragged
-    (150, 256, 512, 64),   # fused-kernel shapes with a ragged last row tile
+    (150, 256, 512, 64),   # shapes of the chain kernel, which takes some of them (test_gpu_tiles.py: where it begins)
     (257, 512, 256, 128),
     (1000, 256, 256, 128),
-    (100, 768, 1024, 128),  # fused kernel: four output-block pairs per wavefront forward, three backward
-    (65, 1280, 1280, 128),  # fused kernel: ten chunks of the contraction, five pairs (the loop for any count), ragged rows
+    (100, 768, 1024, 128),
+    (65, 1280, 1280, 128),
 ]
 
 

@@ -16,9 +16,9 @@ SHAPES = [
     (7, 5, 4, 3, 3),
     (70, 33, 31, 9, 2),
     (100, 130, 260, 129, 3),  # fp32: the streaming kernels, layer by layer
-    (100, 512, 512, 128, 3),  # bf16: all three projections in one launch per direction, ragged last row tile
-    (257, 256, 768, 128, 2),  # output wider than the input: separate outputs forward, one summed output backward
-    (64, 1024, 256, 128, 4),  # input wider than 512: the backward pass sums layer by layer
+    (100, 512, 512, 128, 3),  # bf16: all three projections in one launch forward, ragged last row tile
+    (257, 256, 768, 128, 2),  # output wider than the input
+    (64, 1024, 256, 128, 4),  # more products than most
     (33, 512, 256, 128, 8),
 ]
 

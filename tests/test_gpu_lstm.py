@@ -407,8 +407,8 @@ def test_layer_stack_matches_sequence_layers_full_size():
 @pytest.mark.parametrize("groups", [1, 4])
 def test_layer_stack_full_size_against_oracle(groups):
     """The language model's two layers over all 35 steps at batch 20 (Appendix D), forward and back-propagation
-    through time and depth, directly against the fp64 oracle: with one rank-375 factor pair per path (groups = 1,
-    the fused schedule) and with one pair per gate and path (groups = 4, Appendix D's table, the general schedule)."""
+    through time and depth, directly against the fp64 oracle: with one rank-375 factor pair per path (groups = 1) and
+    with one pair per gate and path (groups = 4, Appendix D's table)."""
     import paper_2103_03936_amd as pf
     T, B, d, h, r, L = 35, 20, 1500, 1500, 375, 2
     a = _stack_inputs(T, B, d, h, r, groups, L, seed=21)

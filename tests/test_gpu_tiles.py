@@ -82,15 +82,18 @@ ROUNDED = 2.0 ** -9 * 3 ** 0.5
 @pytest.mark.parametrize("M,n_in,n_out,r", [
     (4095, 512, 2048, 128), (4096, 512, 2048, 128), (8192, 512, 256, 128), (8193, 512, 256, 128), (8193, 768, 256, 128),
     (4096, 1024, 512, 128), (4999, 256, 256, 128), (5000, 256, 256, 128), (10001, 256, 256, 128), (10000, 256, 256, 64),
-    (16385, 256, 256, 64), (24000, 512, 256, 64)])
-def test_linear_routes(M, n_in, n_out, r):
+    (16385, 256, 256, 64), (24001, 512, 256, 64),
+    # the chain kernel's loops: a ragged last row tile, one to eight pairs of output blocks, any number of them, ten chunks
+    (33, 256, 256, 128), (4129, 768, 1024, 128), (4129, 1024, 768, 128), (5003, 1280, 1280, 128), (4129, 2048, 512, 128)])
+@pytest.mark.parametrize("saved_T", [True, False])
+def test_linear_routes(M, n_in, n_out, r, saved_T):
     import torch
     import paper_2103_03936_amd as pf
     g = torch.Generator(device="cuda").manual_seed(M)
     n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
     X, V, U, dY, b = n(M, n_in), n(n_in, r, std=n_in ** -0.5), n(n_out, r, std=r ** -0.5), n(M, n_out), n(n_out)
     Y, T = pf.pf_lowrank_linear_fwd(X, V, U, b)
-    dX, dU, dV, db = pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T, has_bias=True)
+    dX, dU, dV, db = pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T if saved_T else None, has_bias=True)
     x, v, u, dy = (t.double() for t in (X, V, U, dY))
     t, dt = x @ v, dy @ u
     for name, got, want in (("Y", Y, t @ u.t() + b.double()), ("T", T, t), ("dX", dX, dt @ v.t()), ("dU", dU, dy.t() @ t),
@@ -117,3 +120,20 @@ def test_linear_shared_routes(G, M, n_in, n_out):
                                 ("db", db, dy.sum(0))):
             assert _rel(got[k], want) <= ROUNDED, name
     assert _rel(dX, total) <= ROUNDED
+
+
+@pytest.mark.parametrize("M,n_in,n_out", [(33, 256, 512), (4129, 1024, 512), (4129, 1024, 768), (5003, 1280, 1280), (4129, 512, 2048)])
+def test_linear_routes_epilogue(M, n_in, n_out):
+    """Residual and ReLU forward, skip gradient and mask backward, where the chain kernel applies them and where tiles do; an
+    output that the chain kernel adds to is rounded twice."""
+    import torch
+    import paper_2103_03936_amd as pf
+    r, g = 128, torch.Generator(device="cuda").manual_seed(M)
+    n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(torch.bfloat16)
+    X, V, U, dZ, b = n(M, n_in).clamp_(min=0), n(n_in, r, std=n_in ** -0.5), n(n_out, r, std=r ** -0.5), n(M, n_out), n(n_out)
+    R, skip = n(M, n_out), n(M, n_in)
+    Y, T = pf.pf_lowrank_linear_fwd_ep(X, V, U, b, residual=R, act="relu")
+    dX = pf.pf_lowrank_linear_bwd_ep(X, V, U, dZ, T_saved=T, dX_add=skip, x_is_relu=True, has_bias=True)[0]
+    x, v, u, dz = (t.double() for t in (X, V, U, dZ))
+    assert _rel(Y, (x @ v @ u.t() + b.double() + R.double()).clamp(min=0)) <= ROUNDED
+    assert _rel(dX, (dz @ u @ v.t() + skip.double()) * (x > 0)) <= ROUNDED
