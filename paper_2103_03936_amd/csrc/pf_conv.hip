@@ -1,7 +1,8 @@
 // Factorized convolution (paper Section 2.2): thin k x k convolution into r channels
 // followed by a 1x1 convolution, forward and backward, plus the dense comparator.
-// Host-side validation, workspace planning and dispatch; the any-shape path runs every
-// stage as an implicit GEMM (operands gathered by functors) on the guarded tile GEMM.
+// Host-side validation, workspace planning and dispatch; most shapes run on the tiled
+// products (pf_tile.h), what those do not take as implicit GEMMs (operands gathered by
+// functors) on the guarded element-wise GEMM.
 #include "pf_conv_chain.h"
 #include "pf_conv_wgrad.h"
 #include "pf_epilogue.h"

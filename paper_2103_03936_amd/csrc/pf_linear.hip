@@ -1,6 +1,7 @@
 // Factorized fully connected layer (paper Section 2.1): Y = (X V) U^T + bias and its
 // gradients, plus the dense comparator.  Host-side validation, workspace planning and
-// dispatch; the any-shape path composes the guarded tile GEMM.
+// dispatch; any shape runs on the tiled products (pf_tile.h), dimensions below one of their
+// pieces on the guarded element-wise GEMM.
 #include "pf_conv_chain.h"
 #include "pf_linear_chain.h"
 #include "pf_skinny.h"
