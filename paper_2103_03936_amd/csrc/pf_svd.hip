@@ -1,17 +1,22 @@
 // Truncated-SVD factor initialisation (Algorithm 1: W ~ U V^T with U = Ut_r S_r^(1/2), V = Vt_r S_r^(1/2)):
-// preconditioned one-sided Jacobi in double precision, eight columns at a time.
+// preconditioned one-sided Jacobi in double precision.
 //
 // The matrix with fewer columns is taken (A = W or W^T, rows >= cols) and stored column-major.  One-sided Jacobi
 // orthogonalises every pair of columns once per sweep; on A itself a sweep moves rows x cols numbers cols times and
-// eight or more sweeps follow.  So it first runs on something smaller that has the same right singular vectors:
-//   G = A^T A + shift I,  G = L L^T,  one-sided Jacobi on the cols x cols matrix L: L W = V S  (columns of V orthonormal,
-//   no rotations accumulated: the normalised columns themselves are the eigenvectors of G),
+// eight or more sweeps follow.  So an orthogonal V comes first that does most of it:
+//   G = A^T A, V = its eigenvectors (pf_svd_eigen.hip), made orthonormal by two Newton steps V (3 I - V^T V) / 2, or, where
+//   clusters of eigenvalues leave vectors that cannot be made so (and for few columns, and very many):
+//   G + shift I = L L^T, one-sided Jacobi on the cols x cols matrix L: L W = V S (no rotations accumulated: the normalised
+//   columns themselves are the eigenvectors of G; the shift, the rounding level of G, keeps L defined for any matrix);
 //   B = A V: columns orthogonal to about eps kappa^2.
-// V is a preconditioner only.  Then the one-sided Jacobi runs on B with V carried along, to the same threshold as it
-// would on A: when a check of all pairs finds them orthogonal (well-conditioned matrices) nothing is left to do, otherwise
-// the pairs that are not are rotated, and, unless a second check is content, sweeps follow until one finds nothing to rotate.
-// So singular values far below the largest come out as exactly as without the preconditioner.  The shift (rounding level of G) keeps L defined for any matrix.
+// V is a preconditioner only.  All pairs of B's columns are checked against the threshold that the iteration on A would use.
+// What is not orthogonal is taken out, V carried along: by B (I + K), K the first-order rotations from the Gram matrix, where
+// they are so small that I + K is orthogonal to rounding, otherwise by rotations of the pairs of blocks that hold some.
+// Unless a second check is content, sweeps of the Jacobi iteration follow until one finds nothing to rotate.
+// So singular values far below the largest come out as exactly as without the preconditioner.
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
+// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.8 with the eigenvectors; a matrix that turns out clustered pays for both (1024 x
+// 512 with orthonormal columns: 15.6 -> 17.3 ms).
 //
 // A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
 // every column of one block against every column of the other (in a sweep's first round also within the blocks) found on
@@ -21,12 +26,11 @@
 // A barrier's wait is bounded: after about a second without the others a workgroup gives up; the call then reports no
 // convergence and its outputs are NaN.
 #include "pf_gemm.h"
-#include "pf_svd_pair.h"
+#include "pf_svd_eigen.h"
 
 namespace pf {
 
-constexpr int SVD_NT = 512;  // threads of the cooperative kernels
-constexpr int SVD_B = 8;     // columns per block
+constexpr int SVD_B = 8; // columns per block
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 
 // A pair counts as orthogonal when |a_p . a_q| <= tol |a_p| |a_q|.  The inner product of two columns of `rows` doubles carries
@@ -63,8 +67,30 @@ __device__ __forceinline__ f64x2_t svd_frag(const double *M, int ld, int col, in
     return v;
 }
 
-// C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows.  unless
-// (nullable): nothing is done when it is 0.
+// Sum over the four wavefronts of a workgroup of a 32 x 32 tile: each has it as 2 x 2 MFMA tiles over its share of the contraction.
+// put(i, j, sum) for the elements of thread tid.
+template <class PUT>
+__device__ __forceinline__ void svd_tile_out(const f64x4_t (&acc)[2][2], double (&part)[4][32][33], PUT put)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[wave][16 * a + g + 4 * v][16 * b + c] = acc[a][b][v];
+    __syncthreads();
+    for (int e = tid; e < 1024; e += 256) {
+        const int i = e >> 5, j = e & 31;
+        put(i, j, (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]));
+    }
+}
+
+constexpr int SVD_U = 4; // pieces of eight contraction indices that a wavefront has in flight
+
+// C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows, and SVD_U pieces are
+// requested together: a piece takes about a microsecond to arrive, its MFMAs 32 clocks each (2048 x 512: 88 us with one at a
+// time).  unless (nullable): nothing is done when it is 0.
 __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *unless)
 {
     if (unless && *unless == 0u) return;
@@ -78,99 +104,173 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
-    for (int r = 8 * wave; r < nr; r += 32) {
-        f64x2_t x[2], y[2];
+    for (int r = 8 * SVD_U * wave; r < nr; r += 32 * SVD_U) {
+        f64x2_t x[SVD_U][2], y[SVD_U][2];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            x[a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 2 * g, nr);
-            y[a] = svd_frag(M, ld, 32 * tj + 16 * a + c, nc, r + 2 * g, nr);
-        }
+        for (int u = 0; u < SVD_U; ++u)
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][0], y[b][0], acc[a][b], 0, 0, 0);
-                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][1], y[b][1], acc[a][b], 0, 0, 0);
+            for (int a = 0; a < 2; ++a) {
+                x[u][a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
+                y[u][a] = svd_frag(M, ld, 32 * tj + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
             }
+#pragma unroll
+        for (int u = 0; u < SVD_U; ++u)
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][a][e], y[u][b][e], acc[a][b], 0, 0, 0);
     }
     __shared__ double part[4][32][33];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) part[wave][16 * a + g + 4 * v][16 * b + c] = acc[a][b][v];
-    __syncthreads();
-    for (int e = tid; e < 1024; e += 256) {
-        const int i = e >> 5, j = e & 31, gi = 32 * ti + i, gj = 32 * tj + j;
-        const double s = (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]);
+    svd_tile_out(acc, part, [&](int i, int j, double s) {
+        const int gi = 32 * ti + i, gj = 32 * tj + j;
         if (gi < nc && gj < nc && (ti != tj || i >= j)) {
             C[(i64)gj * ldc + gi] = s;
             C[(i64)gi * ldc + gj] = s;
         }
-    }
+    });
 }
 
-// counts the pairs of columns whose Gram entry says that they are not orthogonal
-__global__ __launch_bounds__(256) void svd_check_kernel(const double *G, unsigned *violations, int nc, int ld, double tol, const unsigned *unless)
+// The first-order rotation that takes the inner product g_ij of two columns out (0 where they count as orthogonal): with
+// K = (k_ij), k_ij = -k_ji, the columns of B (I + K) are orthogonal to second order.
+__device__ __forceinline__ double svd_small_rotation(double g_ii, double g_jj, double g_ij, double tol2)
+{
+    return svd_orthogonal(g_ii, g_jj, g_ij, tol2) ? 0.0 : g_ij / (g_jj - g_ii);
+}
+// The largest row sum of |K| for which B (I + K) will do: I + K is orthogonal to its square, the rounding level.
+constexpr double SVD_COARSE = 3e-8;
+
+// Counts the pairs of columns whose Gram entry says that they are not orthogonal, and says whether K is too large.  One column
+// per workgroup.
+__global__ __launch_bounds__(256) void svd_check_kernel(const double *G, unsigned *violations, unsigned *coarse, int nc, int ld, double tol,
+                                                         const unsigned *unless)
 {
     if (unless && *unless == 0u) return;
-    const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;
-    bool bad = false;
-    if (idx < (i64)nc * nc) {
-        const int i = (int)(idx % nc), j = (int)(idx / nc);
-        if (i > j) {
-            bad = !svd_orthogonal(G[(i64)j * ld + j], G[(i64)i * ld + i], G[(i64)j * ld + i], tol * tol);
-        }
+    const int j = blockIdx.x;
+    const double gj = G[(i64)j * ld + j];
+    int bad = 0;
+    double sum = 0.0;
+    for (int i = threadIdx.x; i < nc; i += 256) {
+        if (i == j) continue;
+        const double gi = G[(i64)i * ld + i], g = G[(i64)j * ld + i];
+        if (svd_orthogonal(gi, gj, g, tol * tol)) continue;
+        bad += i > j ? 1 : 0;
+        sum += fabs(g / (gj - gi));
     }
-    if (bad) atomicAdd(violations, 1u);
+    __shared__ double red[256];
+    __shared__ unsigned count;
+    if (threadIdx.x == 0) count = 0u;
+    red[threadIdx.x] = sum;
+    __syncthreads();
+    if (bad) atomicAdd(&count, (unsigned)bad);
+    for (int s = 128; s > 0; s >>= 1) {
+        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        if (count) atomicAdd(violations, count);
+        if (!(red[0] <= SVD_COARSE)) *coarse = 1u;
+    }
 }
 
-// B[:, j] = A V[:, j] in rows 0 .. of BV, V itself below: 64 x 64 tiles, a wavefront 32 columns x 32 rows.  V = the
-// normalised columns of L.
-__global__ __launch_bounds__(256) void svd_apply_kernel(const double *At, const double *L, double *BV, int nr, int nc, int ld,
-                                                         int ldl, int ldb)
+// How far the columns behind the Gram matrix S may be from orthonormal for one more Newton step to make them so: the norm of
+// S - I is at most nc times its largest element, a step leaves 3/4 of its square (2e-13 here, at the very most).
+constexpr double SVD_MIXED = 5e-7; // over nc
+__global__ __launch_bounds__(256) void svd_mixed_kernel(const double *S, unsigned *mixed, int nc, int ld)
 {
+    const int j = blockIdx.x;
+    bool bad = false;
+    for (int i = threadIdx.x; i < nc; i += 256) bad |= !(fabs(S[(i64)j * ld + i] - (i == j ? 1.0 : 0.0)) <= SVD_MIXED / nc);
+    if (bad) *mixed = 1u;
+}
+
+// out[:, j] = sum_k left[:, k] right[k, j], all column-major: one tile of 32 columns x 32 rows per workgroup, the wavefronts split k.
+//   SVD_TIMES    right as it is (B = A V)
+//   SVD_NEWTON   right = 3/2 I - S / 2, S the Gram matrix of left's columns: the Newton step towards orthonormal columns
+//   SVD_CORRECT  right = I + K from the Gram matrix of left's columns, when a check found violations[0] pairs and K small; rows
+//                from split on go to out2
+enum { SVD_TIMES, SVD_NEWTON, SVD_CORRECT };
+template <int MODE>
+__global__ __launch_bounds__(256) void svd_product_kernel(const double *left, const double *right, double *out, double *out2, int nr, int nc,
+                                                           int ld, int ldr, int ldo, int ldo2, int split, double tol, const SvdCtrl *ctrl)
+{
+    if (MODE == SVD_CORRECT && (ctrl->violations[0] == 0u || ctrl->coarse[0])) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const int j0 = blockIdx.y * 64 + (wave >> 1) * 32, i0 = blockIdx.x * 64 + (wave & 1) * 32;
+    const int j0 = blockIdx.y * 32, i0 = blockIdx.x * 32;
     f64x4_t acc[2][2];
+    double gj[2] = {1.0, 1.0};
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 2; ++a) {
+        const int j = j0 + 16 * a + c;
+        if (MODE == SVD_CORRECT && j < nc) gj[a] = right[(i64)j * ldr + j];
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
-    for (int k = 0; k < nc; k += 8) {
-        f64x2_t x[2], y[2];
+    }
+    for (int k = 8 * SVD_U * wave; k < nc; k += 32 * SVD_U) {
+        f64x2_t x[SVD_U][2], y[SVD_U][2], gk[SVD_U];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            x[a] = svd_frag(L, ldl, j0 + 16 * a + c, nc, k + 2 * g, nc);
-            const int row = i0 + 16 * a + c, kk = k + 2 * g;
+        for (int u = 0; u < SVD_U; ++u) {
+            const int kk = k + 8 * u + 2 * g;
 #pragma unroll
-            for (int e = 0; e < 2; ++e) y[a][e] = row < nr && kk + e < nc ? At[(i64)(kk + e) * ld + row] : 0.0;
+            for (int a = 0; a < 2; ++a) {
+                const int row = i0 + 16 * a + c;
+                x[u][a] = svd_frag(right, ldr, j0 + 16 * a + c, nc, kk, nc);
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    y[u][a][e] = row < nr && kk + e < nc ? left[(i64)(kk + e) * ld + row] : 0.0;
+                    if (MODE == SVD_CORRECT) gk[u][e] = kk + e < nc ? right[(i64)(kk + e) * (ldr + 1)] : 1.0;
+                }
+            }
         }
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int u = 0; u < SVD_U; ++u)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][0], y[b][0], acc[a][b], 0, 0, 0);
-                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a][1], y[b][1], acc[a][b], 0, 0, 0);
+            for (int e = 0; e < 2; ++e) {
+                const int kk = k + 8 * u + 2 * g + e;
+                double w[2];
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const int j = j0 + 16 * a + c;
+                    w[a] = x[u][a][e];
+                    if (MODE == SVD_NEWTON) w[a] = (j == kk ? 1.5 : 0.0) - 0.5 * w[a];
+                    if (MODE == SVD_CORRECT) w[a] = j == kk ? 0.0 : svd_small_rotation(gk[u][e], gj[a], w[a], tol * tol);
+                }
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[a], y[u][b][e], acc[a][b], 0, 0, 0);
             }
     }
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int j = j0 + 16 * a + g + 4 * v, i = i0 + 16 * b + c;
-                if (j < nc && i < nr) BV[(i64)j * ldb + i] = acc[a][b][v];
-            }
+    __shared__ double part[4][32][33];
+    svd_tile_out(acc, part, [&](int jj, int ii, double s) {
+        const int j = j0 + jj, i = i0 + ii;
+        if (j >= nc || i >= nr) return;
+        if (MODE == SVD_CORRECT) s += left[(i64)j * ld + i];
+        if (MODE == SVD_CORRECT && i >= split)
+            out2[(i64)j * ldo2 + i - split] = s;
+        else
+            out[(i64)j * ldo + i] = s;
+    });
+}
+
+// the corrected columns back into BV
+__global__ __launch_bounds__(256) void svd_corrected_kernel(const double *B, const double *V, double *BV, int ldb, int split, int ldv,
+                                                             const SvdCtrl *ctrl)
+{
+    if (ctrl->violations[0] == 0u || ctrl->coarse[0]) return;
+    const int j = blockIdx.x;
+    for (int i = threadIdx.x; i < ldb; i += 256)
+        BV[(i64)j * ldb + i] = i < split ? B[(i64)j * split + i] : V[(i64)j * ldv + i - split];
 }
 
 // L[:, j] /= |L[:, j]|, also into the V part of BV (rows v0 ..)
-__global__ __launch_bounds__(256) void svd_normalise_kernel(double *L, double *BV, int nc, int ldl, int ldb, int v0)
+__global__ __launch_bounds__(256) void svd_normalise_kernel(double *L, double *BV, int nc, int ldl, int ldb, int v0, const unsigned *unless)
 {
+    if (unless && *unless == 0u) return;
     double *a = L + (i64)blockIdx.x * ldl, *b = BV + (i64)blockIdx.x * ldb;
     double acc = 0.0;
     for (int i = threadIdx.x; i < nc; i += 256) acc += a[i] * a[i];
@@ -402,8 +502,9 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
 
 // G (overwritten) -> L with G + shift I = L L^T, sixteen columns at a time; then one-sided Jacobi on L.
 __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel,
-                                                                   double tol)
+                                                                   double tol, const unsigned *unless)
 {
+    if (unless && *unless == 0u) return;
     __shared__ SvdShared sh;
     __shared__ double d[16][17];
     __shared__ double shift_s;
@@ -507,7 +608,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, const do
     unsigned generation = 0;
     int ran = 0;
     bool ok = ctrl->failed == 0u;
-    const unsigned found = ctrl->violations[first ? 0 : 1];
+    const unsigned found = first ? (ctrl->coarse[0] ? ctrl->violations[0] : 0u) : ctrl->violations[1]; // (else corrected already)
     if (ok && found != 0u)
         ok = svd_sweeps(BV, ld, nc, nr, rows, tol, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
                         ctrl->rot[first ? 1 : 2], false, ctrl, sh, &ran, first ? G : nullptr, ldg);
@@ -539,12 +640,12 @@ __global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double
 // position of column j in descending order of singular value (ties: lower index first; NaN before all others)
 __global__ __launch_bounds__(256) void svd_rank_kernel(const double *sig, int *rank, int nc)
 {
-    const int j = blockIdx.x * 256 + threadIdx.x;
+    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63; // a wavefront per column (a thread: 63 us at 512)
     if (j >= nc) return;
     const double s = sig[j];
     int k = 0;
-    for (int i = 0; i < nc; ++i) k += svd_before(sig[i], i, s, j) ? 1 : 0;
-    rank[j] = k;
+    for (int i = 0; i < nc; i += 64) k += __popcll(__ballot(i + lane < nc && svd_before(sig[min(i + lane, nc - 1)], i + lane, s, j)));
+    if (lane == 0) rank[j] = k;
 }
 
 // column j of B (= sigma_j x left vector) and of V (right vector, from row v0 on) -> column rank[j] of the balanced factors
@@ -593,16 +694,6 @@ static int plan_svd(const pf_svd_desc *d, SvdPlan *p)
     return PF_OK;
 }
 
-// A launch whose workgroups are all resident (they wait for one another)
-template <class... ARGS>
-static int launch_cooperative(hipStream_t s, const char *name, void (*kernel)(ARGS...), int blocks, ARGS... args)
-{
-    TimingScope ts(name, s);
-    void *list[] = {(void *)&args...};
-    const hipError_t e = hipLaunchCooperativeKernel((const void *)kernel, dim3(blocks), dim3(SVD_NT), list, 0, s);
-    return e == hipSuccess ? PF_OK : set_hip_error(e);
-}
-
 } // namespace pf
 
 using namespace pf;
@@ -615,14 +706,14 @@ size_t pf_svd_split_workspace_bytes(const pf_svd_desc *d)
     return plan_svd(d, &p) == PF_OK ? p.bytes : 0;
 }
 
-int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V, void *sigma, void *info, void *workspace,
+int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void *sigma, void *info, void *workspace,
                  size_t workspace_bytes, void *stream)
 {
     SvdPlan p;
     int st = plan_svd(d, &p);
     if (st != PF_OK) return st;
-    if (!W || !U || !V) return PF_ERR_NULL;
-    if (any_misaligned({W, U, V, sigma, info}, 4)) return PF_ERR_UNSUPPORTED;
+    if (!W || !U || !V_out) return PF_ERR_NULL;
+    if (any_misaligned({W, U, V_out, sigma, info}, 4)) return PF_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < p.bytes) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
@@ -641,25 +732,48 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V, void *si
     // one workgroup per pair of blocks (at least eight for the factorization), all of them resident
     const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2;
     const int nwg = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
+    double *V = BV + p.lda; // (leading dimension ldb, as B's)
+    const dim3 square((nc + 31) / 32, (nc + 31) / 32);
+    // V: eigenvectors of G made orthonormal; where they cannot be (ctrl->mixed), and for few or very many columns, by Jacobi
+    const bool eigen = nc >= SVD_EIGEN_MIN && nc <= SVD_EIGEN_MAX;
+    const unsigned *unless = eigen ? &ctrl->mixed : nullptr;
+    if (eigen) {
+        if (st == PF_OK) st = launch_svd_eigenvectors(s, G, L, sig, BV, ctrl, nc, p.ldn);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nc, nc, p.ldn, p.ldn, (const unsigned *)nullptr);
+        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)BV, (const double *)G, L,
+                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldn, 0, 0, 0.0, (const SvdCtrl *)ctrl);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)L, G, nc, nc, p.ldn, p.ldn, (const unsigned *)nullptr);
+        PF_LAUNCH(st, "svd_mixed", svd_mixed_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->mixed, nc, p.ldn);
+        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)L, (const double *)G, V,
+                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, unless);
+    }
     if (st == PF_OK)
-        st = launch_cooperative(s, "svd_precondition", svd_precondition_kernel, nwg, G, L, ctrl, nc, p.ldn,
-                                16.0 * 2.220446049250313e-16 * (nc + 16), svd_tolerance_v(nc));
-    PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda);
-    PF_LAUNCH(st, "svd_apply", svd_apply_kernel, dim3((p.lda + 63) / 64, (nc + 63) / 64), dim3(256), s, (const double *)At,
-              (const double *)L, BV, p.lda, nc, p.lda, p.ldn, p.ldb);
+        st = launch_cooperative(s, "svd_precondition", svd_precondition_kernel, nwg, SVD_NT, G, L, ctrl, nc, p.ldn,
+                                16.0 * 2.220446049250313e-16 * (nc + 16), svd_tolerance_v(nc), unless);
+    PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda, unless);
+    PF_LAUNCH(st, "svd_apply", svd_product_kernel<SVD_TIMES>, dim3((p.lda + 31) / 32, (nc + 31) / 32), dim3(256), s, (const double *)At,
+              (const double *)V, BV, (double *)nullptr, p.lda, nc, p.lda, p.ldb, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl);
     for (int first = 1; first >= 0; --first) {
-        const unsigned *unless = first ? nullptr : &ctrl->violations[0];
+        unless = first ? nullptr : &ctrl->violations[0];
         PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, unless);
-        PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3((unsigned)(((i64)nc * nc + 255) / 256)), dim3(256), s, (const double *)G,
-                  &ctrl->violations[1 - first], nc, p.ldn, svd_tolerance(nr), unless);
+        PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->violations[1 - first],
+                  &ctrl->coarse[1 - first], nc, p.ldn, svd_tolerance(nr), unless);
+        if (first) {
+            PF_LAUNCH(st, "svd_correct", svd_product_kernel<SVD_CORRECT>, dim3((p.ldb + 31) / 32, (nc + 31) / 32), dim3(256), s,
+                      (const double *)BV, (const double *)G, At, L, p.ldb, nc, p.ldb, p.ldn, p.lda, p.ldn, p.lda, svd_tolerance(nr),
+                      (const SvdCtrl *)ctrl);
+            PF_LAUNCH(st, "svd_corrected", svd_corrected_kernel, dim3(nc), dim3(256), s, (const double *)At, (const double *)L, BV, p.ldb,
+                      p.lda, p.ldn, (const SvdCtrl *)ctrl);
+        }
         if (st == PF_OK)
-            st = launch_cooperative(s, "svd_finish", svd_finish_kernel, nwg, BV, (const double *)G, ctrl, nr, nc, p.ldb, p.ldb, p.ldn,
+            st = launch_cooperative(s, "svd_finish", svd_finish_kernel, nwg, SVD_NT, BV, (const double *)G, ctrl, nr, nc, p.ldb, p.ldb, p.ldn,
                                     svd_tolerance(nr), first);
     }
     PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, ctrl, nr, p.ldb);
-    PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 255) / 256), dim3(256), s, (const double *)sig, rank, nc);
+    PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 3) / 4), dim3(256), s, (const double *)sig, rank, nc);
     PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(nc), dim3(256), s, (const double *)BV, (const double *)sig,
-              (const int *)rank, (float *)U, (float *)V, (float *)sigma, nr, nc, p.lda, p.ldb, (int)d->r, p.transposed,
+              (const int *)rank, (float *)U, (float *)V_out, (float *)sigma, nr, nc, p.lda, p.ldb, (int)d->r, p.transposed,
               (const SvdCtrl *)ctrl, (int *)info);
     return st;
 }

@@ -1,0 +1,30 @@
+// Eigenvectors of a symmetric matrix in double precision (pf_svd_eigen.hip): the SVD's fast preconditioner.
+#pragma once
+
+#include "pf_common.h"
+#include "pf_svd_pair.h"
+
+namespace pf {
+
+constexpr int SVD_NT = 512; // threads of the cooperative kernels
+
+// Columns that the tridiagonal route takes.  Up to 16 the two blocks of columns of the Jacobi iteration are one workgroup's and need
+// few barriers (16 columns of 16 rows: 232 us a call on it, 222 on this one; 20 columns: 359 and 243; 64: 748 and 358; 512: 11000
+// and 1800); above 2048 a column of the matrix exceeds what a wavefront keeps of it.
+constexpr int SVD_EIGEN_MIN = 17, SVD_EIGEN_MAX = 2048;
+
+// A launch whose workgroups are all resident (they wait for one another)
+template <class... ARGS>
+static int launch_cooperative(hipStream_t s, const char *name, void (*kernel)(ARGS...), int blocks, int threads, ARGS... args)
+{
+    TimingScope ts(name, s);
+    void *list[] = {(void *)&args...};
+    const hipError_t e = hipLaunchCooperativeKernel((const void *)kernel, dim3(blocks), dim3(threads), list, 0, s);
+    return e == hipSuccess ? PF_OK : set_hip_error(e);
+}
+
+// X (n columns, leading dimension ld) = unit eigenvectors of the symmetric G, as orthogonal as the gaps between the eigenvalues
+// allow.  G (overwritten), L (n columns of ld), tau (n) and X (2 n columns of ld) are scratch.
+int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, SvdCtrl *ctrl, int n, int ld);
+
+} // namespace pf

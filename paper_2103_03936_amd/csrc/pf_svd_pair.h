@@ -15,7 +15,9 @@ struct SvdCtrl {
     unsigned arrived[3];    // grid barriers of the three cooperative launches
     unsigned failed;        // a barrier's wait ran out
     unsigned broken;        // a singular value is not finite: the matrix was not
-    unsigned violations[2]; // pairs of B that are not orthogonal after the preconditioner, and after the first sweep
+    unsigned mixed;         // the eigenvectors of G are not orthogonal enough to be made so: the preconditioner is Jacobi's
+    unsigned coarse[2];     // (per check) some column of B is farther from orthogonal than one correction takes out
+    unsigned violations[2]; // pairs of B that are not orthogonal after the preconditioner, and after the first correction or sweep
     unsigned rot[3][SVD_MAX_SWEEPS + 1]; // pairs rotated per sweep: of L (in pairs of blocks with a large angle), of B first, of B then
     unsigned sweeps;        // sweeps over the pairs of B, a check that found nothing included
     unsigned last;          // pairs rotated in the last of them

@@ -148,3 +148,44 @@ def test_close_singular_values_are_separated(m, n, big):
         got, ref = got.double().cpu().numpy(), ref * np.sqrt(sv)
         err = np.abs(got * np.sign((got * ref).sum(0)) - ref).max(0) / np.abs(ref).max(0)
         assert err.max() <= bound, (err.max(), bound)
+
+
+@pytest.mark.parametrize("n", [16, 17, 63, 64, 65, 128, 129, 255, 257, 511, 513, 1023, 1025, 1537])
+def test_eigenvector_route(n):
+    """Both sides of every size at which the tridiagonal preconditioner changes its split (16 columns: Jacobi's), odd sizes, tall and
+    nearly square: float32 factors, so the oracle's product to a few roundings, and no rotations left."""
+    import paper_2103_03936_amd as pf
+    W, r = _matrix(n + 3 if n % 2 else 2 * n, n, seed=51 + n), max(1, n // 4)
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), r, return_info=True)
+    assert int(info[1]) == 0 and int(info[0]) <= 3
+    u, s, vt = np.linalg.svd(W.astype(np.float64), full_matrices=False)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - s)) <= 2.0 ** -23 * s[0]
+    # U and V round by 2^-24 each, element by element
+    want = (u[:, :r] * s[:r]) @ vt[:r]
+    got = U.double().cpu().numpy() @ V.double().cpu().numpy().T
+    assert np.linalg.norm(got - want) <= 2.0 ** -22 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("kind", ["orthonormal", "zero rows", "repeated", "diagonal", "graded"])
+def test_clustered_matrices(kind):
+    """Eigenvalues that coincide, a matrix that falls apart, and values over seven decades: whichever preconditioner runs, the
+    factors reproduce the matrix (full rank kept) and nothing is left to rotate."""
+    import paper_2103_03936_amd as pf
+    m, n = 200, 96
+    q, _ = np.linalg.qr(_matrix(m, n, 61).astype(np.float64))
+    p, _ = np.linalg.qr(_matrix(n, n, 62).astype(np.float64))
+    s = {"repeated": np.repeat([4.0, 2.0, 1.0], n // 3), "graded": np.logspace(0, -7, n)}.get(kind, np.ones(n))
+    W = (q * s) @ p.T
+    if kind == "zero rows":
+        W = _matrix(m, n, 63).astype(np.float64)
+        W[:, 10:40] = 0.0
+    if kind == "diagonal":
+        W = np.zeros((m, n))
+        W[np.arange(n), np.arange(n)] = np.arange(n) % 7 + 1.0
+    W = W.astype(np.float32)
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+    assert int(info[1]) == 0
+    got = U.double().cpu().numpy() @ V.double().cpu().numpy().T
+    assert np.linalg.norm(got - W) <= 2.0 ** -22 * np.linalg.norm(W.astype(np.float64))
+    ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]
