@@ -35,10 +35,11 @@ struct TileEl<float> {
     static constexpr int V = 4, BK = 32, PAD = 4;
 };
 
-// BM x BN tile, WM x WN wavefronts over it; the 4 / (WM WN) wavefronts that share a block split the contraction
-template <int BM_, int BN_, int WM_, int WN_, int NS_>
+// BM x BN tile, 4 DEEP wavefronts, WM x WN of them over the tile; those that share a block split the contraction, whose chunks are
+// DEEP times as long
+template <int BM_, int BN_, int WM_, int WN_, int NS_, int DEEP_ = 1>
 struct TileCfg {
-    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, WK = 4 / (WM_ * WN_);
+    static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, DEEP = DEEP_, WK = 4 * DEEP / (WM_ * WN_);
     // Wavefronts per SIMD that a kernel of plain products is compiled for: the registers would allow fewer if the compiler
     // had its way (float, 64 x 64: one workgroup per compute unit -> three, 8192 x 1024 x 256 60 -> 49 us, 88 TFLOP/s)
     template <typename CT>
@@ -136,12 +137,12 @@ __device__ __forceinline__ uint4 floats_piece(const float *f)
 
 // Matrix stored [rows][K] with k contiguous, leading dimension ld; SEG: k comes in segments of `seg` (whole pieces), each a
 // matrix of its own that starts `jump` elements after the one before
-template <typename CT, int ROWS, bool SEG = false>
+template <typename CT, int ROWS, bool SEG = false, int DEEP = 1>
 struct LoadKC {
     typedef typename TileEl<CT>::elem elem;
     static constexpr bool KC = true;
-    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V,
-                         CH = ROWS * CPR / TILE_THREADS, LDS = ROWS * PITCH, XF = 1;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK * DEEP, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V, NT = TILE_THREADS * DEEP,
+                         CH = ROWS * CPR / NT, LDS = ROWS * PITCH, XF = 1;
     const elem *rp[CH];
     int K, kc, row, kl, ks;
     int seg = 0;
@@ -154,7 +155,7 @@ struct LoadKC {
         row = tid / CPR;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const int r = min(row0 + row + i * (TILE_THREADS / CPR), rows - 1);
+            const int r = min(row0 + row + i * (NT / CPR), rows - 1);
             rp[i] = (const elem *)p + (i64)r * ld;
         }
         kl = ks = kbeg;
@@ -176,7 +177,7 @@ struct LoadKC {
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
             if (tail) v = piece_shift<sizeof(elem)>(v, s);
-            *(uint4 *)&lds[(row + i * (TILE_THREADS / CPR)) * PITCH + kc] = v;
+            *(uint4 *)&lds[(row + i * (NT / CPR)) * PITCH + kc] = v;
         }
         ks += BK;
     }
@@ -185,12 +186,12 @@ struct LoadKC {
 // Matrix stored [K][cols] with the row / column index contiguous; kscale (nullable): row k is multiplied by kscale[k].
 // SUM of floats: a thread may see a thousand rows of an unsplit gradient, so it adds them in runs of sixteen chunks (16384 rows of
 // zero mean: one chain 4.3e-7 off, relative, runs 1.4e-7).
-template <typename CT, int ROWS, bool SUM = false, bool SCALE = false>
+template <typename CT, int ROWS, bool SUM = false, bool SCALE = false, int DEEP = 1>
 struct LoadMC {
     typedef typename TileEl<CT>::elem elem;
     static constexpr bool KC = false;
-    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V,
-                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = SCALE ? CH : 1;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK * DEEP, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V, NT = TILE_THREADS * DEEP,
+                         CH = BK * CPR / NT, LDS = BK * PITCH, KSTEP = NT / CPR, XF = SCALE ? CH : 1;
     const elem *p;
     const float *kscale;
     i64 ld;
@@ -573,7 +574,7 @@ __device__ __forceinline__ void tile_product(LA &la, LB &lb, int nch, unsigned c
 {
     typedef typename TileEl<CT>::elem elem;
     constexpr int NS = CFG::NS, MI = CFG::BM / 32 / CFG::WM, NI = CFG::BN / 32 / CFG::WN;
-    constexpr int STEPS = 4 / CFG::WK; // a chunk has four steps
+    constexpr int STEPS = 4 * CFG::DEEP / CFG::WK; // a chunk has four steps, or DEEP times that
     static_assert(NS % 2 == 0, "the LDS buffer of a stage is its parity");
     elem *As[2], *Bs[2];
     As[0] = (elem *)smem;
@@ -706,7 +707,7 @@ __device__ __forceinline__ void tile_pieces(const unsigned char *smem, int tid, 
     constexpr int V = TileEl<CT>::V, CPR = CFG::BN / V, P = CFG::BN + 4;
     const float *Cs = (const float *)smem;
 #pragma unroll 2
-    for (int q = tid; q < CFG::BM * CPR; q += TILE_THREADS) {
+    for (int q = tid; q < CFG::BM * CPR; q += TILE_THREADS * CFG::DEEP) {
         const int m = q / CPR, n = q % CPR * V;
         float v[V];
 #pragma unroll

@@ -57,8 +57,8 @@ struct TileArgs {
     TileProb p[TILE_MAX_PROBS];
 };
 
-// Tile shapes a launch can use.
-enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x64, TS_32x128, TS_COUNT };
+// Tile shapes a launch can use (TS_32D: 32 x 32 by eight wavefronts).
+enum TileShape { TS_32, TS_64, TS_128x64, TS_128, TS_32x64, TS_32x128, TS_32D, TS_COUNT };
 
 // One product: add it to a launch.  ksplit <= 0 asks for the split that plan_tiles chose.
 TileProb tile_prob(int type, int M, int N, int K, const void *A, i64 lda, const void *B, i64 ldb, void *C, i64 ldc);

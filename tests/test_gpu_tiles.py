@@ -18,6 +18,9 @@ LINEAR = [
     (257, 65, 127, 33),
     (1500, 129, 72, 17),     # gradients split over the rows
     (2050, 1032, 1160, 264),  # large tiles with ragged edges
+    (160, 517, 260, 37),      # one workgroup per compute unit: chunks of twice the length, the last one nearly empty or not whole,
+    (130, 2047, 40, 64),      # alone, and with the contraction split as well
+    (300, 255, 1030, 96),
 ]
 
 CONV = [
