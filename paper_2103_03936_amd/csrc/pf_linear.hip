@@ -240,7 +240,7 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     if (p.t.fwd_bytes > p.fwd_bytes) p.fwd_bytes = p.t.fwd_bytes;
     if (p.t.bwd_bytes > p.bwd_bytes) p.bwd_bytes = p.t.bwd_bytes;
     p.small = d->dtype == PF_F32 && linear_small_supported(d->M, d->in, d->out, d->r);
-    p.n_small = p.small ? (size_t)(8 * d->M * d->r) : 0; // at most eight slices per intermediate
+    p.n_small = p.small ? (size_t)(LS_MAX_SLICES * d->M * d->r) : 0; // slices per intermediate
     if (p.small) {
         const size_t one = align_up(p.n_small * sizeof(float));
         if (one > p.fwd_bytes) p.fwd_bytes = one;

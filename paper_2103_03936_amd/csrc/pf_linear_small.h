@@ -7,16 +7,16 @@ namespace pf {
 
 constexpr int LS_MAX_K = 128;  // rows M, and rank r, at most (the contraction length of the second launch's tiles)
 constexpr int LS_MAX_PROB = 4; // products of one tile launch
-constexpr int LS_MAX_SLICES = 8;
+constexpr int LS_MAX_SLICES = 4;
 
-// launch 1: P[s][m][n] = sum over k in slice s of A[m * lda + k] W[k * ldw + n]; K a multiple of 32 S, N of 32
+// launch 1: P[s][m][n] = sum over k in slice s of A[m * lda + k] W[k * ldw + n]; K a multiple of 8 S, N of 32
 struct LsSliceArgs {
     const float *A, *W;
     float *P;
     i64 lda, ldw;
     int M, K, N, S;
 };
-int linear_small_slices(i64 K); // slices for a contraction of length K (a multiple of 32): 8, 4, 2 or 1
+int linear_small_slices(i64 K); // slices for a contraction of length K (a multiple of 32): 4, 2 or 1
 int launch_ls_slices(hipStream_t s, const char *name, const LsSliceArgs &a0, const LsSliceArgs &a1 = LsSliceArgs{});
 
 enum { LS_MK = 0, LS_KM = 1 };

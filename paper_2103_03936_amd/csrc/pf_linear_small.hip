@@ -14,45 +14,59 @@
 namespace pf {
 
 constexpr int LS_PITCH = 33; // floats between the k rows of a staged operand tile (32 values + 1 against conflicts)
+// Eight wavefronts per workgroup: a slice of 128 contraction indices is then two pieces per wavefront, and four slices do where four
+// wavefronts needed eight, which every workgroup of the second launch reads (64 x 512 -> 128 -> 512, forward 3.4 + 8.4 us).
+constexpr int LS_W = 8, LS_NT = 64 * LS_W;
+
+__device__ __forceinline__ float ls_sum(const float (&red)[LS_W][32 * LS_PITCH], int at)
+{
+    return ((red[0][at] + red[1][at]) + (red[2][at] + red[3][at])) + ((red[4][at] + red[5][at]) + (red[6][at] + red[7][at]));
+}
 
 // ----------------------------------------------------------------- launch 1
-// P[s][m][n] = sum over k in slice s of A[m][k] W[k][n]; grid (N / 32, row blocks, S).  The four wavefronts take a
-// quarter of the slice each and add their tiles in LDS.
-__global__ __launch_bounds__(256) void ls_slices_kernel(LsSliceArgs a0, LsSliceArgs a1)
+// P[s][m][n] = sum over k in slice s of A[m][k] W[k][n]; grid (N / 32, row blocks, S).  The eight wavefronts are dealt the slice
+// eight contraction indices at a time and add their tiles in LDS.
+__global__ __launch_bounds__(LS_NT) void ls_slices_kernel(LsSliceArgs a0, LsSliceArgs a1)
 {
     const LsSliceArgs a = blockIdx.z >= (unsigned)a0.S ? a1 : a0;
     const int s = blockIdx.z >= (unsigned)a0.S ? blockIdx.z - a0.S : blockIdx.z;
     const int ct = blockIdx.x, rb = blockIdx.y;
     if (ct * 32 >= a.N) return; // (the two problems may differ in width)
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, half = lane >> 5, col = lane & 31;
-    const int KS = a.K / a.S, kq = KS / 4; // kq: a multiple of 8
-    const int k0 = s * KS + w * kq;
+    const int KS = a.K / a.S;
     const int row = rb * 32 + col;
-    const float *Ar = a.A + (i64)(row < a.M ? row : a.M - 1) * a.lda;
-    const float *Wc = a.W + ct * 32 + col;
+    const float *Ar = a.A + (i64)(row < a.M ? row : a.M - 1) * a.lda + s * KS + 4 * half;
+    const float *Wc = a.W + (i64)(s * KS + 4 * half) * a.ldw + ct * 32 + col;
     f32x16_t acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (int kb = 0; kb < kq; kb += 8) { // lane half h holds k = k0 + kb + 4 h + 0..3
-        const int k = k0 + kb + 4 * half;
-        f32x4_t av = *(const f32x4_t *)(Ar + k);
-        if (row >= a.M) av = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        float bv[4];
+    for (int kb = 8 * w; kb < KS; kb += 16 * LS_W) { // lane half h holds k = kb + 4 h + 0..3; two pieces in flight
+        const int kc = min(kb + 8 * LS_W, KS - 8);
+        f32x4_t av[2];
+        float bv[2][4];
+        av[0] = *(const f32x4_t *)(Ar + kb);
+        av[1] = *(const f32x4_t *)(Ar + kc);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) bv[j] = Wc[(i64)(k + j) * a.ldw];
+        for (int j = 0; j < 4; ++j) {
+            bv[0][j] = Wc[(i64)(kb + j) * a.ldw];
+            bv[1][j] = Wc[(i64)(kc + j) * a.ldw];
+        }
+        if (kb + 8 * LS_W >= KS) av[1] = f32x4_t{0.f, 0.f, 0.f, 0.f}; // (a piece past the end: someone else's, times zero)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[j], bv[j], acc, 0, 0, 0);
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(row < a.M ? av[u][j] : 0.f, bv[u][j], acc, 0, 0, 0);
     }
-    __shared__ float red[4][32 * LS_PITCH];
+    __shared__ float red[LS_W][32 * LS_PITCH];
 #pragma unroll
     for (int v = 0; v < 16; ++v) red[w][(8 * (v >> 2) + 4 * half + (v & 3)) * LS_PITCH + col] = acc[v];
     __syncthreads();
     float *P = a.P + (i64)s * a.M * a.N;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int e = tid + 256 * i, m = e >> 5, n = e & 31;
-        const float v = (red[0][m * LS_PITCH + n] + red[1][m * LS_PITCH + n]) + (red[2][m * LS_PITCH + n] + red[3][m * LS_PITCH + n]);
-        if (rb * 32 + m < a.M) P[(i64)(rb * 32 + m) * a.N + ct * 32 + n] = v;
+    for (int i = 0; i < 1024 / LS_NT; ++i) {
+        const int e = tid + LS_NT * i, m = e >> 5, n = e & 31;
+        if (rb * 32 + m < a.M) P[(i64)(rb * 32 + m) * a.N + ct * 32 + n] = ls_sum(red, m * LS_PITCH + n);
     }
 }
 
@@ -62,56 +76,61 @@ __global__ __launch_bounds__(256) void ls_slices_kernel(LsSliceArgs a0, LsSliceA
 //   LS_MK: element (i, k) at p[i * ld + k]   (a row-major activation, or U / V read as the right operand)
 //   LS_KM: element (i, k) at p[k * ld + i]   (dY or X as the left operand of a factor gradient; T as the right one)
 // and either may be the sum of `slices` slices `sstride` floats apart.
-// (16-byte loads along the fast index; the loads of all slices of a piece are issued before the first add, and
-// slices are added in order)
-// SL: whether the operand comes in slices.  The loads are unconditional (a slice index past the end re-reads slice
-// 0 and is left out of the sum), so that all of them are in flight together.
+// A thread has two 16-byte pieces of either operand; all their slices are requested before the first is looked at (a slice past the
+// end re-reads the first and counts zero times; slices are added in order).
 template <bool SL>
-__device__ __forceinline__ f32x4_t ls_piece(const float *p, int slices, i64 sstride, bool live)
-{
-    if (!SL) {
-        const f32x4_t v = *(const f32x4_t *)p;
-        return live ? v : f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-    f32x4_t v[LS_MAX_SLICES];
-#pragma unroll
-    for (int sl = 0; sl < LS_MAX_SLICES; ++sl) v[sl] = *(const f32x4_t *)(p + (i64)(sl < slices ? sl : 0) * sstride);
-    f32x4_t sum = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int sl = 0; sl < LS_MAX_SLICES; ++sl) {
-        const float keep = sl < slices ? 1.f : 0.f;
-        sum += v[sl] * keep;
-    }
-    return live ? sum : f32x4_t{0.f, 0.f, 0.f, 0.f};
-}
+struct LsPieces {
+    static constexpr int NP = 32 * LS_MAX_K / 4 / LS_NT, NS = SL ? LS_MAX_SLICES : 1;
+    f32x4_t v[NP][NS];
+    bool mk, live[NP];
+    int k[NP], i[NP], slices;
 
-template <bool SL>
-__device__ __forceinline__ void ls_stage(float *dst, const LsOperand &o, int i0, int ni, int K, int tid)
-{
-    if (o.layout == LS_MK) { // piece = 4 consecutive k of row i (K a multiple of 4); consecutive threads along k
-        const int k4n = K >> 2, total = 32 * k4n;
-#pragma unroll 4
-        for (int e = tid; e < total; e += 256) {
-            const int i = e / k4n, k = 4 * (e - i * k4n);
-            const bool live = i0 + i < ni;
-            const f32x4_t v = ls_piece<SL>(o.p + (i64)(live ? i0 + i : i0) * o.ld + k, o.slices, o.sstride, live);
+    __device__ __forceinline__ void load(const LsOperand &o, int i0, int ni, int K, int tid)
+    {
+        mk = o.layout == LS_MK;
+        slices = o.slices;
+        const int k4n = K >> 2, total = 8 * K; // (K and ni are multiples of 4 where it matters)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dst[(k + j) * LS_PITCH + i] = v[j];
-        }
-    } else { // piece = 4 consecutive i of row k; consecutive threads along i
-        const int total = 8 * K;
-#pragma unroll 4
-        for (int e = tid; e < total; e += 256) {
-            const int k = e >> 3, i = 4 * (e & 7);
-            const bool live = i0 + i < ni; // (ni is a multiple of 4 wherever this layout is used)
-            const f32x4_t v = ls_piece<SL>(o.p + (i64)k * o.ld + (live ? i0 + i : i0), o.slices, o.sstride, live);
+        for (int q = 0; q < NP; ++q) {
+            const int e = min(tid + LS_NT * q, total - 1);
+            const int r = mk ? e / k4n : e >> 3;
+            i[q] = mk ? r : 4 * (e & 7);      // consecutive threads along k (piece = 4 k of row i) ..
+            k[q] = mk ? 4 * (e - r * k4n) : r; // .. or along i (piece = 4 i of row k)
+            live[q] = i0 + i[q] < ni;
+            const int ii = live[q] ? i0 + i[q] : i0;
+            const float *p = o.p + (mk ? (i64)ii * o.ld + k[q] : (i64)k[q] * o.ld + ii);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dst[k * LS_PITCH + i + j] = v[j];
+            for (int s = 0; s < NS; ++s) v[q][s] = *(const f32x4_t *)(p + (i64)(s < slices ? s : 0) * o.sstride);
         }
     }
+    __device__ __forceinline__ void stage(float *dst)
+    {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            f32x4_t t = v[q][0];
+#pragma unroll
+            for (int s = 1; s < NS; ++s) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) t[j] += s < slices ? v[q][s][j] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dst[mk ? (k[q] + j) * LS_PITCH + i[q] : k[q] * LS_PITCH + i[q] + j] = live[q] ? t[j] : 0.f;
+        }
+    }
+};
+
+template <bool SA, bool SB>
+__device__ __forceinline__ void ls_stage(const LsTileProb &pr, int m0, int n0, float *As, float *Bs, int tid)
+{
+    LsPieces<SA> a;
+    LsPieces<SB> b;
+    a.load(pr.A, m0, pr.M, pr.K, tid);
+    b.load(pr.B, n0, pr.N, pr.K, tid);
+    a.stage(As);
+    b.stage(Bs);
 }
 
-__global__ __launch_bounds__(256) void ls_tiles_kernel(LsTileArgs a)
+__global__ __launch_bounds__(LS_NT) void ls_tiles_kernel(LsTileArgs a)
 {
     // which problem does this workgroup belong to?
     int q = 0;
@@ -123,19 +142,34 @@ __global__ __launch_bounds__(256) void ls_tiles_kernel(LsTileArgs a)
     const int m0 = 32 * (t / nt), n0 = 32 * (t % nt);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, half = lane >> 5, col = lane & 31;
     __shared__ float As[LS_MAX_K * LS_PITCH], Bs[LS_MAX_K * LS_PITCH];
-    __shared__ float red[4][32 * LS_PITCH];
+    __shared__ float red[LS_W][32 * LS_PITCH];
     const int K = pr.K;
-    if (pr.A.slices > 1) // (uniform)
-        ls_stage<true>(As, pr.A, m0, pr.M, K, tid);
+    if (pr.A.slices > 1) // (uniform; no product has both operands in slices)
+        ls_stage<true, false>(pr, m0, n0, As, Bs, tid);
+    else if (pr.B.slices > 1)
+        ls_stage<false, true>(pr, m0, n0, As, Bs, tid);
     else
-        ls_stage<false>(As, pr.A, m0, pr.M, K, tid);
-    if (pr.B.slices > 1)
-        ls_stage<true>(Bs, pr.B, n0, pr.N, K, tid);
-    else
-        ls_stage<false>(Bs, pr.B, n0, pr.N, K, tid);
+        ls_stage<false, false>(pr, m0, n0, As, Bs, tid);
     __syncthreads();
+    f32x16_t acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    // wavefront w takes k = 2 (8 j + w) + half: the k pairs are dealt round the eight wavefronts, four in flight
+    for (int kp = w; 2 * kp < K; kp += 4 * LS_W) {
+        float av[4], bv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = 2 * (kp + LS_W * u) + half;
+            av[u] = k < K ? As[k * LS_PITCH + col] : 0.f;
+            bv[u] = k < K ? Bs[k * LS_PITCH + col] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bv[u], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) red[w][(8 * (v >> 2) + 4 * half + (v & 3)) * LS_PITCH + col] = acc[v];
     if (pr.A_copy && n0 == 0) { // the summed left operand leaves once (T for the backward pass): [M][K]
-        for (int e = tid; e < 32 * K; e += 256) {
+        for (int e = tid; e < 32 * K; e += LS_NT) {
             const int i = e / K, k = e - i * K;
             if (m0 + i < pr.M) pr.A_copy[(i64)(m0 + i) * K + k] = As[k * LS_PITCH + i];
         }
@@ -149,30 +183,13 @@ __global__ __launch_bounds__(256) void ls_tiles_kernel(LsTileArgs a)
         const float sum = (part[0] + part[1]) + (part[2] + part[3]);
         pr.colsum[m0 + tid] = pr.accumulate ? pr.colsum[m0 + tid] + sum : sum;
     }
-    f32x16_t acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    // wavefront w takes k = 2 (4 j + w) + half: the k pairs are dealt round the four wavefronts
-    for (int kp = w; 2 * kp < K; kp += 16) { // four k pairs per round: their LDS reads go out together
-        float av[4], bv[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = 2 * (kp + 4 * u) + half;
-            av[u] = k < K ? As[k * LS_PITCH + col] : 0.f;
-            bv[u] = k < K ? Bs[k * LS_PITCH + col] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], bv[u], acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) red[w][(8 * (v >> 2) + 4 * half + (v & 3)) * LS_PITCH + col] = acc[v];
     __syncthreads();
     if (!pr.C) return;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int e = tid + 256 * i, m = e >> 5, n = e & 31;
+    for (int i = 0; i < 1024 / LS_NT; ++i) {
+        const int e = tid + LS_NT * i, m = e >> 5, n = e & 31;
         if (m0 + m < pr.M && n0 + n < pr.N) {
-            float v = (red[0][m * LS_PITCH + n] + red[1][m * LS_PITCH + n]) + (red[2][m * LS_PITCH + n] + red[3][m * LS_PITCH + n]);
+            float v = ls_sum(red, m * LS_PITCH + n);
             if (pr.bias) v += pr.bias[n0 + n];
             float *c = pr.C + (i64)(m0 + m) * pr.ldc + n0 + n;
             *c = pr.accumulate ? *c + v : v;
@@ -188,7 +205,7 @@ bool linear_small_supported(i64 M, i64 n_in, i64 n_out, i64 r)
 
 int linear_small_slices(i64 K)
 {
-    for (int s = 8; s > 1; s >>= 1)
+    for (int s = LS_MAX_SLICES; s > 1; s >>= 1)
         if (K % (32 * s) == 0) return s;
     return 1;
 }
@@ -199,7 +216,7 @@ int launch_ls_slices(hipStream_t s, const char *name, const LsSliceArgs &a0, con
     const int n = a0.N > a1.N ? a0.N : a1.N, m = a0.M > a1.M ? a0.M : a1.M;
     if (n <= 0 || m <= 0) return st;
     const dim3 grid((unsigned)(n / 32), (unsigned)((m + 31) / 32), (unsigned)(a0.S + a1.S));
-    PF_LAUNCH(st, name, ls_slices_kernel, grid, dim3(256), s, a0, a1);
+    PF_LAUNCH(st, name, ls_slices_kernel, grid, dim3(LS_NT), s, a0, a1);
     return st;
 }
 
@@ -226,7 +243,7 @@ int launch_ls_tiles(hipStream_t s, const char *name, const LsTileArgs &a)
 {
     int st = PF_OK;
     if (a.nwg <= 0) return st;
-    PF_LAUNCH(st, name, ls_tiles_kernel, dim3((unsigned)a.nwg), dim3(256), s, a);
+    PF_LAUNCH(st, name, ls_tiles_kernel, dim3((unsigned)a.nwg), dim3(LS_NT), s, a);
     return st;
 }
 
