@@ -188,8 +188,20 @@ struct LinearPlan {
 //   53 / 16, 88 / 51, 135 / 87
 // and rank 64 (whose factors are re-ordered first): 1024 -> 256 forward 12 / 10, 13 / 13, 14 / 13, 16 / 17, at 32768 rows 29 / 25;
 // backward 23 / 9, 33 / 24, 35 / 27, 42 / 39, 62 / 74.
+// Few rows: while 32 rows x 128 outputs are at most one workgroup per compute unit, the kernel that deals them so is the fastest (us,
+// this / what the rules below chose; at twice as many workgroups it takes twice as long):
+//   512 -> 512   6.0 / 6.9 at 32 rows, 6.8 / 7.5 at 2048 (256 workgroups), 12.3 / 7.9 at 4096
+//   256 -> 1024  5.0 / 8.7,            5.5 / 9.3 at 1024,                   9.9 / 9.6 at 2048
+//   512 -> 2048  6.1 / 9.3,            6.8 / 10.6 at 512,                   12.4 / 11.1 at 1024
+//  1024 -> 512   8.1 / 10.6,           9.2 / 11.3 at 2048,                  17.2 / 11.7 at 4096
+//  1024 -> 4096  8.3 / 10.1,           8.9 / 11.5 at 256,                   16.8 / 11.8 at 512
+static bool rows_fwd_pays(i64 M, i64 in, i64 out, i64 r, int G = 1)
+{
+    return linear_rows_supported(in, out, r) && (M + 31) / 32 * (out / 128) * G <= 256;
+}
 static bool chain_fwd_pays(i64 M, i64 in, i64 out, i64 r)
 {
+    if (rows_fwd_pays(M, in, out, r)) return true; // (linear_fwd_fused takes that kernel)
     if (r != 128) return M >= 10000 && M <= 16384;
     if (M > 8192) return in <= 512;
     return in + out <= 1536 || (M >= 4096 && in <= 2048);
@@ -517,7 +529,7 @@ static int linear_fwd_fused(const pf_linear_desc *d, const bf16_t *X, const bf16
         c.ep_add = (const uint16_t *)ep.add;
         c.ep_relu = ep.relu;
         if (ep.used) *ep.used = true;
-        return launch_linear_chain2(s, "linear_fwd_fused", c);
+        return rows_fwd_pays(d->M, in, out, r) ? launch_linear_rows(s, "linear_fwd_rows", c) : launch_linear_chain2(s, "linear_fwd_fused", c);
     }
     uint16_t *w1 = ws.take<uint16_t>((size_t)(in > out ? in : out) * r);
     int st = launch_pack_chain(s, make_pack_w1((const uint16_t *)V, (uint4 *)w1, in, r, 1, 1, r, 0),
@@ -808,7 +820,8 @@ static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_line
     sp.one = one;
     sp.p = plan_linear(&one);
     const int G = d->groups;
-    sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS && chain_shared_fwd_pays(d->M, d->n_in);
+    sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS &&
+                   (chain_shared_fwd_pays(d->M, d->n_in) || rows_fwd_pays(d->M, d->n_in, d->n_out, d->r, G));
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
     // one layer's workspace, then one more dX (layer by layer)
@@ -1101,7 +1114,8 @@ int pf_lowrank_linear_shared_fwd(const pf_linear_shared_desc *d, const void *X, 
         c.gs_bias = out;
         c.gs_out = M * out;
         c.gs_mid = M * r;
-        return launch_linear_chain2(s, "linear_shared_fwd_fused", c);
+        return rows_fwd_pays(M, in, out, r, d->groups) ? launch_linear_rows(s, "linear_shared_fwd_rows", c)
+                                                       : launch_linear_chain2(s, "linear_shared_fwd_fused", c);
     }
     if (sp.t.ok) {
         Workspace ws(workspace, workspace_bytes);

@@ -39,4 +39,8 @@ bool linear_chain2_supported(i64 n_in, i64 n_out, i64 r);
 constexpr int LC_MAX_GROUPS = 8;
 int launch_linear_chain2(hipStream_t s, const char *name, const LinChainArgs &a);
 
+// The same for few rows (pf_linear_rows.hip): 32 rows x 128 outputs per workgroup.  C1 at most 1024; no mask, no column sums.
+bool linear_rows_supported(i64 n_in, i64 n_out, i64 r);
+int launch_linear_rows(hipStream_t s, const char *name, const LinChainArgs &a);
+
 } // namespace pf

@@ -86,6 +86,9 @@ ROUNDED = 2.0 ** -9 * 3 ** 0.5
     (4095, 512, 2048, 128), (4096, 512, 2048, 128), (8192, 512, 256, 128), (8193, 512, 256, 128), (8193, 768, 256, 128),
     (4096, 1024, 512, 128), (4999, 256, 256, 128), (5000, 256, 256, 128), (10001, 256, 256, 128), (10000, 256, 256, 64),
     (16385, 256, 256, 64), (24001, 512, 256, 64),
+    # the kernel for few rows, one row to the last that it takes and one more: both sides of every contraction length
+    (1, 256, 256, 128), (32, 512, 512, 128), (65, 768, 256, 128), (129, 1024, 512, 128), (2048, 512, 512, 128), (2049, 512, 512, 128),
+    (31, 1280, 256, 128), (256, 1024, 4096, 128),
     # the chain kernel's loops: a ragged last row tile, one to eight pairs of output blocks, any number of them, ten chunks
     (33, 256, 256, 128), (4129, 768, 1024, 128), (4129, 1024, 768, 128), (5003, 1280, 1280, 128), (4129, 2048, 512, 128)])
 @pytest.mark.parametrize("saved_T", [True, False])
@@ -105,7 +108,7 @@ def test_linear_routes(M, n_in, n_out, r, saved_T):
 
 
 @pytest.mark.parametrize("G,M,n_in,n_out", [(3, 8192, 256, 512), (3, 8193, 256, 512), (2, 4096, 1024, 256), (2, 4097, 1024, 256),
-                                            (8, 33, 512, 256), (9, 33, 512, 256)])
+                                            (8, 33, 512, 256), (9, 33, 512, 256), (3, 682, 768, 512), (3, 704, 512, 512)])
 def test_linear_shared_routes(G, M, n_in, n_out):
     import torch
     import paper_2103_03936_amd as pf
@@ -125,7 +128,7 @@ def test_linear_shared_routes(G, M, n_in, n_out):
     assert _rel(dX, total) <= ROUNDED
 
 
-@pytest.mark.parametrize("M,n_in,n_out", [(33, 256, 512), (4129, 1024, 512), (4129, 1024, 768), (5003, 1280, 1280), (4129, 512, 2048)])
+@pytest.mark.parametrize("M,n_in,n_out", [(33, 256, 512), (47, 1024, 256), (4129, 1024, 512), (4129, 1024, 768), (5003, 1280, 1280), (4129, 512, 2048)])
 def test_linear_routes_epilogue(M, n_in, n_out):
     """Residual and ReLU forward, skip gradient and mask backward, where the chain kernel applies them and where tiles do; an
     output that the chain kernel adds to is rounded twice."""
