@@ -522,6 +522,8 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
     const int npx = g.N * vdT.HC * V, phases = g.s * g.s;
     TileArgs a = {}, b = {};
     if (dX) {
+        // the two phases of a row in one workgroup, where half a piece lies in a row of the grid and both phases are all of it
+        const bool rows = kk > 1 && g.s == 2 && g.H == 2 * g.Ho && g.W == 2 * g.Wo && g.Wo % (V / 2) == 0;
         for (int f = 0; f < phases; ++f) {
             int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
             const int ni = phase_taps(g, f / g.s, ti, oi), nj = phase_taps(g, f % g.s, tj, oj), nt = ni * nj;
@@ -554,6 +556,7 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
                 q.o.W = g.W;
             }
             tile_add(b, p.sh_g, dt, q, 1);
+            if (rows && f % 2) tile_pair(b);
         }
     }
     if (dX || dUk) {

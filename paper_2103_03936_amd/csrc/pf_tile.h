@@ -20,6 +20,8 @@
 
 #include "pf_common.h"
 
+#include <type_traits>
+
 namespace pf {
 
 template <typename CT>
@@ -312,6 +314,39 @@ __device__ __forceinline__ uint4 ldg16_at(const elem *p, int off)
     return ldg16((const char *)p + (uint32_t)(off * (int)sizeof(elem)));
 }
 
+// With stride 2, and gW a multiple of a piece, the pixels of a piece are every second element from one on: two 16-byte loads,
+// the second V - 1 elements after the first, hold them (the even ones of the first, the odd ones of the second).  What travels with
+// the piece: the second load, where the two wanted to be, and which elements lie in the plane; at the ends of the tensor, where the
+// loads were pulled back, the elements are fetched one by one when the piece is stored.
+template <typename elem, int V>
+struct Strided {
+    static constexpr int XF = 6;
+    static __device__ __forceinline__ void load(const elem *p, int off, int total, uint32_t keep, uint4 &r, int *x)
+    {
+        const int a = min(max(off, 0), max(total - (2 * V - 1), 0));
+        r = ldg16_at(p, a);
+        const uint4 t = ldg16_at(p, a + V - 1);
+        x[0] = off, x[1] = (int)keep;
+        x[2] = (int)t.x, x[3] = (int)t.y, x[4] = (int)t.z, x[5] = (int)t.w;
+    }
+    static __device__ __forceinline__ uint4 piece(const elem *p, int total, const unsigned char *lut, uint4 r, const int *x)
+    {
+        const int off = x[0];
+        if (off < 0 || off + 2 * V - 1 > total) {
+            elem v[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = (x[1] >> e & 1) ? p[off + 2 * e] : elem(0);
+            return *(const uint4 *)v;
+        }
+        const uint32_t t0 = x[2], t1 = x[3], t2 = x[4], t3 = x[5];
+        if constexpr (sizeof(elem) == 4)
+            r = make_uint4(r.x, r.z, t1, t3);
+        else
+            r = make_uint4((r.x & 0xffffu) | r.y << 16, (r.z & 0xffffu) | r.w << 16, t0 >> 16 | (t1 & 0xffff0000u), t2 >> 16 | (t3 & 0xffff0000u));
+        return MaskTable<V>::apply(lut, (uint32_t)x[1], r);
+    }
+};
+
 // B operand (k = (channel, tap), n = pixel): one tile row per k, pixels contiguous.  Tables in LDS: offset of every tap,
 // mask of every (tap, piece of the tile).
 template <typename CT, int ROWS, bool GATHER>
@@ -319,14 +354,14 @@ struct LoadPixMC {
     typedef typename TileEl<CT>::elem elem;
     static constexpr bool KC = false;
     static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V,
-                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = CH;
+                         CH = BK * CPR / TILE_THREADS, LDS = BK * PITCH, KSTEP = TILE_THREADS / CPR, XF = GATHER ? 6 * CH : CH;
     static constexpr int TAPS = (TILE_MAX_TAPS + 3) / 4 * 16; // bytes of the offset table
     static constexpr int TAB = MaskTable<V>::BYTES + TAPS + TILE_MAX_TAPS * CPR;
     const elem *p;
     const unsigned char *tab;
     int pos0, last; // element of channel 0 at the piece's position; last element a piece may start at
     int HW, ntap, K, mc, col, krow, kl, ks, inc_c, inc_t;
-    bool masked;
+    bool masked, pairs; // (pairs: strided pieces by two loads)
     int lc[CH], lt[CH]; // (first element of the channel, tap) of the rows to load next
     int pixoff[GATHER ? V : 1];
 
@@ -366,6 +401,7 @@ struct LoadPixMC {
             pos0 += pos;
         }
         last = (int)g.total - V;
+        pairs = GATHER && g.s == 2 && g.gW % V == 0 && g.total >= 2 * V - 1;
         inc_c = BK / g.ntap;
         inc_t = BK - inc_c * g.ntap;
         inc_c *= HW;
@@ -383,13 +419,15 @@ struct LoadPixMC {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             const int off = pos0 + lc[i] + toff(lt[i]);
-            if (GATHER) {
+            if (GATHER && pairs) {
+                const uint32_t m = kl + krow + i * KSTEP < K ? tmask(lt[i]) : 0u;
+                Strided<elem, V>::load(p, off + pixoff[0], last + V, m, r[i], &x[GATHER ? 6 * i : 0]);
+            } else if (GATHER) {
                 const uint32_t m = kl + krow + i * KSTEP < K ? tmask(lt[i]) : 0u;
                 elem v[V];
 #pragma unroll
                 for (int e = 0; e < V; ++e) v[e] = (m >> e & 1) ? p[off + pixoff[GATHER ? e : 0]] : elem(0);
                 r[i] = *(const uint4 *)v;
-                x[i] = 0;
             } else {
                 const int a = min(max(off, 0), last);
                 r[i] = ldg16_at(p, a);
@@ -412,6 +450,7 @@ struct LoadPixMC {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             uint4 v = r[i];
+            if (GATHER && pairs) v = Strided<elem, V>::piece(p, last + V, tab, v, &x[GATHER ? 6 * i : 0]);
             if (!GATHER) {
                 const int s = (x[i] >> 8) - V;
                 if (s != 0) v = piece_shift<sizeof(elem)>(v, s);

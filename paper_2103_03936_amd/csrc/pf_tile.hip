@@ -121,6 +121,12 @@ void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ks
     a.blocks += (p.tm * p.tn * p.ksplit * p.nb + 7) / 8 * 8;
 }
 
+void tile_pair(TileArgs &a)
+{
+    a.p[a.n - 2].pair = 1;
+    a.blocks = a.p[a.n - 1].block0;
+}
+
 template <typename CT>
 int launch_linear_t(hipStream_t s, const char *name, TileShape shape, const TileArgs &a);
 template <typename CT>

@@ -52,17 +52,31 @@ tile_conv_kernel(TileArgs by_value)
     const TileProb &p = a.p[t.prob];
     const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v); };
     const int kbeg = t.ks * p.kper, nch = (min(p.K, kbeg + p.kper) - kbeg + BK - 1) / BK; // (not TILE_WG)
-    if (p.type == TILE_CONV || (GATHER && p.type == TILE_CONVG)) {
+    constexpr bool STRIDED = GATHER && !WG; // (a strided input is the right operand of launches without weight gradients only)
+    if (p.type == TILE_CONV || (STRIDED && p.type == TILE_CONVG)) {
         AK la;
         la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid);
-        if (GATHER && p.type == TILE_CONVG) {
-            BPG lb;
+        if (STRIDED && p.type == TILE_CONVG) {
+            typename std::conditional<STRIDED, BPG, BP>::type lb;
             lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
             tile_product<CT, CFG>(la, lb, nch, smem, tid);
         } else {
             BP lb;
             lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
             tile_product<CT, CFG>(la, lb, nch, smem, tid);
+            if constexpr (GATHER) {
+                if (p.pair) {
+                    const TileProb &p2 = a.p[t.prob + 1];
+                    PairOut<CT, CFG> both;
+                    both.keep(smem, tid);
+                    __syncthreads();
+                    la.init(p2.A, p2.lda, p2.M, p2.K, t.m0, 0, tid);
+                    lb.init(p2.pb, t.n0, 0, tid, tile_tables);
+                    tile_product<CT, CFG>(la, lb, (p2.K + BK - 1) / BK, smem, tid);
+                    both.put(p, t.m0, t.n0, smem, tid);
+                    return;
+                }
+            }
         }
         tile_pieces<CT, CFG>(smem, tid, put);
     } else if (p.type == TILE_CONVT) {
@@ -119,7 +133,7 @@ static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
         if (p.type == TILE_WGG) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, true>::table_bytes(p.pb);
         if (b > tab) tab = b;
         wg = wg || p.type == TILE_WG || p.type == TILE_WGG || p.type == TILE_WGT;
-        gather = gather || p.type == TILE_CONVG || p.type == TILE_WGG;
+        gather = gather || p.type == TILE_CONVG || p.type == TILE_WGG || p.pair;
     }
     tab = (tab + 15) / 16 * 16;
 #define PF_TILE_CONV(G, W)                                                                                              \

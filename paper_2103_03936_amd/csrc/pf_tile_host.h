@@ -38,6 +38,7 @@ enum TileType {
 
 struct TileProb {
     int type, M, N, K;
+    int pair;                         // TILE_CONV: the next problem has the odd pixels of this one's rows, and no workgroups
     int tm, tn, ksplit, kper, block0; // kper: chunk-aligned extent of a split (images for TILE_WG)
     const void *A, *B;
     i64 lda, ldb;
@@ -84,6 +85,8 @@ struct TileGroup {
 TileGroup plan_tile_group(int dtype, const TileNeed *need, int n);
 
 void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &p, int ksplit);
+// The last problem goes with the one before it (TileProb::pair).
+void tile_pair(TileArgs &a);
 int launch_tiles_linear(hipStream_t s, const char *name, int dtype, TileShape shape, const TileArgs &a);
 // (`wg`: the shape of the weight gradients' tiles, pixels being summed over)
 int launch_tiles_conv(hipStream_t s, const char *name, int dtype, TileShape shape, TileShape wg, const TileArgs &a);

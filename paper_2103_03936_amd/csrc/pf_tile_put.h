@@ -106,6 +106,78 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
     }
 }
 
+// Two tiles that are the even and the odd pixels of the same rows (a dX with stride 2, whose pixels x = 2 i and 2 i + 1 are reached by
+// different taps): the first one's sums stay in registers while the second is multiplied, and whole pieces of neighbouring pixels
+// leave.  Pixel by pixel, as elements 2 apart, the store and what is added and masks took 15 of the 24 us of a 64 x 64 tile.
+template <typename CT, class CFG>
+struct PairOut {
+    typedef typename TileEl<CT>::elem elem;
+    static constexpr int V = TileEl<CT>::V, W2 = V / 2, CPR = CFG::BN / W2, P = CFG::BM * CPR / TILE_THREADS, PITCH = CFG::BN + 4;
+    float c0[P][W2];
+
+    // (wavefronts that share a block: their sums together)
+    static __device__ __forceinline__ float at(const unsigned char *smem, int m, int n)
+    {
+        const float *Cs = (const float *)smem;
+        float v = Cs[m * PITCH + n];
+#pragma unroll
+        for (int w = 1; w < CFG::WK; ++w) v += Cs[(w * CFG::BM + m) * PITCH + n];
+        return v;
+    }
+    __device__ __forceinline__ void keep(const unsigned char *smem, int tid)
+    {
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            const int q = tid + TILE_THREADS * j;
+#pragma unroll
+            for (int e = 0; e < W2; ++e) c0[j][e] = at(smem, q / CPR, q % CPR * W2 + e);
+        }
+    }
+    __device__ __forceinline__ void put(const TileProb &p, int m0, int n0, const unsigned char *smem, int tid) const
+    {
+        const TileOut &o = p.o;
+        const int n = n0 + tid % CPR * W2, cell = o.HC * V, img = n / cell, pos = n - img * cell, y = pos / o.gW, x = pos - y * o.gW;
+        if (n >= p.N || img >= o.N || pos >= o.HW) return;
+        elem *c = (elem *)o.C;
+        const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask;
+        const int per = 4; // pieces whose operands are in flight together
+#pragma unroll
+        for (int j0 = 0; j0 < P; j0 += per) {
+            uint4 ra[per], rm[per];
+            i64 to[per];
+#pragma unroll
+            for (int u = 0; u < per; ++u) {
+                const int m = min(m0 + (tid + TILE_THREADS * (j0 + u)) / CPR, p.M - 1);
+                to[u] = ((i64)img * o.CH + m) * ((i64)o.H * o.W) + (i64)(2 * y + o.ph) * o.W + 2 * x;
+                if (add) ra[u] = ldg16(add + to[u]);
+                if (mask) rm[u] = ldg16(mask + to[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < per; ++u) {
+                const int j = j0 + u, row = (tid + TILE_THREADS * j) / CPR;
+                if (m0 + row >= p.M) continue;
+                float v[V], f[8];
+#pragma unroll
+                for (int e = 0; e < W2; ++e) {
+                    v[2 * e] = c0[j][e];
+                    v[2 * e + 1] = at(smem, row, tid % CPR * W2 + e);
+                }
+                if (add) {
+                    piece_floats<CT>(ra[u], f);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) v[e] += f[e];
+                }
+                if (mask) {
+                    piece_floats<CT>(rm[u], f);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) v[e] = f[e] > 0.f ? v[e] : 0.f;
+                }
+                stg16(c + to[u], floats_piece<CT>(v));
+            }
+        }
+    }
+};
+
 // Stores a tile and, from the loader that added them up, row sums r0 .. of at most nr.
 template <typename CT, class CFG, class L>
 __device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, L &l, int r0, int nr, bool sums,

@@ -143,3 +143,33 @@ def test_linear_routes_epilogue(M, n_in, n_out):
     x, v, u, dz = (t.double() for t in (X, V, U, dZ))
     assert _rel(Y, (x @ v @ u.t() + b.double() + R.double()).clamp(min=0)) <= ROUNDED
     assert _rel(dX, (dz @ u @ v.t() + skip.double()) * (x > 0)) <= ROUNDED
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 20, 16, 16, 24, 12, 3), (5, 9, 8, 24, 12, 8, 3), (2, 70, 12, 8, 16, 40, 3), (3, 12, 7, 9, 16, 8, 3),
+                                   (2, 16, 10, 6, 16, 8, 5), (1, 12, 2, 8, 12, 8, 3), (2, 16, 32, 4, 16, 8, 1)])
+def test_strided_conv_epilogue(shape, dtype):
+    """Stride 2, input read by pairs of loads and the even and odd pixels of dX in one workgroup where rows hold whole pieces, and
+    where they do not; skip gradient and mask against the plain gradient: the same sums, added to and masked before one rounding."""
+    import torch
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, r, k = shape
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(H * W + k)
+    n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(dt)
+    pad, Ho, Wo = k // 2, (H + 2 * (k // 2) - k) // 2 + 1, (W + 2 * (k // 2) - k) // 2 + 1
+    X, Uk, Vp, dY, add = n(N, C, H, W).clamp_(min=0), n(r, C, k, k, std=(C * k * k) ** -0.5), n(Cout, r, std=r ** -0.5), n(N, Cout, Ho, Wo), n(N, C, H, W)
+    Y, T = pf.pf_lowrank_conv_fwd(X, Uk, Vp, 2, pad)
+    want_T = torch.nn.functional.conv2d(X.double().cpu(), Uk.double().cpu(), stride=2, padding=pad)
+    # T: float sums of C k k terms, or rounded to bf16
+    assert _rel(T.cpu(), want_T) <= (2.0 ** -20 if dtype == "f32" else ROUNDED)
+    dX = pf.pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=T, stride=2, pad=pad)[0]
+    got = pf.pf_lowrank_conv_bwd_ep(X, Uk, Vp, None, dY, T_saved=T, stride=2, pad=pad, dX_add=add, x_is_relu=True)[0]
+    want = torch.where(X > 0, dX.float() + add.float(), torch.zeros((), device="cuda"))
+    if dtype == "f32":
+        assert torch.equal(got, want)
+    else:
+        assert _rel(got, want.double()) <= ROUNDED
+    ref = torch.nn.grad.conv2d_input((N, C, H, W), Uk.double().cpu(), torch.einsum("or,nohw->nrhw", Vp.double().cpu(), dY.double().cpu()),
+                                     stride=2, padding=pad)
+    assert _rel(dX.cpu(), ref) <= (2.0 ** -20 if dtype == "f32" else ROUNDED)
