@@ -14,9 +14,14 @@
 // wavefronts of a workgroup, so each reads only its share of the exchanged activations, in the lanes' own order, and no LDS is
 // needed before the sum.
 //
-// The barrier between phases: workgroups count arrivals in eight groups (an atomic each on a line of its own), the last of a
-// group tells eight copies of the group flags, and everybody polls one of the copies: 1.9 us over 256 workgroups, where
-// polling one flag per workgroup took 4.6 us (all pollers hit the same few memory channels).
+// Between phases a wavefront waits for the tasks whose results it reads, and for no others: a task that is done stores the
+// slot's number to its flag, in eight copies, and the readers poll the 6 to 48 flags that fill their contraction indices, those of
+// a die in one copy.  Before, a barrier over all workgroups (arrivals counted in eight groups, whose last tell eight copies of the
+// group flags) cost 1.9 us a phase: an atomic's round trip more, and everybody waited for the slowest.  Whole calls, us: 1500
+// units, two layers, batch 20, 35 steps 1266 -> 1242; 650 units 818 -> 762; 256 units, three layers, batch 4, 70 steps 865 -> 762.
+// (One copy of the flags: 1376; the pollers get in each other's way.)  What a slot of 11 us consists of now at 1500 units, forward:
+// two hand-overs of 0.9, the first reads of what was handed over 0.8 each, matrix instructions 0.8 and 2.4, the wavefronts' sums 0.3
+// and 0.6, gates 0.7.
 #include "pf_lstm_persist_index.h"
 
 #include <atomic>
@@ -42,13 +47,50 @@ __device__ __forceinline__ void lp_share(float *p, float v) // a store that othe
 }
 
 // ------------------------------------------------------------------ phases
+// The end of a task's part of a slot: everything that the workgroup has shared is visible, then its flag (all threads)
+__device__ __forceinline__ void lp_publish(unsigned *flags, int flag, unsigned epoch)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+    __syncthreads();
+    if (threadIdx.x < LP_GROUPS) __hip_atomic_store(flags + threadIdx.x * LP_COPY + flag, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// All workgroups of a cooperative launch are resident, so every flag comes; a wait is bounded all the same (by polls, of
+// about a microsecond each: a process that is suspended does not count), and everyone leaves when one gives up, with NaN in
+// what it has not written.
+__device__ __forceinline__ bool lp_poll(const unsigned *flag, unsigned epoch, unsigned *failed)
+{
+    bool good = false;
+    for (int spin = 0; spin < 4000000; ++spin) {
+        const unsigned v = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!__any((int)(v - epoch) < 0)) {
+            good = true;
+            break;
+        }
+        if ((spin & 255) == 255 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
+    }
+    if (!good && (threadIdx.x & 63) == 0) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" ::: "memory"); // no read of shared data before this
+#endif
+    return good;
+}
+// A wavefront's wait; *ok (LDS, 1 at first) tells the workgroup after its next __syncthreads
+__device__ __forceinline__ void lp_await(const unsigned *flag, unsigned epoch, unsigned *failed, int *ok)
+{
+    if (!lp_poll(flag, epoch, failed)) *ok = 0;
+}
+
+// A barrier of n workgroups, once in a launch: they count arrivals in eight groups (an atomic each on a line of its own), the last
+// of a group tells eight copies of the group flags, and everybody polls one of the copies.
 struct LpSync {
     unsigned *base;
     int wg;
     int *ok; // LDS
 
-    // everything this workgroup has shared is visible; then it counts itself in (all threads; barrier b of n workgroups)
-    __device__ __forceinline__ void arrive(int b, int n, unsigned epoch)
+    // everything this workgroup has shared is visible; then it counts itself in (all threads)
+    __device__ __forceinline__ void arrive(int n)
     {
 #if defined(__HIP_DEVICE_COMPILE__)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -56,40 +98,25 @@ struct LpSync {
         __syncthreads();
         if (threadIdx.x < 64) {
             const int g = wg % LP_GROUPS, members = n / LP_GROUPS; // (n: a multiple)
-            unsigned *counter = base + b * LP_BAR, *flags = counter + LP_GROUPS * 64;
+            unsigned *flags = base + LP_GROUPS * 64;
             int before = 0;
             if (threadIdx.x == 0)
-                before = (int)__hip_atomic_fetch_add(counter + g * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                before = (int)__hip_atomic_fetch_add(base + g * 64, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             before = __builtin_amdgcn_readfirstlane(before);
-            if ((unsigned)before == (unsigned)members * epoch - 1u && threadIdx.x < LP_GROUPS)
-                __hip_atomic_store(flags + threadIdx.x * 64 + g, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (before == members - 1 && threadIdx.x < LP_GROUPS)
+                __hip_atomic_store(flags + threadIdx.x * 64 + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    // All workgroups of a cooperative launch are resident, so all of them arrive; the wait is bounded all the same (by polls, of
-    // about a microsecond each: a process that is suspended does not count), and everyone leaves when one gives up, with NaN in
-    // what it has not written.
-    __device__ __forceinline__ bool wait(int b, unsigned epoch)
+    __device__ __forceinline__ bool wait()
     {
         if (threadIdx.x < 64) {
-            const unsigned *flags = base + b * LP_BAR + LP_GROUPS * 64 + (wg % LP_GROUPS) * 64;
-            const int i = min((int)threadIdx.x, LP_GROUPS - 1);
-            bool good = false;
-            for (int spin = 0; spin < 4000000; ++spin) {
-                const unsigned v = __hip_atomic_load(flags + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (!__any((int)(v - epoch) < 0)) {
-                    good = true;
-                    break;
-                }
-                if ((spin & 255) == 255 &&
-                    __hip_atomic_load(base + 2 * LP_BAR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            }
-            if (threadIdx.x == 0) {
-                if (!good) __hip_atomic_store(base + 2 * LP_BAR, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                *ok = good;
-            }
+            const unsigned *flags = base + LP_GROUPS * 64 + (wg % LP_GROUPS) * 64;
+            const bool good = lp_poll(flags + min((int)threadIdx.x, LP_GROUPS - 1), 1u, base + LP_FAILED);
+            if (threadIdx.x == 0) *ok = good;
         }
         __syncthreads();
         const bool all = *ok != 0;
+        __syncthreads(); // (nobody clears it before all have read it)
 #if defined(__HIP_DEVICE_COMPILE__)
         asm volatile("" ::: "memory"); // no read of shared data before this
 #endif
@@ -316,7 +343,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), wg = blockIdx.x;
     const int T = a.T, B = a.B, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
     LpSync sync = {a.sync, wg, &ok};
-    const bool in1 = wg < a.n1, in2 = wg < a.n2;
+    unsigned *flags = a.sync + LP_BAR, *failed = a.sync + LP_FAILED;
+    const bool in2 = wg < a.n2;
     // the initial states and the first layer's Tx into the lanes' order
     if (in2) {
         // (the few states by the last workgroups, which have one element less of the other)
@@ -333,13 +361,14 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
             const float v = a.l[0].Tx[((i64)at.row * B + min(m, B - 1)) * gr + q * r + min(cc, r - 1)];
             lp_share(lp_xt(a, 0, 1, at.row) + at.o, cc < r ? v : 0.f);
         }
-        sync.arrive(1, a.n2, 1u);
+        sync.arrive(a.n2);
     }
     // phase 1: columns tcol .. tcol + tncol - 1 of a product; groups tg0 .. of h
     const LpColumns cols = lp_columns(a, wg, a.n1, G * rp, 8, 1);
     const bool has1 = cols.has;
     const int tl = cols.l, tpath = cols.path, tcol = cols.col, tncol = cols.n;
-    const int tper = (hp / 32 + LP_WAVES - 1) / LP_WAVES, tg0 = w * tper, tng = has1 ? min(tper, hp / 32 - tg0) : 0;
+    const LpShare share1 = lp_fwd_share1(a, cols, w, U);
+    const int tg0 = share1.first, tng = share1.n;
     float wt[TN][TKG][4];
     {
         const float *V = tpath ? a.l[tl].Vx : a.l[tl].Vh;
@@ -352,9 +381,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
     // phase 2: units u0 .. of layer zl
     const LpUnits units = lp_units(a, wg, a.n2, U);
     const bool has2 = units.has;
-    const int zl = units.l, u0 = units.u0, zx = w >> 2, zgroups = rp / 32;
-    const int zper = G4 ? zgroups : (zgroups + 3) / 4, zg0 = (G4 ? (w & 3) * zgroups : (w & 3) * zper);
-    const int zng = !has2 ? 0 : G4 ? zgroups : min(zper, zgroups - zg0);
+    const LpShare share2 = lp_fwd_share2(a, units, w);
+    const int zl = units.l, u0 = units.u0, zx = w >> 2, zg0 = share2.first, zng = share2.n;
     float wz[NT][KG][8];
     {
         const float *Um = zx ? a.l[zl].Ux : a.l[zl].Uh;
@@ -376,32 +404,36 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
 #pragma unroll
         for (int g = 0; g < 4; ++g) pb[g] = a.l[zl].bias ? a.l[zl].bias[(i64)g * h + un] : 0.f;
     }
+    const unsigned *mine = flags + wg % LP_GROUPS * LP_COPY;
+    const unsigned *await1 = mine + lp_flag(2, share1.on.task(tid & 63)), *await2 = mine + lp_flag(1, share2.on.task(tid & 63));
     int slot = 0;
-    bool lost = false; // a wait gave up
-    for (; slot < T + L - 1; ++slot) {
-        if (in1) {
-            if ((lost = !sync.wait(1, slot + 1))) break;
+    bool lost = !sync.wait(); // a wait gave up
+    for (; !lost && slot < T + L - 1; ++slot) {
+        if (has1) {
             const int t = slot - tl;
-            if (has1 && t >= 0 && t < T) {
+            if (t >= 0 && t < T) {
+                if (share1.waits && t + tpath > 0) lp_await(await1, slot, failed, &ok);
                 f32x4_t acc[TN][RB];
                 lp_zero(acc);
                 lp_multiply<1, lp_depth(RB, TKG, TN, WR), 1>(acc, wt, (tncol + 7) / 8,
                                                              (tpath ? lp_xh(a, tl - 1, t + 1) : lp_xh(a, tl, t)) + tg0 * RB * 128, 0, tng);
                 lp_exchange<1>(red, acc);
+                if ((lost = !ok)) break;
                 lp_put_T<TN, 8, RB>(a, red, lp_xt(a, tl, tpath, t), (tpath ? a.l[tl].Tx : a.l[tl].Th) + (i64)t * B * gr, tcol, tncol);
             }
-            sync.arrive(0, a.n1, slot + 1);
+            lp_publish(flags, lp_flag(1, cols.task), slot + 1);
         }
-        if (in2) {
+        if (has2) {
             const int t = slot - zl;
-            if ((lost = !sync.wait(0, slot + 1))) break;
             float gv[4] = {}, cv = 0.f, hv = 0.f;
-            const bool active = has2 && t >= 0 && t < T;
+            const bool active = t >= 0 && t < T;
             if (active) {
+                if (share2.waits) lp_await(await2, slot + 1, failed, &ok);
                 f32x4_t acc[NT][RB];
                 lp_zero(acc);
                 lp_multiply<2, lp_depth(RB, KG, NT, WR), 1>(acc, wz, NT, lp_xt(a, zl, zx, t) + zg0 * RB * 128, 0, zng);
                 lp_exchange<2>(red, acc);
+                if ((lost = !ok)) break;
                 float z[4];
                 const int rb = min(em >> 2, RB - 1);
                 if constexpr (G4) {
@@ -423,7 +455,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
                 if (el) lp_share(lp_xh(a, zl, t + 1) + lp_place<RB>(un, em), un < h ? hv : 0.f);
                 c_prev = cv;
             }
-            sync.arrive(1, a.n2, slot + 2); // the others need h only
+            lp_publish(flags, lp_flag(2, units.task), slot + 1); // the others need h only
             if (active && kept) {
                 const LstmRunLayer &y = a.l[zl];
                 const i64 idx = (i64)t * B * h + (i64)em * h + un, base = ((i64)t * B + em) * 4 * h + un;
@@ -454,15 +486,16 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     __shared__ int ok;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), wg = blockIdx.x;
     const int T = a.T, B = a.B, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
-    LpSync sync = {a.sync, wg, &ok};
-    const bool in1 = wg < a.n1, in2 = wg < a.n2;
+    unsigned *flags = a.sync + LP_BAR, *failed = a.sync + LP_FAILED;
+    if (tid == 0) ok = 1; // (waits that give up clear it)
+    __syncthreads();
     // phase 1: units u0 .. of layer zl
     const LpUnits units = lp_units(a, wg, a.n1, 16 * NT);
     const bool has1 = units.has;
     const int zl = units.l, u0 = units.u0;
     const bool two = zl + 1 < L;
-    const int zx = two ? w >> 2 : 0, zgroups = G * rp / 32, parts = two ? 4 : 8, zper = (zgroups + parts - 1) / parts;
-    const int zg0 = (w & (parts - 1)) * zper, zng = has1 ? min(zper, zgroups - zg0) : 0;
+    const LpShare share1 = lp_bwd_share1(a, units, w, SL);
+    const int zx = two ? w >> 2 : 0, zg0 = share1.first, zng = share1.n;
     float wz[NT][KG][8];
     {
         const float *V = zx ? a.l[zl + 1].Vx : a.l[zl].Vh;
@@ -479,9 +512,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     const LpColumns cols = lp_columns(a, wg, a.n2, rp, TW, G4 ? 4 : SL);
     const bool has2 = cols.has;
     const int tq = cols.q, tl = cols.l, tpath = cols.path, tcol = cols.col, tncol = cols.n;
-    const int tgroups = (G4 ? hp : 4 * hp) / 32, tslice = (tgroups + SL - 1) / SL, tper = (tslice + LP_WAVES - 1) / LP_WAVES;
-    const int ts0 = G4 ? 0 : tq * tslice, tg0 = ts0 + w * tper;
-    const int tng = has2 ? min(tper, min(ts0 + tslice, tgroups) - tg0) : 0;
+    const LpShare share2 = lp_bwd_share2(a, cols, w, SL, 16 * NT);
+    const int tg0 = share2.first, tng = share2.n;
     float wt[TN][TKG][2 << TCB];
     {
         const float *Um = tpath ? a.l[tl].Ux : a.l[tl].Uh;
@@ -494,13 +526,15 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     float dcs[NIT];
 #pragma unroll
     for (int it = 0; it < NIT; ++it) dcs[it] = 0.f;
+    const unsigned *mine = flags + wg % LP_GROUPS * LP_COPY;
+    const unsigned *await1 = mine + lp_flag(2, share1.on.task(tid & 63)), *await2 = mine + lp_flag(1, share2.on.task(tid & 63));
     int u = 0;
     bool lost = false; // a wait gave up
     for (; u < T + L; ++u) {
-        if (in1) {
+        if (has1) {
             const LstmRunLayer &y = a.l[zl];
             const int t = T - 1 - (u - (L - 1 - zl));
-            const bool active = has1 && t >= -1 && t < T, own = t + 1 < T, above = t >= 0 && two;
+            const bool active = t >= -1 && t < T, own = t + 1 < T, above = t >= 0 && two;
             float pa[NIT], pg[NIT][4], pcp[NIT], pco[NIT];
             auto element = [&](int it, int &m, int &un) __attribute__((always_inline)) {
                 const int e = tid + LP_NT * it, p = e >> 3;
@@ -523,14 +557,16 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                     if (t == T - 1) dcs[it] = in && y.dcT ? y.dcT[idx] : 0.f;
                 }
             }
-            if (u > 0 && (lost = !sync.wait(1, u))) break;
             if (active) {
                 f32x4_t acc[NT][RB];
                 lp_zero(acc);
-                if (zx ? above : own)
+                if (share1.waits && (zx ? above : own)) {
+                    lp_await(await1, u, failed, &ok);
                     lp_multiply<2, lp_depth(RB, KG, NT, WR, SL), SL>(acc, wz, NT, (zx ? lp_xt(a, zl + 1, 1, t) : lp_xt(a, zl, 0, t + 1)) + zg0 * RB * 128,
                                                                      rp * 4 * RB, zng);
+                }
                 lp_exchange<2>(red, acc);
+                if ((lost = !ok)) break;
                 float *xz = lp_xh(a, zl, max(t, 0));
                 float dv[NIT][4], dcv[NIT];
 #pragma unroll
@@ -554,7 +590,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                         for (int g = 0; g < 4; ++g) lp_share(xz + lp_place<RB>(g * hp + un, m), un < h ? dv[it][g] : 0.f);
                     }
                 }
-                if (u + 1 < T + L) sync.arrive(0, a.n1, u + 1);
+                lp_publish(flags, lp_flag(1, units.task), u + 1);
                 if (t >= 0) {
 #pragma unroll
                     for (int it = 0; it < NIT; ++it) {
@@ -567,30 +603,34 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                         }
                     }
                 }
-            } else if (u + 1 < T + L) {
-                sync.arrive(0, a.n1, u + 1);
             }
         }
-        if (in2 && u + 1 < T + L) {
+        if (has2 && u + 1 < T + L) {
             const int t = T - 1 - (u - (L - 1 - tl));
-            if ((lost = !sync.wait(0, u + 1))) break;
-            if (has2 && t >= 0 && t < T) {
+            if (t >= 0 && t < T) {
+                if (share2.waits) lp_await(await2, u + 1, failed, &ok);
                 f32x4_t acc[TN][RB];
                 lp_zero(acc);
                 lp_multiply<TCB, lp_depth(RB, TKG, TN, WR), 1>(acc, wt, (tncol + TW - 1) / TW, lp_xh(a, tl, t) + ((G4 ? tq * (hp / 32) : 0) + tg0) * RB * 128,
                                                                0, tng);
                 lp_exchange<TCB>(red, acc);
+                if ((lost = !ok)) break;
                 lp_put_T<TN, TW, RB>(a, red, lp_xt(a, tl, tpath, t) + (SL > 1 ? tq * rp * 4 * RB : 0),
                                      SL > 1 ? nullptr : (tpath ? a.l[tl].dTx : a.l[tl].dTh) + (i64)t * B * gr, (G4 ? tq * rp : 0) + tcol, tncol);
+                lp_publish(flags, lp_flag(2, cols.task), u + 1);
             }
-            sync.arrive(1, a.n2, u + 1);
         }
+    }
+    if (SL > 1) { // the slices' sums: all of dT is there
+        LpSync sync = {a.sync, wg, &ok};
+        if (!lost && wg < a.n2) sync.arrive(a.n2);
+        if (!lost && wg < a.n1) lost = !sync.wait();
     }
     if (lost) {
         lp_void_bwd(a, cols, units, u, SL, RB, wg, tid);
         return;
     }
-    if (SL > 1 && in1) { // (these workgroups have waited for the last dT)
+    if (SL > 1 && wg < a.n1) {
         const int nx = rp * 4 * RB;
         for (LpWalk at(nx, wg * LP_NT + tid, a.n1 * LP_NT); at.row < (2 * L - 1) * T; at.next()) {
             const int o = at.o, pr = at.row / T, t = at.row - pr * T, l = lp_layer(pr), path = lp_path(pr);
@@ -607,7 +647,6 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
 }
 
 // ------------------------------------------------------------------ host side
-constexpr int LP_MOST_CUS = 256;
 // compute units of the current device that a launch may use, 0 if it cannot run cooperative launches
 static int lp_cus()
 {

@@ -8,8 +8,13 @@ namespace pf {
 constexpr int LP_MAX_LAYERS = 4;
 constexpr int LP_NT = 512, LP_WAVES = 8; // threads
 constexpr int LP_GROUPS = 8;             // of workgroups in a barrier
-constexpr int LP_BAR = 2 * LP_GROUPS * 64; // words of one: a line per group counter, then the copies of the flags
-constexpr int LP_SYNC = 2 * LP_BAR + 64;   // both barriers, the word of a failed wait
+constexpr int LP_BAR = 2 * LP_GROUPS * 64; // words of one: a line per group counter, then the copies of its flags
+constexpr int LP_MOST_CUS = 256;           // tasks of a phase, at most
+// How far each task is: words, in eight copies (a workgroup polls one of them), 16 tasks to a line of 256 bytes
+constexpr int LP_COPY = 2 * LP_MOST_CUS / 16 * 64, LP_FLAGS = LP_GROUPS * LP_COPY;
+__host__ __device__ __forceinline__ int lp_flag(int phase, int task) { return ((phase - 1) * LP_MOST_CUS + task) / 16 * 64 + task % 16; }
+constexpr int LP_SYNC = LP_BAR + LP_FLAGS + 64; // the last 64: the word of a failed wait
+constexpr int LP_FAILED = LP_BAR + LP_FLAGS;
 
 struct LpArgs {
     LstmRunLayer l[LP_MAX_LAYERS];
@@ -40,7 +45,7 @@ __host__ __device__ __forceinline__ float *lp_xh(const LpArgs &a, int l, int slo
 // A workgroup's units u0 .. u0 + n - 1 of layer l (n workgroups of U units each take part; !has: none for this one)
 struct LpUnits {
     bool has;
-    int l, u0, n;
+    int l, u0, n, task;
 };
 __host__ __device__ __forceinline__ LpUnits lp_units(const LpArgs &a, int wg, int parts, int U)
 {
@@ -50,12 +55,13 @@ __host__ __device__ __forceinline__ LpUnits lp_units(const LpArgs &a, int wg, in
     t.l = t.has ? task / per_layer : 0;
     t.u0 = t.has ? (task - t.l * per_layer) * U : 0;
     t.n = U;
+    t.task = task;
     return t;
 }
 // Its columns col .. col + n - 1 of T (or dT) of product p: of `cols` columns, in tiles of TW, block q of the product's `blocks`
 struct LpColumns {
     bool has;
-    int p, q, l, path, col, n;
+    int p, q, l, path, col, n, task;
 };
 __host__ __device__ __forceinline__ LpColumns lp_columns(const LpArgs &a, int wg, int parts, int cols, int TW, int blocks)
 {
@@ -67,7 +73,88 @@ __host__ __device__ __forceinline__ LpColumns lp_columns(const LpArgs &a, int wg
     t.l = lp_layer(t.p), t.path = lp_path(t.p);
     t.col = t.has ? (task - b * per_block) * TW * a.nt1 : 0;
     t.n = TW * a.nt1 < cols - t.col ? TW * a.nt1 : cols - t.col;
+    t.task = task;
     return t;
+}
+
+// The tasks whose results a wavefront reads (at most 64, one per lane that polls): `blocks` runs of n tasks, `stride` apart, from
+// base + first on, a run going on at base after base + wrap - 1.  Their results fill whole groups of 32 indices of an exchanged
+// matrix, and so whole lines: none of those is read before every task that writes to it is done.
+struct LpWatch {
+    int base, first, n, wrap, blocks, stride;
+    __host__ __device__ __forceinline__ int task(int lane) const
+    {
+        const int b = lane < n * blocks ? lane / n : 0, i = lane < n * blocks ? lane - b * n : 0;
+        return base + b * stride + (first + i < wrap ? first + i : first + i - wrap);
+    }
+};
+// those of units k0 .. k0 + len - 1 of layer l, in tasks of U (past hp: on from unit 0)
+__host__ __device__ __forceinline__ LpWatch lp_watch_units(const LpArgs &a, int l, int k0, int len, int U)
+{
+    const int per_layer = (a.hp + U - 1) / U;
+    LpWatch w = {l * per_layer, k0 / U, 0, per_layer, 1, 0};
+    if (len <= 0) return w;
+    const int last = k0 + len - 1;
+    w.n = (last < a.hp ? last / U : per_layer + (last - a.hp) / U) - w.first + 1;
+    if (w.n > per_layer) w.n = per_layer;
+    return w;
+}
+// those of columns k0 .. k0 + len - 1 of T of product p (all gates' columns, rp each where a block is one gate; else every block)
+__host__ __device__ __forceinline__ LpWatch lp_watch_columns(const LpArgs &a, int p, int k0, int len, int cols, int TW, int blocks, bool gates)
+{
+    const int per_block = (cols / TW + a.nt1 - 1) / a.nt1, tile = TW * a.nt1, last = k0 + len - 1;
+    const int q0 = gates ? k0 / cols : 0, q1 = gates ? last / cols : 0;
+    LpWatch w = {p * blocks * per_block, q0 * per_block + (k0 - q0 * cols) / tile, 0, 1 << 30, gates ? 1 : blocks, per_block};
+    if (len > 0) w.n = q1 * per_block + (last - q1 * cols) / tile - w.first + 1;
+    return w;
+}
+
+// Wavefront w's share of a task's contraction: n groups of 32 indices from group `first` on, and whom it waits for before it reads
+// them (!waits: nobody, they are there or there are none).
+struct LpShare {
+    int first, n;
+    bool waits;
+    LpWatch on;
+};
+__host__ __device__ __forceinline__ int lp_left(int per, int left) { return per < left ? per : left; }
+__host__ __device__ __forceinline__ LpShare lp_fwd_share1(const LpArgs &a, const LpColumns &c, int w, int U)
+{
+    LpShare s;
+    const int total = a.hp / 32, per = (total + LP_WAVES - 1) / LP_WAVES;
+    s.first = w * per, s.n = c.has ? lp_left(per, total - s.first) : 0;
+    s.waits = s.n > 0;
+    s.on = lp_watch_units(a, c.path ? c.l - 1 : c.l, 32 * s.first, 32 * s.n, U);
+    return s;
+}
+__host__ __device__ __forceinline__ LpShare lp_fwd_share2(const LpArgs &a, const LpUnits &z, int w) // (wavefronts 0 - 3: Th, 4 - 7: Tx)
+{
+    LpShare s;
+    const int total = a.rp / 32, per = a.G != 1 ? total : (total + 3) / 4, p = w >= 4 ? 2 * z.l : z.l ? 2 * z.l - 1 : 0;
+    s.first = (w & 3) * per, s.n = !z.has ? 0 : a.G != 1 ? per : lp_left(per, total - s.first);
+    s.waits = s.n > 0 && (z.l > 0 || w < 4); // (the first layer's Tx is there)
+    s.on = lp_watch_columns(a, p, 32 * s.first, 32 * s.n, a.G * a.rp, 8, 1, false);
+    return s;
+}
+__host__ __device__ __forceinline__ LpShare lp_bwd_share1(const LpArgs &a, const LpUnits &z, int w, int SL)
+{
+    LpShare s;
+    const bool two = z.l + 1 < a.L;
+    const int parts = two ? 4 : 8, total = a.G * a.rp / 32, per = (total + parts - 1) / parts, p = two && w >= 4 ? 2 * z.l + 2 : z.l ? 2 * z.l - 1 : 0;
+    s.first = (w & (parts - 1)) * per, s.n = z.has ? lp_left(per, total - s.first) : 0;
+    s.waits = s.n > 0;
+    s.on = a.G != 1 ? lp_watch_columns(a, p, 32 * s.first, 32 * s.n, a.rp, 8, 4, true)
+                    : lp_watch_columns(a, p, 32 * s.first, 32 * s.n, a.rp, 16, SL, false);
+    return s;
+}
+__host__ __device__ __forceinline__ LpShare lp_bwd_share2(const LpArgs &a, const LpColumns &c, int w, int SL, int U) // (slice q of 4 hp, or gate q)
+{
+    LpShare s;
+    const int total = (a.G != 1 ? a.hp : 4 * a.hp) / 32, slice = (total + SL - 1) / SL, per = (slice + LP_WAVES - 1) / LP_WAVES;
+    const int s0 = a.G != 1 ? 0 : c.q * slice;
+    s.first = s0 + w * per, s.n = c.has ? lp_left(per, lp_left(s0 + slice, total) - s.first) : 0;
+    s.waits = s.n > 0;
+    s.on = lp_watch_units(a, c.l, 32 * s.first % a.hp, 32 * s.n, U);
+    return s;
 }
 
 // Walks the elements first, first + step, ... of a list of rows of n elements each; row and o are the current element's row

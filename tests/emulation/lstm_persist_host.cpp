@@ -75,4 +75,57 @@ int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot)
         }
     return wrong;
 }
+
+// The tasks that every wavefront waits for against those whose results it reads: how many wavefronts differ, -1: no such launch.
+int emu_watch(int T, int B, int h, int r, int G, int L, int bwd)
+{
+    const LstmGeom g = {T, B, h, r, G, G * r, L};
+    const LpPlan p = lp_plan(g, bwd, 256);
+    if (p.NT == 0) return -1;
+    std::vector<LstmRunLayer> l(LP_MAX_LAYERS);
+    LpArgs a;
+    lp_fill(a, p, g, l.data(), nullptr, nullptr);
+    const int U = bwd || G != 1 ? 16 * (G != 1 ? 1 : p.NT) : 4 * p.NT, TW = bwd && G == 1 ? 16 : 8;
+    const int cols = bwd ? a.rp : G * a.rp, blocks = !bwd ? 1 : G != 1 ? 4 : p.SL;
+    auto units = [&](int wg) { return lp_units(a, wg, bwd ? a.n1 : a.n2, U); };
+    auto columns = [&](int wg) { return lp_columns(a, wg, bwd ? a.n2 : a.n1, cols, TW, blocks); };
+    int wrong = 0;
+    for (int wg = 0; wg < p.nwg; ++wg)
+        for (int w = 0; w < LP_WAVES; ++w)
+            for (int phase = 0; phase < 2; ++phase) {
+                const LpUnits z = units(wg);
+                const LpColumns c = columns(wg);
+                const bool from_units = (phase == 0) == (bwd == 0); // what is read was written by tasks of units
+                const LpShare s = from_units ? (bwd ? lp_bwd_share2(a, c, w, p.SL, U) : lp_fwd_share1(a, c, w, U))
+                                             : (bwd ? lp_bwd_share1(a, z, w, p.SL) : lp_fwd_share2(a, z, w));
+                std::vector<int> want(256), got(256);
+                if (s.waits) {
+                    for (int i = 0; i < 64; ++i) {
+                        const int t = s.on.task(i);
+                        if (t < 0 || t >= 256) return 1 << 20;
+                        got[t] = 1;
+                    }
+                    if (s.on.n * s.on.blocks > 64) ++wrong;
+                }
+                const int k0 = 32 * s.first, k1 = k0 + 32 * (s.n > 0 ? s.n : 0);
+                for (int v = 0; v < p.nwg && s.n > 0; ++v) {
+                    if (from_units) {
+                        const LpUnits y = units(v);
+                        const int layer = !bwd && c.path ? c.l - 1 : c.l;
+                        for (int k = k0; k < k1 && y.has && y.l == layer; ++k)
+                            if (k % a.hp >= y.u0 && k % a.hp < y.u0 + y.n) want[y.task] = 1;
+                    } else {
+                        const LpColumns y = columns(v);
+                        const bool above = bwd ? z.l + 1 < L && w >= 4 : w >= 4;
+                        if (!bwd && above && z.l == 0) continue; // (computed beforehand)
+                        for (int k = k0; k < k1 && y.has && y.path == (above ? 1 : 0) && y.l == z.l + (bwd && above); ++k) {
+                            const int col = bwd ? k % a.rp : k, gate = bwd && G != 1 ? k / a.rp : -1;
+                            if (col >= y.col && col < y.col + y.n && (gate < 0 || gate == y.q)) want[y.task] = 1;
+                        }
+                    }
+                }
+                if (s.n > 0 && want != got) ++wrong;
+            }
+    return wrong;
+}
 }

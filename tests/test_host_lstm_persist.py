@@ -49,3 +49,18 @@ def test_workgroups_that_give_up_leave_nan(emu, T, B, h, r, groups, layers, bwd)
     they wrote before stays."""
     for slot in {0, 1, layers, T - 1, T + layers - 2}:
         assert emu.emu_void(T, B, h, r, groups, layers, bwd, slot) == 0, slot
+
+
+@pytest.mark.parametrize("groups", [1, 4])
+@pytest.mark.parametrize("bwd", [0, 1])
+def test_wavefronts_wait_for_what_they_read(emu, groups, bwd):
+    """The flags that a wavefront polls are those of the tasks that write its part of the exchanged matrix, over all widths."""
+    ran = 0
+    for h in [4, 33, 96, 130, 260, 500, 777, 1216, 1500, 1536]:
+        for B in (1, 12, 20, 32):
+            for layers in (1, 2, 3):
+                for r in {h // 4, min(h, 33), min(h, 384)}:
+                    wrong = emu.emu_watch(3, B, h, r, groups, layers, bwd)
+                    assert wrong <= 0, (h, B, layers, r)
+                    ran += wrong == 0
+    assert ran > 30
