@@ -4,7 +4,7 @@
 // The SVD (pf_svd.hip) uses the result as a preconditioner only: it is made orthonormal there, rejected where it is not nearly so
 // already (clusters of eigenvalues), and what it leaves of the columns' inner products is checked and taken out.  One-sided Jacobi,
 // which does the same for any matrix, needs eight sweeps of n / 8 - 1 rounds with a grid barrier each.  At n = 512: 9.8 ms there;
-// here 1.07 ms for the reduction (2.1 us a step), 0.17 for the eigenvectors of T, 0.12 for the reflectors.
+// here 0.95 ms for the reduction, 0.17 for the eigenvectors of T, 0.12 for the reflectors.
 #include "pf_svd_eigen.h"
 
 #include <type_traits>
@@ -29,14 +29,24 @@ __device__ __forceinline__ double lane_value(double x, int lane)
     const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane), hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
     return __longlong_as_double((u64)hi << 32 | lo);
 }
-// the sum over the 64 lanes, in all of them: neighbours, pairs, the mirrored halves of eight and sixteen, then the four rows
+// the sum over the 64 lanes, in all of them: neighbours, pairs, the mirrored halves of eight and sixteen; then the rows of 16 change
+// places in pairs, and the halves (the four rows by readlane and scalar operands: the
+// tail below 138 us, 134 so)
 __device__ __forceinline__ double wave_sum(double x)
 {
     x = dpp_plus<0xB1>(x);
     x = dpp_plus<0x4E>(x);
     x = dpp_plus<0x141>(x);
     x = dpp_plus<0x140>(x);
-    return (lane_value(x, 0) + lane_value(x, 16)) + (lane_value(x, 32) + lane_value(x, 48));
+    const auto swapped_plus = [](auto lo, auto hi) {
+        return __longlong_as_double((u64)hi[0] << 32 | lo[0]) + __longlong_as_double((u64)hi[1] << 32 | lo[1]);
+    };
+    u64 b = __double_as_longlong(x);
+    x = swapped_plus(__builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false),
+                     __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
+    b = __double_as_longlong(x);
+    return swapped_plus(__builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false),
+                        __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
 }
 
 // 1 / q and 1 / sqrt(q) of any normal double: the hardware's approximation (at least 2^-23) and two Newton steps
@@ -110,17 +120,19 @@ __device__ __forceinline__ double group_sum(double x, double *red)
 // L[k][k + 1], tau to tau[k].
 // The chain of an exchange, two sums and a square root per step is what it takes, so a workgroup is one wavefront where the
 // matrix allows it: everything but its columns' own elements of the vectors (LDS) stays in the lanes that need it, and nothing
-// waits for a barrier (n = 512, us: 1070; two wavefronts 1280, four 1290, eight 1615; two columns a wavefront 1180, eight 1390).
+// waits for a barrier (n = 512 to the last column, us: 1070; two wavefronts 1280, four 1290, eight 1615; two columns a wavefront 1180, eight 1390).
 // NT > 64: the vectors are formed row tid + NT m per thread and handed to the wavefronts through LDS.
+// The last SVD_TAIL columns are left to svd_tridiag_tail_kernel: what they are by then goes back to G.
 // A wait is bounded; when it runs out, everyone leaves and ctrl->failed says so.
+constexpr int SVD_TAIL = 128;
 template <int RPT, int CPW, int NT>
-__global__ __launch_bounds__(NT) void svd_tridiag_kernel(const double *G, double *L, double *tau_out, u64 *slots, SvdCtrl *ctrl, int n, int ld)
+__global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, double *tau_out, u64 *slots, SvdCtrl *ctrl, int n, int ld)
 {
     constexpr int ROWS = 64 * RPT, NW = NT / 64, RV = (ROWS + NT - 1) / NT;
     __shared__ double xs[ROWS], ws[ROWS], red1[NW], red2[NW];
     __shared__ int gave_up;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = blockIdx.x, nwg = gridDim.x;
-    u64 *P = slots, *C = slots + (i64)n * ld;
+    u64 *P = slots, *C = slots + (i64)(n - SVD_TAIL) * ld;
     const auto column = [&](int j) { return (j * NW + wave) * nwg + g; };
     double a[CPW][RPT], vr[RPT], vc[CPW]; // the columns; v at this lane's rows and at this wavefront's columns
 #pragma unroll
@@ -129,9 +141,14 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(const double *G, double
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
             const int c = column(j), r = lane + 64 * i;
-            a[j][i] = c < n && r < n ? G[(i64)c * ld + r] : 0.0;
+            a[j][i] = G[(i64)min(c, n - 1) * ld + min(r, n - 1)];
         }
     }
+    __builtin_amdgcn_sched_barrier(0); // (a select on each load would become a branch around it, and every load a wait of its own)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j)
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) a[j][i] = column(j) < n && lane + 64 * i < n ? a[j][i] : 0.0;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) vr[i] = 0.0;
     double x[RV], w[RV], v[RV];
@@ -259,13 +276,166 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(const double *G, double
         }
     };
     constexpr int STEP = RPT <= 8 ? 1 : RPT / 2;
+    const int end = n - SVD_TAIL;
     static_for<0, RPT, STEP>([&](auto i0) {
         constexpr int I0 = decltype(i0)::value;
-        if (!left) run(i0, 64 * I0, min(64 * (I0 + STEP), n - 1));
+        if (!left) run(i0, 64 * I0, min(64 * (I0 + STEP), end));
     });
     __syncthreads();
     if (left || gave_up) return;
-    if (g == 0 && tid == 0) L[(i64)(n - 1) * ld + n - 1] = xs[n - 1];
+    // the last step's update and what is left (nobody reads G any more but its owner)
+#pragma unroll
+    for (int j = 0; j < CPW; ++j) {
+        const int c = column(j);
+        if (c >= end && c < n) {
+            const double wc = ws[c];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                const int r = lane + 64 * i;
+                if (r >= end && r < n) G[(i64)c * ld + r] = fma(-ws[r], vc[j], fma(-vr[i], wc, a[j][i]));
+            }
+        }
+    }
+}
+
+// The same reduction of a matrix of at most SVD_TAIL columns, the last of G's, by one workgroup of four wavefronts, one per SIMD:
+// nothing leaves the compute unit, a step has one barrier.  Row 32 q + 4 (lane / 8) + wavefront of the matrix, which stands at the
+// end of 128 x 128, is held by eight lanes, 16 columns each; so a product's sum is one over eight lanes, an operand read from LDS
+// serves four rows, and what is done falls away in quarters.  The vectors (elements lane and lane + 64) every wavefront forms for
+// itself, with the same arithmetic.
+// A step takes 0.95 us where it takes 2.1 between compute units, 1.75 at the end: n = 512 1072 -> 829 + 121 us, n = 128 224 -> 121 (eight
+// wavefronts 134; each q by itself, its sums in a row: 130).
+// The chain of a step: x to LDS and back into the lanes' columns, update and product, their sums to LDS, the barrier, v.p, the
+// next x.  The product is with x, not v = (e + x / (alpha - beta)), so the norm, a square root and a reciprocal run beside it; row and
+// column k + 1, where v is 1, are used for the last time in step k and not updated.
+template <int Q0>
+__device__ __forceinline__ void tridiag_tail_steps(double (&a)[4][16], double (&x)[2], double &sq, double *X, double *W, double (*P)[SVD_TAIL],
+                                                   double (*R)[SVD_TAIL], double *L, double *tau_out, int k0, int k1, int base, int n, int ld)
+{
+    constexpr int J0 = 2 * Q0; // columns from 16 J0 on
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ri = lane >> 3, cb = lane & 7;
+    const auto columns = [&](const double *from, double (&to)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = J0; j < 8; ++j) {
+            const double2 t = *(const double2 *)(from + 16 * j + 2 * cb);
+            to[2 * j] = t.x, to[2 * j + 1] = t.y;
+        }
+    };
+    double xc[16], xi[4]; // x below row k + 1, zeros above, at this lane's columns and rows
+    columns(X, xc);
+#pragma unroll
+    for (int q = Q0; q < 4; ++q) xi[q] = X[32 * q + 4 * ri + wave];
+    for (int k = k0; k < k1; ++k) {
+        double *p = P[k & 1], *row = R[k & 1];
+        double dot[4] = {};
+#pragma unroll
+        for (int j = 2 * J0; j < 16; ++j)
+#pragma unroll
+            for (int q = Q0; q < 4; ++q) dot[q] = fma(a[q][j], xc[j], dot[q]);
+#pragma unroll
+        for (int q = Q0; q < 4; ++q) dot[q] = dpp_plus<0xB1>(dot[q]);
+#pragma unroll
+        for (int q = Q0; q < 4; ++q) dot[q] = dpp_plus<0x4E>(dot[q]);
+#pragma unroll
+        for (int q = Q0; q < 4; ++q) dot[q] = dpp_plus<0x141>(dot[q]);
+        const double rest = wave_sum(sq), alpha = lane_value(k + 1 < 64 ? x[0] : x[1], (k + 1) & 63);
+        double tau = 0.0, beta = alpha, inv = 0.0;
+        if (!(rest == 0.0)) {
+            const double q = fma(alpha, alpha, rest), y = rsqrt_any(q), len = q * y;
+            beta = alpha < 0.0 ? len : -len;
+            tau = fma(fabs(alpha), y, 1.0);
+            inv = rcp_any(alpha - beta);
+        }
+        if (cb == 0) {
+#pragma unroll
+            for (int q = Q0; q < 4; ++q) p[32 * q + 4 * ri + wave] = dot[q];
+        }
+        if (32 * Q0 + 4 * ri + wave == k + 1) { // (row k + 1: steps k of this Q0 have it among the first 32 that are left)
+#pragma unroll
+            for (int j = J0; j < 8; ++j) *(double2 *)(row + 16 * j + 2 * cb) = make_double2(a[Q0][2 * j], a[Q0][2 * j + 1]);
+        }
+        double v[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int t = lane + 64 * m;
+            v[m] = t > k + 1 ? x[m] * inv : t == k + 1 ? 1.0 : 0.0;
+            if (wave == 0 && t >= k) L[(i64)(base + k) * ld + base + t] = t > k + 1 ? v[m] : t == k + 1 ? beta : x[m];
+        }
+        if (threadIdx.x == 0) tau_out[base + k] = tau;
+        __syncthreads(); // (the next step writes the other of P and R)
+        double pv[2], sum = 0.0;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int t = lane + 64 * m;
+            x[m] = t > k ? row[t] : 0.0;
+            pv[m] = t > k ? fma(inv, p[t], x[m]) : 0.0;
+            sum = fma(pv[m], v[m], sum);
+        }
+        const double b1 = lane_value(k + 1 < 64 ? pv[0] : pv[1], (k + 1) & 63);
+        sum = wave_sum(sum);
+        const double h = 0.5 * tau * tau * sum, w1 = fma(tau, b1, -h);
+        sq = 0.0;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int t = lane + 64 * m;
+            const double w = t > k ? fma(tau, pv[m], -h * v[m]) : 0.0;
+            x[m] = t > k ? fma(-v[m], w1, x[m]) - w : 0.0;
+            W[t] = w;
+            X[t] = t > k + 2 ? x[m] : 0.0;
+            if (t > k + 2) sq = fma(x[m], x[m], sq);
+        }
+        wave_sync();
+        double wc[16];
+        columns(W, wc);
+#pragma unroll
+        for (int q = Q0; q < 4; ++q) {
+            const int i = 32 * q + 4 * ri + wave;
+            const double wv = -W[i] * inv, xv = -xi[q] * inv;
+#pragma unroll
+            for (int j = 2 * J0; j < 16; ++j) a[q][j] = fma(wv, xc[j], fma(xv, wc[j], a[q][j]));
+            xi[q] = X[i];
+        }
+        columns(X, xc);
+        wave_sync(); // (they have been read)
+    }
+}
+__global__ __launch_bounds__(256) void svd_tridiag_tail_kernel(const double *G, double *L, double *tau_out, int n, int ld)
+{
+    __shared__ __attribute__((aligned(16))) double X[4][SVD_TAIL], W[4][SVD_TAIL], P[2][SVD_TAIL], R[2][SVD_TAIL];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ri = lane >> 3, cb = lane & 7;
+    const int base = n - SVD_TAIL, first = max(-base, 0); // place t of the 128 is row (and column) base + t of G, first .. 127 exist
+    double a[4][16], x[2], sq = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int r = 32 * q + 4 * ri + wave, c = 16 * (j >> 1) + 2 * cb + (j & 1); // (the matrix is symmetric: lanes read along it)
+            a[q][j] = G[(i64)(base + max(r, first)) * ld + base + max(c, first)];
+        }
+    __builtin_amdgcn_sched_barrier(0); // (a select on each load would become a branch around it, and every load a wait of its own)
+    if (first > 0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int r = 32 * q + 4 * ri + wave, c = 16 * (j >> 1) + 2 * cb + (j & 1);
+                a[q][j] = r >= first && c >= first ? a[q][j] : 0.0;
+            }
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int t = lane + 64 * m;
+        const double y = G[(i64)(base + first) * ld + base + max(t, first)];
+        x[m] = t >= first ? y : 0.0;
+        X[wave][t] = t > first + 1 ? y : 0.0;
+        if (t > first + 1) sq = fma(y, y, sq);
+    }
+    wave_sync();
+    static_for<0, 4, 1>([&](auto q0) {
+        constexpr int Q0 = decltype(q0)::value;
+        tridiag_tail_steps<Q0>(a, x, sq, X[wave], W[wave], P, R, L, tau_out, max(first, 32 * Q0 - 1), min(32 * Q0 + 31, SVD_TAIL - 1), base, n, ld);
+    });
+    if (threadIdx.x == 63) L[(i64)(n - 1) * ld + n - 1] = x[1];
 }
 
 // The reflectors made whole (zeros above, the 1 at row k + 1), T's diagonal and subdiagonal to T[0 .. n) and T[n .. 2 n): the
@@ -518,11 +688,14 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     int st = PF_OK;
     u64 *slots = (u64 *)X;
     double *T = G; // (free once it is tridiagonal; 2 n <= n ld)
-    const i64 words = 2 * (i64)n * ld;
-    const i64 blocks = (words + 1023) / 1024;
-    PF_LAUNCH(st, "svd_slots", svd_slots_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), s, slots, words);
-    if (st == PF_OK)
-        st = launch_cooperative(s, "svd_tridiag", svd_tridiag_kernel<RPT, CPW, NT>, (n + NT / 64 * CPW - 1) / (NT / 64 * CPW), NT, (const double *)G, L, tau, slots, ctrl, n, ld);
+    if constexpr (64 * RPT > SVD_TAIL) {
+        const i64 words = 2 * (i64)(n - SVD_TAIL) * ld; // P's rows and C's, one per step
+        const i64 blocks = (words + 1023) / 1024;
+        PF_LAUNCH(st, "svd_slots", svd_slots_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), s, slots, words);
+        if (st == PF_OK)
+            st = launch_cooperative(s, "svd_tridiag", svd_tridiag_kernel<RPT, CPW, NT>, (n + NT / 64 * CPW - 1) / (NT / 64 * CPW), NT, G, L, tau, slots, ctrl, n, ld);
+    }
+    PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, (const double *)G, L, tau, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1; // what 64 KB of LDS hold
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
