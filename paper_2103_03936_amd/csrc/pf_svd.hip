@@ -56,16 +56,13 @@ __global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *A
 }
 
 // Lane l of a wavefront holds column c0 + l % 16 of a column-major matrix at rows r0 + 2 (l / 16) + {0, 1}: fragments of
-// two 16x16x4 MFMAs, for the left and for the right operand alike.  Columns >= nc and rows >= nr read as zero.
+// two 16x16x4 MFMAs, for the left and for the right operand alike.  Past the last column or row a neighbour is read, and
+// svd_masked makes it zero when it is used: a select on the load itself becomes a branch around it, with a wait of its own.
 __device__ __forceinline__ f64x2_t svd_frag(const double *M, int ld, int col, int nc, int row, int nr)
 {
-    f64x2_t v = {0.0, 0.0};
-    if (col < nc && row < nr) {
-        v = *(const f64x2_t *)(M + (i64)col * ld + row);
-        if (row + 1 >= nr) v[1] = 0.0;
-    }
-    return v;
+    return *(const f64x2_t *)(M + (i64)min(col, nc - 1) * ld + min(row, (nr - 1) & ~1));
 }
+__device__ __forceinline__ double svd_masked(double v, bool in) { return in ? v : 0.0; }
 
 // Sum over the four wavefronts of a workgroup of a 32 x 32 tile: each has it as 2 x 2 MFMA tiles over its share of the contraction.
 // put(i, j, sum) for the elements of thread tid.
@@ -89,8 +86,9 @@ __device__ __forceinline__ void svd_tile_out(const f64x4_t (&acc)[2][2], double 
 constexpr int SVD_U = 4; // pieces of eight contraction indices that a wavefront has in flight
 
 // C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows, and SVD_U pieces are
-// requested together: a piece takes about a microsecond to arrive, its MFMAs 32 clocks each (2048 x 512: 88 us with one at a
-// time).  unless (nullable): nothing is done when it is 0.
+// requested while the SVD_U before are multiplied: a piece takes about a microsecond to arrive, its MFMAs 64 clocks each (2048 x 512:
+// 88 us with one at a time, 64 with SVD_U and a wait before they are multiplied, 36 so; the product of the two below 58 -> 38
+// us).  unless (nullable): nothing is done when it is 0.
 __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *unless)
 {
     if (unless && *unless == 0u) return;
@@ -104,24 +102,43 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
-    for (int r = 8 * SVD_U * wave; r < nr; r += 32 * SVD_U) {
+    struct Pieces {
         f64x2_t x[SVD_U][2], y[SVD_U][2];
+    };
+    const auto fetch = [&](Pieces &p, int r) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < SVD_U; ++u)
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
-                x[u][a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
-                y[u][a] = svd_frag(M, ld, 32 * tj + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
+                p.x[u][a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
+                p.y[u][a] = svd_frag(M, ld, 32 * tj + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
             }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto multiply = [&](const Pieces &p, int r) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < SVD_U; ++u)
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
+            for (int e = 0; e < 2; ++e) {
+                const bool in = r + 8 * u + 2 * g + e < nr; // (columns past the last give sums that nobody stores)
+                double x[2], y[2];
+#pragma unroll
+                for (int a = 0; a < 2; ++a) x[a] = svd_masked(p.x[u][a][e], in), y[a] = svd_masked(p.y[u][a][e], in);
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[u][a][e], y[u][b][e], acc[a][b], 0, 0, 0);
+                    for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a], y[b], acc[a][b], 0, 0, 0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int STEP = 32 * SVD_U;
+    Pieces p0, p1;
+    fetch(p0, 8 * SVD_U * wave);
+    for (int r = 8 * SVD_U * wave; r < nr; r += 2 * STEP) {
+        fetch(p1, r + STEP);
+        multiply(p0, r);
+        fetch(p0, r + 2 * STEP);
+        multiply(p1, r + STEP);
     }
     __shared__ double part[4][32][33];
     svd_tile_out(acc, part, [&](int i, int j, double s) {
@@ -210,40 +227,58 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
     }
-    for (int k = 8 * SVD_U * wave; k < nc; k += 32 * SVD_U) {
+    struct Pieces {
         f64x2_t x[SVD_U][2], y[SVD_U][2], gk[SVD_U];
+    };
+    const auto fetch = [&](Pieces &p, int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < SVD_U; ++u) {
             const int kk = k + 8 * u + 2 * g;
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
-                const int row = i0 + 16 * a + c;
-                x[u][a] = svd_frag(right, ldr, j0 + 16 * a + c, nc, kk, nc);
+                const int row = min(i0 + 16 * a + c, nr - 1);
+                p.x[u][a] = svd_frag(right, ldr, j0 + 16 * a + c, nc, kk, nc);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    y[u][a][e] = row < nr && kk + e < nc ? left[(i64)(kk + e) * ld + row] : 0.0;
-                    if (MODE == SVD_CORRECT) gk[u][e] = kk + e < nc ? right[(i64)(kk + e) * (ldr + 1)] : 1.0;
-                }
+                for (int e = 0; e < 2; ++e) p.y[u][a][e] = left[(i64)min(kk + e, nc - 1) * ld + row];
             }
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                if (MODE == SVD_CORRECT) p.gk[u][e] = right[(i64)min(kk + e, nc - 1) * (ldr + 1)];
         }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto multiply = [&](const Pieces &p, int k) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < SVD_U; ++u)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int kk = k + 8 * u + 2 * g + e;
-                double w[2];
+                const bool in = kk < nc; // (columns and rows past the last give sums that nobody stores)
+                double w[2], y[2];
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
                     const int j = j0 + 16 * a + c;
-                    w[a] = x[u][a][e];
+                    w[a] = p.x[u][a][e];
                     if (MODE == SVD_NEWTON) w[a] = (j == kk ? 1.5 : 0.0) - 0.5 * w[a];
-                    if (MODE == SVD_CORRECT) w[a] = j == kk ? 0.0 : svd_small_rotation(gk[u][e], gj[a], w[a], tol * tol);
+                    if (MODE == SVD_CORRECT) w[a] = j == kk ? 0.0 : svd_small_rotation(p.gk[u][e], gj[a], w[a], tol * tol);
+                    w[a] = svd_masked(w[a], in);
+                    y[a] = svd_masked(p.y[u][a][e], in);
                 }
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[a], y[u][b][e], acc[a][b], 0, 0, 0);
+                    for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[a], y[b], acc[a][b], 0, 0, 0);
             }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr int STEP = 32 * SVD_U;
+    Pieces p0, p1;
+    fetch(p0, 8 * SVD_U * wave);
+    for (int k = 8 * SVD_U * wave; k < nc; k += 2 * STEP) {
+        fetch(p1, k + STEP);
+        multiply(p0, k);
+        fetch(p0, k + 2 * STEP);
+        multiply(p1, k + STEP);
     }
     __shared__ double part[4][32][33];
     svd_tile_out(acc, part, [&](int jj, int ii, double s) {
@@ -399,11 +434,15 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
         f64x2_t y[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) y[u] = svd_frag(M, ld, col, nc, r + 8 * NW * u + 2 * g, nr);
+        __builtin_amdgcn_sched_barrier(0);
         if (r < 8 * NW) fetch(tid);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u][0], y[u][0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(y[u][1], y[u][1], acc, 0, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const double v = svd_masked(y[u][e], col < nc && r + 8 * NW * u + 2 * g + e < nr);
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+            }
         }
     }
     if (8 * wave >= nr) fetch(tid); // (fewer rows than wavefronts)
