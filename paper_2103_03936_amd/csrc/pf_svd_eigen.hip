@@ -612,7 +612,8 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
 // A wavefront applies all reflectors to CB of Z's columns, kept in registers, two at a time:
 //   H1 H2 z = z - tau2 d2 v2 - tau1 (d1 - tau2 d2 v1.v2) v1,  d = v.z
 // so a pair costs the chain one sum over the wavefront.  The next DEPTH pairs are on their way meanwhile (one reflector at a time and
-// one ahead: 298 us at 512, now 122; bound by the instructions of the sums, with one wavefront on every other SIMD).
+// one ahead: 298 us at 512; two, all rows read 121; without the rows where both are zero, in blocks of 64: 104; two wavefronts a
+// workgroup instead of four, which read the same reflectors together: 138).
 template <int RPT, int CB, int DEPTH>
 __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const double *tau, double *X, int n, int ld)
 {
@@ -622,12 +623,12 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
     // pair q: reflectors last - 2 q (first to be applied) and the one before it; where there is none, a factor of zero.  Rows past
     // the last are read from it, and z is zero there.
     const int last = n - 3, pairs = (n - 1) / 2;
-    const auto fetch = [&](int q, int d) {
+    const auto fetch = [&](auto i0, int q, int d) {
         const int kb = max(last - 2 * q, 0), ka = max(kb - 1, 0);
         t1[d] = tau[ka];
         t2[d] = tau[kb];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
+        for (int i = decltype(i0)::value; i < RPT; ++i) {
             const int r = min(lane + 64 * i, n - 1);
             v1[d][i] = L[(i64)ka * ld + r];
             v2[d][i] = L[(i64)kb * ld + r];
@@ -641,38 +642,52 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
             const int r = lane + 64 * i;
             z[b][i] = r < n && j0 + b < n ? X[(i64)(j0 + b) * ld + r] : 0.0;
         }
+    // pairs [q0, end), whose vectors are zero above row 64 I0: those rows are not read
+    const auto apply = [&](auto i0, int q0, int end) {
+        constexpr int I0 = decltype(i0)::value;
+        if (q0 >= end) return;
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d) fetch(d, d);
-    for (int q0 = 0; q0 < pairs; q0 += DEPTH) {
+        for (int d = 0; d < DEPTH; ++d) fetch(i0, q0 + d, d);
+        for (; q0 < end; q0 += DEPTH) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int kb = last - 2 * (q0 + d);
-            double d1[CB], d2[CB], cross = 0.0;
+            for (int d = 0; d < DEPTH; ++d) {
+                const int kb = last - 2 * (q0 + d);
+                double d1[CB], d2[CB], cross = 0.0;
 #pragma unroll
-            for (int b = 0; b < CB; ++b) d1[b] = d2[b] = 0.0;
+                for (int b = 0; b < CB; ++b) d1[b] = d2[b] = 0.0;
 #pragma unroll
-            for (int i = 0; i < RPT; ++i) {
-                cross = fma(v1[d][i], lane + 64 * i < n ? v2[d][i] : 0.0, cross);
+                for (int i = I0; i < RPT; ++i) {
+                    cross = fma(v1[d][i], lane + 64 * i < n ? v2[d][i] : 0.0, cross);
+#pragma unroll
+                    for (int b = 0; b < CB; ++b) {
+                        d1[b] = fma(v1[d][i], z[b][i], d1[b]);
+                        d2[b] = fma(v2[d][i], z[b][i], d2[b]);
+                    }
+                }
+                const bool in = q0 + d < end;
+                const double tau1 = in && kb > 0 ? t1[d] : 0.0, tau2 = in && kb >= 0 ? t2[d] : 0.0;
+                cross = wave_sum(cross);
 #pragma unroll
                 for (int b = 0; b < CB; ++b) {
-                    d1[b] = fma(v1[d][i], z[b][i], d1[b]);
-                    d2[b] = fma(v2[d][i], z[b][i], d2[b]);
+                    d2[b] = -tau2 * wave_sum(d2[b]);
+                    d1[b] = -tau1 * fma(d2[b], cross, wave_sum(d1[b]));
                 }
+#pragma unroll
+                for (int b = 0; b < CB; ++b)
+#pragma unroll
+                    for (int i = I0; i < RPT; ++i) z[b][i] = lane + 64 * i < n ? fma(d1[b], v1[d][i], fma(d2[b], v2[d][i], z[b][i])) : 0.0;
+                fetch(i0, q0 + DEPTH + d, d);
             }
-            const double tau1 = kb > 0 ? t1[d] : 0.0, tau2 = kb >= 0 ? t2[d] : 0.0;
-            cross = wave_sum(cross);
-#pragma unroll
-            for (int b = 0; b < CB; ++b) {
-                d2[b] = -tau2 * wave_sum(d2[b]);
-                d1[b] = -tau1 * fma(d2[b], cross, wave_sum(d1[b]));
-            }
-#pragma unroll
-            for (int b = 0; b < CB; ++b)
-#pragma unroll
-                for (int i = 0; i < RPT; ++i) z[b][i] = lane + 64 * i < n ? fma(d1[b], v1[d][i], fma(d2[b], v2[d][i], z[b][i])) : 0.0;
-            fetch(q0 + DEPTH + d, d);
         }
-    }
+    };
+    constexpr int STEP = RPT <= 8 ? 1 : RPT / 2;
+    int q0 = 0;
+    static_for<0, RPT, STEP>([&](auto i) {
+        constexpr int I0 = RPT - STEP - decltype(i)::value;
+        const int end = I0 == 0 ? pairs : last >= 64 * I0 ? (last - 64 * I0) / 2 + 1 : 0;
+        apply(std::integral_constant<int, I0>{}, q0, end);
+        q0 = max(q0, end);
+    });
 #pragma unroll
     for (int b = 0; b < CB; ++b)
 #pragma unroll
@@ -697,7 +712,8 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     }
     PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, (const double *)G, L, tau, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);
-    const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1; // what 64 KB of LDS hold
+    // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 151 us), else what 64 KB of LDS hold
+    const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 512 ? 2 : np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1;
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
                   (size_t)(2 * (np + 2 * SVD_CHUNK) + 2 * waves * (np + SVD_CHUNK)) * 8, s, (const double *)T, X, n, ld);
     PF_LAUNCH(st, "svd_reflect", (svd_reflect_kernel<RPT, CB, DEPTH>), dim3((n + 4 * CB - 1) / (4 * CB)), dim3(256), s, (const double *)L,
