@@ -167,8 +167,11 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
     const auto run = [&](auto i0, int k0, int k1) {
         constexpr int I0 = decltype(i0)::value, M0 = 64 * I0 / NT;
         for (int k = k0; k < k1; ++k) {
-            const double rest = group_sum<NT>(sq, red2); // (also: what the last step left in LDS is there)
-            if constexpr (NT == 64) wave_sync();
+            double rest;
+            if constexpr (NT > 64)
+                rest = group_sum<NT>(sq, red2); // (also: what the last step left in LDS is there)
+            else
+                wave_sync();
             const double alpha = xs[k + 1];
             double xc[CPW], wc[CPW];
 #pragma unroll
@@ -196,7 +199,26 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
                     }
                 }
             }
+            // the products with x below row k + 1
+            double dot[CPW];
+#pragma unroll
+            for (int i = I0; i < RPT; ++i) xr[i] = lane + 64 * i > k + 1 ? xr[i] : 0.0;
+#pragma unroll
+            for (int j = 0; j < CPW; ++j) {
+                dot[j] = 0.0;
+#pragma unroll
+                for (int i = I0; i < RPT; ++i) dot[j] = fma(a[j][i], xr[i], dot[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < CPW; ++j) dot[j] = wave_sum(dot[j]);
+#pragma unroll
+            for (int j = 0; j < CPW; ++j) {
+                const int c = column(j);
+                if (lane == j && c > k && c < n) slot_put(P + (i64)k * ld + c, dot[j]);
+            }
+            asm volatile("" ::: "memory"); // (everything is on its way before anyone waits)
             // this step's v
+            if constexpr (NT == 64) rest = wave_sum(sq);
             double tau = 0.0, beta = alpha, inv = 0.0;
             if (!(rest == 0.0)) {
                 const double q = fma(alpha, alpha, rest), y = rsqrt_any(q), len = q * y;
@@ -207,25 +229,13 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
 #pragma unroll
             for (int i = I0; i < RPT; ++i) {
                 const int r = lane + 64 * i;
-                vr[i] = r > k + 1 ? xr[i] * inv : r == k + 1 ? 1.0 : 0.0;
+                vr[i] = r == k + 1 ? 1.0 : xr[i] * inv;
             }
-            double dot[CPW];
 #pragma unroll
             for (int j = 0; j < CPW; ++j) {
                 const int c = column(j);
                 vc[j] = c > k + 1 ? xc[j] * inv : c == k + 1 ? 1.0 : 0.0;
-                dot[j] = 0.0;
-#pragma unroll
-                for (int i = I0; i < RPT; ++i) dot[j] = fma(a[j][i], vr[i], dot[j]);
             }
-#pragma unroll
-            for (int j = 0; j < CPW; ++j) dot[j] = wave_sum(dot[j]);
-#pragma unroll
-            for (int j = 0; j < CPW; ++j) {
-                const int c = column(j);
-                if (lane == j && c > k && c < n) slot_put(P + (i64)k * ld + c, dot[j]);
-            }
-            asm volatile("" ::: "memory"); // (everything is on its way before anyone waits)
 #pragma unroll
             for (int m = M0; m < RV; ++m) {
                 const int t = tid + NT * m;
@@ -236,11 +246,12 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
                 if (g == k % nwg && t >= k && t < n) L[(i64)k * ld + t] = t > k + 1 ? v[m] : t == k + 1 ? beta : x[m];
             }
             if (g == k % nwg && tid == 0) tau_out[k] = tau;
-            // p and the next column; row k + 1 of p for everyone
-            u64 bp[RV], bc[RV], b1;
+            // the products and the next column; row k + 1 of both for everyone
+            u64 bp[RV], bc[RV], b1, c1;
             for (int spin = 0;; ++spin) {
                 bool wait = false;
                 b1 = slot_get(P + (i64)k * ld + k + 1);
+                c1 = slot_get(C + (i64)k * ld + k + 1);
 #pragma unroll
                 for (int m = M0; m < RV; ++m) {
                     const int t = min(max(tid + NT * m, k + 1), n - 1); // (rows that nobody needs read a neighbour's slot)
@@ -249,7 +260,7 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
                 }
 #pragma unroll
                 for (int m = M0; m < RV; ++m) wait |= bp[m] == SLOT_EMPTY || bc[m] == SLOT_EMPTY;
-                if (!__any(wait || b1 == SLOT_EMPTY)) break;
+                if (!__any(wait || b1 == SLOT_EMPTY || c1 == SLOT_EMPTY)) break;
                 if (spin > 2000000 || ((spin & 255) == 255 && __hip_atomic_load(&ctrl->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
                     __hip_atomic_store(&ctrl->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     gave_up = 1;
@@ -257,18 +268,21 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
                     break;
                 }
             }
-            double s = 0.0;
+            double s = 0.0, p[RV]; // G v: with v = e + x inv, column k + 1 and the product
 #pragma unroll
-            for (int m = M0; m < RV; ++m) s = fma(__longlong_as_double(bp[m]), v[m], s);
+            for (int m = M0; m < RV; ++m) {
+                p[m] = fma(inv, __longlong_as_double(bp[m]), __longlong_as_double(bc[m]));
+                s = fma(p[m], v[m], s);
+            }
             s = group_sum<NT>(s, red1);
             if constexpr (NT > 64) left = gave_up != 0;
             if (left) return;
-            const double h = 0.5 * tau * tau * s, w1 = fma(tau, __longlong_as_double(b1), -h);
+            const double h = 0.5 * tau * tau * s, w1 = fma(tau, fma(inv, __longlong_as_double(b1), __longlong_as_double(c1)), -h);
             sq = 0.0;
 #pragma unroll
             for (int m = M0; m < RV; ++m) {
                 const int t = tid + NT * m;
-                w[m] = t > k && t < n ? fma(tau, __longlong_as_double(bp[m]), -h * v[m]) : 0.0;
+                w[m] = t > k && t < n ? fma(tau, p[m], -h * v[m]) : 0.0;
                 x[m] = t > k && t < n ? fma(-v[m], w1, __longlong_as_double(bc[m])) - w[m] : 0.0;
                 if (t < ROWS) ws[t] = w[m], xs[t] = x[m];
                 if (t > k + 2) sq = fma(x[m], x[m], sq);
