@@ -4,7 +4,7 @@
 // The SVD (pf_svd.hip) uses the result as a preconditioner only: it is made orthonormal there, rejected where it is not nearly so
 // already (clusters of eigenvalues), and what it leaves of the columns' inner products is checked and taken out.  One-sided Jacobi,
 // which does the same for any matrix, needs eight sweeps of n / 8 - 1 rounds with a grid barrier each.  At n = 512: 9.8 ms there;
-// here 0.95 ms for the reduction, 0.17 for the eigenvectors of T, 0.12 for the reflectors.
+// here 0.80 ms for the reduction, 0.15 for the eigenvectors of T, 0.09 for the reflectors.
 #include "pf_svd_eigen.h"
 
 #include <type_traits>
@@ -29,25 +29,43 @@ __device__ __forceinline__ double lane_value(double x, int lane)
     const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane), hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
     return __longlong_as_double((u64)hi << 32 | lo);
 }
-// the sum over the 64 lanes, in all of them: neighbours, pairs, the mirrored halves of eight and sixteen; then the rows of 16 change
-// places in pairs, and the halves (the four rows by readlane and scalar operands: the
-// tail below 138 us, 134 so)
-__device__ __forceinline__ double wave_sum(double x)
+// x + y after the upper half of x and the lower half of y, or x's odd rows of 16 and y's even ones, have changed places: half of
+// the lanes have a sum over two halves (rows) of x, the others of y
+__device__ __forceinline__ double halves_plus(double x, double y)
+{
+    const u64 a = __double_as_longlong(x), b = __double_as_longlong(y);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double((u64)hi[0] << 32 | lo[0]) + __longlong_as_double((u64)hi[1] << 32 | lo[1]);
+}
+__device__ __forceinline__ double rows_plus(double x, double y)
+{
+    const u64 a = __double_as_longlong(x), b = __double_as_longlong(y);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)a, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double((u64)hi[0] << 32 | lo[0]) + __longlong_as_double((u64)hi[1] << 32 | lo[1]);
+}
+// the sum over a row of 16 lanes, in all of them: neighbours, pairs, the mirrored halves of eight and sixteen
+__device__ __forceinline__ double row_sum(double x)
 {
     x = dpp_plus<0xB1>(x);
     x = dpp_plus<0x4E>(x);
     x = dpp_plus<0x141>(x);
-    x = dpp_plus<0x140>(x);
-    const auto swapped_plus = [](auto lo, auto hi) {
-        return __longlong_as_double((u64)hi[0] << 32 | lo[0]) + __longlong_as_double((u64)hi[1] << 32 | lo[1]);
-    };
-    u64 b = __double_as_longlong(x);
-    x = swapped_plus(__builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false),
-                     __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
-    b = __double_as_longlong(x);
-    return swapped_plus(__builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false),
-                        __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
+    return dpp_plus<0x140>(x);
 }
+// the sum over the 64 lanes, in all of them (the four rows by readlane and scalar operands: the tail below 138 us, 134 so)
+__device__ __forceinline__ double wave_sum(double x)
+{
+    x = row_sum(x);
+    x = rows_plus(x, x);
+    return halves_plus(x, x);
+}
+// four sums at once, with seven additions for 24: row q of the lanes has that of x[fold4_at(q)]
+__device__ __forceinline__ double fold4(double x0, double x1, double x2, double x3)
+{
+    return row_sum(rows_plus(halves_plus(x0, x1), halves_plus(x2, x3)));
+}
+__device__ __forceinline__ int fold4_at(int q) { return (q & 1) << 1 | q >> 1; }
 
 // 1 / q and 1 / sqrt(q) of any normal double: the hardware's approximation (at least 2^-23) and two Newton steps
 __device__ __forceinline__ double rcp_any(double q)
@@ -116,8 +134,9 @@ __device__ __forceinline__ double group_sum(double x, double *red)
 //   v from column k, p = G v, w = tau p - (tau^2 v.p / 2) v, G -= v w^T + w v^T
 // needs p and column k + 1 from the other workgroups and nothing else: from them everyone forms w, the next column and the next
 // v for itself, with the same arithmetic.  So a step is one exchange; column k + 1 as it was before the step goes out ahead of
-// the products.  v goes to column k of L (below row k + 1, where it is 1), T's diagonal and subdiagonal to L[k][k] and
-// L[k][k + 1], tau to tau[k].
+// the products, and those are G x, x the column below row k + 1: v = e + x / (alpha - beta) and G e is column k + 1, so what is
+// sent need not wait for the norm (829 -> 752 us); the products of a wavefront's four columns are summed together (-> 674).
+// v goes to column k of L (below row k + 1, where it is 1), T's diagonal and subdiagonal to L[k][k] and L[k][k + 1], tau to tau[k].
 // The chain of an exchange, two sums and a square root per step is what it takes, so a workgroup is one wavefront where the
 // matrix allows it: everything but its columns' own elements of the vectors (LDS) stays in the lanes that need it, and nothing
 // waits for a barrier (n = 512 to the last column, us: 1070; two wavefronts 1280, four 1290, eight 1615; two columns a wavefront 1180, eight 1390).
@@ -209,12 +228,18 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
 #pragma unroll
                 for (int i = I0; i < RPT; ++i) dot[j] = fma(a[j][i], xr[i], dot[j]);
             }
+            if constexpr (CPW == 4) {
+                const double sum = fold4(dot[0], dot[1], dot[2], dot[3]);
+                const int c = column(fold4_at(lane >> 4));
+                if ((lane & 15) == 0 && c > k && c < n) slot_put(P + (i64)k * ld + c, sum);
+            } else {
 #pragma unroll
-            for (int j = 0; j < CPW; ++j) dot[j] = wave_sum(dot[j]);
+                for (int j = 0; j < CPW; ++j) dot[j] = wave_sum(dot[j]);
 #pragma unroll
-            for (int j = 0; j < CPW; ++j) {
-                const int c = column(j);
-                if (lane == j && c > k && c < n) slot_put(P + (i64)k * ld + c, dot[j]);
+                for (int j = 0; j < CPW; ++j) {
+                    const int c = column(j);
+                    if (lane == j && c > k && c < n) slot_put(P + (i64)k * ld + c, dot[j]);
+                }
             }
             asm volatile("" ::: "memory"); // (everything is on its way before anyone waits)
             // this step's v
@@ -317,7 +342,7 @@ __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, d
 // end of 128 x 128, is held by eight lanes, 16 columns each; so a product's sum is one over eight lanes, an operand read from LDS
 // serves four rows, and what is done falls away in quarters.  The vectors (elements lane and lane + 64) every wavefront forms for
 // itself, with the same arithmetic.
-// A step takes 0.95 us where it takes 2.1 between compute units, 1.75 at the end: n = 512 1072 -> 829 + 121 us, n = 128 224 -> 121 (eight
+// A step takes 0.95 us where it takes 2.1 between compute units, 1.75 at the end: n = 512 1072 -> 829 + 121 us (the rest 674 by now), n = 128 224 -> 121 (eight
 // wavefronts 134; each q by itself, its sums in a row: 130).
 // The chain of a step: x to LDS and back into the lanes' columns, update and product, their sums to LDS, the barrier, v.p, the
 // next x.  The product is with x, not v = (e + x / (alpha - beta)), so the norm, a square root and a reciprocal run beside it; row and
@@ -623,17 +648,17 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
 }
 
 // ------------------------------------------------------------------ X = Q Z
-// A wavefront applies all reflectors to CB of Z's columns, kept in registers, two at a time:
+// A wavefront applies all reflectors to one of Z's columns, kept in registers, two at a time:
 //   H1 H2 z = z - tau2 d2 v2 - tau1 (d1 - tau2 d2 v1.v2) v1,  d = v.z
 // so a pair costs the chain one sum over the wavefront.  The next DEPTH pairs are on their way meanwhile (one reflector at a time and
-// one ahead: 298 us at 512; two, all rows read 121; without the rows where both are zero, in blocks of 64: 104; two wavefronts a
+// one ahead: 298 us at 512; two, all rows read 121; without the rows where both are zero, in blocks of 64: 104; three sums in one: 91; two wavefronts a
 // workgroup instead of four, which read the same reflectors together: 138).
-template <int RPT, int CB, int DEPTH>
+template <int RPT, int DEPTH>
 __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const double *tau, double *X, int n, int ld)
 {
-    const int lane = threadIdx.x & 63, j0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * CB;
-    if (j0 >= n) return;
-    double z[CB][RPT], v1[DEPTH][RPT], v2[DEPTH][RPT], t1[DEPTH], t2[DEPTH];
+    const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (j >= n) return;
+    double z[RPT], v1[DEPTH][RPT], v2[DEPTH][RPT], t1[DEPTH], t2[DEPTH];
     // pair q: reflectors last - 2 q (first to be applied) and the one before it; where there is none, a factor of zero.  Rows past
     // the last are read from it, and z is zero there.
     const int last = n - 3, pairs = (n - 1) / 2;
@@ -650,12 +675,9 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
         __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
-    for (int b = 0; b < CB; ++b)
+    for (int i = 0; i < RPT; ++i) z[i] = X[(i64)j * ld + min(lane + 64 * i, n - 1)];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const int r = lane + 64 * i;
-            z[b][i] = r < n && j0 + b < n ? X[(i64)(j0 + b) * ld + r] : 0.0;
-        }
+    for (int i = 0; i < RPT; ++i) z[i] = lane + 64 * i < n ? z[i] : 0.0;
     // pairs [q0, end), whose vectors are zero above row 64 I0: those rows are not read
     const auto apply = [&](auto i0, int q0, int end) {
         constexpr int I0 = decltype(i0)::value;
@@ -666,30 +688,20 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
 #pragma unroll
             for (int d = 0; d < DEPTH; ++d) {
                 const int kb = last - 2 * (q0 + d);
-                double d1[CB], d2[CB], cross = 0.0;
-#pragma unroll
-                for (int b = 0; b < CB; ++b) d1[b] = d2[b] = 0.0;
+                double d1 = 0.0, d2 = 0.0, cross = 0.0;
 #pragma unroll
                 for (int i = I0; i < RPT; ++i) {
                     cross = fma(v1[d][i], lane + 64 * i < n ? v2[d][i] : 0.0, cross);
-#pragma unroll
-                    for (int b = 0; b < CB; ++b) {
-                        d1[b] = fma(v1[d][i], z[b][i], d1[b]);
-                        d2[b] = fma(v2[d][i], z[b][i], d2[b]);
-                    }
+                    d1 = fma(v1[d][i], z[i], d1);
+                    d2 = fma(v2[d][i], z[i], d2);
                 }
                 const bool in = q0 + d < end;
                 const double tau1 = in && kb > 0 ? t1[d] : 0.0, tau2 = in && kb >= 0 ? t2[d] : 0.0;
-                cross = wave_sum(cross);
+                const double sums = fold4(cross, d1, d2, 0.0);
+                d2 = -tau2 * lane_value(sums, 16);
+                d1 = -tau1 * fma(d2, lane_value(sums, 0), lane_value(sums, 32));
 #pragma unroll
-                for (int b = 0; b < CB; ++b) {
-                    d2[b] = -tau2 * wave_sum(d2[b]);
-                    d1[b] = -tau1 * fma(d2[b], cross, wave_sum(d1[b]));
-                }
-#pragma unroll
-                for (int b = 0; b < CB; ++b)
-#pragma unroll
-                    for (int i = I0; i < RPT; ++i) z[b][i] = lane + 64 * i < n ? fma(d1[b], v1[d][i], fma(d2[b], v2[d][i], z[b][i])) : 0.0;
+                for (int i = I0; i < RPT; ++i) z[i] = lane + 64 * i < n ? fma(d1, v1[d][i], fma(d2, v2[d][i], z[i])) : 0.0;
                 fetch(i0, q0 + DEPTH + d, d);
             }
         }
@@ -703,15 +715,13 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
         q0 = max(q0, end);
     });
 #pragma unroll
-    for (int b = 0; b < CB; ++b)
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-            const int r = lane + 64 * i;
-            if (r < n && j0 + b < n) X[(i64)(j0 + b) * ld + r] = z[b][i];
-        }
+    for (int i = 0; i < RPT; ++i) {
+        const int r = lane + 64 * i;
+        if (r < n) X[(i64)j * ld + r] = z[i];
+    }
 }
 
-template <int RPT, int CPW, int NT, int CB, int DEPTH>
+template <int RPT, int CPW, int NT, int DEPTH>
 static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, SvdCtrl *ctrl, int n, int ld)
 {
     int st = PF_OK;
@@ -730,7 +740,7 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 512 ? 2 : np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1;
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
                   (size_t)(2 * (np + 2 * SVD_CHUNK) + 2 * waves * (np + SVD_CHUNK)) * 8, s, (const double *)T, X, n, ld);
-    PF_LAUNCH(st, "svd_reflect", (svd_reflect_kernel<RPT, CB, DEPTH>), dim3((n + 4 * CB - 1) / (4 * CB)), dim3(256), s, (const double *)L,
+    PF_LAUNCH(st, "svd_reflect", (svd_reflect_kernel<RPT, DEPTH>), dim3((n + 3) / 4), dim3(256), s, (const double *)L,
               (const double *)tau, X, n, ld);
     return st;
 }
@@ -739,13 +749,13 @@ int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, do
 {
     if (n > SVD_EIGEN_MAX) return PF_ERR_UNSUPPORTED;
     // what the registers hold without spilling: up to 512 rows one wavefront per workgroup, four columns each
-    const auto run = n <= 64     ? eigenvectors<1, 4, 64, 1, 4>
-                     : n <= 128  ? eigenvectors<2, 4, 64, 1, 4>
-                     : n <= 256  ? eigenvectors<4, 4, 64, 1, 4>
-                     : n <= 512  ? eigenvectors<8, 4, 64, 1, 4>
-                     : n <= 1024 ? eigenvectors<16, 2, 256, 1, 2>
-                     : n <= 1536 ? eigenvectors<24, 2, 256, 1, 1>
-                                 : eigenvectors<32, 2, 256, 1, 1>;
+    const auto run = n <= 64     ? eigenvectors<1, 4, 64, 4>
+                     : n <= 128  ? eigenvectors<2, 4, 64, 4>
+                     : n <= 256  ? eigenvectors<4, 4, 64, 4>
+                     : n <= 512  ? eigenvectors<8, 4, 64, 4>
+                     : n <= 1024 ? eigenvectors<16, 2, 256, 2>
+                     : n <= 1536 ? eigenvectors<24, 2, 256, 1>
+                                 : eigenvectors<32, 2, 256, 1>;
     return run(s, G, L, tau, X, ctrl, n, ld);
 }
 
