@@ -143,7 +143,7 @@ struct ConvEpilogue {
     const float *scale, *shift;
     const void *add, *mask;
     int relu;
-    float *dshift; // backward, tiled products only: sums of dZ per channel
+    float *dshift; // backward: sums of dZ per channel
 };
 
 struct ConvPlan {
@@ -676,7 +676,8 @@ static int conv_bwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X,
     if (st != PF_OK) return st;
     WgradReduceArgs r0{part_dUk, dUk, p.wg_groups, T, g.r, g.C, (i64)g.C * T, T, 1, accumulate, nullptr};
     WgradReduceArgs r1{part_dVp, dVp, p.wg_groups2, 1, g.r, g.Cout, 1, g.r, 0, accumulate, ep.scale}; // dVp = scale (dZ T^T)
-    return launch_wgrad_reduce(s, r0, r1);
+    const ColsumTilesArgs cs{nullptr, ep.dshift, 0, g.Cout, accumulate, (const uint16_t *)dY, g.N, g.Ho * g.Wo};
+    return launch_wgrad_reduce(s, r0, r1, ep.dshift ? &cs : nullptr);
 }
 
 // ------------------------------------------------------------------ dense
@@ -819,7 +820,7 @@ int pf_dense_conv_bwd(const pf_conv_desc *d, const void *X, const void *Wd, cons
 } // extern "C"
 
 // What the backward call for this descriptor does by itself: fold a batch-norm scale into the filters and the sum of
-// their gradients (chain kernels and tiled products), and form the shift gradient (tiled products).  Otherwise the
+// their gradients, and form the shift gradient (chain kernels and tiled products).  Otherwise the
 // caller scales beforehand and sums afterwards.
 void pf::conv_bwd_takes(const pf_conv_desc *d, bool want_dX, bool *scale, bool *dshift)
 {
@@ -828,8 +829,7 @@ void pf::conv_bwd_takes(const pf_conv_desc *d, bool want_dX, bool *scale, bool *
     if (check_conv_desc(d, &g) != PF_OK || g.N == 0) return;
     const ConvPlan p = plan_conv(g, d->dtype);
     const bool chain = d->dtype == PF_BF16 && p.chain && want_dX;
-    *scale = chain ? p.wgrad : p.tiles;
-    *dshift = !chain && p.tiles;
+    *scale = *dshift = chain ? p.wgrad : p.tiles;
 }
 
 // ------------------------------------------------ entry points with an epilogue
@@ -920,7 +920,7 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         *fused = true; // the kernel adds the skip gradient and masks as it stores dX
         return conv_bwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY,
                               (const bf16_t *)T_saved, p.saved_bytes ? W_saved : nullptr, (bf16_t *)dX, (float *)dUk,
-                              (float *)dVp, accumulate, ws, s, ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, nullptr});
+                              (float *)dVp, accumulate, ws, s, ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift});
     }
     return conv_bwd_generic<bf16_t>(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp,
                                     (const bf16_t *)dY, (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dUk,

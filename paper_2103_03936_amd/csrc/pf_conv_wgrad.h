@@ -22,11 +22,14 @@ struct WgradReduceArgs {
     const float *nscale; // nullable: the sum of column n is multiplied by nscale[n] (a fixed batch-norm scale)
 };
 
-// out[c] (+)= sum over tiles of partial[tile][c]; cols a multiple of 32
+// out[c] (+)= sum over tiles of partial[tile][c]; cols a multiple of 32.  Or, with planes (16-byte aligned), out[c] (+)= sum over
+// images and pixels of planes[n][c][p], N images of HW pixels.
 struct ColsumTilesArgs {
     const float *partial;
     float *out;
     int tiles, cols, accumulate;
+    const uint16_t *planes;
+    int N, HW;
 };
 
 bool wgrad_supported(int M, int Nc, int H, int W, int k, int stride, int pad);

@@ -376,12 +376,61 @@ __global__ __launch_bounds__(WG_THREADS, 1) void conv_wgrad_pair_kernel(WgradArg
     }
 }
 
+// The sum of channel c over N images [C][HW], in thread 0: planes of whole 16-byte pieces are read so, four in flight per thread.
+__device__ float plane_sum(const uint16_t *planes, int c, int N, int C, int HW)
+{
+    const auto f = [](uint32_t bits) { return __uint_as_float(bits); };
+    const int tid = threadIdx.x;
+    float acc = 0.f;
+    if (HW % 8 == 0) {
+        const int pv = HW / 8;
+        const i64 count = (i64)N * pv;
+        for (i64 i0 = tid; i0 < count; i0 += 1024) {
+            u32x4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const i64 i = i0 + 256 * u < count ? i0 + 256 * u : count - 1;
+                const int n = (int)(i / pv), q = (int)(i - (i64)n * pv);
+                v[u] = *(const u32x4_alias *)(planes + ((i64)n * C + c) * HW + (i64)q * 8);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float e[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) e[k] = f(v[u][k] << 16) + f(v[u][k] & 0xffff0000u);
+                acc += i0 + 256 * u < count ? (e[0] + e[1]) + (e[2] + e[3]) : 0.f;
+            }
+        }
+    } else {
+        for (i64 i = tid; i < (i64)N * HW; i += 256) {
+            const int n = (int)(i / HW), p = (int)(i - (i64)n * HW);
+            acc += f((uint32_t)planes[((i64)n * C + c) * HW + p] << 16);
+        }
+    }
+    __shared__ float red[256];
+    red[tid] = acc;
+    __syncthreads();
+    for (int s = 128; s > 0; s >>= 1) {
+        if (tid < s) red[tid] += red[tid + s];
+        __syncthreads();
+    }
+    return red[0];
+}
+
 // out[m * s_m + n * s_n + tap * s_tap] (+)= sum_g partial[g][tap][m][n]; four consecutive n per output
 // The blocks past blocks01 add up per-tile column sums instead (a bias gradient): 16 columns per block,
-// sixteen threads per column take every sixteenth tile, and their sums are added in a fixed order.
+// sixteen threads per column take every sixteenth tile, and their sums are added in a fixed order.  Or the planes of a channel each (a
+// shift gradient): beside the other sums they cost nothing, as a launch of their own 4 us (128 images of 8 x 8, 256 channels: a
+// layer's step 51.5 -> 47.7 us).
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs r0, WgradReduceArgs r1, int blocks0,
                                                             ColsumTilesArgs cs, int blocks01)
 {
+    if ((int)blockIdx.x >= blocks01 && cs.planes) {
+        const int c = blockIdx.x - blocks01;
+        const float total = plane_sum(cs.planes, c, cs.N, cs.cols, cs.HW);
+        if (threadIdx.x == 0) cs.out[c] = cs.accumulate ? cs.out[c] + total : total;
+        return;
+    }
     if ((int)blockIdx.x >= blocks01) {
         __shared__ float part[16][16];
         const int tc = threadIdx.x & 15, tg = threadIdx.x >> 4;
@@ -529,9 +578,9 @@ int launch_wgrad_reduce(hipStream_t s, const WgradReduceArgs &r0, const WgradRed
     const i64 c0 = r0.out ? (i64)r0.taps * r0.M * r0.Nc : 0, c1 = r1.out ? (i64)r1.taps * r1.M * r1.Nc : 0;
     const int b0 = (int)((c0 / 4 + 63) / 64), b1 = (int)((c1 / 4 + 63) / 64);
     ColsumTilesArgs c = {};
-    if (cs && cs->out && cs->tiles > 0) c = *cs;
-    if (c.cols % 16 != 0) return PF_ERR_UNSUPPORTED;
-    const int b2 = c.cols / 16;
+    if (cs && cs->out && (cs->tiles > 0 || cs->planes)) c = *cs;
+    if (!c.planes && c.cols % 16 != 0) return PF_ERR_UNSUPPORTED;
+    const int b2 = c.planes ? c.cols : c.cols / 16;
     if (b0 + b1 + b2 == 0) return st;
     PF_LAUNCH(st, "wgrad_reduce", wgrad_reduce_kernel, dim3(b0 + b1 + b2), dim3(256), s, r0, r1, b0, c, b0 + b1);
     return st;

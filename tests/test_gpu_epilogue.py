@@ -156,6 +156,21 @@ def test_epilogue_options_one_at_a_time():
     assert torch.equal(Ya, Yb) and torch.equal(Ta, Tb)
 
 
+@pytest.mark.parametrize("N,H,W", [(130, 8, 8), (33, 8, 8), (40, 7, 7), (40, 6, 6), (37, 8, 5)])
+def test_shift_gradient_on_the_chain_path(N, H, W):
+    """Its blocks beside the filter gradients' sums: planes of whole 16-byte pieces and others, a last round that is not full, added
+    to what is there.  A thread adds N H W / 256 floats in a row, then eight halvings: that many roundings of the absolute sum."""
+    import paper_2103_03936_amd as pf
+    a = workloads.conv_inputs(N, 256, H, W, 256, 64, 3, 1, 1, dtype="bf16", seed=95)
+    g = {k_: to_gpu(v, "bf16") for k_, v in a.items()}
+    _, T, Ws = pf.pf_lowrank_conv_fwd(g["X"], g["Uk"], g["Vp"], 1, 1, save_W=True)
+    grads = (torch.ones(64, 256, 3, 3, device="cuda"), torch.ones(256, 64, device="cuda"), torch.ones(256, device="cuda"))
+    pf.pf_lowrank_conv_bwd_ep(g["X"], g["Uk"], g["Vp"], None, g["dY"], T_saved=T, stride=1, pad=1, W_saved=Ws, grads=grads)
+    dZ = g["dY"].double()
+    bound = (N * H * W / 256 + 12) * 2.0 ** -24 * (1 + dZ.abs().sum(dim=(0, 2, 3)))
+    assert bool(((grads[2].double() - 1 - dZ.sum(dim=(0, 2, 3))).abs() <= bound).all())
+
+
 def test_epilogue_validation():
     import ctypes
     import paper_2103_03936_amd as pf
