@@ -141,7 +141,7 @@ static LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
     p.T = plan_tiles(d->dtype, M, G * r, in, 16);
     p.Y = plan_tiles(d->dtype, M, G * out, r, 1);
     p.dT = plan_tiles(d->dtype, M, G * r, out, 16);
-    const TileNeed need[3] = {{M, in, G * r, false}, {G * out, r, M, true}, {in, G * r, M, true}};
+    const TileNeed need[3] = {{M, in, G * r, false}, {G * out, r, M, true, true}, {in, G * r, M, true, true}};
     p.grads = plan_tile_group(d->dtype, need, 3);
     const int ks = p.T.ksplit > p.dT.ksplit ? p.T.ksplit : p.dT.ksplit;
     p.n_mid = (size_t)(G * M * r);

@@ -82,6 +82,26 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
             if (last) break;
         }
     }
+    // bf16 gradients that contract over many rows: bringing the lines of both operands in takes 8 bytes a clock of a compute unit, twice
+    // what `work` says, and 128 x 128 tiles need half as much, if they come out at most two to a compute unit, all at once, and none of
+    // their columns is padding.  A backward call of one layer (dX, dU and dV in one launch), us, 64 x 64 / 128 x 128: 8192 rows, 512 ->
+    // 128 -> 2048 49.1 / 43.7, rank 256 69.8 / 64.1; 6000 rows, 1024 -> 256 -> 512 49.7 / 40.7; the launch of three 512 -> 128 -> 512
+    // that share their input 48.4 / 27.1.  Not so with fewer rows (4096, 512 -> 128 -> 2048 33.3 / 37.2), more than two (16384, 512 ->
+    // 128 -> 2048 72.5 / 86.1), padding (8192, 768 -> 192 -> 768 48.9 / 53.7) or more than 32 chunks to a workgroup (6100, 1024 -> 384
+    // -> 1024 66 / 73).
+    if (bf && n == 3 && need[1].tn && need[2].tn && need[1].K >= 6000 && need[1].N % 128 == 0 && need[2].N % 128 == 0) {
+        const auto tiles = [&](int i) { return ((need[i].M + 127) / 128) * ((need[i].N + 127) / 128); };
+        const i64 rest = 512 - tiles(0), each = tiles(1) + tiles(2);
+        i64 ks = rest / each;
+        for (int i = 1; i < 3; ++i)
+            while (ks > 1 && ks * need[i].M * need[i].N > (2 << 20)) --ks;
+        if (ks >= 1 && rest >= each && tiles(0) + ks * each >= 384 && need[1].K <= 64 * 32 * ks) {
+            best.shape = TS_128;
+            best.ksplit[0] = 1;
+            best.ksplit[1] = best.ksplit[2] = (int)ks;
+            return best;
+        }
+    }
     // 32 x 32 tiles that leave a compute unit with one workgroup: eight wavefronts share its chunks, twice as long, so that two
     // wavefronts of a SIMD cover each other's waits.  Float, 188 workgroups of 47 chunks (64 x 1500 times 1500 x 3000) 18.2 -> 15.2 us,
     // 256 of 16 chunks 9.7 -> 8.0, of 8 chunks 6.8 -> 6.4; with two workgroups there already (bf16, 470 of 10 chunks) 6.6 -> 7.2.

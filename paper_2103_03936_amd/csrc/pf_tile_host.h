@@ -76,6 +76,7 @@ TilePlan plan_tiles(int dtype, i64 M, i64 N, i64 K, int max_split);
 struct TileNeed {
     i64 M, N, K;
     bool split;
+    bool tn; // the contraction is the slow index of both operands
 };
 struct TileGroup {
     TileShape shape;

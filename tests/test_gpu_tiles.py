@@ -21,6 +21,7 @@ LINEAR = [
     (160, 517, 260, 37),      # one workgroup per compute unit: chunks of twice the length, the last one nearly empty or not whole,
     (130, 2047, 40, 64),      # alone, and with the contraction split as well
     (300, 255, 1030, 96),
+    (6337, 500, 264, 128),    # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
 ]
 
 CONV = [
@@ -54,7 +55,7 @@ def test_lstm_cell(shape, groups):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4)])
+@pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3)])
 def test_linear_shared(shape, dtype):
     """The middle one splits the contraction of dT, whose layers then lie one after the other instead of side by side."""
     test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=shape[0] != 700, seed=24)
