@@ -5,7 +5,7 @@
 // orthogonalises every pair of columns once per sweep; on A itself a sweep moves rows x cols numbers cols times and
 // eight or more sweeps follow.  So an orthogonal V comes first that does most of it:
 //   G = A^T A, V = its eigenvectors (pf_svd_eigen.hip), made orthonormal by two Newton steps V (3 I - V^T V) / 2, or, where
-//   clusters of eigenvalues leave vectors that cannot be made so (and for few columns, and very many):
+//   eigenvalues that are one to rounding leave vectors that cannot be made so (and for few columns, and very many):
 //   G + shift I = L L^T, one-sided Jacobi on the cols x cols matrix L: L W = V S (no rotations accumulated: the normalised
 //   columns themselves are the eigenvectors of G; the shift, the rounding level of G, keeps L defined for any matrix);
 //   B = A V: columns orthogonal to about eps kappa^2.
@@ -15,8 +15,10 @@
 // Unless a second check is content, sweeps of the Jacobi iteration follow until one finds nothing to rotate.
 // So singular values far below the largest come out as exactly as without the preconditioner.
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
-// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.8 with the eigenvectors; a matrix that turns out clustered pays for both (1024 x
-// 512 with orthonormal columns: 15.6 -> 17.3 ms).
+// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.34 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.33
+// (rounding to float tells the values apart).  A matrix that has two singular values below 1e-8 of the largest, so that their
+// squares are one, and not by columns that are zero, pays for both: with Jacobi's alone / with both, ms, 300 x 60 with values down to
+// 1e-9 1.37 / 1.46, 576 x 64 of rank 8 1.67 / 1.87, 600 x 160 of rank 20 5.18 / 5.45, 2304 x 256 of rank 32 14.9 / 14.1.
 //
 // A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
 // every column of one block against every column of the other (in a sweep's first round also within the blocks) found on
@@ -44,7 +46,7 @@ static double svd_tolerance(int rows)
 // That of the preconditioner, whose columns become V: rounding level.
 static double svd_tolerance_v(int rows) { return (double)(rows < 64 ? 64 : rows) * 2.220446049250313e-16; }
 
-__global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *At, SvdCtrl *ctrl, int n, int nr, int nc, int ld,
+__global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *At, SvdCtrl *ctrl, int *place, int n, int nr, int nc, int ld,
                                                         int transposed)
 {
     if (blockIdx.x == 0)
@@ -52,6 +54,7 @@ __global__ __launch_bounds__(256) void svd_init_kernel(const float *W, double *A
     const i64 idx = (i64)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (i64)nc * ld) return;
     const int j = (int)(idx / ld), i = (int)(idx % ld);
+    if (i == 0) place[j] = 0;
     At[idx] = i >= nr ? 0.0 : (double)(transposed ? W[(i64)j * n + i] : W[(i64)i * n + j]);
 }
 
@@ -88,8 +91,10 @@ constexpr int SVD_U = 4; // pieces of eight contraction indices that a wavefront
 // C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows, and SVD_U pieces are
 // requested while the SVD_U before are multiplied: a piece takes about a microsecond to arrive, its MFMAs 64 clocks each (2048 x 512:
 // 88 us with one at a time, 64 with SVD_U and a wait before they are multiplied, 36 so; the product of the two below 58 -> 38
-// us).  unless (nullable): nothing is done when it is 0.
-__global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *unless)
+// us).  unless (nullable): nothing is done when it is 0.  place (nullable): -1 for columns that have an inner product other than
+// zero with another.
+__global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *unless,
+                                                        int *place)
 {
     if (unless && *unless == 0u) return;
     const int ti = blockIdx.x, tj = blockIdx.y;
@@ -141,13 +146,19 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
         multiply(p1, r + STEP);
     }
     __shared__ double part[4][32][33];
+    __shared__ int met[2][32];
+    if (tid < 64) met[tid >> 5][tid & 31] = 0;
     svd_tile_out(acc, part, [&](int i, int j, double s) {
         const int gi = 32 * ti + i, gj = 32 * tj + j;
         if (gi < nc && gj < nc && (ti != tj || i >= j)) {
             C[(i64)gj * ldc + gi] = s;
             C[(i64)gi * ldc + gj] = s;
+            if (place && gi != gj && !(s == 0.0)) met[0][i] = met[1][j] = 1;
         }
     });
+    if (!place) return;
+    __syncthreads();
+    if (tid < 64 && met[tid >> 5][tid & 31]) place[32 * (tid < 32 ? ti : tj) + (tid & 31)] = -1;
 }
 
 // The first-order rotation that takes the inner product g_ij of two columns out (0 where they count as orthogonal): with
@@ -205,19 +216,22 @@ __global__ __launch_bounds__(256) void svd_mixed_kernel(const double *S, unsigne
 
 // out[:, j] = sum_k left[:, k] right[k, j], all column-major: one tile of 32 columns x 32 rows per workgroup, the wavefronts split k.
 //   SVD_TIMES    right as it is (B = A V)
-//   SVD_NEWTON   right = 3/2 I - S / 2, S the Gram matrix of left's columns: the Newton step towards orthonormal columns
+//   SVD_NEWTON   right = 3/2 I - S / 2, S the Gram matrix of left's columns: the Newton step towards orthonormal columns; what
+//                rounding left in unit vectors (place) and in their rows goes
 //   SVD_CORRECT  right = I + K from the Gram matrix of left's columns, when a check found violations[0] pairs and K small; rows
 //                from split on go to out2
 enum { SVD_TIMES, SVD_NEWTON, SVD_CORRECT };
 template <int MODE>
 __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, const double *right, double *out, double *out2, int nr, int nc,
-                                                           int ld, int ldr, int ldo, int ldo2, int split, double tol, const SvdCtrl *ctrl)
+                                                           int ld, int ldr, int ldo, int ldo2, int split, double tol, const SvdCtrl *ctrl,
+                                                           const int *place)
 {
     if (MODE == SVD_CORRECT && (ctrl->violations[0] == 0u || ctrl->coarse[0])) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
     const int j0 = blockIdx.y * 32, i0 = blockIdx.x * 32;
     f64x4_t acc[2][2];
     double gj[2] = {1.0, 1.0};
+    const int unit = MODE == SVD_NEWTON ? place[min(i0 + (tid & 31), nc - 1)] : -1, units = MODE == SVD_NEWTON ? (int)ctrl->isolated : 0;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
         const int j = j0 + 16 * a + c;
@@ -284,6 +298,7 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
     svd_tile_out(acc, part, [&](int jj, int ii, double s) {
         const int j = j0 + jj, i = i0 + ii;
         if (j >= nc || i >= nr) return;
+        if (MODE == SVD_NEWTON && (unit >= 0 || j < units)) s = unit == j ? 1.0 : 0.0; // (ii is tid & 31)
         if (MODE == SVD_CORRECT) s += left[(i64)j * ld + i];
         if (MODE == SVD_CORRECT && i >= split)
             out2[(i64)j * ldo2 + i - split] = s;
@@ -763,11 +778,9 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void
     SvdCtrl *ctrl = ws.take<SvdCtrl>(1);
     const int nc = p.nc, nr = p.nr;
     const i64 cells = (i64)nc * p.lda;
-    PF_LAUNCH(st, "svd_init", svd_init_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), s, (const float *)W, At, ctrl,
+    PF_LAUNCH(st, "svd_init", svd_init_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), s, (const float *)W, At, ctrl, rank,
               (int)d->n, nr, nc, p.lda, p.transposed);
     const dim3 gram((nc + 31) / 32, (nc + 31) / 32);
-    PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn,
-              (const unsigned *)nullptr);
     // one workgroup per pair of blocks (at least eight for the factorization), all of them resident
     const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2;
     const int nwg = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
@@ -776,32 +789,40 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void
     // V: eigenvectors of G made orthonormal; where they cannot be (ctrl->mixed), and for few or very many columns, by Jacobi
     const bool eigen = nc >= SVD_EIGEN_MIN && nc <= SVD_EIGEN_MAX;
     const unsigned *unless = eigen ? &ctrl->mixed : nullptr;
+    int *const place = rank; // (before the ranks are there)
+    PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn,
+              (const unsigned *)nullptr, eigen ? place : (int *)nullptr);
     if (eigen) {
-        if (st == PF_OK) st = launch_svd_eigenvectors(s, G, L, sig, BV, ctrl, nc, p.ldn);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nc, nc, p.ldn, p.ldn, (const unsigned *)nullptr);
+        if (st == PF_OK) st = launch_svd_eigenvectors(s, G, L, sig, BV, place, ctrl, nc, p.ldn);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nc, nc, p.ldn, p.ldn,
+                  (const unsigned *)nullptr, (int *)nullptr);
         PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)BV, (const double *)G, L,
-                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldn, 0, 0, 0.0, (const SvdCtrl *)ctrl);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)L, G, nc, nc, p.ldn, p.ldn, (const unsigned *)nullptr);
+                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldn, 0, 0, 0.0, (const SvdCtrl *)ctrl, (const int *)place);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)L, G, nc, nc, p.ldn, p.ldn,
+                  (const unsigned *)nullptr, (int *)nullptr);
         PF_LAUNCH(st, "svd_mixed", svd_mixed_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->mixed, nc, p.ldn);
         PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)L, (const double *)G, V,
-                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, unless);
+                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl, (const int *)place);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, unless,
+                  (int *)nullptr);
     }
     if (st == PF_OK)
         st = launch_cooperative(s, "svd_precondition", svd_precondition_kernel, nwg, SVD_NT, G, L, ctrl, nc, p.ldn,
                                 16.0 * 2.220446049250313e-16 * (nc + 16), svd_tolerance_v(nc), unless);
     PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda, unless);
     PF_LAUNCH(st, "svd_apply", svd_product_kernel<SVD_TIMES>, dim3((p.lda + 31) / 32, (nc + 31) / 32), dim3(256), s, (const double *)At,
-              (const double *)V, BV, (double *)nullptr, p.lda, nc, p.lda, p.ldb, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl);
+              (const double *)V, BV, (double *)nullptr, p.lda, nc, p.lda, p.ldb, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl,
+              (const int *)nullptr);
     for (int first = 1; first >= 0; --first) {
         unless = first ? nullptr : &ctrl->violations[0];
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, unless);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, unless,
+                  (int *)nullptr);
         PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->violations[1 - first],
                   &ctrl->coarse[1 - first], nc, p.ldn, svd_tolerance(nr), unless);
         if (first) {
             PF_LAUNCH(st, "svd_correct", svd_product_kernel<SVD_CORRECT>, dim3((p.ldb + 31) / 32, (nc + 31) / 32), dim3(256), s,
                       (const double *)BV, (const double *)G, At, L, p.ldb, nc, p.ldb, p.ldn, p.lda, p.ldn, p.lda, svd_tolerance(nr),
-                      (const SvdCtrl *)ctrl);
+                      (const SvdCtrl *)ctrl, (const int *)nullptr);
             PF_LAUNCH(st, "svd_corrected", svd_corrected_kernel, dim3(nc), dim3(256), s, (const double *)At, (const double *)L, BV, p.ldb,
                       p.lda, p.ldn, (const SvdCtrl *)ctrl);
         }

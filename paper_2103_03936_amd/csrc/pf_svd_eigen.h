@@ -9,8 +9,8 @@ namespace pf {
 constexpr int SVD_NT = 512; // threads of the cooperative kernels
 
 // Columns that the tridiagonal route takes.  Up to 16 the two blocks of columns of the Jacobi iteration are one workgroup's and need
-// few barriers (16 columns of 16 rows: 232 us a call on it, 222 on this one; 20 columns: 359 and 243; 64: 748 and 358; 512: 11000
-// and 1800); above 2048 a column of the matrix exceeds what a wavefront keeps of it.
+// few barriers (16 columns of 16 rows: 232 us a call on it, 222 on this one; 20 columns: 359 and 243; 64: 791 and 250; 512: 11750
+// and 1340); above 2048 a column of the matrix exceeds what a wavefront keeps of it.
 constexpr int SVD_EIGEN_MIN = 17, SVD_EIGEN_MAX = 2048;
 
 // A launch whose workgroups are all resident (they wait for one another)
@@ -24,7 +24,9 @@ static int launch_cooperative(hipStream_t s, const char *name, void (*kernel)(AR
 }
 
 // X (n columns, leading dimension ld) = unit eigenvectors of the symmetric G, as orthogonal as the gaps between the eigenvalues
-// allow.  G (overwritten), L (n columns of ld), tau (n) and X (2 n columns of ld) are scratch.
-int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, SvdCtrl *ctrl, int n, int ld);
+// allow, in ascending order of the eigenvalues.  place[j]: -1, or 0 where row j of G is zero off the diagonal; such rows are given
+// eigenvalues below all of G's, and place comes back with the column of X that is the j-th unit vector, one of the first ctrl->isolated.
+// G (overwritten), L (n columns of ld), tau (n) and X (2 n columns of ld) are scratch.
+int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, int *place, SvdCtrl *ctrl, int n, int ld);
 
 } // namespace pf

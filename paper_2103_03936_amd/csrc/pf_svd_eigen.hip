@@ -95,9 +95,57 @@ __device__ __forceinline__ void wave_sync()
 // exchange is one store and one load, with no flag and no barrier.
 constexpr u64 SLOT_EMPTY = ~0ull;
 
-__global__ __launch_bounds__(256) void svd_slots_kernel(u64 *slots, i64 n)
+// A row of G that is zero off the diagonal (a zero column of the matrix, or one orthogonal to all others) has a unit vector for
+// its eigenvector, and several such rows may well have one eigenvalue: a filter bank with pruned filters has a zero for each.  Left
+// as they are, their vectors would come out alike, and the whole matrix would go to the Jacobi iteration as well.  So their diagonal
+// entries, which nothing else depends on, become distinct and lie below all other eigenvalues, at the scale of the rest of the
+// matrix.  A call with a quarter of the columns zero, us, before -> now (Jacobi's preconditioner alone): 1024 x 512 10540 -> 1340
+// (11390), 2304 x 256 4260 -> 720 (3910), 576 x 64 995 -> 290 (840); where no row is so, 576 x 64 248 -> 249.
+template <int CHUNKS>
+__device__ __forceinline__ void svd_isolate(double *G, int *place, SvdCtrl *ctrl, int n, int ld)
 {
-    for (i64 i = (i64)blockIdx.x * 256 + threadIdx.x; i < n; i += (i64)gridDim.x * 256) slots[i] = SLOT_EMPTY;
+    __shared__ int count[4 * CHUNKS];
+    __shared__ double most[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    u64 alone[CHUNKS];
+    double scale = 0.0;
+#pragma unroll
+    for (int m = 0; m < CHUNKS; ++m) {
+        const int j = min(tid + 256 * m, n - 1), flag = place[j];
+        if (flag < 0) scale = fmax(scale, G[(i64)j * ld + j]);
+        alone[m] = __ballot(tid + 256 * m < n && flag == 0);
+        if (lane == 0) count[4 * m + wave] = __popcll(alone[m]);
+    }
+    for (int s = 32; s > 0; s >>= 1) scale = fmax(scale, __shfl_xor(scale, s, 64));
+    if (lane == 0) most[wave] = scale;
+    __syncthreads();
+    int all = 0;
+    for (int i = 0; i < 4 * CHUNKS; ++i) all += count[i];
+    scale = fmax(fmax(most[0], most[1]), fmax(most[2], most[3]));
+    if (!(scale > 0.0)) scale = 1.0;
+#pragma unroll
+    for (int m = 0; m < CHUNKS; ++m) {
+        const int j = tid + 256 * m;
+        int at = __popcll(alone[m] & ((1ull << lane) - 1));
+        for (int i = 0; i < 4 * m + wave; ++i) at += count[i];
+        if (alone[m] >> lane & 1) {
+            place[j] = at;
+            G[(i64)j * ld + j] = -scale * (double)(all - at) / (double)all;
+        }
+    }
+    if (tid == 0) ctrl->isolated = (unsigned)all;
+    __syncthreads();
+}
+
+// (the last workgroup has svd_isolate)
+template <int CHUNKS>
+__global__ __launch_bounds__(256) void svd_slots_kernel(u64 *slots, i64 n, double *G, int *place, SvdCtrl *ctrl, int nc, int ld)
+{
+    if (blockIdx.x == gridDim.x - 1) {
+        svd_isolate<CHUNKS>(G, place, ctrl, nc, ld);
+        return;
+    }
+    for (i64 i = (i64)blockIdx.x * 256 + threadIdx.x; i < n; i += (i64)(gridDim.x - 1) * 256) slots[i] = SLOT_EMPTY;
 }
 __device__ __forceinline__ void slot_put(u64 *slot, double x)
 {
@@ -438,20 +486,28 @@ __device__ __forceinline__ void tridiag_tail_steps(double (&a)[4][16], double (&
         wave_sync(); // (they have been read)
     }
 }
-__global__ __launch_bounds__(256) void svd_tridiag_tail_kernel(const double *G, double *L, double *tau_out, int n, int ld)
+__global__ __launch_bounds__(256) void svd_tridiag_tail_kernel(double *G, double *L, double *tau_out, int *place, SvdCtrl *ctrl, int n, int ld)
 {
     __shared__ __attribute__((aligned(16))) double X[4][SVD_TAIL], W[4][SVD_TAIL], P[2][SVD_TAIL], R[2][SVD_TAIL];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ri = lane >> 3, cb = lane & 7;
     const int base = n - SVD_TAIL, first = max(-base, 0); // place t of the 128 is row (and column) base + t of G, first .. 127 exist
     double a[4][16], x[2], sq = 0.0;
+    const auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int r = 32 * q + 4 * ri + wave, c = 16 * (j >> 1) + 2 * cb + (j & 1); // (the matrix is symmetric: lanes read along it)
-            a[q][j] = G[(i64)(base + max(r, first)) * ld + base + max(c, first)];
-        }
-    __builtin_amdgcn_sched_barrier(0); // (a select on each load would become a branch around it, and every load a wait of its own)
+            for (int j = 0; j < 16; ++j) {
+                const int r = 32 * q + 4 * ri + wave, c = 16 * (j >> 1) + 2 * cb + (j & 1); // (the matrix is symmetric: lanes read along it)
+                a[q][j] = G[(i64)(base + max(r, first)) * ld + base + max(c, first)];
+            }
+        __builtin_amdgcn_sched_barrier(0); // (a select on each load would become a branch around it, and every load a wait of its own)
+    };
+    const int flag0 = place[min(lane, n - 1)], flag1 = place[min(lane + 64, n - 1)];
+    fetch();
+    if (base <= 0 && __any(flag0 == 0 || flag1 == 0)) { // (every wavefront comes to the same answer)
+        svd_isolate<1>(G, place, ctrl, n, ld);
+        fetch();
+    }
     if (first > 0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -722,7 +778,7 @@ __global__ __launch_bounds__(256) void svd_reflect_kernel(const double *L, const
 }
 
 template <int RPT, int CPW, int NT, int DEPTH>
-static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, SvdCtrl *ctrl, int n, int ld)
+static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, int *place, SvdCtrl *ctrl, int n, int ld)
 {
     int st = PF_OK;
     u64 *slots = (u64 *)X;
@@ -730,13 +786,15 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     if constexpr (64 * RPT > SVD_TAIL) {
         const i64 words = 2 * (i64)(n - SVD_TAIL) * ld; // P's rows and C's, one per step
         const i64 blocks = (words + 1023) / 1024;
-        PF_LAUNCH(st, "svd_slots", svd_slots_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), s, slots, words);
+        PF_LAUNCH(st, "svd_slots", svd_slots_kernel<(64 * RPT + 255) / 256>, dim3((unsigned)(blocks < 1024 ? blocks : 1024) + 1), dim3(256), s, slots,
+                  words, G, place, ctrl, n, ld);
         if (st == PF_OK)
             st = launch_cooperative(s, "svd_tridiag", svd_tridiag_kernel<RPT, CPW, NT>, (n + NT / 64 * CPW - 1) / (NT / 64 * CPW), NT, G, L, tau, slots, ctrl, n, ld);
     }
-    PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, (const double *)G, L, tau, n, ld);
+    PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, G, L, tau, place, ctrl, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);
-    // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 151 us), else what 64 KB of LDS hold
+    // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 151 us), else what 64 KB of LDS hold, or one: with
+    // more than 2032 columns that one takes 65920 bytes, of the 160 KB that a workgroup may have
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 512 ? 2 : np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1;
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
                   (size_t)(2 * (np + 2 * SVD_CHUNK) + 2 * waves * (np + SVD_CHUNK)) * 8, s, (const double *)T, X, n, ld);
@@ -745,7 +803,7 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     return st;
 }
 
-int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, SvdCtrl *ctrl, int n, int ld)
+int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, double *X, int *place, SvdCtrl *ctrl, int n, int ld)
 {
     if (n > SVD_EIGEN_MAX) return PF_ERR_UNSUPPORTED;
     // what the registers hold without spilling: up to 512 rows one wavefront per workgroup, four columns each
@@ -756,7 +814,7 @@ int launch_svd_eigenvectors(hipStream_t s, double *G, double *L, double *tau, do
                      : n <= 1024 ? eigenvectors<16, 2, 256, 2>
                      : n <= 1536 ? eigenvectors<24, 2, 256, 1>
                                  : eigenvectors<32, 2, 256, 1>;
-    return run(s, G, L, tau, X, ctrl, n, ld);
+    return run(s, G, L, tau, X, place, ctrl, n, ld);
 }
 
 } // namespace pf

@@ -15,6 +15,7 @@ struct SvdCtrl {
     unsigned arrived[3];    // grid barriers of the three cooperative launches
     unsigned failed;        // a barrier's wait ran out
     unsigned broken;        // a singular value is not finite: the matrix was not
+    unsigned isolated;      // columns of the matrix that are orthogonal to all others, to the bit (zero columns among them)
     unsigned mixed;         // the eigenvectors of G are not orthogonal enough to be made so: the preconditioner is Jacobi's
     unsigned coarse[2];     // (per check) some column of B is farther from orthogonal than one correction takes out
     unsigned violations[2]; // pairs of B that are not orthogonal after the preconditioner, and after the first correction or sweep

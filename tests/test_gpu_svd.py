@@ -166,6 +166,68 @@ def test_eigenvector_route(n):
     assert np.linalg.norm(got - want) <= 2.0 ** -22 * np.linalg.norm(want)
 
 
+def _uncoupled(m, n, seed):
+    """A quarter of the columns zero (pruned filters), two more large and alone in their rows, the others small."""
+    W = 1e-2 * _matrix(m, n, seed).astype(np.float64)
+    zero, single = np.arange(1, n, 4), [0, n // 4 * 2]
+    W[:, zero] = 0.0
+    W[:2] = 0.0
+    for i, j in enumerate(single):
+        W[:, j] = 0.0
+        W[i, j] = 10.0 * (i + 1)
+    return W.astype(np.float32), zero, single
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("m,n", [(40, 17), (130, 64), (200, 127), (200, 128), (200, 129), (400, 257), (700, 600)])
+def test_uncoupled_columns(m, n, transposed):
+    """Columns that are orthogonal to all others, zero columns among them: the factors reproduce the matrix (full rank kept) to the
+    roundings of its two parts, the rows of zero columns are zero, and nothing is left to rotate."""
+    import paper_2103_03936_amd as pf
+    W, zero, single = _uncoupled(m, n, 71 + n)
+    assert not set(zero) & set(single)
+    A = np.ascontiguousarray(W.T) if transposed else W
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(A), n, return_info=True)
+    assert int(info[1]) == 0 and int(info[0]) <= 3
+    U, V = (V, U) if transposed else (U, V)
+    assert torch.count_nonzero(V[torch.as_tensor(zero)]) == 0
+    assert torch.count_nonzero(sigma[n - len(zero):]) == 0
+    got = U.double().cpu().numpy() @ V.double().cpu().numpy().T
+    large = np.isin(np.arange(n), single)
+    for part in (large, ~large):
+        assert np.linalg.norm((got - W)[:, part]) <= 2.0 ** -22 * np.linalg.norm(W[:, part].astype(np.float64))
+    ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]
+
+
+@pytest.mark.parametrize("kind", ["zero columns", "diagonal", "zero"])
+def test_uncoupled_columns_take_no_longer(kind):
+    """Eigenvalues of uncoupled columns may coincide without a second preconditioner: with one, these calls took 1.8 (diagonal) to 8
+    (zero columns) times as long as one on an ordinary matrix of their size."""
+    import paper_2103_03936_amd as pf
+    plain = to_gpu(_matrix(1024, 512, 81))
+    other = plain.clone()
+    if kind == "zero columns":
+        other[:, ::4] = 0
+    else:
+        other.zero_()
+        if kind == "diagonal":
+            other[range(512), range(512)] = 1
+
+    def best(X):
+        times = []
+        for _ in range(8):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            pf.pf_svd_split(X, 128)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times[2:])
+
+    assert best(other) <= 1.4 * best(plain)
+
+
 @pytest.mark.parametrize("kind", ["orthonormal", "zero rows", "repeated", "diagonal", "graded"])
 def test_clustered_matrices(kind):
     """Eigenvalues that coincide, a matrix that falls apart, and values over seven decades: whichever preconditioner runs, the
