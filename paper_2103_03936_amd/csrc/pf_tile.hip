@@ -83,19 +83,35 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
         }
     }
     // bf16 gradients that contract over many rows: bringing the lines of both operands in takes 8 bytes a clock of a compute unit, twice
-    // what `work` says, and 128 x 128 tiles need half as much, if they come out at most two to a compute unit, all at once, and none of
-    // their columns is padding.  A backward call of one layer (dX, dU and dV in one launch), us, 64 x 64 / 128 x 128: 8192 rows, 512 ->
-    // 128 -> 2048 49.1 / 43.7, rank 256 69.8 / 64.1; 6000 rows, 1024 -> 256 -> 512 49.7 / 40.7; the launch of three 512 -> 128 -> 512
-    // that share their input 48.4 / 27.1.  Not so with fewer rows (4096, 512 -> 128 -> 2048 33.3 / 37.2), more than two (16384, 512 ->
-    // 128 -> 2048 72.5 / 86.1), padding (8192, 768 -> 192 -> 768 48.9 / 53.7) or more than 32 chunks to a workgroup (6100, 1024 -> 384
-    // -> 1024 66 / 73).
-    if (bf && n == 3 && need[1].tn && need[2].tn && need[1].K >= 6000 && need[1].N % 128 == 0 && need[2].N % 128 == 0) {
-        const auto tiles = [&](int i) { return ((need[i].M + 127) / 128) * ((need[i].N + 127) / 128); };
-        const i64 rest = 512 - tiles(0), each = tiles(1) + tiles(2);
+    // what `work` says, and 128 x 128 tiles need half as much, if they come out at most two to a compute unit, all at once.  A
+    // backward call of one layer (dX, dU and dV in one launch), us, the plan above / 128 x 128: 8192 rows, 512 -> 128 -> 2048 49.1 /
+    // 43.7, rank 256 69.8 / 64.1; 7500 rows, two layers of 640 -> 256 -> 384 that share their input 88.3 / 47.4; the launch of three 512
+    // -> 128 -> 512 48.4 / 27.1.  Not so
+    //   with fewer rows (4096, 512 -> 128 -> 2048 33.3 / 37.2),
+    //   with more than two to a compute unit (16384, 512 -> 128 -> 2048 72.5 / 86.1) or fewer than one and a half,
+    //   with more than 32 chunks to a workgroup (6100, 1024 -> 384 -> 1024 66 / 73) or padding of the rank (8192, 768 -> 192 -> 768 48.9 /
+    //   53.7),
+    //   where the plan above has nearly seven workgroups to a compute unit or more, which hide each other's waits (7500, 1000 -> 128 ->
+    //   256 34.6 / 49.4), or splits more than five ways, so that its chunks are few (20000, 320 -> 128 -> 128 33.1 / 56.9),
+    //   or where it brings less than 400 KB into a compute unit (8192, 384 -> 128 -> 384 25.7 / 30.1).
+    // Measured over 6750 shapes of 6000 to 40000 rows, widths 64 to 4096, ranks 128 to 512, one to four layers, that pass all but the
+    // last two lines (which alone are 0.89 of the plan above, geometric mean, 976 of them more than 5 % slower than it, at most 1.7
+    // times): 4461 are taken, 0.83 of the plan above, 104 of them more than 5 % slower, at most 1.25 times.
+    if (bf && n == 3 && need[1].tn && need[2].tn && need[1].K >= 6000 && need[1].N % 128 == 0 && need[2].N % 128 == 0 && best.ksplit[1] <= 5 &&
+        best.ksplit[2] <= 5) {
+        const auto tiles = [&](int i, TileShape sh) {
+            return ((need[i].M + SHAPES[sh].bm - 1) / SHAPES[sh].bm) * ((need[i].N + SHAPES[sh].bn - 1) / SHAPES[sh].bn);
+        };
+        i64 now = 0, bytes = 0; // workgroups of the plan above, and what they bring into all compute units
+        for (int i = 0; i < 3; ++i) {
+            now += tiles(i, best.shape) * best.ksplit[i];
+            bytes += tiles(i, best.shape) * need[i].K * (SHAPES[best.shape].bm + SHAPES[best.shape].bn) * 2;
+        }
+        const i64 rest = 512 - tiles(0, TS_128), each = tiles(1, TS_128) + tiles(2, TS_128);
         i64 ks = rest / each;
         for (int i = 1; i < 3; ++i)
             while (ks > 1 && ks * need[i].M * need[i].N > (2 << 20)) --ks;
-        if (ks >= 1 && rest >= each && tiles(0) + ks * each >= 384 && need[1].K <= 64 * 32 * ks) {
+        if (ks >= 1 && rest >= each && tiles(0, TS_128) + ks * each >= 384 && need[1].K <= 64 * 32 * ks && now <= 1740 && bytes >= 256 * 400 * 1024) {
             best.shape = TS_128;
             best.ksplit[0] = 1;
             best.ksplit[1] = best.ksplit[2] = (int)ks;

@@ -21,7 +21,8 @@ LINEAR = [
     (160, 517, 260, 37),      # one workgroup per compute unit: chunks of twice the length, the last one nearly empty or not whole,
     (130, 2047, 40, 64),      # alone, and with the contraction split as well
     (300, 255, 1030, 96),
-    (6337, 500, 264, 128),    # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
+    (6337, 500, 264, 128),    # many rows, but too little for the larger tiles of
+    (6337, 484, 1030, 128),   # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
 ]
 
 CONV = [
@@ -55,9 +56,11 @@ def test_lstm_cell(shape, groups):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3)])
+@pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3),
+                                   (6100, 264, 330, 128, 3)])
 def test_linear_shared(shape, dtype):
-    """The middle one splits the contraction of dT, whose layers then lie one after the other instead of side by side."""
+    """The second one splits the contraction of dT, whose layers then lie one after the other instead of side by side; the last one's
+    bf16 gradients are on 128 x 128 tiles, of which none is shared by two layers."""
     test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=shape[0] != 700, seed=24)
 
 
@@ -174,3 +177,27 @@ def test_strided_conv_epilogue(shape, dtype):
     ref = torch.nn.grad.conv2d_input((N, C, H, W), Uk.double().cpu(), torch.einsum("or,nohw->nrhw", Vp.double().cpu(), dY.double().cpu()),
                                      stride=2, padding=pad)
     assert _rel(dX.cpu(), ref) <= (2.0 ** -20 if dtype == "f32" else ROUNDED)
+
+
+@pytest.mark.parametrize("n_in,r,n_out,M,more", [(320, 128, 128, 20000, 24000), (1000, 128, 256, 7500, 7900), (640, 128, 768, 11000, 11500)])
+def test_fewer_rows_take_no_longer(n_in, r, n_out, M, more):
+    """bf16 backward: large tiles that left compute units waiting took 1.3 to 1.7 times as long for the smaller numbers of rows."""
+    import torch
+    import paper_2103_03936_amd as pf
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
+
+    def best(rows):
+        X, V, U, dY, T = n(rows, n_in), n(n_in, r), n(n_out, r), n(rows, n_out), n(rows, r)
+        times = []
+        for _ in range(6):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(10):
+                pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T, has_bias=True)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times[1:])
+
+    assert best(M) <= 1.1 * best(more)
