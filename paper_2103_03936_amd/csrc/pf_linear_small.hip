@@ -51,7 +51,10 @@ __global__ __launch_bounds__(LS_NT) void ls_slices_kernel(LsSliceArgs a0, LsSlic
             bv[0][j] = Wc[(i64)(kb + j) * a.ldw];
             bv[1][j] = Wc[(i64)(kc + j) * a.ldw];
         }
-        if (kb + 8 * LS_W >= KS) av[1] = f32x4_t{0.f, 0.f, 0.f, 0.f}; // (a piece past the end: someone else's, times zero)
+        if (kb + 8 * LS_W >= KS) { // (a piece past the end is someone else's; both factors are zeroed, for either may be infinite)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) av[1][j] = bv[1][j] = 0.f;
+        }
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll

@@ -130,3 +130,25 @@ def test_random_geometries(dtype):
         if case >= 12:  # shapes of the fused bf16 kernel
             n_in, n_out, r = 256 * int(rng.integers(1, 4)), 256 * int(rng.integers(1, 4)), 128
         _run(M, n_in, n_out, r, dtype, bool(rng.integers(0, 2)), bool(rng.integers(0, 2)), seed=500 + case)
+
+
+@pytest.mark.parametrize("n_in,n_out", [(32, 160), (64, 96), (96, 512), (256, 32), (512, 256), (160, 64)])
+def test_infinite_weight(n_in, n_out):
+    """Few-row float layers: an infinite weight makes what it is a factor of infinite, with the sign that it has in double, and no NaN,
+    wherever in a slice of the contraction it lies (slices of 32 to 160 indices, which wavefronts take eight at a time)."""
+    import paper_2103_03936_amd as pf
+    g = torch.Generator(device="cuda").manual_seed(n_in)
+    n = lambda *s: torch.rand(s, generator=g, device="cuda") + 0.5  # (positive: no sum of infinities of both signs)
+    M, r = 5, 32
+    X, V, U, dY = n(M, n_in), n(n_in, r), n(n_out, r), n(M, n_out)
+    for k in range(7, max(n_in, n_out), 8):
+        v, u = V.clone(), U.clone()
+        if k < n_in:
+            v[k, k % r] = -float("inf")
+        _, T = pf.pf_lowrank_linear_fwd(X, v, U, None)
+        assert torch.equal(torch.isinf(T), torch.isinf(X.double() @ v.double())) and not torch.isnan(T).any(), k
+        if k < n_out:
+            u[k, k % r] = float("inf")
+        dX = pf.pf_lowrank_linear_bwd(X, V, u, dY)[0]
+        want = dY.double() @ u.double() @ V.double().t()
+        assert torch.equal(torch.isinf(dX), torch.isinf(want)) and not torch.isnan(dX).any(), k
