@@ -78,18 +78,19 @@ __host__ __device__ __forceinline__ double svd_rcp(double q)
 
 // The rotation (c, s) that takes gamma out of [[alpha, gamma], [gamma, beta]], all in double: s / c = t solves
 // t^2 + 2 z t - 1 = 0, z = (beta - alpha) / (2 gamma), |t| <= 1.  With d = beta - alpha and g = 2 gamma that is
-// t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that alpha + beta is near 1: the arguments of the two approximations are then
-// in float's range (at least the threshold's square), while t itself may be as small as it is.
+// t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that the larger of d and g is near 1: the arguments of the two approximations are then
+// in float's range, while t itself may be as small as it is.  (Not alpha + beta: what rounding leaves of the norm of a column that
+// rotations have all but cancelled, as in a matrix of lower rank, may be zero or below.)
 __host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2)
 {
     f64x2_t r = {1.0, 0.0};
     if (svd_orthogonal(alpha, beta, gamma, tol2)) return r;
 #if defined(__HIP_DEVICE_COMPILE__)
-    const int e = -__builtin_amdgcn_frexp_exp(alpha + beta);
+    const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(beta - alpha), fabs(2.0 * gamma)));
     const double d = __builtin_amdgcn_ldexp(beta - alpha, e), g = __builtin_amdgcn_ldexp(2.0 * gamma, e);
 #else
     int e;
-    (void)frexp(alpha + beta, &e);
+    (void)frexp(fmax(fabs(beta - alpha), fabs(2.0 * gamma)), &e);
     const double d = ldexp(beta - alpha, -e), g = ldexp(2.0 * gamma, -e);
 #endif
     const double q = d * d + g * g, n = fabs(d) + q * svd_rsqrt(q), t = (d < 0.0 ? -g : g) * svd_rcp(n), c = svd_rsqrt(1.0 + t * t);

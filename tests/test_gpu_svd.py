@@ -116,6 +116,21 @@ def test_conv_info():
     assert 1 <= int(info[0]) <= 24 and int(info[1]) == 0
 
 
+@pytest.mark.parametrize("m,n,kept", [(60, 24, 20), (30, 12, 5), (200, 130, 70)])
+def test_zero_rows(m, n, kept):
+    """Fewer rows other than zero than columns (filters of pruned inputs): factors and singular values are finite and right, whatever
+    the rounding of columns that the rotations cancel."""
+    import paper_2103_03936_amd as pf
+    for seed in range(40):
+        W = _matrix(m, n, 101 + seed)
+        W[np.random.default_rng(seed).permutation(m)[kept:]] = 0.0
+        U, V, sigma = pf.pf_svd_split(to_gpu(W), n)
+        ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
+        assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0], seed
+        got = U.double().cpu().numpy() @ V.double().cpu().numpy().T
+        assert np.linalg.norm(got - W) <= 2.0 ** -22 * np.linalg.norm(W.astype(np.float64)), seed
+
+
 @pytest.mark.parametrize("shape", [(40, 1), (30, 24), (17, 70), (300, 130)])
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
 def test_not_finite_is_reported(shape, value):

@@ -75,3 +75,12 @@ def test_rotation_is_exact_to_double(emu):
         assert abs(float(c * c + s * s - 1)) <= 8 * 2.0 ** -53
         # columns p, q -> c p - s q, s p + c q: their inner product, relative to what it was
         assert abs(float((c * s * (a - b) + (c * c - s * s) * g) / g)) <= 16 * 2.0 ** -53, (alpha, beta, gamma)
+
+
+def test_rotation_of_cancelled_columns(emu):
+    """Norms that rounding left zero, opposite or negative, with an inner product between them: still a rotation, by 45 degrees at most."""
+    cs = (ctypes.c_double * 2)()
+    for alpha, beta, gamma in ((0.0, 0.0, 1e-40), (-1e-30, 1e-30, 1e-31), (1e-30, -1e-30, -1e-29), (-2e-33, 1e-33, 0.0), (-1e-320, 1e-310, 1e-315),
+                               (1e-30, -1e-30 * (1 - 2 ** -50), 1e-50), (0.0, 4e300, 1e-10), (0.0, 0.0, 5e-324)):
+        emu.emu_rotation(alpha, beta, gamma, cs)
+        assert abs(cs[0] ** 2 + cs[1] ** 2 - 1) <= 8 * 2.0 ** -53 and abs(cs[1]) <= 0.5 ** 0.5 * (1 + 2.0 ** -50), (alpha, beta, gamma)
