@@ -420,7 +420,7 @@ __device__ __forceinline__ void svd_rotate_row(const f64x2_t *cs, double (&x)[16
 // pairs were rotated; large_pair: some pair was farther from orthogonal than SVD_SMALL.  known (nullable): the Gram matrix of all
 // columns as it was before this sweep; where it says that every pair is orthogonal nothing is read.
 constexpr double SVD_SMALL = 3e-8; // rotations this small leave their square: orthogonal to rounding level
-__device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr, int rows, int p, int q, bool within, double tol,
+__device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr, int rows, int p, int q, bool within, double tol, double nil,
                                               SvdShared &sh, bool &large_pair, const double *known, int ldk)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
@@ -430,7 +430,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
     if (known) {
         const int i = tid >> 4 & 15, j = tid & 15, ci = column(i), cj = column(j);
         const bool some = candidate(i, j) && ci < nc && cj < nc &&
-                          !svd_orthogonal(known[(i64)ci * ldk + ci], known[(i64)cj * ldk + cj], known[(i64)cj * ldk + ci], tol * tol);
+                          !svd_orthogonal(known[(i64)ci * ldk + ci], known[(i64)cj * ldk + cj], known[(i64)cj * ldk + ci], tol * tol, nil);
         if (!__syncthreads_or(some)) return 0;
     }
     // Gram matrix, rows dealt to the wavefronts eight at a time, eight pieces in flight; the rows that this thread will
@@ -475,7 +475,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
             b += sh.part[w][j][j];
         }
         sh.g[i][j] = y;
-        const bool some = candidate(i, j) && !svd_orthogonal(a, b, y, tol2), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
+        const bool some = candidate(i, j) && !svd_orthogonal(a, b, y, tol2, nil), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
         const bool anyone = __any(some), anylarge = __any(large);
         if (lane == 0) sh.any[wave] = anylarge ? 2 : anyone ? 1 : 0;
     }
@@ -490,7 +490,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
         for (int t = 0; t < rounds; ++t) {
             const int i0 = svd_inner_lo(t, a), i1 = svd_inner_hi(t, a), j0 = svd_inner_lo(t, b), j1 = svd_inner_hi(t, b);
             const double g00 = sh.g[i0][j0], g01 = sh.g[i0][j1], g10 = sh.g[i1][j0], g11 = sh.g[i1][j1];
-            const f64x2_t rb = svd_rotation(sh.g[j0][j0], sh.g[j1][j1], sh.g[j0][j1], tol2);
+            const f64x2_t rb = svd_rotation(sh.g[j0][j0], sh.g[j1][j1], sh.g[j0][j1], tol2, nil);
             f64x2_t ra; // that of row pair a: lane (0, a) has it
             ra[0] = __shfl(rb[0], a, 64);
             ra[1] = __shfl(rb[1], a, 64);
@@ -522,7 +522,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
 
 // At most `most` sweeps, until one rotates nothing -- or, with `quick`, nothing but small angles.  Returns false when a barrier
 // gave up.
-__device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, int most, unsigned *arrived,
+__device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, double nil, int most, unsigned *arrived,
                                            unsigned &generation, unsigned *rot, bool quick, SvdCtrl *ctrl, SvdShared &sh,
                                            int *ran, const double *known = nullptr, int ldk = 0)
 {
@@ -538,7 +538,7 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
                     q = t;
                 }
                 bool large = false;
-                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, sh, large, known, ldk);
+                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, nil, sh, large, known, ldk);
                 if (did > 0 && (large || !quick) && threadIdx.x == 0)
                     __hip_atomic_fetch_add(&rot[sweep], (unsigned)did, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads(); // (the LDS tables are used again)
@@ -649,7 +649,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, dou
         if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
     }
     int ran = 0;
-    (void)svd_sweeps(L, ld, nc, nc, nc, tol, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
+    (void)svd_sweeps(L, ld, nc, nc, nc, tol, 0.0, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
 }
 
 // One-sided Jacobi on B with V carried along, when a check found pairs to rotate.  First one sweep over the pairs of blocks that
@@ -663,13 +663,24 @@ __global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, const do
     int ran = 0;
     bool ok = ctrl->failed == 0u;
     const unsigned found = first ? (ctrl->coarse[0] ? ctrl->violations[0] : 0u) : ctrl->violations[1]; // (else corrected already)
-    if (ok && found != 0u)
-        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
+    double nil = 0.0;
+    if (ok && found != 0u) {
+        for (int j = threadIdx.x; j < nc; j += SVD_NT) nil = fmax(nil, G[(i64)j * ldg + j]);
+        for (int s = 32; s > 0; s >>= 1) nil = fmax(nil, __shfl_xor(nil, s, 64));
+        if ((threadIdx.x & 63) == 0) sh.part[0][0][threadIdx.x >> 6] = nil;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < SVD_NT / 64; ++w) nil = fmax(nil, sh.part[0][0][w]);
+        nil = svd_nil(nil);
+        __syncthreads();
+        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, nil, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
                         ctrl->rot[first ? 1 : 2], false, ctrl, sh, &ran, first ? G : nullptr, ldg);
+    }
     if (!first && blockIdx.x == 0 && threadIdx.x == 0) {
         // (a check that found nothing counts as one clean sweep)
         ctrl->sweeps = !ok ? SVD_MAX_SWEEPS : ctrl->violations[0] == 0u ? 1 : found == 0u ? 2 : 1 + ran;
         ctrl->last = !ok ? 1u : found == 0u ? 0u : ctrl->rot[2][ran - 1];
+        ctrl->nil = nil;
     }
 }
 
@@ -686,7 +697,7 @@ __global__ __launch_bounds__(256) void svd_sigma_kernel(const double *At, double
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        sig[blockIdx.x] = sqrt(red[0]);
+        sig[blockIdx.x] = red[0] < ctrl->nil ? 0.0 : sqrt(red[0]);
         if (!(red[0] < __builtin_huge_val())) ctrl->broken = 1u; // (also a matrix of one column, which has no pairs)
     }
 }

@@ -22,6 +22,7 @@ struct SvdCtrl {
     unsigned rot[3][SVD_MAX_SWEEPS + 1]; // pairs rotated per sweep: of L (in pairs of blocks with a large angle), of B first, of B then
     unsigned sweeps;        // sweeps over the pairs of B, a check that found nothing included
     unsigned last;          // pairs rotated in the last of them
+    double nil;             // squared norm below which the sweeps took a column of B for zero
 };
 
 // What a call reports: sweeps, rotations of the last one, and whether its outputs are worth nothing because a barrier's wait
@@ -47,12 +48,20 @@ __host__ __device__ __forceinline__ bool svd_before(double a, int i, double b, i
 }
 
 // Whether two columns with inner product gamma and squared norms alpha and beta are orthogonal to sqrt(tol2), relative.
+// A column whose squared norm is below `nil` is orthogonal to any.
 // Written so that NaN and infinity say no: a matrix that holds any never counts as converged.
-__host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double beta, double gamma, double tol2)
+__host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
 {
     const double g2 = gamma * gamma;
-    return g2 <= tol2 * (alpha * beta) && g2 < __builtin_huge_val();
+    return (g2 <= tol2 * (alpha * beta) || alpha < nil || beta < nil) && g2 < __builtin_huge_val();
 }
+
+// `nil` for columns of which the longest has squared norm `longest`.  The columns that a matrix of lower rank leaves over are rounding
+// noise, smaller with every sweep, but never orthogonal to one another: there is no room for them.  Down to 2^-160 of the longest
+// (of two floats that are that far apart the larger exceeds 2^11) a column counts, for a graded matrix may have such singular values;
+// below that it is zero.
+constexpr double SVD_NIL = 0x1p-320;
+__host__ __device__ __forceinline__ double svd_nil(double longest) { return longest < __builtin_huge_val() ? SVD_NIL * longest : 0.0; }
 
 // 1 / sqrt(q) and 1 / q to a few units of the last place: a float approximation (23 bits) and two Newton steps in double.
 __host__ __device__ __forceinline__ double svd_rsqrt(double q)
@@ -81,10 +90,10 @@ __host__ __device__ __forceinline__ double svd_rcp(double q)
 // t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that the larger of d and g is near 1: the arguments of the two approximations are then
 // in float's range, while t itself may be as small as it is.  (Not alpha + beta: what rounding leaves of the norm of a column that
 // rotations have all but cancelled, as in a matrix of lower rank, may be zero or below.)
-__host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2)
+__host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
 {
     f64x2_t r = {1.0, 0.0};
-    if (svd_orthogonal(alpha, beta, gamma, tol2)) return r;
+    if (svd_orthogonal(alpha, beta, gamma, tol2, nil)) return r;
 #if defined(__HIP_DEVICE_COMPILE__)
     const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(beta - alpha), fabs(2.0 * gamma)));
     const double d = __builtin_amdgcn_ldexp(beta - alpha, e), g = __builtin_amdgcn_ldexp(2.0 * gamma, e);

@@ -6,6 +6,10 @@ using namespace pf;
 
 extern "C" {
 int emu_orthogonal(double alpha, double beta, double gamma, double tol) { return svd_orthogonal(alpha, beta, gamma, tol * tol); }
+int emu_orthogonal_nil(double alpha, double beta, double gamma, double tol, double longest)
+{
+    return svd_orthogonal(alpha, beta, gamma, tol * tol, svd_nil(longest));
+}
 void emu_rotation(double alpha, double beta, double gamma, double *cs)
 {
     const f64x2_t r = svd_rotation(alpha, beta, gamma, 0.0);

@@ -116,15 +116,17 @@ def test_conv_info():
     assert 1 <= int(info[0]) <= 24 and int(info[1]) == 0
 
 
-@pytest.mark.parametrize("m,n,kept", [(60, 24, 20), (30, 12, 5), (200, 130, 70)])
+@pytest.mark.parametrize("m,n,kept", [(60, 24, 20), (30, 12, 5), (200, 130, 70), (576, 64, 20)])
 def test_zero_rows(m, n, kept):
     """Fewer rows other than zero than columns (filters of pruned inputs): factors and singular values are finite and right, whatever
-    the rounding of columns that the rotations cancel."""
+    the rounding of columns that the rotations cancel; those columns come out zero, and the sweeps end."""
     import paper_2103_03936_amd as pf
     for seed in range(40):
         W = _matrix(m, n, 101 + seed)
         W[np.random.default_rng(seed).permutation(m)[kept:]] = 0.0
-        U, V, sigma = pf.pf_svd_split(to_gpu(W), n)
+        U, V, sigma, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+        assert int(info[1]) == 0, seed
+        assert all(torch.count_nonzero(t[..., kept:]) == 0 for t in (U, V, sigma)), seed
         ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
         assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0], seed
         got = U.double().cpu().numpy() @ V.double().cpu().numpy().T

@@ -21,6 +21,7 @@ def emu(tmp_path_factory):
     subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
     lib, d = ctypes.CDLL(out), ctypes.c_double
     lib.emu_orthogonal.argtypes = [d, d, d, d]
+    lib.emu_orthogonal_nil.argtypes = [d, d, d, d, d]
     lib.emu_rotation.argtypes = [d, d, d, ctypes.c_void_p]
     lib.emu_before.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
     return lib
@@ -44,6 +45,16 @@ def test_not_finite_is_not_orthogonal(emu):
     for a, b, g in ((1, 1, 0), (0, 0, 0), (1e80, 1e-80, 1e-14), (2.0, 0.0, 0.0)):
         assert emu.emu_orthogonal(a, b, g, 1e-13), (a, b, g)
     assert not emu.emu_orthogonal(4, 4, 1e-12, 1e-13)
+
+
+def test_rounding_noise_is_orthogonal(emu):
+    """Columns 2^-160 of the longest and shorter, or with a norm that rounding left below zero, count as zero; longer ones and what is
+    not finite do not."""
+    inf, nan, tiny = float("inf"), float("nan"), 2.0 ** -321
+    for a, b, g, longest, want in ((tiny, tiny, tiny, 1, 1), (-tiny, 1, 2 ** -161, 1, 1), (1, 0.0, 1e-300, 1, 1), (4 * tiny, 4 * tiny, 4 * tiny, 1, 0),
+                                   (4 * tiny, 4 * tiny, 4 * tiny, 16, 1), (1, 1, 1e-12, 1, 0), (nan, tiny, nan, 1, 0), (tiny, nan, nan, nan, 0),
+                                   (tiny, inf, inf, inf, 0), (tiny, tiny, tiny, inf, 0)):
+        assert bool(emu.emu_orthogonal_nil(a, b, g, 1e-13, longest)) == bool(want), (a, b, g, longest)
 
 
 def test_a_singular_value_that_is_not_finite_is_never_reported_as_converged(emu):
