@@ -48,18 +48,20 @@ __host__ __device__ __forceinline__ bool svd_before(double a, int i, double b, i
 }
 
 // Whether two columns with inner product gamma and squared norms alpha and beta are orthogonal to sqrt(tol2), relative.
-// A column whose squared norm is below `nil` is orthogonal to any.
+// A column whose squared norm is below `nil` is orthogonal to any, one below 2^120 nil to others like it.
 // Written so that NaN and infinity say no: a matrix that holds any never counts as converged.
 __host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
 {
-    const double g2 = gamma * gamma;
-    return (g2 <= tol2 * (alpha * beta) || alpha < nil || beta < nil) && g2 < __builtin_huge_val();
+    const double g2 = gamma * gamma, low = 0x1p120 * nil;
+    const bool noise = nil == 0.0 ? false : (alpha < nil) | (beta < nil) | ((alpha < low) & (beta < low));
+    return (g2 <= tol2 * (alpha * beta) || noise) && g2 < __builtin_huge_val();
 }
 
 // `nil` for columns of which the longest has squared norm `longest`.  The columns that a matrix of lower rank leaves over are rounding
-// noise, smaller with every sweep, but never orthogonal to one another: there is no room for them.  Down to 2^-160 of the longest
-// (of two floats that are that far apart the larger exceeds 2^11) a column counts, for a graded matrix may have such singular values;
-// below that it is zero.
+// noise, smaller with every sweep, but never orthogonal to one another: there is no room for them, and what a sweep takes out of one
+// the rotation against another brings back.  Below 2^-160 of the longest (of two floats that are that far apart the larger exceeds
+// 2^11) a column is zero; above, it counts, for a graded matrix may have such singular values, but from 2^-100 down it is made
+// orthogonal to longer ones only (576 x 64 of rank 20: 8 to 16 sweeps without, at most 24 before there was a limit).
 constexpr double SVD_NIL = 0x1p-320;
 __host__ __device__ __forceinline__ double svd_nil(double longest) { return longest < __builtin_huge_val() ? SVD_NIL * longest : 0.0; }
 
@@ -85,23 +87,29 @@ __host__ __device__ __forceinline__ double svd_rcp(double q)
     return y * (2.0 - q * y);
 }
 
+// x over the power of two that brings y into [1/2, 1)
+__host__ __device__ __forceinline__ double svd_scaled(double x, double y)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_ldexp(x, -__builtin_amdgcn_frexp_exp(y));
+#else
+    int e;
+    (void)frexp(y, &e);
+    return ldexp(x, -e);
+#endif
+}
+
 // The rotation (c, s) that takes gamma out of [[alpha, gamma], [gamma, beta]], all in double: s / c = t solves
 // t^2 + 2 z t - 1 = 0, z = (beta - alpha) / (2 gamma), |t| <= 1.  With d = beta - alpha and g = 2 gamma that is
-// t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that the larger of d and g is near 1: the arguments of the two approximations are then
+// t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that |d| + |g| is near 1: the arguments of the two approximations are then
 // in float's range, while t itself may be as small as it is.  (Not alpha + beta: what rounding leaves of the norm of a column that
 // rotations have all but cancelled, as in a matrix of lower rank, may be zero or below.)
 __host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
 {
     f64x2_t r = {1.0, 0.0};
     if (svd_orthogonal(alpha, beta, gamma, tol2, nil)) return r;
-#if defined(__HIP_DEVICE_COMPILE__)
-    const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(beta - alpha), fabs(2.0 * gamma)));
-    const double d = __builtin_amdgcn_ldexp(beta - alpha, e), g = __builtin_amdgcn_ldexp(2.0 * gamma, e);
-#else
-    int e;
-    (void)frexp(fmax(fabs(beta - alpha), fabs(2.0 * gamma)), &e);
-    const double d = ldexp(beta - alpha, -e), g = ldexp(2.0 * gamma, -e);
-#endif
+    const double d1 = beta - alpha, g1 = 2.0 * gamma, most = fabs(d1) + fabs(g1);
+    const double d = svd_scaled(d1, most), g = svd_scaled(g1, most);
     const double q = d * d + g * g, n = fabs(d) + q * svd_rsqrt(q), t = (d < 0.0 ? -g : g) * svd_rcp(n), c = svd_rsqrt(1.0 + t * t);
     r[0] = c;
     r[1] = c * t;

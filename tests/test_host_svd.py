@@ -48,12 +48,13 @@ def test_not_finite_is_not_orthogonal(emu):
 
 
 def test_rounding_noise_is_orthogonal(emu):
-    """Columns 2^-160 of the longest and shorter, or with a norm that rounding left below zero, count as zero; longer ones and what is
-    not finite do not."""
-    inf, nan, tiny = float("inf"), float("nan"), 2.0 ** -321
-    for a, b, g, longest, want in ((tiny, tiny, tiny, 1, 1), (-tiny, 1, 2 ** -161, 1, 1), (1, 0.0, 1e-300, 1, 1), (4 * tiny, 4 * tiny, 4 * tiny, 1, 0),
-                                   (4 * tiny, 4 * tiny, 4 * tiny, 16, 1), (1, 1, 1e-12, 1, 0), (nan, tiny, nan, 1, 0), (tiny, nan, nan, nan, 0),
-                                   (tiny, inf, inf, inf, 0), (tiny, tiny, tiny, inf, 0)):
+    """Columns 2^-160 of the longest and shorter, or with a norm that rounding left below zero, count as zero, two of 2^-100 as orthogonal
+    to each other; longer ones and what is not finite do not."""
+    inf, nan, tiny, low = float("inf"), float("nan"), 2.0 ** -321, 2.0 ** -201
+    for a, b, g, longest, want in ((tiny, tiny, tiny, 1, 1), (-tiny, 1, 2 ** -161, 1, 1), (1, 0.0, 1e-300, 1, 1), (4 * tiny, 1, 2 ** -160, 1, 0),
+                                   (4 * tiny, 1, 2 ** -160, 16, 1), (low, low, low, 1, 1), (low, 4 * low, low, 1, 0), (low, 1, 2 ** -101, 1, 0),
+                                   (1, 1, 1e-12, 1, 0), (nan, tiny, nan, 1, 0), (tiny, nan, nan, nan, 0), (tiny, inf, inf, inf, 0),
+                                   (tiny, tiny, tiny, inf, 0)):
         assert bool(emu.emu_orthogonal_nil(a, b, g, 1e-13, longest)) == bool(want), (a, b, g, longest)
 
 
