@@ -5,7 +5,7 @@
 // orthogonalises every pair of columns once per sweep; on A itself a sweep moves rows x cols numbers cols times and
 // eight or more sweeps follow.  So an orthogonal V comes first that does most of it:
 //   G = A^T A, V = its eigenvectors (pf_svd_eigen.hip), made orthonormal by two Newton steps V (3 I - V^T V) / 2, or, where
-//   eigenvalues that are one to rounding leave vectors that cannot be made so (and for few columns, and very many):
+//   close eigenvalues leave vectors that cannot be made so (and for few columns, and very many):
 //   G + shift I = L L^T, one-sided Jacobi on the cols x cols matrix L: L W = V S (no rotations accumulated: the normalised
 //   columns themselves are the eigenvectors of G; the shift, the rounding level of G, keeps L defined for any matrix);
 //   B = A V: columns orthogonal to about eps kappa^2.
@@ -15,10 +15,10 @@
 // Unless a second check is content, sweeps of the Jacobi iteration follow until one finds nothing to rotate.
 // So singular values far below the largest come out as exactly as without the preconditioner.
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
-// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.34 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.33
-// (rounding to float tells the values apart).  A matrix that has two singular values below 1e-8 of the largest, so that their
-// squares are one, and not by columns that are zero, pays for both: with Jacobi's alone / with both, ms, 300 x 60 with values down to
-// 1e-9 1.37 / 1.46, 576 x 64 of rank 8 1.67 / 1.87, 600 x 160 of rank 20 5.18 / 5.45, 2304 x 256 of rank 32 14.9 / 14.1.
+// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.35 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.3
+// (rounding to float tells the values apart); matrices of lower rank, whose noise takes sweeps either way, 576 x 64 of rank 8 1.67 and 1.22,
+// 2304 x 256 of rank 32 15.0 and 10.3, 1024 x 512 with 16 columns twice 17.2 and 7.8.  A matrix whose eigenvalues lie close without being
+// one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.46, 1024 x 256 8.9 / 9.2.
 //
 // A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
 // every column of one block against every column of the other (in a sweep's first round also within the blocks) found on

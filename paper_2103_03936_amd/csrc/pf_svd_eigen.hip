@@ -555,7 +555,14 @@ __global__ __launch_bounds__(256) void svd_unpack_kernel(double *L, double *T, i
 // All of it are chains of n steps.  The determinants follow a three-term recurrence, one dependent FMA per step, where a chain of
 // pivots has a reciprocal (512: 427 us with those, 170 now); T is scaled to norm 1/2 .. 1, and the last two determinants are scaled
 // back together every eight steps, in which they grow by 3^8 at most.  A pivot is the quotient of two neighbours.
-constexpr int SVD_CHUNK = 8;
+// Eigenvalues that are one to rounding (those of the null space of a matrix of lower rank, to begin with) would give vectors that are
+// one as well.  So where more than one lie in an interval of 65^-7, 2^-42, of the whole, their vectors are those of T with a diagonal
+// that grows by SVD_APART from row to row: distinct eigenvalues, far enough apart (2^-33) for vectors orthogonal to 1e-5, which the
+// Newton steps make so to rounding.  All wavefronts whose eigenvalue lies in the interval come to the same answer, and the others'
+// vectors need not change: they are orthogonal to these to n SVD_APART over the gap.  576 x 64 of rank 8, a call: 1.87 ms where the Jacobi
+// preconditioner came after such vectors, 1.22 now.
+constexpr int SVD_CHUNK = 8, SVD_ALIKE = 7;
+constexpr double SVD_APART = 1.0 / (1ll << 33);
 __device__ __forceinline__ void rescale(double &p0, double &p1)
 {
     const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
@@ -564,14 +571,14 @@ __device__ __forceinline__ void rescale(double &p0, double &p1)
 }
 __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, int ld)
 {
-    // T, (diagonal, squared subdiagonal above it) from the top, padded with rows that change no sign; then, per wavefront, what
-    // the two directions have, element by element from their ends on, padded to whole chunks
+    // T, (diagonal, squared subdiagonal above it) from the top, padded with rows that change no sign; then, per wavefront, the
+    // T of eigenvalues that are one, or what the two directions have, element by element from their ends on, padded to whole chunks
     extern __shared__ f64x2_t lds2[];
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK;
     f64x2_t *T = lds2;
     const double *E = D + n; // E[i]: between i and i + 1
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
-    double *top = (double *)(lds2 + np + 2 * SVD_CHUNK) + 2 * (np + SVD_CHUNK) * wave, *bottom = top + np + SVD_CHUNK;
+    double *top = (double *)(lds2 + (np + 2 * SVD_CHUNK) * (1 + wave)), *bottom = top + np + SVD_CHUNK;
     // all eigenvalues lie within the row sums
     double lo = __builtin_huge_val(), hi = -lo;
     for (int i = lane; i < n; i += 64) {
@@ -598,14 +605,30 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
     __syncthreads();
     const int j = blockIdx.x * waves + wave;
     if (j >= n) return;
+    const f64x2_t *S = T;
+    int fewer = 0, most = n; // eigenvalues below lo, and below hi
+    bool alike = false;
     for (int round = 0; round < 9; ++round) {
+        if (round == SVD_ALIKE && most - fewer > 1 && !alike) {
+            f64x2_t *own = (f64x2_t *)top;
+            for (int i = lane; i < np + 2 * SVD_CHUNK; i += 64) {
+                f64x2_t t = T[i];
+                t[0] = fma(SVD_APART, (double)i, t[0]);
+                own[i] = t;
+            }
+            wave_sync();
+            S = own;
+            alike = true;
+            hi += n * SVD_APART; // (the eigenvalues move up by less)
+            round = 4;
+        }
         const double x = lo + (hi - lo) * ((lane + 1) * (1.0 / 65.0));
         double p0 = 0.0, p1 = 1.0; // the last two determinants
         int below = 0;
         f64x2_t a[SVD_CHUNK], b[SVD_CHUNK]; // two chunks in turn: one is on its way from LDS while the other is worked on
         const auto fetch = [&](f64x2_t (&t)[SVD_CHUNK], int i) {
 #pragma unroll
-            for (int u = 0; u < SVD_CHUNK; ++u) t[u] = T[i + u];
+            for (int u = 0; u < SVD_CHUNK; ++u) t[u] = S[i + u];
             __builtin_amdgcn_sched_barrier(0);
         };
         const auto steps = [&](const f64x2_t (&t)[SVD_CHUNK]) {
@@ -629,9 +652,12 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
         const u64 above = __ballot(below > j);
         const int f = above ? __ffsll(above) - 1 : 64; // the first point with the eigenvalue below it
         const double nlo = f > 0 ? lo + (hi - lo) * (f * (1.0 / 65.0)) : lo, nhi = f < 64 ? lo + (hi - lo) * ((f + 1) * (1.0 / 65.0)) : hi;
+        if (f > 0) fewer = __builtin_amdgcn_readlane(below, f - 1);
+        if (f < 64) most = __builtin_amdgcn_readlane(below, f);
         lo = nlo;
         hi = nhi;
     }
+    wave_sync();
     const double lambda = 0.5 * (lo + hi);
     // determinants from the top (lane 0) and from the bottom (lane 1), and the pivots that they are quotients of
     double *mine = lane & 1 ? bottom : top;
@@ -644,6 +670,10 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
                 const int i = lane ? max(n - 1 - s - u, 0) : s + u;
                 di[u] = T[i][0] - lambda;
                 e2[u] = T[lane ? i + 1 : i][1];
+            }
+            if (alike) { // (S is no longer there)
+#pragma unroll
+                for (int u = 0; u < SVD_CHUNK; ++u) di[u] = fma(SVD_APART, (double)(lane ? n - 1 - s - u : s + u), di[u]);
             }
 #pragma unroll
             for (int u = 0; u < SVD_CHUNK; ++u) {
@@ -661,7 +691,7 @@ __global__ void svd_tridiag_vectors_kernel(const double *D, double *X, int n, in
     double best = __builtin_huge_val();
     int k = 0;
     for (int i = lane; i < n; i += 64) {
-        const double defect = fabs(top[i] + bottom[n - 1 - i] - (T[i][0] - lambda));
+        const double defect = fabs(top[i] + bottom[n - 1 - i] - (fma(alike ? SVD_APART : 0.0, (double)i, T[i][0]) - lambda));
         if (defect < best) best = defect, k = i;
     }
     for (int s = 32; s > 0; s >>= 1) {
@@ -794,10 +824,10 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, G, L, tau, place, ctrl, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);
     // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 151 us), else what 64 KB of LDS hold, or one: with
-    // more than 2032 columns that one takes 65920 bytes, of the 160 KB that a workgroup may have
+    // more than 2032 columns that one takes 66048 bytes, of the 160 KB that a workgroup may have
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 512 ? 2 : np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1;
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
-                  (size_t)(2 * (np + 2 * SVD_CHUNK) + 2 * waves * (np + SVD_CHUNK)) * 8, s, (const double *)T, X, n, ld);
+                  (size_t)(1 + waves) * (np + 2 * SVD_CHUNK) * 16, s, (const double *)T, X, n, ld);
     PF_LAUNCH(st, "svd_reflect", (svd_reflect_kernel<RPT, DEPTH>), dim3((n + 3) / 4), dim3(256), s, (const double *)L,
               (const double *)tau, X, n, ld);
     return st;
