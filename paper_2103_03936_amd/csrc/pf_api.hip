@@ -1,6 +1,9 @@
 // Status strings, error bookkeeping, per-kernel timing and the small utility kernels.
 #include <string.h>
 
+#include <string.h>
+
+#include <atomic>
 #include <vector>
 
 #include "pf_gemm.h"
@@ -25,6 +28,20 @@ struct TimingTotal {
     int64_t launches;
     double total_ms;
 };
+int cooperative_cus()
+{
+    static std::atomic<int> known[16]; // (0: not asked yet)
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (dev >= 0 && dev < 16 && known[dev].load(std::memory_order_relaxed) != 0)
+        return known[dev].load(std::memory_order_relaxed) - 1;
+    int n = 0, coop = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) n = 0;
+    if (dev >= 0 && dev < 16) known[dev].store(n + 1, std::memory_order_relaxed);
+    return n;
+}
+
 static bool g_timing_on = false;
 static std::vector<TimingRecord> g_pending;
 static std::vector<TimingTotal> g_totals;

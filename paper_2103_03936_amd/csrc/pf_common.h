@@ -89,6 +89,8 @@ __device__ __forceinline__ bf16x8_t lds_frag_tr(const uint16_t *tile, int pitch,
 // ------------------------------------------------------------ host helpers
 int set_hip_error(hipError_t e); // records e for pf_last_hip_error(), returns PF_ERR_LAUNCH
 
+int cooperative_cus();           // compute units of the current device, 0 if it cannot run cooperative launches
+
 struct TimingScope {
     TimingScope(const char *name, hipStream_t s);
     ~TimingScope();

@@ -24,7 +24,6 @@
 // and 0.6, gates 0.7.
 #include "pf_lstm_persist_index.h"
 
-#include <atomic>
 
 namespace pf {
 
@@ -650,17 +649,8 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
 // compute units of the current device that a launch may use, 0 if it cannot run cooperative launches
 static int lp_cus()
 {
-    static std::atomic<int> known[16]; // (0: not asked yet)
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (dev >= 0 && dev < 16 && known[dev].load(std::memory_order_relaxed) != 0)
-        return known[dev].load(std::memory_order_relaxed) - 1;
-    int n = 0, coop = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 0;
-    if (n > LP_MOST_CUS) n = LP_MOST_CUS;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) n = 0;
-    if (dev >= 0 && dev < 16) known[dev].store(n + 1, std::memory_order_relaxed);
-    return n;
+    const int n = cooperative_cus();
+    return n < LP_MOST_CUS ? n : LP_MOST_CUS;
 }
 
 // Whether the largest device could take the call, and what it needs there: sizes do not depend on the device (a workspace may be

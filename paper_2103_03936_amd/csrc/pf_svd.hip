@@ -798,7 +798,7 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void
     double *V = BV + p.lda; // (leading dimension ldb, as B's)
     const dim3 square((nc + 31) / 32, (nc + 31) / 32);
     // V: eigenvectors of G made orthonormal; where they cannot be (ctrl->mixed), and for few or very many columns, by Jacobi
-    const bool eigen = nc >= SVD_EIGEN_MIN && nc <= SVD_EIGEN_MAX;
+    const bool eigen = svd_takes_eigenvectors(nc, cooperative_cus());
     const unsigned *unless = eigen ? &ctrl->mixed : nullptr;
     int *const place = rank; // (before the ranks are there)
     PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn,

@@ -13,6 +13,16 @@ constexpr int SVD_NT = 512; // threads of the cooperative kernels
 // and 1340); above 2048 a column of the matrix exceeds what a wavefront keeps of it.
 constexpr int SVD_EIGEN_MIN = 17, SVD_EIGEN_MAX = 2048;
 
+// The columns that the reduction leaves to one workgroup; and the workgroups that have the others, of four or eight columns each,
+// which wait for one another.  A device that cannot hold them all at once (one per compute unit) does without them.
+constexpr int SVD_TAIL = 128;
+__host__ __device__ constexpr int svd_eigen_columns(int n) { return n <= 512 ? 4 : 8; }
+inline int svd_eigen_workgroups(int n) { return n <= SVD_TAIL ? 0 : (n + svd_eigen_columns(n) - 1) / svd_eigen_columns(n); }
+inline bool svd_takes_eigenvectors(int n, int cus)
+{
+    return n >= SVD_EIGEN_MIN && n <= SVD_EIGEN_MAX && svd_eigen_workgroups(n) <= cus;
+}
+
 // A launch whose workgroups are all resident (they wait for one another)
 template <class... ARGS>
 static int launch_cooperative(hipStream_t s, const char *name, void (*kernel)(ARGS...), int blocks, int threads, ARGS... args)

@@ -191,7 +191,6 @@ __device__ __forceinline__ double group_sum(double x, double *red)
 // NT > 64: the vectors are formed row tid + NT m per thread and handed to the wavefronts through LDS.
 // The last SVD_TAIL columns are left to svd_tridiag_tail_kernel: what they are by then goes back to G.
 // A wait is bounded; when it runs out, everyone leaves and ctrl->failed says so.
-constexpr int SVD_TAIL = 128;
 template <int RPT, int CPW, int NT>
 __global__ __launch_bounds__(NT) void svd_tridiag_kernel(double *G, double *L, double *tau_out, u64 *slots, SvdCtrl *ctrl, int n, int ld)
 {
@@ -818,8 +817,9 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
         const i64 blocks = (words + 1023) / 1024;
         PF_LAUNCH(st, "svd_slots", svd_slots_kernel<(64 * RPT + 255) / 256>, dim3((unsigned)(blocks < 1024 ? blocks : 1024) + 1), dim3(256), s, slots,
                   words, G, place, ctrl, n, ld);
+        static_assert(NT / 64 * CPW == svd_eigen_columns(64 * RPT), "a workgroup's columns");
         if (st == PF_OK)
-            st = launch_cooperative(s, "svd_tridiag", svd_tridiag_kernel<RPT, CPW, NT>, (n + NT / 64 * CPW - 1) / (NT / 64 * CPW), NT, G, L, tau, slots, ctrl, n, ld);
+            st = launch_cooperative(s, "svd_tridiag", svd_tridiag_kernel<RPT, CPW, NT>, svd_eigen_workgroups(n), NT, G, L, tau, slots, ctrl, n, ld);
     }
     PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, G, L, tau, place, ctrl, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);

@@ -1,6 +1,6 @@
 // The decisions of the Jacobi SVD on the host (test infrastructure, CPU only).  Built by tests/test_host_svd.py; nothing in
 // the product loads it.
-#include "pf_svd_pair.h"
+#include "pf_svd_eigen.h"
 
 using namespace pf;
 
@@ -16,6 +16,7 @@ void emu_rotation(double alpha, double beta, double gamma, double *cs)
     cs[0] = r[0], cs[1] = r[1];
 }
 int emu_before(double a, int i, double b, int j) { return svd_before(a, i, b, j); }
+int emu_takes_eigenvectors(int n, int cus) { return svd_takes_eigenvectors(n, cus); }
 void emu_outcome(unsigned failed, unsigned broken, unsigned sweeps, unsigned last, int nc, int *out)
 {
     SvdCtrl c = {};

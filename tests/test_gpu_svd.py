@@ -167,7 +167,7 @@ def test_close_singular_values_are_separated(m, n, big):
         assert err.max() <= bound, (err.max(), bound)
 
 
-@pytest.mark.parametrize("n", [16, 17, 63, 64, 65, 128, 129, 255, 257, 511, 513, 1023, 1025, 1537])
+@pytest.mark.parametrize("n", [16, 17, 63, 64, 65, 128, 129, 255, 257, 511, 513, 1023, 1025, 1537, 2033, 2048, 2049])
 def test_eigenvector_route(n):
     """Both sides of every size at which the tridiagonal preconditioner changes its split (16 columns: Jacobi's), odd sizes, tall and
     nearly square: float32 factors, so the oracle's product to a few roundings, and no rotations left."""

@@ -96,3 +96,11 @@ def test_rotation_of_cancelled_columns(emu):
                                (1e-30, -1e-30 * (1 - 2 ** -50), 1e-50), (0.0, 4e300, 1e-10), (0.0, 0.0, 5e-324)):
         emu.emu_rotation(alpha, beta, gamma, cs)
         assert abs(cs[0] ** 2 + cs[1] ** 2 - 1) <= 8 * 2.0 ** -53 and abs(cs[1]) <= 0.5 ** 0.5 * (1 + 2.0 ** -50), (alpha, beta, gamma)
+
+
+def test_workgroups_that_wait_for_one_another_are_all_resident(emu):
+    """The tridiagonal route is taken by devices with a compute unit for each of its workgroups, the Jacobi iteration by others."""
+    for n, workgroups in ((17, 0), (128, 0), (129, 33), (512, 128), (513, 65), (1537, 193), (2048, 256)):
+        assert emu.emu_takes_eigenvectors(n, workgroups) and emu.emu_takes_eigenvectors(n, 304)
+        assert workgroups == 0 or not emu.emu_takes_eigenvectors(n, workgroups - 1)
+    assert not emu.emu_takes_eigenvectors(16, 256) and not emu.emu_takes_eigenvectors(2049, 304)
