@@ -1,8 +1,6 @@
 // Status strings, error bookkeeping, per-kernel timing and the small utility kernels.
 #include <string.h>
 
-#include <string.h>
-
 #include <atomic>
 #include <vector>
 

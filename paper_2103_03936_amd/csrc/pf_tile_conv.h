@@ -64,7 +64,7 @@ tile_conv_kernel(TileArgs by_value)
             BP lb;
             lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
             tile_product<CT, CFG>(la, lb, nch, smem, tid);
-            if constexpr (GATHER) {
+            if constexpr (GATHER && PairOut<CT, CFG>::TAKEN) {
                 if (p.pair) {
                     const TileProb &p2 = a.p[t.prob + 1];
                     PairOut<CT, CFG> both;
@@ -128,6 +128,7 @@ static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
     bool gather = false, wg = false;
     for (int i = 0; i < a.n; ++i) {
         const TileProb &p = a.p[i];
+        if (p.pair && !PairOut<CT, CFG>::TAKEN) return PF_ERR_UNSUPPORTED;
         int b = BP::TAB;
         if (p.type == TILE_WG || p.type == TILE_WGT) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, false>::table_bytes(p.pb);
         if (p.type == TILE_WGG) b = (LoadPixKC<CT, 64, false>::table_bytes(p.pa) + 15) / 16 * 16 + LoadPixKC<CT, 64, true>::table_bytes(p.pb);

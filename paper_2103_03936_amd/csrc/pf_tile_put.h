@@ -111,6 +111,7 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
 // leave.  Pixel by pixel, as elements 2 apart, the store and what is added and masks took 15 of the 24 us of a 64 x 64 tile.
 template <typename CT, class CFG>
 struct PairOut {
+    static constexpr bool TAKEN = CFG::BM == 64 && CFG::BN == 64; // (the shape of these products' tiles)
     typedef typename TileEl<CT>::elem elem;
     static constexpr int V = TileEl<CT>::V, W2 = V / 2, CPR = CFG::BN / W2, P = CFG::BM * CPR / TILE_THREADS, PITCH = CFG::BN + 4;
     float c0[P][W2];
@@ -140,7 +141,8 @@ struct PairOut {
         if (n >= p.N || img >= o.N || pos >= o.HW) return;
         elem *c = (elem *)o.C;
         const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask;
-        const int per = 4; // pieces whose operands are in flight together
+        constexpr int per = 4; // pieces whose operands are in flight together
+        static_assert(P % per == 0 && TILE_THREADS % CPR == 0, "a thread's pieces are whole rounds, in the same pixels of every row");
 #pragma unroll
         for (int j0 = 0; j0 < P; j0 += per) {
             uint4 ra[per], rm[per];
