@@ -17,4 +17,20 @@ int emu_pair(int dtype, int shape, int wg)
     tile_pair(a);
     return launch_tiles_conv(nullptr, "pair", dtype, (TileShape)shape, (TileShape)wg, a);
 }
+
+// tile shape of a product [M][K] [K][N] of which the plan may split the contraction, and the split
+int emu_plan(int dtype, long long M, long long N, long long K, int max_split, int *split)
+{
+    const TilePlan p = plan_tiles(dtype, M, N, K, max_split);
+    *split = p.ksplit;
+    return p.shape;
+}
+// the same for the gradients of a layer [M][in] -> r -> out in one launch (dX, dU, dV)
+int emu_gradients(int dtype, long long M, long long in, long long out, long long r, int *split)
+{
+    const TileNeed need[3] = {{M, in, r, false}, {out, r, M, true, true}, {in, r, M, true, true}};
+    const TileGroup g = plan_tile_group(dtype, need, 3);
+    for (int i = 0; i < 3; ++i) split[i] = g.ksplit[i];
+    return g.shape;
+}
 }

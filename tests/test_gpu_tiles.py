@@ -18,9 +18,13 @@ LINEAR = [
     (257, 65, 127, 33),
     (1500, 129, 72, 17),     # gradients split over the rows
     (2050, 1032, 1160, 264),  # large tiles with ragged edges
-    (160, 517, 260, 37),      # one workgroup per compute unit: chunks of twice the length, the last one nearly empty or not whole,
-    (130, 2047, 40, 64),      # alone, and with the contraction split as well
+    (160, 517, 260, 37),      # one workgroup per compute unit: chunks of twice the length, the last one nearly empty or not whole
+    (130, 2047, 40, 64),
     (300, 255, 1030, 96),
+    (282, 3492, 400, 86),     # ... with the contraction split as well (float), into slices of 15 chunks or 7 1/2 long ones
+    (96, 4093, 300, 218),     # (both types)
+    (300, 256, 256, 250),     # ... and all gradients, with the bias's (float)
+    (515, 160, 150, 514),     # (bf16)
     (6337, 500, 264, 128),    # many rows, but too little for the larger tiles of
     (6337, 484, 1030, 128),   # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
 ]
@@ -151,17 +155,19 @@ def test_linear_routes_epilogue(M, n_in, n_out):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(3, 20, 16, 16, 24, 12, 3), (5, 9, 8, 24, 12, 8, 3), (2, 70, 12, 8, 16, 40, 3), (3, 12, 7, 9, 16, 8, 3),
-                                   (2, 16, 10, 6, 16, 8, 5), (1, 12, 2, 8, 12, 8, 3), (2, 16, 32, 4, 16, 8, 1)])
+                                   (2, 16, 10, 6, 16, 8, 5), (1, 12, 2, 8, 12, 8, 3), (2, 16, 32, 4, 16, 8, 1),
+                                   (3, 20, 16, 16, 24, 12, 2, 0), (5, 9, 6, 8, 12, 8, 2, 0), (2, 70, 10, 24, 16, 40, 4, 1), (3, 12, 9, 17, 16, 8, 2, 0)])
 def test_strided_conv_epilogue(shape, dtype):
     """Stride 2, input read by pairs of loads and the even and odd pixels of dX in one workgroup where rows hold whole pieces, and
-    where they do not; skip gradient and mask against the plain gradient: the same sums, added to and masked before one rounding."""
+    where they do not; even filters, whose padding is no half of them; skip gradient and mask against the plain gradient: the same sums, added to and masked before one rounding."""
     import torch
     import paper_2103_03936_amd as pf
-    N, C, H, W, Cout, r, k = shape
+    N, C, H, W, Cout, r, k, *p = shape
     dt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
     g = torch.Generator(device="cuda").manual_seed(H * W + k)
     n = lambda *s, std=1.0: (torch.randn(s, generator=g, device="cuda") * std).to(dt)
-    pad, Ho, Wo = k // 2, (H + 2 * (k // 2) - k) // 2 + 1, (W + 2 * (k // 2) - k) // 2 + 1
+    pad = p[0] if p else k // 2
+    Ho, Wo = (H + 2 * pad - k) // 2 + 1, (W + 2 * pad - k) // 2 + 1
     X, Uk, Vp, dY, add = n(N, C, H, W).clamp_(min=0), n(r, C, k, k, std=(C * k * k) ** -0.5), n(Cout, r, std=r ** -0.5), n(N, Cout, Ho, Wo), n(N, C, H, W)
     Y, T = pf.pf_lowrank_conv_fwd(X, Uk, Vp, 2, pad)
     want_T = torch.nn.functional.conv2d(X.double().cpu(), Uk.double().cpu(), stride=2, padding=pad)

@@ -33,3 +33,28 @@ def emu(tmp_path_factory):
 def test_paired_pixels_have_one_tile_shape(emu, dtype, shape):
     """The kernel that stores even and odd pixels together deals 64 x 64 tiles to its threads; other shapes are refused before a launch."""
     assert emu.emu_pair(dtype, shape, TS_64) == UNSUPPORTED
+
+
+def _plan(emu, dtype, M, N, K):
+    split = ctypes.c_int()
+    i64 = ctypes.c_longlong
+    return emu.emu_plan(dtype, i64(M), i64(N), i64(K), 16, ctypes.byref(split)), split.value
+
+
+def _gradients(emu, dtype, M, n_in, n_out, r):
+    split = (ctypes.c_int * 3)()
+    i64 = ctypes.c_longlong
+    return emu.emu_gradients(dtype, i64(M), i64(n_in), i64(n_out), i64(r), split), list(split)
+
+
+def test_plans_that_the_gpu_tests_count_on(emu):
+    """Shapes of test_gpu_tiles.LINEAR that stand for a tile shape reach it: 32 x 32 by eight wavefronts with and without a split, also for
+    gradients, and 128 x 128 gradients."""
+    for dtype in (F32, BF16):
+        assert _plan(emu, dtype, 96, 218, 4093) == (TS_32D, 8)
+    assert _plan(emu, F32, 282, 86, 3492) == (TS_32D, 7)
+    assert _plan(emu, F32, 160, 37, 260) == _plan(emu, BF16, 160, 37, 517) == (TS_32D, 1)
+    assert _gradients(emu, F32, 300, 256, 256, 250)[0] == _gradients(emu, BF16, 515, 160, 150, 514)[0] == TS_32D
+    shape, split = _gradients(emu, BF16, 6337, 484, 1030, 128)
+    assert shape == TS_128 and split[1] == split[2] > 1
+    assert _gradients(emu, BF16, 6337, 500, 264, 128)[0] == TS_64
