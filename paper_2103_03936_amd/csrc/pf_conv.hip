@@ -676,7 +676,7 @@ static int conv_bwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X,
     if (st != PF_OK) return st;
     WgradReduceArgs r0{part_dUk, dUk, p.wg_groups, T, g.r, g.C, (i64)g.C * T, T, 1, accumulate, nullptr};
     WgradReduceArgs r1{part_dVp, dVp, p.wg_groups2, 1, g.r, g.Cout, 1, g.r, 0, accumulate, ep.scale}; // dVp = scale (dZ T^T)
-    const ColsumTilesArgs cs{nullptr, ep.dshift, 0, g.Cout, accumulate, (const uint16_t *)dY, g.N, g.Ho * g.Wo};
+    const ColsumTilesArgs cs{nullptr, ep.dshift, 0, g.Cout, accumulate, dY, g.N, g.Ho * g.Wo};
     return launch_wgrad_reduce(s, r0, r1, ep.dshift ? &cs : nullptr);
 }
 

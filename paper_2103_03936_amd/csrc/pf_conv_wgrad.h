@@ -28,7 +28,7 @@ struct ColsumTilesArgs {
     const float *partial;
     float *out;
     int tiles, cols, accumulate;
-    const uint16_t *planes;
+    const bf16_t *planes;
     int N, HW;
 };
 

@@ -15,6 +15,7 @@
 // MFMA fragment is one aligned 16-byte LDS read.  For a 3x3 stage the B rows are staged three times, shifted
 // by tx - 1 with the zero border baked in.
 #include "pf_conv_wgrad.h"
+#include "pf_plane_sum.h"
 
 namespace pf {
 
@@ -374,47 +375,6 @@ __global__ __launch_bounds__(WG_THREADS, 1) void conv_wgrad_pair_kernel(WgradArg
     } else {
         conv_wgrad_body<1, MB2, 4, HC, WC>(a2, (b - nwg1) % nx2, (b - nwg1) / nx2, 0, wg_lds);
     }
-}
-
-// The sum of channel c over N images [C][HW], in thread 0: planes of whole 16-byte pieces are read so, four in flight per thread.
-__device__ float plane_sum(const uint16_t *planes, int c, int N, int C, int HW)
-{
-    const auto f = [](uint32_t bits) { return __uint_as_float(bits); };
-    const int tid = threadIdx.x;
-    float acc = 0.f;
-    if (HW % 8 == 0) {
-        const int pv = HW / 8;
-        const i64 count = (i64)N * pv;
-        for (i64 i0 = tid; i0 < count; i0 += 1024) {
-            u32x4 v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const i64 i = i0 + 256 * u < count ? i0 + 256 * u : count - 1;
-                const int n = (int)(i / pv), q = (int)(i - (i64)n * pv);
-                v[u] = *(const u32x4_alias *)(planes + ((i64)n * C + c) * HW + (i64)q * 8);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float e[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) e[k] = f(v[u][k] << 16) + f(v[u][k] & 0xffff0000u);
-                acc += i0 + 256 * u < count ? (e[0] + e[1]) + (e[2] + e[3]) : 0.f;
-            }
-        }
-    } else {
-        for (i64 i = tid; i < (i64)N * HW; i += 256) {
-            const int n = (int)(i / HW), p = (int)(i - (i64)n * HW);
-            acc += f((uint32_t)planes[((i64)n * C + c) * HW + p] << 16);
-        }
-    }
-    __shared__ float red[256];
-    red[tid] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
-    return red[0];
 }
 
 // out[m * s_m + n * s_n + tap * s_tap] (+)= sum_g partial[g][tap][m][n]; four consecutive n per output

@@ -8,6 +8,7 @@
 // the output); where the layer runs on the fused chain kernels those apply it as they store (pf_conv_chain.hip,
 // pf_linear_chain.hip) and nothing is launched here.
 #include "pf_epilogue.h"
+#include "pf_plane_sum.h"
 
 namespace pf {
 
@@ -138,42 +139,13 @@ __global__ __launch_bounds__(256) void dvp_finish_kernel(const float *raw, const
     }
 }
 
-// out[c] (+)= sum over images and pixels of dZ[n][c][p]: one workgroup per channel, fixed summation order.
-// Planes that are a whole number of 16-byte pieces are read eight (bf16) or four (float) elements at a time.
+// out[c] (+)= sum over images and pixels of dZ[n][c][p]: one workgroup per channel
 template <typename T>
 __global__ __launch_bounds__(256) void channel_sum_kernel(const T *dZ, float *out, int N, int C, int HW, int accumulate)
 {
-    const int c = blockIdx.x, tid = threadIdx.x;
-    constexpr int V = 16 / sizeof(T);
-    float acc = 0.f;
-    if (HW % V == 0) {
-        const int pv = HW / V; // pieces per plane
-        for (i64 i = tid; i < (i64)N * pv; i += 256) {
-            const int n = (int)(i / pv), q = (int)(i - (i64)n * pv);
-            const T *src = dZ + ((i64)n * C + c) * HW + (i64)q * V;
-            if (sizeof(T) == 2) {
-                float f[8];
-                load8<T>(src, f);
-                acc += ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
-            } else {
-                const float4 v = *(const float4 *)src;
-                acc += (v.x + v.y) + (v.z + v.w);
-            }
-        }
-    } else {
-        for (i64 i = tid; i < (i64)N * HW; i += 256) {
-            const int n = (int)(i / HW), p = (int)(i - (i64)n * HW);
-            acc += to_float(dZ[((i64)n * C + c) * HW + p]);
-        }
-    }
-    __shared__ float red[256];
-    red[tid] = acc;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
-    if (tid == 0) out[c] = accumulate ? out[c] + red[0] : red[0];
+    const int c = blockIdx.x;
+    const float total = plane_sum(dZ, c, N, C, HW);
+    if (threadIdx.x == 0) out[c] = accumulate ? out[c] + total : total;
 }
 
 template <typename T>
