@@ -93,17 +93,21 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
     //   53.7),
     //   where the plan above has nearly seven workgroups to a compute unit or more, which hide each other's waits (7500, 1000 -> 128 ->
     //   256 34.6 / 49.4), or splits more than five ways, so that its chunks are few (20000, 320 -> 128 -> 128 33.1 / 56.9),
-    //   or where it brings less than 400 KB into a compute unit (8192, 384 -> 128 -> 384 25.7 / 30.1).
-    // Measured over 6750 shapes of 6000 to 40000 rows, widths 64 to 4096, ranks 128 to 512, one to four layers, that pass all but the
-    // last two lines (which alone are 0.89 of the plan above, geometric mean, 976 of them more than 5 % slower than it, at most 1.7
-    // times): 4461 are taken, 0.83 of the plan above, 104 of them more than 5 % slower, at most 1.25 times.
+    //   where it brings less than 400 KB into a compute unit (8192, 384 -> 128 -> 384 25.7 / 30.1),
+    //   or where padding takes more than a seventeenth of the work (10183, 576 -> 128 -> 1344 47.5 / 56.8; 7740, 832 -> 128 -> 176 34 / 39).
+    // Measured over 399 shapes of 6000 to 40000 rows, widths 64 to 4096, ranks 128 to 512, one to four layers, that pass all but the
+    // last line: 0.88 of the plan above (geometric mean), but 31 more than 5 % slower, at most 1.24 times.  180 are taken, 0.86 of the
+    // plan above, one of them more than 5 % slower (1.06).
     if (bf && n == 3 && need[1].tn && need[2].tn && need[1].K >= 6000 && need[1].N % 128 == 0 && need[2].N % 128 == 0 && best.ksplit[1] <= 5 &&
         best.ksplit[2] <= 5) {
         const auto tiles = [&](int i, TileShape sh) {
             return ((need[i].M + SHAPES[sh].bm - 1) / SHAPES[sh].bm) * ((need[i].N + SHAPES[sh].bn - 1) / SHAPES[sh].bn);
         };
         i64 now = 0, bytes = 0; // workgroups of the plan above, and what they bring into all compute units
+        double work = 0, dealt = 0; // of all products; of their 128 x 128 tiles
         for (int i = 0; i < 3; ++i) {
+            work += (double)need[i].M * need[i].N * need[i].K;
+            dealt += 128.0 * 128.0 * tiles(i, TS_128) * need[i].K;
             now += tiles(i, best.shape) * best.ksplit[i];
             bytes += tiles(i, best.shape) * need[i].K * (SHAPES[best.shape].bm + SHAPES[best.shape].bn) * 2;
         }
@@ -111,7 +115,8 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
         i64 ks = rest / each;
         for (int i = 1; i < 3; ++i)
             while (ks > 1 && ks * need[i].M * need[i].N > (2 << 20)) --ks;
-        if (ks >= 1 && rest >= each && tiles(0, TS_128) + ks * each >= 384 && need[1].K <= 64 * 32 * ks && now <= 1740 && bytes >= 256 * 400 * 1024) {
+        if (ks >= 1 && rest >= each && tiles(0, TS_128) + ks * each >= 384 && need[1].K <= 64 * 32 * ks && now <= 1740 &&
+            bytes >= 256 * 400 * 1024 && work >= 0.94 * dealt) {
             best.shape = TS_128;
             best.ksplit[0] = 1;
             best.ksplit[1] = best.ksplit[2] = (int)ks;

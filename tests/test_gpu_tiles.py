@@ -26,7 +26,8 @@ LINEAR = [
     (300, 256, 256, 250),     # ... and all gradients, with the bias's (float)
     (515, 160, 150, 514),     # (bf16)
     (6337, 500, 264, 128),    # many rows, but too little for the larger tiles of
-    (6337, 484, 1030, 128),   # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
+    (6337, 484, 1030, 128),   # (too much padding for them)
+    (6500, 489, 985, 128),    # bf16 gradients on 128 x 128 tiles, two workgroups per compute unit
 ]
 
 CONV = [
@@ -61,7 +62,7 @@ def test_lstm_cell(shape, groups):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3),
-                                   (6100, 264, 330, 128, 3)])
+                                   (6100, 264, 330, 128, 3), (6100, 380, 378, 128, 3)])
 def test_linear_shared(shape, dtype):
     """The second one splits the contraction of dT, whose layers then lie one after the other instead of side by side; the last one's
     bf16 gradients are on 128 x 128 tiles, of which none is shared by two layers."""
