@@ -15,10 +15,11 @@
 // needed before the sum.
 //
 // Between phases a wavefront waits for the tasks whose results it reads, and for no others: a task that is done stores the
-// slot's number to its flag, in eight copies, and the readers poll the 6 to 48 flags that fill their contraction indices, those of
-// a die in one copy.  Before, a barrier over all workgroups (arrivals counted in eight groups, whose last tell eight copies of the
-// group flags) cost 1.9 us a phase: an atomic's round trip more, and everybody waited for the slowest.  Whole calls, us: 1500
-// units, two layers, batch 20, 35 steps 1266 -> 1242; 650 units 818 -> 762; 256 units, three layers, batch 4, 70 steps 865 -> 762.
+// slot's number to its flag, in eight copies, and the readers poll the flags of those that fill their contraction indices (2 at
+// 128 units, 48 at most), those of a die in one copy.  Before, a barrier over all workgroups (arrivals counted in eight groups,
+// whose last tell eight copies of the group flags) cost 1.9 us a phase: an atomic's round trip more, and everybody waited for the
+// slowest.  Whole calls, us: 1500 units, two layers, batch 20, 35 steps 1266 -> 1242; 650 units 818 -> 762; 256 units, three
+// layers, batch 4, 70 steps 865 -> 762.
 // (One copy of the flags: 1376; the pollers get in each other's way.)  What a slot of 11 us consists of now at 1500 units, forward:
 // two hand-overs of 0.9, the first reads of what was handed over 0.8 each, matrix instructions 0.8 and 2.4, the wavefronts' sums 0.3
 // and 0.6, gates 0.7.

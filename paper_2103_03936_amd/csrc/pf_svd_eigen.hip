@@ -552,8 +552,9 @@ __global__ __launch_bounds__(256) void svd_unpack_kernel(double *L, double *T, i
 // from the top (lane 0) and from the bottom (lane 1); where the two meet with the smallest defect the vector is 1, outward it
 // follows from the pivots.
 // All of it are chains of n steps.  The determinants follow a three-term recurrence, one dependent FMA per step, where a chain of
-// pivots has a reciprocal (512: 427 us with those, 170 now); T is scaled to norm 1/2 .. 1, and the last two determinants are scaled
-// back together every eight steps, in which they grow by 3^8 at most.  A pivot is the quotient of two neighbours.
+// pivots has a reciprocal (512, four wavefronts a workgroup: 427 us with those, 170 so); T is scaled to norm 1/2 .. 1, and the
+// last two determinants are scaled back together every eight steps, in which they grow by 3^8 at most.  A pivot is the quotient of
+// two neighbours.
 // Eigenvalues that are one to rounding (those of the null space of a matrix of lower rank, to begin with) would give vectors that are
 // one as well.  So where more than one lie in an interval of 65^-7, 2^-42, of the whole, their vectors are those of T with a diagonal
 // that grows by SVD_APART from row to row: distinct eigenvalues, far enough apart (2^-33) for vectors orthogonal to 1e-5, which the
@@ -823,7 +824,7 @@ static int eigenvectors(hipStream_t s, double *G, double *L, double *tau, double
     }
     PF_LAUNCH(st, "svd_tridiag_tail", svd_tridiag_tail_kernel, dim3(1), dim3(256), s, G, L, tau, place, ctrl, n, ld);
     PF_LAUNCH(st, "svd_unpack", svd_unpack_kernel, dim3(n), dim3(256), s, L, T, n, ld);
-    // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 151 us), else what 64 KB of LDS hold, or one: with
+    // two wavefronts per workgroup while those do not fill the chip (512: 171 -> 149 us), else what 64 KB of LDS hold, or one: with
     // more than 2032 columns that one takes 66048 bytes, of the 160 KB that a workgroup may have
     const int np = (n + SVD_CHUNK - 1) / SVD_CHUNK * SVD_CHUNK, waves = np <= 512 ? 2 : np <= 800 ? 4 : np <= 1000 ? 3 : np <= 1344 ? 2 : 1;
     PF_LAUNCH_LDS(st, "svd_tridiag_vectors", svd_tridiag_vectors_kernel, dim3((n + waves - 1) / waves), dim3(64 * waves),
