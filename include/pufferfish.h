@@ -456,13 +456,13 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x,
 /* W[c_out, c_in, k, k] to [c_in k^2, c_out] first (Section 2.2).       */
 /* Sweeps stop once a whole sweep found every column pair orthogonal to */
 /* max(m,n) * 2^-52 relative (the rounding level of the inner products; */
-/* at least 1e-15); at most 24 sweeps run.                              */
+/* at least 1e-15); at most 40 sweeps run.                              */
 /* The call is asynchronous, so convergence cannot                      */
 /* come back in the status: info (nullable, DEVICE int[2]) receives     */
 /* info[0] = sweeps over the columns of W that ran (they start from a   */
 /* preconditioned basis, whose own sweeps are not counted; checking it  */
 /* is the first), info[1] = rotations applied in the last               */
-/* of them -- 0 means converged; anything else means the 24 sweeps did  */
+/* of them -- 0 means converged; anything else means the 40 sweeps did  */
 /* not suffice and the factors are approximate, or that W holds NaN or  */
 /* infinity, which then show in the outputs.  (The workgroups wait      */
 /* for one another in bounded waits; should one ever run out, all       */

@@ -13,12 +13,15 @@
 // What is not orthogonal is taken out, V carried along: by B (I + K), K the first-order rotations from the Gram matrix, where
 // they are so small that I + K is orthogonal to rounding, otherwise by rotations of the pairs of blocks that hold some.
 // Unless a second check is content, sweeps of the Jacobi iteration follow until one finds nothing to rotate.
-// So singular values far below the largest come out as exactly as without the preconditioner.
+// So singular values far below the largest come out as exactly as without the preconditioner, down to 2^-92 of it or so (V carries
+// 2^-52 of the long columns into the short ones, and what A V rounds of that stays).
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
 // 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.35 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.3
 // (rounding to float tells the values apart); matrices of lower rank, whose noise takes sweeps either way, 576 x 64 of rank 8 1.67 and 1.22,
 // 2304 x 256 of rank 32 15.0 and 10.3, 1024 x 512 with 16 columns twice 17.2 and 7.8.  A matrix whose eigenvalues lie close without being
-// one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.46, 1024 x 256 8.9 / 9.2.
+// one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.46, 1024 x 256 8.9 / 9.3.  So does
+// one in two blocks that share no row and no column, the first of lower rank and the other 1e-9 of it, whose columns the noise gets
+// among: 1024 x 256 12.4 / 18.0 (1e-6 of it: 12.1 / 8.6).
 //
 // A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
 // every column of one block against every column of the other (in a sweep's first round also within the blocks) found on
@@ -420,8 +423,8 @@ __device__ __forceinline__ void svd_rotate_row(const f64x2_t *cs, double (&x)[16
 // pairs were rotated; large_pair: some pair was farther from orthogonal than SVD_SMALL.  known (nullable): the Gram matrix of all
 // columns as it was before this sweep; where it says that every pair is orthogonal nothing is read.
 constexpr double SVD_SMALL = 3e-8; // rotations this small leave their square: orthogonal to rounding level
-__device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr, int rows, int p, int q, bool within, double tol, double nil,
-                                              SvdShared &sh, bool &large_pair, const double *known, int ldk)
+__device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr, int rows, int p, int q, bool within, double tol, SvdShort few,
+                                              SvdShared &sh, bool &large_pair, bool &held_pair, const double *known, int ldk)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
     constexpr int NW = SVD_NT / 64;
@@ -430,7 +433,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
     if (known) {
         const int i = tid >> 4 & 15, j = tid & 15, ci = column(i), cj = column(j);
         const bool some = candidate(i, j) && ci < nc && cj < nc &&
-                          !svd_orthogonal(known[(i64)ci * ldk + ci], known[(i64)cj * ldk + cj], known[(i64)cj * ldk + ci], tol * tol, nil);
+                          !svd_orthogonal(known[(i64)ci * ldk + ci], known[(i64)cj * ldk + cj], known[(i64)cj * ldk + ci], tol * tol, few.nil, few.low);
         if (!__syncthreads_or(some)) return 0;
     }
     // Gram matrix, rows dealt to the wavefronts eight at a time, eight pieces in flight; the rows that this thread will
@@ -475,14 +478,16 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
             b += sh.part[w][j][j];
         }
         sh.g[i][j] = y;
-        const bool some = candidate(i, j) && !svd_orthogonal(a, b, y, tol2, nil), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
-        const bool anyone = __any(some), anylarge = __any(large);
-        if (lane == 0) sh.any[wave] = anylarge ? 2 : anyone ? 1 : 0;
+        const bool some = candidate(i, j) && !svd_orthogonal(a, b, y, tol2, few.nil, few.low), large = some && y * y > SVD_SMALL * SVD_SMALL * (a * b);
+        const bool held = few.low > 0.0 && candidate(i, j) && !some && !svd_orthogonal(a, b, y, tol2, few.nil);
+        const bool anyone = __any(some), anylarge = __any(large), anyheld = __any(held);
+        if (lane == 0) sh.any[wave] = (anyone ? 1 : 0) | (anylarge ? 2 : 0) | (anyheld ? 4 : 0);
     }
     __syncthreads();
-    const int any = max(max(sh.any[0], sh.any[1]), max(sh.any[2], sh.any[3]));
-    large_pair = any > 1;
-    if (!any) return 0;
+    const int any = sh.any[0] | sh.any[1] | sh.any[2] | sh.any[3];
+    large_pair = any & 2;
+    held_pair = any & 4;
+    if (!(any & 1)) return 0;
     int rotations = 0;
     if (wave == 0) {
         // lane (a, b) owns the four entries where row pair a meets column pair b
@@ -490,7 +495,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
         for (int t = 0; t < rounds; ++t) {
             const int i0 = svd_inner_lo(t, a), i1 = svd_inner_hi(t, a), j0 = svd_inner_lo(t, b), j1 = svd_inner_hi(t, b);
             const double g00 = sh.g[i0][j0], g01 = sh.g[i0][j1], g10 = sh.g[i1][j0], g11 = sh.g[i1][j1];
-            const f64x2_t rb = svd_rotation(sh.g[j0][j0], sh.g[j1][j1], sh.g[j0][j1], tol2, nil);
+            const f64x2_t rb = svd_rotation(sh.g[j0][j0], sh.g[j1][j1], sh.g[j0][j1], tol2, few.nil, few.low);
             f64x2_t ra; // that of row pair a: lane (0, a) has it
             ra[0] = __shfl(rb[0], a, 64);
             ra[1] = __shfl(rb[1], a, 64);
@@ -522,7 +527,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
 
 // At most `most` sweeps, until one rotates nothing -- or, with `quick`, nothing but small angles.  Returns false when a barrier
 // gave up.
-__device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, double nil, int most, unsigned *arrived,
+__device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, SvdShort few, int most, unsigned *arrived,
                                            unsigned &generation, unsigned *rot, bool quick, SvdCtrl *ctrl, SvdShared &sh,
                                            int *ran, const double *known = nullptr, int ldk = 0)
 {
@@ -537,8 +542,9 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
                     p = q;
                     q = t;
                 }
-                bool large = false;
-                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, nil, sh, large, known, ldk);
+                bool large = false, held = false;
+                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, few, sh, large, held, known, ldk);
+                if (held && threadIdx.x == 0) __hip_atomic_store(&ctrl->held[sweep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (did > 0 && (large || !quick) && threadIdx.x == 0)
                     __hip_atomic_fetch_add(&rot[sweep], (unsigned)did, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads(); // (the LDS tables are used again)
@@ -546,6 +552,10 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
             if (!svd_grid_barrier(arrived, &ctrl->failed, generation, gridDim.x)) return false;
         }
         if (__hip_atomic_load(&rot[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+            if (few.low > 0.0 && __hip_atomic_load(&ctrl->held[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                few.low = 0.0; // the short columns' turn
+                continue;
+            }
             ++sweep;
             break;
         }
@@ -649,7 +659,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, dou
         if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
     }
     int ran = 0;
-    (void)svd_sweeps(L, ld, nc, nc, nc, tol, 0.0, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
+    (void)svd_sweeps(L, ld, nc, nc, nc, tol, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
 }
 
 // One-sided Jacobi on B with V carried along, when a check found pairs to rotate.  First one sweep over the pairs of blocks that
@@ -663,24 +673,25 @@ __global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, const do
     int ran = 0;
     bool ok = ctrl->failed == 0u;
     const unsigned found = first ? (ctrl->coarse[0] ? ctrl->violations[0] : 0u) : ctrl->violations[1]; // (else corrected already)
-    double nil = 0.0;
+    SvdShort few = {0.0, 0.0};
     if (ok && found != 0u) {
-        for (int j = threadIdx.x; j < nc; j += SVD_NT) nil = fmax(nil, G[(i64)j * ldg + j]);
-        for (int s = 32; s > 0; s >>= 1) nil = fmax(nil, __shfl_xor(nil, s, 64));
-        if ((threadIdx.x & 63) == 0) sh.part[0][0][threadIdx.x >> 6] = nil;
+        double longest = 0.0;
+        for (int j = threadIdx.x; j < nc; j += SVD_NT) longest = fmax(longest, G[(i64)j * ldg + j]);
+        for (int s = 32; s > 0; s >>= 1) longest = fmax(longest, __shfl_xor(longest, s, 64));
+        if ((threadIdx.x & 63) == 0) sh.part[0][0][threadIdx.x >> 6] = longest;
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < SVD_NT / 64; ++w) nil = fmax(nil, sh.part[0][0][w]);
-        nil = svd_nil(nil);
+        for (int w = 0; w < SVD_NT / 64; ++w) longest = fmax(longest, sh.part[0][0][w]);
+        few = svd_short(longest);
         __syncthreads();
-        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, nil, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
+        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, few, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
                         ctrl->rot[first ? 1 : 2], false, ctrl, sh, &ran, first ? G : nullptr, ldg);
     }
     if (!first && blockIdx.x == 0 && threadIdx.x == 0) {
         // (a check that found nothing counts as one clean sweep)
         ctrl->sweeps = !ok ? SVD_MAX_SWEEPS : ctrl->violations[0] == 0u ? 1 : found == 0u ? 2 : 1 + ran;
         ctrl->last = !ok ? 1u : found == 0u ? 0u : ctrl->rot[2][ran - 1];
-        ctrl->nil = nil;
+        ctrl->nil = few.nil;
     }
 }
 

@@ -7,7 +7,7 @@
 
 namespace pf {
 
-constexpr int SVD_MAX_SWEEPS = 24;
+constexpr int SVD_MAX_SWEEPS = 40;
 typedef __attribute__((ext_vector_type(2))) double f64x2_t;
 
 // Device-side state of a call
@@ -20,9 +20,10 @@ struct SvdCtrl {
     unsigned coarse[2];     // (per check) some column of B is farther from orthogonal than one correction takes out
     unsigned violations[2]; // pairs of B that are not orthogonal after the preconditioner, and after the first correction or sweep
     unsigned rot[3][SVD_MAX_SWEEPS + 1]; // pairs rotated per sweep: of L (in pairs of blocks with a large angle), of B first, of B then
+    unsigned held[SVD_MAX_SWEEPS + 1];   // whether a sweep of B left pairs of short columns as they were
     unsigned sweeps;        // sweeps over the pairs of B, a check that found nothing included
     unsigned last;          // pairs rotated in the last of them
-    double nil;             // squared norm below which the sweeps took a column of B for zero
+    double nil;             // squared norm below which a column of B is zero
 };
 
 // What a call reports: sweeps, rotations of the last one, and whether its outputs are worth nothing because a barrier's wait
@@ -48,22 +49,28 @@ __host__ __device__ __forceinline__ bool svd_before(double a, int i, double b, i
 }
 
 // Whether two columns with inner product gamma and squared norms alpha and beta are orthogonal to sqrt(tol2), relative.
-// A column whose squared norm is below `nil` is orthogonal to any, one below 2^120 nil to others like it.
+// A column whose squared norm is below `nil` is orthogonal to any, one below `low` to others like it.
 // Written so that NaN and infinity say no: a matrix that holds any never counts as converged.
-__host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
+__host__ __device__ __forceinline__ bool svd_orthogonal(double alpha, double beta, double gamma, double tol2, double nil = 0.0, double low = 0.0)
 {
-    const double g2 = gamma * gamma, low = 0x1p120 * nil;
+    const double g2 = gamma * gamma;
     const bool noise = nil == 0.0 ? false : (alpha < nil) | (beta < nil) | ((alpha < low) & (beta < low));
     return (g2 <= tol2 * (alpha * beta) || noise) && g2 < __builtin_huge_val();
 }
 
-// `nil` for columns of which the longest has squared norm `longest`.  The columns that a matrix of lower rank leaves over are rounding
+// The two for columns of which the longest has squared norm `longest`.  The columns that a matrix of lower rank leaves over are rounding
 // noise, smaller with every sweep, but never orthogonal to one another: there is no room for them, and what a sweep takes out of one
-// the rotation against another brings back.  Below 2^-160 of the longest (of two floats that are that far apart the larger exceeds
-// 2^11) a column is zero; above, it counts, for a graded matrix may have such singular values, but from 2^-100 down it is made
-// orthogonal to longer ones only (576 x 64 of rank 20: 8 to 16 sweeps without, at most 24 before there was a limit).
-constexpr double SVD_NIL = 0x1p-320;
-__host__ __device__ __forceinline__ double svd_nil(double longest) { return longest < __builtin_huge_val() ? SVD_NIL * longest : 0.0; }
+// the rotation against another brings back.  Below 2^-280 of the longest, less than any float is of another, a column is zero.
+// From 2^-100 down columns are held back from one another until the longer ones take no more rotations: noise is gone by then,
+// and what a graded matrix has of singular values so small is still separated.  (Sweeps for 576 x 64 of rank 40: 13, 7 now; of rank 20,
+// where a limit of 2^-160 and no holding back takes 24 or more: 18 at most.)
+struct SvdShort {
+    double nil, low;
+};
+__host__ __device__ __forceinline__ SvdShort svd_short(double longest)
+{
+    return longest < __builtin_huge_val() ? SvdShort{0x1p-560 * longest, 0x1p-200 * longest} : SvdShort{0.0, 0.0};
+}
 
 // 1 / sqrt(q) and 1 / q to a few units of the last place: a float approximation (23 bits) and two Newton steps in double.
 __host__ __device__ __forceinline__ double svd_rsqrt(double q)
@@ -104,10 +111,11 @@ __host__ __device__ __forceinline__ double svd_scaled(double x, double y)
 // t = +-g / (|d| + sqrt(d^2 + g^2)), scaled so that |d| + |g| is near 1: the arguments of the two approximations are then
 // in float's range, while t itself may be as small as it is.  (Not alpha + beta: what rounding leaves of the norm of a column that
 // rotations have all but cancelled, as in a matrix of lower rank, may be zero or below.)
-__host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2, double nil = 0.0)
+__host__ __device__ __forceinline__ f64x2_t svd_rotation(double alpha, double beta, double gamma, double tol2, double nil = 0.0,
+                                                         double low = 0.0)
 {
     f64x2_t r = {1.0, 0.0};
-    if (svd_orthogonal(alpha, beta, gamma, tol2, nil)) return r;
+    if (svd_orthogonal(alpha, beta, gamma, tol2, nil, low)) return r;
     const double d1 = beta - alpha, g1 = 2.0 * gamma, most = fabs(d1) + fabs(g1);
     const double d = svd_scaled(d1, most), g = svd_scaled(g1, most);
     const double q = d * d + g * g, n = fabs(d) + q * svd_rsqrt(q), t = (d < 0.0 ? -g : g) * svd_rcp(n), c = svd_rsqrt(1.0 + t * t);

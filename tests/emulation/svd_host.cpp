@@ -6,9 +6,10 @@ using namespace pf;
 
 extern "C" {
 int emu_orthogonal(double alpha, double beta, double gamma, double tol) { return svd_orthogonal(alpha, beta, gamma, tol * tol); }
-int emu_orthogonal_nil(double alpha, double beta, double gamma, double tol, double longest)
+int emu_orthogonal_short(double alpha, double beta, double gamma, double tol, double longest, int hold)
 {
-    return svd_orthogonal(alpha, beta, gamma, tol * tol, svd_nil(longest));
+    const SvdShort few = svd_short(longest);
+    return svd_orthogonal(alpha, beta, gamma, tol * tol, few.nil, hold ? few.low : 0.0);
 }
 void emu_rotation(double alpha, double beta, double gamma, double *cs)
 {

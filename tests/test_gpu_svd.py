@@ -133,6 +133,28 @@ def test_zero_rows(m, n, kept):
         assert np.linalg.norm(got - W) <= 2.0 ** -22 * np.linalg.norm(W.astype(np.float64)), seed
 
 
+@pytest.mark.parametrize("scale", [1e-6, 1e-9, 1e-12, 1e-20, 1e-26])
+@pytest.mark.parametrize("lower", [False, True])
+def test_blocks_of_very_different_size(scale, lower):
+    """Two blocks that share no row and no column, one of them tiny: every singular value to the rounding of its float, whether or not the
+    large one's null space holds columns of rounding noise."""
+    import paper_2103_03936_amd as pf
+    a, b = _matrix(40, 20, 121).astype(np.float64), scale * _matrix(30, 20, 122).astype(np.float64)
+    if lower:
+        a[8:] = 0.0
+    W = np.zeros((70, 40))
+    W[:40, ::2], W[40:, 1::2] = a, b
+    W = W.astype(np.float32)
+    _, _, sigma, info = pf.pf_svd_split(to_gpu(W), 40, return_info=True)
+    assert int(info[1]) == 0
+    ref = np.concatenate([np.linalg.svd(W[:40, ::2][:8 if lower else 40].astype(np.float64), compute_uv=False),
+                          np.linalg.svd(W[40:, 1::2].astype(np.float64), compute_uv=False)])
+    got = sigma.double().cpu().numpy()
+    assert np.max(np.abs(got[:len(ref)] / ref - 1)) <= 2.0 ** -22
+    # (noise: what the rotations of the tiny block's columns round, and twice the rounding of the large one's)
+    assert not lower or np.max(got[len(ref):]) <= 2.0 ** -44 * ref[-20] + 2.0 ** -100 * ref[0]
+
+
 @pytest.mark.parametrize("shape", [(40, 1), (30, 24), (17, 70), (300, 130)])
 @pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
 def test_not_finite_is_reported(shape, value):

@@ -21,7 +21,7 @@ def emu(tmp_path_factory):
     subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
     lib, d = ctypes.CDLL(out), ctypes.c_double
     lib.emu_orthogonal.argtypes = [d, d, d, d]
-    lib.emu_orthogonal_nil.argtypes = [d, d, d, d, d]
+    lib.emu_orthogonal_short.argtypes = [d, d, d, d, d, ctypes.c_int]
     lib.emu_rotation.argtypes = [d, d, d, ctypes.c_void_p]
     lib.emu_before.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
     return lib
@@ -48,14 +48,16 @@ def test_not_finite_is_not_orthogonal(emu):
 
 
 def test_rounding_noise_is_orthogonal(emu):
-    """Columns 2^-160 of the longest and shorter, or with a norm that rounding left below zero, count as zero, two of 2^-100 as orthogonal
-    to each other; longer ones and what is not finite do not."""
-    inf, nan, tiny, low = float("inf"), float("nan"), 2.0 ** -321, 2.0 ** -201
-    for a, b, g, longest, want in ((tiny, tiny, tiny, 1, 1), (-tiny, 1, 2 ** -161, 1, 1), (1, 0.0, 1e-300, 1, 1), (4 * tiny, 1, 2 ** -160, 1, 0),
-                                   (4 * tiny, 1, 2 ** -160, 16, 1), (low, low, low, 1, 1), (low, 4 * low, low, 1, 0), (low, 1, 2 ** -101, 1, 0),
+    """Columns 2^-280 of the longest and shorter, or with a norm that rounding left below zero, count as zero, two of 2^-100 as orthogonal
+    to each other while they are held back; longer ones and what is not finite do not."""
+    inf, nan, tiny, low = float("inf"), float("nan"), 2.0 ** -561, 2.0 ** -201
+    for a, b, g, longest, want in ((tiny, tiny, tiny, 1, 3), (-tiny, 1, 2 ** -281, 1, 3), (1, 0.0, 1e-300, 1, 3), (4 * tiny, 1, 2 ** -280, 1, 0),
+                                   (4 * tiny, 1, 2 ** -280, 16, 3), (low, low, low, 1, 1), (low, 4 * low, low, 1, 0), (low, 1, 2 ** -101, 1, 0),
                                    (1, 1, 1e-12, 1, 0), (nan, tiny, nan, 1, 0), (tiny, nan, nan, nan, 0), (tiny, inf, inf, inf, 0),
-                                   (tiny, tiny, tiny, inf, 0)):
-        assert bool(emu.emu_orthogonal_nil(a, b, g, 1e-13, longest)) == bool(want), (a, b, g, longest)
+                                   (low, low, low, inf, 0)):
+        for hold in (1, 0):
+            got = emu.emu_orthogonal_short(a, b, g, 1e-13, longest, hold)
+            assert bool(got) == bool(want & (1 if hold else 2)), (a, b, g, longest, hold)
 
 
 def test_a_singular_value_that_is_not_finite_is_never_reported_as_converged(emu):
