@@ -4,9 +4,12 @@
 // products (pf_tile.h), what those do not take as implicit GEMMs (operands gathered by
 // functors) on the guarded element-wise GEMM.
 #include "pf_conv_chain.h"
+#include "pf_conv_px.h"
 #include "pf_conv_wgrad.h"
 #include "pf_epilogue.h"
 #include "pf_tile_host.h"
+
+#include <math.h>
 
 namespace pf {
 
@@ -162,6 +165,10 @@ struct ConvPlan {
     int ks_tU, ks_tV;        // ... image splits of the two filter gradients
     size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
+    int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction (bf16), 0: not
+    int px_bwd, px_bwd_threads;
+    int px_groups[2], px_per[2]; // ... and the pixel groups of their filter gradients, tiles per group
+    size_t px_pack, px_dT, px_part; // ... elements of the re-ordered thin filters and of dT, floats of the partial sums
     size_t saved_bytes;      // the backward direction's packed weights when the forward call saves them
 };
 
@@ -242,6 +249,69 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.n_part_t = (size_t)p.ks_tU * g.r * g.C * kk + (size_t)p.ks_tV * ((size_t)g.Cout * g.r + g.Cout) + 320;
 }
 
+// The pixel-major kernels (pf_conv_px.h): which takes a direction, and whether one does.  Costs in microseconds, fitted to times of 190
+// shapes over 1 to 256 images of 4 x 4 to 32 x 32 pixels, 32 to 2048 channels, ranks 8 to 128 (9 % rms; the tiled products 12 %).
+// A workgroup of P pixels costs a fixed part, one for the filters that it reads (per 64 channels and 32 ranks), one per chunk of
+// input channels and per 64 output channels, one where planes are not whole 16-byte pieces, and memory traffic as far as the chip is full;
+// small tiles read the filters more often, large ones leave compute units idle.
+struct PxCost {
+    int P, threads, CH; // pixels, threads, channels of a chunk
+    double round, filters, chunk, out, ragged, traffic, launch;
+    double wg, wg_part, wg_both; // backward: the filter gradients' share
+};
+static const PxCost PX_FWD[] = {{128, 512, 128, 3.12, 0.17, 0.00, 0.72, 0.43, 0.32, 3.54}, {64, 512, 128, 3.15, 0.11, 0.23, 0.43, 0.37, 0.12, 2.81},
+                                {32, 512, 256, 4.03, 0.09, 0.00, 0.09, 0.22, 0.08, 2.73},  {128, 256, 64, 0.00, 0.28, 0.00, 1.70, 0.66, 0.94, 4.27},
+                                {64, 256, 64, 0.33, 0.16, 0.00, 1.01, 0.62, 0.58, 4.15},   {32, 256, 128, 1.27, 0.14, 0.00, 0.37, 0.37, 0.37, 3.93}};
+static const PxCost PX_BWD[] = {{128, 512, 128, 1.58, 0.19, 0.35, 0.70, 0.64, 0.13, 15.50, 0.74, 0.00, 2.52},
+                                {64, 512, 128, 1.48, 0.13, 0.30, 0.29, 0.56, 0.00, 15.46, 0.54, 0.32, 4.55},
+                                {32, 512, 256, 4.46, 0.11, 0.21, 0.00, 0.41, 0.06, 13.32, 0.21, 0.00, 5.34},
+                                {128, 256, 64, 2.13, 0.20, 0.24, 1.50, 0.91, 0.27, 13.62, 0.77, 7.71, 1.86},
+                                {64, 256, 64, 0.00, 0.12, 0.25, 0.81, 0.87, 0.00, 15.60, 0.81, 11.55, 2.47},
+                                {32, 256, 128, 0.00, 0.09, 0.03, 0.23, 0.60, 0.00, 16.59, 1.14, 13.10, 2.17}};
+
+static void plan_conv_px(const ConvGeom &g, int dtype, ConvPlan &p)
+{
+    p.px_fwd = p.px_bwd = 0;
+    if (dtype != PF_BF16 || !p.tiles || !px_fits(g.N, g.C, g.H, g.W, g.Cout, g.r, g.k, g.s, g.p, g.Ho, g.Wo)) return;
+    const PxPlane pl = px_plane(g.N, g.H, g.W, g.k);
+    const i64 npx = (i64)g.N * g.H * g.W;
+    const int kk = g.k * g.k, RB = px_rank_blocks(g.r);
+    const double ragged = g.H * g.W % 8 ? 1 : 0, filters = (g.C * kk + g.Cout) * RB / 64.0, mb = 4e-6 * g.r * ((double)g.C * kk + g.Cout);
+    const double wg = (npx + 127) / 128 / 256.0 *
+                      ((g.C + px_slab(g.k, g.r) - 1) / px_slab(g.k, g.r) * (kk == 1 ? 3.0 : RB == 2 ? 6.5 : 4.6) + (g.Cout + 127) / 128 * 3.0) * (1 + 0.2 * ragged);
+    // in: channels of the direction's input, out: of its output
+    const auto best = [&](const PxCost (&list)[6], int in, int out, int &P, int &threads) {
+        double least = 1e30;
+        for (const PxCost &c : list) {
+            const i64 tiles = (npx + c.P - 1) / c.P, room = c.threads == 256 ? 512 : 256, rounds = (tiles + room - 1) / room;
+            if ((g.r > 64 && c.threads == 256) || !px_tile_fits(pl, c.P)) continue;
+            const double full = tiles < room ? (double)tiles / room : 1;
+            const double t = c.launch + c.wg * wg + c.wg_part * mb + c.wg_both * sqrt(wg * mb) +
+                             rounds * (c.round + c.filters * filters + c.chunk * ((in + c.CH - 1) / c.CH) + c.out * out / 64 +
+                                       c.ragged * ragged * (in + 2 * out) / 64 + c.traffic * full * (in + out) / 64);
+            if (t < least) least = t, P = c.P, threads = c.threads;
+        }
+        return least;
+    };
+    // the tiled products; of the chain kernel's shapes one workgroup per image, which streams both factors
+    const double m = npx * 1e-7, macs = (g.C * kk + g.Cout) * (1 + 0.5 * ragged);
+    const double tiled_fwd = 12.8 + m * (1.08 * RB * g.C * kk + 6.7 * RB * g.Cout + 1.75 * macs) + 2.64e-3 * g.C * kk + 3.4 * ragged;
+    const double tiled_bwd = 20.8 + m * (1.78 * RB * g.C * kk + 8.7 * RB * g.Cout + 5.26 * macs) + 4.8 * ragged + 4.83 * mb;
+    const double chain_fwd = ((g.N + 255) / 256) * (9 + (0.055 * g.C * kk + 0.35 * g.Cout) * RB / 64);
+    int P = 0, threads = 0;
+    double t = best(PX_FWD, g.C, g.Cout, P, threads);
+    if (P && (p.chain ? t < 0.95 * chain_fwd : g.r <= 64 || t < tiled_fwd)) p.px_fwd = P, p.px_fwd_threads = threads;
+    if ((p.chain && p.wgrad) || !px_wgrad_fits(pl)) return;
+    P = 0;
+    t = best(PX_BWD, g.Cout, g.C, P, threads);
+    if (!P || !(p.chain || g.r <= 32 || 1.03 * t < tiled_bwd)) return;
+    p.px_bwd = P, p.px_bwd_threads = threads;
+    px_wgrad_plan((int)npx, g.r, g.C, g.k, g.Cout, p.px_groups, p.px_per);
+    p.px_pack = px_pack_elems(g.C, g.r, g.k);
+    p.px_dT = (size_t)npx * ((g.r + 7) / 8 * 8);
+    p.px_part = (size_t)p.px_groups[0] * g.r * g.C * kk + (size_t)p.px_groups[1] * g.Cout * (g.r + 1) + 256;
+}
+
 static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
 {
     ConvPlan p;
@@ -258,9 +328,11 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
     p.n_w2 = chain_w2_elems(g.Cout, g.r, 1);
     p.n_w1b = chain_w1_elems(g.Cout, g.r, 1);
     p.n_w2b = chain_w2_elems(g.C, g.r, g.k);
-    p.saved_bytes = p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
     p.wgrad = p.chain && wgrad_supported(g.r, g.C, g.H, g.W, g.k, g.s, g.p) &&
               wgrad_supported(g.r, g.Cout, g.H, g.W, 1, 1, 0);
+    plan_conv_px(g, dtype, p);
+    // (saved by a forward call for the kernels that take the backward direction)
+    p.saved_bytes = p.px_bwd ? (p.px_fwd ? align_up(p.px_pack * 2) : 0) : p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
     p.wg_groups = p.wg_ipg = p.wg_groups2 = p.wg_ipg2 = 1;
     if (p.wgrad && g.N > 0) {
         // Image groups of the two problems of the launch.  A problem has `units` independent output blocks;
@@ -321,6 +393,10 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
         const size_t b = 2 * align_up(p.n_T * el) + 4 * align_up(p.n_pack * el) +
                          align_up((p.n_part_t > p.n_part_T ? p.n_part_t : p.n_part_T) * 4);
         if (f > p.fwd_bytes) p.fwd_bytes = f;
+        if (b > p.bwd_bytes) p.bwd_bytes = b;
+    }
+    if (p.px_bwd) {
+        const size_t b = align_up(p.px_dT * 2) + align_up(p.px_pack * 2) + align_up(p.px_part * 4);
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
     return p;
@@ -603,6 +679,21 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
 }
 
 // ----------------------------------------------------- fused small-image path (bf16)
+// What a forward call keeps for a backward call that is given the same scale: both factors the way the backward direction reads them
+// (its first stage runs on scale * Vp).
+static PackW1 chain_saved_w1(const ConvGeom &g, const void *Vp, void *W_save, const float *scale)
+{
+    PackW1 q = make_pack_w1(W_save ? (const uint16_t *)Vp : nullptr, (uint4 *)W_save, g.Cout, g.r, 1, 1, g.r, 0, g.H, g.W);
+    q.cscale = scale;
+    return q;
+}
+static PackW2 chain_saved_w2(const ConvGeom &g, const ConvPlan &p, const void *Uk, void *W_save)
+{
+    const int T = g.k * g.k;
+    return make_pack_w2(W_save ? (const uint16_t *)Uk : nullptr, W_save ? (uint4 *)((char *)W_save + align_up(p.n_w1b * 2)) : nullptr, g.C,
+                        g.r, g.k, T - 1, T, (i64)g.C * T, -1);
+}
+
 static int conv_fwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X, const bf16_t *Uk, const bf16_t *Vp,
                           bf16_t *Y, bf16_t *T_save, void *W_save, Workspace &ws, hipStream_t s, const ConvEpilogue &ep)
 {
@@ -612,17 +703,9 @@ static int conv_fwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X,
     // Both factors are re-ordered into MFMA fragment order by one small launch (read in place, one lane per row,
     // the 1x1 filters Vp[Cout][r] reach the compute unit at a quarter of the rate).  The same launch can re-order
     // both factors the way the backward pass wants them (W_save), which saves that pass a launch of its own.
-    uint16_t *s1 = (uint16_t *)W_save, *s2 = W_save ? (uint16_t *)((char *)W_save + align_up(p.n_w1b * 2)) : nullptr;
-    int st = launch_pack_chain(
-        s, make_pack_w1((const uint16_t *)Uk, (uint4 *)w1, g.C, g.r, g.k, (i64)g.C * T, T, 1, g.H, g.W),
-        make_pack_w2(W_save ? (const uint16_t *)Uk : nullptr, (uint4 *)s2, g.C, g.r, g.k, T - 1, T, (i64)g.C * T, -1),
-        // (kept for a backward call that is given the same scale: its first stage runs on scale * Vp)
-        [&] {
-            PackW1 q = make_pack_w1(W_save ? (const uint16_t *)Vp : nullptr, (uint4 *)s1, g.Cout, g.r, 1, 1, g.r, 0, g.H, g.W);
-            q.cscale = ep.scale;
-            return q;
-        }(),
-        make_pack_w2((const uint16_t *)Vp, (uint4 *)w2, g.Cout, g.r, 1, 0, g.r, 1, 0));
+    int st = launch_pack_chain(s, make_pack_w1((const uint16_t *)Uk, (uint4 *)w1, g.C, g.r, g.k, (i64)g.C * T, T, 1, g.H, g.W),
+                               chain_saved_w2(g, p, Uk, W_save), chain_saved_w1(g, Vp, W_save, ep.scale),
+                               make_pack_w2((const uint16_t *)Vp, (uint4 *)w2, g.Cout, g.r, 1, 0, g.r, 1, 0));
     if (st != PF_OK) return st;
     ChainArgs a{(const uint16_t *)X, (const uint4 *)w1, (const uint4 *)w2, nullptr, (uint16_t *)Y,
                 (uint16_t *)T_save,  g.C,               g.Cout,            g.H,     g.W,
@@ -678,6 +761,39 @@ static int conv_bwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X,
     WgradReduceArgs r1{part_dVp, dVp, p.wg_groups2, 1, g.r, g.Cout, 1, g.r, 0, accumulate, ep.scale}; // dVp = scale (dZ T^T)
     const ColsumTilesArgs cs{nullptr, ep.dshift, 0, g.Cout, accumulate, dY, g.N, g.Ho * g.Wo};
     return launch_wgrad_reduce(s, r0, r1, ep.dshift ? &cs : nullptr);
+}
+
+// ----------------------------------------------------- pixel-major kernels (bf16)
+// Three launches: dT and dX, the partial sums of both filter gradients (and of the shift gradient), their sums.  Without the re-ordered
+// filters of the forward call one more before them.
+static int conv_bwd_px(const ConvGeom &g, const ConvPlan &p, const bf16_t *X, const bf16_t *Uk, const bf16_t *Vp, const bf16_t *dY,
+                       const bf16_t *T_saved, const void *W_saved, bf16_t *dX, float *dUk, float *dVp, int accumulate, Workspace &ws,
+                       hipStream_t s, const ConvEpilogue &ep)
+{
+    uint16_t *dT = ws.take<uint16_t>(p.px_dT), *pack = ws.take<uint16_t>(p.px_pack);
+    float *part = ws.take<float>(p.px_part);
+    const PxPlane pl = px_plane(g.N, g.H, g.W, g.k);
+    int st = PF_OK;
+    if (!W_saved) st = launch_px_pack(s, PxPack{(const uint16_t *)Uk, pack, g.C, g.r, g.k * g.k});
+    if (st != PF_OK) return st;
+    const PxBwdArgs b{pl, g.C, g.Cout, g.r, (const uint16_t *)dY, (const uint16_t *)Vp, W_saved ? (const uint16_t *)W_saved : pack,
+                      (uint16_t *)dX, dT, ep.scale, {nullptr, nullptr, (const uint16_t *)ep.add, (const uint16_t *)ep.mask, 0}};
+    st = launch_px_bwd(s, b, g.k, p.px_bwd, p.px_bwd_threads);
+    if (st != PF_OK) return st;
+    const int kk = g.k * g.k, r8 = (g.r + 7) / 8 * 8;
+    const i64 nU = (i64)g.r * g.C * kk, nV = (i64)g.r * g.Cout;
+    float *partV = part + p.px_groups[0] * nU, *sums = partV + (p.px_groups[1] * nV + 63) / 64 * 64;
+    const PxWgradArgs w{px_plane(g.N, g.H, g.W, 1), pl, g.r, 2,
+                        {{dT, (const uint16_t *)X, r8, g.C, kk, (g.C + px_slab(g.k, g.r) - 1) / px_slab(g.k, g.r), p.px_groups[0], p.px_per[0], part, nullptr},
+                         {(const uint16_t *)T_saved, (const uint16_t *)dY, g.r, g.Cout, 1, (g.Cout + 127) / 128, p.px_groups[1], p.px_per[1], partV,
+                          ep.dshift ? sums : nullptr}}};
+    st = launch_px_wgrad(s, w);
+    if (st != PF_OK) return st;
+    SplitSumArgs ss = {};
+    split_sum_add(ss, SplitSum{part, dUk, nU, nU, p.px_groups[0], accumulate, nullptr, 0, 0});
+    split_sum_add(ss, SplitSum{partV, dVp, nV, nV, p.px_groups[1], accumulate, ep.scale, g.r, 0, g.r, g.Cout});
+    if (ep.dshift) split_sum_add(ss, SplitSum{sums, ep.dshift, g.Cout, g.Cout, p.px_groups[1], accumulate, nullptr, 0, 0});
+    return launch_split_sums(s, ss);
 }
 
 // ------------------------------------------------------------------ dense
@@ -851,6 +967,19 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
     const ConvEpilogue all = {scale, shift, residual, nullptr, act == PF_ACT_RELU ? 1 : 0, nullptr};
+    if (!p.saved_bytes) W_save = nullptr;
+    if (p.px_fwd) {
+        *fused = true;
+        PxFwdArgs x{px_plane(g.N, g.H, g.W, g.k), g.C, g.Cout, g.r, (const uint16_t *)X, (const uint16_t *)Uk, (const uint16_t *)Vp,
+                    (uint16_t *)Y, (uint16_t *)T_save, {scale, shift, (const uint16_t *)residual, nullptr, all.relu}, {}, {}, {}};
+        if (W_save && p.px_bwd) {
+            x.pack = {(const uint16_t *)Uk, (uint16_t *)W_save, g.C, g.r, g.k * g.k};
+        } else if (W_save && p.saved_bytes) {
+            x.chain1 = chain_saved_w1(g, Vp, W_save, scale);
+            x.chain2 = chain_saved_w2(g, p, Uk, W_save);
+        }
+        return launch_px_fwd(s, x, g.k, p.px_fwd, p.px_fwd_threads);
+    }
     if (p.tiles && !(d->dtype == PF_BF16 && p.chain)) {
         *fused = true;
         if (d->dtype == PF_F32)
@@ -900,6 +1029,14 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         }
         return st;
     }
+    if (!p.saved_bytes) W_saved = nullptr;
+    if (p.px_bwd && dX && dUk && dVp && T_saved) {
+        *fused = true;
+        return conv_bwd_px(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY, (const bf16_t *)T_saved, W_saved,
+                           (bf16_t *)dX, (float *)dUk, (float *)dVp, accumulate, ws, s,
+                           ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift});
+    }
+    if (p.px_bwd) W_saved = nullptr; // (in the order of the kernels above)
     if (p.tiles && !(d->dtype == PF_BF16 && p.chain && dX)) {
         *fused = true;
         const ConvEpilogue ep = {scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift};
@@ -919,7 +1056,7 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     {
         *fused = true; // the kernel adds the skip gradient and masks as it stores dX
         return conv_bwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY,
-                              (const bf16_t *)T_saved, p.saved_bytes ? W_saved : nullptr, (bf16_t *)dX, (float *)dUk,
+                              (const bf16_t *)T_saved, W_saved, (bf16_t *)dX, (float *)dUk,
                               (float *)dVp, accumulate, ws, s, ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift});
     }
     return conv_bwd_generic<bf16_t>(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp,
