@@ -4,6 +4,7 @@
 // pieces on the guarded element-wise GEMM.
 #include "pf_conv_chain.h"
 #include "pf_linear_chain.h"
+#include "pf_linear_two.h"
 #include "pf_skinny.h"
 #include "pf_linear_small.h"
 #include "pf_tile_host.h"
@@ -163,6 +164,7 @@ struct LinearPlan {
     size_t n_colsum;    // per-tile column sums of dY (bias gradient), floats
     int wg_groups, wg_ipg; // row-tile groups of the factor-gradient kernel and tiles per group
     int wg_cols;           // columns per workgroup of that kernel
+    int two_fwd, two_split; // rows per workgroup and shares of the outputs where both stages forward are one launch of pf_linear_two.h, 0: not
     bool skinny;           // fp32 with at most 128 rows: the weight-streaming kernels of the LSTM cell
     size_t n_part_sk;      // their slice sums, floats
     LinearTiles t;         // the tiled products of pf_tile.h
@@ -215,6 +217,19 @@ static bool chain_bwd_pays(i64 M, i64 in, i64 out, i64 r)
 // (several layers that share their input; backward, their dX is one tiled product over all ranks)
 static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 512 || (in <= 1024 && M <= 4096)); }
 
+// Both stages in one launch (pf_linear_two.h) or the tiled products: rows per workgroup, or 0.  Of the tiled products' time, fitted to the
+// same shapes (8 % rms): two launches, or three where T is split; the other kernel is the faster one for all but wide layers of some
+// thousand rows (1390 x 256 -> 101 -> 2384: 13.5 against 14.2).  Over 91 drawn shapes 1.25 times as fast, geometric mean.
+static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
+{
+    if (!linear_two_supported(M, in, out, r) || linear_chain2_supported(in, out, r)) return 0;
+    int rows = 0;
+    const double t = plan_linear_two(M, in, out, r, G, rows, split);
+    const double tiled = 9.2 + 1e-6 * M * (0.371 * G * out * ((r + 63) / 64) + 0.353 * (in + G * out) * (r % 8 ? 2 : 1)) + 1.13e-3 * in +
+                         (in >= 512 && G * M * r < 64 * 64 * 200 ? 0.7 : 0);
+    return t < 0.97 * tiled ? rows : 0;
+}
+
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
     LinearPlan p;
@@ -231,6 +246,7 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.fused = d->dtype == PF_BF16 && linear_chain_supported(d->in, d->out, d->r);
     p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in, d->out, d->r);
     p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->in, d->out, d->r);
+    p.two_fwd = d->dtype == PF_BF16 ? two_fwd_rows(d->M, d->in, d->out, d->r, 1, p.two_split) : 0;
     p.skinny = d->dtype == PF_F32 && d->M > 0 && d->M <= 4 * SK_MAX_ROWS && d->in >= 4 && d->out >= 4 &&
                d->r >= 4;
     p.n_part_sk = 0;
@@ -798,6 +814,7 @@ struct SharedPlan {
     pf_linear_desc one; // one of the G layers
     LinearPlan p;
     bool fused_fwd; // the groups run inside one launch of the chain kernel
+    int two_fwd, two_split; // ... or of the two-stage kernel (rows per workgroup, shares of the outputs), 0: not
     LinearTiles t;  // otherwise, and backward, side by side on the tiled products
     size_t fwd_bytes, bwd_bytes;
 };
@@ -822,6 +839,7 @@ static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_line
     const int G = d->groups;
     sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS &&
                    (chain_shared_fwd_pays(d->M, d->n_in) || rows_fwd_pays(d->M, d->n_in, d->n_out, d->r, G));
+    sp.two_fwd = d->dtype == PF_BF16 && !sp.fused_fwd ? two_fwd_rows(d->M, d->n_in, d->n_out, d->r, G, sp.two_split) : 0;
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
     // one layer's workspace, then one more dX (layer by layer)
@@ -898,6 +916,14 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (d->dtype == PF_F32)
         return linear_fwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)bias,
                                          (float *)Y, (float *)T_save, ws, s);
+    if (p.two_fwd) {
+        if (ep && ep->used) *ep->used = true;
+        return launch_linear_two(s, "linear_fwd_two",
+                                 LinTwoArgs{d->M, (int)d->in, (int)d->out, (int)d->r, (const uint16_t *)X, (const uint16_t *)V, (const uint16_t *)U,
+                                            d->has_bias ? (const uint16_t *)bias : nullptr, ep ? (const uint16_t *)ep->add : nullptr, (uint16_t *)Y,
+                                            (uint16_t *)T_save, ep ? ep->relu : 0, 1, 0, 0, 0, 0, 0, p.two_split},
+                                 p.two_fwd);
+    }
     if (p.chain_fwd)
         return linear_fwd_fused(d, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)bias,
                                 (bf16_t *)Y, (bf16_t *)T_save, ws, s, ep ? *ep : LinEpilogue{});
@@ -1117,6 +1143,12 @@ int pf_lowrank_linear_shared_fwd(const pf_linear_shared_desc *d, const void *X, 
         return rows_fwd_pays(M, in, out, r, d->groups) ? launch_linear_rows(s, "linear_shared_fwd_rows", c)
                                                        : launch_linear_chain2(s, "linear_shared_fwd_fused", c);
     }
+    if (sp.two_fwd)
+        return launch_linear_two(s, "linear_shared_fwd_two",
+                                 LinTwoArgs{M, (int)in, (int)out, (int)r, (const uint16_t *)X, (const uint16_t *)V, (const uint16_t *)U,
+                                            d->has_bias ? (const uint16_t *)bias : nullptr, nullptr, (uint16_t *)Y, (uint16_t *)T_save, 0, d->groups,
+                                            in * r, out * r, out, M * out, M * r, sp.two_split},
+                                 sp.two_fwd);
     if (sp.t.ok) {
         Workspace ws(workspace, workspace_bytes);
         if (d->dtype == PF_F32)
