@@ -165,7 +165,7 @@ struct ConvPlan {
     int ks_tU, ks_tV;        // ... image splits of the two filter gradients
     size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
-    int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction (bf16), 0: not
+    int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction, 0: not
     int px_bwd, px_bwd_threads;
     int px_groups[2], px_per[2]; // ... and the pixel groups of their filter gradients, tiles per group
     size_t px_pack, px_dT, px_part; // ... elements of the re-ordered thin filters and of dT, floats of the partial sums
@@ -250,7 +250,8 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
 }
 
 // The pixel-major kernels (pf_conv_px.h): which takes a direction, and whether one does.  Costs in microseconds, fitted to times of 190
-// shapes over 1 to 256 images of 4 x 4 to 32 x 32 pixels, 32 to 2048 channels, ranks 8 to 128 (9 % rms; the tiled products 12 %).
+// shapes in bf16, 140 in float and 100 with stride over 1 to 256 images of 4 x 4 to 32 x 32 pixels, 32 to 2048 channels, ranks 1 to 128
+// (3 to 15 % rms; the tiled products 10 to 14 %).
 // A workgroup of P pixels costs a fixed part, one for the filters that it reads (per 64 channels and 32 ranks), one per chunk of
 // input channels and per 64 output channels, one where planes are not whole 16-byte pieces, and memory traffic as far as the chip is full;
 // small tiles read the filters more often, large ones leave compute units idle.
@@ -262,53 +263,76 @@ struct PxCost {
 static const PxCost PX_FWD[] = {{128, 512, 128, 3.12, 0.17, 0.00, 0.72, 0.43, 0.32, 3.54}, {64, 512, 128, 3.15, 0.11, 0.23, 0.43, 0.37, 0.12, 2.81},
                                 {32, 512, 256, 4.03, 0.09, 0.00, 0.09, 0.22, 0.08, 2.73},  {128, 256, 64, 0.00, 0.28, 0.00, 1.70, 0.66, 0.94, 4.27},
                                 {64, 256, 64, 0.33, 0.16, 0.00, 1.01, 0.62, 0.58, 4.15},   {32, 256, 128, 1.27, 0.14, 0.00, 0.37, 0.37, 0.37, 3.93}};
+static const PxCost PX_FWD_F32[] = {{128, 512, 64, 0.12, 1.11, 0.79, 1.10, 0.30, 1.44, 6.59}, {64, 512, 64, 1.26, 0.60, 0.98, 0.73, 0.29, 0.72, 3.93},
+                                    {32, 512, 128, 3.22, 0.39, 0.69, 0.25, 0.17, 0.33, 2.66}};
+static const PxCost PX_FWD_STRIDED[] = {{32, 512, 128, 2.97, 0.08, 0.77, 0.11, 0.20, 0.17, 3.29}, {64, 512, 128, 5.99, 0.13, 1.37, 0.17, 0.00, 1.19, 0.00}};
+static const PxCost PX_FWD_STRIDED_F32[] = {{32, 512, 64, 0.36, 0.36, 0.87, 0.04, 0.07, 1.15, 6.65}, {64, 512, 64, 6.22, 0.43, 0.93, 0.79, 0.41, 1.12, 0.00}};
 static const PxCost PX_BWD[] = {{128, 512, 128, 1.58, 0.19, 0.35, 0.70, 0.64, 0.13, 15.50, 0.74, 0.00, 2.52},
                                 {64, 512, 128, 1.48, 0.13, 0.30, 0.29, 0.56, 0.00, 15.46, 0.54, 0.32, 4.55},
                                 {32, 512, 256, 4.46, 0.11, 0.21, 0.00, 0.41, 0.06, 13.32, 0.21, 0.00, 5.34},
                                 {128, 256, 64, 2.13, 0.20, 0.24, 1.50, 0.91, 0.27, 13.62, 0.77, 7.71, 1.86},
                                 {64, 256, 64, 0.00, 0.12, 0.25, 0.81, 0.87, 0.00, 15.60, 0.81, 11.55, 2.47},
                                 {32, 256, 128, 0.00, 0.09, 0.03, 0.23, 0.60, 0.00, 16.59, 1.14, 13.10, 2.17}};
+static const PxCost PX_BWD_F32[] = {{128, 512, 64, 0.72, 2.06, 0.14, 0.13, 0.51, 2.81, 18.49, 0.81, 0.00, 0.00},
+                                    {64, 512, 64, 2.64, 1.08, 1.03, 0.00, 0.49, 1.55, 15.49, 0.44, 12.60, 0.00},
+                                    {32, 512, 128, 2.69, 0.00, 3.07, 0.38, 0.56, 1.04, 15.13, 0.00, 37.05, 0.00}};
+// The tiled products: a fixed part; per 10^7 pixels of 32 ranks x columns of the thin product, x output channels, of columns and output
+// channels alone; per 1000 terms of the thin sum, for ragged planes, per 10^6 factor elements and per 1000 pixels of a plane.
+struct TiledCost {
+    double launches, thin, wide, macs, terms, ragged, factors, plane;
+};
+static const TiledCost TILED_FWD[2][2] = {{{12.8, 1.08, 6.7, 1.75, 2.64, 3.4, 0, 0}, {15.71, 9.57, 24.16, 1.53, 2.46, 2.42, 11.43, 0}}, // stride 1: bf16, float
+                                          {{17.87, 5.24, 0, 2.39, 0.95, 4.45, 7.53, 0}, {16.89, 1.42, 22.14, 11.52, 4.0, 1.16, 0, 0}}}; // more
+static const TiledCost TILED_BWD[2] = {{20.8, 1.78, 8.7, 5.26, 0, 4.8, 19.3, 0}, {19.05, 30.08, 0, 27.47, 0, 5.03, 143.25, 30}};
 
-static void plan_conv_px(const ConvGeom &g, int dtype, ConvPlan &p)
+template <typename T>
+static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
 {
-    p.px_fwd = p.px_bwd = 0;
-    if (dtype != PF_BF16 || !p.tiles || !px_fits(g.N, g.C, g.H, g.W, g.Cout, g.r, g.k, g.s, g.p, g.Ho, g.Wo)) return;
-    const PxPlane pl = px_plane(g.N, g.H, g.W, g.k);
-    const i64 npx = (i64)g.N * g.H * g.W;
-    const int kk = g.k * g.k, RB = px_rank_blocks(g.r);
-    const double ragged = g.H * g.W % 8 ? 1 : 0, filters = (g.C * kk + g.Cout) * RB / 64.0, mb = 4e-6 * g.r * ((double)g.C * kk + g.Cout);
+    constexpr bool f32 = sizeof(T) == 4;
+    constexpr int V = PxEl<T>::V, S = PxEl<T>::S;
+    if (!p.tiles || !px_fits<T>(g.N, g.C, g.H, g.W, g.Cout, g.r, g.k, g.s, g.p, g.Ho, g.Wo)) return;
+    const PxPlane<S> pl = px_plane<S>(g.N, g.H, g.W, g.k), po = px_plane<S>(g.N, g.Ho, g.Wo, 1);
+    const i64 npx = (i64)g.N * g.Ho * g.Wo;
+    const int kk = g.k * g.k, RB = px_rank_blocks(g.r), s1 = px_slab<T>(g.k, g.r), s2 = px_slab<T>(1, g.r);
+    const double ragged = g.Ho * g.Wo % V ? 1 : 0, filters = (g.C * kk + g.Cout) * RB / 64.0, mf = 1e-6 * g.r * ((double)g.C * kk + g.Cout);
     const double wg = (npx + 127) / 128 / 256.0 *
-                      ((g.C + px_slab(g.k, g.r) - 1) / px_slab(g.k, g.r) * (kk == 1 ? 3.0 : RB == 2 ? 6.5 : 4.6) + (g.Cout + 127) / 128 * 3.0) * (1 + 0.2 * ragged);
+                      ((g.C + s1 - 1) / s1 * px_wgrad_cost<T>(g.k, g.r) + (g.Cout + s2 - 1) / s2 * px_wgrad_cost<T>(1, g.r)) * (1 + 0.2 * ragged);
     // in: channels of the direction's input, out: of its output
-    const auto best = [&](const PxCost (&list)[6], int in, int out, int &P, int &threads) {
+    const auto best = [&](const auto &list, int in, int out, int &P, int &threads) {
         double least = 1e30;
         for (const PxCost &c : list) {
             const i64 tiles = (npx + c.P - 1) / c.P, room = c.threads == 256 ? 512 : 256, rounds = (tiles + room - 1) / room;
-            if ((g.r > 64 && c.threads == 256) || !px_tile_fits(pl, c.P)) continue;
+            if ((g.r > 64 && c.threads == 256) || (g.s > 1 && kk == 9 && c.P == 64) || !px_tile_fits(pl, po, g.s, c.P)) continue;
             const double full = tiles < room ? (double)tiles / room : 1;
-            const double t = c.launch + c.wg * wg + c.wg_part * mb + c.wg_both * sqrt(wg * mb) +
+            const double t = c.launch + c.wg * wg + 4 * c.wg_part * mf + c.wg_both * sqrt(4 * wg * mf) +
                              rounds * (c.round + c.filters * filters + c.chunk * ((in + c.CH - 1) / c.CH) + c.out * out / 64 +
                                        c.ragged * ragged * (in + 2 * out) / 64 + c.traffic * full * (in + out) / 64);
             if (t < least) least = t, P = c.P, threads = c.threads;
         }
         return least;
     };
-    // the tiled products; of the chain kernel's shapes one workgroup per image, which streams both factors
-    const double m = npx * 1e-7, macs = (g.C * kk + g.Cout) * (1 + 0.5 * ragged);
-    const double tiled_fwd = 12.8 + m * (1.08 * RB * g.C * kk + 6.7 * RB * g.Cout + 1.75 * macs) + 2.64e-3 * g.C * kk + 3.4 * ragged;
-    const double tiled_bwd = 20.8 + m * (1.78 * RB * g.C * kk + 8.7 * RB * g.Cout + 5.26 * macs) + 4.8 * ragged + 4.83 * mb;
+    const auto tiled = [&](const TiledCost &c) {
+        const double m = npx * 1e-7;
+        return c.launches + m * (c.thin * RB * g.C * kk + c.wide * RB * g.Cout + c.macs * (g.C * kk + g.Cout) * (1 + 0.5 * ragged)) +
+               1e-3 * c.terms * g.C * kk + c.ragged * ragged + c.factors * mf + 1e-3 * c.plane * g.H * g.W;
+    };
+    // of the chain kernel's shapes one workgroup per image streams both factors
     const double chain_fwd = ((g.N + 255) / 256) * (9 + (0.055 * g.C * kk + 0.35 * g.Cout) * RB / 64);
     int P = 0, threads = 0;
-    double t = best(PX_FWD, g.C, g.Cout, P, threads);
-    if (P && (p.chain ? t < 0.95 * chain_fwd : g.r <= 64 || t < tiled_fwd)) p.px_fwd = P, p.px_fwd_threads = threads;
-    if ((p.chain && p.wgrad) || !px_wgrad_fits(pl)) return;
+    double t;
+    if constexpr (f32) t = g.s > 1 ? best(PX_FWD_STRIDED_F32, g.C, g.Cout, P, threads) : best(PX_FWD_F32, g.C, g.Cout, P, threads);
+    else t = g.s > 1 ? best(PX_FWD_STRIDED, g.C, g.Cout, P, threads) : best(PX_FWD, g.C, g.Cout, P, threads);
+    if (P && (p.chain ? t < 0.95 * chain_fwd : (!f32 && g.r <= 64) || t < (f32 ? 0.9 : 1) * tiled(TILED_FWD[g.s > 1][f32]))) p.px_fwd = P, p.px_fwd_threads = threads;
+    // backward: unit stride
+    if (g.s > 1 || !px_bwd_takes<T>(g.k, g.r) || (p.chain && p.wgrad) || !px_wgrad_fits(pl)) return;
     P = 0;
-    t = best(PX_BWD, g.Cout, g.C, P, threads);
-    if (!P || !(p.chain || g.r <= 32 || 1.03 * t < tiled_bwd)) return;
+    if constexpr (f32) t = best(PX_BWD_F32, g.Cout, g.C, P, threads);
+    else t = best(PX_BWD, g.Cout, g.C, P, threads);
+    if (!P || !(p.chain || (!f32 && g.r <= 32) || 1.03 * t < tiled(TILED_BWD[f32]))) return;
     p.px_bwd = P, p.px_bwd_threads = threads;
-    px_wgrad_plan((int)npx, g.r, g.C, g.k, g.Cout, p.px_groups, p.px_per);
+    px_wgrad_plan<T>((int)npx, g.r, g.C, g.k, g.Cout, p.px_groups, p.px_per);
     p.px_pack = px_pack_elems(g.C, g.r, g.k);
-    p.px_dT = (size_t)npx * ((g.r + 7) / 8 * 8);
+    p.px_dT = (size_t)npx * px_ranks<T>(g.r);
     p.px_part = (size_t)p.px_groups[0] * g.r * g.C * kk + (size_t)p.px_groups[1] * g.Cout * (g.r + 1) + 256;
 }
 
@@ -330,9 +354,11 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
     p.n_w2b = chain_w2_elems(g.C, g.r, g.k);
     p.wgrad = p.chain && wgrad_supported(g.r, g.C, g.H, g.W, g.k, g.s, g.p) &&
               wgrad_supported(g.r, g.Cout, g.H, g.W, 1, 1, 0);
-    plan_conv_px(g, dtype, p);
+    p.px_fwd = p.px_bwd = 0;
+    if (dtype == PF_BF16) plan_conv_px<uint16_t>(g, p);
+    else plan_conv_px<float>(g, p);
     // (saved by a forward call for the kernels that take the backward direction)
-    p.saved_bytes = p.px_bwd ? (p.px_fwd ? align_up(p.px_pack * 2) : 0) : p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
+    p.saved_bytes = p.px_bwd ? (p.px_fwd ? align_up(p.px_pack * (dtype == PF_BF16 ? 2 : 4)) : 0) : p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
     p.wg_groups = p.wg_ipg = p.wg_groups2 = p.wg_ipg2 = 1;
     if (p.wgrad && g.N > 0) {
         // Image groups of the two problems of the launch.  A problem has `units` independent output blocks;
@@ -396,7 +422,8 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
     if (p.px_bwd) {
-        const size_t b = align_up(p.px_dT * 2) + align_up(p.px_pack * 2) + align_up(p.px_part * 4);
+        const size_t el = dtype == PF_BF16 ? 2 : 4;
+        const size_t b = align_up(p.px_dT * el) + align_up(p.px_pack * el) + align_up(p.px_part * 4);
         if (b > p.bwd_bytes) p.bwd_bytes = b;
     }
     return p;
@@ -763,30 +790,29 @@ static int conv_bwd_chain(const ConvGeom &g, const ConvPlan &p, const bf16_t *X,
     return launch_wgrad_reduce(s, r0, r1, ep.dshift ? &cs : nullptr);
 }
 
-// ----------------------------------------------------- pixel-major kernels (bf16)
+// ----------------------------------------------------- pixel-major kernels
 // Three launches: dT and dX, the partial sums of both filter gradients (and of the shift gradient), their sums.  Without the re-ordered
 // filters of the forward call one more before them.
-static int conv_bwd_px(const ConvGeom &g, const ConvPlan &p, const bf16_t *X, const bf16_t *Uk, const bf16_t *Vp, const bf16_t *dY,
-                       const bf16_t *T_saved, const void *W_saved, bf16_t *dX, float *dUk, float *dVp, int accumulate, Workspace &ws,
+template <typename T>
+static int conv_bwd_px(const ConvGeom &g, const ConvPlan &p, const T *X, const T *Uk, const T *Vp, const T *dY, const T *T_saved,
+                       const T *W_saved, T *dX, float *dUk, float *dVp, int accumulate, Workspace &ws,
                        hipStream_t s, const ConvEpilogue &ep)
 {
-    uint16_t *dT = ws.take<uint16_t>(p.px_dT), *pack = ws.take<uint16_t>(p.px_pack);
+    T *dT = ws.take<T>(p.px_dT), *pack = ws.take<T>(p.px_pack);
     float *part = ws.take<float>(p.px_part);
-    const PxPlane pl = px_plane(g.N, g.H, g.W, g.k);
+    const PxPlaneOf<T> pl = px_plane<PxEl<T>::S>(g.N, g.H, g.W, g.k);
     int st = PF_OK;
-    if (!W_saved) st = launch_px_pack(s, PxPack{(const uint16_t *)Uk, pack, g.C, g.r, g.k * g.k});
+    if (!W_saved) st = launch_px_pack(s, PxPack<T>{Uk, pack, g.C, g.r, g.k * g.k});
     if (st != PF_OK) return st;
-    const PxBwdArgs b{pl, g.C, g.Cout, g.r, (const uint16_t *)dY, (const uint16_t *)Vp, W_saved ? (const uint16_t *)W_saved : pack,
-                      (uint16_t *)dX, dT, ep.scale, {nullptr, nullptr, (const uint16_t *)ep.add, (const uint16_t *)ep.mask, 0}};
+    const PxBwdArgs<T> b{pl, g.C, g.Cout, g.r, dY, Vp, W_saved ? W_saved : pack, dX, dT, ep.scale, {nullptr, nullptr, (const T *)ep.add, (const T *)ep.mask, 0}};
     st = launch_px_bwd(s, b, g.k, p.px_bwd, p.px_bwd_threads);
     if (st != PF_OK) return st;
-    const int kk = g.k * g.k, r8 = (g.r + 7) / 8 * 8;
+    const int kk = g.k * g.k, s1 = px_slab<T>(g.k, g.r), s2 = px_slab<T>(1, g.r);
     const i64 nU = (i64)g.r * g.C * kk, nV = (i64)g.r * g.Cout;
     float *partV = part + p.px_groups[0] * nU, *sums = partV + (p.px_groups[1] * nV + 63) / 64 * 64;
-    const PxWgradArgs w{px_plane(g.N, g.H, g.W, 1), pl, g.r, 2,
-                        {{dT, (const uint16_t *)X, r8, g.C, kk, (g.C + px_slab(g.k, g.r) - 1) / px_slab(g.k, g.r), p.px_groups[0], p.px_per[0], part, nullptr},
-                         {(const uint16_t *)T_saved, (const uint16_t *)dY, g.r, g.Cout, 1, (g.Cout + 127) / 128, p.px_groups[1], p.px_per[1], partV,
-                          ep.dshift ? sums : nullptr}}};
+    const PxWgradArgs<T> w{px_plane<PxEl<T>::S>(g.N, g.H, g.W, 1), pl, g.r, 2,
+                           {{dT, X, px_ranks<T>(g.r), g.C, kk, (g.C + s1 - 1) / s1, p.px_groups[0], p.px_per[0], part, nullptr},
+                            {T_saved, dY, g.r, g.Cout, 1, (g.Cout + s2 - 1) / s2, p.px_groups[1], p.px_per[1], partV, ep.dshift ? sums : nullptr}}};
     st = launch_px_wgrad(s, w);
     if (st != PF_OK) return st;
     SplitSumArgs ss = {};
@@ -970,15 +996,17 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     if (!p.saved_bytes) W_save = nullptr;
     if (p.px_fwd) {
         *fused = true;
-        PxFwdArgs x{px_plane(g.N, g.H, g.W, g.k), g.C, g.Cout, g.r, (const uint16_t *)X, (const uint16_t *)Uk, (const uint16_t *)Vp,
-                    (uint16_t *)Y, (uint16_t *)T_save, {scale, shift, (const uint16_t *)residual, nullptr, all.relu}, {}, {}, {}};
-        if (W_save && p.px_bwd) {
-            x.pack = {(const uint16_t *)Uk, (uint16_t *)W_save, g.C, g.r, g.k * g.k};
-        } else if (W_save && p.saved_bytes) {
-            x.chain1 = chain_saved_w1(g, Vp, W_save, scale);
-            x.chain2 = chain_saved_w2(g, p, Uk, W_save);
-        }
-        return launch_px_fwd(s, x, g.k, p.px_fwd, p.px_fwd_threads);
+        PackW1 w1 = {};
+        PackW2 w2 = {};
+        if (W_save && p.saved_bytes && !p.px_bwd) w1 = chain_saved_w1(g, Vp, W_save, scale), w2 = chain_saved_w2(g, p, Uk, W_save);
+        const auto go = [&](auto el) {
+            typedef decltype(el) T;
+            const PxPack<T> pack = {(const T *)Uk, p.px_bwd ? (T *)W_save : nullptr, g.C, g.r, g.k * g.k};
+            const PxFwdArgs<T> x{px_plane<PxEl<T>::S>(g.N, g.H, g.W, g.k), px_plane<PxEl<T>::S>(g.N, g.Ho, g.Wo, 1), g.s, g.C, g.Cout, g.r, (const T *)X, (const T *)Uk, (const T *)Vp, (T *)Y,
+                                 (T *)T_save, {scale, shift, (const T *)residual, nullptr, all.relu}, pack, w1, w2};
+            return launch_px_fwd(s, x, g.k, p.px_fwd, p.px_fwd_threads);
+        };
+        return d->dtype == PF_F32 ? go(float()) : go(uint16_t());
     }
     if (p.tiles && !(d->dtype == PF_BF16 && p.chain)) {
         *fused = true;
@@ -1032,9 +1060,13 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     if (!p.saved_bytes) W_saved = nullptr;
     if (p.px_bwd && dX && dUk && dVp && T_saved) {
         *fused = true;
-        return conv_bwd_px(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (const bf16_t *)dY, (const bf16_t *)T_saved, W_saved,
-                           (bf16_t *)dX, (float *)dUk, (float *)dVp, accumulate, ws, s,
-                           ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift});
+        const auto go = [&](auto el) {
+            typedef decltype(el) T;
+            return conv_bwd_px(g, p, (const T *)X, (const T *)Uk, (const T *)Vp, (const T *)dY, (const T *)T_saved, (const T *)W_saved, (T *)dX,
+                               (float *)dUk, (float *)dVp, accumulate, ws, s,
+                               ConvEpilogue{scale, nullptr, dX_add, x_is_relu ? X : nullptr, 0, dshift});
+        };
+        return d->dtype == PF_F32 ? go(float()) : go(uint16_t());
     }
     if (p.px_bwd) W_saved = nullptr; // (in the order of the kernels above)
     if (p.tiles && !(d->dtype == PF_BF16 && p.chain && dX)) {

@@ -15,46 +15,74 @@ namespace pf {
 // 128 images of 128 x 16 x 16, rank 32, 3 x 3: 15 us (the halo on X and nine taps per wavefront 19: the sums of four wavefronts that split
 // the pixels met in LDS, 295 KB in and out); a tile takes 1800 clocks of products and their LDS reads, 2000 of addresses, table and stores,
 // the partial sums of a workgroup 4500, which is the rate at which the chip writes them.
-template <int KK, int RB>
+template <typename T, int KK, int RB>
 struct PxWgCfg {
-    static constexpr int NT = 512, P = 128, SC = KK == 9 ? (RB == 4 ? 32 : 64) : 128, CB = SC / 32;
+    static constexpr int V = PxEl<T>::V, PC = PxEl<T>::PC, F4 = sizeof(T) == 4;
+    static constexpr int NT = 512, P = 128, SC = KK == 9 ? (RB == 4 ? 32 : 64) : F4 ? 64 : 128, CB = SC / 32;
     // one tap: a wavefront has MB rank blocks of one channel block
     static constexpr int MB = KK == 1 && RB == 4 ? 2 : 1, MW = RB / MB, NB = KK == 9 ? CB : 1, CW = CB / NB; // (RB blocks of ranks)
     static constexpr int TG = KK == 1 ? 1 : RB == 4 ? 2 : 4, KS = 8 / (CW * MW * TG);
     static constexpr int NTAP = (KK + TG - 1) / TG, TW = KK == 1 ? 0 : TG == 4 ? 4 : 8, TROW = TG * TW; // taps of a wavefront, words of the table per pixel pair
     static constexpr int NA = KK == 9 ? NTAP : MB;
-    static constexpr int AROWS = KK == 9 ? PX_WG_ROWS : 136, APANEL = AROWS * 128, ABYTES = (RB + 1) / 2 * APANEL, ZERO = AROWS - 1;
-    static constexpr int BROWS = 136, BPANEL = BROWS * 128, BBYTES = (SC + 63) / 64 * BPANEL;
+    static constexpr int AROWS = KK == 9 ? PX_WG_ROWS : 136, APANEL = AROWS * 128, APANELS = (32 * RB + PC - 1) / PC, ABYTES = APANELS * APANEL, ZERO = AROWS - 1;
+    static constexpr int BROWS = 136, BPANEL = BROWS * 128, BBYTES = (SC + PC - 1) / PC * BPANEL;
     static constexpr int TABLE = 64 * TROW * 4, BUF = ABYTES + BBYTES + TABLE;
-    static constexpr int AO = RB * 4, BO = SC / 8, BLOCKS = ((AO + BO) * 32 + NT - 1) / NT; // octets, blocks per thread
+    static constexpr int AO = 32 * RB / V, BO = SC / V, GS = V == 8 ? 4 : 5, BLOCKS = ((AO + BO) * (2 << GS) + NT - 1) / NT; // pieces, groups of a tile (log2), blocks per thread
     static constexpr int OPITCH = SC * KK + 4, ROUNDS = 1, OROWS = 32 * RB / ROUNDS, OBYTES = KS * OROWS * OPITCH * 4;
     static constexpr int BYTES = 2 * BUF > OBYTES ? 2 * BUF : OBYTES;
     static __host__ __device__ constexpr int tap0(int tg) { return TG == 4 ? (tg ? 2 * tg + 1 : 0) : 5 * tg; } // first tap of a group (3, 2, 2, 2 or 5, 4)
-    static_assert(BYTES <= 160 * 1024 && KS * TG * CW * MW == 8 && (KK == 9 || KS <= 2), "");
+    static_assert(BYTES <= 160 * 1024 && KS * TG * CW * MW == 8 && (KK == 9 || KS <= 4) && SC / V * 32 == (KK == 9 ? SC / V * 32 : NT), "");
 };
 
-template <int KK, int RB>
-__device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, int index, unsigned char *smem)
+// Float, one tap: products of one tile, 32 ranks x 32 channels over a wavefront's share of the pixels, in runs of 32 pixels with sums of their
+// own.  A row holds 32 ranks or channels, which is what the lanes of an operand want: plain reads, free of conflicts.
+template <typename F>
+__device__ __forceinline__ void px_wgrad_f32(const unsigned char *as, const unsigned char *bs, int ks, f32x16_t &acc)
 {
-    typedef PxWgCfg<KK, RB> F;
-    constexpr int NT = F::NT;
+    const int lane = threadIdx.x & 63, hi = lane >> 5;
+    // pixel 8 st + e + 4 hi of a run: where its piece lies in the row depends on st and e through their exclusive or only
+    uint32_t own[4];
+#pragma unroll
+    for (int z = 0; z < 4; ++z) own[z] = 4 * hi * 128 + ((hi << 4) ^ ((lane & 31) >> 2 << 4) ^ (z << 5)) + (lane & 3) * 4;
+#pragma unroll
+    for (int run = 0; run < 4 / F::KS; ++run) {
+        const int row0 = (ks * (4 / F::KS) + run) * 32;
+        f32x16_t sum;
+        px_clear(sum);
+#pragma unroll
+        for (int st = 0; st < 4; ++st)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int at = (row0 + 8 * st + e) * 128 + own[e ^ st];
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(*(const float *)(as + at), *(const float *)(bs + at), sum, 0, 0, 0);
+            }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] += sum[v];
+    }
+}
+
+template <typename T, int KK, int RB>
+__device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T> &p, int index, unsigned char *smem)
+{
+    typedef PxWgCfg<T, KK, RB> F;
+    constexpr int NT = F::NT, V = F::V;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hi = lane >> 5;
     const int unit = index % p.units, group = index / p.units, c0 = unit * F::SC;
-    const PxPlane &gt = KK == 9 ? a.gk : a.g1, &g1 = a.g1;
+    const PxPlaneOf<T> &gt = KK == 9 ? a.gk : a.g1, &g1 = a.g1;
     const int tiles = (g1.N * g1.HW + F::P - 1) / F::P, t0 = group * p.per, t1 = min(tiles, t0 + p.per);
-    // A thread's blocks: A's octets, then B's, with as many groups of pixels as a tile can have.  Without a halo a row is a pixel of the tile.
-    const int gshift = g1.HW % 8 == 0 ? 4 : 5, ashift = KK == 9 ? 5 : gshift, nA = F::AO << ashift, nB = F::BO << gshift;
-    int at[F::BLOCKS][8];
+    // A thread's blocks: A's pieces, then B's, with as many groups of pixels as a tile can have.  Without a halo a row is a pixel of the tile.
+    const int gshift = g1.HW % V == 0 ? F::GS : F::GS + 1, ashift = KK == 9 ? F::GS + 1 : gshift, nA = F::AO << ashift, nB = F::BO << gshift;
+    int at[F::BLOCKS][V];
     bool live[F::BLOCKS];
-    uint4 reg[F::BLOCKS][8];
-    const bool whole = g1.HW % 8 == 0; // (rows of a block then stay the same from tile to tile)
+    uint4 reg[F::BLOCKS][V];
+    const bool whole = g1.HW % V == 0; // (rows of a block then stay the same from tile to tile)
 #pragma unroll
     for (int u = 0; u < F::BLOCKS; ++u) {
         const int i = tid + NT * u;
         const bool isa = i < nA;
         const int j = isa ? i : i - nA, shift = isa ? ashift : gshift, gi = j & ((1 << shift) - 1), o = j >> shift;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) at[u][e] = (isa ? (o >> 3) * F::APANEL : F::ABYTES + (o >> 3) * F::BPANEL) + px_at(gi * 8 + e, o & 7);
+        for (int e = 0; e < V; ++e) at[u][e] = (isa ? (o >> 3) * F::APANEL : F::ABYTES + (o >> 3) * F::BPANEL) + px_at(gi * V + e, o & 7);
     }
     const auto fetch = [&](int tile) __attribute__((always_inline)) {
         const PxTile ta = px_tile(gt, tile * F::P, F::P), tb = px_tile(g1, tile * F::P, F::P);
@@ -64,19 +92,19 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
             if (i < nA + nB) {
                 const bool isa = i < nA;
                 const int j = isa ? i : i - nA, shift = isa ? ashift : gshift, gi = j & ((1 << shift) - 1), o = j >> shift;
-                const int ch = isa ? p.a_ch : p.C, c = (isa ? 0 : c0) + 8 * o;
-                const uint16_t *src = isa ? p.A : p.B;
+                const int ch = isa ? p.a_ch : p.C, c = (isa ? 0 : c0) + V * o;
+                const T *src = isa ? p.A : p.B;
                 int n, q;
                 live[u] = KK == 9 && isa ? px_group(gt, ta, gi, n, q) : px_group(g1, tb, gi, n, q);
                 if (!live[u]) n = q = 0;
                 // (channels past the last are sums that nobody stores)
                 const int off = (n * ch + min(c, ch - 1)) * g1.HW + q, most = max(ch - 1 - c, 0) * g1.HW;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) reg[u][k] = ldg16((const char *)src + 2u * (uint32_t)(off + min(k * g1.HW, most)));
+                for (int k = 0; k < V; ++k) reg[u][k] = px_load(src, off + min(k * g1.HW, most));
                 if (!whole && !(KK == 9 && isa)) {
                     const int s0 = n * g1.HW + q - tb.p0, base = isa ? (o >> 3) * F::APANEL : F::ABYTES + (o >> 3) * F::BPANEL;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) at[u][e] = base + px_at(s0 + e >= 0 && s0 + e < tb.p1 - tb.p0 ? s0 + e : F::BROWS - 1, o & 7);
+                    for (int e = 0; e < V; ++e) at[u][e] = base + px_at(s0 + e >= 0 && s0 + e < tb.p1 - tb.p0 ? s0 + e : F::BROWS - 1, o & 7);
                 }
             }
         }
@@ -86,7 +114,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
         for (int u = 0; u < F::BLOCKS; ++u)
             if (tid + NT * u < nA + nB && live[u]) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) *(uint4 *)(buf + at[u][e]) = px_turn(reg[u], e);
+                for (int e = 0; e < V; ++e) *(uint4 *)(buf + at[u][e]) = px_turn(reg[u], e);
             }
     };
     // rows of dT for pixels 8 j + e and 8 j + e + 4 of the tile and every tap
@@ -121,9 +149,9 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
         for (int j = 0; j < F::NB; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    float sum[KK == 1 ? 8 : 1];
+    float sum[KK == 1 ? V : 1];
 #pragma unroll
-    for (int e = 0; e < (KK == 1 ? 8 : 1); ++e) sum[e] = 0.f;
+    for (int e = 0; e < (KK == 1 ? V : 1); ++e) sum[e] = 0.f;
     // this lane's part of a transposing read: row and, in bytes, octet and half of a block of 32 channels
     const int trow = 8 * hi + (lane >> 2 & 3), toct = (lane >> 4 & 1) * 2 + (lane >> 1 & 1), thalf = (lane & 1) * 8;
     typedef __attribute__((address_space(3))) bf16x4_t *lds_ptr;
@@ -137,7 +165,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
     if (t0 < t1) {
         fetch(t0);
         if (KK == 9) {
-            if (tid < 16 * ((RB + 1) / 2)) *(uint4 *)(smem + (tid & 1) * F::BUF + (tid >> 4) * F::APANEL + F::ZERO * 128 + (tid >> 1 & 7) * 16) = px_zero();
+            if (tid < 16 * F::APANELS) *(uint4 *)(smem + (tid & 1) * F::BUF + (tid >> 4) * F::APANEL + F::ZERO * 128 + (tid >> 1 & 7) * 16) = px_zero();
             table(t0, smem);
         }
         ragged(t0, smem);
@@ -151,8 +179,9 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
             fetch(tile + 1);
             if (KK == 9) table(tile + 1, next);
         }
+        if constexpr (F::F4) px_wgrad_f32<F>(buf + mi * F::APANEL, bs + ci * F::BPANEL, ks, acc[0][0]);
 #pragma unroll
-        for (int q = 0; q < 8 / F::KS; ++q) {
+        for (int q = 0; q < (F::F4 ? 0 : 8 / F::KS); ++q) {
             const int step = ks * (8 / F::KS) + q, row = step * 16 + trow;
             bf16x8_t b[F::NB];
 #pragma unroll
@@ -191,10 +220,10 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
         if (KK == 1 && p.sums) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                float v[8];
-                piece_floats<bf16_t>(*(const uint4 *)(bs + (tid >> 8) * F::BPANEL + px_at((tid & 31) + 32 * k, tid >> 5 & 7)), v);
+                float v[V];
+                px_unpack<T>(*(const uint4 *)(bs + (tid >> 8) * F::BPANEL + px_at((tid & 31) + 32 * k, tid >> 5 & 7)), v);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) sum[KK == 1 ? e : 0] += v[e];
+                for (int e = 0; e < V; ++e) sum[KK == 1 ? e : 0] += v[e];
             }
         }
         if (tile + 1 < t1) {
@@ -237,34 +266,51 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs &a, const PxGrad &p, 
     }
     if (KK == 1 && p.sums) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
+        for (int e = 0; e < V; ++e) {
             float v = sum[KK == 1 ? e : 0];
 #pragma unroll
             for (int d = 1; d < 32; d <<= 1) v += __shfl_xor(v, d, 64);
-            const int c = c0 + (tid >> 5) * 8 + e;
+            const int c = c0 + (tid >> 5) * V + e;
             if ((tid & 31) == 0 && c < p.C) p.sums[(i64)group * p.C + c] = v;
         }
     }
 }
 
-template <int K1, int RB>
-__global__ __launch_bounds__(512, 2) void conv_px_wgrad_kernel(PxWgradArgs a)
+template <typename T, int K1, int RB>
+__global__ __launch_bounds__(512, 2) void conv_px_wgrad_kernel(PxWgradArgs<T> a)
 {
-    constexpr int b1 = PxWgCfg<K1, RB>::BYTES, b2 = PxWgCfg<1, RB>::BYTES;
+    constexpr int b1 = PxWgCfg<T, K1, RB>::BYTES, b2 = PxWgCfg<T, 1, RB>::BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[b1 > b2 ? b1 : b2];
     const int first = a.p[0].units * a.p[0].groups, b = blockIdx.x;
     if (K1 == 9 && a.p[0].kk == 9 && b < first)
-        px_wgrad<K1, RB>(a, a.p[0], b, smem);
+        px_wgrad<T, K1, RB>(a, a.p[0], b, smem);
     else
-        px_wgrad<1, RB>(a, b < first ? a.p[0] : a.p[1], b < first ? b : b - first, smem);
+        px_wgrad<T, 1, RB>(a, b < first ? a.p[0] : a.p[1], b < first ? b : b - first, smem);
 }
 
-int px_slab(int k, int r) { return k == 1 ? 128 : px_rank_blocks(r) == 4 ? 32 : 64; }
+template <typename T>
+int px_slab(int k, int r)
+{
+    if (sizeof(T) == 4) return 64;
+    return k == 1 ? 128 : px_rank_blocks(r) == 4 ? 32 : 64;
+}
+template int px_slab<uint16_t>(int, int);
+template int px_slab<float>(int, int);
+template <typename T>
+double px_wgrad_cost(int k, int r) // us per tile
+{
+    const int RB = px_rank_blocks(r);
+    if (sizeof(T) == 4) return 1.7;
+    return k == 3 ? (RB == 2 ? 6.5 : 4.6) : 3.0;
+}
+template double px_wgrad_cost<uint16_t>(int, int);
+template double px_wgrad_cost<float>(int, int);
+template <typename T>
 void px_wgrad_plan(int npx, int r, int C1, int k, int C2, int (&groups)[2], int (&per)[2])
 {
-    const int tiles = (npx + 127) / 128, RB = px_rank_blocks(r);
-    const int units[2] = {(C1 + px_slab(k, r) - 1) / px_slab(k, r), (C2 + 127) / 128};
-    const double cost[2] = {k == 3 ? (RB == 2 ? 6.5 : 4.6) : 3.0, 3.0};
+    const int tiles = (npx + 127) / 128, s1 = px_slab<T>(k, r), s2 = px_slab<T>(1, r);
+    const int units[2] = {(C1 + s1 - 1) / s1, (C2 + s2 - 1) / s2};
+    const double cost[2] = {px_wgrad_cost<T>(k, r), px_wgrad_cost<T>(1, r)};
     const double mb[2] = {4e-6 * r * C1 * k * k, 4e-6 * r * C2};
     double best = 1e30;
     for (int p1 = 1; p1 <= tiles; ++p1) { // tiles per group of the first problem; the second takes as long
@@ -282,21 +328,32 @@ void px_wgrad_plan(int npx, int r, int C1, int k, int C2, int (&groups)[2], int 
     }
 }
 
-template <int K1>
-static int px_wgrad_r(hipStream_t s, const PxWgradArgs &a)
+template void px_wgrad_plan<uint16_t>(int, int, int, int, int, int (&)[2], int (&)[2]);
+template void px_wgrad_plan<float>(int, int, int, int, int, int (&)[2], int (&)[2]);
+
+template <typename T, int K1, int RB>
+static int px_wgrad_l(hipStream_t s, const PxWgradArgs<T> &a)
 {
     int st = PF_OK, blocks = 0;
     for (int i = 0; i < a.n; ++i) blocks += a.p[i].units * a.p[i].groups;
-    const dim3 grid(blocks), nt(512);
-    if (a.r <= 32) PF_LAUNCH(st, "conv_wgrad_px", (conv_px_wgrad_kernel<K1, 1>), grid, nt, s, a);
-    else if (a.r <= 64) PF_LAUNCH(st, "conv_wgrad_px", (conv_px_wgrad_kernel<K1, 2>), grid, nt, s, a);
-    else PF_LAUNCH(st, "conv_wgrad_px", (conv_px_wgrad_kernel<K1, 4>), grid, nt, s, a);
+    PF_LAUNCH(st, "conv_wgrad_px", (conv_px_wgrad_kernel<T, K1, RB>), dim3(blocks), dim3(512), s, a);
     return st;
 }
-int launch_px_wgrad(hipStream_t s, const PxWgradArgs &a)
+template <int K1>
+static int px_wgrad_r(hipStream_t s, const PxWgradArgs<uint16_t> &a)
 {
-    if (a.n < 1 || a.r > 128) return PF_ERR_UNSUPPORTED;
-    return a.p[0].kk == 9 ? px_wgrad_r<9>(s, a) : px_wgrad_r<1>(s, a);
+    return a.r <= 32 ? px_wgrad_l<uint16_t, K1, 1>(s, a) : a.r <= 64 ? px_wgrad_l<uint16_t, K1, 2>(s, a) : px_wgrad_l<uint16_t, K1, 4>(s, a);
 }
+template <typename T>
+int launch_px_wgrad(hipStream_t s, const PxWgradArgs<T> &a)
+{
+    if (a.n < 1 || !px_bwd_takes<T>(a.p[0].kk == 9 ? 3 : 1, a.r)) return PF_ERR_UNSUPPORTED;
+    if constexpr (sizeof(T) == 4)
+        return px_wgrad_l<T, 1, 1>(s, a);
+    else
+        return a.p[0].kk == 9 ? px_wgrad_r<9>(s, a) : px_wgrad_r<1>(s, a);
+}
+template int launch_px_wgrad(hipStream_t, const PxWgradArgs<uint16_t> &);
+template int launch_px_wgrad(hipStream_t, const PxWgradArgs<float> &);
 
 } // namespace pf

@@ -1,4 +1,4 @@
-"""GPU parity of the pixel-major convolution kernels (pf_conv_px.h), every tile size with every rank block, against torch in float32:
+"""GPU parity of the pixel-major convolution kernels (pf_conv_px.h), every tile size with every rank block, against torch in 64 bits:
 planes that are whole 16-byte pieces and not, tiles over several images, a last tile that is not full, ranks and channels beside their blocks."""
 import ctypes
 import os
@@ -26,6 +26,8 @@ SHAPES = [
     (7, 264, 3, 5, 136, 37, 1),
     (3, 24, 13, 3, 520, 65, 1),
 ]
+SHAPES_F32 = [s for s in SHAPES if s[5] <= 64] + [(2, 44, 5, 5, 36, 7, 3), (40, 12, 2, 3, 4, 40, 3), (3, 68, 13, 3, 100, 30, 1),
+                                                 (9, 12, 5, 5, 76, 1, 1), (2, 264, 10, 6, 4, 32, 1)]  # (whole pieces: four)
 
 
 @pytest.fixture(scope="module")
@@ -41,6 +43,10 @@ def px(tmp_path_factory):
     return lib
 
 
+def _entry(px, name, dtype):
+    return getattr(px, f"px_{name}_{'f32' if dtype == torch.float32 else 'bf16'}")
+
+
 def _call(f, *args):
     conv = [ctypes.c_void_p(a.data_ptr()) if torch.is_tensor(a) else ctypes.c_void_p(None) if a is None else a for a in args]
     return f(*conv, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
@@ -51,55 +57,97 @@ def _close(got, want, rel, what):
     assert torch.isfinite(got.float()).all() and err <= rel, f"{what}: {err:.2e} > {rel:.0e}"
 
 
-@pytest.mark.parametrize("shape", SHAPES)
-def test_parity(px, shape):
-    """Rounding to bf16 changes an output by a share of 2^-8 = 3.9e-3 at most (1.7e-3 rms over many; the smallest shape has 64 outputs).
-    T and dT are rounded before the second stage, here and in the reference; filter gradients add bf16 products in float."""
+@pytest.mark.parametrize("dtype, shape", [(torch.bfloat16, s) for s in SHAPES] + [(torch.float32, s) for s in SHAPES_F32])
+def test_parity(px, dtype, shape):
+    """Rounding to bf16 changes an output by a share of 2^-8 = 3.9e-3 at most (1.7e-3 rms over many; the smallest shape has 64 outputs);
+    sums of some thousand float products have errors of 2^-24 each.  T and dT are rounded before the second stage, here and in the
+    reference; filter gradients add products of bf16 in float."""
     N, C, H, W, Cout, r, k = shape
+    f32 = dtype == torch.float32
+    tol, V = (1e-6, 4) if f32 else (4e-3, 8)
     g = torch.Generator(device="cuda").manual_seed(7)
     n = lambda *s: torch.randn(*s, generator=g, device="cuda")
-    b = lambda t: t.bfloat16()
+    b = lambda t: t.to(dtype)
     X, dZ = b(n(N, C, H, W).clamp_min(0)), b(n(N, Cout, H, W))
     Uk, Vp = b(n(r, C, k, k) * (C * k * k) ** -0.5), b(n(Cout, r) * r ** -0.5)
     scale, shift = torch.rand(Cout, generator=g, device="cuda") + 0.5, n(Cout) * 0.2
     res, add = b(n(N, Cout, H, W)), b(n(N, C, H, W))
-    T = F.conv2d(X.float(), Uk.float(), padding=k // 2)
+    h, out = lambda t: t.cpu().double(), lambda t: t.cuda()
+    T = out(F.conv2d(h(X), h(Uk), padding=k // 2))
     col = lambda v: v[None, :, None, None]
-    Vs = b(Vp.float() * scale[:, None]).float()
-    dT = F.conv2d(dZ.float(), Vs.t()[:, :, None, None].contiguous())
-    dX = torch.nn.grad.conv2d_input(X.shape, Uk.float(), b(dT).float(), padding=k // 2)
-    r8, taken = (r + 7) // 8 * 8, 0
+    Vs = b(Vp.float() * scale[:, None])
+    dT = out(F.conv2d(h(dZ), h(Vs).t()[:, :, None, None]))
+    dX = out(torch.nn.grad.conv2d_input(X.shape, h(Uk), h(b(dT)), padding=k // 2))
+    rv, taken, back = (r + V - 1) // V * V, 0, not f32 or (k == 1 and r <= 32)
     for P, threads in TILES:
-        pack = torch.zeros(px.px_pack_size(C, r, k), dtype=torch.bfloat16, device="cuda")
+        pack = torch.zeros(px.px_pack_size(C, r, k), dtype=dtype, device="cuda")
         for ep in (False, True):
-            Y, T1 = torch.full_like(res, float("nan")), torch.full((N, r, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
-            st = _call(px.px_fwd, N, C, H, W, Cout, r, k, P, threads, X, Uk, Vp, scale if ep else None, shift if ep else None,
+            Y, T1 = torch.full_like(res, float("nan")), torch.full((N, r, H, W), float("nan"), dtype=dtype, device="cuda")
+            st = _call(_entry(px, "fwd", dtype), N, C, H, W, Cout, r, k, 1, P, threads, X, Uk, Vp, scale if ep else None, shift if ep else None,
                        res if ep else None, int(ep), Y, T1, pack)
             if st:
-                assert st == 100 or (threads == 256 and r > 64), st
+                assert st == 100 or (threads == 256 and (f32 or r > 64)), st
                 break
             taken += 1
             what = f"{shape} {P} pixels, {threads} threads"
-            _close(T1, T, 4e-3, what + " T")
-            want = F.conv2d(T1.float(), Vp.float()[:, :, None, None])
-            _close(Y, (want * col(scale) + col(shift) + res.float()).clamp_min(0) if ep else want, 4e-3, what + " Y")
-            dX1, dT1 = torch.full_like(X, float("nan")), torch.full((N, r8, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
-            assert _call(px.px_bwd, N, C, H, W, Cout, r, k, P, threads, dZ, Vp, pack, scale, add if ep else None, X if ep else None, dX1, dT1) == 0
-            _close(dT1[:, :r], dT, 4e-3, what + " dT")
+            _close(T1, T, tol, what + " T")
+            want = out(F.conv2d(h(T1), h(Vp)[:, :, None, None]))
+            _close(Y, (want * col(scale) + col(shift) + res).clamp_min(0) if ep else want, tol, what + " Y")
+            if not back:
+                continue
+            dX1, dT1 = torch.full_like(X, float("nan")), torch.full((N, rv, H, W), float("nan"), dtype=dtype, device="cuda")
+            assert _call(_entry(px, "bwd", dtype), N, C, H, W, Cout, r, k, P, threads, dZ, Vp, pack, scale, add if ep else None, X if ep else None,
+                         dX1, dT1) == 0
+            _close(dT1[:, :r], dT, tol, what + " dT")
             assert not dT1[:, r:].any()
-            _close(dX1, (dX + add.float()) * (X > 0) if ep else dX, 4e-3, what + " dX")
-    assert taken >= 6, "most tile sizes take the shape"
-    Tb, dTb = b(T).contiguous(), torch.zeros(N, r8, H, W, dtype=torch.bfloat16, device="cuda")
+            _close(dX1, (dX + add) * (X > 0) if ep else dX, tol, what + " dX")
+    assert taken >= (3 if f32 else 6), "most tile sizes take the shape"
+    if not back:
+        return
+    Tb, dTb = b(T).contiguous(), torch.zeros(N, rv, H, W, dtype=dtype, device="cuda")
     dTb[:, :r] = b(dT)
     tiles = (N * H * W + 127) // 128
+    want_U = out(torch.nn.grad.conv2d_weight(h(X), Uk.shape, h(dTb[:, :r]), padding=k // 2))
+    want_V = torch.einsum("nop,nrp->or", dZ.flatten(2).double(), Tb.flatten(2).double())
     for per in {1, 3, tiles}:
         groups = (tiles + per - 1) // per
         pU, pV, ps = (torch.full((groups, m), float("nan"), device="cuda") for m in (r * C * k * k, r * Cout, Cout))
-        assert _call(px.px_wgrad, N, C, H, W, Cout, r, k, per, dTb, X, Tb, dZ, pU, pV, ps) == 0
-        # (sums of some thousand float products at 2^-24 each)
-        _close(pU.sum(0).view(r, C, k, k), torch.nn.grad.conv2d_weight(X.double(), Uk.shape, dTb[:, :r].double(), padding=k // 2), 1e-5, f"{shape} dUk")
-        _close(pV.sum(0).view(r, Cout).t(), torch.einsum("nop,nrp->or", dZ.flatten(2).double(), Tb.flatten(2).double()), 1e-5, f"{shape} dVp")
+        assert _call(_entry(px, "wgrad", dtype), N, C, H, W, Cout, r, k, per, dTb, X, Tb, dZ, pU, pV, ps) == 0
+        _close(pU.sum(0).view(r, C, k, k), want_U, 1e-5, f"{shape} dUk")
+        _close(pV.sum(0).view(r, Cout).t(), want_V, 1e-5, f"{shape} dVp")
         _close(ps.sum(0), dZ.double().sum((0, 2, 3)), 1e-5, f"{shape} sums")
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("shape", [
+    # N, C, H, W, Cout, r, k, stride
+    (3, 136, 16, 16, 264, 64, 3, 2),
+    (9, 72, 9, 11, 40, 13, 3, 2),   # output planes of 5 x 6
+    (2, 24, 8, 33, 16, 32, 3, 2),
+    (40, 8, 7, 7, 72, 40, 1, 2),
+    (3, 264, 16, 16, 136, 37, 1, 2),
+    (5, 16, 7, 21, 24, 8, 1, 3),
+])
+def test_strided_forward(px, dtype, shape):
+    """Bounds as above."""
+    N, C, H, W, Cout, r, k, stride = shape
+    tol = 1e-6 if dtype == torch.float32 else 4e-3
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, Uk, Vp = n(N, C, H, W).to(dtype), (n(r, C, k, k) * (C * k * k) ** -0.5).to(dtype), (n(Cout, r) * r ** -0.5).to(dtype)
+    h, out = lambda t: t.cpu().double(), lambda t: t.cuda()
+    T = out(F.conv2d(h(X), h(Uk), stride=stride, padding=k // 2))
+    res, taken = n(N, Cout, *T.shape[2:]).to(dtype), 0
+    for P, threads in TILES:
+        Y, T1 = torch.full_like(res, float("nan")), torch.full(T.shape, float("nan"), dtype=dtype, device="cuda")
+        st = _call(_entry(px, "fwd", dtype), N, C, H, W, Cout, r, k, stride, P, threads, X, Uk, Vp, None, None, res, 0, Y, T1, None)
+        if st:
+            assert st == 100 or threads == 256 or P == 128 or (P == 64 and k == 3), st
+            continue
+        taken += 1
+        _close(T1, T, tol, f"{shape} {P} T")
+        _close(Y, out(F.conv2d(h(T1), h(Vp)[:, :, None, None])) + res, tol, f"{shape} {P} Y")
+    assert taken >= 1
 
 
 def test_infinite_input(px):
@@ -112,7 +160,7 @@ def test_infinite_input(px):
     Uk[:, 5] = Uk[:, 5].abs()
     for P, threads in TILES:
         Y, T = torch.empty(N, Cout, H, W, dtype=torch.bfloat16, device="cuda"), torch.empty(N, r, H, W, dtype=torch.bfloat16, device="cuda")
-        assert _call(px.px_fwd, N, C, H, W, Cout, r, k, P, threads, X, Uk, Vp, None, None, None, 0, Y, T, None) == 0
+        assert _call(px.px_fwd_bf16, N, C, H, W, Cout, r, k, 1, P, threads, X, Uk, Vp, None, None, None, 0, Y, T, None) == 0
         want = torch.zeros(H, W, dtype=torch.bool, device="cuda")
         want[3:6, 3:6] = True
         assert (torch.isposinf(Y) == want).all() and torch.isfinite(Y[:, :, ~want]).all(), (P, threads)

@@ -19,21 +19,28 @@ def emu(tmp_path_factory):
     return ctypes.CDLL(out)
 
 
+@pytest.mark.parametrize("S", [2, 3])
 @pytest.mark.parametrize("k", [1, 3])
 @pytest.mark.parametrize("P", [32, 64, 128])
-def test_tiles(emu, k, P):
+def test_tiles(emu, S, k, P):
     """Every tap of every pixel of every tile is the pixel it should be, or a slot that nothing is stored to; loads stay in their planes."""
     for H, W, N in [(4, 4, 40), (8, 8, 5), (7, 7, 11), (16, 16, 2), (32, 32, 1), (5, 5, 40), (4, 32, 3), (32, 4, 3), (31, 29, 2), (2, 4, 9),
                     (13, 17, 3), (10, 10, 7), (9, 1, 30), (14, 14, 3), (3, 11, 9), (1, 8, 40)]:
-        assert emu.emu_px(N, H, W, k, P, 100000, 100000) == 0, (H, W, N)
+        assert emu.emu_px(S, N, H, W, k, 1, P, 100000, 100000) == 0, (H, W, N)
+        for stride in (2, 3):
+            if ((H - 1) // stride + 1) * ((W - 1) // stride + 1) >= 1 << S:
+                assert emu.emu_px(S, N, H, W, k, stride, P, 100000, 100000) == 0, (H, W, N, stride)
 
 
+@pytest.mark.parametrize("S,groups", [(2, 64), (3, 32)])
 @pytest.mark.parametrize("P,rows", [(32, 160), (64, 192), (128, 256)])
-def test_common_planes_fit(emu, P, rows):
+def test_common_planes_fit(emu, P, rows, S, groups):
     """Planes of 4 x 4 to 32 x 32 pixels fit the LDS that a tile has."""
     for H in range(4, 33):
         for W in {4, 5, 7, 8, H, 32}:
-            assert emu.emu_px(max(2, 300 // (H * W)), H, W, 3, P, rows, 32) == 0, (H, W)
+            assert emu.emu_px(S, max(2, 300 // (H * W)), H, W, 3, 1, P, rows, groups if P > 32 else groups // 2) == 0, (H, W)
+            if P == 32 and H >= 8 and W >= 8: # with stride
+                assert emu.emu_px(S, max(2, 600 // (H * W)), H, W, 3, 2, P, 256, groups) == 0, (H, W)
 
 
 def test_banks(emu):
