@@ -217,17 +217,20 @@ static bool chain_bwd_pays(i64 M, i64 in, i64 out, i64 r)
 // (several layers that share their input; backward, their dX is one tiled product over all ranks)
 static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 512 || (in <= 1024 && M <= 4096)); }
 
-// Both stages in one launch (pf_linear_two.h) or the tiled products: rows per workgroup, or 0.  Of the tiled products' time, fitted to the
-// same shapes (8 % rms): two launches, or three where T is split; the other kernel is the faster one for all but wide layers of some
-// thousand rows (1390 x 256 -> 101 -> 2384: 13.5 against 14.2).  Over 91 drawn shapes 1.25 times as fast, geometric mean.
+// Both stages in one launch (pf_linear_two.h): rows per workgroup, or 0 for the other kernels.  Their times, fitted to 130 shapes (7 and 9 %
+// rms): the tiled products' two launches, or three where T is split; at rank 128 and widths in multiples of 256 those of the chain kernel, or
+// the tiled products where it does not pay.  Over 43 drawn shapes 1.51 times as fast as the tiled products, geometric mean, over 60 of
+// the others 1.14 (8192 x 512 -> 128 -> 512 three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by
+// both); few rows and inputs up to 1024 wide stay with the row kernel (423 x 512 -> 512: 6.6 against 7.3).
 static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
 {
-    if (!linear_two_supported(M, in, out, r) || linear_chain2_supported(in, out, r)) return 0;
+    if (!linear_two_supported(M, in, out, r) || rows_fwd_pays(M, in, out, r, G)) return 0;
     int rows = 0;
-    const double t = plan_linear_two(M, in, out, r, G, rows, split);
-    const double tiled = 9.2 + 1e-6 * M * (0.371 * G * out * ((r + 63) / 64) + 0.353 * (in + G * out) * (r % 8 ? 2 : 1)) + 1.13e-3 * in +
-                         (in >= 512 && G * M * r < 64 * 64 * 200 ? 0.7 : 0);
-    return t < 0.97 * tiled ? rows : 0;
+    const double t = plan_linear_two(M, in, out, r, G, rows, split), m = 1e-6 * M;
+    const double chain = 8.07 + m * (0.625 * G * out + 0.205 * (in + G * out)) + 2.44e-3 * in;
+    const double tiled = 9.12 + m * (0.655 * G * out * ((r + 63) / 64) + 0.138 * (in + G * out) * (r % 8 ? 2 : 1)) + 1.09e-3 * in +
+                         (in >= 512 && G * M * r < 64 * 64 * 200 ? 0.5 : 0);
+    return t < (linear_chain2_supported(in, out, r) ? chain : 0.97 * tiled) ? rows : 0;
 }
 
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
@@ -839,7 +842,8 @@ static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_line
     const int G = d->groups;
     sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS &&
                    (chain_shared_fwd_pays(d->M, d->n_in) || rows_fwd_pays(d->M, d->n_in, d->n_out, d->r, G));
-    sp.two_fwd = d->dtype == PF_BF16 && !sp.fused_fwd ? two_fwd_rows(d->M, d->n_in, d->n_out, d->r, G, sp.two_split) : 0;
+    sp.two_fwd = d->dtype == PF_BF16 ? two_fwd_rows(d->M, d->n_in, d->n_out, d->r, G, sp.two_split) : 0;
+    if (sp.two_fwd) sp.fused_fwd = false;
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
     // one layer's workspace, then one more dX (layer by layer)

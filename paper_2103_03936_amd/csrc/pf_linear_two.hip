@@ -5,28 +5,30 @@
 namespace pf {
 
 // A workgroup of eight wavefronts takes 32 MB rows through both stages.  Both factors stream through LDS as they lie in memory (the
-// first one's fragments come from transposing reads), two parts of about 32 KB in flight in registers beside two in LDS: what bounds
-// the kernel is latency (a chunk of 40 KB takes 1500 clocks, of which its loads are 700 at the 58 bytes a clock that a compute unit takes
-// in with 32 KB outstanding, its LDS traffic 830) and, for many rows, the factors read again by every workgroup.  2000 rows, 256 ->
-// rank 64 -> 1024: 10.4 us on the tiled products (two or three launches), 6.6; 500 x 384 -> 96 -> 384: 9.2 -> 7.0; 8192 x 384 -> 96 ->
-// 1536: 23.7 -> 17.5.  Rank 128 and widths in multiples of 256 have a kernel of their own (8192 x 512 -> 512: 9.6, here 12.7), above
-// rank 128 the tiled products are faster (8192 x 768 -> 192 -> 768: 22.4 against 23.3, 1000 x 1024 -> 256 -> 1024 12.7 against 19), and
-// backward they form dX beside the gradients (500 x 384 -> 96 -> 384: 10.7 against 13.0 with both stages here).
+// first one's fragments come from transposing reads): beside the products of a chunk the next one goes to LDS, piece by piece, and the one
+// after that is requested.  Nothing is loaded or stored under a condition (BufSrc), so that a wait is for what is used and not for all that
+// was issued since.  What bounds it: the memory pipe (19 clocks for a kilobyte of a factor, of which every workgroup reads all), and the
+// chain of barrier, LDS reads, eight dependent products and the way of the outputs through LDS: 128 outputs of 32 rows take 1500 clocks,
+// with all of them alone under 600 each.  2000 rows, 256 -> rank 64 -> 1024: 10.4 us on the tiled products (two or three launches),
+// 6.6 before the pipelining, 5.9; 8192 x 512 -> 128 -> 512, three layers side by side 30.1 -> 19.0; 500 x 512 -> 128 -> 2048 18.8 -> 14.6.
+// Above rank 128 the tiled products are faster, and backward they form dX beside the gradients (500 x 384 -> 96 -> 384: 10.7 against 13.0
+// with both stages here).
 // WM x WN wavefronts over (ranks, rows), WK of them split the contraction of the first stage; the second takes 128 outputs at a time.
 template <int RB, int MB>
 struct LinTwoCfg {
     static constexpr int NT = 512, MR = 32 * MB, Kp = 32 * RB, KC = RB == 4 && MB == 4 ? 64 : 128;
-    static constexpr int WM = RB, WN = 8 / RB < MB ? 8 / RB : MB, WK = 8 / (WM * WN), NB = MB / WN;
+    static constexpr int WM = RB, WN = 8 / RB < MB ? 8 / RB : MB, WK = 8 / (WM * WN), NB = MB / WN, STEPS = KC / 16 / WK;
     static constexpr int VP = Kp + 8, XP = KC + 8;                                          // pitches (elements)
     static constexpr int VCH = KC * RB * 4 / NT, XCH = MR * KC / 8 / NT > 0 ? MR * KC / 8 / NT : 1; // pieces per thread
     static constexpr int VBYTES = KC * VP * 2, XBYTES = MR * XP * 2, BUF = VBYTES + XBYTES;
     static constexpr int SP = Kp + 4, SBYTES = WK > 1 ? WK * MR * SP * 4 : 0;                // sums of the first stage
-    static constexpr int OC = 128, ON = MB < 2 ? 1 : 2, NB2 = MB / ON, WK2 = 8 / (4 * ON);
-    static constexpr int AP = Kp + 8, ABYTES = OC * AP * 2, ACH = OC * RB * 4 / NT, ABUF = RB == 4 && MB == 4 ? 1 : 2;
-    static constexpr int CP = OC + 4, CBYTES = WK2 * MR * CP * 4, OUT = MR * OC / 8 / NT;
-    static_assert(KC / 16 % WK == 0 && 2 * RB % WK2 == 0, "whole steps");
-    static constexpr int TP = Kp + 8, TBYTES = MR * TP * 2;
-    static constexpr int S1 = 2 * BUF > SBYTES ? 2 * BUF : SBYTES, S2 = ABUF * ABYTES + CBYTES, BYTES = TBYTES + (S1 > S2 ? S1 : S2);
+    // second stage: a wavefront has 32 outputs of NB2 blocks of rows
+    static constexpr int OC = 128, NB2 = MB < 4 ? 1 : 2, AP = Kp + 8, ABYTES = OC * AP * 2, ACH = OC * RB * 4 / NT;
+    static constexpr int TP = Kp + 8, TBYTES = MR * TP * 2, OP = OC + 8, OBYTES = MR * OP * 2, BIAS = OC * 2;
+    static constexpr int S1 = TBYTES + (2 * BUF > SBYTES ? 2 * BUF : SBYTES);
+    static constexpr int O0 = 0, A0 = TBYTES > 2 * OBYTES ? TBYTES : 2 * OBYTES, B0 = A0 + 2 * ABYTES, S2 = B0 + 2 * BIAS; // (mid is gone when outputs come)
+    static constexpr int BYTES = S1 > S2 ? S1 : S2;
+    static_assert(KC / 16 % WK == 0 && 2 * RB % ACH == 0, "whole steps");
     static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
@@ -47,7 +49,8 @@ struct LinPiece {
     }
 };
 
-template <int RB, int MB>
+// EVEN: ranks in whole pieces.  Everything is then loaded and stored through descriptors without a branch.
+template <int RB, int MB, bool EVEN, bool ADD>
 __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
 {
     typedef LinTwoCfg<RB, MB> F;
@@ -64,82 +67,86 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     const int chunks = (N + F::OC - 1) / F::OC, c_begin = chunks * (int)blockIdx.y / a.osplit, c_end = chunks * ((int)blockIdx.y + 1) / a.osplit;
 
     // ------------------------------------------------ mid
-    uint4 vr[2][F::VCH], xr[2][F::XCH];
+    uint4 vr[F::VCH], xr[2][F::XCH]; // (the factors come from L2, the input from further away)
     const int steps = (K + KC - 1) / KC;
-    // A thread's pieces lie in one column of the factor and one of the input.  Ranks in whole pieces: nothing to put in place.
-    const bool even = r % 8 == 0;
+    // A thread's pieces lie in one column of the factor and one of the input.
+    const BufSrc sV(W1, 2LL * K * r), sX(a.in, 2LL * M * K), sU(W2, 2LL * N * r), sB(bias, 2LL * N), sA(a.add, 2LL * M * N), sY(out, 2LL * M * N);
     const int vrow = tid / (RB * 4), vcol = tid % (RB * 4), xrow = tid / (KC / 8), xcol = tid % (KC / 8) * 8;
     constexpr int VSTEP = NT / (RB * 4), XSTEP = NT / (KC / 8);
     const bool vin = vcol * 8 < r;
     uint32_t xat[F::XCH];
 #pragma unroll
-    for (int u = 0; u < F::XCH; ++u) xat[u] = (uint32_t)min(m0 + xrow + XSTEP * u, M - 1) * (uint32_t)K + xcol;
-    const auto load1 = [&](int q, uint4 (&v)[F::VCH], uint4 (&x)[F::XCH]) __attribute__((always_inline)) {
-        const int k0 = q * KC;
-        if (even && k0 + KC <= K) {
-#pragma unroll
-            for (int u = 0; u < F::VCH; ++u) v[u] = ldg16((const char *)(W1 + (i64)k0 * r) + 2u * (uint32_t)(vin ? (vrow + VSTEP * u) * r + vcol * 8 : 0));
-#pragma unroll
-            for (int u = 0; u < F::XCH; ++u) x[u] = ldg16((const char *)(a.in + k0) + 2u * xat[u]);
-            return;
-        }
-#pragma unroll
-        for (int u = 0; u < F::VCH; ++u) v[u] = LinPiece(k0 + vrow + VSTEP * u, vcol, K, r).load(W1, K * r);
-#pragma unroll
-        for (int u = 0; u < F::XCH; ++u) x[u] = ldg16((const char *)a.in + 2u * (xat[u] + (uint32_t)(min(k0 + xcol, K - 8) - xcol)));
+    for (int u = 0; u < F::XCH; ++u) xat[u] = (uint32_t)(m0 + xrow + XSTEP * u) * (uint32_t)K + xcol;
+    const auto load_v = [&](int q, int u) __attribute__((always_inline)) {
+        const int row = q * KC + vrow + VSTEP * u;
+        vr[u] = EVEN ? sV.load(vin ? 2u * (uint32_t)(row * r + vcol * 8) : BUF_OUT) : LinPiece(row, vcol, K, r).load(W1, K * r);
     };
-    const auto store1 = [&](int q, unsigned char *buf, const uint4 (&v)[F::VCH], const uint4 (&x)[F::XCH]) __attribute__((always_inline)) {
-        const int k0 = q * KC;
-        unsigned char *vb = buf + vrow * (F::VP * 2) + vcol * 16, *xb = buf + F::VBYTES + xrow * (F::XP * 2) + xcol * 2;
-        if (even && k0 + KC <= K) { // (ranks past the last are sums that nobody reads)
-#pragma unroll
-            for (int u = 0; u < F::VCH; ++u) *(uint4 *)(vb + VSTEP * u * (F::VP * 2)) = v[u];
-#pragma unroll
-            for (int u = 0; u < F::XCH; ++u)
-                if (MR >= XSTEP || xrow < MR) *(uint4 *)(xb + XSTEP * u * (F::XP * 2)) = x[u];
-            return;
-        }
-#pragma unroll
-        for (int u = 0; u < F::VCH; ++u) *(uint4 *)(vb + VSTEP * u * (F::VP * 2)) = LinPiece(k0 + vrow + VSTEP * u, vcol, K, r).fix(v[u], K * r);
-        const bool in = k0 + xcol < K;
-#pragma unroll
-        for (int u = 0; u < F::XCH; ++u)
-            if (MR >= XSTEP || xrow < MR) {
-                const uint4 w = x[u];
-                *(uint4 *)(xb + XSTEP * u * (F::XP * 2)) = make_uint4(in ? w.x : 0u, in ? w.y : 0u, in ? w.z : 0u, in ? w.w : 0u);
-            }
+    const auto load_x = [&](int q, int u, uint4 &x) __attribute__((always_inline)) { x = sX.load(q * KC + xcol < K ? 2u * (xat[u] + q * KC) : BUF_OUT); };
+    const auto store_v = [&](int q, int u, unsigned char *buf) __attribute__((always_inline)) { // (ranks past the last are sums that nobody reads)
+        *(uint4 *)(buf + (vrow + VSTEP * u) * (F::VP * 2) + vcol * 16) = EVEN ? vr[u] : LinPiece(q * KC + vrow + VSTEP * u, vcol, K, r).fix(vr[u], K * r);
     };
-    load1(0, vr[0], xr[0]);
-    if (steps > 1) load1(1, vr[1], xr[1]);
+    const auto store_x = [&](int u, unsigned char *buf, const uint4 &x) __attribute__((always_inline)) {
+        if (MR >= XSTEP || xrow < MR) *(uint4 *)(buf + F::VBYTES + (xrow + XSTEP * u) * (F::XP * 2) + xcol * 2) = x;
+    };
+#pragma unroll
+    for (int u = 0; u < F::XCH; ++u) load_x(0, u, xr[0][u]);
+#pragma unroll
+    for (int u = 0; u < F::VCH; ++u) load_v(0, u);
+#pragma unroll
+    for (int u = 0; u < F::XCH; ++u) load_x(1, u, xr[1][u]);
     const int wk = wave / (F::WM * F::WN), wm = wave / F::WN % F::WM, wn = wave % F::WN;
     f32x16_t acc[F::NB];
 #pragma unroll
     for (int j = 0; j < F::NB; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-    for (int q0 = 0; q0 < steps; q0 += 2) {
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int q = q0 + p;
-            if (q < steps) {
-                unsigned char *buf = base + p * F::BUF;
-                store1(q, buf, vr[p], xr[p]);
-                if (q + 2 < steps) load1(q + 2, vr[p], xr[p]);
-                __syncthreads();
-#pragma unroll
-                for (int s = 0; s < KC / 16 / F::WK; ++s) {
-                    const int st = wk * (KC / 16 / F::WK) + s;
-                    if (q * KC + st * 16 >= K) break;
-                    const bf16x8_t f = lds_frag_tr((const uint16_t *)buf, F::VP, st * 16, wm * 32, lane);
-#pragma unroll
-                    for (int j = 0; j < F::NB; ++j) {
-                        const bf16x8_t b = *(const bf16x8_t *)(buf + F::VBYTES + ((wn * F::NB + j) * 32 + (lane & 31)) * (F::XP * 2) + (st * 16 + hi * 8) * 2);
-                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, b, acc[j], 0, 0, 0);
-                    }
-                }
-            }
-        }
+    for (int u = 0; u < F::XCH; ++u) {
+        store_x(u, base, xr[0][u]);
+        load_x(2, u, xr[0][u]);
     }
+#pragma unroll
+    for (int u = 0; u < F::VCH; ++u) {
+        store_v(0, u, base);
+        load_v(1, u);
+    }
+    // a chunk's products beside the next one's way to LDS and the one after that's from memory
+    const auto step1 = [&](int q, const unsigned char *buf, unsigned char *next, uint4 (&x)[F::XCH]) __attribute__((always_inline)) {
+        __syncthreads();
+        bf16x8_t f[2], b[2][F::NB];
+        const auto frags = [&](int s) __attribute__((always_inline)) {
+            const int st = wk * F::STEPS + s;
+            f[s & 1] = lds_frag_tr((const uint16_t *)buf, F::VP, st * 16, wm * 32, lane);
+#pragma unroll
+            for (int j = 0; j < F::NB; ++j)
+                b[s & 1][j] = *(const bf16x8_t *)(buf + F::VBYTES + ((wn * F::NB + j) * 32 + (lane & 31)) * (F::XP * 2) + (st * 16 + hi * 8) * 2);
+        };
+        frags(0);
+#pragma unroll
+        for (int s = 0; s < F::STEPS; ++s) {
+            if (s + 1 < F::STEPS) frags(s + 1);
+#pragma unroll
+            for (int j = 0; j < F::NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s & 1], b[s & 1][j], acc[j], 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < F::XCH; ++u)
+                if (u * F::STEPS / F::XCH == s) {
+                    store_x(u, next, x[u]);
+                    load_x(q + 3, u, x[u]);
+                }
+#pragma unroll
+            for (int u = 0; u < F::VCH; ++u)
+                if (u * F::STEPS / F::VCH == s) {
+                    store_v(q + 1, u, next);
+                    load_v(q + 2, u);
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    for (int q = 0; q < steps - 1; q += 2) {
+        step1(q, base, base + F::BUF, xr[1]);
+        step1(q + 1, base + F::BUF, base, xr[0]);
+    }
+    if (steps & 1) step1(steps - 1, base, base + F::BUF, xr[1]);
 
     // the sums -> LDS in bf16, zero past the last rank whatever the input holds
     if constexpr (F::WK == 1) {
@@ -180,33 +187,47 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     }
 
     // ------------------------------------------------ out
-    uint4 ar[2][F::ACH];
-    const int parts = c_end - c_begin;
-    const auto load2 = [&](int q, uint4 (&to)[F::ACH]) __attribute__((always_inline)) {
-        const int o0 = (c_begin + q) * F::OC;
-        if (even && o0 + F::OC <= N) {
-#pragma unroll
-            for (int u = 0; u < F::ACH; ++u) to[u] = ldg16((const char *)(W2 + (i64)o0 * r) + 2u * (uint32_t)(vin ? (vrow + VSTEP * u) * r + vcol * 8 : 0));
-            return;
-        }
-#pragma unroll
-        for (int u = 0; u < F::ACH; ++u) to[u] = LinPiece(o0 + vrow + VSTEP * u, vcol, N, r).load(W2, N * r);
+    // 128 at a time.  A lane of the products has four neighbouring outputs of a row in every fourth register: stored from there, 32 bytes of
+    // a row side by side, a kilobyte took 65 clocks of the memory pipe, of whole rows 20.  So they pass through LDS, in bf16 and two buffers,
+    // where the residual waits in the places of the outputs that it is added to; a piece of a row belongs to one thread on both ways.
+    constexpr int NB2 = F::NB2, OP = F::OP;
+    const int wo = wave % 4, wr = wave / 4 * NB2; // outputs, first block of rows
+    const bool active = MB > 1 || __builtin_amdgcn_readfirstlane(wave) < 4;
+    uint4 ar[F::ACH], add[2][ADD ? MB : 1], bs;
+    const int parts = c_end - c_begin, orow = tid / 16, ocol = tid % 16 * 8; // (and every 32nd row from there)
+    uint16_t *as0 = (uint16_t *)(lt_smem + F::A0), *as1 = (uint16_t *)(lt_smem + F::A0 + F::ABYTES);
+    uint16_t *os0 = (uint16_t *)(lt_smem + F::O0), *os1 = (uint16_t *)(lt_smem + F::O0 + F::OBYTES);
+    uint16_t *bs0 = (uint16_t *)(lt_smem + F::B0), *bs1 = (uint16_t *)(lt_smem + F::B0 + F::BIAS);
+    const auto load_u = [&](int q, int u) __attribute__((always_inline)) {
+        const int row = (c_begin + q) * F::OC + vrow + VSTEP * u;
+        ar[u] = EVEN ? sU.load(vin ? 2u * (uint32_t)(row * r + vcol * 8) : BUF_OUT) : LinPiece(row, vcol, N, r).load(W2, N * r);
     };
-    load2(0, ar[0]);
-    if (parts > 1) load2(1, ar[1]);
-    uint4 add[F::OUT], bs;
-    const int orow = tid / 16, ocol = tid % 16 * 8; // (and every 32nd row from there)
-    const auto load_ep = [&](int o0) __attribute__((always_inline)) {
-        const int o = min(o0 + ocol, N - 8);
-        bs = bias ? ldg16((const char *)bias + 2u * (uint32_t)o) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int u = 0; u < F::OUT; ++u) {
-            const uint32_t at = (uint32_t)min(m0 + orow + 32 * u, M - 1) * (uint32_t)N + o;
-            if (a.add) add[u] = ldg16((const char *)a.add + 2u * at);
-        }
+    const auto store_u = [&](int q, int u, uint16_t *as) __attribute__((always_inline)) { // (half a step past the last rank: zero)
+        const int row = vrow + VSTEP * u;
+        *(uint4 *)&as[row * F::AP + vcol * 8] = EVEN ? ar[u] : LinPiece((c_begin + q) * F::OC + row, vcol, N, r).fix(ar[u], N * r);
     };
-    load_ep(c_begin * F::OC);
+    const auto out_at = [&](int q, int u) __attribute__((always_inline)) {
+        const int o = (c_begin + q) * F::OC + ocol, row = m0 + orow + 32 * u;
+        return (q >= 0) & (o < N) & (row < M) ? 2u * ((uint32_t)row * (uint32_t)N + o) : BUF_OUT;
+    };
+    const auto load_b = [&](int q) __attribute__((always_inline)) { bs = sB.load(tid < 16 ? 2u * (uint32_t)((c_begin + q) * F::OC + ocol) : BUF_OUT); };
+#pragma unroll
+    for (int u = 0; u < F::ACH; ++u) load_u(0, u);
+    if (tid < 64) load_b(0);
+    if constexpr (ADD) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int u = 0; u < MB; ++u) add[i][u] = sA.load(out_at(i, u));
+    }
     __syncthreads();
+    bf16x8_t tf[NB2][2 * RB];
+    if (active) {
+#pragma unroll
+        for (int j = 0; j < NB2; ++j)
+#pragma unroll
+            for (int st = 0; st < 2 * RB; ++st) tf[j][st] = *(const bf16x8_t *)&ts[((wr + j) * 32 + (lane & 31)) * TP + st * 16 + hi * 8];
+    }
     if (mid && blockIdx.y == 0) {
         const int per = (r + 7) / 8;
         for (int i = tid; i < MR * per; i += NT) {
@@ -225,83 +246,108 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
             }
         }
     }
-    const int om = wave % 4, on = wave / 4 % F::ON, wk2 = wave / (4 * F::ON);
-    float *cs = (float *)(base + F::ABUF * F::ABYTES);
-    f32x16_t y[F::NB2];
+    const bool relu = a.relu != 0;
+    __syncthreads();
 #pragma unroll
-    for (int j = 0; j < F::NB2; ++j)
+    for (int u = 0; u < F::ACH; ++u) {
+        store_u(0, u, as0);
+        load_u(1, u);
+    }
+    if (tid < 64) {
+        if (tid < 16) *(uint4 *)&bs0[ocol] = bs;
+        load_b(1);
+    }
+    if constexpr (ADD) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) y[j][v] = 0.f;
-    for (int q0 = 0; q0 < parts; q0 += 2) {
+        for (int u = 0; u < MB; ++u) {
+            *(uint4 *)&os0[(orow + 32 * u) * OP + ocol] = add[0][u];
+            add[0][u] = sA.load(out_at(2, u));
+        }
+    }
+    // 128 outputs' products, beside them the next factor rows on their way to LDS, those after them from memory, and the outputs before
+    const auto step2 = [&](int q, const uint16_t *as, uint16_t *anext, uint16_t *os, uint16_t *obefore, const uint16_t *bias_s, uint16_t *bnext,
+                           uint4 (&x)[ADD ? MB : 1]) __attribute__((always_inline)) {
+        __syncthreads();
+        uint4 before[MB];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            const int q = q0 + p, o0 = (c_begin + q) * F::OC;
-            if (q < parts) {
-                uint16_t *as = (uint16_t *)(base + (F::ABUF == 2 ? p * F::ABYTES : 0));
-                if (F::ABUF == 1) __syncthreads();
-                if (even && o0 + F::OC <= N) { // (half a step past the last rank: zero)
+        for (int u = 0; u < MB; ++u) before[u] = *(const uint4 *)&obefore[(orow + 32 * u) * OP + ocol];
+        const auto frag = [&](int st) __attribute__((always_inline)) { return *(const bf16x8_t *)&as[(wo * 32 + (lane & 31)) * F::AP + st * 16 + hi * 8]; };
+        bf16x8_t f[2];
+        f32x16_t y[NB2];
+        if (active) f[0] = frag(0);
+        if (active) { // the sums start from the bias and the residual
 #pragma unroll
-                    for (int u = 0; u < F::ACH; ++u) {
-                        const uint4 w = ar[p][u];
-                        *(uint4 *)&as[(vrow + VSTEP * u) * F::AP + vcol * 8] = make_uint4(vin ? w.x : 0u, vin ? w.y : 0u, vin ? w.z : 0u, vin ? w.w : 0u);
-                    }
-                } else {
+            for (int k = 0; k < 4; ++k) {
+                const uint2 b = *(const uint2 *)&bias_s[wo * 32 + 8 * k + 4 * hi];
 #pragma unroll
-                    for (int u = 0; u < F::ACH; ++u)
-                        *(uint4 *)&as[(vrow + VSTEP * u) * F::AP + vcol * 8] = LinPiece(o0 + vrow + VSTEP * u, vcol, N, r).fix(ar[p][u], N * r);
-                }
-                if (q + 2 < parts) load2(q + 2, ar[p]);
-                __syncthreads();
-#pragma unroll
-                for (int s = 0; s < 2 * RB / F::WK2; ++s) {
-                    const int st = wk2 * (2 * RB / F::WK2) + s;
-                    if (st * 16 >= r) break;
-                    const bf16x8_t f = *(const bf16x8_t *)&as[(om * 32 + (lane & 31)) * F::AP + st * 16 + hi * 8];
-#pragma unroll
-                    for (int j = 0; j < F::NB2; ++j) {
-                        const bf16x8_t b = *(const bf16x8_t *)&ts[((on * F::NB2 + j) * 32 + (lane & 31)) * TP + st * 16 + hi * 8];
-                        y[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, b, y[j], 0, 0, 0);
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < F::NB2; ++j)
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        const f32x4_t w = {y[j][4 * k], y[j][4 * k + 1], y[j][4 * k + 2], y[j][4 * k + 3]};
-                        *(f32x4_t *)&cs[(wk2 * MR + (on * F::NB2 + j) * 32 + (lane & 31)) * F::CP + om * 32 + 8 * k + 4 * hi] = w;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) y[j][4 * k + e] = 0.f;
-                    }
-                __syncthreads();
-                if (o0 + ocol < N) {
-                    float b[8];
-                    piece_floats<bf16_t>(bs, b);
-#pragma unroll
-                    for (int u = 0; u < F::OUT; ++u) {
-                        const int row = orow + 32 * u;
-                        float v[8], f[8];
-#pragma unroll
-                        for (int e = 0; e < 8; e += 4) {
-                            f32x4_t w = *(const f32x4_t *)&cs[row * F::CP + ocol + e];
-                            if (F::WK2 == 2) w += *(const f32x4_t *)&cs[(MR + row) * F::CP + ocol + e];
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) v[e + x] = w[x] + b[e + x];
-                        }
-                        if (a.add) {
-                            piece_floats<bf16_t>(add[u], f);
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] += f[e];
-                        }
-                        if (a.relu) {
-#pragma unroll
-                            for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
-                        }
-                        if (m0 + row < M) stg16((char *)out + 2u * ((uint32_t)(m0 + row) * (uint32_t)N + o0 + ocol), floats_piece<bf16_t>(v));
+                for (int j = 0; j < NB2; ++j) {
+                    y[j][4 * k] = __uint_as_float(b.x << 16), y[j][4 * k + 1] = __uint_as_float(b.x & 0xffff0000u);
+                    y[j][4 * k + 2] = __uint_as_float(b.y << 16), y[j][4 * k + 3] = __uint_as_float(b.y & 0xffff0000u);
+                    if constexpr (ADD) {
+                        const uint2 d = *(const uint2 *)&os[((wr + j) * 32 + (lane & 31)) * OP + wo * 32 + 8 * k + 4 * hi];
+                        y[j][4 * k] += __uint_as_float(d.x << 16), y[j][4 * k + 1] += __uint_as_float(d.x & 0xffff0000u);
+                        y[j][4 * k + 2] += __uint_as_float(d.y << 16), y[j][4 * k + 3] += __uint_as_float(d.y & 0xffff0000u);
                     }
                 }
-                if (q + 1 < parts) load_ep(o0 + F::OC);
             }
         }
+#pragma unroll
+        for (int st = 0; st < 2 * RB; ++st) {
+            if (active) {
+                if (st + 1 < 2 * RB) f[(st + 1) & 1] = frag(st + 1);
+#pragma unroll
+                for (int j = 0; j < NB2; ++j) y[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[st & 1], tf[j][st], y[j], 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < F::ACH; ++u)
+                if (u * 2 * RB / F::ACH == st) {
+                    store_u(q + 1, u, anext);
+                    load_u(q + 2, u);
+                }
+#pragma unroll
+            for (int u = 0; u < MB; ++u)
+                if (u * 2 * RB / MB == st) {
+                    sY.store(out_at(q - 1, u), before[u]);
+                    if constexpr (ADD) {
+                        *(uint4 *)&obefore[(orow + 32 * u) * OP + ocol] = x[u];
+                        x[u] = sA.load(out_at(q + 3, u));
+                    }
+                }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (tid < 64) {
+            if (tid < 16) *(uint4 *)&bnext[ocol] = bs;
+            load_b(q + 2);
+        }
+        if (active) {
+#pragma unroll
+            for (int j = 0; j < NB2; ++j) {
+                if (relu) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) y[j][v] = fmaxf(y[j][v], 0.f);
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *(uint2 *)&os[((wr + j) * 32 + (lane & 31)) * OP + wo * 32 + 8 * k + 4 * hi] =
+                        make_uint2(pack_bf16x2(y[j][4 * k], y[j][4 * k + 1]), pack_bf16x2(y[j][4 * k + 2], y[j][4 * k + 3]));
+            }
+        }
+    };
+    const auto last = [&](int q, const uint16_t *os) __attribute__((always_inline)) {
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < MB; ++u) sY.store(out_at(q, u), *(const uint4 *)&os[(orow + 32 * u) * OP + ocol]);
+    };
+    int q = 0;
+    for (; q < parts - 1; q += 2) {
+        step2(q, as0, as1, os0, os1, bs0, bs1, add[1]);
+        step2(q + 1, as1, as0, os1, os0, bs1, bs0, add[0]);
+    }
+    if (parts & 1) {
+        step2(q, as0, as1, os0, os1, bs0, bs1, add[1]);
+        last(q, os0);
+    } else {
+        last(q - 1, os1);
     }
 }
 
@@ -313,22 +359,23 @@ bool linear_two_supported(i64 M, i64 K, i64 N, i64 r)
     return M >= 1 && K >= 8 && N >= 8 && K % 8 == 0 && N % 8 == 0 && r >= 8 && r <= 128 && M * K < lim && M * N < lim && K * r < lim && N * r < lim;
 }
 
-// Fitted to times of 108 shapes (1 to 16384 rows, 128 to 4096 wide, ranks 16 to 128) with every number of rows and share of the outputs, 10 %
-// rms: a chunk of the first stage costs 0.21 us, 128 outputs 0.12 per 32 rows, and what a compute unit reads 17 and 31 ns per KB.
+// Fitted to times of 130 shapes (1 to 16384 rows, 128 to 4096 wide, ranks 8 to 128) with every number of rows and share of the outputs, 8 %
+// rms: what a workgroup costs and 32 rows through a chunk of either stage, and what a compute unit reads and writes 12 and 14 ns per KB.
 double plan_linear_two(i64 M, i64 K, i64 N, i64 r, int groups, int &rows, int &osplit)
 {
     double best = 1e30;
     const int RB = lt_blocks(r), chunks = (int)((N + 127) / 128);
     for (int mb = 1; mb <= 4; mb *= 2) {
         const i64 tiles = (M + 32 * mb - 1) / (32 * mb);
-        const double steps = (double)((K + (RB == 4 && mb == 4 ? 63 : 127)) / (RB == 4 && mb == 4 ? 64 : 128));
-        for (int os = 1; os <= chunks && os <= 16; os *= 2) {
+        const int KC = RB == 4 && mb == 4 ? 64 : 128;
+        const double steps = (double)((K + KC - 1) / KC);
+        for (int os = 1; os <= chunks && os <= 8; os *= 2) {
             const int per = (chunks + os - 1) / os;
             const i64 rounds = (tiles * os * groups + 255) / 256;
             const double full = tiles * os * groups < 256 ? tiles * os * groups / 256.0 : 1;
             const double kb1 = K * (r + 32.0 * mb) / 512, kb2 = per * 128.0 * (r + 32 * mb) / 512;
-            const double t = 3.8 + rounds * (0.21 * steps + 0.116 * per * mb + 0.0172 * kb1 + 0.0312 * kb2 + 0.0026 * full * (kb1 + kb2) +
-                                             (r % 8 ? 0.37 * (steps + per) : 0));
+            const double t = 3.49 + rounds * (0.77 + 0.0392 * steps * mb + 0.0044 * per + 0.0452 * per * mb + 0.0121 * kb1 + 0.0137 * kb2 +
+                                              0.0049 * full * (kb1 + kb2) + (r % 8 ? 0.33 * (steps + per) : 0));
             if (t < best) best = t, rows = 32 * mb, osplit = os;
         }
     }
@@ -340,7 +387,11 @@ static int lt_launch(hipStream_t s, const char *name, const LinTwoArgs &a)
 {
     typedef LinTwoCfg<RB, MB> F;
     int st = PF_OK;
-    PF_LAUNCH(st, name, (linear_two_kernel<RB, MB>), dim3((unsigned)((a.M + F::MR - 1) / F::MR), a.osplit, a.groups), dim3(F::NT), s, a);
+    const dim3 grid((unsigned)((a.M + F::MR - 1) / F::MR), a.osplit, a.groups);
+    if (a.r % 8 == 0 && a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, true>), grid, dim3(F::NT), s, a);
+    else if (a.r % 8 == 0) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false>), grid, dim3(F::NT), s, a);
+    else if (a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, true>), grid, dim3(F::NT), s, a);
+    else PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, false>), grid, dim3(F::NT), s, a);
     return st;
 }
 template <int RB>

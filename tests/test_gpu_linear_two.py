@@ -32,8 +32,8 @@ def test_parity(two, M, K, N, r, G):
     n = lambda *s: torch.randn(*s, generator=g, device="cuda")
     X, V, U = n(M, K).bfloat16(), (n(G, K, r) * K ** -0.5).bfloat16(), (n(G, N, r) * r ** -0.5).bfloat16()
     bias, add = n(G, N).bfloat16(), n(M, N).bfloat16()
-    chunks = (N + 127) // 128
     for rows in (32, 64, 128):
+        chunks = (N + 127) // 128
         for osplit in {1, min(2, chunks), chunks}:
             for ep in (False, True):
                 Y, T = (torch.full((G, M, w), float("nan"), dtype=torch.bfloat16, device="cuda") for w in (N, r))
