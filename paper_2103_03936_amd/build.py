@@ -4,6 +4,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -32,16 +33,19 @@ def build(verbose=False, jobs=8):
         obj = os.path.join(objdir, os.path.basename(src) + ".o")
         objs.append(obj)
         cmd = [hipcc] + [f for f in FLAGS if f != "-shared"] + ["-c", src, "-o", obj]
-        procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+        log = tempfile.TemporaryFile("w+")  # (a pipe that nobody reads yet stops a compiler that says much)
+        procs.append((log, subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT)))
         while len([p for _, p in procs if p.poll() is None]) >= jobs:
             for _, p in procs:
                 if p.poll() is None:
                     p.wait()
                     break
     failed = False
-    for src, p in procs:
-        out, _ = p.communicate()
-        lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
+    for log, p in procs:
+        p.wait()
+        with log:
+            log.seek(0)
+            lines = [l for l in log.read().splitlines() if "packed-fp32-ops" not in l]
         if p.returncode != 0 or verbose:
             sys.stderr.write("\n".join(lines) + "\n")
         failed |= p.returncode != 0

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     };
     const auto out_at = [&](int q, int u) __attribute__((always_inline)) {
         const int o = (c_begin + q) * F::OC + ocol, row = m0 + orow + 32 * u;
-        return (q >= 0) & (o < N) & (row < M) ? 2u * ((uint32_t)row * (uint32_t)N + o) : BUF_OUT;
+        return ((q >= 0) & (o < N) & (row < M)) ? 2u * ((uint32_t)row * (uint32_t)N + o) : BUF_OUT;
     };
     const auto load_b = [&](int q) __attribute__((always_inline)) { bs = sB.load(tid < 16 ? 2u * (uint32_t)((c_begin + q) * F::OC + ocol) : BUF_OUT); };
 #pragma unroll
