@@ -4,6 +4,7 @@
 // pieces on the guarded element-wise GEMM.
 #include "pf_conv_chain.h"
 #include "pf_linear_chain.h"
+#include "pf_linear_grad.h"
 #include "pf_linear_two.h"
 #include "pf_skinny.h"
 #include "pf_linear_small.h"
@@ -165,6 +166,9 @@ struct LinearPlan {
     int wg_groups, wg_ipg; // row-tile groups of the factor-gradient kernel and tiles per group
     int wg_cols;           // columns per workgroup of that kernel
     int two_fwd, two_split; // rows per workgroup and shares of the outputs where both stages forward are one launch of pf_linear_two.h, 0: not
+    int two_bwd, two_bwd_split; // the same for dT and dX; the factor gradients are then those of pf_linear_grad.h
+    LinGradPlan lg;
+    size_t n_lg; // their partial sums, floats
     bool skinny;           // fp32 with at most 128 rows: the weight-streaming kernels of the LSTM cell
     size_t n_part_sk;      // their slice sums, floats
     LinearTiles t;         // the tiled products of pf_tile.h
@@ -233,6 +237,23 @@ static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
     return t < (linear_chain2_supported(in, out, r) ? chain : 0.97 * tiled) ? rows : 0;
 }
 
+// Backward, dT and dX in one launch of it and the factor gradients in another (pf_linear_grad.h): rows per workgroup, or 0 for the other
+// kernels, by times fitted to 170 shapes (600 to 17000 rows, 128 to 4096 wide, ranks 8 to 128; 9 and 8 % rms).  Of these the rule takes 77,
+// 1.32 times as fast (geometric mean, the worst 0.92), where X masks dX 1.37.  512 -> 128 -> 2048, us, before / now: 44.5 / 40.3 at 8192
+// rows; 2048 -> 512 with mask 53.9 / 42.1, at 16384 rows 102 / 66; 1536 -> 96 -> 384 52.0 / 31.8.  Few rows stay with the tiled products,
+// which form dX and the gradients side by side (1000 rows, 512 -> 512: 13.5 / 19.2).
+static int two_bwd_rows(i64 M, i64 in, i64 out, i64 r, int &split)
+{
+    if (!linear_two_supported(M, out, in, r) || !plan_linear_grad(M, in, out, r).splits) return 0;
+    const double m = 1e-6 * M, w = (double)(in + out);
+    const double before = 11.56 + m * (1.488 * in + 0.699 * out + 6.26 * r + 0.00717 * w * r) + 2.1e-4 * w;
+    const double now = 12.74 + m * (0.367 * w + 7.75 * r + 0.00246 * w * r) + 8.9e-4 * w + 2.24e-5 * w * r;
+    if (now >= 0.97 * before) return 0;
+    int rows = 0;
+    plan_linear_two(M, out, in, r, 1, rows, split);
+    return rows;
+}
+
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
     LinearPlan p;
@@ -250,6 +271,12 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in, d->out, d->r);
     p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->in, d->out, d->r);
     p.two_fwd = d->dtype == PF_BF16 ? two_fwd_rows(d->M, d->in, d->out, d->r, 1, p.two_split) : 0;
+    p.two_bwd = d->dtype == PF_BF16 ? two_bwd_rows(d->M, d->in, d->out, d->r, p.two_bwd_split) : 0;
+    p.n_lg = 0;
+    if (p.two_bwd) {
+        p.lg = plan_linear_grad(d->M, d->in, d->out, d->r);
+        p.n_lg = (size_t)p.lg.splits * (d->r * (d->in + d->out) + d->out) + 128;
+    }
     p.skinny = d->dtype == PF_F32 && d->M > 0 && d->M <= 4 * SK_MAX_ROWS && d->in >= 4 && d->out >= 4 &&
                d->r >= 4;
     p.n_part_sk = 0;
@@ -307,6 +334,11 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
                            align_up(p.n_colsum * sizeof(float));
         if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
         if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
+    }
+    if (p.two_bwd) { // (not where its partial sums alone would make a call outgrow the library's own scratch)
+        const size_t part = p.n_lg > p.t.n_part_T ? p.n_lg : p.t.n_part_T, bwd = 2 * align_up(p.n_T * 2) + align_up(part * 4);
+        if (bwd > p.bwd_bytes && bwd > PF_STATIC_SCRATCH_BYTES) p.two_bwd = 0;
+        else if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
     }
     return p;
 }
@@ -625,6 +657,46 @@ static int linear_bwd_fused(const pf_linear_desc *d, const LinearPlan &p, const 
     }
     if (st != PF_OK) return st;
     return linear_wgrads_fused(d, p, X, dY, T_saved ? T_saved : T16, dT16, dU, dV, dbias, colsum, accumulate, part, s);
+}
+
+// dT = dY U and dX = dT V^T in one launch, both factor gradients and the bias gradient in another, the sums over their splits.
+static int linear_bwd_two(const pf_linear_desc *d, const LinearPlan &p, const bf16_t *X, const bf16_t *V, const bf16_t *U, const bf16_t *dY,
+                          const bf16_t *T_saved, bf16_t *dX, float *dU, float *dV, float *dbias, int accumulate, Workspace &ws, hipStream_t s,
+                          const LinEpilogue &ep)
+{
+    const int in = (int)d->in, out = (int)d->out, r = (int)d->r;
+    bf16_t *Tws = ws.take<bf16_t>(p.n_T), *dT = ws.take<bf16_t>(p.n_T);
+    float *part = ws.take<float>(p.n_lg > p.t.n_part_T ? p.n_lg : p.t.n_part_T);
+    const bool want_db = d->has_bias && dbias;
+    int st = PF_OK;
+    if (dU && !T_saved) {
+        st = tiles_mid<bf16_t>(s, "linear_T=X*V", p.t.T, 1, (int)d->M, r, in, X, 0, V, Tws, r, 0, part);
+        if (st != PF_OK) return st;
+    }
+    LinTwoArgs two{d->M, out, in, r, (const uint16_t *)dY, (const uint16_t *)U, (const uint16_t *)V, nullptr, (const uint16_t *)ep.add,
+                   (uint16_t *)dX, (uint16_t *)dT, 0, 1, 0, 0, 0, 0, 0, p.two_bwd_split, (const uint16_t *)ep.mask};
+    if (ep.used) *ep.used = true;
+    st = launch_linear_two(s, "linear_bwd_data_two", two, p.two_bwd);
+    if (st != PF_OK) return st;
+    LinGradArgs a{d->M, r, p.lg.splits, p.lg.per, 0, {}};
+    SplitSumArgs ss = {};
+    const auto take = [&](size_t n) { // partial sums start 256-byte aligned
+        float *f = part;
+        part += (n + 63) / 64 * 64;
+        return f;
+    };
+    const auto grad = [&](const bf16_t *A, const bf16_t *B, int cols, float *dst, float *sums) {
+        const i64 n = (i64)cols * r;
+        LinGradProb &q = a.p[a.n++];
+        q = LinGradProb{(const uint16_t *)A, (const uint16_t *)B, cols, take(p.lg.splits * n), sums ? take((size_t)p.lg.splits * cols) : nullptr};
+        split_sum_add(ss, SplitSum{q.out, dst, n, n, p.lg.splits, accumulate, nullptr, 0, 0});
+        if (sums) split_sum_add(ss, SplitSum{q.sums, sums, cols, cols, p.lg.splits, accumulate, nullptr, 0, 0});
+    };
+    // (for the bias gradient alone any matrix of rank r does)
+    if (dU || want_db) grad(dY, !dU ? dT : T_saved ? T_saved : Tws, out, dU, want_db ? dbias : nullptr);
+    if (dV) grad(X, dT, in, dV, nullptr);
+    if (a.n) st = launch_linear_grad(s, a);
+    return st == PF_OK ? launch_split_sums(s, ss) : st;
 }
 
 // --------------------------------------- fp32, few rows, dimensions in whole tiles
@@ -970,6 +1042,9 @@ int pf::linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
         return linear_bwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)dY,
                                          (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                          (float *)dbias, accumulate, ws, s);
+    if (p.two_bwd && dX)
+        return linear_bwd_two(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY, (const bf16_t *)T_saved,
+                              (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias, accumulate, ws, s, ep ? *ep : LinEpilogue{});
     if (p.chain_bwd && dX)
         return linear_bwd_fused(d, p, (const bf16_t *)X, (const bf16_t *)V, (const bf16_t *)U, (const bf16_t *)dY,
                                 (const bf16_t *)T_saved, (bf16_t *)dX, (float *)dU, (float *)dV, (float *)dbias,

@@ -1,5 +1,6 @@
 // The factorized fully connected layer forward in one launch, in bf16, ranks up to 128, any widths that are whole 16-byte pieces:
 //     mid[rows][r] = in[rows][K] W1[K][r],   out[rows][N] = act(mid W2[N][r]^T + bias + add)
+// and backward with in = dY, W1 = U, W2 = V, mid = dT, out = dX.
 // (pf_linear_chain.h has the kernel for rank 128 and widths that are multiples of 256.)
 #pragma once
 
@@ -16,6 +17,7 @@ struct LinTwoArgs {
     int groups;                          // layers side by side that share their input, elements from one to the next:
     i64 s_W1, s_W2, s_bias, s_out, s_mid;
     int osplit; // workgroups that share a row tile's outputs (each forms mid again)
+    const uint16_t *mask; // [M][N], may be NULL (ranks in whole pieces only): outputs are kept where it is positive
 };
 
 bool linear_two_supported(i64 M, i64 K, i64 N, i64 r);

@@ -49,8 +49,20 @@ struct LinPiece {
     }
 };
 
+// bf16 elements of v where those of m are above zero (as integers 1 .. 0x7f80: NaN is not)
+__device__ __forceinline__ uint4 lt_kept(uint4 v, uint4 m)
+{
+    typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+    const auto one = [](uint32_t x, uint32_t k) __attribute__((always_inline)) {
+        const us2 left = __builtin_elementwise_sub_sat(us2{0x7f80, 0x7f80}, (us2)(__builtin_bit_cast(us2, k) - us2{1, 1})); // 0: not kept
+        return x & __builtin_bit_cast(uint32_t, (us2)(us2{0, 0} - __builtin_elementwise_min(left, us2{1, 1})));
+    };
+    return make_uint4(one(v.x, m.x), one(v.y, m.y), one(v.z, m.z), one(v.w, m.w));
+}
+
 // EVEN: ranks in whole pieces.  Everything is then loaded and stored through descriptors without a branch.
-template <int RB, int MB, bool EVEN, bool ADD>
+// ADD, MASK: a residual is added; outputs are kept where `mask` is positive (its pieces are those that a thread stores).
+template <int RB, int MB, bool EVEN, bool ADD, bool MASK>
 __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
 {
     typedef LinTwoCfg<RB, MB> F;
@@ -70,7 +82,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     uint4 vr[F::VCH], xr[2][F::XCH]; // (the factors come from L2, the input from further away)
     const int steps = (K + KC - 1) / KC;
     // A thread's pieces lie in one column of the factor and one of the input.
-    const BufSrc sV(W1, 2LL * K * r), sX(a.in, 2LL * M * K), sU(W2, 2LL * N * r), sB(bias, 2LL * N), sA(a.add, 2LL * M * N), sY(out, 2LL * M * N);
+    const BufSrc sV(W1, 2LL * K * r), sX(a.in, 2LL * M * K), sU(W2, 2LL * N * r), sB(bias, 2LL * N), sA(a.add, 2LL * M * N), sM(a.mask, 2LL * M * N), sY(out, 2LL * M * N);
     const int vrow = tid / (RB * 4), vcol = tid % (RB * 4), xrow = tid / (KC / 8), xcol = tid % (KC / 8) * 8;
     constexpr int VSTEP = NT / (RB * 4), XSTEP = NT / (KC / 8);
     const bool vin = vcol * 8 < r;
@@ -193,7 +205,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     constexpr int NB2 = F::NB2, OP = F::OP;
     const int wo = wave % 4, wr = wave / 4 * NB2; // outputs, first block of rows
     const bool active = MB > 1 || __builtin_amdgcn_readfirstlane(wave) < 4;
-    uint4 ar[F::ACH], add[2][ADD ? MB : 1], bs;
+    uint4 ar[F::ACH], add[2][ADD ? MB : 1], keep[2][MASK ? MB : 1], bs;
     const int parts = c_end - c_begin, orow = tid / 16, ocol = tid % 16 * 8; // (and every 32nd row from there)
     uint16_t *as0 = (uint16_t *)(lt_smem + F::A0), *as1 = (uint16_t *)(lt_smem + F::A0 + F::ABYTES);
     uint16_t *os0 = (uint16_t *)(lt_smem + F::O0), *os1 = (uint16_t *)(lt_smem + F::O0 + F::OBYTES);
@@ -219,6 +231,10 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int u = 0; u < MB; ++u) add[i][u] = sA.load(out_at(i, u));
+    }
+    if constexpr (MASK) {
+#pragma unroll
+        for (int u = 0; u < MB; ++u) keep[0][u] = sM.load(out_at(0, u)), keep[1][u] = make_uint4(0, 0, 0, 0);
     }
     __syncthreads();
     bf16x8_t tf[NB2][2 * RB];
@@ -266,7 +282,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     }
     // 128 outputs' products, beside them the next factor rows on their way to LDS, those after them from memory, and the outputs before
     const auto step2 = [&](int q, const uint16_t *as, uint16_t *anext, uint16_t *os, uint16_t *obefore, const uint16_t *bias_s, uint16_t *bnext,
-                           uint4 (&x)[ADD ? MB : 1]) __attribute__((always_inline)) {
+                           uint4 (&x)[ADD ? MB : 1], uint4 (&m)[MASK ? MB : 1]) __attribute__((always_inline)) {
         __syncthreads();
         uint4 before[MB];
 #pragma unroll
@@ -307,6 +323,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
 #pragma unroll
             for (int u = 0; u < MB; ++u)
                 if (u * 2 * RB / MB == st) {
+                    if constexpr (MASK) before[u] = lt_kept(before[u], m[u]), m[u] = sM.load(out_at(q + 1, u));
                     sY.store(out_at(q - 1, u), before[u]);
                     if constexpr (ADD) {
                         *(uint4 *)&obefore[(orow + 32 * u) * OP + ocol] = x[u];
@@ -333,21 +350,24 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
             }
         }
     };
-    const auto last = [&](int q, const uint16_t *os) __attribute__((always_inline)) {
+    const auto last = [&](int q, const uint16_t *os, const uint4 (&m)[MASK ? MB : 1]) __attribute__((always_inline)) {
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < MB; ++u) sY.store(out_at(q, u), *(const uint4 *)&os[(orow + 32 * u) * OP + ocol]);
+        for (int u = 0; u < MB; ++u) {
+            const uint4 v = *(const uint4 *)&os[(orow + 32 * u) * OP + ocol];
+            sY.store(out_at(q, u), MASK ? lt_kept(v, m[MASK ? u : 0]) : v);
+        }
     };
     int q = 0;
     for (; q < parts - 1; q += 2) {
-        step2(q, as0, as1, os0, os1, bs0, bs1, add[1]);
-        step2(q + 1, as1, as0, os1, os0, bs1, bs0, add[0]);
+        step2(q, as0, as1, os0, os1, bs0, bs1, add[1], keep[1]);
+        step2(q + 1, as1, as0, os1, os0, bs1, bs0, add[0], keep[0]);
     }
     if (parts & 1) {
-        step2(q, as0, as1, os0, os1, bs0, bs1, add[1]);
-        last(q, os0);
+        step2(q, as0, as1, os0, os1, bs0, bs1, add[1], keep[1]);
+        last(q, os0, keep[0]);
     } else {
-        last(q - 1, os1);
+        last(q - 1, os1, keep[1]);
     }
 }
 
@@ -388,15 +408,24 @@ static int lt_launch(hipStream_t s, const char *name, const LinTwoArgs &a)
     typedef LinTwoCfg<RB, MB> F;
     int st = PF_OK;
     const dim3 grid((unsigned)((a.M + F::MR - 1) / F::MR), a.osplit, a.groups);
-    if (a.r % 8 == 0 && a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, true>), grid, dim3(F::NT), s, a);
-    else if (a.r % 8 == 0) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false>), grid, dim3(F::NT), s, a);
-    else if (a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, true>), grid, dim3(F::NT), s, a);
-    else PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, false>), grid, dim3(F::NT), s, a);
+    const bool even = a.r % 8 == 0;
+    if constexpr (MB < 4)
+        if (even && a.add && a.mask) {
+            PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, true, true>), grid, dim3(F::NT), s, a);
+            return st;
+        }
+    if (even && a.mask) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false, true>), grid, dim3(F::NT), s, a);
+    else if (even && a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, true, false>), grid, dim3(F::NT), s, a);
+    else if (even) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false, false>), grid, dim3(F::NT), s, a);
+    else if (a.mask) return PF_ERR_UNSUPPORTED; // (backward takes ranks in whole pieces)
+    else if (a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, true, false>), grid, dim3(F::NT), s, a);
+    else PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, false, false>), grid, dim3(F::NT), s, a);
     return st;
 }
 template <int RB>
 static int lt_rows(hipStream_t s, const char *name, const LinTwoArgs &a, int rows)
 {
+    if (rows == 128 && a.add && a.mask) rows = 64; // (both arrays' pieces beside the sums of 128 rows do not fit the registers)
     return rows == 128 ? lt_launch<RB, 4>(s, name, a) : rows == 64 ? lt_launch<RB, 2>(s, name, a) : rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
 }
 int launch_linear_two(hipStream_t s, const char *name, const LinTwoArgs &a, int rows)

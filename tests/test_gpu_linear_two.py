@@ -1,5 +1,6 @@
-"""GPU parity of the two-stage forward kernel (pf_linear_two.h) with every number of rows per workgroup, against torch in float32: widths
-and ranks beside their tiles, one row, layers that share their input, outputs shared by several workgroups."""
+"""GPU parity of the two-stage kernel (pf_linear_two.h) with every number of rows per workgroup, against torch in float32: widths
+and ranks beside their tiles, one row, layers that share their input, outputs shared by several workgroups, masks; of the factor
+gradients (pf_linear_grad.h) with columns, ranks and runs of rows beside their tiles; and of the backward call on both."""
 import ctypes
 import os
 import subprocess
@@ -21,7 +22,7 @@ def two(tmp_path_factory):
     subprocess.run([hipcc, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-shared", "-I", os.path.join(PACKAGE, "csrc"),
                     os.path.join(ROOT, "tests", "emulation", "linear_two_launch.cpp"), "-o", out, "-L" + PACKAGE, "-lpufferfish",
                     "-Wl,-rpath," + PACKAGE], check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE)
-    return ctypes.CDLL(out).linear_two
+    return ctypes.CDLL(out)
 
 
 @pytest.mark.parametrize("M,K,N,r,G", [(1, 8, 8, 8, 1), (33, 136, 264, 19, 2), (300, 72, 40, 128, 1), (129, 1032, 520, 65, 3), (200, 264, 1048, 100, 1),
@@ -39,8 +40,8 @@ def test_parity(two, M, K, N, r, G):
                 Y, T = (torch.full((G, M, w), float("nan"), dtype=torch.bfloat16, device="cuda") for w in (N, r))
                 args = [X, V, U, bias if ep else None, add if ep and G == 1 else None]
                 p = lambda t: ctypes.c_void_p(None if t is None else t.data_ptr())
-                st = two(ctypes.c_longlong(M), K, N, r, G, rows, osplit, *map(p, args), int(ep), p(Y), p(T),
-                         ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+                st = two.linear_two(ctypes.c_longlong(M), K, N, r, G, rows, osplit, *map(p, args), int(ep), p(Y), p(T), None,
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
                 assert st == 0
                 want = T.float() @ U.float().transpose(1, 2).contiguous()
                 if ep:
@@ -48,3 +49,62 @@ def test_parity(two, M, K, N, r, G):
                 for got, ref in ((T, X.float() @ V.float()), (Y, want)):
                     err = (got.double() - ref.double()).norm() / ref.double().norm().clamp_min(1e-30)
                     assert err <= 4e-3, (rows, osplit, ep, err)
+
+
+@pytest.mark.parametrize("M,K,N,r", [(1, 8, 8, 8), (70, 136, 264, 24), (300, 72, 136, 64), (129, 264, 648, 128)])
+def test_mask(two, M, K, N, r):
+    """An output stays where the mask is above zero: not at zeros of either sign, negative values or NaN."""
+    g = torch.Generator(device="cuda").manual_seed(4)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, V, U, add = n(M, K).bfloat16(), (n(K, r) * K ** -0.5).bfloat16(), (n(N, r) * r ** -0.5).bfloat16(), n(M, N).bfloat16()
+    special = torch.tensor([0.0, -0.0, float("nan"), float("inf"), float("-inf"), 1e-37, -1e-37, 3e38], device="cuda").bfloat16()
+    mask = torch.where(n(M, N) > 0.5, special[torch.arange(M * N, device="cuda") % 8].reshape(M, N), n(M, N).bfloat16())
+    kept = mask.float() > 0
+    p = lambda t: ctypes.c_void_p(None if t is None else t.data_ptr())
+    for rows in (32, 64, 128):
+        for a in (None, add):
+            for osplit in {1, (N + 127) // 128}:
+                Y, T = (torch.full((M, w), float("nan"), dtype=torch.bfloat16, device="cuda") for w in (N, r))
+                assert two.linear_two(ctypes.c_longlong(M), K, N, r, 1, rows, osplit, p(X), p(V), p(U), None, p(a), 0, p(Y), p(T), p(mask),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+                want = T.float() @ U.float().t().contiguous() + (0 if a is None else a.float())
+                assert bool((Y[~kept] == 0).all())
+                assert float((Y[kept].double() - want[kept].double()).norm()) <= 4e-3 * float(want.double().norm())  # one rounding to bf16
+
+
+@pytest.mark.parametrize("M,cols,r", [(64, (8, 8), 8), (65, (136, 120), 40), (1000, (264, 72), 64), (700, (128, 640), 128), (1030, (1032, 8), 24),
+                                      (577, (256, 128), 96)])
+def test_gradients(two, M, cols, r):
+    """Sums over M products that float32 holds exactly: 2^-24 each on the way, in a random direction (twice that is allowed)."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    A, B, chunks = [n(M, c) for c in cols], [n(M, r) for _ in cols], (M + 63) // 64
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    for per in {1, 2, 3, chunks}:
+        splits = (chunks + per - 1) // per
+        out = [torch.full((splits, c, r), float("nan"), device="cuda") for c in cols]
+        sums = torch.full((splits, cols[0]), float("nan"), device="cuda")
+        assert two.linear_grad(ctypes.c_longlong(M), r, splits, per, 2, cols[0], p(A[0]), p(B[0]), p(out[0]), p(sums), cols[1], p(A[1]), p(B[1]), p(out[1]),
+                               ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        for got, ref in [(o.double().sum(0), a.double().t() @ b.double()) for o, a, b in zip(out, A, B)] + [(sums.double().sum(0), A[0].double().sum(0))]:
+            assert float((got - ref).norm() / ref.norm()) <= M ** 0.5 * 2 ** -23, per
+
+
+@pytest.mark.parametrize("shape", [(5000, 384, 640, 96), (6001, 1032, 264, 64), (8192, 512, 512, 128)])
+def test_backward(shape):
+    """The public call where it takes both kernels (more rows than the oracle's tests have): T kept or not, mask and skip gradient."""
+    import paper_2103_03936_amd as pf
+    M, K, N, r = shape
+    g = torch.Generator(device="cuda").manual_seed(6)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, V, U = n(M, K).bfloat16(), (n(K, r) * K ** -0.5).bfloat16(), (n(N, r) * r ** -0.5).bfloat16()
+    dY, add = n(M, N).bfloat16(), n(M, K).bfloat16()
+    T = (X.float() @ V.float()).bfloat16()
+    dT = (dY.float() @ U.float()).bfloat16().float()
+    dX, grads = dT @ V.float().t().contiguous(), (dY.float().t() @ T.float(), X.float().t() @ dT, dY.float().sum(0))
+    for a, relu, kept in ((None, False, True), (add, False, False), (None, True, True), (add, True, True)):
+        want = dX + (0 if a is None else a.float())
+        want = torch.where(X.float() > 0, want, torch.zeros_like(want)) if relu else want
+        got = pf.pf_lowrank_linear_bwd_ep(X, V, U, dY, T_saved=T if kept else None, dX_add=a, x_is_relu=relu, has_bias=True)
+        for x, ref in zip(got, (want,) + grads):  # (a share of 2^-8 per rounding to bf16; dT and T may round either way here)
+            assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
