@@ -166,6 +166,7 @@ struct ConvPlan {
     size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction, 0: not
+    bool plain_chain; // ... but the chain kernel takes the calls without an epilogue
     int px_bwd, px_bwd_threads;
     int px_groups[2], px_per[2]; // ... and the pixel groups of their filter gradients, tiles per group
     size_t px_pack, px_dT, px_part; // ... elements of the re-ordered thin filters and of dT, floats of the partial sums
@@ -316,13 +317,19 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
         return c.launches + m * (c.thin * RB * g.C * kk + c.wide * RB * g.Cout + c.macs * (g.C * kk + g.Cout) * (1 + 0.5 * ragged)) +
                1e-3 * c.terms * g.C * kk + c.ragged * ragged + c.factors * mf + 1e-3 * c.plane * g.H * g.W;
     };
-    // of the chain kernel's shapes one workgroup per image streams both factors
+    // of the chain kernel's shapes one workgroup per image streams both factors; without scale, shift, residual input and ReLU its output
+    // is the cheaper part (over 32 shapes 9 % rms)
     const double chain_fwd = ((g.N + 255) / 256) * (9 + (0.055 * g.C * kk + 0.35 * g.Cout) * RB / 64);
+    const double chain_plain = ((g.N + 255) / 256) * (8.8 + (0.057 * g.C * kk + 0.117 * g.Cout) * RB / 64);
     int P = 0, threads = 0;
     double t;
     if constexpr (f32) t = g.s > 1 ? best(PX_FWD_STRIDED_F32, g.C, g.Cout, P, threads) : best(PX_FWD_F32, g.C, g.Cout, P, threads);
     else t = g.s > 1 ? best(PX_FWD_STRIDED, g.C, g.Cout, P, threads) : best(PX_FWD, g.C, g.Cout, P, threads);
     if (P && (p.chain ? t < 0.95 * chain_fwd : (!f32 && g.r <= 64) || t < (f32 ? 0.9 : 1) * tiled(TILED_FWD[g.s > 1][f32]))) p.px_fwd = P, p.px_fwd_threads = threads;
+    // Such calls stay with the chain kernel where it is the faster one, us, chain / here: 128 images of 256 x 8 x 8, rank 64, 3 x 3 14.3 / 14.2,
+    // and 38.6 / 41.1 with the backward direction, which finds its filters packed in either case; 94 of 512 -> 1024 21.3 / 24.9; one tap, rank
+    // 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5.  (All times with inputs from memory.)
+    p.plain_chain = p.chain && t >= 1.02 * chain_plain;
     // backward: unit stride
     if (g.s > 1 || !px_bwd_takes<T>(g.k, g.r) || (p.chain && p.wgrad) || !px_wgrad_fits(pl)) return;
     P = 0;
@@ -355,8 +362,10 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
     p.wgrad = p.chain && wgrad_supported(g.r, g.C, g.H, g.W, g.k, g.s, g.p) &&
               wgrad_supported(g.r, g.Cout, g.H, g.W, 1, 1, 0);
     p.px_fwd = p.px_bwd = 0;
+    p.plain_chain = false;
     if (dtype == PF_BF16) plan_conv_px<uint16_t>(g, p);
     else plan_conv_px<float>(g, p);
+    if (p.px_bwd) p.plain_chain = false; // (the filters it reads are packed by the forward kernel of its own)
     // (saved by a forward call for the kernels that take the backward direction)
     p.saved_bytes = p.px_bwd ? (p.px_fwd ? align_up(p.px_pack * (dtype == PF_BF16 ? 2 : 4)) : 0) : p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
     p.wg_groups = p.wg_ipg = p.wg_groups2 = p.wg_ipg2 = 1;
@@ -994,7 +1003,8 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     hipStream_t s = (hipStream_t)stream;
     const ConvEpilogue all = {scale, shift, residual, nullptr, act == PF_ACT_RELU ? 1 : 0, nullptr};
     if (!p.saved_bytes) W_save = nullptr;
-    if (p.px_fwd) {
+    const bool plain = !scale && !shift && !residual && !all.relu;
+    if (p.px_fwd && !(plain && p.plain_chain)) {
         *fused = true;
         PackW1 w1 = {};
         PackW2 w2 = {};

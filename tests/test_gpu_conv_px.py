@@ -164,3 +164,26 @@ def test_infinite_input(px):
         want = torch.zeros(H, W, dtype=torch.bool, device="cuda")
         want[3:6, 3:6] = True
         assert (torch.isposinf(Y) == want).all() and torch.isfinite(Y[:, :, ~want]).all(), (P, threads)
+
+
+@pytest.mark.parametrize("shape", [(4, 256, 8, 8, 256, 64, 3), (3, 256, 8, 8, 1024, 128, 1), (28, 512, 8, 8, 256, 128, 1)])
+def test_plain_calls_and_epilogues(shape):
+    """Calls without an epilogue may run on another kernel than those with one: the same output, to two roundings of T and Y (2^-9 of a
+    value at most each, on either side), and the same factors kept for the backward direction."""
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, r, k = shape
+    g = torch.Generator(device="cuda").manual_seed(11)
+    b = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    X, Uk, Vp = b(N, C, H, W), b(r, C, k, k) * (C * k * k) ** -0.5, b(Cout, r) * r ** -0.5
+    Y, T, kept = pf.pf_lowrank_conv_fwd(X, Uk, Vp, pad=k // 2, save_W=True)
+    Ye, Te, kept_e = pf.pf_lowrank_conv_fwd_ep(X, Uk, Vp, residual=torch.zeros_like(Y), pad=k // 2, save_W=True)
+    mid = F.conv2d(X.cpu().float(), Uk.cpu().float(), padding=k // 2)
+    ref = F.conv2d(mid.bfloat16().float(), Vp.cpu().float()[:, :, None, None])
+    for y, t in ((Y, T), (Ye, Te)):
+        _close(t.cpu().float().reshape(mid.shape), mid, 4e-3, "T")
+        _close(y.cpu().float(), ref, 4e-3, "Y")
+    assert (kept is None) == (kept_e is None) and (kept is None or torch.equal(kept, kept_e))
+    dY = b(N, Cout, H, W)
+    one = pf.pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=T, pad=k // 2, W_saved=kept)
+    other = pf.pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=T, pad=k // 2, W_saved=kept_e)
+    assert all(torch.equal(x, y) for x, y in zip(one, other))
