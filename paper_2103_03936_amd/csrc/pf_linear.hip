@@ -166,6 +166,7 @@ struct LinearPlan {
     int wg_groups, wg_ipg; // row-tile groups of the factor-gradient kernel and tiles per group
     int wg_cols;           // columns per workgroup of that kernel
     int two_fwd, two_split; // rows per workgroup and shares of the outputs where both stages forward are one launch of pf_linear_two.h, 0: not
+    bool plain_chain;       // ... but the chain kernel takes the calls without residual input and ReLU
     int two_bwd, two_bwd_split; // the same for dT and dX; the factor gradients are then those of pf_linear_grad.h
     LinGradPlan lg;
     size_t n_lg; // their partial sums, floats
@@ -237,6 +238,17 @@ static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
     return t < (linear_chain2_supported(in, out, r) ? chain : 0.97 * tiled) ? rows : 0;
 }
 
+// The times above are of calls with a residual input.  Without one and without a ReLU the chain kernel is the faster one for inputs up to 512
+// wide while it has one workgroup per compute unit (us, chain / two-stage, inputs from memory: 8192 x 512 -> 512 9.3 / 10.8, 8192 x 512 ->
+// 256 7.4 / 8.6, 6000 x 256 -> 256 6.6 / 7.7, but 4096 x 256 -> 1024 10.4 / 8.8, 9000 x 512 -> 512 15.3 / 11.9).  Its times over 22 shapes, 2 % rms;
+// the two-stage kernel's are 0.7 above the plan's there.
+static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r)
+{
+    int rows, split;
+    return M <= 8192 && in <= 512 && (out == 256 || out == 512 || out == 1024) &&
+           5.04 + 4.15e-3 * out - 2.4e-4 * in + 2.37e-7 * M * (in + out) < plan_linear_two(M, in, out, r, 1, rows, split) + 0.7;
+}
+
 // Backward, dT and dX in one launch of it and the factor gradients in another (pf_linear_grad.h): rows per workgroup, or 0 for the other
 // kernels, by times fitted to 170 shapes (600 to 17000 rows, 128 to 4096 wide, ranks 8 to 128; 9 and 8 % rms).  Of these the rule takes 77,
 // 1.32 times as fast (geometric mean, the worst 0.92), where X masks dX 1.37.  512 -> 128 -> 2048, us, before / now: 44.5 / 40.3 at 8192
@@ -271,6 +283,7 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.chain_fwd = p.fused && chain_fwd_pays(d->M, d->in, d->out, d->r);
     p.chain_bwd = p.fused && d->M > 0 && chain_bwd_pays(d->M, d->in, d->out, d->r);
     p.two_fwd = d->dtype == PF_BF16 ? two_fwd_rows(d->M, d->in, d->out, d->r, 1, p.two_split) : 0;
+    p.plain_chain = p.chain_fwd && plain_chain_pays(d->M, d->in, d->out, d->r);
     p.two_bwd = d->dtype == PF_BF16 ? two_bwd_rows(d->M, d->in, d->out, d->r, p.two_bwd_split) : 0;
     p.n_lg = 0;
     if (p.two_bwd) {
@@ -992,7 +1005,8 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (d->dtype == PF_F32)
         return linear_fwd_generic<float>(d, (const float *)X, (const float *)V, (const float *)U, (const float *)bias,
                                          (float *)Y, (float *)T_save, ws, s);
-    if (p.two_fwd) {
+    const bool plain = !ep || (!ep->add && !ep->relu);
+    if (p.two_fwd && !(plain && p.plain_chain)) {
         if (ep && ep->used) *ep->used = true;
         return launch_linear_two(s, "linear_fwd_two",
                                  LinTwoArgs{d->M, (int)d->in, (int)d->out, (int)d->r, (const uint16_t *)X, (const uint16_t *)V, (const uint16_t *)U,

@@ -108,3 +108,15 @@ def test_backward(shape):
         got = pf.pf_lowrank_linear_bwd_ep(X, V, U, dY, T_saved=T if kept else None, dX_add=a, x_is_relu=relu, has_bias=True)
         for x, ref in zip(got, (want,) + grads):  # (a share of 2^-8 per rounding to bf16; dT and T may round either way here)
             assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
+
+
+@pytest.mark.parametrize("M,K,N", [(8192, 512, 512), (6001, 256, 256), (8193, 512, 256)])
+def test_plain_calls_and_epilogues(M, K, N):
+    """Calls without residual input and ReLU may run on another kernel than those with them.  Bounds as above."""
+    import paper_2103_03936_amd as pf
+    g = torch.Generator(device="cuda").manual_seed(6)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, V, U, bias = n(M, K).bfloat16(), (n(K, 128) * K ** -0.5).bfloat16(), (n(N, 128) * 128 ** -0.5).bfloat16(), n(N).bfloat16()
+    for Y, T in (pf.pf_lowrank_linear_fwd(X, V, U, bias), pf.pf_lowrank_linear_fwd_ep(X, V, U, bias, residual=X.new_zeros(M, N))):
+        for got, ref in ((T, X.float() @ V.float()), (Y, T.float() @ U.float().t() + bias.float())):
+            assert (got.double() - ref.double()).norm() <= 4e-3 * ref.double().norm()
