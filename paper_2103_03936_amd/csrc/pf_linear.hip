@@ -242,11 +242,13 @@ static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
 // wide while it has one workgroup per compute unit (us, chain / two-stage, inputs from memory: 8192 x 512 -> 512 9.3 / 10.8, 8192 x 512 ->
 // 256 7.4 / 8.6, 6000 x 256 -> 256 6.6 / 7.7, but 4096 x 256 -> 1024 10.4 / 8.8, 9000 x 512 -> 512 15.3 / 11.9).  Its times over 22 shapes, 2 % rms;
 // the two-stage kernel's are 0.7 above the plan's there.
-static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r)
+// G layers that share their input are G times the rows to it: three of 512 -> 512 at 1400 rows 8.3 / 10.0, of 256 -> 256 6.8 / 7.6, but at 2730
+// rows (258 workgroups) 14.7 / 11.9.
+static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r, int G = 1)
 {
     int rows, split;
-    return M <= 8192 && in <= 512 && (out == 256 || out == 512 || out == 1024) &&
-           5.04 + 4.15e-3 * out - 2.4e-4 * in + 2.37e-7 * M * (in + out) < plan_linear_two(M, in, out, r, 1, rows, split) + 0.7;
+    return (M + 31) / 32 * G <= 256 && in <= 512 && (out == 256 || out == 512 || out == 1024) &&
+           5.04 + 4.15e-3 * out - 2.4e-4 * in + 2.37e-7 * G * M * (in + out) < plan_linear_two(M, in, out, r, G, rows, split) + 0.7;
 }
 
 // Backward, dT and dX in one launch of it and the factor gradients in another (pf_linear_grad.h): rows per workgroup, or 0 for the other
@@ -928,6 +930,7 @@ static SharedPlan make_shared_plan(const pf_linear_shared_desc *d, const pf_line
     sp.fused_fwd = d->dtype == PF_BF16 && sp.p.chain2 && d->M > 0 && G > 1 && G <= LC_MAX_GROUPS &&
                    (chain_shared_fwd_pays(d->M, d->n_in) || rows_fwd_pays(d->M, d->n_in, d->n_out, d->r, G));
     sp.two_fwd = d->dtype == PF_BF16 ? two_fwd_rows(d->M, d->n_in, d->n_out, d->r, G, sp.two_split) : 0;
+    if (sp.two_fwd && sp.fused_fwd && plain_chain_pays(d->M, d->n_in, d->n_out, d->r, G)) sp.two_fwd = 0;
     if (sp.two_fwd) sp.fused_fwd = false;
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     sp.fwd_bytes = sp.p.fwd_bytes;
