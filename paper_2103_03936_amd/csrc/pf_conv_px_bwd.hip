@@ -83,9 +83,9 @@ __global__ __launch_bounds__(NT, 2) void conv_px_bwd_kernel(PxBwdArgs<T> a)
     blk.load(a.dZ, g, a.Cout, 0, zr);
     const int w1 = wave % F::WPX, r1 = wave / F::WPX; // pixel blocks and rank blocks of the first stage (r1 >= WRB: none)
     const int npx = t.pb - t.pa;
-    int slot1[F::NB1];
+    int slot1[F::NB1]; // (the spare row's sums are stored there too, and nobody reads them)
 #pragma unroll
-    for (int j = 0; j < F::NB1; ++j) slot1[j] = px_slot(g, min(t.pa + (w1 + j * F::WPX) * 32 + (lane & 31), t.pb - 1)) - t.base;
+    for (int j = 0; j < F::NB1; ++j) slot1[j] = px_row(g, t, min(t.pa + (w1 + j * F::WPX) * 32 + (lane & 31), t.pb - 1), R::rows - 1);
     PxSum<T, F::NB1> sum1[F::MB1];
 #pragma unroll
     for (int i = 0; i < F::MB1; ++i) sum1[i].clear();

@@ -97,6 +97,15 @@ PX_HD PxTile px_tile(const PxPlane<S> &g, const PxPlane<S> &o, int st, int p0, i
 template <int S>
 PX_HD PxTile px_tile(const PxPlane<S> &g, int p0, int P) { return px_tile(g, g, 1, p0, P); }
 
+// Row of a panel that holds pixel p of the tile's range: its slot, or the `spare` row for pixels of the first and last halo row that no tap
+// reaches (a range starts h (W + 1) pixels before the tile: one more than the slots where the tile starts a row).
+template <int S>
+PX_HD int px_row(const PxPlane<S> &g, const PxTile &t, int p, int spare)
+{
+    const int s = px_slot(g, p) - t.base;
+    return s >= 0 && s < t.slots ? s : spare;
+}
+
 // Group gi of the tile's pixels: neighbours in the plane of image n from q on (whole 16-byte pieces where a plane is a
 // multiple of them).  The last group of a plane is pulled back inside it.  False: past the end.
 template <int S>

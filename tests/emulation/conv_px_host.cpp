@@ -41,6 +41,12 @@ static int tiles(int N, int H, int W, int k, int st, int P, int rows, int groups
                     const int want = y < 0 || y >= H || x < 0 || x >= W ? -1 : n1 * g.HW + y * W + x;
                     if (holds[s] != want) return 8;
                 }
+        // the rows that the backward kernel gives the tile's range: inside the panel, the pixel's slot wherever a tap reads it
+        for (int p = t.pa; st == 1 && p < t.pb; ++p) {
+            const int row = px_row(g, t, p, rows - 1), s = px_slot(g, p) - t.base;
+            if (row < 0 || row >= rows || (row != s && (s >= 0 && s < t.slots))) return 14;
+            if (row == s && holds[s] != p) return 15;
+        }
         // the same pixels in rows of V per group
         for (int p = t.pa; st == 1 && p < t.pb; ++p) {
             const int im = p / g.HW, row = px_linear(g, t, im, p % g.HW);
