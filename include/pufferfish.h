@@ -178,8 +178,8 @@ typedef struct {
 size_t pf_lowrank_conv_fwd_workspace_bytes(const pf_conv_desc *d);
 size_t pf_lowrank_conv_bwd_workspace_bytes(const pf_conv_desc *d);
 
-/* Bytes of the optional W_save buffer: both factors re-ordered the way the
- * backward pass's kernels read them (0 when that pass reads them in place). */
+/* Bytes of the optional W_save buffer, in either dtype: the factors that the
+ * backward pass's kernels read re-ordered (0 when they read them in place). */
 size_t pf_lowrank_conv_saved_weights_bytes(const pf_conv_desc *d);
 
 /* T = Uk * X (k x k, stride, pad), Y = Vp * T (1x1).  T_save nullable.

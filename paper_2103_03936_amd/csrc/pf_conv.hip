@@ -905,7 +905,7 @@ size_t pf_lowrank_conv_saved_weights_bytes(const pf_conv_desc *d)
 {
     ConvGeom g;
     if (check_conv_desc(d, &g) != PF_OK) return 0;
-    return d->dtype == PF_BF16 ? plan_conv(g, d->dtype).saved_bytes : 0;
+    return plan_conv(g, d->dtype).saved_bytes; // (what the forward call writes, in either type)
 }
 
 int pf_lowrank_conv_fwd(const pf_conv_desc *d, const void *X, const void *Uk, const void *Vp, void *Y, void *T_save,

@@ -122,7 +122,7 @@ def test_conv_validation():
     b = pf.lib.pf_lowrank_conv_bwd
     assert b(ctypes.byref(_conv()), FAKE, FAKE, FAKE, None, None, None, FAKE, FAKE, FAKE, 0, None, z, None) == 1
     assert b(ctypes.byref(_conv()), FAKE, FAKE, FAKE, FAKE, None, None, FAKE, FAKE, FAKE, 0, None, z, None) == 4
-    # the saved-weights buffer exists for the fused bf16 path only
+    # the saved-weights buffer exists where the backward kernels read re-ordered factors only
     assert pf.lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(_conv())) == 0
     fused = _conv(N=4, C=256, H=8, W=8, Cout=256, r=64, dtype=1)
     assert pf.lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(fused)) == 2 * (256 * 64 + 9 * 256 * 64)

@@ -166,6 +166,30 @@ def test_infinite_input(px):
         assert (torch.isposinf(Y) == want).all() and torch.isfinite(Y[:, :, ~want]).all(), (P, threads)
 
 
+@pytest.mark.parametrize("dtype, shape", [(torch.float32, (226, 64, 14, 14, 64, 16, 1)), (torch.float32, (12, 96, 14, 14, 96, 24, 1)),
+                                          (torch.float32, (2, 44, 5, 5, 36, 7, 3)), (torch.bfloat16, (12, 128, 16, 16, 128, 32, 3))])
+def test_saved_filters_stay_in_their_buffer(dtype, shape):
+    """A forward call writes as many bytes of W_save as the query states and none beyond, and the backward call gives the same with and
+    without them."""
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, r, k = shape
+    g = torch.Generator(device="cuda").manual_seed(12)
+    b = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    X, Uk, Vp, dY = b(N, C, H, W), b(r, C, k, k) * (C * k * k) ** -0.5, b(Cout, r) * r ** -0.5, b(N, Cout, H, W)
+    d = pf.pf_conv_desc(N, C, H, W, Cout, r, k, 1, k // 2, pf.PF_NCHW, pf.PF_F32 if dtype == torch.float32 else pf.PF_BF16, pf.PF_F32)
+    size, guard = pf.lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(d)), 1 << 20
+    kept = torch.full((size + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(pf.lib.pf_lowrank_conv_fwd_workspace_bytes(ctypes.byref(d)), dtype=torch.uint8, device="cuda")
+    Y, T = torch.empty_like(dY), torch.empty(N, r, H, W, dtype=dtype, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert pf.lib.pf_lowrank_conv_fwd(ctypes.byref(d), p(X), p(Uk), p(Vp), p(Y), p(T), p(kept), p(ws), ctypes.c_size_t(ws.numel()),
+                                      ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    assert bool((kept[size:] == 0xA5).all()) and (size == 0) == (k == 3 and dtype == torch.float32)
+    one = pf.pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=T, pad=k // 2)
+    other = pf.pf_lowrank_conv_bwd(X, Uk, Vp, dY, T_saved=T, pad=k // 2, W_saved=kept[:size] if size else None)
+    assert all(torch.equal(x, y) for x, y in zip(one, other))
+
+
 @pytest.mark.parametrize("shape", [(4, 256, 8, 8, 256, 64, 3), (3, 256, 8, 8, 1024, 128, 1), (28, 512, 8, 8, 256, 128, 1)])
 def test_plain_calls_and_epilogues(shape):
     """Calls without an epilogue may run on another kernel than those with one: the same output, to two roundings of T and Y (2^-9 of a
