@@ -83,16 +83,16 @@ __global__ __launch_bounds__(NT, 2) void conv_px_bwd_kernel(PxBwdArgs<T> a)
     blk.load(a.dZ, g, a.Cout, 0, zr);
     const int w1 = wave % F::WPX, r1 = wave / F::WPX; // pixel blocks and rank blocks of the first stage (r1 >= WRB: none)
     const int npx = t.pb - t.pa;
-    int slot1[F::NB1]; // (the spare row's sums are stored there too, and nobody reads them)
+    int slot1[F::NB1];
 #pragma unroll
-    for (int j = 0; j < F::NB1; ++j) slot1[j] = px_row(g, t, min(t.pa + (w1 + j * F::WPX) * 32 + (lane & 31), t.pb - 1), R::rows - 1);
+    for (int j = 0; j < F::NB1; ++j) slot1[j] = px_slot(g, min(t.pa + (w1 + j * F::WPX) * 32 + (lane & 31), t.pb - 1)) - t.base;
     PxSum<T, F::NB1> sum1[F::MB1];
 #pragma unroll
     for (int i = 0; i < F::MB1; ++i) sum1[i].clear();
     for (int c0 = 0; c0 < a.Cout; c0 += R::CH) {
         if (c0) __syncthreads();
         blk.store(zs, zr);
-        if (c0 + R::CH < a.Cout) blk.load(a.dZ, g, a.Cout, c0 + R::CH, zr);
+        blk.load(a.dZ, g, a.Cout, c0 + R::CH, zr); // (zeros past the last channel)
 #pragma unroll
         for (int part = 0; part < F::VPARTS; ++part) {
             const int o0 = c0 + part * F::VROWS;

@@ -66,7 +66,7 @@ PX_HD int px_slot(const PxPlane<S> &g, int p)
 
 struct PxTile {
     int p0, p1;      // pixels of the tile
-    int pa, pb;      // pixels with the halo
+    int pa, pb;      // pixels with the halo: from the first to the last that a tap reaches, all of which have slots
     int base, slots; // first slot, slots
 };
 
@@ -89,22 +89,14 @@ PX_HD PxTile px_tile(const PxPlane<S> &g, const PxPlane<S> &o, int st, int p0, i
     const int n1 = px_div(t.p1 - 1, o.HW, o.mHW), q1 = t.p1 - 1 - n1 * o.HW, y1 = px_div(q1, o.W, o.mW), x1 = q1 - y1 * o.W;
     t.base = (n0 * g.Hp + y0 * st + g.h) * g.Wp + x0 * st + g.h - reach;
     t.slots = (n1 * g.Hp + y1 * st + g.h) * g.Wp + x1 * st + g.h + reach - t.base + 1;
-    const int a = y0 * st * g.W + x0 * st - back, b = y1 * st * g.W + x1 * st + 1 + back;
+    // (left and right of a row lie zero slots, not the rows beside it)
+    const int a = y0 * st * g.W + x0 * st - back + (x0 == 0 ? g.h : 0), b = y1 * st * g.W + x1 * st + 1 + back - (x1 * st + 1 == g.W ? g.h : 0);
     t.pa = n0 * g.HW + (a > 0 ? a : 0);
     t.pb = n1 * g.HW + (b < g.HW ? b : g.HW);
     return t;
 }
 template <int S>
 PX_HD PxTile px_tile(const PxPlane<S> &g, int p0, int P) { return px_tile(g, g, 1, p0, P); }
-
-// Row of a panel that holds pixel p of the tile's range: its slot, or the `spare` row for pixels of the first and last halo row that no tap
-// reaches (a range starts h (W + 1) pixels before the tile: one more than the slots where the tile starts a row).
-template <int S>
-PX_HD int px_row(const PxPlane<S> &g, const PxTile &t, int p, int spare)
-{
-    const int s = px_slot(g, p) - t.base;
-    return s >= 0 && s < t.slots ? s : spare;
-}
 
 // Group gi of the tile's pixels: neighbours in the plane of image n from q on (whole 16-byte pieces where a plane is a
 // multiple of them).  The last group of a plane is pulled back inside it.  False: past the end.

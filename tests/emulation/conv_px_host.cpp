@@ -41,11 +41,11 @@ static int tiles(int N, int H, int W, int k, int st, int P, int rows, int groups
                     const int want = y < 0 || y >= H || x < 0 || x >= W ? -1 : n1 * g.HW + y * W + x;
                     if (holds[s] != want) return 8;
                 }
-        // the rows that the backward kernel gives the tile's range: inside the panel, the pixel's slot wherever a tap reads it
-        for (int p = t.pa; st == 1 && p < t.pb; ++p) {
-            const int row = px_row(g, t, p, rows - 1), s = px_slot(g, p) - t.base;
-            if (row < 0 || row >= rows || (row != s && (s >= 0 && s < t.slots))) return 14;
-            if (row == s && holds[s] != p) return 15;
+        // every pixel of the range has a slot of the tile, which holds it (the backward kernel computes and stores them all)
+        for (int p = t.pa; p < t.pb; ++p) {
+            const int s = px_slot(g, p) - t.base;
+            if (st == 1 && (s < 0 || s >= t.slots)) return 14;
+            if (s >= 0 && s < t.slots && holds[s] != p) return 15;
         }
         // the same pixels in rows of V per group
         for (int p = t.pa; st == 1 && p < t.pb; ++p) {
