@@ -31,7 +31,7 @@ struct PxWgCfg {
     static constexpr int OPITCH = SC * KK + 4, ROUNDS = 1, OROWS = 32 * RB / ROUNDS, OBYTES = KS * OROWS * OPITCH * 4;
     static constexpr int BYTES = 2 * BUF > OBYTES ? 2 * BUF : OBYTES;
     static __host__ __device__ constexpr int tap0(int tg) { return TG == 4 ? (tg ? 2 * tg + 1 : 0) : 5 * tg; } // first tap of a group (3, 2, 2, 2 or 5, 4)
-    static_assert(BYTES <= 160 * 1024 && KS * TG * CW * MW == 8 && (KK == 9 || KS <= 4) && SC / V * 32 == (KK == 9 ? SC / V * 32 : NT), "");
+    static_assert(BYTES + 16 <= 160 * 1024 && KS * TG * CW * MW == 8 && (KK == 9 || KS <= 4) && SC / V * 32 == (KK == 9 ? SC / V * 32 : NT), "");
 };
 
 // Float, one tap: products of one tile, 32 ranks x 32 channels over a wavefront's share of the pixels, in runs of 32 pixels with sums of their
@@ -58,6 +58,40 @@ __device__ __forceinline__ void px_wgrad_f32(const unsigned char *as, const unsi
             }
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] += sum[v];
+    }
+}
+
+// Nine taps, channels whose X is infinite or NaN in a pixel at the edge of its plane: there a tap that reaches out of the plane multiplied
+// it by the row of zeros, which is NaN for a term that does not exist.  Their gradients again, the terms that exist and no others, in runs of
+// 128 pixels with sums of their own.  Such a value leaves none of its channel's sums finite, so the check costs a comparison of what is
+// stored (nothing to be seen in 40 us of both gradients); what it starts takes milliseconds at worst and is for values that no healthy step has.
+template <typename T, int SC>
+__device__ __forceinline__ void px_wgrad_edges(const PxWgradArgs<T> &a, const PxGrad<T> &p, int c0, int begin, int end, float *part, uint32_t *flag)
+{
+    const PxPlaneOf<T> &g = a.gk;
+    const int n = min(SC, p.C - c0), tid = threadIdx.x, NT = blockDim.x;
+    for (int c = tid; c < n; c += NT) flag[c] = 0;
+    __syncthreads();
+    for (int i = tid; i < (end - begin) * n; i += NT) {
+        const int c = i / (end - begin), px = begin + i - c * (end - begin), im = px_div(px, g.HW, g.mHW), q = px - im * g.HW, y = px_div(q, g.W, g.mW), x = q - y * g.W;
+        const bool edge = y == 0 || y == g.H - 1 || x == 0 || x == g.W - 1;
+        if (edge && !isfinite(px_float(p.B[(im * p.C + c0 + c) * g.HW + q]))) flag[c] = 1;
+    }
+    __syncthreads();
+    for (int i = tid; i < a.r * n * 9; i += NT) {
+        const int rank = i / (n * 9), j = i - rank * n * 9, c = j / 9, tap = j - c * 9, dy = 1 - tap / 3, dx = 1 - tap % 3;
+        if (!flag[c]) continue;
+        float all = 0.f;
+        for (int run = begin; run < end; run += 128) {
+            float sum = 0.f;
+            for (int px = run; px < min(run + 128, end); ++px) {
+                const int im = px_div(px, g.HW, g.mHW), q = px - im * g.HW, y = px_div(q, g.W, g.mW), x = q - y * g.W;
+                if (y + dy >= 0 && y + dy < g.H && x + dx >= 0 && x + dx < g.W)
+                    sum += px_float(p.A[(im * p.a_ch + rank) * g.HW + q + dy * g.W + dx]) * px_float(p.B[(im * p.C + c0 + c) * g.HW + q]);
+            }
+            all += sum;
+        }
+        part[rank * p.C * 9 + (c0 + c) * 9 + tap] = all;
     }
 }
 
@@ -162,6 +196,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
         for (int e = 0; e < 4; ++e) r[e] = lo[e], r[4 + e] = up[e];
         return r;
     };
+    if (KK == 9 && tid == 0) *(uint32_t *)(smem + F::BYTES) = 0; // (read at the very end)
     if (t0 < t1) {
         fetch(t0);
         if (KK == 9) {
@@ -235,6 +270,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
     float *os = (float *)smem;
     float *part = p.part + (i64)group * a.r * p.C * KK;
     const int cols = min(F::SC, p.C - c0) * KK;
+    float odd = 0.f; // (NaN once something is not finite)
 #pragma unroll
     for (int r0 = 0; r0 < 32 * RB; r0 += F::OROWS) {
         __syncthreads();
@@ -261,8 +297,15 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
 #pragma unroll
                 for (int w = 1; w < F::KS; ++w) v += *(const f32x4_t *)&os[(w * F::OROWS + row) * F::OPITCH + col];
                 *(f32x4_t *)&part[rank * p.C * KK + c0 * KK + col] = v;
+                if (KK == 9) odd = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, fmaf(v[3], 0.f, odd))));
             }
         }
+    }
+    if constexpr (KK == 9) {
+        uint32_t *flag = (uint32_t *)(smem + F::BYTES);
+        if (odd != 0.f) *flag = 1;
+        __syncthreads();
+        if (*flag) px_wgrad_edges<T, F::SC>(a, p, c0, t0 * F::P, min(t1 * F::P, g1.N * g1.HW), part, (uint32_t *)smem);
     }
     if (KK == 1 && p.sums) {
 #pragma unroll
@@ -280,7 +323,7 @@ template <typename T, int K1, int RB>
 __global__ __launch_bounds__(512, 2) void conv_px_wgrad_kernel(PxWgradArgs<T> a)
 {
     constexpr int b1 = PxWgCfg<T, K1, RB>::BYTES, b2 = PxWgCfg<T, 1, RB>::BYTES;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[b1 > b2 ? b1 : b2];
+    __shared__ __attribute__((aligned(16))) unsigned char smem[(b1 > b2 ? b1 : b2) + 16];
     const int first = a.p[0].units * a.p[0].groups, b = blockIdx.x;
     if (K1 == 9 && a.p[0].kk == 9 && b < first)
         px_wgrad<T, K1, RB>(a, a.p[0], b, smem);

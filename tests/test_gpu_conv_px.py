@@ -166,6 +166,35 @@ def test_infinite_input(px):
         assert (torch.isposinf(Y) == want).all() and torch.isfinite(Y[:, :, ~want]).all(), (P, threads)
 
 
+@pytest.mark.parametrize("shape", [(3, 72, 12, 12, 24, 20, 3), (5, 64, 5, 7, 16, 33, 3), (4, 40, 16, 16, 8, 128, 3), (2, 136, 9, 11, 8, 64, 3)])
+def test_infinite_edges_in_gradients(px, shape):
+    """An infinite (or NaN) pixel at the edge of its plane is in the gradients of the taps that see it and in no others, as a sum over the
+    terms that exist has it; what is finite is within float rounding of it (M terms of 2^-24 in a random direction, twice that is allowed)."""
+    N, C, H, W, Cout, r, k = shape
+    g = torch.Generator(device="cuda").manual_seed(13)
+    b = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    dT, mid, dZ, rv, tiles = torch.zeros(N, (r + 7) // 8 * 8, H, W, device="cuda").bfloat16(), b(N, r, H, W), b(N, Cout, H, W), (r + 7) // 8 * 8, (N * H * W + 127) // 128
+    dT[:, :r] = b(N, r, H, W).abs() + 0.1
+    for places in ([(0, 5, 0, 0, "inf")], [(N - 1, C - 1, H - 1, 2, "-inf"), (1, 7, 3, W - 1, "inf")], [(0, 3, 2, 0, "nan"), (1, 4, 2, 2, "inf")]):
+        X = b(N, C, H, W)
+        for n, c, y, x, v in places:
+            X[n, c, y, x] = float(v)
+        want = torch.empty(r, C, 3, 3, dtype=torch.float64)
+        A, B = dT[:, :r].cpu().double(), X.cpu().double()
+        for i in range(3):
+            for j in range(3):
+                ys, xs, yo, xo = slice(max(0, i - 1), H + min(0, i - 1)), slice(max(0, j - 1), W + min(0, j - 1)), slice(max(0, 1 - i), H + min(0, 1 - i)), slice(max(0, 1 - j), W + min(0, 1 - j))
+                want[:, :, i, j] = (A[:, :, None, yo, xo] * B[:, None, :, ys, xs]).sum((0, 3, 4))
+        for per in {1, 3, tiles}:
+            groups = (tiles + per - 1) // per
+            pU, pV, ps = (torch.full((groups, m), float("nan"), device="cuda") for m in (r * C * 9, r * Cout, Cout))
+            assert _call(px.px_wgrad_bf16, N, C, H, W, Cout, r, k, per, dT, X, mid, dZ, pU, pV, ps) == 0
+            got, ok = pU.cpu().double().sum(0).view(r, C, 3, 3), torch.isfinite(want)
+            assert (torch.isfinite(got) == ok).all() and (torch.isposinf(got) == torch.isposinf(want)).all() and (torch.isnan(got) == torch.isnan(want)).all(), (places, per)
+            assert float((got - want)[ok].norm() / want[ok].norm()) <= (N * H * W) ** 0.5 * 2 ** -23
+            assert torch.isfinite(pV).all()
+
+
 @pytest.mark.parametrize("dtype, shape", [(torch.float32, (226, 64, 14, 14, 64, 16, 1)), (torch.float32, (12, 96, 14, 14, 96, 24, 1)),
                                           (torch.float32, (2, 44, 5, 5, 36, 7, 3)), (torch.bfloat16, (12, 128, 16, 16, 128, 32, 3))])
 def test_saved_filters_stay_in_their_buffer(dtype, shape):
