@@ -154,8 +154,8 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
 
 bool linear_grad_supported(i64 M, i64 in, i64 out, i64 r)
 {
-    const i64 lim = 1LL << 30;
-    return M >= 64 && in >= 8 && out >= 8 && in % 8 == 0 && out % 8 == 0 && r >= 8 && r <= 128 && r % 8 == 0 && M * in < lim && M * out < lim;
+    const i64 lim = 1LL << 30; // (descriptors of less than 2^31 bytes: of both matrices)
+    return M >= 64 && in >= 8 && out >= 8 && in % 8 == 0 && out % 8 == 0 && r >= 8 && r <= 128 && r % 8 == 0 && M * in < lim && M * out < lim && M * r < lim;
 }
 
 // One workgroup to a compute unit, in one round, of at least two chunks.
