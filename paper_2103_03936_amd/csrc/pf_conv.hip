@@ -970,17 +970,23 @@ int pf_dense_conv_bwd(const pf_conv_desc *d, const void *X, const void *Wd, cons
 
 } // extern "C"
 
-// What the backward call for this descriptor does by itself: fold a batch-norm scale into the filters and the sum of
-// their gradients, and form the shift gradient (chain kernels and tiled products).  Otherwise the
-// caller scales beforehand and sums afterwards.
-void pf::conv_bwd_takes(const pf_conv_desc *d, bool want_dX, bool *scale, bool *dshift)
+// The pixel-major kernels form all gradients from a T that was kept.
+static bool bwd_on_px(const pf::ConvPlan &p, const void *T_saved, const void *dX, const void *dUk, const void *dVp)
+{
+    return p.px_bwd && dX && dUk && dVp && T_saved;
+}
+
+// What the backward call with these arguments does by itself: fold a batch-norm scale into the filters and the sum of
+// their gradients, and form the shift gradient (pixel-major kernels, chain kernels with their filter gradients, tiled products).
+// Otherwise the caller scales beforehand and sums afterwards.
+void pf::conv_bwd_takes(const pf_conv_desc *d, const void *T_saved, const void *dX, const void *dUk, const void *dVp, bool *scale, bool *dshift)
 {
     *scale = *dshift = false;
     ConvGeom g;
     if (check_conv_desc(d, &g) != PF_OK || g.N == 0) return;
-    const ConvPlan p = plan_conv(g, d->dtype);
-    const bool chain = d->dtype == PF_BF16 && p.chain && want_dX;
-    *scale = *dshift = chain ? p.wgrad : p.tiles;
+    const ConvPlan &p = plan_conv(g, d->dtype);
+    const bool chain = d->dtype == PF_BF16 && p.chain && dX;
+    *scale = *dshift = bwd_on_px(p, T_saved, dX, dUk, dVp) || (chain ? p.wgrad : p.tiles);
 }
 
 // ------------------------------------------------ entry points with an epilogue
@@ -1068,7 +1074,7 @@ int pf::conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
         return st;
     }
     if (!p.saved_bytes) W_saved = nullptr;
-    if (p.px_bwd && dX && dUk && dVp && T_saved) {
+    if (bwd_on_px(p, T_saved, dX, dUk, dVp)) {
         *fused = true;
         const auto go = [&](auto el) {
             typedef decltype(el) T;

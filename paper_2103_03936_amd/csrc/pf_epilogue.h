@@ -27,6 +27,6 @@ int conv_bwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, cons
                       const void *dZ, const void *T_saved, const void *W_saved, const void *dX_add, int x_is_relu,
                       void *dX, void *dUk, void *dVp, int accumulate, void *workspace, size_t workspace_bytes,
                       void *stream, bool *fused, float *dshift = nullptr);
-void conv_bwd_takes(const pf_conv_desc *d, bool want_dX, bool *scale, bool *dshift);
+void conv_bwd_takes(const pf_conv_desc *d, const void *T_saved, const void *dX, const void *dUk, const void *dVp, bool *scale, bool *dshift);
 
 } // namespace pf

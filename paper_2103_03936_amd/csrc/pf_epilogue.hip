@@ -258,7 +258,7 @@ int pf_lowrank_conv_bwd_ep(const pf_conv_desc *d, const void *X, const void *Uk,
     // the fast paths fold the scale into their own filters and gradient sums; the element-wise one runs on
     // a scaled copy of the 1x1 filters and finishes dVp afterwards
     bool takes_scale, takes_dshift;
-    conv_bwd_takes(d, dX != nullptr, &takes_scale, &takes_dshift);
+    conv_bwd_takes(d, T_saved, dX, dUk, dVp, &takes_scale, &takes_dshift);
     const bool in_kernel = scale && takes_scale;
     const bool scaled = !in_kernel && scale && Vp && d->Cout > 0 && d->r > 0 && d->N > 0;
     if (scaled) {

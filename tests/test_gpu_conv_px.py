@@ -219,6 +219,34 @@ def test_saved_filters_stay_in_their_buffer(dtype, shape):
     assert all(torch.equal(x, y) for x, y in zip(one, other))
 
 
+@pytest.mark.parametrize("shape", [(2, 256, 4, 12, 256, 64, 3), (3, 256, 6, 10, 512, 128, 1)])
+def test_batch_norm_in_the_backward_kernels(shape):
+    """Planes that the chain kernel takes forward and not the gradients of its filters: the pixel-major kernels fold the scale in and form the
+    shift gradient, in three launches; without a T that was kept other kernels do, to the same results (dT and dVp in bf16 and float,
+    the scaled filters are rounded in either case: a share of 2^-8 per rounding)."""
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, r, k = shape
+    g = torch.Generator(device="cuda").manual_seed(14)
+    b = lambda *s: torch.randn(*s, generator=g, device="cuda").bfloat16()
+    X, Uk, Vp, dZ = b(N, C, H, W), b(r, C, k, k) * (C * k * k) ** -0.5, b(Cout, r) * r ** -0.5, b(N, Cout, H, W)
+    scale = torch.rand(Cout, generator=g, device="cuda") + 0.5
+    Y, T, kept = pf.pf_lowrank_conv_fwd_ep(X, Uk, Vp, scale, pad=k // 2, save_W=True)
+    pf.timing_reset()
+    pf.timing_enable(True)
+    one = pf.pf_lowrank_conv_bwd_ep(X, Uk, Vp, scale, dZ, T_saved=T, pad=k // 2, W_saved=kept)
+    pf.timing_enable(False)
+    assert sorted(n for n in pf.timing_collect()) == ["conv_bwd_px", "conv_wgrad_px", "split_sums"]
+    other = pf.pf_lowrank_conv_bwd_ep(X, Uk, Vp, scale, dZ, pad=k // 2)
+    h, Vs = lambda t: t.cpu().double(), (Vp.float() * scale[:, None]).bfloat16()
+    dT = F.conv2d(h(dZ), h(Vs).t()[:, :, None, None]).bfloat16().double()
+    P = (h(dZ) * scale.cpu().double()[:, None, None]).flatten(2)
+    want = (torch.nn.grad.conv2d_input(X.shape, h(Uk), dT, padding=k // 2), torch.nn.grad.conv2d_weight(h(X), Uk.shape, dT, padding=k // 2),
+            (P @ h(T).flatten(2).transpose(1, 2)).sum(0), h(dZ).sum((0, 2, 3)))
+    for got in (one, other):
+        for x, ref, what in zip(got, want, ("dX", "dUk", "dVp", "dshift")):
+            _close(x.cpu(), ref, 4e-3, f"{shape} {what}")
+
+
 @pytest.mark.parametrize("shape", [(4, 256, 8, 8, 256, 64, 3), (3, 256, 8, 8, 1024, 128, 1), (28, 512, 8, 8, 256, 128, 1)])
 def test_plain_calls_and_epilogues(shape):
     """Calls without an epilogue may run on another kernel than those with one: the same output, to two roundings of T and Y (2^-9 of a
