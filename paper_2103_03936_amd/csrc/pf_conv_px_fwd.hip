@@ -384,14 +384,38 @@ bool px_fits(int N, int C, int H, int W, int Cout, int r, int k, int stride, int
 template bool px_fits<uint16_t>(int, int, int, int, int, int, int, int, int, int, int);
 template bool px_fits<float>(int, int, int, int, int, int, int, int, int, int, int);
 
-// Tiles repeat with the position of their first pixel in the plane: all of them, or as many as there are positions.
+// Have all tiles at most `slots` slots and `groups` groups?  A plan asks this for each tile size in both directions, so it is answered from a
+// bound where that will do: `all` pixels on R rows more than one of n planes have all + h R + h Wp (n - 1) slots and the reach of the taps,
+// and no more groups than (pixels + (V - 1) n) / V.  Otherwise from tiles: how far one reaches depends on where in the plane it starts,
+// on a multiple of `step`, and inside a plane on the column alone (with stride, on the row within V as well), so the first rows and
+// the end of a plane stand for all.  A plan takes 1 to 3 us so, where trying every tile took 42 (16 x 16 pixels) to 7700 (225 x 225).
 template <int S>
 static bool px_tiles_fit(const PxPlane<S> &g, const PxPlane<S> &o, int stride, int P, int slots, int groups)
 {
+    constexpr int V = 1 << S;
+    const auto gcd_with = [](int p, int n) { return n % p ? n & -n : p; }; // of a power of two and n
     const i64 npx = (i64)o.N * o.HW, tiles = (npx + P - 1) / P;
-    for (i64 i = 0; i < tiles && i < o.HW; ++i) { // (p0 = i P: all that i P mod HW can be)
-        const PxTile t = px_tile(g, o, stride, (int)(i * P), P);
-        if (t.slots > slots || px_groups(g, t) > groups) return false;
+    const int step = gcd_with(P, o.HW), all = npx < P ? (int)npx : P;
+    if (stride == 1) {
+        const int planes = (o.HW - step + all - 1) / o.HW, rows = (o.W - gcd_with(step, o.W) + all - 1) / o.W; // (more than one)
+        const int range = all + 2 * g.h * (g.W + 1);
+        const int most = g.HW % V == 0 ? (range + (g.h ? 2 : 1) * (V - 1)) / V : (range + (V - 1) * (planes + 1)) / V;
+        if (all + g.h * (rows + planes * g.Wp + 2 * (g.Wp + 1)) <= slots && most <= groups) return true;
+    }
+    const auto fits = [&](i64 p0) {
+        const PxTile t = px_tile(g, o, stride, (int)p0, P);
+        return t.slots <= slots && px_groups(g, t) <= groups;
+    };
+    const i64 period = (i64)step * (o.W / gcd_with(step, o.W)) * (stride > 1 ? V : 1); // of the column (and the row within V)
+    const i64 head = period + 4 * o.W, tail = (o.HW - 4 * o.W - P) / step * step;
+    if (tiles <= 256 || head >= tail) {
+        for (i64 i = 0; i < tiles && i < o.HW / step; ++i) // (i P mod HW takes every position)
+            if (!fits(i * P)) return false;
+        return true;
+    }
+    for (i64 q = 0; q < o.HW; q += step) { // (more than 256 tiles: the end of a plane is followed by another, if it can be)
+        if (q >= head && q < tail) q = tail;
+        if (!fits(q)) return false;
     }
     return true;
 }

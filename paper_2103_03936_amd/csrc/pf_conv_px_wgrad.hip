@@ -356,13 +356,14 @@ void px_wgrad_plan(int npx, int r, int C1, int k, int C2, int (&groups)[2], int 
     const double cost[2] = {px_wgrad_cost<T>(k, r), px_wgrad_cost<T>(1, r)};
     const double mb[2] = {4e-6 * r * C1 * k * k, 4e-6 * r * C2};
     double best = 1e30;
-    for (int p1 = 1; p1 <= tiles; ++p1) { // tiles per group of the first problem; the second takes as long
-        const int g1 = (tiles + p1 - 1) / p1;
-        if (g1 > 1 && units[0] * g1 + units[1] > 256) continue;
-        int p2 = (int)(p1 * cost[0] / cost[1]);
-        p2 = p2 < 1 ? 1 : p2 > tiles ? tiles : p2;
-        int g2 = (tiles + p2 - 1) / p2;
-        while (g2 > 1 && units[0] * g1 + units[1] * g2 > 256) p2++, g2 = (tiles + p2 - 1) / p2;
+    // tiles per group of the first problem, from the fewest that one round of the chip allows to where they alone take longer than the best;
+    // the second takes as long, or what room is left
+    const int most1 = units[1] + units[0] < 256 ? (256 - units[1]) / units[0] : 1;
+    for (int p1 = (tiles + most1 - 1) / most1; p1 <= tiles && p1 * cost[0] < best; ++p1) {
+        const int g1 = (tiles + p1 - 1) / p1, room = 256 - units[0] * g1, most2 = room > units[1] ? room / units[1] : 1;
+        int p2 = (int)(p1 * cost[0] / cost[1]), least = (tiles + most2 - 1) / most2;
+        p2 = p2 < least ? least : p2 > tiles ? tiles : p2;
+        const int g2 = (tiles + p2 - 1) / p2;
         const double a = p1 * cost[0], b = p2 * cost[1], t = (a > b ? a : b) + (g1 * mb[0] + g2 * mb[1]) * 1.5;
         if (t < best) {
             best = t;
