@@ -163,6 +163,7 @@ struct ConvPlan {
     TileShape sh_T, sh_Y, sh_dT, sh_g, sh_w; // ... the tile shapes of their launches
     int ks_T, ks_dT;         // ... splits of the products that give T and dT
     int ks_tU, ks_tV;        // ... image splits of the two filter gradients
+    i64 t_U, t_V;            // ... and their tiles
     size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction, 0: not
@@ -244,6 +245,7 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
         const i64 per = (g.N + ks - 1) / ks;
         return (int)((g.N + per - 1) / per);
     };
+    p.t_U = tU, p.t_V = tV;
     p.ks_tU = split(tU, (i64)g.r * g.C * kk);
     p.ks_tV = split(tV, (i64)g.Cout * (g.r + 1));
     p.n_pack = kk > 1 ? (size_t)g.r * g.C * kk : 0;
@@ -252,7 +254,7 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
 
 // The pixel-major kernels (pf_conv_px.h): which takes a direction, and whether one does.  Costs in microseconds, fitted to times of 190
 // shapes in bf16, 140 in float and 100 with stride over 1 to 256 images of 4 x 4 to 32 x 32 pixels, 32 to 2048 channels, ranks 1 to 128
-// (3 to 15 % rms; the tiled products 10 to 14 %).
+// (3 to 15 % rms).
 // A workgroup of P pixels costs a fixed part, one for the filters that it reads (per 64 channels and 32 ranks), one per chunk of
 // input channels and per 64 output channels, one where planes are not whole 16-byte pieces, and memory traffic as far as the chip is full;
 // small tiles read the filters more often, large ones leave compute units idle.
@@ -277,14 +279,36 @@ static const PxCost PX_BWD[] = {{128, 512, 128, 1.58, 0.19, 0.35, 0.70, 0.64, 0.
 static const PxCost PX_BWD_F32[] = {{128, 512, 64, 0.72, 2.06, 0.14, 0.13, 0.51, 2.81, 18.49, 0.81, 0.00, 0.00},
                                     {64, 512, 64, 2.64, 1.08, 1.03, 0.00, 0.49, 1.55, 15.49, 0.44, 12.60, 0.00},
                                     {32, 512, 128, 2.69, 0.00, 3.07, 0.38, 0.56, 1.04, 15.13, 0.00, 37.05, 0.00}};
-// The tiled products: a fixed part; per 10^7 pixels of 32 ranks x columns of the thin product, x output channels, of columns and output
-// channels alone; per 1000 terms of the thin sum, for ragged planes, per 10^6 factor elements and per 1000 pixels of a plane.
-struct TiledCost {
-    double launches, thin, wide, macs, terms, ragged, factors, plane;
+// Whether they take a direction: the estimate, corrected, against that of the tiled products, both of the geometric mean of a call without
+// epilogue and one with, fitted to 2050 shapes forward and 1130 backward, half of them of 60 to 4000 pixels, planes of 3 x 3 to 80 x 80 (6
+// to 10 % rms, hence the margins).  Over these shapes a call is 1.52 (bf16) and 1.30 times (float) as fast forward as on the tiled products
+// alone, 1.20 and 1.5 backward; of a hundred shapes two are more than 5 % slower.  These kernels are the slower ones where a few
+// workgroups pass through many channels, which the tiled products deal out (us, tiled / here: 1 image of 992 x 4 x 4 -> 128, rank 57, 3 x 3
+// 20 / 30, 7 of 816 x 3 x 3 -> 168 backward 22 / 38), and in float where a large plane's traffic counts (215 of 64 x 40 x 40, stride 2 92 / 113).
+struct PxCorrection {
+    double estimate, outputs, ragged_outputs, rounds; // forward: per round, of it and a piece of output channels (as that, in ragged planes); per round after the first
 };
-static const TiledCost TILED_FWD[2][2] = {{{12.8, 1.08, 6.7, 1.75, 2.64, 3.4, 0, 0}, {15.71, 9.57, 24.16, 1.53, 2.46, 2.42, 11.43, 0}}, // stride 1: bf16, float
-                                          {{17.87, 5.24, 0, 2.39, 0.95, 4.45, 7.53, 0}, {16.89, 1.42, 22.14, 11.52, 4.0, 1.16, 0, 0}}}; // more
-static const TiledCost TILED_BWD[2] = {{20.8, 1.78, 8.7, 5.26, 0, 4.8, 19.3, 0}, {19.05, 30.08, 0, 27.47, 0, 5.03, 143.25, 30}};
+static const PxCorrection PX_FWD_COR[2][2] = {{{0.907, 0.894, 0.5, 0.765}, {0.956, 0.853, 0, 1.717}}, // stride 1: bf16, float
+                                              {{0.933, 0.699, 0.817, 0}, {0.968, 0.567, 1.168, 2.18}}}; // more
+struct PxBwdCorrection {
+    double estimate, ragged, odd, in, out, chain, chain_ranks; // per round in ragged planes, with ranks that are not whole pieces; per 10^7
+                                                              // elements of dX, of dZ; per round and 64 channels of dZ, and 32 ranks of them
+};
+static const PxBwdCorrection PX_BWD_COR[2] = {{0.861, 1.131, 1.04, 4.777, 3.669, 0.214, 0.089}, {0.833, 0.602, 0.411, 7.081, 9.211, 0, 0}};
+// The tiled products: the launches, one more where the first stage's contraction is split; its chain of chunks (times the rounds that its
+// workgroups need), 10^7 terms of 32 ranks, 10^6 partial sums; the second stage's chain, 10^7 elements out and in; ragged planes, and their
+// elements and terms.  Backward the first stage is dT; then dX and both gradients side by side: rounds of chunks, the longest chain,
+// 10^6 partial sums and factor elements.
+struct TiledFwdCost {
+    double launches, split, chain, thin, part, wide, out, in, ragged, ragged_elements;
+};
+static const TiledFwdCost TILED_FWD[2][2] = {{{8.711, 4.405, 0.504, 0.316, 2.025, 1.544, 14.777, 1.258, 3.646, 0.365}, {8.991, 4.409, 0.614, 4.427, 1.936, 3.136, 22.369, 0.358, 2.782, 0.412}},
+                                             {{9.495, 4.275, 1.468, 1.13, 2.693, 2.383, 6.862, 2.389, 2.878, 5.239}, {8.73, 3.831, 0.951, 4.24, 1.457, 4.34, 14.368, 3.389, 2.024, 3.259}}};
+struct TiledBwdCost {
+    double launches, split, chain, rounds, longest, part, factors, in, out, ragged, ragged_elements;
+};
+static const TiledBwdCost TILED_BWD[2] = {{14.609, 3.899, 0.493, 0.348, 0.854, 2.17, 0, 24.072, 3.553, 5.189, 2.854},
+                                          {14.145, 3.915, 0.894, 1.727, 1.092, 0, 36.439, 18.785, 1.8, 4.532, 12.376}};
 
 template <typename T>
 static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
@@ -312,11 +336,27 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
         }
         return least;
     };
-    const auto tiled = [&](const TiledCost &c) {
-        const double m = npx * 1e-7;
-        return c.launches + m * (c.thin * RB * g.C * kk + c.wide * RB * g.Cout + c.macs * (g.C * kk + g.Cout) * (1 + 0.5 * ragged)) +
-               1e-3 * c.terms * g.C * kk + c.ragged * ragged + c.factors * mf + 1e-3 * c.plane * g.H * g.W;
+    const double m = npx * 1e-7, padded = (double)((g.Ho * g.Wo + V - 1) / V * V) * g.N, ragged_m = ragged * m * (g.C * kk + g.Cout);
+    // rounds that workgroups of 64 columns and `rows` of `of` rows need, two to a compute unit
+    const auto turns = [&](int of, int rows, int ks) {
+        const double r = (double)((of + rows - 1) / rows) * ceil(padded / 64) * ks / 512;
+        return r < 1 ? 1 : r;
     };
+    const int rows1 = g.r <= 32 ? 32 : 64, K = 8 * V; // of the first stage; a chunk of a contraction
+    const auto chunks = [&](int n) { return (n + K - 1) / K; };
+    const auto tiled_fwd = [&](const TiledFwdCost &c) {
+        return c.launches + c.split * (p.ks_T > 1) + c.chain * turns(g.r, rows1, p.ks_T) * chunks(g.C * kk) / p.ks_T + c.thin * m * RB * g.C * kk +
+               (p.ks_T > 1 ? c.part * 1e-6 * p.ks_T * g.r * padded : 0) + c.wide * turns(g.Cout, 64, 1) * chunks(g.r) + c.out * m * g.Cout +
+               c.in * 1e-7 * g.N * g.H * g.W * g.C + c.ragged * ragged + c.ragged_elements * ragged_m;
+    };
+    const auto tiled_bwd = [&](const TiledBwdCost &c) {
+        const double runs = padded / (f32 ? 32 : 64), rows = chunks(g.r * kk), U = runs / p.ks_tU, W = runs / p.ks_tV;
+        return c.launches + c.split * (p.ks_dT > 1) + c.chain * turns(g.r, rows1, p.ks_dT) * chunks(g.Cout) / p.ks_dT +
+               c.rounds * (ceil(g.C / 64.0) * ceil(padded / 64) * rows + (p.t_U + p.t_V) * runs) / 512 + c.longest * (rows > U ? (rows > W ? rows : W) : U > W ? U : W) +
+               c.part * 1e-6 * ((double)p.ks_tU * g.r * g.C * kk + (double)p.ks_tV * g.Cout * g.r) + c.factors * mf + c.in * m * g.C + c.out * m * g.Cout +
+               c.ragged * ragged + c.ragged_elements * ragged_m;
+    };
+    const auto rounds = [&](int P, int threads) { return (double)(((npx + P - 1) / P + (threads == 256 ? 511 : 255)) / (threads == 256 ? 512 : 256)); };
     // of the chain kernel's shapes one workgroup per image streams both factors; without scale, shift, residual input and ReLU its output
     // is the cheaper part (over 32 shapes 9 % rms)
     const double chain_fwd = ((g.N + 255) / 256) * (9 + (0.055 * g.C * kk + 0.35 * g.Cout) * RB / 64);
@@ -325,7 +365,13 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
     double t;
     if constexpr (f32) t = g.s > 1 ? best(PX_FWD_STRIDED_F32, g.C, g.Cout, P, threads) : best(PX_FWD_F32, g.C, g.Cout, P, threads);
     else t = g.s > 1 ? best(PX_FWD_STRIDED, g.C, g.Cout, P, threads) : best(PX_FWD, g.C, g.Cout, P, threads);
-    if (P && (p.chain ? t < 0.95 * chain_fwd : (!f32 && g.r <= 64) || t < (f32 ? 0.9 : 1) * tiled(TILED_FWD[g.s > 1][f32]))) p.px_fwd = P, p.px_fwd_threads = threads;
+    if (P && !p.chain) {
+        const PxCorrection &c = PX_FWD_COR[g.s > 1][f32];
+        const int at_once = px_outputs(RB, P, threads);
+        const double n = rounds(P, threads), pieces = n * ((g.Cout + at_once - 1) / at_once);
+        t = c.estimate * t + (c.outputs + c.ragged_outputs * ragged) * pieces + c.rounds * (n - 1);
+    }
+    if (P && (p.chain ? t < 0.95 * chain_fwd : t < (f32 ? 0.9 : 0.95) * tiled_fwd(TILED_FWD[g.s > 1][f32]))) p.px_fwd = P, p.px_fwd_threads = threads;
     // Such calls stay with the chain kernel where it is the faster one, us, chain / here: 128 images of 256 x 8 x 8, rank 64, 3 x 3 14.3 / 14.2,
     // and 38.6 / 41.1 with the backward direction, which finds its filters packed in either case; 94 of 512 -> 1024 21.3 / 24.9; one tap, rank
     // 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5.  (All times with inputs from memory.)
@@ -335,7 +381,11 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
     P = 0;
     if constexpr (f32) t = best(PX_BWD_F32, g.Cout, g.C, P, threads);
     else t = best(PX_BWD, g.Cout, g.C, P, threads);
-    if (!P || !(p.chain || (!f32 && g.r <= 32) || 1.03 * t < tiled(TILED_BWD[f32]))) return;
+    const PxBwdCorrection &c = PX_BWD_COR[f32];
+    if (!P) return;
+    t = c.estimate * t + m * (c.in * g.C + c.out * g.Cout) +
+        rounds(P, threads) * (c.ragged * ragged + c.odd * (g.r % 8 ? 1 : 0) + (c.chain + c.chain_ranks * RB) * g.Cout / 64);
+    if (!p.chain && t >= 0.95 * tiled_bwd(TILED_BWD[f32])) return;
     p.px_bwd = P, p.px_bwd_threads = threads;
     px_wgrad_plan<T>((int)npx, g.r, g.C, g.k, g.Cout, p.px_groups, p.px_per);
     p.px_pack = px_pack_elems(g.C, g.r, g.k);

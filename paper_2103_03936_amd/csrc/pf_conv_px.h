@@ -87,6 +87,12 @@ struct PxWgradArgs {
     PxGrad<T> p[2];      // the first one may have nine taps
 };
 
+// Output channels that the forward kernel forms at a time
+constexpr int px_outputs(int rank_blocks, int P, int threads)
+{
+    return threads == 512 ? (P == 32 ? 256 : 128) : P == 32 ? 128 : rank_blocks * P == 512 ? 32 : 64;
+}
+
 // Shapes the kernels take: sizes, alignment of the rows, 32-bit offsets (float: ranks up to 64)
 template <typename T>
 bool px_fits(int N, int C, int H, int W, int Cout, int r, int k, int stride, int pad, int Ho, int Wo);

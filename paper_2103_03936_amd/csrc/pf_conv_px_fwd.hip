@@ -36,7 +36,7 @@ struct PxFwdCfg {
     static constexpr int RING = NT == 512 && PARTS % 2 == 0 ? 2 : 1, XRING = KK == 1 ? 2 : 1; // parts, chunks in flight
     static constexpr int WBUF = NT == 512 ? 2 : 1, WBYTES = 32 * RB * WPITCH;
     // second stage
-    static constexpr int OC = NT == 512 ? (PB == 1 ? 256 : 128) : PB == 1 ? 128 : RB * PB == 16 ? 32 : 64; // output channels at a time
+    static constexpr int OC = px_outputs(RB, P, NT);
     static constexpr int OM = OC / 32, ON = WAVES / OM, ONB = PB / ON; // wavefronts over (channels, pixels)
     static constexpr int RP = 32 * RB / V, TP = (32 * RB + PxEl<T>::PC - 1) / PxEl<T>::PC; // pieces of all ranks, panels
     static constexpr int CP = P + 4;                                   // pitch of float tiles

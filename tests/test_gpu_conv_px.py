@@ -195,7 +195,7 @@ def test_infinite_edges_in_gradients(px, shape):
             assert torch.isfinite(pV).all()
 
 
-@pytest.mark.parametrize("dtype, shape", [(torch.float32, (226, 64, 14, 14, 64, 16, 1)), (torch.float32, (12, 96, 14, 14, 96, 24, 1)),
+@pytest.mark.parametrize("dtype, shape", [(torch.float32, (88, 64, 13, 10, 64, 16, 1)), (torch.float32, (12, 96, 14, 14, 96, 24, 1)),
                                           (torch.float32, (2, 44, 5, 5, 36, 7, 3)), (torch.bfloat16, (12, 128, 16, 16, 128, 32, 3))])
 def test_saved_filters_stay_in_their_buffer(dtype, shape):
     """A forward call writes as many bytes of W_save as the query states and none beyond, and the backward call gives the same with and

@@ -23,7 +23,7 @@ def _saved(*shape, **opt):
     return pf.lib.pf_lowrank_conv_saved_weights_bytes(ctypes.byref(_desc(*shape, **opt)))
 
 
-@pytest.mark.parametrize("shape, el", [((226, 64, 14, 14, 64, 16, 1), 4), ((12, 96, 14, 14, 96, 24, 1), 4), ((128, 128, 16, 16, 256, 32, 1), 4),
+@pytest.mark.parametrize("shape, el", [((88, 64, 13, 10, 64, 16, 1), 4), ((12, 96, 14, 14, 96, 24, 1), 4), ((128, 128, 16, 16, 256, 32, 1), 4),
                                        ((128, 128, 16, 16, 128, 32, 3), 2)])
 def test_saved_filters_have_the_size_that_is_written(shape, el):
     """Where the pixel-major kernels take both directions the forward call keeps the thin filters for the backward one: every tap of
@@ -101,3 +101,16 @@ def test_time_of_a_plan():
     assert max(worst.values()) < 100e-6, max(worst, key=worst.get)
     rounds = [[_seconds(s) for s in RESNET50] for _ in range(6)][1:]
     assert max(min(t) for t in zip(*rounds)) < 10e-6
+
+
+@pytest.mark.parametrize("shape", [(7, 816, 3, 3, 168, 14, 3), (2, 1040, 13, 10, 40, 18, 3), (3, 1024, 10, 10, 64, 16, 3), (1, 640, 8, 8, 128, 32, 3),
+                                   (3, 576, 25, 4, 80, 20, 3)])
+def test_few_tiles_with_many_channels_are_dealt_out(shape):
+    """Shapes that the tiled products ran in half to four fifths of the time that the pixel-major kernels take: nothing is kept for those."""
+    assert _saved(*shape, dtype=pf.PF_BF16) == 0
+
+
+@pytest.mark.parametrize("shape", [(128, 128, 16, 16, 128, 32, 3), (256, 64, 32, 32, 64, 16, 3), (32, 256, 14, 14, 256, 64, 3)])
+def test_layers_of_the_pixel_major_kernels(shape):
+    """... and shapes that they run 1.3 to 2.9 times as fast in both directions."""
+    assert _saved(*shape, dtype=pf.PF_BF16) > 0
