@@ -9,6 +9,8 @@
 #include "pf_skinny.h"
 #include "pf_linear_small.h"
 #include "pf_tile_host.h"
+
+#include <math.h>
 #include "pf_conv_wgrad.h"
 #include <mutex>
 #include "pf_gemm.h"
@@ -222,10 +224,12 @@ static bool chain_bwd_pays(i64 M, i64 in, i64 out, i64 r)
 // (several layers that share their input; backward, their dX is one tiled product over all ranks)
 static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 512 || (in <= 1024 && M <= 4096)); }
 
-// Both stages in one launch (pf_linear_two.h): rows per workgroup, or 0 for the other kernels.  Their times, fitted to 130 shapes (7 and 9 %
-// rms): the tiled products' two launches, or three where T is split; at rank 128 and widths in multiples of 256 those of the chain kernel, or
-// the tiled products where it does not pay.  Over 43 drawn shapes 1.51 times as fast as the tiled products, geometric mean, over 60 of
-// the others 1.14 (8192 x 512 -> 128 -> 512 three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by
+// Both stages in one launch (pf_linear_two.h): rows per workgroup, or 0 for the other kernels.  Their times: the tiled products' two
+// launches, or three where T is split, and the corrected ones of the two-stage kernel (plan_linear_two) against them, the geometric mean of
+// a plain call and one with residual and ReLU, fitted to 785 shapes (7 and 10 % rms: ranks above 64, four blocks wide, cost it more than the
+// plan says, most of all where they are not whole pieces and are fitted in registers: 7 x 576 -> 67 -> 2824 10.6 / 12.9 us, 1313 x 1104
+// -> 83 -> 2016 16.0 / 19.3); at rank 128 and widths in multiples of 256 those of the chain kernel, fitted to 130 shapes.  Over the 785
+// shapes 1.42 times as fast where it is taken, three of a thousand calls more than 5 % slower; over 60 of the others 1.14 (8192 x 512 -> 128 -> 512 three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by
 // both); few rows and inputs up to 1024 wide stay with the row kernel (423 x 512 -> 512: 6.6 against 7.3).
 static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
 {
@@ -233,15 +237,22 @@ static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
     int rows = 0;
     const double t = plan_linear_two(M, in, out, r, G, rows, split), m = 1e-6 * M;
     const double chain = 8.07 + m * (0.625 * G * out + 0.205 * (in + G * out)) + 2.44e-3 * in;
-    const double tiled = 9.12 + m * (0.655 * G * out * ((r + 63) / 64) + 0.138 * (in + G * out) * (r % 8 ? 2 : 1)) + 1.09e-3 * in +
-                         (in >= 512 && G * M * r < 64 * 64 * 200 ? 0.5 : 0);
-    return t < (linear_chain2_supported(in, out, r) ? chain : 0.97 * tiled) ? rows : 0;
+    if (linear_chain2_supported(in, out, r)) return t < chain ? rows : 0;
+    const double odd = r % 8 ? 1 : 0, wide = r > 64 ? 1 : 0, tiles = (double)G * ((M + 63) / 64) * ((r + 63) / 64);
+    const double tiled = 8.37 + m * (0.359 * in + G * out * (0.808 + 0.22 * ((r + 63) / 64)) + 0.172 * odd * (in + G * out)) + 0.69 * odd + 0.52 * wide +
+                         (1.07e-3 + (tiles > 100 ? 0.49e-3 : 0)) * in + (in >= 512 && tiles < 200 ? 0.67 : 0);
+    // chunks of the first stage, pieces of outputs, rounds of workgroups
+    const double chunk = wide && rows == 128 ? 64 : 128, steps = ceil(in / chunk), per = ceil(ceil(out / 128.0) / split);
+    const double rounds = ceil((double)((M + rows - 1) / rows) * split * G / 256);
+    const double two = 0.94 * t + 0.885 * wide + rounds * (0.164 * odd * per + wide * (0.059 * steps + 0.058 * per) + wide * odd * (0.188 * steps + 0.387 * per));
+    return two < 0.95 * tiled ? rows : 0;
 }
 
 // The times above are of calls with a residual input.  Without one and without a ReLU the chain kernel is the faster one for inputs up to 512
 // wide while it has one workgroup per compute unit (us, chain / two-stage, inputs from memory: 8192 x 512 -> 512 9.3 / 10.8, 8192 x 512 ->
 // 256 7.4 / 8.6, 6000 x 256 -> 256 6.6 / 7.7, but 4096 x 256 -> 1024 10.4 / 8.8, 9000 x 512 -> 512 15.3 / 11.9).  Its times over 22 shapes, 2 % rms;
-// the two-stage kernel's are 0.7 above the plan's there.
+// the two-stage kernel's are 0.7 above the plan's there.  Of other widths it is the slower one at
+// every number of rows from 1100 to 8192 (256 or 512 -> 768 1.02 to 1.50 times as long, 1280 1.11 to 1.66, 1536 1.13 to 1.51).
 // G layers that share their input are G times the rows to it: three of 512 -> 512 at 1400 rows 8.3 / 10.0, of 256 -> 256 6.8 / 7.6, but at 2730
 // rows (258 workgroups) 14.7 / 11.9.
 static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r, int G = 1)
@@ -252,20 +263,26 @@ static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r, int G = 1)
 }
 
 // Backward, dT and dX in one launch of it and the factor gradients in another (pf_linear_grad.h): rows per workgroup, or 0 for the other
-// kernels, by times fitted to 170 shapes (600 to 17000 rows, 128 to 4096 wide, ranks 8 to 128; 9 and 8 % rms).  Of these the rule takes 77,
-// 1.32 times as fast (geometric mean, the worst 0.92), where X masks dX 1.37.  512 -> 128 -> 2048, us, before / now: 44.5 / 40.3 at 8192
+// kernels, by times fitted to 170 shapes (600 to 17000 rows, 128 to 4096 wide, ranks 8 to 128; 9 and 8 % rms); of rank 128 and widths in
+// multiples of 256 they are all that counts.  Elsewhere a closer fit has to agree, to 700 shapes from 200 rows on and calls without and with
+// a skip gradient and a mask (9 and 5 % rms).  Of these the rule takes 180, 1.29 times as fast (geometric mean; a few small ranks up to a
+// tenth slower with both, 6851 x 512 -> 40 -> 176 19.6 / 22.0).  512 -> 128 -> 2048, us, before / now: 44.5 / 40.3 at 8192
 // rows; 2048 -> 512 with mask 53.9 / 42.1, at 16384 rows 102 / 66; 1536 -> 96 -> 384 52.0 / 31.8.  Few rows stay with the tiled products,
 // which form dX and the gradients side by side (1000 rows, 512 -> 512: 13.5 / 19.2).
 static int two_bwd_rows(i64 M, i64 in, i64 out, i64 r, int &split)
 {
     if (!linear_two_supported(M, out, in, r) || !plan_linear_grad(M, in, out, r).splits) return 0;
-    const double m = 1e-6 * M, w = (double)(in + out);
-    const double before = 11.56 + m * (1.488 * in + 0.699 * out + 6.26 * r + 0.00717 * w * r) + 2.1e-4 * w;
-    const double now = 12.74 + m * (0.367 * w + 7.75 * r + 0.00246 * w * r) + 8.9e-4 * w + 2.24e-5 * w * r;
-    if (now >= 0.97 * before) return 0;
     int rows = 0;
-    plan_linear_two(M, out, in, r, 1, rows, split);
-    return rows;
+    const LinGradPlan lg = plan_linear_grad(M, in, out, r);
+    const double m = 1e-6 * M, w = (double)(in + out), tiles = ceil(M / 64.0) * ceil(r / 64.0), t = plan_linear_two(M, out, in, r, 1, rows, split);
+    const double coarse_before = 11.56 + m * (1.488 * in + 0.699 * out + 6.26 * r + 0.00717 * w * r) + 2.1e-4 * w;
+    const double coarse_now = 12.74 + m * (0.367 * w + 7.75 * r + 0.00246 * w * r) + 8.9e-4 * w + 2.24e-5 * w * r;
+    if (coarse_now >= 0.97 * coarse_before) return 0;
+    if (linear_chain2_supported(in, out, r)) return rows;
+    const double before = 5.34 + m * (1.44 * in + 0.197 * out + 3.92 * r + 0.00137 * w * r + 0.743 * w * ceil(r / 64.0)) + (tiles < 200 ? 4.67 : 0) +
+                          1.025e-3 * (tiles > 512 ? tiles / 512 : 1) * out + 3.62e-4 * M;
+    const double now = 11.29 + 0.391 * t + (0.22 + 0.00389 * r) * lg.per + 1.835e-6 * lg.splits * w * r + m * (0.699 * in + 0.388 * out) + (r > 64 ? 2.73 : 0) + 5.0e-4 * w;
+    return now < 0.95 * before ? rows : 0;
 }
 
 static LinearPlan make_linear_plan(const pf_linear_desc *d)

@@ -110,6 +110,27 @@ def test_backward(shape):
             assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
 
 
+def _launches(pf, call):
+    """What a call launches, by the library's own records."""
+    pf.timing_reset()
+    pf.timing_enable(True)
+    call()
+    pf.timing_enable(False)
+    return set(pf.timing_collect())
+
+
+@pytest.mark.parametrize("M,K,r,N,forward,two", [(2000, 256, 64, 1024, True, True), (3001, 640, 96, 640, True, True), (7, 576, 67, 2824, True, False),
+                                                 (1313, 1104, 83, 2016, True, False), (8192, 512, 128, 2048, False, True), (6001, 1032, 64, 264, False, True),
+                                                 (4891, 480, 72, 496, False, False), (4246, 768, 64, 256, False, False)])
+def test_where_it_is_the_faster_one(M, K, r, N, forward, two):
+    """Shapes on both sides of the rule: 1.2 to 1.5 times as fast on these kernels, or on the tiled products."""
+    import paper_2103_03936_amd as pf
+    b = lambda *s: torch.randn(*s, device="cuda").bfloat16()
+    X, V, U, T, dY = b(M, K), b(K, r), b(N, r), b(M, r), b(M, N)
+    names = _launches(pf, (lambda: pf.pf_lowrank_linear_fwd(X, V, U)) if forward else (lambda: pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T)))
+    assert (("linear_fwd_two" if forward else "linear_bwd_data_two") in names) == two, names
+
+
 @pytest.mark.parametrize("M,K,N", [(8192, 512, 512), (6001, 256, 256), (8193, 512, 256)])
 def test_plain_calls_and_epilogues(M, K, N):
     """Calls without residual input and ReLU may run on another kernel than those with them.  Bounds as above."""
