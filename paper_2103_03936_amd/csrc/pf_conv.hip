@@ -167,7 +167,7 @@ struct ConvPlan {
     size_t n_part_T;         // ... their partial sums (floats)
     size_t n_pack, n_part_t; // ... re-ordered filters (elements), partial sums (floats)
     int px_fwd, px_fwd_threads; // pixels and threads per workgroup of the pixel-major kernels where they take the direction, 0: not
-    bool plain_chain; // ... but the chain kernel takes the calls without an epilogue
+    bool plain_chain, plain_chain_kept; // ... but the chain kernel takes the calls without an epilogue; those that keep filters for px_bwd
     int px_bwd, px_bwd_threads;
     int px_groups[2], px_per[2]; // ... and the pixel groups of their filter gradients, tiles per group
     size_t px_pack, px_dT, px_part; // ... elements of the re-ordered thin filters and of dT, floats of the partial sums
@@ -304,6 +304,14 @@ struct TiledFwdCost {
 };
 static const TiledFwdCost TILED_FWD[2][2] = {{{8.711, 4.405, 0.504, 0.316, 2.025, 1.544, 14.777, 1.258, 3.646, 0.365}, {8.991, 4.409, 0.614, 4.427, 1.936, 3.136, 22.369, 0.358, 2.782, 0.412}},
                                              {{9.495, 4.275, 1.468, 1.13, 2.693, 2.383, 6.862, 2.389, 2.878, 5.239}, {8.73, 3.831, 0.951, 4.24, 1.457, 4.34, 14.368, 3.389, 2.024, 3.259}}};
+// The chain kernel, planes of 8 x 8, of 7 x 7 and others, over 313 shapes of 1 to 256 images (plain calls 4 to 7 % rms, with epilogue 11 to 13):
+// an image, 32 ranks of 64 terms and of 64 output channels, a full chip's 4096 elements in or out, 64 input channels.  (7 x 7 with epilogue: 0.327
+// per output channel fits best, but makes 512 -> 2048 of rank 128, 45 us, 53.)
+struct ChainCost {
+    double image, thin, wide, move, in;
+};
+static const ChainCost CHAIN_PLAIN[3] = {{8.54, 0.0526, 0.1001, 0.1915, 0.0531}, {8.011, 0.0609, 0.1075, 0.2105, 0.0297}, {9.6, 0.0655, 0.116, 0.2988, 0.1316}};
+static const ChainCost CHAIN_EP[3] = {{9.422, 0.0511, 0.3086, 0.1989, 0.0858}, {9.345, 0.0596, 0.26, 0.128, 0.0302}, {11.113, 0.0658, 0.3066, 0.3898, 0.0964}};
 struct TiledBwdCost {
     double launches, split, chain, rounds, longest, part, factors, in, out, ragged, ragged_elements;
 };
@@ -357,25 +365,36 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
                c.ragged * ragged + c.ragged_elements * ragged_m;
     };
     const auto rounds = [&](int P, int threads) { return (double)(((npx + P - 1) / P + (threads == 256 ? 511 : 255)) / (threads == 256 ? 512 : 256)); };
-    // of the chain kernel's shapes one workgroup per image streams both factors; without scale, shift, residual input and ReLU its output
-    // is the cheaper part (over 32 shapes 9 % rms)
-    const double chain_fwd = ((g.N + 255) / 256) * (9 + (0.055 * g.C * kk + 0.35 * g.Cout) * RB / 64);
-    const double chain_plain = ((g.N + 255) / 256) * (8.8 + (0.057 * g.C * kk + 0.117 * g.Cout) * RB / 64);
+    // the chain kernel's shapes: one workgroup per image streams both factors
+    const auto chain = [&](const ChainCost (&list)[3]) {
+        const ChainCost &c = list[g.H != g.W || (g.H != 7 && g.H != 8) ? 2 : g.H == 7];
+        return (g.N + 255) / 256 * (c.image + RB / 64.0 * (c.thin * g.C * kk + c.wide * g.Cout) + c.in * g.C / 64) +
+               (g.N < 256 ? g.N / 256.0 : 1) * c.move * g.H * g.W / 4096 * (g.C + g.Cout);
+    };
     int P = 0, threads = 0;
     double t;
     if constexpr (f32) t = g.s > 1 ? best(PX_FWD_STRIDED_F32, g.C, g.Cout, P, threads) : best(PX_FWD_F32, g.C, g.Cout, P, threads);
     else t = g.s > 1 ? best(PX_FWD_STRIDED, g.C, g.Cout, P, threads) : best(PX_FWD, g.C, g.Cout, P, threads);
-    if (P && !p.chain) {
-        const PxCorrection &c = PX_FWD_COR[g.s > 1][f32];
+    if (P) {
         const int at_once = px_outputs(RB, P, threads);
         const double n = rounds(P, threads), pieces = n * ((g.Cout + at_once - 1) / at_once);
-        t = c.estimate * t + (c.outputs + c.ragged_outputs * ragged) * pieces + c.rounds * (n - 1);
+        bool takes;
+        if (p.chain) {
+            takes = 0.92 * t + 0.852 * pieces < 0.95 * chain(CHAIN_EP);
+            // Calls without an epilogue stay with the chain kernel where it is the faster one, us, chain / here: 128 images of 256 x 8 x 8, rank
+            // 64, 3 x 3 14.3 / 14.2; 94 of 512 -> 1024 21.3 / 24.9; one tap, rank 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5
+            // ... and where filters are to be kept for the pixel-major backward direction, if it pays the launch that re-orders them as well: 33
+            // images of 512 x 5 x 9 -> 2048, rank 128, one tap 27.6 / 37.1
+            const double here = 0.824 * t + 0.318 * pieces, there = chain(CHAIN_PLAIN);
+            p.plain_chain = here >= 0.92 * there;
+            p.plain_chain_kept = here >= there + 4;
+        } else {
+            const PxCorrection &c = PX_FWD_COR[g.s > 1][f32];
+            t = c.estimate * t + (c.outputs + c.ragged_outputs * ragged) * pieces + c.rounds * (n - 1);
+            takes = t < (f32 ? 0.9 : 0.95) * tiled_fwd(TILED_FWD[g.s > 1][f32]);
+        }
+        if (takes) p.px_fwd = P, p.px_fwd_threads = threads;
     }
-    if (P && (p.chain ? t < 0.95 * chain_fwd : t < (f32 ? 0.9 : 0.95) * tiled_fwd(TILED_FWD[g.s > 1][f32]))) p.px_fwd = P, p.px_fwd_threads = threads;
-    // Such calls stay with the chain kernel where it is the faster one, us, chain / here: 128 images of 256 x 8 x 8, rank 64, 3 x 3 14.3 / 14.2,
-    // and 38.6 / 41.1 with the backward direction, which finds its filters packed in either case; 94 of 512 -> 1024 21.3 / 24.9; one tap, rank
-    // 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5.  (All times with inputs from memory.)
-    p.plain_chain = p.chain && t >= 1.02 * chain_plain;
     // backward: unit stride
     if (g.s > 1 || !px_bwd_takes<T>(g.k, g.r) || (p.chain && p.wgrad) || !px_wgrad_fits(pl)) return;
     P = 0;
@@ -412,10 +431,9 @@ static ConvPlan make_conv_plan(const ConvGeom &g, int dtype)
     p.wgrad = p.chain && wgrad_supported(g.r, g.C, g.H, g.W, g.k, g.s, g.p) &&
               wgrad_supported(g.r, g.Cout, g.H, g.W, 1, 1, 0);
     p.px_fwd = p.px_bwd = 0;
-    p.plain_chain = false;
+    p.plain_chain = p.plain_chain_kept = false;
     if (dtype == PF_BF16) plan_conv_px<uint16_t>(g, p);
     else plan_conv_px<float>(g, p);
-    if (p.px_bwd) p.plain_chain = false; // (the filters it reads are packed by the forward kernel of its own)
     // (saved by a forward call for the kernels that take the backward direction)
     p.saved_bytes = p.px_bwd ? (p.px_fwd ? align_up(p.px_pack * (dtype == PF_BF16 ? 2 : 4)) : 0) : p.chain ? align_up(p.n_w1b * 2) + align_up(p.n_w2b * 2) : 0;
     p.wg_groups = p.wg_ipg = p.wg_groups2 = p.wg_ipg2 = 1;
@@ -1060,7 +1078,8 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
     const ConvEpilogue all = {scale, shift, residual, nullptr, act == PF_ACT_RELU ? 1 : 0, nullptr};
     if (!p.saved_bytes) W_save = nullptr;
     const bool plain = !scale && !shift && !residual && !all.relu;
-    if (p.px_fwd && !(plain && p.plain_chain)) {
+    const bool px_kept = p.px_bwd && W_save;
+    if (p.px_fwd && !(plain && (px_kept ? p.plain_chain_kept : p.plain_chain))) {
         *fused = true;
         PackW1 w1 = {};
         PackW2 w2 = {};
@@ -1093,8 +1112,10 @@ int pf::conv_fwd_entry_ep(const pf_conv_desc *d, const void *X, const void *Uk, 
             ep = all;
             *fused = true;
         }
-        return conv_fwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (bf16_t *)Y,
-                              (bf16_t *)T_save, W_save, ws, s, ep);
+        st = conv_fwd_chain(g, p, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (bf16_t *)Y, (bf16_t *)T_save,
+                            px_kept ? nullptr : W_save, ws, s, ep);
+        if (px_kept && st == PF_OK) st = launch_px_pack(s, PxPack<uint16_t>{(const uint16_t *)Uk, (uint16_t *)W_save, g.C, g.r, g.k * g.k});
+        return st;
     }
     return conv_fwd_generic<bf16_t>(g, (const bf16_t *)X, (const bf16_t *)Uk, (const bf16_t *)Vp, (bf16_t *)Y,
                                     (bf16_t *)T_save, ws, s);

@@ -247,7 +247,7 @@ def test_batch_norm_in_the_backward_kernels(shape):
             _close(x.cpu(), ref, 4e-3, f"{shape} {what}")
 
 
-@pytest.mark.parametrize("shape", [(4, 256, 8, 8, 256, 64, 3), (3, 256, 8, 8, 1024, 128, 1), (28, 512, 8, 8, 256, 128, 1)])
+@pytest.mark.parametrize("shape", [(4, 256, 8, 8, 256, 64, 3), (3, 256, 8, 8, 1024, 128, 1), (28, 512, 8, 8, 256, 128, 1), (33, 512, 5, 9, 2048, 128, 1)])
 def test_plain_calls_and_epilogues(shape):
     """Calls without an epilogue may run on another kernel than those with one: the same output, to two roundings of T and Y (2^-9 of a
     value at most each, on either side), and the same factors kept for the backward direction."""
