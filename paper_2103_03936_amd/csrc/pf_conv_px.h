@@ -1,4 +1,5 @@
-// Convolutions on pixel-major tiles, bf16 and float, 1 x 1 or 3 x 3 taps: forward with any stride, backward planes of equal size.
+// Convolutions on pixel-major tiles, bf16 and float, 1 x 1 or 3 x 3 taps: forward, and backward for planes of equal size.
+// (The forward kernel takes any stride; calls reach it with 1 and 2, those of the tiled products, which are what it is chosen over.)
 //
 // The activations lie in memory with the pixel fast and are multiplied with the channel as the contraction.  The tiled products
 // (pf_tile.h) keep that direction in LDS, so a tap is a shifted, masked copy of the operand: nine loads, masks and LDS writes of

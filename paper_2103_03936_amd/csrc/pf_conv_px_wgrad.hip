@@ -28,7 +28,7 @@ struct PxWgCfg {
     static constexpr int BROWS = 136, BPANEL = BROWS * 128, BBYTES = (SC + PC - 1) / PC * BPANEL;
     static constexpr int TABLE = 64 * TROW * 4, BUF = ABYTES + BBYTES + TABLE;
     static constexpr int AO = 32 * RB / V, BO = SC / V, GS = V == 8 ? 4 : 5, BLOCKS = ((AO + BO) * (2 << GS) + NT - 1) / NT; // pieces, groups of a tile (log2), blocks per thread
-    static constexpr int OPITCH = SC * KK + 4, ROUNDS = 1, OROWS = 32 * RB / ROUNDS, OBYTES = KS * OROWS * OPITCH * 4;
+    static constexpr int OPITCH = SC * KK + 4, OROWS = 32 * RB, OBYTES = KS * OROWS * OPITCH * 4;
     static constexpr int BYTES = 2 * BUF > OBYTES ? 2 * BUF : OBYTES;
     static __host__ __device__ constexpr int tap0(int tg) { return TG == 4 ? (tg ? 2 * tg + 1 : 0) : 5 * tg; } // first tap of a group (3, 2, 2, 2 or 5, 4)
     static_assert(BYTES + 16 <= 160 * 1024 && KS * TG * CW * MW == 8 && (KK == 9 || KS <= 4) && SC / V * 32 == (KK == 9 ? SC / V * 32 : NT), "");
@@ -271,34 +271,30 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
     float *part = p.part + (i64)group * a.r * p.C * KK;
     const int cols = min(F::SC, p.C - c0) * KK;
     float odd = 0.f; // (NaN once something is not finite)
+    __syncthreads();
 #pragma unroll
-    for (int r0 = 0; r0 < 32 * RB; r0 += F::OROWS) {
-        __syncthreads();
+    for (int i = 0; i < F::NA; ++i) {
+        const int tap = KK == 9 ? F::tap0(tg) + i : 0, row0 = (mi * F::MB + (KK == 9 ? 0 : i)) * 32;
+        if (KK == 9 && i == F::NA - 1 && tg > 0) break;
 #pragma unroll
-        for (int i = 0; i < F::NA; ++i) {
-            const int tap = KK == 9 ? F::tap0(tg) + i : 0, row0 = (mi * F::MB + (KK == 9 ? 0 : i)) * 32;
-            if (KK == 9 && i == F::NA - 1 && tg > 0) break;
+        for (int v = 0; v < 16; ++v) {
+            const int row = row0 + (v >> 2) * 8 + (v & 3) + 4 * hi;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + (v >> 2) * 8 + (v & 3) + 4 * hi - r0;
-                if (F::ROUNDS > 1 && (row0 + (v >> 2) * 8 < r0 || row0 + (v >> 2) * 8 >= r0 + F::OROWS)) continue;
-#pragma unroll
-                for (int j = 0; j < F::NB; ++j)
-                    os[(ks * F::OROWS + row) * F::OPITCH + ((ci * F::NB + j) * 32 + (lane & 31)) * KK + tap] = acc[i][j][v];
-            }
+            for (int j = 0; j < F::NB; ++j)
+                os[(ks * F::OROWS + row) * F::OPITCH + ((ci * F::NB + j) * 32 + (lane & 31)) * KK + tap] = acc[i][j][v];
         }
-        __syncthreads();
-        constexpr int PR = F::SC * KK / 4; // pieces of four floats in a row
+    }
+    __syncthreads();
+    constexpr int PR = F::SC * KK / 4; // pieces of four floats in a row
 #pragma unroll 4
-        for (int i = tid; i < F::OROWS * PR; i += NT) {
-            const int row = i / PR, col = (i - row * PR) * 4, rank = r0 + row;
-            if (rank < a.r && col < cols) {
-                f32x4_t v = *(const f32x4_t *)&os[row * F::OPITCH + col];
+    for (int i = tid; i < F::OROWS * PR; i += NT) {
+        const int rank = i / PR, col = (i - rank * PR) * 4;
+        if (rank < a.r && col < cols) {
+            f32x4_t v = *(const f32x4_t *)&os[rank * F::OPITCH + col];
 #pragma unroll
-                for (int w = 1; w < F::KS; ++w) v += *(const f32x4_t *)&os[(w * F::OROWS + row) * F::OPITCH + col];
-                *(f32x4_t *)&part[rank * p.C * KK + c0 * KK + col] = v;
-                if (KK == 9) odd = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, fmaf(v[3], 0.f, odd))));
-            }
+            for (int w = 1; w < F::KS; ++w) v += *(const f32x4_t *)&os[(w * F::OROWS + rank) * F::OPITCH + col];
+            *(f32x4_t *)&part[rank * p.C * KK + c0 * KK + col] = v;
+            if (KK == 9) odd = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, fmaf(v[3], 0.f, odd))));
         }
     }
     if constexpr (KK == 9) {

@@ -67,10 +67,6 @@ __device__ __forceinline__ void stg16(void *p, uint4 v)
     *(u32x4_any *)p = w;
 }
 
-// What is made of a loaded piece is made after this place (otherwise the compiler converts it as soon as it can, where it has to wait).
-__device__ __forceinline__ void use_here(uint4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
-__device__ __forceinline__ void use_here(uint2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
-
 // An array of less than 2^31 bytes seen through a buffer descriptor: a load from beyond its end (BUF_OUT always is) gives zeros, a store
 // there is dropped.  So neither needs a branch, and the compiler can count what is in flight: after a load under a condition it waits for
 // everything that was issued since.
@@ -83,12 +79,6 @@ struct BufSrc {
         typedef unsigned int v4 __attribute__((ext_vector_type(4)));
         const v4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)at, 0, 0);
         return make_uint4(v.x, v.y, v.z, v.w);
-    }
-    __device__ __forceinline__ uint2 load8(uint32_t at) const
-    {
-        typedef unsigned int v2 __attribute__((ext_vector_type(2)));
-        const v2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)at, 0, 0);
-        return make_uint2(v.x, v.y);
     }
     __device__ __forceinline__ void store(uint32_t at, uint4 u) const
     {
