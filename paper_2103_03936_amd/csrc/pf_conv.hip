@@ -382,11 +382,12 @@ static void plan_conv_px(const ConvGeom &g, ConvPlan &p)
         if (p.chain) {
             takes = 0.92 * t + 0.852 * pieces < 0.95 * chain(CHAIN_EP);
             // Calls without an epilogue stay with the chain kernel where it is the faster one, us, chain / here: 128 images of 256 x 8 x 8, rank
-            // 64, 3 x 3 14.3 / 14.2; 94 of 512 -> 1024 21.3 / 24.9; one tap, rank 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5
+            // 64, 3 x 3 14.3 / 14.2, and 37.8 / 40.5 with the backward direction, replayed from a graph (its filters are kept beside: hence the wide
+            // margin); 94 of 512 -> 1024 21.3 / 24.9; one tap, rank 128, 134 of 256 -> 1024 18.0 / 20.8, but 28 of 512 -> 256 12.5 / 9.5
             // ... and where filters are to be kept for the pixel-major backward direction, if it pays the launch that re-orders them as well: 33
             // images of 512 x 5 x 9 -> 2048, rank 128, one tap 27.6 / 37.1
             const double here = 0.824 * t + 0.318 * pieces, there = chain(CHAIN_PLAIN);
-            p.plain_chain = here >= 0.92 * there;
+            p.plain_chain = here >= 0.86 * there;
             p.plain_chain_kept = here >= there + 4;
         } else {
             const PxCorrection &c = PX_FWD_COR[g.s > 1][f32];
