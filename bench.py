@@ -115,10 +115,11 @@ class ConvWorkload:
             add("conv_dVp=dY*Tt", f2, s * (npix * Co + npix * r) + 4 * Co * r)
             add("conv_dX=Ukt*dT", f1, s * (r * K + npix * C) + 4 * npix * r)
             add("conv_dUk=dT*Xcolt", f1, s * npix * C + 4 * (npix * r + r * K))
-            # fused small-image path
-            add("conv_fwd_fused", f1 + f2, s * (npix * C + r * K + Co * r + npix * Co + npix * r))
-            add("conv_bwd_data_fused", f1 + f2, s * (npix * Co + r * K + Co * r + npix * C + npix * r))
-            add("conv_wgrad_pair", f1 + f2, s * (npix * C + npix * Co + 2 * npix * r) + 4 * (r * K + Co * r))
+            # fused small-image path, pixel-major kernels
+            for fwd, bwd, grads in (("conv_fwd_fused", "conv_bwd_data_fused", "conv_wgrad_pair"), ("conv_fwd_px", "conv_bwd_px", "conv_wgrad_px")):
+                add(fwd, f1 + f2, s * (npix * C + r * K + Co * r + npix * Co + npix * r))
+                add(bwd, f1 + f2, s * (npix * Co + r * K + Co * r + npix * C + npix * r))
+                add(grads, f1 + f2, s * (npix * C + npix * Co + 2 * npix * r) + 4 * (r * K + Co * r))
         return out
 
     def algorithmic_bytes(self):
@@ -239,7 +240,7 @@ class LinearWorkload:
             e[1] += nbytes
             e[2] += 1
 
-        for i, o, r in self.layers.values():
+        for name, (i, o, r) in self.layers.items():
             add("linear_T=X*V", 2.0 * M * r * i, s * (M * i + i * r + M * r))
             add("linear_Y=T*Ut", 2.0 * M * r * o, s * (M * r + o * r + M * o))
             add("linear_dT=dY*U", 2.0 * M * r * o, s * (M * o + o * r) + 4 * M * r)
@@ -256,10 +257,16 @@ class LinearWorkload:
             add("linear_fwd_fused", 2.0 * M * r * (i + o), s * (M * i + M * o + M * r + r * (i + o)))
             add("linear_bwd_data_fused", 2.0 * M * r * (i + o), s * (M * o + M * i + M * r + r * (i + o)))
             add("linear_wgrad_pair", 2.0 * M * r * (i + o), s * (M * i + M * o + 2 * M * r) + 4 * r * (i + o))
+            # both stages in one launch, both factor gradients in another: layers with an input of their own
+            if name not in self.shared:
+                add("linear_fwd_two", 2.0 * M * r * (i + o), s * (M * i + M * o + M * r + r * (i + o)))
+                add("linear_bwd_data_two", 2.0 * M * r * (i + o), s * (M * o + M * i + M * r + r * (i + o)))
+                add("linear_grads", 2.0 * M * r * (i + o), s * (M * i + M * o + 2 * M * r) + 4 * r * (i + o))
         if self.shared:  # one launch for all the projections of the shared input: X moves once
             i, o, r = self.layers[self.shared[0]]
             G = len(self.shared)
-            add("linear_shared_fwd_fused", 2.0 * G * M * r * (i + o), s * (M * i + G * (M * o + M * r + r * (i + o))))
+            for name in ("linear_shared_fwd_fused", "linear_shared_fwd_two"):
+                add(name, 2.0 * G * M * r * (i + o), s * (M * i + G * (M * o + M * r + r * (i + o))))
         return out
 
     def algorithmic_bytes(self):
