@@ -379,7 +379,7 @@ bool px_fits(int N, int C, int H, int W, int Cout, int r, int k, int stride, int
     if ((k != 1 && k != 3) || stride < 1 || pad != k / 2 || Ho != (H - 1) / stride + 1 || Wo != (W - 1) / stride + 1) return false;
     if (N < 1 || Ho * Wo < V || C % V || Cout % V || r > 16 * V || (i64)Cout * r < V) return false;
     const i64 px = (i64)N * H * W, lim = (1LL << 31) / (i64)sizeof(T); // 32-bit byte offsets
-    return px * C < lim && px * Cout < lim && px * (r + V) < lim && (i64)r * C * k * k < lim && (i64)Cout * r < lim;
+    return px * C < lim && px * Cout < lim && px * (r + V) < lim && (i64)px_pack_elems(C, r, k) < lim && (i64)Cout * r < lim;
 }
 template bool px_fits<uint16_t>(int, int, int, int, int, int, int, int, int, int, int);
 template bool px_fits<float>(int, int, int, int, int, int, int, int, int, int, int);

@@ -26,6 +26,12 @@ static int fits(int N, int H, int W, int k, int st, int P)
 }
 extern "C" int emu_fits(int f32, int N, int H, int W, int k, int st, int P) { return f32 ? fits<float>(N, H, W, k, st, P) : fits<uint16_t>(N, H, W, k, st, P); }
 
+// shapes that the kernels take
+extern "C" int emu_takes(int f32, int N, int C, int H, int W, int Cout, int r, int k)
+{
+    return f32 ? px_fits<float>(N, C, H, W, Cout, r, k, 1, k / 2, H, W) : px_fits<uint16_t>(N, C, H, W, Cout, r, k, 1, k / 2, H, W);
+}
+
 // the groups of both filter gradients, and by every number of tiles per group
 template <typename T>
 static void plan(int npx, int r, int C1, int k, int C2, int *out)

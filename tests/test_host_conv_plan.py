@@ -65,6 +65,16 @@ def test_tiles_that_fit(emu):
     assert refused <= asked // 1000, (refused, asked)
 
 
+def test_arrays_within_32_bit_offsets(emu):
+    """Every array that the kernels index is below 2^31 bytes, the re-ordered thin filters (ranks padded to 32) with it."""
+    for f32, el in ((0, 2), (1, 4)):
+        for k in (1, 3):
+            most = (1 << 31) // (k * k * 32 * el) // 8 * 8  # channels whose filters fill that
+            assert emu.emu_takes(f32, 1, most - 8, 2, 4, 8, 1, k) == 1
+            for C in (most, most + 8):
+                assert emu.emu_takes(f32, 1, C, 2, 4, 8, 1, k) == (k * k * C * 32 * el < 1 << 31), (f32, k, C)
+
+
 def test_groups_of_the_filter_gradients(emu):
     """The bounded search finds what the search over every number of tiles does."""
     rng = random.Random(2)
