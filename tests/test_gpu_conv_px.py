@@ -219,6 +219,39 @@ def test_saved_filters_stay_in_their_buffer(dtype, shape):
     assert all(torch.equal(x, y) for x, y in zip(one, other))
 
 
+@pytest.mark.parametrize("dtype, shape", [(torch.float32, (88, 64, 13, 10, 64, 16, 1)), (torch.bfloat16, (12, 128, 16, 16, 128, 32, 3)),
+                                          (torch.bfloat16, (30, 96, 9, 11, 128, 20, 1))])
+def test_gradients_are_added(dtype, shape):
+    """The public backward call with batch norm adds to what a flat buffer holds at an odd element, on these kernels, and to nothing else."""
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, r, k = shape
+    g = torch.Generator(device="cuda").manual_seed(15)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    b = lambda *s: n(*s).to(dtype)
+    X, Uk, Vp, dZ = b(N, C, H, W), b(r, C, k, k) * (C * k * k) ** -0.5, b(Cout, r) * r ** -0.5, b(N, Cout, H, W)
+    scale = torch.rand(Cout, generator=g, device="cuda") + 0.5
+    Y, T, kept = pf.pf_lowrank_conv_fwd_ep(X, Uk, Vp, scale, pad=k // 2, save_W=True)
+    plain = pf.pf_lowrank_conv_bwd_ep(X, Uk, Vp, scale, dZ, T_saved=T, pad=k // 2, W_saved=kept)
+    shapes, flat = ((r, C, k, k), (Cout, r), (Cout,)), n(1 + r * C * k * k + Cout * r + Cout + 3)
+    held, at, out = flat.clone(), 1, []
+    for s in shapes:
+        size = torch.Size(s).numel()
+        out.append(flat[at:at + size].view(s))
+        at += size
+    pf.timing_reset()
+    pf.timing_enable(True)
+    dX = pf.pf_lowrank_conv_bwd_ep(X, Uk, Vp, scale, dZ, T_saved=T, pad=k // 2, W_saved=kept, grads=tuple(out))[0]
+    pf.timing_enable(False)
+    assert {"conv_bwd_px", "conv_wgrad_px", "split_sums"} == set(pf.timing_collect())
+    assert torch.equal(dX, plain[0]) and flat[0] == held[0] and torch.equal(flat[-3:], held[-3:])
+    at = 1
+    for o, p in zip(out, plain[1:]):
+        was = held[at:at + p.numel()].view(p.shape)
+        at += p.numel()
+        assert torch.equal(o, was + p) or float((o - was - p).abs().max()) <= 2 ** -22 * float((was.abs() + p.abs()).max())  # (one addition)
+    _close(plain[3], dZ.double().sum((0, 2, 3)), 1e-5, "dshift")
+
+
 @pytest.mark.parametrize("shape", [(2, 256, 4, 12, 256, 64, 3), (3, 256, 6, 10, 512, 128, 1)])
 def test_batch_norm_in_the_backward_kernels(shape):
     """Planes that the chain kernel takes forward and not the gradients of its filters: the pixel-major kernels fold the scale in and form the

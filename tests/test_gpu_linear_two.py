@@ -90,10 +90,11 @@ def test_gradients(two, M, cols, r):
             assert float((got - ref).norm() / ref.norm()) <= M ** 0.5 * 2 ** -23, per
 
 
-@pytest.mark.parametrize("shape", [(5000, 384, 640, 96), (6001, 1032, 264, 64), (8192, 512, 512, 128)])
+@pytest.mark.parametrize("shape", [(5000, 1536, 384, 96), (6001, 1032, 264, 64), (8192, 512, 512, 128)])
 def test_backward(shape):
     """The public call where it takes both kernels (more rows than the oracle's tests have): T kept or not, mask and skip gradient."""
     import paper_2103_03936_amd as pf
+    got = None
     M, K, N, r = shape
     g = torch.Generator(device="cuda").manual_seed(6)
     n = lambda *s: torch.randn(*s, generator=g, device="cuda")
@@ -105,9 +106,53 @@ def test_backward(shape):
     for a, relu, kept in ((None, False, True), (add, False, False), (None, True, True), (add, True, True)):
         want = dX + (0 if a is None else a.float())
         want = torch.where(X.float() > 0, want, torch.zeros_like(want)) if relu else want
-        got = pf.pf_lowrank_linear_bwd_ep(X, V, U, dY, T_saved=T if kept else None, dX_add=a, x_is_relu=relu, has_bias=True)
+
+        def call():
+            nonlocal got
+            got = pf.pf_lowrank_linear_bwd_ep(X, V, U, dY, T_saved=T if kept else None, dX_add=a, x_is_relu=relu, has_bias=True)
+
+        assert {"linear_bwd_data_two", "linear_grads"} <= _launches(pf, call)
         for x, ref in zip(got, (want,) + grads):  # (a share of 2^-8 per rounding to bf16; dT and T may round either way here)
             assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
+
+
+@pytest.mark.parametrize("wanted", [(1, 1, 1), (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 0, 1), (0, 1, 1), (0, 0, 0)])
+def test_backward_in_parts(wanted):
+    """Gradients that are wanted, added to what a flat buffer holds at an odd element, dX beside them; the others are not formed and the
+    buffer's other elements stay as they are.  Bounds as above."""
+    import paper_2103_03936_amd as pf
+    M, K, N, r = 6001, 1032, 264, 64
+    g = torch.Generator(device="cuda").manual_seed(7)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, V, U, dY = n(M, K).bfloat16(), (n(K, r) * K ** -0.5).bfloat16(), (n(N, r) * r ** -0.5).bfloat16(), n(M, N).bfloat16()
+    T = (X.float() @ V.float()).bfloat16()
+    dT = (dY.float() @ U.float()).bfloat16().float()
+    want = [dT @ V.float().t().contiguous(), dY.float().t() @ T.float(), X.float().t() @ dT, dY.float().sum(0)]
+    shapes, flat = ((N, r), (K, r), (N,)), n(1 + N * r + K * r + N + 3) * 30
+    held, at, out = flat.clone(), 1, []
+    for s in shapes:
+        size = torch.Size(s).numel()
+        out.append(flat[at:at + size].view(s))
+        at += size
+    grads = tuple(o if w else None for o, w in zip(out, wanted))
+    got = None
+
+    def call():
+        nonlocal got
+        got = pf.pf_lowrank_linear_bwd(X, V, U, dY, T_saved=T, has_bias=True, grads=grads)
+
+    names = _launches(pf, call)
+    assert ("linear_bwd_data_two" in names) and ("linear_grads" in names) == any(wanted)
+    assert float((got[0].double() - want[0].double()).norm() / want[0].double().norm()) <= 4e-3
+    before, at = held[1:], 0
+    for o, w, ref in zip(out, wanted, want[1:]):
+        was = before[at:at + ref.numel()].view(ref.shape)
+        at += ref.numel()
+        if w:
+            assert float((o.double() - was.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
+        else:
+            assert torch.equal(o, was)
+    assert flat[0] == held[0] and torch.equal(flat[-3:], held[-3:])
 
 
 def _launches(pf, call):
