@@ -390,7 +390,7 @@ template bool px_fits<float>(int, int, int, int, int, int, int, int, int, int, i
 // on a multiple of `step`, and inside a plane on the column alone (with stride, on the row within V as well), so the first rows and
 // the end of a plane stand for all.  A plan takes 1 to 3 us so, where trying every tile took 42 (16 x 16 pixels) to 7700 (225 x 225).
 template <int S>
-static bool px_tiles_fit(const PxPlane<S> &g, const PxPlane<S> &o, int stride, int P, int slots, int groups)
+static bool px_tiles_fit(const PxPlane<S> &g, const PxPlane<S> &o, int stride, int P, int slots, int groups, bool loose = false)
 {
     constexpr int V = 1 << S;
     const auto gcd_with = [](int p, int n) { return n % p ? n & -n : p; }; // of a power of two and n
@@ -403,7 +403,7 @@ static bool px_tiles_fit(const PxPlane<S> &g, const PxPlane<S> &o, int stride, i
         if (all + g.h * (rows + planes * g.Wp + 2 * (g.Wp + 1)) <= slots && most <= groups) return true;
     }
     const auto fits = [&](i64 p0) {
-        const PxTile t = px_tile(g, o, stride, (int)p0, P);
+        const PxTile t = px_tile(g, o, stride, (int)p0, P, loose);
         return t.slots <= slots && px_groups(g, t) <= groups;
     };
     const i64 period = (i64)step * (o.W / gcd_with(step, o.W)) * (stride > 1 ? V : 1); // of the column (and the row within V)
@@ -432,7 +432,7 @@ bool px_tile_fits(const PxPlane<S> &g, const PxPlane<S> &o, int stride, int P)
 template bool px_tile_fits(const PxPlane<3> &, const PxPlane<3> &, int, int);
 template bool px_tile_fits(const PxPlane<2> &, const PxPlane<2> &, int, int);
 template <int S>
-bool px_wgrad_fits(const PxPlane<S> &g) { return px_tiles_fit(g, g, 1, 128, 1 << 30, (PX_WG_ROWS - 8) >> S); }
+bool px_wgrad_fits(const PxPlane<S> &g) { return px_tiles_fit(g, g, 1, 128, 1 << 30, (PX_WG_ROWS - 8) >> S, true); }
 template bool px_wgrad_fits(const PxPlane<3> &);
 template bool px_wgrad_fits(const PxPlane<2> &);
 

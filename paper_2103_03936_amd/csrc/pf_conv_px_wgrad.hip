@@ -63,13 +63,15 @@ __device__ __forceinline__ void px_wgrad_f32(const unsigned char *as, const unsi
 
 // Nine taps, channels whose X is infinite or NaN in a pixel at the edge of its plane: there a tap that reaches out of the plane multiplied
 // it by the row of zeros, which is NaN for a term that does not exist.  Their gradients again, the terms that exist and no others, in runs of
-// 128 pixels with sums of their own.  Such a value leaves none of its channel's sums finite, so the check costs a comparison of what is
-// stored (nothing to be seen in 40 us of both gradients); what it starts takes milliseconds at worst and is for values that no healthy step has.
+// 128 pixels with sums of their own.  Such a value leaves none of its channel's sums finite, with any rank through any tap, so one sum of
+// each channel is looked at (a check of all as they leave, and a barrier for it, took 0.4 of 22.5 us); what it starts takes milliseconds at
+// worst and is for values that no healthy step has.
 template <typename T, int SC>
 __device__ __forceinline__ void px_wgrad_edges(const PxWgradArgs<T> &a, const PxGrad<T> &p, int c0, int begin, int end, float *part, uint32_t *flag)
 {
     const PxPlaneOf<T> &g = a.gk;
     const int n = min(SC, p.C - c0), tid = threadIdx.x, NT = blockDim.x;
+    __syncthreads(); // (what `flag` lies on has been read, and what is written again has been stored)
     for (int c = tid; c < n; c += NT) flag[c] = 0;
     __syncthreads();
     for (int i = tid; i < (end - begin) * n; i += NT) {
@@ -119,7 +121,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
         for (int e = 0; e < V; ++e) at[u][e] = (isa ? (o >> 3) * F::APANEL : F::ABYTES + (o >> 3) * F::BPANEL) + px_at(gi * V + e, o & 7);
     }
     const auto fetch = [&](int tile) __attribute__((always_inline)) {
-        const PxTile ta = px_tile(gt, tile * F::P, F::P), tb = px_tile(g1, tile * F::P, F::P);
+        const PxTile ta = px_tile(gt, tile * F::P, F::P, true), tb = px_tile(g1, tile * F::P, F::P, true);
 #pragma unroll
         for (int u = 0; u < F::BLOCKS; ++u) {
             const int i = tid + NT * u;
@@ -153,7 +155,7 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
     };
     // rows of dT for pixels 8 j + e and 8 j + e + 4 of the tile and every tap
     const auto table = [&](int tile, unsigned char *buf) __attribute__((always_inline)) {
-        const PxTile t = px_tile(gt, tile * F::P, F::P);
+        const PxTile t = px_tile(gt, tile * F::P, F::P, true);
         if (tid < 64 * 6) {
             const int j = tid / 6, dy = 1 - tid % 6 / 2, half = tid & 1, p = t.p0 + (j >> 2) * 8 + (j & 3) + 4 * half;
             const int n = px_div(p, gt.HW, gt.mHW), q = p - n * gt.HW, y = px_div(q, gt.W, gt.mW), x = q - y * gt.W;
@@ -270,7 +272,6 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
     float *os = (float *)smem;
     float *part = p.part + (i64)group * a.r * p.C * KK;
     const int cols = min(F::SC, p.C - c0) * KK;
-    float odd = 0.f; // (NaN once something is not finite)
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < F::NA; ++i) {
@@ -284,6 +285,12 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
                 os[(ks * F::OROWS + row) * F::OPITCH + ((ci * F::NB + j) * 32 + (lane & 31)) * KK + tap] = acc[i][j][v];
         }
     }
+    if (KK == 9 && mi == 0) { // (a channel's sums with the first rank tell)
+        float odd = 0.f;
+#pragma unroll
+        for (int j = 0; j < F::NB; ++j) odd = fmaf(acc[0][j][0], 0.f, odd);
+        if (lane < 32 && odd != 0.f) *(uint32_t *)(smem + F::BYTES) = 1;
+    }
     __syncthreads();
     constexpr int PR = F::SC * KK / 4; // pieces of four floats in a row
 #pragma unroll 4
@@ -294,14 +301,10 @@ __device__ __forceinline__ void px_wgrad(const PxWgradArgs<T> &a, const PxGrad<T
 #pragma unroll
             for (int w = 1; w < F::KS; ++w) v += *(const f32x4_t *)&os[(w * F::OROWS + rank) * F::OPITCH + col];
             *(f32x4_t *)&part[rank * p.C * KK + c0 * KK + col] = v;
-            if (KK == 9) odd = fmaf(v[0], 0.f, fmaf(v[1], 0.f, fmaf(v[2], 0.f, fmaf(v[3], 0.f, odd))));
         }
     }
     if constexpr (KK == 9) {
-        uint32_t *flag = (uint32_t *)(smem + F::BYTES);
-        if (odd != 0.f) *flag = 1;
-        __syncthreads();
-        if (*flag) px_wgrad_edges<T, F::SC>(a, p, c0, t0 * F::P, min(t1 * F::P, g1.N * g1.HW), part, (uint32_t *)smem);
+        if (*(const uint32_t *)(smem + F::BYTES)) px_wgrad_edges<T, F::SC>(a, p, c0, t0 * F::P, min(t1 * F::P, g1.N * g1.HW), part, (uint32_t *)smem);
     }
     if (KK == 1 && p.sums) {
 #pragma unroll

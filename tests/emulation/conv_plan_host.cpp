@@ -5,10 +5,10 @@ using namespace pf;
 
 // every tile
 template <typename T>
-static bool fit_all(const PxPlaneOf<T> &g, const PxPlaneOf<T> &o, int st, int P, int slots, int groups)
+static bool fit_all(const PxPlaneOf<T> &g, const PxPlaneOf<T> &o, int st, int P, int slots, int groups, bool loose = false)
 {
     for (i64 i = 0; i < ((i64)o.N * o.HW + P - 1) / P && i < o.HW; ++i) {
-        const PxTile t = px_tile(g, o, st, (int)(i * P), P);
+        const PxTile t = px_tile(g, o, st, (int)(i * P), P, loose);
         if (t.slots > slots || px_groups(g, t) > groups) return false;
     }
     return true;
@@ -21,7 +21,7 @@ static int fits(int N, int H, int W, int k, int st, int P)
     const PxPlaneOf<T> g = px_plane<S>(N, H, W, k), o = px_plane<S>(N, (H - 1) / st + 1, (W - 1) / st + 1, 1);
     const int rows = P == 128 || st > 1 ? 256 : P == 64 ? 192 : 160, groups = (P == 32 && st == 1 ? 128 : 256) / V;
     int r = px_tile_fits(g, o, st, P) | fit_all<T>(g, o, st, P, rows - 1, groups) << 1;
-    if (st == 1 && P == 128) r |= px_wgrad_fits(g) << 2 | fit_all<T>(g, g, 1, P, 1 << 30, (PX_WG_ROWS - 8) >> S) << 3;
+    if (st == 1 && P == 128) r |= px_wgrad_fits(g) << 2 | fit_all<T>(g, g, 1, P, 1 << 30, (PX_WG_ROWS - 8) >> S, true) << 3;
     return r;
 }
 extern "C" int emu_fits(int f32, int N, int H, int W, int k, int st, int P) { return f32 ? fits<float>(N, H, W, k, st, P) : fits<uint16_t>(N, H, W, k, st, P); }

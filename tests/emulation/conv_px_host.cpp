@@ -47,10 +47,17 @@ static int tiles(int N, int H, int W, int k, int st, int P, int rows, int groups
             if (st == 1 && (s < 0 || s >= t.slots)) return 14;
             if (s >= 0 && s < t.slots && holds[s] != p) return 15;
         }
-        // the same pixels in rows of V per group
-        for (int p = t.pa; st == 1 && p < t.pb; ++p) {
-            const int im = p / g.HW, row = px_linear(g, t, im, p % g.HW);
-            if (row < 0 || !px_group(g, t, row / V, n, q) || n != im || q + row % V != p % g.HW) return 12;
+        // the same pixels, and one more at either end for kernels without slots, in rows of V per group
+        for (int loose = 0; st == 1 && loose < 2; ++loose) {
+            const PxTile l = px_tile(g, p0, P, loose);
+            if (l.pa > t.pa || l.pa < t.pa - g.h || l.pb < t.pb || l.pb > t.pb + g.h) return 16;
+            int count = 0;
+            while (px_group(g, l, count, n, q)) ++count;
+            if (count != px_groups(g, l)) return 13;
+            for (int p = l.pa; p < l.pb; ++p) {
+                const int im = p / g.HW, row = px_linear(g, l, im, p % g.HW);
+                if (row < 0 || !px_group(g, l, row / V, n, q) || n != im || q + row % V != p % g.HW) return 12;
+            }
         }
         // every pixel leaves once, whole groups within their plane
         std::vector<int> left(t.p1 - t.p0, 0);
