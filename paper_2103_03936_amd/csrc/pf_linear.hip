@@ -132,6 +132,7 @@ int linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, cons
 struct LinearTiles {
     bool ok;               // every dimension holds a 16-byte piece
     TilePlan T, dT, Y;     // tile shapes and splits of the intermediates and the output
+    bool T_sliced, dT_sliced; // their readers take the partial sums (float) and add them up
     TileGroup grads;       // dX, dU and dV in one launch
     size_t n_mid, n_part_T, n_part_g, fwd_bytes, bwd_bytes; // elements of T, partial sums (floats)
 };
@@ -142,11 +143,14 @@ static LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
     p.ok = d->M > 0 && d->in >= piece && d->out >= piece && d->r >= piece && (G == 1 || d->r % piece == 0);
     if (!p.ok) return p;
     const i64 M = d->M, in = d->in, out = d->out, r = d->r;
-    p.T = plan_tiles(d->dtype, M, G * r, in, 16);
     p.Y = plan_tiles(d->dtype, M, G * out, r, 1);
-    p.dT = plan_tiles(d->dtype, M, G * r, out, 16);
     const TileNeed need[3] = {{M, in, G * r, false}, {G * out, r, M, true, true}, {in, G * r, M, true, true}};
     p.grads = plan_tile_group(d->dtype, need, 3);
+    const i64 rows = (M + 31) / 32 * 32, ins = (in + 31) / 32, outs = (G * out + 31) / 32; // (floats of T that the tiles of Y, dX and dV read)
+    const MidPlan T = plan_mid(d->dtype, M, G * r, in, 16, p.Y.shape, 4 * outs * rows * r, 128 * r);
+    const MidPlan dT = plan_mid(d->dtype, M, G * r, out, 16, p.grads.shape, 8 * ins * rows * G * r, 128 * (M > G * r ? M : G * r));
+    p.T = T.t, p.T_sliced = T.sliced;
+    p.dT = dT.t, p.dT_sliced = dT.sliced;
     const int ks = p.T.ksplit > p.dT.ksplit ? p.T.ksplit : p.dT.ksplit;
     p.n_mid = (size_t)(G * M * r);
     p.n_part_T = ks > 1 ? (size_t)(ks * G * M * r) : 0;
@@ -154,6 +158,11 @@ static LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
     const size_t el = d->dtype == PF_BF16 ? 2 : 4;
     p.fwd_bytes = align_up(p.n_mid * el) + align_up(p.n_part_T * 4);
     p.bwd_bytes = 2 * align_up(p.n_mid * el) + align_up((p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g) * 4);
+    if (p.dT_sliced) { // (not where these partial sums would make a call outgrow the library's own scratch)
+        const size_t bwd = p.bwd_bytes + align_up(p.n_part_T * 4);
+        if (bwd > PF_STATIC_SCRATCH_BYTES) p.dT_sliced = false;
+        else p.bwd_bytes = bwd;
+    }
     return p;
 }
 
@@ -172,10 +181,10 @@ struct LinearPlan {
     int two_bwd, two_bwd_split; // the same for dT and dX; the factor gradients are then those of pf_linear_grad.h
     LinGradPlan lg;
     size_t n_lg; // their partial sums, floats
-    bool skinny;           // fp32 with at most 128 rows: the weight-streaming kernels of the LSTM cell
+    bool skinny_fwd, skinny_bwd; // fp32, few rows and large factors: the weight-streaming kernels of the LSTM cell
     size_t n_part_sk;      // their slice sums, floats
     LinearTiles t;         // the tiled products of pf_tile.h
-    bool small;            // fp32 with at most 128 rows and dimensions in whole tiles: two launches per direction
+    bool small_fwd, small_bwd; // fp32 with at most 128 rows and dimensions in whole tiles: two launches per direction
     size_t n_small;        // slices of the rank-r intermediate(s) between them, floats
 };
 
@@ -285,6 +294,19 @@ static int two_bwd_rows(i64 M, i64 in, i64 out, i64 r, int &split)
     return now < 0.95 * before ? rows : 0;
 }
 
+// Few rows in float: the streaming kernels read a factor at 8 rows at a time and take four or five launches a direction, the tiled products
+// two (their readers add the slices of T and dT) and pad to 32 rows.  Calls of 1 to 24 rows, us, streaming / tiled: forward 2048 -> 512 ->
+// 2048 15.7 / 15.0 at one row, 4000 -> 500 -> 4000 17.2 / 16.8, but 2000 -> 1000 -> 2000 16.8 / 20.0, at 8 rows 18.5 / 20.1, at 16 20.5 /
+// 20.2 (odd ranks cost the tiles unaligned pieces: 3712 -> 467 -> 1869 16.8 / 18.2 at one row); forward and backward 2048 -> 512 -> 2048 35.3 / 33.3, but 4096 -> 512 -> 2048 38.1 / 42.0, at 8 rows 40.7 / 42.9, at 16
+// 45.4 / 43.2; 4096 -> 2000 -> 4096 82.7 / 98.3 at 16 rows.  Smaller layers 448 -> 112 -> 768 29.3 / 22.5 at one row, 46.9 / 23.2 at 128.
+static void skinny_pays(const pf_linear_desc *d, bool &fwd, bool &bwd)
+{
+    const double weights = (double)d->r * (d->in + d->out);
+    const bool any = d->dtype == PF_F32 && d->M > 0 && d->M <= SK_MAX_ROWS && d->in >= 4 && d->out >= 4 && d->r >= 4;
+    fwd = any && weights >= 2.5e6 && ((d->M <= 8 && d->r >= 700) || (d->M <= 2 && d->r >= 450 && d->r % 4));
+    bwd = any && weights >= (d->M <= 2 ? 2.5e6 : 2.8e6) + (d->M > 8 ? 0.35e6 * (d->M - 8) : 0);
+}
+
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
 {
     LinearPlan p;
@@ -309,10 +331,9 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
         p.lg = plan_linear_grad(d->M, d->in, d->out, d->r);
         p.n_lg = (size_t)p.lg.splits * (d->r * (d->in + d->out) + d->out) + 128;
     }
-    p.skinny = d->dtype == PF_F32 && d->M > 0 && d->M <= 4 * SK_MAX_ROWS && d->in >= 4 && d->out >= 4 &&
-               d->r >= 4;
+    skinny_pays(d, p.skinny_fwd, p.skinny_bwd);
     p.n_part_sk = 0;
-    if (p.skinny) {
+    if (p.skinny_fwd || p.skinny_bwd) {
         SkinnyArgs a;
         const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
         const size_t n1 = skinny_rows(M, nullptr, in, nullptr, r, in, r, nullptr, a);   // T = X V
@@ -329,9 +350,13 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     p.t = make_linear_tiles(d, 1);
     if (p.t.fwd_bytes > p.fwd_bytes) p.fwd_bytes = p.t.fwd_bytes;
     if (p.t.bwd_bytes > p.bwd_bytes) p.bwd_bytes = p.t.bwd_bytes;
-    p.small = d->dtype == PF_F32 && linear_small_supported(d->M, d->in, d->out, d->r);
-    p.n_small = p.small ? (size_t)(LS_MAX_SLICES * d->M * d->r) : 0; // slices per intermediate
-    if (p.small) {
+    const bool small = d->dtype == PF_F32 && linear_small_supported(d->M, d->in, d->out, d->r);
+    // (wide layers are faster on the tiled products: 4096 -> 128 -> 4096 forward 17.3 / 15.5 us at 128 rows, 12.7 / 13.7 at one; forward and
+    // backward together 39.9 / 33.1 at 64 rows, 256 -> 64 -> 4096 28.4 / 25.7 at 128; 2048 -> 128 -> 512 21.4 / 23.9 at 64)
+    p.small_fwd = small && (d->M <= 64 || d->in + d->out <= 6144);
+    p.small_bwd = small && d->in + d->out <= 4096;
+    p.n_small = small ? (size_t)(LS_MAX_SLICES * d->M * d->r) : 0; // slices per intermediate
+    if (small) {
         const size_t one = align_up(p.n_small * sizeof(float));
         if (one > p.fwd_bytes) p.fwd_bytes = one;
         if (2 * one > p.bwd_bytes) p.bwd_bytes = 2 * one;
@@ -459,10 +484,11 @@ static int linear_bwd_generic(const pf_linear_desc *d, const T *X, const T *V, c
 
 // ---------------------------------------------------- any shape of at least a 16-byte piece
 // T = A B_g (A [M][K], B_g [K][r]) for G layers, in the call's element type: T_g at out + g * sout with leading dimension
-// ldo; through partial sums when the products have too few tiles for the chip.  A steps by sa from layer to layer.
+// ldo; through partial sums when the products have too few tiles for the chip (slices: how many, and they stay where they are,
+// [split][G][M][r] at part).  A steps by sa from layer to layer.
 template <typename T>
 static int tiles_mid(hipStream_t s, const char *name, const TilePlan &t, int G, int M, int r, int K, const T *A, i64 sa,
-                     const T *B, T *out, i64 ldo, i64 sout, float *part)
+                     const T *B, T *out, i64 ldo, i64 sout, float *part, int *slices = nullptr)
 {
     const int dt = sizeof(T) == 2 ? PF_BF16 : PF_F32;
     TileArgs a = {};
@@ -479,7 +505,8 @@ static int tiles_mid(hipStream_t s, const char *name, const TilePlan &t, int G, 
     }
     tile_add(a, t.shape, dt, p, t.ksplit);
     int st = launch_tiles_linear(s, name, dt, t.shape, a);
-    if (st != PF_OK || !split) return st;
+    if (slices) *slices = a.p[0].ksplit;
+    if (st != PF_OK || !split || (slices && *slices > 1)) return st;
     SplitSumArgs ss = {};
     const i64 n = (i64)G * M * r;
     split_sum_add(ss, SplitSum{part, (float *)out, n, n, a.p[0].ksplit, 0, nullptr, 0, sizeof(T) == 2});
@@ -495,10 +522,12 @@ static int linear_fwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G
     T *Tws = ws.take<T>(p.n_mid);
     float *part = ws.take<float>(p.n_part_T);
     T *Tt = T_save ? T_save : Tws;
-    int st = tiles_mid<T>(s, "linear_T=X*V", p.T, G, M, r, in, X, 0, V, Tt, r, (i64)M * r, part);
+    int slices = 1;
+    int st = tiles_mid<T>(s, "linear_T=X*V", p.T, G, M, r, in, X, 0, V, Tt, r, (i64)M * r, part, p.T_sliced ? &slices : nullptr);
     if (st != PF_OK) return st;
     TileArgs a = {};
     TileProb q = tile_prob(TILE_NT, M, out, r, Tt, r, U, r, Y, out);
+    if (slices > 1) q.A = part, q.aslices = slices, q.sstride = (i64)G * M * r, q.acopy = T_save;
     q.nb = G;
     q.sa = (i64)M * r;
     q.sb = (i64)out * r;
@@ -522,8 +551,9 @@ static int linear_bwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G
 {
     const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
     T *Tws = ws.take<T>(p.n_mid), *dT = ws.take<T>(p.n_mid);
+    float *mid = p.dT_sliced ? ws.take<float>(p.n_part_T) : nullptr; // (partial sums of dT that the gradients' launch reads)
     float *part = ws.take<float>(p.n_part_T > p.n_part_g ? p.n_part_T : p.n_part_g);
-    int st = PF_OK;
+    int st = PF_OK, slices = 1;
     if (dU && !T_saved) {
         st = tiles_mid<T>(s, "linear_T=X*V", p.T, G, M, r, in, X, 0, V, Tws, r, (i64)M * r, part);
         if (st != PF_OK) return st;
@@ -532,7 +562,7 @@ static int linear_bwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G
     const bool side = G > 1 && p.dT.ksplit == 1;
     const i64 ldd = side ? (i64)G * r : r, sd = side ? r : (i64)M * r;
     if (dX || dV) {
-        st = tiles_mid<T>(s, "linear_dT=dY*U", p.dT, G, M, r, out, dY, (i64)M * out, U, dT, ldd, sd, part);
+        st = tiles_mid<T>(s, "linear_dT=dY*U", p.dT, G, M, r, out, dY, (i64)M * out, U, dT, ldd, sd, mid ? mid : part, mid ? &slices : nullptr);
         if (st != PF_OK) return st;
     }
     const TileShape sh = p.grads.shape;
@@ -541,6 +571,7 @@ static int linear_bwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G
     SplitSumArgs ss = {};
     if (dX) {
         TileProb q = tile_prob(TILE_NT, M, in, G * r, dT, side ? ldd : r, V, r, dX, in);
+        if (slices > 1) q.A = mid, q.aslices = slices, q.sstride = (i64)G * M * r;
         if (G > 1) {
             q.bseg = r;
             q.bjump = (i64)in * r;
@@ -556,6 +587,7 @@ static int linear_bwd_tiles(const pf_linear_desc *d, const LinearTiles &p, int G
     }
     const auto grad = [&](const T *A, i64 sa, int m, const T *B, i64 ldb, i64 sb, float *dst, int ks, float *sums) {
         TileProb q = tile_prob(TILE_TN, m, r, M, A, m, B, ldb, dst, r);
+        if (slices > 1 && B == dT) q.B = mid, q.bslices = slices, q.sstride = (i64)G * M * r;
         q.nb = G;
         q.sa = sa;
         q.sb = sb;
@@ -1013,10 +1045,10 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (d->M == 0) return PF_OK;
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    if (d->dtype == PF_F32 && p.small)
+    if (d->dtype == PF_F32 && p.small_fwd)
         return linear_fwd_small(d, p, (const float *)X, (const float *)V, (const float *)U,
                                 (const float *)bias, (float *)Y, (float *)T_save, ws, s);
-    if (d->dtype == PF_F32 && p.skinny)
+    if (d->dtype == PF_F32 && p.skinny_fwd)
         return linear_fwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)bias, (float *)Y, (float *)T_save, ws, s);
     if (d->dtype == PF_F32 && p.t.ok)
@@ -1060,11 +1092,11 @@ int pf::linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
     hipStream_t s = (hipStream_t)stream;
-    if (d->dtype == PF_F32 && p.small)
+    if (d->dtype == PF_F32 && p.small_bwd)
         return linear_bwd_small(d, p, (const float *)X, (const float *)V, (const float *)U,
                                 (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                 (float *)dbias, accumulate, ws, s);
-    if (d->dtype == PF_F32 && p.skinny)
+    if (d->dtype == PF_F32 && p.skinny_bwd)
         return linear_bwd_skinny(d, p, (const float *)X, (const float *)V, (const float *)U,
                                  (const float *)dY, (const float *)T_saved, (float *)dX, (float *)dU, (float *)dV,
                                  (float *)dbias, accumulate, ws, s);

@@ -297,6 +297,127 @@ struct LoadMC {
     }
 };
 
+// An operand that comes as up to TILE_MAX_SLICES partial sums in float, `stride` floats apart: the launch that formed them split its
+// contraction, and the sum is taken on the way to LDS, in order, instead of by a launch of its own (3 to 4 us where the products
+// themselves take 4 to 9).  All slices of a piece are requested together; one past the last re-reads the last and counts zero times.
+constexpr int TILE_MAX_SLICES = 4;
+template <typename CT>
+struct SlicePiece {
+    static constexpr int V = TileEl<CT>::V, W = V / 4, CH = TILE_MAX_SLICES * W; // 16-byte loads of a piece
+    static __device__ __forceinline__ void load(const float *p, int slices, i64 stride, uint4 *r)
+    {
+#pragma unroll
+        for (int s = 0; s < TILE_MAX_SLICES; ++s)
+#pragma unroll
+            for (int w = 0; w < W; ++w) r[s * W + w] = ldg16(p + min(s, slices - 1) * stride + 4 * w);
+    }
+    static __device__ __forceinline__ uint4 sum(const uint4 *r, int slices)
+    {
+        float v[V];
+#pragma unroll
+        for (int w = 0; w < W; ++w) piece_floats<float>(r[w], v + 4 * w);
+#pragma unroll
+        for (int s = 1; s < TILE_MAX_SLICES; ++s) {
+            float t[V];
+#pragma unroll
+            for (int w = 0; w < W; ++w) piece_floats<float>(r[s * W + w], t + 4 * w);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = s < slices ? v[e] + t[e] : v[e];
+        }
+        return floats_piece<CT>(v);
+    }
+};
+
+// LoadKC of such an operand; copy (nullable): the sums leave once more, as a matrix [rows][K] of the call's type
+template <typename CT, int ROWS, int DEEP = 1>
+struct LoadKCS {
+    typedef typename TileEl<CT>::elem elem;
+    typedef SlicePiece<CT> SP;
+    static constexpr bool KC = true;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK * DEEP, PITCH = BK + TileEl<CT>::PAD, CPR = BK / V, NT = TILE_THREADS * DEEP,
+                         P = ROWS * CPR / NT, CH = P * SP::CH, LDS = ROWS * PITCH, XF = 1;
+    const float *rp[P];
+    elem *copy;
+    i64 stride, jump;
+    int K, kc, row, row0, rows, kl, ks, slices, seg;
+
+    __device__ __forceinline__ void init(const void *p, i64 ld, int rows_, int K_, int row0_, int kbeg, int tid, int slices_, i64 stride_,
+                                         int seg_, i64 jump_, void *copy_)
+    {
+        K = K_, rows = rows_, row0 = row0_, slices = slices_, stride = stride_, seg = seg_, jump = jump_;
+        copy = (elem *)copy_;
+        kc = (tid % CPR) * V;
+        row = tid / CPR;
+#pragma unroll
+        for (int i = 0; i < P; ++i) rp[i] = (const float *)p + (i64)min(row0 + row + i * (NT / CPR), rows - 1) * ld;
+        kl = ks = kbeg;
+    }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
+    {
+        const int k = min(kl + kc, K - V);
+        const i64 at = seg > 0 ? k + (k / seg) * (jump - seg) : k;
+#pragma unroll
+        for (int i = 0; i < P; ++i) SP::load(rp[i] + at, slices, stride, &r[i * SP::CH]);
+        kl += BK;
+    }
+    template <bool EDGE>
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
+    {
+        const int k = min(ks + kc, K - V), s = ks + kc - k;
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            uint4 v = SP::sum(&r[i * SP::CH], slices);
+            const int m = row0 + row + i * (NT / CPR);
+            if (copy && m < rows) stg16(copy + (i64)m * K + k, v); // (a piece that was pulled back holds what its neighbour writes)
+            if (EDGE && s) v = piece_shift<sizeof(elem)>(v, s);
+            *(uint4 *)&lds[(row + i * (NT / CPR)) * PITCH + kc] = v;
+        }
+        ks += BK;
+    }
+};
+
+// LoadMC of such an operand
+template <typename CT, int ROWS, int DEEP = 1>
+struct LoadMCS {
+    typedef typename TileEl<CT>::elem elem;
+    typedef SlicePiece<CT> SP;
+    static constexpr bool KC = false;
+    static constexpr int V = TileEl<CT>::V, BK = TileEl<CT>::BK * DEEP, PITCH = ROWS + TileEl<CT>::PAD, CPR = ROWS / V, NT = TILE_THREADS * DEEP,
+                         P = BK * CPR / NT, CH = P * SP::CH, LDS = BK * PITCH, KSTEP = NT / CPR, XF = 1;
+    const float *p;
+    i64 ld, stride;
+    int K, mc, shift, krow, kl, ks, slices;
+
+    __device__ __forceinline__ void init(const void *p_, i64 ld_, int cols, int K_, int col0, int kbeg, int tid, int slices_, i64 stride_)
+    {
+        K = K_, ld = ld_, slices = slices_, stride = stride_;
+        mc = (tid % CPR) * V;
+        krow = tid / CPR;
+        const int m = min(col0 + mc, cols - V);
+        shift = col0 + mc - m;
+        p = (const float *)p_ + m;
+        kl = ks = kbeg;
+    }
+    __device__ __forceinline__ void load(uint4 (&r)[CH], int (&x)[XF])
+    {
+#pragma unroll
+        for (int i = 0; i < P; ++i) SP::load(p + (i64)min(kl + krow + i * KSTEP, K - 1) * ld, slices, stride, &r[i * SP::CH]);
+        kl += BK;
+    }
+    template <bool EDGE>
+    __device__ __forceinline__ void store(elem *lds, uint4 (&r)[CH], int (&x)[XF])
+    {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            uint4 v = SP::sum(&r[i * SP::CH], slices);
+            if (shift) v = piece_shift<sizeof(elem)>(v, shift);
+            if (EDGE && ks + krow + i * KSTEP >= K) v = make_uint4(0, 0, 0, 0);
+            *(uint4 *)&lds[(krow + i * KSTEP) * PITCH + mc] = v;
+        }
+        ks += BK;
+    }
+};
+
 // ------------------------------------------------------------------ convolution operands
 constexpr int TILE_MAX_TAPS = 25;
 

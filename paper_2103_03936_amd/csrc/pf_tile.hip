@@ -138,6 +138,25 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
     return best;
 }
 
+// (a workgroup of the readers brings its slices in at 50 bytes a clock; bf16 at 25, for its own intermediate is half of one of them)
+MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most)
+{
+    MidPlan best = {plan_tiles(dtype, M, N, K, max_split), false};
+    if (reader != TS_32 && reader != TS_32D) return best;
+    const ChunkCost cc = chunk_cost(dtype == PF_BF16, TS_32);
+    const i64 tiles = ((M + 31) / 32) * ((N + 31) / 32), chunks = (K + (dtype == PF_BF16 ? 63 : 31)) / (dtype == PF_BF16 ? 64 : 32);
+    const double rate = dtype == PF_BF16 ? 25 : 50;
+    for (int ks = 2; ks <= TILE_MAX_SLICES; ++ks) {
+        const i64 per = (chunks + ks - 1) / ks, count = tiles * ks;
+        if ((ks - 1) * per >= chunks) continue; // (an empty split)
+        const bool deep = count <= 256 && per >= 8;
+        const double own = ceil(count / 256.0) * (per * cc.work + cc.tile), alone = per * cc.one * (deep ? 0.85 : 1) + cc.tile;
+        const double cost = (own > alone ? own : alone) + 3000 + ks * (all > 256 * most ? all / 256.0 : most) / rate;
+        if (cost < best.t.cost) best = MidPlan{TilePlan{deep ? TS_32D : TS_32, ks, cost}, true};
+    }
+    return best;
+}
+
 void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ksplit)
 {
     TileProb &p = a.p[a.n++];

@@ -48,6 +48,9 @@ struct TileProb {
     int aseg, bseg;        // TILE_NT: an operand comes in segments of this many contraction indices (0: one), each a matrix
     i64 ajump, bjump;      // of its own, this many elements after the one before
     const float *ascale;
+    int aslices, bslices;  // > 1: A of TILE_NT, B of TILE_TN are that many partial sums (float) of the operand, `sstride` floats
+    i64 sstride;           // apart; acopy (nullable): [M][K], their sums in the call's type
+    void *acopy;
     PixView pa, pb;
     TileOut o;
 };
@@ -71,6 +74,14 @@ struct TilePlan {
 };
 // The tile shape and k-split that should finish first, at most max_split ways.
 TilePlan plan_tiles(int dtype, i64 M, i64 N, i64 K, int max_split);
+
+// The same for an intermediate M x N whose readers can take its partial sums instead (TileProb::aslices): `all` bytes of it go into
+// their workgroups, `most` of them into one.  sliced: they are to do so, ksplit of them.
+struct MidPlan {
+    TilePlan t;
+    bool sliced;
+};
+MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most);
 
 // Several products in one launch (one tile shape); those marked may split their contraction.
 struct TileNeed {

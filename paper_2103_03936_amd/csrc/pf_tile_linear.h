@@ -5,8 +5,9 @@
 
 namespace pf {
 
-template <typename CT, class CFG>
-__global__ __launch_bounds__(TILE_THREADS * CFG::DEEP, CFG::template OCC<CT>) void tile_linear_kernel(TileArgs by_value)
+// SLICES: left operands of TILE_NT and right ones of TILE_TN may be partial sums (the registers of four slices: two wavefronts a SIMD)
+template <typename CT, class CFG, bool SLICES>
+__global__ __launch_bounds__(TILE_THREADS * CFG::DEEP, SLICES ? 2 : CFG::template OCC<CT>) void tile_linear_kernel(TileArgs by_value)
 {
     const TileArgs &a = tile_args(by_value);
     constexpr int BM = CFG::BM, BN = CFG::BN, DEEP = CFG::DEEP, BK = TileEl<CT>::BK * DEEP;
@@ -27,15 +28,22 @@ __global__ __launch_bounds__(TILE_THREADS * CFG::DEEP, CFG::template OCC<CT>) vo
     typedef typename TileEl<CT>::elem elem;
     const elem *A = (const elem *)p.A + t.zb * p.sa, *B = (const elem *)p.B + t.zb * p.sb;
     if (p.type == TILE_NT) {
-        AKS la;
         BKC lb;
-        la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
         lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
-        la.seg = p.aseg;
-        la.jump = p.ajump;
         lb.seg = p.bseg;
         lb.jump = p.bjump;
-        tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        if (SLICES && p.aslices > 1) {
+            LoadKCS<CT, BM, DEEP> la;
+            elem *copy = p.acopy && t.n0 == 0 ? (elem *)p.acopy + t.zb * p.sa : nullptr;
+            la.init((const float *)p.A + t.zb * p.sa, p.lda, p.M, p.K, t.m0, kbeg, tid, p.aslices, p.sstride, p.aseg, p.ajump, copy);
+            tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        } else {
+            AKS la;
+            la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
+            la.seg = p.aseg;
+            la.jump = p.ajump;
+            tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        }
         tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) {
             put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v);
         });
@@ -50,10 +58,16 @@ __global__ __launch_bounds__(TILE_THREADS * CFG::DEEP, CFG::template OCC<CT>) vo
         });
     } else {
         AM la;
-        BMC lb;
         la.init(A, p.lda, p.M, p.K, t.m0, kbeg, tid);
-        lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
-        tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        if (SLICES && p.bslices > 1) {
+            LoadMCS<CT, BN, DEEP> lb;
+            lb.init((const float *)p.B + t.zb * p.sb, p.ldb, p.N, p.K, t.n0, kbeg, tid, p.bslices, p.sstride);
+            tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        } else {
+            BMC lb;
+            lb.init(B, p.ldb, p.N, p.K, t.n0, kbeg, tid);
+            tile_product<CT, CFG>(la, lb, nch, smem, tid);
+        }
         finish<CT, CFG, AM>(p, t.ks, t.zb, t.m0, t.n0, la, t.m0, p.M, p.o.sums && t.n0 == 0, smem, tid);
     }
 }
@@ -62,7 +76,21 @@ template <typename CT, class CFG>
 static int launch_linear(hipStream_t s, const char *name, const TileArgs &a)
 {
     int st = PF_OK;
-    PF_LAUNCH(st, name, (tile_linear_kernel<CT, CFG>), dim3(a.blocks), dim3(TILE_THREADS * CFG::DEEP), s, a);
+    bool slices = false;
+    for (int i = 0; i < a.n; ++i) {
+        const TileProb &p = a.p[i];
+        if (p.aslices > TILE_MAX_SLICES || p.bslices > TILE_MAX_SLICES || (p.aslices > 1 && p.type != TILE_NT) || (p.bslices > 1 && p.type != TILE_TN))
+            return PF_ERR_UNSUPPORTED;
+        slices = slices || p.aslices > 1 || p.bslices > 1;
+    }
+    const dim3 grid(a.blocks), block(TILE_THREADS * CFG::DEEP);
+    if constexpr (CFG::BM * CFG::BN <= 32 * 32) {
+        if (slices) PF_LAUNCH(st, name, (tile_linear_kernel<CT, CFG, true>), grid, block, s, a);
+        else PF_LAUNCH(st, name, (tile_linear_kernel<CT, CFG, false>), grid, block, s, a);
+    } else {
+        if (slices) return PF_ERR_UNSUPPORTED; // (they take the registers of a larger tile's sums)
+        PF_LAUNCH(st, name, (tile_linear_kernel<CT, CFG, false>), grid, block, s, a);
+    }
     return st;
 }
 template <typename CT>

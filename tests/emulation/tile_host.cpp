@@ -25,6 +25,16 @@ int emu_plan(int dtype, long long M, long long N, long long K, int max_split, in
     *split = p.ksplit;
     return p.shape;
 }
+// slices of the intermediate T (backward: dT) of a layer [M][in] -> r -> out that its readers add up, 1: none
+int emu_slices(int dtype, long long M, long long in, long long out, long long r, int backward)
+{
+    const TileNeed need[3] = {{M, in, r, false}, {out, r, M, true, true}, {in, r, M, true, true}};
+    const TileShape reader = backward ? plan_tile_group(dtype, need, 3).shape : plan_tiles(dtype, M, out, r, 1).shape;
+    const long long rows = (M + 31) / 32 * 32, ins = (in + 31) / 32, outs = (out + 31) / 32;
+    const MidPlan p = backward ? plan_mid(dtype, M, r, out, 16, reader, 8 * ins * rows * r, 128 * (M > r ? M : r))
+                               : plan_mid(dtype, M, r, in, 16, reader, 4 * outs * rows * r, 128 * r);
+    return p.sliced ? p.t.ksplit : 1;
+}
 // the same for the gradients of a layer [M][in] -> r -> out in one launch (dX, dU, dV)
 int emu_gradients(int dtype, long long M, long long in, long long out, long long r, int *split)
 {

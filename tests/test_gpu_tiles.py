@@ -69,6 +69,24 @@ def test_linear_shared(shape, dtype):
     test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=shape[0] != 700, seed=24)
 
 
+# Intermediates in slices that their readers add up (tests/test_host_tiles.py: which of these have them, and how many): one row to
+# just past a tile of them, ranks of one piece to several chunks, rows of slices that no piece divides.
+SLICED = [(1, 1030, 517, 97), (31, 2047, 1021, 181), (33, 640, 1280, 8), (65, 1000, 1064, 250), (128, 1152, 256, 116), (250, 704, 832, 181)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("saved_T", [True, False])
+@pytest.mark.parametrize("shape", SLICED)
+def test_linear_slices(shape, saved_T, dtype):
+    test_gpu_linear._run(*shape, dtype=dtype, bias=True, saved_T=saved_T, seed=25)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(33, 1000, 1064, 40, 3), (20, 1500, 1504, 16, 2)])
+def test_linear_shared_slices(shape, dtype):
+    test_gpu_linear_shared._run(*shape, dtype=dtype, saved_T=True, seed=26)
+
+
 def test_bias_gradient_of_many_rows():
     """Float sums over 16384 rows of zero mean, unsplit.  Chains of n additions of such terms are off by about 2^-24 sqrt(n / 6)
     of the sum, rms: 2^-22 for runs of at most 96 rows, which the thousands of one thread's single chain would miss."""

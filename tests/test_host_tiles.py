@@ -63,3 +63,13 @@ def test_plans_that_the_gpu_tests_count_on(emu):
 def test_padded_gradients_stay_on_smaller_tiles(emu, M, n_in, n_out):
     """128 x 128 tiles, of which padding took more than a seventeenth, were the slower ones (the first 47.5 -> 56.8 us)."""
     assert _gradients(emu, BF16, M, n_in, n_out, 128)[0] == TS_64
+
+
+@pytest.mark.parametrize("dtype,shape,forward,backward", [
+    (F32, (1, 1030, 517, 97), 4, 4), (F32, (31, 2047, 1021, 181), 1, 4), (F32, (33, 640, 1280, 8), 4, 4),
+    (F32, (65, 1000, 1064, 250), 4, 4), (F32, (128, 1152, 256, 116), 4, 4), (F32, (250, 704, 832, 181), 4, 4),
+    (BF16, (1, 1030, 517, 97), 3, 3), (BF16, (31, 2047, 1021, 181), 4, 2), (BF16, (33, 640, 1280, 8), 4, 4),
+    (BF16, (65, 1000, 1064, 250), 2, 2), (BF16, (128, 1152, 256, 116), 3, 1), (BF16, (250, 704, 832, 181), 2, 1)])
+def test_slices_that_the_gpu_tests_count_on(emu, dtype, shape, forward, backward):
+    M, n_in, n_out, r = (ctypes.c_longlong(v) for v in shape)
+    assert (emu.emu_slices(dtype, M, n_in, n_out, r, 0), emu.emu_slices(dtype, M, n_in, n_out, r, 1)) == (forward, backward)
