@@ -22,6 +22,7 @@
 #include "pf_gemm.h"
 #include "pf_lstm_persist.h"
 #include "pf_skinny.h"
+#include "pf_tile_host.h"
 #include "pf_common.h"
 
 namespace pf {
@@ -29,7 +30,6 @@ namespace pf {
 LstmRecurrence lstm_recurrence = {};
 
 constexpr int ST_MAX_LAYERS = 4;
-constexpr int ST_RANK_MMA_ROWS = 128; // T B from which the weight gradients go to the matrix unit
 
 __device__ __forceinline__ float st_sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
 
@@ -574,35 +574,47 @@ static int check_stack_desc(const pf_lstm_stack_desc *d, StackGeom *g)
     return PF_OK;
 }
 
-// C[Mt x N] = A[Mt x K] W (+ bias) for Mt = T B rows, 512 rows per launch pair (product + slice sums)
-constexpr int ST_ROWS = SK_MAX_ROWS * SK_MAX_PROB;
-static int st_tall(hipStream_t s, const char *name, bool nk, i64 Mt, const float *A, i64 lda, const float *W, i64 ldw,
-                   int K, int N, float *out, i64 ldo, const float *bias, float *part)
+// The products over all rows T B at once, on the tiled kernels (pf_tile.h): Tx = X Vx of the first layer (and, step by step, zx = Tx Ux^T)
+// before the recurrence, dTx = dz Ux and dx = dTx Vx^T after it.  The streaming kernels passed over the factors once for every 32 rows and
+// needed a launch for their slices: 700 rows, 1500 units, one pair for all gates 148 us in twelve launches, 90 in five; 4 x 32 rows, 640
+// units, a pair per gate: 294 -> 257 for the call, zx alone 63 -> 8.
+struct StackTall {
+    TilePlan Tx, zx, dx;
+    MidPlan dTx;
+    size_t n_part; // partial sums, floats
+};
+static StackTall make_tall(const StackGeom &g)
 {
-    int st = PF_OK;
-    for (i64 m0 = 0; m0 < Mt && st == PF_OK; m0 += ST_ROWS) {
-        const int Mg = (int)(Mt - m0 < ST_ROWS ? Mt - m0 : ST_ROWS);
-        SkinnyArgs a;
-        skinny_rows(Mg, A + m0 * lda, lda, W, ldw, K, N, part, a);
-        st = launch_skinny_gemm(s, name, a, nk);
-        if (st != PF_OK) break;
-        SliceSumArgs ss = {};
-        ss.s[ss.nseg++] = skinny_rows_seg(a, Mg, out + m0 * ldo, ldo, bias);
-        st = launch_slice_sum(s, ss);
-    }
-    return st;
+    StackTall t;
+    const i64 Mt = (i64)g.T * g.B, K = g.G == 1 ? 4 * g.h : g.h;
+    t.Tx = plan_tiles(PF_F32, Mt, g.gr, g.din, 16);
+    t.zx = plan_tiles(PF_F32, Mt, 4 * (i64)g.h, g.r, 1);
+    t.dx = plan_tiles(PF_F32, Mt, g.din, g.gr, 1);
+    t.dTx = plan_mid(PF_F32, Mt, g.gr, K, 16, t.dx.shape, (Mt + 31) / 32 * ((g.din + 31) / 32) * 128 * g.gr, 128 * g.gr);
+    const int ks = t.Tx.ksplit > t.dTx.t.ksplit ? t.Tx.ksplit : t.dTx.t.ksplit;
+    t.n_part = ks > 1 ? (size_t)(ks * Mt * g.gr) + 64 : 0;
+    return t;
 }
-static size_t st_tall_part(i64 Mt, int K, int N)
+static const StackTall &plan_tall(const StackGeom &g)
 {
-    SkinnyArgs a;
-    size_t m = 0;
-    const int full = (int)(Mt < ST_ROWS ? Mt : ST_ROWS), last = (int)(Mt % ST_ROWS);
-    if (full > 0) m = skinny_rows(full, nullptr, K, nullptr, N, K, N, nullptr, a);
-    if (last > 0) {
-        const size_t v = skinny_rows(last, nullptr, K, nullptr, N, K, N, nullptr, a);
-        if (v > m) m = v;
-    }
-    return m;
+    static thread_local PlanCache<PlanKey<5>, StackTall> cache;
+    return cache.get(PlanKey<5>{{(i64)g.T * g.B, g.din, g.h, g.r, g.G}}, [&] { return make_tall(g); });
+}
+// out [Mt][gr] = q, a product of that shape; slices (nullable): how many partial sums at `part` it stays in
+static int tall_mid(hipStream_t s, const char *name, const TilePlan &t, TileProb q, i64 count, float *out, float *part, int *slices)
+{
+    TileArgs a = {};
+    q.o.f32 = 1;
+    q.o.C = t.ksplit > 1 ? part : out;
+    q.o.split_stride = count;
+    tile_add(a, t.shape, PF_F32, q, t.ksplit);
+    int st = launch_tiles_linear(s, name, PF_F32, t.shape, a);
+    const int got = a.p[0].ksplit;
+    if (slices) *slices = got;
+    if (st != PF_OK || t.ksplit == 1 || (slices && got > 1)) return st;
+    SplitSumArgs ss = {};
+    split_sum_add(ss, SplitSum{part, out, count, count, got, 0, nullptr, 0, 0});
+    return launch_split_sums(s, ss);
 }
 
 // slice sums of several regions, four segments per launch
@@ -1068,10 +1080,7 @@ static int plan_stack(const StackGeom &g, StackPlan *out)
     auto upd = [&](size_t v) {
         if (v > m) m = v;
     };
-    upd(st_tall_part(Mt, g.din, g.gr));                    // Tx = X Vx, layer 0
-    upd(st_tall_part(Mt, g.r, g.G == 1 ? 4 * g.h : g.h));  // zx = Tx Ux^T
-    upd(st_tall_part(Mt, g.G == 1 ? 4 * g.h : g.h, g.r));  // dTx = dz Ux
-    upd(st_tall_part(Mt, g.gr, g.din));                    // dx = dTx Vx^T
+    upd(plan_tall(g).n_part);                              // Tx = X Vx, layer 0; dTx = dz Ux
     StackPtrs none = {};
     StackPacked nonep = {};
     nonep.fused_z = zg_supported(g.G, g.r);
@@ -1175,11 +1184,12 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     hipStream_t s = (hipStream_t)stream;
     const i64 Mt = (i64)g.T * g.B;
     const int h = g.h, r = g.r, gr = g.gr;
+    const StackTall tall = plan_tall(g);
+    const TileProb tx0 = tile_prob(TILE_NN, (int)Mt, gr, g.din, x, g.din, p.Vx[0], gr, nullptr, gr);
     if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), false)) {
         float *part = ws.take<float>(pl.n_part), *run = ws.take<float>(pl.n_run_f);
         if (!ws.ok()) return PF_ERR_WORKSPACE;
-        st = st_tall(s, "lstm_stack_Tx0=X*Vx", false, Mt, (const float *)x, g.din, p.Vx[0], gr, g.din, gr, p.Tx_all[0], gr,
-                     nullptr, part);
+        st = tall_mid(s, "lstm_stack_Tx0=X*Vx", tall.Tx, tx0, Mt * gr, p.Tx_all[0], part, nullptr);
         if (st != PF_OK) return st;
         LstmRunLayer layers[ST_MAX_LAYERS];
         run_layers(g, p, layers);
@@ -1193,18 +1203,21 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     stack_pack(g, p, false, packed, &pk, false, s, &st);
     if (st != PF_OK) return st;
     // the input path of the first layer for every time step at once
-    st = st_tall(s, "lstm_stack_Tx0=X*Vx", false, Mt, (const float *)x, g.din, p.Vx[0], gr, g.din, gr, p.Tx_all[0], gr,
-                 nullptr, part);
+    st = tall_mid(s, "lstm_stack_Tx0=X*Vx", tall.Tx, tx0, Mt * gr, p.Tx_all[0], part, nullptr);
     if (st != PF_OK) return st;
     if (pk.fused_z) {
         // z of the first layer's input path is formed inside the fused kernel, step by step
-    } else if (g.G == 1) {
-        st = st_tall(s, "lstm_stack_zx0=Tx*Uxt", true, Mt, p.Tx_all[0], gr, p.Ux[0], r, r, 4 * h, zx0, 4 * (i64)h,
-                     p.bias[0], part);
     } else {
-        for (int q = 0; q < 4 && st == PF_OK; ++q)
-            st = st_tall(s, "lstm_stack_zx0=Tx*Uxt", true, Mt, p.Tx_all[0] + (i64)q * r, gr, p.Ux[0] + (i64)q * h * r, r, r,
-                         h, zx0 + (i64)q * h, 4 * (i64)h, p.bias[0] ? p.bias[0] + (i64)q * h : nullptr, part);
+        TileArgs a = {};
+        TileProb q = tile_prob(TILE_NT, (int)Mt, g.G == 1 ? 4 * h : h, r, p.Tx_all[0], gr, p.Ux[0], r, zx0, 4 * (i64)h);
+        q.nb = g.G;
+        q.sa = r;
+        q.sb = (i64)h * r;
+        q.sc = q.sbias = h;
+        q.o.bias = p.bias[0];
+        tile_add(a, tall.zx.shape, PF_F32, q, 1);
+        st = launch_tiles_linear(s, "lstm_stack_zx0=Tx*Uxt", PF_F32, tall.zx.shape, a);
+        if (st != PF_OK) return st;
     }
     for (int slot = 0; slot < g.T + g.L - 1 && st == PF_OK; ++slot)
         st = stack_fwd_slot(g, p, pk, zx0, slot, part, pl.n_part, false, s, nullptr);
@@ -1313,71 +1326,48 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x, const 
     if (st != PF_OK) return st;
     // the input path of the first layer for all steps at once
     const i64 Mt = (i64)T * B;
-    if (g.G == 1) {
-        st = st_tall(s, "lstm_stack_dTx0=dz*Ux", false, Mt, b.dz_all[0], 4 * (i64)h, p.Ux[0], r, 4 * h, r, b.dTx_all[0], gr,
-                     nullptr, part);
-    } else {
-        for (int q = 0; q < 4 && st == PF_OK; ++q)
-            st = st_tall(s, "lstm_stack_dTx0=dz*Ux", false, Mt, b.dz_all[0] + (i64)q * h, 4 * (i64)h,
-                         p.Ux[0] + (i64)q * h * r, r, h, r, b.dTx_all[0] + (i64)q * r, gr, nullptr, part);
-    }
+    const StackTall tall = plan_tall(g);
+    TileProb q = tile_prob(TILE_NN, (int)Mt, r, g.G == 1 ? 4 * h : h, b.dz_all[0], 4 * (i64)h, p.Ux[0], r, nullptr, gr);
+    q.nb = g.G;
+    q.sa = h;
+    q.sb = (i64)h * r;
+    q.sc = r;
+    int slices = 1;
+    st = tall_mid(s, "lstm_stack_dTx0=dz*Ux", tall.dTx.t, q, Mt * gr, b.dTx_all[0], part, dx_all && tall.dTx.sliced ? &slices : nullptr);
     if (st != PF_OK) return st;
     if (dx_all) {
-        st = st_tall(s, "lstm_stack_dx=dTx*Vxt", true, Mt, b.dTx_all[0], gr, p.Vx[0], gr, gr, g.din, (float *)dx_all, g.din,
-                     nullptr, part);
+        TileArgs a = {};
+        TileProb y = tile_prob(TILE_NT, (int)Mt, g.din, gr, b.dTx_all[0], gr, p.Vx[0], gr, dx_all, g.din);
+        if (slices > 1) y.A = part, y.aslices = slices, y.sstride = Mt * gr, y.acopy = b.dTx_all[0];
+        tile_add(a, tall.dx.shape, PF_F32, y, 1);
+        st = launch_tiles_linear(s, "lstm_stack_dx=dTx*Vxt", PF_F32, tall.dx.shape, a);
         if (st != PF_OK) return st;
     }
-    // parameter gradients, layer by layer, each a few rank-(T B) updates in one launch
-    const SliceSumArgs none = {};
+    // Parameter gradients, sums over T B rows on the matrix unit, as many layers to a launch as it takes problems; the bias gradient rides
+    // on the input path's dU.  Few rows went by rank updates, two launches a layer: 3 layers of 128 units, a pair per gate, 36 rows 57 -> 10 us,
+    // of 848 units, one pair, 80 rows 77 -> 32.
+    const int per = 2 * g.G + 2;
+    RankMmaArgs rm = {};
+    rm.accumulate = accumulate;
     for (int l = 0; l < L && st == PF_OK; ++l) {
-        const float *xin = l ? p.h_all[l - 1] : (const float *)x;
-        const int din = l ? h : g.din;
-        if (Mt >= ST_RANK_MMA_ROWS) {
-            // enough rows for the matrix unit; the bias gradient rides on the input path's dU
-            RankMmaArgs rm = {};
-            rm.accumulate = accumulate;
-            bool ok = true;
-            for (int path = 0; path < 2; ++path) {
-                const float *Tm = path ? p.Th_all[l] : p.Tx_all[l];
-                float *dU = path ? b.dUh[l] : b.dUx[l];
-                for (int q = 0; q < g.G; ++q)
-                    ok = ok && rank_mma_add(rm, nullptr, 0, b.dz_all[l] + (i64)q * h, 4 * (i64)h, Tm + (i64)q * r, gr,
-                                            dU + (i64)q * h * r, r, g.G == 1 ? 4 * h : h, r, (int)Mt,
-                                            path == 0 && b.dbias[l] ? b.dbias[l] + (i64)q * h : nullptr);
-            }
-            ok = ok && rank_mma_add(rm, nullptr, 0, xin, din, b.dTx_all[l], gr, b.dVx[l], gr, din, gr, (int)Mt);
-            // dVh = sum_t h_{t-1}^T dTh_t: the left operand is h0, then h_0 .. h_{T-2}
-            ok = ok && rank_mma_add(rm, p.h0[l], B, p.h_all[l], h, b.dTh_all[l], gr, b.dVh[l], gr, h, gr, (int)Mt);
-            if (ok) {
-                st = launch_rank_mma(s, "lstm_stack_grads", rm);
-                continue;
-            }
-            // (a dimension below four: the general kernel below takes the layer)
-        }
-        RankArgs ra = {};
-        ra.M = (int)Mt;
-        ra.accumulate = accumulate;
+        bool ok = true;
         for (int path = 0; path < 2; ++path) {
             const float *Tm = path ? p.Th_all[l] : p.Tx_all[l];
             float *dU = path ? b.dUh[l] : b.dUx[l];
-            if (g.G == 1) {
-                rank_add(ra, b.dz_all[l], 4 * (i64)h, Tm, gr, dU, r, 4 * h, r);
-            } else {
-                for (int q = 0; q < 4; ++q)
-                    rank_add(ra, b.dz_all[l] + (i64)q * h, 4 * (i64)h, Tm + (i64)q * r, gr, dU + (i64)q * h * r, r, h, r);
-            }
+            for (int gate = 0; gate < g.G; ++gate)
+                ok = ok && rank_mma_add(rm, nullptr, 0, b.dz_all[l] + (i64)gate * h, 4 * (i64)h, Tm + (i64)gate * r, gr,
+                                        dU + (i64)gate * h * r, r, g.G == 1 ? 4 * h : h, r, (int)Mt,
+                                        path == 0 && b.dbias[l] ? b.dbias[l] + (i64)gate * h : nullptr);
         }
-        rank_add(ra, xin, din, b.dTx_all[l], gr, b.dVx[l], gr, din, gr);
-        // dVh = sum_t h_{t-1}^T dTh_t: the rows t >= 1 here, the h0 row block in a second launch below
-        if (T > 1) rank_add(ra, p.h_all[l], h, b.dTh_all[l] + (i64)B * gr, gr, b.dVh[l], gr, h, gr, (int)(Mt - B));
-        if (b.dbias[l]) rank_add(ra, b.dz_all[l], 4 * (i64)h, nullptr, 0, b.dbias[l], 1, 4 * h, 1);
-        st = launch_rank_update(s, "lstm_stack_grads", ra, none);
-        if (st != PF_OK) return st;
-        RankArgs rb = {};
-        rb.M = B;
-        rb.accumulate = (T > 1) ? 1 : accumulate;
-        rank_add(rb, p.h0[l], h, b.dTh_all[l], gr, b.dVh[l], gr, h, gr);
-        st = launch_rank_update(s, "lstm_stack_grads", rb, none);
+        ok = ok && rank_mma_add(rm, nullptr, 0, l ? p.h_all[l - 1] : (const float *)x, l ? h : g.din, b.dTx_all[l], gr, b.dVx[l], gr,
+                                l ? h : g.din, gr, (int)Mt);
+        // dVh = sum_t h_{t-1}^T dTh_t: the left operand is h0, then h_0 .. h_{T-2}
+        ok = ok && rank_mma_add(rm, p.h0[l], B, p.h_all[l], h, b.dTh_all[l], gr, b.dVh[l], gr, h, gr, (int)Mt);
+        if (!ok) return PF_ERR_UNSUPPORTED; // (not reached: every extent is at least four)
+        if (l + 1 == L || rm.nprob + per > RM_MAX_PROB) {
+            st = launch_rank_mma(s, "lstm_stack_grads", rm);
+            rm.nprob = 0;
+        }
     }
     return st;
 }

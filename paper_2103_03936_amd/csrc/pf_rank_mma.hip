@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256, XI == 1 ? 3 : 2) void rank_mma_kernel(RankMmaA
     int pi = 0;
 #pragma unroll
     for (int q = 1; q < RM_MAX_PROB; ++q)
-        if (q < a.nprob && (int)blockIdx.x >= a.p[q].wg0) pi = q;
+        if ((int)blockIdx.x >= a.wg0[q]) pi = q;
     const RankMmaProb &pb = a.p[pi];
     const int local = blockIdx.x - pb.wg0;
     const int I = pb.I;
@@ -282,10 +282,11 @@ static int rank_mma_plan(RankMmaArgs &a, int xi)
         p.jt = (p.J + RM_TJ - 1) / RM_TJ;
         p.ntile = ((p.I + 64 * xi - 1) / (64 * xi)) * p.jt;
         p.nwg = (p.ntile + 7) / 8 * 8;
-        p.wg0 = a.nwg;
+        p.wg0 = a.wg0[q] = a.nwg;
         a.nwg += p.nwg;
         tiles += p.ntile;
     }
+    for (int q = a.nprob; q < RM_MAX_PROB; ++q) a.wg0[q] = 0x7fffffff;
     return tiles;
 }
 

@@ -195,9 +195,10 @@ struct RankMmaProb {
     i64 lda, ldb, ldo;
     int M0, M, I, J, wg0, jt, ntile, nwg; // jt = column tiles; nwg = ntile rounded up to a multiple of eight
 };
-constexpr int RM_MAX_PROB = 12;
+constexpr int RM_MAX_PROB = 32; // (three layers with a factor pair per gate)
 struct RankMmaArgs {
     RankMmaProb p[RM_MAX_PROB];
+    int wg0[RM_MAX_PROB];           // the problems' first workgroups once more, side by side: a few scalar loads find a problem
     int nprob, accumulate, nwg, xi; // nwg, xi (tile height / 64) and the problems' tile fields: set by the launch
 };
 // false: the kernel does not take this problem (a row shorter than four floats, too many problems); out == NULL: skipped

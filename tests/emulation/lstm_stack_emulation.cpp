@@ -10,6 +10,7 @@
 #include <vector>
 #include "pf_gemm.h"
 #include "pf_skinny.h"
+#include "pf_tile_host.h"
 
 struct Buf { const char *p; size_t n; };
 static std::vector<Buf> g_bufs;
@@ -42,6 +43,7 @@ int emu_skinny_pack_kernel(dim3 grid, const SkinnyPackArgs &a);
 int emu_slice_sum_kernel(dim3 grid, const SliceSumArgs &a);
 int emu_rank_update_kernel(dim3 grid, const RankArgs &a, const SliceSumArgs &seg, int nsb);
 template <int XI> int emu_rank_mma_kernel(dim3 grid, const RankMmaArgs &a);
+int emu_split_sums_kernel(dim3 grid, const SplitSumArgs &a);
 int launch_zero_f32(hipStream_t, float *out, i64 count)
 {
     if (count <= 0 || !out) return PF_OK;
@@ -50,15 +52,86 @@ int launch_zero_f32(hipStream_t, float *out, i64 count)
     return PF_OK;
 }
 }
+namespace pf {
+int emu_tiles(TileShape shape, const TileArgs &a);
+template <typename CT>
+int launch_linear_t(hipStream_t, const char *, TileShape shape, const TileArgs &a) { return sizeof(CT) == 4 ? emu_tiles(shape, a) : (int)PF_ERR_UNSUPPORTED; }
+template <typename CT>
+int launch_conv_t(hipStream_t, const char *, TileShape, TileShape, const TileArgs &) { return PF_ERR_UNSUPPORTED; }
+}
 #undef PF_LAUNCH
 #define PF_LAUNCH(st, name, kernel, grid, block, s, ...) \
     do { if ((st) == PF_OK) { ++g_launches; (st) = emu_##kernel(grid, __VA_ARGS__); } } while (0)
 
 #include "pf_skinny.hip"
 #include "pf_rank_mma.hip"
+#include "pf_tile.hip"
 #include "pf_lstm_stack.hip"
 
 namespace pf {
+// The tiled products of floats: out = A B as TileProb describes it, operands that are sums of slices included.
+int emu_tiles(TileShape shape, const TileArgs &a)
+{
+    ++g_launches;
+    const int bm = SHAPES[shape].bm, bn = SHAPES[shape].bn, bk = shape == TS_32D ? 64 : 32;
+    int blocks = 0;
+    for (int q = 0; q < a.n; ++q) {
+        const TileProb &p = a.p[q];
+        if (p.type != TILE_NN && p.type != TILE_NT) { g_err = "tiles: type"; return PF_ERR_LAUNCH; }
+        if (p.block0 != blocks || p.tm != (p.M + bm - 1) / bm || p.tn != (p.N + bn - 1) / bn) { g_err = "tiles: workgroups"; return PF_ERR_LAUNCH; }
+        blocks += (p.tm * p.tn * p.ksplit * p.nb + 7) / 8 * 8;
+        if (p.kper % bk || (i64)p.kper * p.ksplit < p.K || (i64)p.kper * (p.ksplit - 1) >= p.K) { g_err = "tiles: splits"; return PF_ERR_LAUNCH; }
+        if (p.aslices > 1 && (p.type != TILE_NT || p.aslices > TILE_MAX_SLICES || (shape != TS_32 && shape != TS_32D))) { g_err = "tiles: slices"; return PF_ERR_LAUNCH; }
+        for (int z = 0; z < p.nb; ++z)
+            for (int ks = 0; ks < p.ksplit; ++ks) {
+                const int k0 = ks * p.kper, k1 = p.K < k0 + p.kper ? p.K : k0 + p.kper;
+                for (int m = 0; m < p.M; ++m) {
+                    const float *A = (const float *)p.A + z * p.sa + m * p.lda;
+                    const int ns = p.aslices > 1 ? p.aslices : 1;
+                    for (int s = 0; s < ns; ++s) CHK(A + s * p.sstride, p.K, "tiles A");
+                    std::vector<double> row(p.K);
+                    for (int k = 0; k < p.K; ++k)
+                        for (int s = 0; s < ns; ++s) row[k] += A[s * p.sstride + k];
+                    if (p.acopy) {
+                        float *to = (float *)p.acopy + z * p.sa + (i64)m * p.K;
+                        CHK(to, p.K, "tiles A copy");
+                        for (int k = 0; k < p.K; ++k) to[k] = (float)row[k];
+                    }
+                    float *c = (float *)p.o.C + ks * p.o.split_stride + z * p.sc + m * p.o.ld;
+                    CHK(c, p.N, "tiles C");
+                    for (int n = 0; n < p.N; ++n) {
+                        const float *B = (const float *)p.B + z * p.sb + (p.type == TILE_NT ? n * p.ldb : n);
+                        if (m == 0 && p.type == TILE_NT) CHK(B, p.K, "tiles B");
+                        double acc = p.o.bias ? ((const float *)p.o.bias)[z * p.sbias + n] : 0.0;
+                        for (int k = k0; k < k1; ++k) {
+                            const float *b = p.type == TILE_NT ? B + k : B + k * p.ldb;
+                            if (m == 0) CHK(b, 1, "tiles B");
+                            acc += row[k] * *b;
+                        }
+                        c[n] = (float)acc;
+                    }
+                }
+            }
+    }
+    if (blocks != a.blocks) { g_err = "tiles: grid"; return PF_ERR_LAUNCH; }
+    return PF_OK;
+}
+int emu_split_sums_kernel(dim3 grid, const SplitSumArgs &a)
+{
+    if ((int)grid.x != a.blocks[a.n]) { g_err = "split sums: grid"; return PF_ERR_LAUNCH; }
+    for (int q = 0; q < a.n; ++q) {
+        const SplitSum &s = a.s[q];
+        CHK(s.dst, s.count, "split sums out");
+        for (int k = 0; k < s.splits; ++k) CHK(s.src + k * s.stride, s.count, "split sums in");
+        for (i64 i = 0; i < s.count; ++i) {
+            double acc = s.accumulate ? s.dst[i] : 0.0;
+            for (int k = 0; k < s.splits; ++k) acc += s.src[k * s.stride + i];
+            s.dst[i] = (float)acc;
+        }
+    }
+    return PF_OK;
+}
+
 int emu_skinny_pack_kernel(dim3 grid, const SkinnyPackArgs &a)
 {
     if ((i64)grid.x * 256 < a.items) { g_err = "pack grid"; return PF_ERR_LAUNCH; }

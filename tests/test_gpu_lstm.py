@@ -521,3 +521,12 @@ def test_layer_stack_resident_factors_edges(shape, groups):
     import paper_2103_03936_amd as pf
     T, B, d, h, r, L = shape
     _check_stack_case(pf, T, B, d, h, r, L, groups, True, 91, f"resident factors {shape} groups {groups}")
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 260, 9, 4, 1, 1), (2, 1, 1030, 70, 33, 1, 4), (3, 5, 36, 40, 10, 4, 4), (5, 7, 515, 129, 31, 4, 1)])
+def test_layer_stack_few_rows(shape):
+    """One to 35 rows over all steps: products over them with their contraction in slices and not, gradients of all layers in one launch
+    and, of four layers with a factor pair per gate, in two."""
+    import paper_2103_03936_amd as pf
+    T, B, d, h, r, L, G = shape
+    _check_stack_case(pf, T, B, d, h, r, L, G, True, 60, str(shape))
