@@ -1038,7 +1038,7 @@ int pf::linear_fwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (!V || !U || (d->has_bias && !bias)) return PF_ERR_NULL;
     if (d->M > 0 && (!X || !Y)) return PF_ERR_NULL;
     if (any_misaligned({X, V, U, bias, Y, T_save}, align)) return PF_ERR_UNSUPPORTED;
-    const LinearPlan p = plan_linear(d);
+    const LinearPlan &p = plan_linear(d);
     const size_t need = p.fwd_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
@@ -1086,7 +1086,7 @@ int pf::linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, 
     if (!V || !U) return PF_ERR_NULL;
     if (d->M > 0 && (!X || !dY)) return PF_ERR_NULL;
     if (any_misaligned({X, V, U, dY, T_saved, dX}, align) || any_misaligned({dU, dV, dbias}, 4)) return PF_ERR_UNSUPPORTED;
-    const LinearPlan p = plan_linear(d);
+    const LinearPlan &p = plan_linear(d);
     const size_t need = p.bwd_bytes;
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it

@@ -262,10 +262,15 @@ __global__ __launch_bounds__(256) void lstm_slices_pointwise_fwd_kernel(const fl
 
 // ------------------------------------------------------------------ any batch, every extent at least four floats
 // The products of a step on the tiled kernels (pf_tile.h), both paths (and the four gate blocks) side by side: forward
-// T; z as two slices; gates.  Backward gate derivatives; dT; dx and dh_prev; all parameter gradients.  A launch whose
-// products are too small for the chip splits their contraction and one more launch adds the partial sums.
+// T; z as two slices; gates.  Backward gate derivatives; dT; dx and dh_prev; all parameter gradients, the last two in one launch where that
+// pays.  Products too small for the chip split their contraction; slices of T and dT are added by the tiles that read them, others by
+// one more launch.  Forward and backward, us, nine launches with streaming kernels for up to 32 rows before / now: 10 rows, 128 units
+// 39.8 / 22.1, 512 units 42.1 / 28.7 (a pair per gate 31.2), 1500 units 62.0 / 55; 64 rows, 512 units 39.5 / 30.5.
 struct LstmTilePlan {
-    TileGroup T, z, dT, dxh, grads;
+    TileGroup z, dxh, grads;
+    MidGroup T, dT;
+    TileGroup last; // dx, dh_prev and all gradients in one launch
+    bool one;       // ... where that is faster than two
     size_t n_T, n_dT, n_dxh, fwd_bytes, bwd_bytes; // partial sums, floats
 };
 static bool lstm_tiles_ok(const pf_lstm_desc *d) { return d->B > 0 && d->d_in >= 4 && d->h >= 4 && d->r >= 4; }
@@ -273,23 +278,31 @@ static bool lstm_tiles_ok(const pf_lstm_desc *d) { return d->B > 0 && d->d_in >=
 static LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
 {
     LstmTilePlan p;
-    const i64 B = d->B, h = d->h, r = d->r, G = d->groups, gr = G * r, din = d->d_in;
-    const TileNeed T[2] = {{B, gr, din, true}, {B, gr, h, true}};
-    p.T = plan_tile_group(PF_F32, T, 2);
+    const i64 B = d->B, h = d->h, r = d->r, G = d->groups, gr = G * r, din = d->d_in, rows = (B + 31) / 32 * 32;
     const TileNeed z[2] = {{B, 4 * h, r, false}, {B, 4 * h, r, false}};
     p.z = plan_tile_group(PF_F32, z, 2);
-    const TileNeed dT[2] = {{B, gr, G == 4 ? h : 4 * h, true}, {B, gr, G == 4 ? h : 4 * h, true}};
-    p.dT = plan_tile_group(PF_F32, dT, 2);
+    const TileNeed T[2] = {{B, gr, din, true}, {B, gr, h, true}};
+    p.T = plan_mid_group(PF_F32, T, 2, p.z.shape, 8 * rows * r * ((4 * h + 31) / 32), 128 * r);
+    const TileNeed last[6] = {{B, din, gr, false}, {B, h, gr, false}, {4 * h, r, B, false}, {4 * h, r, B, false}, {din, gr, B, false}, {h, gr, B, false}};
+    p.dxh = plan_tile_group(PF_F32, last, 2);
     const TileNeed dxh[2] = {{B, din, gr, true}, {B, h, gr, true}};
-    p.dxh = plan_tile_group(PF_F32, dxh, 2);
-    const TileNeed gd[4] = {{4 * h, r, B, false}, {4 * h, r, B, false}, {din, gr, B, false}, {h, gr, B, false}};
-    p.grads = plan_tile_group(PF_F32, gd, 4);
-    p.n_T = (size_t)((p.T.ksplit[0] + p.T.ksplit[1]) * B * gr) + 64;
-    p.n_dT = (size_t)((p.dT.ksplit[0] + p.dT.ksplit[1]) * B * gr) + 64;
+    const TileGroup split = plan_tile_group(PF_F32, dxh, 2);
+    if (split.cost < p.dxh.cost) p.dxh = split;
+    p.grads = plan_tile_group(PF_F32, last + 2, 4);
+    p.last = plan_tile_group(PF_F32, last, 6);
+    // (not where the long contractions of dx and dh_prev alone fill the time on the gradients' larger tiles: 64 rows, 1500 units, a pair per
+    // gate 86.8 us in two launches, 91.9 in one; 128 rows 131 / 121, 512 units 42.6 / 38.1, 1500 units with one pair at 64 rows 74.7 / 70.4)
+    const bool long_k = p.last.shape == TS_64 && p.last.cost <= 1.01 * (4100 + 1200.0 * ((gr + 31) / 32));
+    p.one = p.last.cost < p.dxh.cost + p.grads.cost && !long_k;
+    const TileNeed dT[2] = {{B, gr, G == 4 ? h : 4 * h, true}, {B, gr, G == 4 ? h : 4 * h, true}};
+    p.dT = plan_mid_group(PF_F32, dT, 2, p.one ? p.last.shape : p.dxh.shape, 4 * rows * gr * ((din + 31) / 32 + (h + 31) / 32) * (p.one ? 2 : 1),
+                          128 * (p.one && B > gr ? B : gr));
+    p.n_T = (size_t)((p.T.g.ksplit[0] + p.T.g.ksplit[1]) * B * gr) + 64;
+    p.n_dT = (size_t)((p.dT.g.ksplit[0] + p.dT.g.ksplit[1]) * B * gr) + 64;
     p.n_dxh = (size_t)(p.dxh.ksplit[0] * B * din + p.dxh.ksplit[1] * B * h) + 64;
     const size_t nz = (size_t)(B * 4 * h);
     p.fwd_bytes = align_up(p.n_T * 4) + align_up(2 * nz * 4);
-    p.bwd_bytes = align_up(nz * 4) + 2 * align_up((size_t)(B * gr) * 4) + align_up((p.n_dT > p.n_dxh ? p.n_dT : p.n_dxh) * 4);
+    p.bwd_bytes = align_up(nz * 4) + 2 * align_up((size_t)(B * gr) * 4) + align_up(p.n_dT * 4) + align_up(p.n_dxh * 4);
     return p;
 }
 static const LstmTilePlan &plan_lstm_tiles(const pf_lstm_desc *d)
@@ -298,10 +311,17 @@ static const LstmTilePlan &plan_lstm_tiles(const pf_lstm_desc *d)
     return cache.get(PlanKey<5>{{d->B, d->d_in, d->h, d->r, d->groups}}, [&] { return make_lstm_tile_plan(d); });
 }
 
-// Adds a product whose result is needed in full: straight to `out`, or through partial sums taken from `part`.
-static void add_split(TileArgs &a, SplitSumArgs &ss, const TileGroup &g, int i, TileProb q, float *out, i64 count, float *&part)
+// Adds a product whose result is needed in full: straight to `out`, or through partial sums taken from `part`; sliced: these are what its
+// readers take.
+struct MidAt {
+    float *p;
+    int slices; // > 1: partial sums at p
+};
+static MidAt add_split(TileArgs &a, SplitSumArgs &ss, const TileGroup &g, int i, TileProb q, float *out, i64 count, float *&part,
+                       bool sliced = false)
 {
     const int ks = g.ksplit[i];
+    MidAt at = {out, 1};
     q.o.f32 = 1;
     q.o.C = out;
     if (ks > 1) {
@@ -310,9 +330,12 @@ static void add_split(TileArgs &a, SplitSumArgs &ss, const TileGroup &g, int i, 
     }
     tile_add(a, g.shape, PF_F32, q, ks);
     if (ks > 1) {
-        split_sum_add(ss, SplitSum{part, out, count, count, a.p[a.n - 1].ksplit, 0, nullptr, 0, 0});
+        const int got = a.p[a.n - 1].ksplit;
+        if (sliced && got > 1) at = MidAt{part, got};
+        else split_sum_add(ss, SplitSum{part, out, count, count, got, 0, nullptr, 0, 0});
         part += (ks * count + 3) / 4 * 4;
     }
+    return at;
 }
 
 static int lstm_fwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_prev, const float *c_prev, const float *Vx,
@@ -324,16 +347,17 @@ static int lstm_fwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
     float *part = ws.take<float>(p.n_T), *z = ws.take<float>((size_t)2 * B * 4 * h);
     TileArgs a = {};
     SplitSumArgs ss = {};
-    add_split(a, ss, p.T, 0, tile_prob(TILE_NN, B, gr, din, x, din, Vx, gr, nullptr, gr), Tx, (i64)B * gr, part);
-    add_split(a, ss, p.T, 1, tile_prob(TILE_NN, B, gr, h, h_prev, h, Vh, gr, nullptr, gr), Th, (i64)B * gr, part);
-    int st = launch_tiles_linear(s, "lstm_T=[x*Vx|h*Vh]", PF_F32, p.T.shape, a);
+    const MidAt T[2] = {
+        add_split(a, ss, p.T.g, 0, tile_prob(TILE_NN, B, gr, din, x, din, Vx, gr, nullptr, gr), Tx, (i64)B * gr, part, p.T.sliced),
+        add_split(a, ss, p.T.g, 1, tile_prob(TILE_NN, B, gr, h, h_prev, h, Vh, gr, nullptr, gr), Th, (i64)B * gr, part, p.T.sliced)};
+    int st = launch_tiles_linear(s, "lstm_T=[x*Vx|h*Vh]", PF_F32, p.T.g.shape, a);
     if (st == PF_OK) st = launch_split_sums(s, ss);
     if (st != PF_OK) return st;
     TileArgs b = {};
     for (int path = 0; path < 2; ++path) {
-        TileProb q = tile_prob(TILE_NT, B, G == 4 ? h : 4 * h, r, path ? Th : Tx, gr, path ? Uh : Ux, r,
-                               z + (i64)path * B * 4 * h, 4 * (i64)h);
+        TileProb q = tile_prob(TILE_NT, B, G == 4 ? h : 4 * h, r, T[path].p, gr, path ? Uh : Ux, r, z + (i64)path * B * 4 * h, 4 * (i64)h);
         q.o.f32 = 1;
+        if (T[path].slices > 1) q.aslices = T[path].slices, q.sstride = (i64)B * gr, q.acopy = path ? Th : Tx;
         if (G == 4) {
             q.nb = 4;
             q.sa = r;
@@ -359,7 +383,9 @@ static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
     const LstmTilePlan p = plan_lstm_tiles(d);
     float *dz = ws.take<float>((size_t)B * 4 * h);
     float *dTx = ws.take<float>((size_t)B * gr), *dTh = ws.take<float>((size_t)B * gr);
-    float *part0 = ws.take<float>(p.n_dT > p.n_dxh ? p.n_dT : p.n_dxh), *part = part0;
+    float *part = ws.take<float>(p.n_dT), *part_dxh = ws.take<float>(p.n_dxh);
+    const bool sliced = p.dT.sliced && (p.one || dx); // (else the launch of dx and dh_prev leaves the sums for the gradients')
+    MidAt dT[2];
     int st = PF_OK;
     PF_LAUNCH(st, "lstm_pointwise_bwd", lstm_pointwise_bwd_kernel, dim3((unsigned)(((i64)B * h + 255) / 256)), dim3(256), s,
               gates, c_prev, c_out, dh, dc_next, dz, dc_prev, B, h);
@@ -374,20 +400,27 @@ static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
             q.sb = (i64)h * r;
             q.sc = r;
         }
-        add_split(a, ss, p.dT, path, q, path ? dTh : dTx, (i64)B * gr, part);
+        dT[path] = add_split(a, ss, p.dT.g, path, q, path ? dTh : dTx, (i64)B * gr, part, sliced);
     }
-    st = launch_tiles_linear(s, "lstm_dT=dz*[Ux|Uh]", PF_F32, p.dT.shape, a);
+    st = launch_tiles_linear(s, "lstm_dT=dz*[Ux|Uh]", PF_F32, p.dT.g.shape, a);
     if (st == PF_OK) st = launch_split_sums(s, ss);
     if (st != PF_OK) return st;
-    TileArgs b = {};
+    TileArgs b = {}, c = {};
     SplitSumArgs sb = {};
-    part = part0;
-    if (dx) add_split(b, sb, p.dxh, 0, tile_prob(TILE_NT, B, din, gr, dTx, gr, Vx, gr, nullptr, din), dx, (i64)B * din, part);
-    add_split(b, sb, p.dxh, 1, tile_prob(TILE_NT, B, h, gr, dTh, gr, Vh, gr, nullptr, h), dh_prev, (i64)B * h, part);
-    st = launch_tiles_linear(s, "lstm_dxh=[dTx*Vxt|dTh*Vht]", PF_F32, p.dxh.shape, b);
-    if (st == PF_OK) st = launch_split_sums(s, sb);
-    if (st != PF_OK) return st;
-    TileArgs c = {};
+    const TileGroup unsplit = {p.last.shape, {1, 1, 1, 1, 1, 1}, 0};
+    const auto input = [&](int path, const float *V, int n, float *out) {
+        TileProb q = tile_prob(TILE_NT, B, n, gr, dT[path].p, gr, V, gr, nullptr, n);
+        if (dT[path].slices > 1) q.aslices = dT[path].slices, q.sstride = (i64)B * gr, q.acopy = p.one ? nullptr : path ? dTh : dTx;
+        add_split(p.one ? c : b, sb, p.one ? unsplit : p.dxh, path, q, out, (i64)B * n, part_dxh);
+    };
+    if (dx) input(0, Vx, din, dx);
+    input(1, Vh, h, dh_prev);
+    if (!p.one) {
+        st = launch_tiles_linear(s, "lstm_dxh=[dTx*Vxt|dTh*Vht]", PF_F32, p.dxh.shape, b);
+        if (st == PF_OK) st = launch_split_sums(s, sb);
+        if (st != PF_OK) return st;
+    }
+    const TileShape shape = p.one ? p.last.shape : p.grads.shape;
     const auto grad = [&](const float *A, i64 lda, int m, const float *Bm, i64 ldb, int n, float *out, float *sums) {
         TileProb q = tile_prob(TILE_TN, m, n, B, A, lda, Bm, ldb, out, n);
         q.o.f32 = 1;
@@ -404,67 +437,31 @@ static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
             q.sc = (i64)h * r;
             q.ssums = h;
         }
-        tile_add(c, p.grads.shape, PF_F32, q, 1);
+        tile_add(c, shape, PF_F32, q, 1);
     }
-    tile_add(c, p.grads.shape, PF_F32, grad(x, din, din, dTx, gr, gr, dVx, nullptr), 1);
-    tile_add(c, p.grads.shape, PF_F32, grad(h_prev, h, h, dTh, gr, gr, dVh, nullptr), 1);
-    return launch_tiles_linear(s, "lstm_grads", PF_F32, p.grads.shape, c);
-}
-
-// ------------------------------------------------------------------ small-batch path (B <= 32)
-// Seven launches per cell instead of two dozen: every product streams its factor once from all compute
-// units (pf_skinny.h); slice sums ride along with the gate arithmetic and with the gradient updates.
-
-// (every extent of the sliced products must hold one 16-byte load: see launch_skinny_gemm)
-static bool lstm_skinny_ok(const pf_lstm_desc *d)
-{
-    return d->B > 0 && d->B <= SK_MAX_ROWS && d->d_in >= 4 && d->h >= 4 && d->r >= 4;
-}
-
-// The four launches with sliced contractions.  Each builder fills the problem list, places the slice sums
-// from `part` on (NULL when only the size is wanted) and returns the number of floats they take.
-static size_t build_T(const pf_lstm_desc *d, const float *x, const float *hp, const float *Vx, const float *Vh,
-                      float *part, SkinnyArgs &a)
-{
-    const int B = (int)d->B, gr = (int)(d->groups * d->r);
-    a = SkinnyArgs{};
-    a.nprob = 2;
-    const i64 pc = (i64)B * gr;
-    a.p[0] = skinny_prob(B, x, d->d_in, Vx, gr, (int)d->d_in, gr, gr, pc);
-    a.p[1] = skinny_prob(B, hp, d->h, Vh, gr, (int)d->h, gr, gr, pc);
-    skinny_plan(a);
-    a.p[0].P = part;
-    a.p[1].P = part ? part + a.p[0].ksplit * pc : nullptr;
-    return (size_t)((a.p[0].ksplit + a.p[1].ksplit) * pc);
-}
-
-// z slices: the x-path problems write slices [0, ks_x), the h-path problems [ks_x, ks_x + ks_h)
-static size_t build_z(const pf_lstm_desc *d, const float *Tx, const float *Th, const float *Ux, const float *Uh,
-                      float *part, SkinnyArgs &a, int *nslices)
-{
-    const int B = (int)d->B, h = (int)d->h, r = (int)d->r, G = d->groups, gr = G * r;
-    a = SkinnyArgs{};
-    const i64 pc = (i64)B * 4 * h;
     for (int path = 0; path < 2; ++path) {
-        const float *T = path ? Th : Tx, *U = path ? Uh : Ux;
-        if (G == 1) {
-            a.p[a.nprob++] = skinny_prob(B, T, gr, U, r, r, 4 * h, 4 * h, pc);
-        } else {
-            for (int g = 0; g < 4; ++g)
-                a.p[a.nprob++] = skinny_prob(B, T ? T + (i64)g * r : nullptr, gr, U ? U + (i64)g * h * r : nullptr, r, r, h,
-                                             4 * h, pc);
-        }
+        const int m = path ? h : din;
+        TileProb q = grad(path ? h_prev : x, m, m, path ? dTh : dTx, gr, gr, path ? dVh : dVx, nullptr);
+        if (p.one && dT[path].slices > 1) q.B = dT[path].p, q.bslices = dT[path].slices, q.sstride = (i64)B * gr;
+        tile_add(c, shape, PF_F32, q, 1);
     }
-    skinny_plan(a);
-    const int per = a.nprob / 2, ksx = a.p[0].ksplit, ksh = a.p[per].ksplit;
-    for (int q = 0; q < a.nprob; ++q) {
-        const int path = q / per, g = q % per;
-        a.p[q].P = part ? part + (i64)(path ? ksx : 0) * pc + (G == 4 ? (i64)g * h : 0) : nullptr;
-    }
-    *nslices = ksx + ksh;
-    return (size_t)((ksx + ksh) * pc);
+    return launch_tiles_linear(s, p.one ? "lstm_dxh,grads" : "lstm_grads", PF_F32, shape, c);
 }
 
+// ------------------------------------------------------------------ backward, few rows and large factors
+// Every product streams its factor once from all compute units (pf_skinny.h); slice sums of dx and dh_prev ride along with the gradient
+// updates.
+
+// Backward with a factor pair per gate and large factors at few rows: 1360 units and 10 rows 37 us here, 45 on the tiled products, at 20
+// rows 41 / 45; 896 units 29 / 27.  (Every extent of the sliced products holds one 16-byte load: see launch_skinny_gemm.)
+static bool lstm_skinny_pays(const pf_lstm_desc *d)
+{
+    const double weights = (double)d->groups * d->r * (d->d_in + d->h) + 8.0 * d->h * d->r;
+    return d->B > 0 && d->B <= SK_MAX_ROWS && d->d_in >= 4 && d->h >= 4 && d->r >= 4 && d->groups == 4 && weights >= 5e6;
+}
+
+// The two launches with sliced contractions.  Each builder fills the problem list, places the slice sums
+// from `part` on (NULL when only the size is wanted) and returns the number of floats they take.
 // dT = dz U per path (per gate block when groups == 4)
 static size_t build_dT(const pf_lstm_desc *d, const float *dz, const float *Ux, const float *Uh, float *part,
                        SkinnyArgs &a)
@@ -509,51 +506,19 @@ static size_t build_dxh(const pf_lstm_desc *d, bool want_dx, const float *dTx, c
 }
 
 struct SkinnyLstmPlan {
-    size_t n_part_fwd, n_part_bwd, fwd_bytes, bwd_bytes;
+    size_t n_part_bwd, bwd_bytes;
 };
 static SkinnyLstmPlan plan_lstm_skinny(const pf_lstm_desc *d)
 {
     SkinnyLstmPlan p;
     SkinnyArgs a;
-    int ns;
-    const size_t f1 = build_T(d, nullptr, nullptr, nullptr, nullptr, nullptr, a);
-    const size_t f2 = build_z(d, nullptr, nullptr, nullptr, nullptr, nullptr, a, &ns);
-    p.n_part_fwd = f1 > f2 ? f1 : f2;
     const size_t b1 = build_dT(d, nullptr, nullptr, nullptr, nullptr, a);
     const size_t b2 = build_dxh(d, true, nullptr, nullptr, nullptr, nullptr, nullptr, a);
     p.n_part_bwd = b1 > b2 ? b1 : b2;
-    p.fwd_bytes = align_up(p.n_part_fwd * sizeof(float));
     p.bwd_bytes = align_up((size_t)(d->B * 4 * d->h) * sizeof(float)) +
                   2 * align_up((size_t)(d->B * d->groups * d->r) * sizeof(float)) +
                   align_up(p.n_part_bwd * sizeof(float));
     return p;
-}
-
-static int lstm_fwd_skinny(const pf_lstm_desc *d, const float *x, const float *h_prev, const float *c_prev,
-                           const float *Vx, const float *Ux, const float *Vh, const float *Uh, const float *bias,
-                           float *h_out, float *c_out, float *gates, float *Tx, float *Th, Workspace &ws, hipStream_t s)
-{
-    const int B = (int)d->B, h = (int)d->h, gr = (int)(d->groups * d->r);
-    const SkinnyLstmPlan p = plan_lstm_skinny(d);
-    float *part = ws.take<float>(p.n_part_fwd);
-    SkinnyArgs a;
-    build_T(d, x, h_prev, Vx, Vh, part, a);
-    int st = launch_skinny_gemm(s, "lstm_T=[x*Vx|h*Vh]", a, false);
-    if (st != PF_OK) return st;
-    SliceSumArgs ss = {};
-    ss.nseg = 2;
-    ss.s[0] = slice_seg(a.p[0], Tx, gr, gr);
-    ss.s[1] = slice_seg(a.p[1], Th, gr, gr);
-    st = launch_slice_sum(s, ss);
-    if (st != PF_OK) return st;
-    int nslices = 0;
-    build_z(d, Tx, Th, Ux, Uh, part, a, &nslices);
-    st = launch_skinny_gemm(s, "lstm_z=[Tx|Th]*[Ux|Uh]t", a, true);
-    if (st != PF_OK) return st;
-    dim3 grid((unsigned)(((i64)B * h + 255) / 256));
-    PF_LAUNCH(st, "lstm_pointwise_fwd", lstm_slices_pointwise_fwd_kernel, grid, dim3(256), s, part, nslices,
-              (i64)B * 4 * h, d->has_bias ? bias : nullptr, (const float *)nullptr, c_prev, h_out, c_out, gates, B, h);
-    return st;
 }
 
 static int lstm_bwd_skinny(const pf_lstm_desc *d, const float *x, const float *h_prev, const float *c_prev,
@@ -620,17 +585,15 @@ extern "C" {
 size_t pf_lowrank_lstm_cell_fwd_workspace_bytes(const pf_lstm_desc *d)
 {
     if (check_lstm_desc(d) != PF_OK) return 0;
-    return lstm_skinny_ok(d)  ? plan_lstm_skinny(d).fwd_bytes
-           : lstm_tiles_ok(d) ? plan_lstm_tiles(d).fwd_bytes
-                              : plan_lstm(d).fwd_bytes;
+    return lstm_tiles_ok(d) ? plan_lstm_tiles(d).fwd_bytes : plan_lstm(d).fwd_bytes;
 }
 
 size_t pf_lowrank_lstm_cell_bwd_workspace_bytes(const pf_lstm_desc *d)
 {
     if (check_lstm_desc(d) != PF_OK) return 0;
-    return lstm_skinny_ok(d)  ? plan_lstm_skinny(d).bwd_bytes
-           : lstm_tiles_ok(d) ? plan_lstm_tiles(d).bwd_bytes
-                              : plan_lstm(d).bwd_bytes;
+    return lstm_skinny_pays(d) ? plan_lstm_skinny(d).bwd_bytes
+           : lstm_tiles_ok(d)  ? plan_lstm_tiles(d).bwd_bytes
+                               : plan_lstm(d).bwd_bytes;
 }
 
 int pf_lowrank_lstm_cell_fwd(const pf_lstm_desc *d, const void *x, const void *h_prev, const void *c_prev,
@@ -650,11 +613,6 @@ int pf_lowrank_lstm_cell_fwd(const pf_lstm_desc *d, const void *x, const void *h
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
-    if (lstm_skinny_ok(d))
-        return lstm_fwd_skinny(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)Vx,
-                               (const float *)Ux, (const float *)Vh, (const float *)Uh, (const float *)bias,
-                               (float *)h_out, (float *)c_out, (float *)gates_save, (float *)Tx_save, (float *)Th_save,
-                               ws, (hipStream_t)stream);
     if (lstm_tiles_ok(d))
         return lstm_fwd_tiles(d, (const float *)x, (const float *)h_prev, (const float *)c_prev, (const float *)Vx,
                               (const float *)Ux, (const float *)Vh, (const float *)Uh, (const float *)bias, (float *)h_out,
@@ -687,7 +645,7 @@ int pf_lowrank_lstm_cell_bwd(const pf_lstm_desc *d, const void *x, const void *h
     if (need > 0 && (!workspace || workspace_bytes < need)) return PF_ERR_WORKSPACE;
     if (pf::any_misaligned({workspace}, 256)) return PF_ERR_UNSUPPORTED; // NULL passes: the size check has caught it
     Workspace ws(workspace, workspace_bytes);
-    if (lstm_skinny_ok(d))
+    if (lstm_skinny_pays(d))
         return lstm_bwd_skinny(d, (const float *)x, (const float *)h_prev, (const float *)c_prev,
                                (const float *)c_out, (const float *)gates_saved, (const float *)Tx_saved,
                                (const float *)Th_saved, (const float *)Vx, (const float *)Ux, (const float *)Vh,

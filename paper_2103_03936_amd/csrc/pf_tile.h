@@ -328,7 +328,7 @@ struct SlicePiece {
     }
 };
 
-// LoadKC of such an operand; copy (nullable): the sums leave once more, as a matrix [rows][K] of the call's type
+// LoadKC of such an operand; copy (nullable): the sums leave once more, in the call's type and with the operand's leading dimension
 template <typename CT, int ROWS, int DEEP = 1>
 struct LoadKCS {
     typedef typename TileEl<CT>::elem elem;
@@ -338,13 +338,13 @@ struct LoadKCS {
                          P = ROWS * CPR / NT, CH = P * SP::CH, LDS = ROWS * PITCH, XF = 1;
     const float *rp[P];
     elem *copy;
-    i64 stride, jump;
+    i64 ld, stride, jump;
     int K, kc, row, row0, rows, kl, ks, slices, seg;
 
-    __device__ __forceinline__ void init(const void *p, i64 ld, int rows_, int K_, int row0_, int kbeg, int tid, int slices_, i64 stride_,
+    __device__ __forceinline__ void init(const void *p, i64 ld_, int rows_, int K_, int row0_, int kbeg, int tid, int slices_, i64 stride_,
                                          int seg_, i64 jump_, void *copy_)
     {
-        K = K_, rows = rows_, row0 = row0_, slices = slices_, stride = stride_, seg = seg_, jump = jump_;
+        ld = ld_, K = K_, rows = rows_, row0 = row0_, slices = slices_, stride = stride_, seg = seg_, jump = jump_;
         copy = (elem *)copy_;
         kc = (tid % CPR) * V;
         row = tid / CPR;
@@ -368,7 +368,7 @@ struct LoadKCS {
         for (int i = 0; i < P; ++i) {
             uint4 v = SP::sum(&r[i * SP::CH], slices);
             const int m = row0 + row + i * (NT / CPR);
-            if (copy && m < rows) stg16(copy + (i64)m * K + k, v); // (a piece that was pulled back holds what its neighbour writes)
+            if (copy && m < rows) stg16(copy + (i64)m * ld + k, v); // (a piece that was pulled back holds what its neighbour writes)
             if (EDGE && s) v = piece_shift<sizeof(elem)>(v, s);
             *(uint4 *)&lds[(row + i * (NT / CPR)) * PITCH + kc] = v;
         }

@@ -50,12 +50,12 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
     const bool bf = dtype == PF_BF16;
     const int bk = bf ? 64 : 32;
     static const TileShape tries[4] = {TS_32, TS_64, TS_128x64, TS_128};
-    TileGroup best = {TS_64, {1, 1, 1, 1}, 1e30};
+    TileGroup best = {TS_64, {1, 1, 1, 1, 1, 1}, 1e30};
     for (TileShape sh : tries) {
         const ChunkCost cc = chunk_cost(bf, sh);
         const i64 bm = SHAPES[sh].bm, bn = SHAPES[sh].bn;
         for (int most = 2; most <= (1 << 20); most *= 2) { // chunks a workgroup of a split product may have
-            TileGroup g = {sh, {1, 1, 1, 1}, 0};
+            TileGroup g = {sh, {1, 1, 1, 1, 1, 1}, 0};
             double total = 0, longest = 0, part = 0, count = 0;
             bool any = false, last = true;
             for (int i = 0; i < n; ++i) {
@@ -139,22 +139,44 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
 }
 
 // (a workgroup of the readers brings its slices in at 50 bytes a clock; bf16 at 25, for its own intermediate is half of one of them)
-MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most)
+MidGroup plan_mid_group(int dtype, const TileNeed *need, int n, TileShape reader, i64 all, i64 most)
 {
-    MidPlan best = {plan_tiles(dtype, M, N, K, max_split), false};
+    MidGroup best = {plan_tile_group(dtype, need, n), false};
     if (reader != TS_32 && reader != TS_32D) return best;
     const ChunkCost cc = chunk_cost(dtype == PF_BF16, TS_32);
-    const i64 tiles = ((M + 31) / 32) * ((N + 31) / 32), chunks = (K + (dtype == PF_BF16 ? 63 : 31)) / (dtype == PF_BF16 ? 64 : 32);
+    const int bk = dtype == PF_BF16 ? 64 : 32;
     const double rate = dtype == PF_BF16 ? 25 : 50;
     for (int ks = 2; ks <= TILE_MAX_SLICES; ++ks) {
-        const i64 per = (chunks + ks - 1) / ks, count = tiles * ks;
-        if ((ks - 1) * per >= chunks) continue; // (an empty split)
-        const bool deep = count <= 256 && per >= 8;
-        const double own = ceil(count / 256.0) * (per * cc.work + cc.tile), alone = per * cc.one * (deep ? 0.85 : 1) + cc.tile;
+        i64 count = 0, longest = 0, shortest = 1 << 30;
+        double total = 0;
+        bool empty = false;
+        for (int i = 0; i < n; ++i) {
+            const i64 tiles = ((need[i].M + 31) / 32) * ((need[i].N + 31) / 32), chunks = (need[i].K + bk - 1) / bk, per = (chunks + ks - 1) / ks;
+            empty = empty || (ks - 1) * per >= chunks;
+            count += tiles * ks;
+            total += (double)tiles * ks * (per * cc.work + cc.tile);
+            longest = per > longest ? per : longest;
+            shortest = per < shortest ? per : shortest;
+        }
+        if (empty) continue;
+        const bool deep = count <= 256 && shortest >= 8;
+        const double own = ceil(count / 256.0) * total / count, alone = longest * cc.one * (deep ? 0.85 : 1) + cc.tile;
         const double cost = (own > alone ? own : alone) + 3000 + ks * (all > 256 * most ? all / 256.0 : most) / rate;
-        if (cost < best.t.cost) best = MidPlan{TilePlan{deep ? TS_32D : TS_32, ks, cost}, true};
+        if (cost >= best.g.cost) continue;
+        best.g.shape = deep ? TS_32D : TS_32;
+        for (int i = 0; i < n; ++i) best.g.ksplit[i] = ks;
+        best.g.cost = cost;
+        best.sliced = true;
     }
     return best;
+}
+
+MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most)
+{
+    const TileNeed need = {M, N, K, true};
+    const MidGroup m = plan_mid_group(dtype, &need, 1, reader, all, most);
+    if (!m.sliced) return MidPlan{plan_tiles(dtype, M, N, K, max_split), false};
+    return MidPlan{TilePlan{m.g.shape, m.g.ksplit[0], m.g.cost}, true};
 }
 
 void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &q, int ksplit)

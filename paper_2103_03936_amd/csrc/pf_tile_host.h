@@ -49,7 +49,7 @@ struct TileProb {
     i64 ajump, bjump;      // of its own, this many elements after the one before
     const float *ascale;
     int aslices, bslices;  // > 1: A of TILE_NT, B of TILE_TN are that many partial sums (float) of the operand, `sstride` floats
-    i64 sstride;           // apart; acopy (nullable): [M][K], their sums in the call's type
+    i64 sstride;           // apart; acopy (nullable): their sums in the call's type, rows lda apart
     void *acopy;
     PixView pa, pb;
     TileOut o;
@@ -75,14 +75,6 @@ struct TilePlan {
 // The tile shape and k-split that should finish first, at most max_split ways.
 TilePlan plan_tiles(int dtype, i64 M, i64 N, i64 K, int max_split);
 
-// The same for an intermediate M x N whose readers can take its partial sums instead (TileProb::aslices): `all` bytes of it go into
-// their workgroups, `most` of them into one.  sliced: they are to do so, ksplit of them.
-struct MidPlan {
-    TilePlan t;
-    bool sliced;
-};
-MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most);
-
 // Several products in one launch (one tile shape); those marked may split their contraction.
 struct TileNeed {
     i64 M, N, K;
@@ -91,10 +83,23 @@ struct TileNeed {
 };
 struct TileGroup {
     TileShape shape;
-    int ksplit[4];
+    int ksplit[6];
     double cost;
 };
 TileGroup plan_tile_group(int dtype, const TileNeed *need, int n);
+
+// The same for intermediates whose readers can take their partial sums instead (TileProb::aslices, bslices): `all` bytes of them go into
+// the readers' workgroups, `most` into one.  sliced: they are to do so.
+struct MidGroup {
+    TileGroup g;
+    bool sliced;
+};
+MidGroup plan_mid_group(int dtype, const TileNeed *need, int n, TileShape reader, i64 all, i64 most);
+struct MidPlan { // of one intermediate M x N
+    TilePlan t;
+    bool sliced;
+};
+MidPlan plan_mid(int dtype, i64 M, i64 N, i64 K, int max_split, TileShape reader, i64 all, i64 most);
 
 void tile_add(TileArgs &a, TileShape shape, int dtype, const TileProb &p, int ksplit);
 // The last problem goes with the one before it (TileProb::pair).

@@ -93,7 +93,7 @@ int emu_tiles(TileShape shape, const TileArgs &a)
                     for (int k = 0; k < p.K; ++k)
                         for (int s = 0; s < ns; ++s) row[k] += A[s * p.sstride + k];
                     if (p.acopy) {
-                        float *to = (float *)p.acopy + z * p.sa + (i64)m * p.K;
+                        float *to = (float *)p.acopy + z * p.sa + m * p.lda;
                         CHK(to, p.K, "tiles A copy");
                         for (int k = 0; k < p.K; ++k) to[k] = (float)row[k];
                     }

@@ -60,6 +60,14 @@ def test_lstm_cell(shape, groups):
     test_gpu_lstm._cell(*shape, groups, seed=23)
 
 
+@pytest.mark.parametrize("groups", [1, 4])
+@pytest.mark.parametrize("shape", [(1, 515, 260, 65), (20, 700, 516, 129), (33, 1030, 900, 225), (3, 1302, 1360, 341), (64, 70, 1500, 375)])
+def test_lstm_cell_slices(shape, groups):
+    """Slices of T and dT that their readers add, dx and dh_prev beside the gradients and in a launch of their own; the fourth one's
+    backward direction with a pair per gate is on the streaming kernels."""
+    test_gpu_lstm._cell(*shape, groups, seed=27)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3),
                                    (6100, 264, 330, 128, 3), (6100, 380, 378, 128, 3)])
