@@ -240,6 +240,9 @@ static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 51
 // -> 83 -> 2016 16.0 / 19.3); at rank 128 and widths in multiples of 256 those of the chain kernel, fitted to 130 shapes.  Over the 785
 // shapes 1.42 times as fast where it is taken, three of a thousand calls more than 5 % slower; over 60 of the others 1.14 (8192 x 512 -> 128 -> 512 three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by
 // both); few rows and inputs up to 1024 wide stay with the row kernel (423 x 512 -> 512: 6.6 against 7.3).
+// Ranks from 136 to 256: tiled products fitted by themselves to 330 shapes of 64 to 19000 rows (7 % rms).  Taken for 128 of them, 1.31 times as
+// fast, none more than a tenth slower (8192 x 640 -> 160 -> 2560 37.4 / 20.8 us, tiled / two-stage; 13797 x 448 -> 176 -> 3584 68.7 / 36.9; with
+// few rows the tiles spread better: 1000 x 768 -> 192 -> 3072 12.4 / 14.9).
 static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
 {
     if (!linear_two_supported(M, in, out, r) || rows_fwd_pays(M, in, out, r, G)) return 0;
@@ -248,6 +251,12 @@ static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
     const double chain = 8.07 + m * (0.625 * G * out + 0.205 * (in + G * out)) + 2.44e-3 * in;
     if (linear_chain2_supported(in, out, r)) return t < chain ? rows : 0;
     const double odd = r % 8 ? 1 : 0, wide = r > 64 ? 1 : 0, tiles = (double)G * ((M + 63) / 64) * ((r + 63) / 64);
+    if (r > 128) {
+        const double rt = (double)((r + 63) / 64);
+        const double tiled = 8.76 + m * G * (out * (0.485 + 0.235 * rt) + 0.227 * in * rt + 0.502 * r) + (0.746e-3 + (tiles > 100 ? 0.986e-3 : 0)) * in +
+                             (in >= 512 && tiles < 200 ? 0.23 : 0) + 4.43e-3 * r + 1.89e-4 * G * out;
+        return t < 0.92 * tiled ? rows : 0;
+    }
     const double tiled = 8.37 + m * (0.359 * in + G * out * (0.808 + 0.22 * ((r + 63) / 64)) + 0.172 * odd * (in + G * out)) + 0.69 * odd + 0.52 * wide +
                          (1.07e-3 + (tiles > 100 ? 0.49e-3 : 0)) * in + (in >= 512 && tiles < 200 ? 0.67 : 0);
     // chunks of the first stage, pieces of outputs, rounds of workgroups
@@ -278,12 +287,19 @@ static bool plain_chain_pays(i64 M, i64 in, i64 out, i64 r, int G = 1)
 // tenth slower with both, 6851 x 512 -> 40 -> 176 19.6 / 22.0).  512 -> 128 -> 2048, us, before / now: 44.5 / 40.3 at 8192
 // rows; 2048 -> 512 with mask 53.9 / 42.1, at 16384 rows 102 / 66; 1536 -> 96 -> 384 52.0 / 31.8.  Few rows stay with the tiled products,
 // which form dX and the gradients side by side (1000 rows, 512 -> 512: 13.5 / 19.2).
+// Ranks from 136 to 256, fitted by themselves to 330 shapes (8 and 7 % rms): taken for 84, 1.34 times as fast, none more than a tenth slower
+// (8192 rows, 640 -> 160 -> 2560 79.7 / 52.3, 3072 -> 192 -> 768 88.1 / 56.4; 3001 x 640 -> 160 -> 2560 39.4 / 42.6 stays).
 static int two_bwd_rows(i64 M, i64 in, i64 out, i64 r, int &split)
 {
     if (!linear_two_supported(M, out, in, r) || !plan_linear_grad(M, in, out, r).splits) return 0;
     int rows = 0;
     const LinGradPlan lg = plan_linear_grad(M, in, out, r);
     const double m = 1e-6 * M, w = (double)(in + out), tiles = ceil(M / 64.0) * ceil(r / 64.0), t = plan_linear_two(M, out, in, r, 1, rows, split);
+    if (r > 128) {
+        const double before = 9.38 + m * (2.27 * in + 0.984 * out + 3.3 * r + 0.415 * w * ceil(r / 64.0)) + 1.24e-3 * out;
+        const double now = 10.4 + 0.898 * t + (0.619 + 0.00297 * r) * lg.per + 1.246e-6 * lg.splits * w * r + m * 0.12 * in + 5.5e-4 * w;
+        return now < 0.92 * before ? rows : 0;
+    }
     const double coarse_before = 11.56 + m * (1.488 * in + 0.699 * out + 6.26 * r + 0.00717 * w * r) + 2.1e-4 * w;
     const double coarse_now = 12.74 + m * (0.367 * w + 7.75 * r + 0.00246 * w * r) + 8.9e-4 * w + 2.24e-5 * w * r;
     if (coarse_now >= 0.97 * coarse_before) return 0;

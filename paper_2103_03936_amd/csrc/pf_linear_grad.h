@@ -23,7 +23,7 @@ struct LinGradPlan {
     int splits, per; // 0: not taken
 };
 
-// Whole 16-byte pieces, ranks up to 128
+// Whole 16-byte pieces, ranks up to 256
 bool linear_grad_supported(i64 M, i64 in, i64 out, i64 r);
 LinGradPlan plan_linear_grad(i64 M, i64 in, i64 out, i64 r);
 int launch_linear_grad(hipStream_t s, const LinGradArgs &a);

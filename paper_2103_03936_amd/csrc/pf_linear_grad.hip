@@ -9,13 +9,14 @@ namespace pf {
 // much a compute unit has in flight towards memory, so three chunks of 64 rows (96 KB at rank 128) are in registers behind the two in
 // LDS, through descriptors (BufSrc) and without a condition, so that a wait is for the oldest of them alone.  A chunk takes 2000 clocks
 // where 240 workgroups load 9.2 TB/s, 5 of them from HBM (16384 x 2048 and x 512, rank 128: 27.6 us; 8192 18.3, of which 9 are launch, first
-// load and 16 MB of partial sums).  8192 rows, 512 -> 2048 and 2048 -> 512: 22.0 on the kernel of pf_linear_wgrad.hip with two tiles in flight.
+// load and 16 MB of partial sums).  Ranks above 128 are six or eight blocks (FLAT: the ranks' chunk dealt out over its run of memory).  8192 rows, 512 -> 2048 and 2048 -> 512: 22.0 on the kernel of pf_linear_wgrad.hip with two tiles in flight.
 template <int RB>
 struct LinGradCfg {
     static constexpr int NT = 512, KC = 64, R = 32 * RB, RING = 3;
-    static constexpr int WM = 2, WN = RB > 1 ? RB / 2 : 1, WK = 8 / (WM * WN), NB = RB > 1 ? 2 : 1, STEPS = KC / 16; // 64 columns by 64 ranks
+    static constexpr int WM = 2, WN = RB > 1 ? RB / 2 : 1 /* (three of them: two wavefronts without ranks) */, WK = 8 / (WM * WN), NB = RB > 1 ? 2 : 1, STEPS = KC / 16; // 64 columns by 64 ranks
     static constexpr int AP = 128 + 8, BP = R + 8, ABYTES = KC * AP * 2, BBYTES = KC * BP * 2, BUF = ABYTES + BBYTES;
     static constexpr int ACH = KC * 16 / NT, BPIECES = KC * RB * 4, BCH = BPIECES / NT > 0 ? BPIECES / NT : 1; // pieces per thread
+    static constexpr bool FLAT = RB > 4; // the ranks' chunk, one run of memory, is dealt out piece by piece
     static constexpr int SP = R + 4, SBYTES = WK * 128 * SP * 4;
     static constexpr int BYTES = (2 * BUF > SBYTES ? 2 * BUF : SBYTES) + 8 * 128 * 4;
     static_assert(STEPS % WK == 0 && BYTES <= 160 * 1024, "");
@@ -37,6 +38,11 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
     constexpr int ASTEP = F::NT / 16, BSTEP = F::NT / (RB * 4);
     uint4 ar[F::RING][F::ACH], br[F::RING][F::BCH];
     const bool ain = col0 + acol < cols, bin = bcol < r && brow < F::KC;
+    const int per = r / 8;
+    int flat[F::BCH]; // where a thread's pieces of the ranks' chunk lie in LDS
+#pragma unroll
+    for (int u = 0; u < F::BCH; ++u)
+        flat[u] = F::FLAT ? (tid + F::NT * u) / per * (F::BP * 2) + (tid + F::NT * u) % per * 16 : (brow + BSTEP * u) * (F::BP * 2) + bcol * 2;
     const auto load = [&](int q, uint4 (&x)[F::ACH], uint4 (&y)[F::BCH]) __attribute__((always_inline)) {
         const int row = begin + q * F::KC;
 #pragma unroll
@@ -46,6 +52,11 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
         }
 #pragma unroll
         for (int u = 0; u < F::BCH; ++u) {
+            if constexpr (F::FLAT) {
+                const int at = row * r + (tid + F::NT * u) * 8; // (a run's rows times r: below 2^30)
+                y[u] = sB.load(((tid + F::NT * u < F::KC * per) & (at < end * r)) ? 2u * (uint32_t)at : BUF_OUT);
+                continue;
+            }
             const int i = row + brow + BSTEP * u;
             y[u] = sB.load((bin & (i < end)) ? 2u * ((uint32_t)i * (uint32_t)r + bcol) : BUF_OUT);
         }
@@ -65,11 +76,12 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
         }
 #pragma unroll
         for (int u = 0; u < F::BCH; ++u)
-            if (F::BPIECES >= F::NT || brow < F::KC) *(uint4 *)(buf + F::ABYTES + (brow + BSTEP * u) * (F::BP * 2) + bcol * 2) = y[u];
+            if (F::FLAT ? tid + F::NT * u < F::KC * per : F::BPIECES >= F::NT || brow < F::KC) *(uint4 *)(buf + F::ABYTES + flat[u]) = y[u];
     };
 #pragma unroll
     for (int i = 0; i < F::RING; ++i) load(i, ar[i], br[i]);
     const int wk = wave / (F::WM * F::WN), wm = wave / F::WN % F::WM, wn = wave % F::WN;
+    const bool ranks = F::WM * F::WN * F::WK == 8 || __builtin_amdgcn_readfirstlane(wave) < F::WM * F::WN * F::WK;
     f32x16_t acc[2][F::NB]; // [block of columns][block of ranks]
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -82,6 +94,7 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
     const auto step = [&](int q, const unsigned char *buf, unsigned char *next, uint4 (&x)[F::ACH], uint4 (&y)[F::BCH]) __attribute__((always_inline)) {
         __syncthreads();
         const uint16_t *as = (const uint16_t *)buf, *bs = (const uint16_t *)(buf + F::ABYTES);
+        if (ranks)
 #pragma unroll
         for (int s = 0; s < F::STEPS / F::WK; ++s) {
             const int k0 = (wk * (F::STEPS / F::WK) + s) * 16;
@@ -117,6 +130,7 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
 
     __syncthreads();
     float *ss = (float *)smem, *cs = (float *)(smem + F::BYTES - 8 * 128 * 4);
+    if (ranks)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -155,7 +169,7 @@ __global__ __launch_bounds__(512, 2) void linear_grad_kernel(LinGradArgs a)
 bool linear_grad_supported(i64 M, i64 in, i64 out, i64 r)
 {
     const i64 lim = 1LL << 30; // (descriptors of less than 2^31 bytes: of both matrices)
-    return M >= 64 && in >= 8 && out >= 8 && in % 8 == 0 && out % 8 == 0 && r >= 8 && r <= 128 && r % 8 == 0 && M * in < lim && M * out < lim && M * r < lim;
+    return M >= 64 && in >= 8 && out >= 8 && in % 8 == 0 && out % 8 == 0 && r >= 8 && r <= 256 && r % 8 == 0 && M * in < lim && M * out < lim && M * r < lim;
 }
 
 // One workgroup to a compute unit, in one round, of at least two chunks.
@@ -182,7 +196,9 @@ int launch_linear_grad(hipStream_t s, const LinGradArgs &a)
     const dim3 grid((unsigned)(tiles * a.splits)), block(512);
     if (a.r <= 32) PF_LAUNCH(st, "linear_grads", linear_grad_kernel<1>, grid, block, s, a);
     else if (a.r <= 64) PF_LAUNCH(st, "linear_grads", linear_grad_kernel<2>, grid, block, s, a);
-    else PF_LAUNCH(st, "linear_grads", linear_grad_kernel<4>, grid, block, s, a);
+    else if (a.r <= 128) PF_LAUNCH(st, "linear_grads", linear_grad_kernel<4>, grid, block, s, a);
+    else if (a.r <= 192) PF_LAUNCH(st, "linear_grads", linear_grad_kernel<6>, grid, block, s, a);
+    else PF_LAUNCH(st, "linear_grads", linear_grad_kernel<8>, grid, block, s, a);
     return st;
 }
 

@@ -1,4 +1,4 @@
-// The factorized fully connected layer forward in one launch, in bf16, ranks up to 128, any widths that are whole 16-byte pieces:
+// The factorized fully connected layer forward in one launch, in bf16, ranks up to 128 (256 in whole 16-byte pieces), any widths in whole pieces:
 //     mid[rows][r] = in[rows][K] W1[K][r],   out[rows][N] = act(mid W2[N][r]^T + bias + add)
 // and backward with in = dY, W1 = U, W2 = V, mid = dT, out = dX.
 // (pf_linear_chain.h has the kernel for rank 128 and widths that are multiples of 256.)
@@ -21,7 +21,7 @@ struct LinTwoArgs {
 };
 
 bool linear_two_supported(i64 M, i64 K, i64 N, i64 r);
-// Rows per workgroup (32, 64 or 128) and shares of the outputs for the least time; microseconds
+// Rows per workgroup (32, 64 or 128; above rank 128 at most 64, above 192 32) and shares of the outputs for the least time; microseconds
 double plan_linear_two(i64 M, i64 K, i64 N, i64 r, int groups, int &rows, int &osplit);
 int launch_linear_two(hipStream_t s, const char *name, const LinTwoArgs &a, int rows);
 

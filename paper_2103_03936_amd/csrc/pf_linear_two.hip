@@ -11,24 +11,28 @@ namespace pf {
 // chain of barrier, LDS reads, eight dependent products and the way of the outputs through LDS: 128 outputs of 32 rows take 1500 clocks,
 // with all of them alone under 600 each.  2000 rows, 256 -> rank 64 -> 1024: 10.4 us on the tiled products (two or three launches),
 // 6.6 before the pipelining, 5.9; 8192 x 512 -> 128 -> 512, three layers side by side 30.1 -> 19.0; 500 x 512 -> 128 -> 2048 18.8 -> 14.6.
-// Above rank 128 the tiled products are faster, and backward they form dX beside the gradients (500 x 384 -> 96 -> 384: 10.7 against 13.0
-// with both stages here).
+// Backward the tiled products form dX beside the gradients (500 x 384 -> 96 -> 384: 10.7 against 13.0 with both stages here).
+// Ranks from 136 to 256 in whole pieces (FLAT) have five, six or eight blocks: a wavefront per block in the first stage, up to 64 rows (32
+// above rank 192: the LDS of a compute unit).  The widths of such factors are no powers of two, so their pieces are dealt out over the
+// chunk, one run of memory; by rows, a fifth to a third of the loads would be of nothing.  8192 rows, tiled products / this: 640 -> 160
+// -> 2560 37.4 / 20.8 us, 768 -> 192 -> 3072 40.4 / 26.1, 1024 -> 256 -> 1024 26.8 / 24.3.
 // WM x WN wavefronts over (ranks, rows), WK of them split the contraction of the first stage; the second takes 128 outputs at a time.
 template <int RB, int MB>
 struct LinTwoCfg {
-    static constexpr int NT = 512, MR = 32 * MB, Kp = 32 * RB, KC = RB == 4 && MB == 4 ? 64 : 128;
+    static constexpr int NT = 512, MR = 32 * MB, Kp = 32 * RB, KC = RB == 8 || (RB == 4 && MB == 4) ? 64 : 128;
+    static constexpr bool FLAT = RB > 4; // a factor's chunk, which is one run of memory, is dealt out piece by piece, and some wavefronts have no ranks
     static constexpr int WM = RB, WN = 8 / RB < MB ? 8 / RB : MB, WK = 8 / (WM * WN), NB = MB / WN, STEPS = KC / 16 / WK;
     static constexpr int VP = Kp + 8, XP = KC + 8;                                          // pitches (elements)
-    static constexpr int VCH = KC * RB * 4 / NT, XCH = MR * KC / 8 / NT > 0 ? MR * KC / 8 / NT : 1; // pieces per thread
+    static constexpr int VCH = (KC * RB * 4 + NT - 1) / NT, XCH = MR * KC / 8 / NT > 0 ? MR * KC / 8 / NT : 1; // pieces per thread
     static constexpr int VBYTES = KC * VP * 2, XBYTES = MR * XP * 2, BUF = VBYTES + XBYTES;
     static constexpr int SP = Kp + 4, SBYTES = WK > 1 ? WK * MR * SP * 4 : 0;                // sums of the first stage
     // second stage: a wavefront has 32 outputs of NB2 blocks of rows
-    static constexpr int OC = 128, NB2 = MB < 4 ? 1 : 2, AP = Kp + 8, ABYTES = OC * AP * 2, ACH = OC * RB * 4 / NT;
+    static constexpr int OC = 128, NB2 = MB < 4 ? 1 : 2, AP = Kp + 8, ABYTES = OC * AP * 2, ACH = (OC * RB * 4 + NT - 1) / NT;
     static constexpr int TP = Kp + 8, TBYTES = MR * TP * 2, OP = OC + 8, OBYTES = MR * OP * 2, BIAS = OC * 2;
     static constexpr int S1 = TBYTES + (2 * BUF > SBYTES ? 2 * BUF : SBYTES);
     static constexpr int O0 = 0, A0 = TBYTES > 2 * OBYTES ? TBYTES : 2 * OBYTES, B0 = A0 + 2 * ABYTES, S2 = B0 + 2 * BIAS; // (mid is gone when outputs come)
     static constexpr int BYTES = S1 > S2 ? S1 : S2;
-    static_assert(KC / 16 % WK == 0 && 2 * RB % ACH == 0, "whole steps");
+    static_assert(KC / 16 % WK == 0 && 2 * RB % ACH == 0 && WK >= 1, "whole steps");
     static_assert(BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
@@ -83,18 +87,32 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     const int steps = (K + KC - 1) / KC;
     // A thread's pieces lie in one column of the factor and one of the input.
     const BufSrc sV(W1, 2LL * K * r), sX(a.in, 2LL * M * K), sU(W2, 2LL * N * r), sB(bias, 2LL * N), sA(a.add, 2LL * M * N), sM(a.mask, 2LL * M * N), sY(out, 2LL * M * N);
-    const int vrow = tid / (RB * 4), vcol = tid % (RB * 4), xrow = tid / (KC / 8), xcol = tid % (KC / 8) * 8;
+    const int per = r / 8, vrow = tid / (RB * 4), vcol = tid % (RB * 4), xrow = tid / (KC / 8), xcol = tid % (KC / 8) * 8;
     constexpr int VSTEP = NT / (RB * 4), XSTEP = NT / (KC / 8);
     const bool vin = vcol * 8 < r;
+    int flat[F::FLAT ? F::ACH : 1]; // where a thread's pieces of a chunk of either factor lie in LDS
+    if constexpr (F::FLAT) {
+        static_assert(F::VP == F::AP && F::VCH <= F::ACH, "both factors' chunks lie alike");
+#pragma unroll
+        for (int u = 0; u < F::ACH; ++u) flat[u] = (tid + NT * u) / per * (F::AP * 2) + (tid + NT * u) % per * 16;
+    }
     uint32_t xat[F::XCH];
 #pragma unroll
     for (int u = 0; u < F::XCH; ++u) xat[u] = (uint32_t)(m0 + xrow + XSTEP * u) * (uint32_t)K + xcol;
     const auto load_v = [&](int q, int u) __attribute__((always_inline)) {
+        if constexpr (F::FLAT) {
+            vr[u] = sV.load(tid + NT * u < KC * per ? 2u * (uint32_t)(q * KC * r + (tid + NT * u) * 8) : BUF_OUT);
+            return;
+        }
         const int row = q * KC + vrow + VSTEP * u;
         vr[u] = EVEN ? sV.load(vin ? 2u * (uint32_t)(row * r + vcol * 8) : BUF_OUT) : LinPiece(row, vcol, K, r).load(W1, K * r);
     };
     const auto load_x = [&](int q, int u, uint4 &x) __attribute__((always_inline)) { x = sX.load(q * KC + xcol < K ? 2u * (xat[u] + q * KC) : BUF_OUT); };
     const auto store_v = [&](int q, int u, unsigned char *buf) __attribute__((always_inline)) { // (ranks past the last are sums that nobody reads)
+        if constexpr (F::FLAT) {
+            if (tid + NT * u < KC * per) *(uint4 *)(buf + flat[u]) = vr[u];
+            return;
+        }
         *(uint4 *)(buf + (vrow + VSTEP * u) * (F::VP * 2) + vcol * 16) = EVEN ? vr[u] : LinPiece(q * KC + vrow + VSTEP * u, vcol, K, r).fix(vr[u], K * r);
     };
     const auto store_x = [&](int u, unsigned char *buf, const uint4 &x) __attribute__((always_inline)) {
@@ -107,6 +125,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
 #pragma unroll
     for (int u = 0; u < F::XCH; ++u) load_x(1, u, xr[1][u]);
     const int wk = wave / (F::WM * F::WN), wm = wave / F::WN % F::WM, wn = wave % F::WN;
+    const bool ranks = !F::FLAT || __builtin_amdgcn_readfirstlane(wave) < F::WM;
     f32x16_t acc[F::NB];
 #pragma unroll
     for (int j = 0; j < F::NB; ++j)
@@ -133,12 +152,13 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
             for (int j = 0; j < F::NB; ++j)
                 b[s & 1][j] = *(const bf16x8_t *)(buf + F::VBYTES + ((wn * F::NB + j) * 32 + (lane & 31)) * (F::XP * 2) + (st * 16 + hi * 8) * 2);
         };
-        frags(0);
+        if (ranks) frags(0);
 #pragma unroll
         for (int s = 0; s < F::STEPS; ++s) {
-            if (s + 1 < F::STEPS) frags(s + 1);
+            if (ranks && s + 1 < F::STEPS) frags(s + 1);
 #pragma unroll
-            for (int j = 0; j < F::NB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s & 1], b[s & 1][j], acc[j], 0, 0, 0);
+            for (int j = 0; j < F::NB; ++j)
+                if (ranks) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s & 1], b[s & 1][j], acc[j], 0, 0, 0);
 #pragma unroll
             for (int u = 0; u < F::XCH; ++u)
                 if (u * F::STEPS / F::XCH == s) {
@@ -162,6 +182,7 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
 
     // the sums -> LDS in bf16, zero past the last rank whatever the input holds
     if constexpr (F::WK == 1) {
+        if (ranks)
 #pragma unroll
         for (int j = 0; j < F::NB; ++j)
 #pragma unroll
@@ -211,10 +232,18 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     uint16_t *os0 = (uint16_t *)(lt_smem + F::O0), *os1 = (uint16_t *)(lt_smem + F::O0 + F::OBYTES);
     uint16_t *bs0 = (uint16_t *)(lt_smem + F::B0), *bs1 = (uint16_t *)(lt_smem + F::B0 + F::BIAS);
     const auto load_u = [&](int q, int u) __attribute__((always_inline)) {
+        if constexpr (F::FLAT) {
+            ar[u] = sU.load(tid + NT * u < F::OC * per ? 2u * (uint32_t)((c_begin + q) * F::OC * r + (tid + NT * u) * 8) : BUF_OUT);
+            return;
+        }
         const int row = (c_begin + q) * F::OC + vrow + VSTEP * u;
         ar[u] = EVEN ? sU.load(vin ? 2u * (uint32_t)(row * r + vcol * 8) : BUF_OUT) : LinPiece(row, vcol, N, r).load(W2, N * r);
     };
     const auto store_u = [&](int q, int u, uint16_t *as) __attribute__((always_inline)) { // (half a step past the last rank: zero)
+        if constexpr (F::FLAT) {
+            if (tid + NT * u < F::OC * per) *(uint4 *)((unsigned char *)as + flat[u]) = ar[u];
+            return;
+        }
         const int row = vrow + VSTEP * u;
         *(uint4 *)&as[row * F::AP + vcol * 8] = EVEN ? ar[u] : LinPiece((c_begin + q) * F::OC + row, vcol, N, r).fix(ar[u], N * r);
     };
@@ -245,9 +274,9 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
             for (int st = 0; st < 2 * RB; ++st) tf[j][st] = *(const bf16x8_t *)&ts[((wr + j) * 32 + (lane & 31)) * TP + st * 16 + hi * 8];
     }
     if (mid && blockIdx.y == 0) {
-        const int per = (r + 7) / 8;
-        for (int i = tid; i < MR * per; i += NT) {
-            const int o = i % per, row = i / per;
+        const int pieces = (r + 7) / 8;
+        for (int i = tid; i < MR * pieces; i += NT) {
+            const int o = i % pieces, row = i / pieces;
             if (m0 + row < M) {
                 const uint4 v = *(const uint4 *)&ts[row * TP + o * 8];
                 uint16_t *to = mid + (i64)(m0 + row) * r + o * 8;
@@ -264,6 +293,10 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     }
     const bool relu = a.relu != 0;
     __syncthreads();
+    if constexpr (F::FLAT) { // (zeros past the last rank, which no piece covers)
+        for (int i = tid; i < 2 * F::OC * (RB * 4 - per); i += NT)
+            *(uint4 *)(lt_smem + F::A0 + i / (RB * 4 - per) * (F::AP * 2) + (per + i % (RB * 4 - per)) * 16) = make_uint4(0, 0, 0, 0);
+    }
 #pragma unroll
     for (int u = 0; u < F::ACH; ++u) {
         store_u(0, u, as0);
@@ -371,30 +404,34 @@ __global__ __launch_bounds__(512, 2) void linear_two_kernel(LinTwoArgs a)
     }
 }
 
-static int lt_blocks(i64 r) { return r <= 32 ? 1 : r <= 64 ? 2 : 4; }
+static int lt_blocks(i64 r) { return r <= 32 ? 1 : r <= 64 ? 2 : r <= 128 ? 4 : r <= 160 ? 5 : r <= 192 ? 6 : 8; }
+static int lt_most(i64 r) { return r <= 128 ? 4 : r <= 192 ? 2 : 1; } // blocks of 32 rows that a workgroup's LDS has room for
 
 bool linear_two_supported(i64 M, i64 K, i64 N, i64 r)
 {
     const i64 lim = 1LL << 30;
-    return M >= 1 && K >= 8 && N >= 8 && K % 8 == 0 && N % 8 == 0 && r >= 8 && r <= 128 && M * K < lim && M * N < lim && K * r < lim && N * r < lim;
+    return M >= 1 && K >= 8 && N >= 8 && K % 8 == 0 && N % 8 == 0 && r >= 8 && (r <= 128 || (r <= 256 && r % 8 == 0)) && M * K < lim && M * N < lim && K * r < lim && N * r < lim;
 }
 
 // Fitted to times of 130 shapes (1 to 16384 rows, 128 to 4096 wide, ranks 8 to 128) with every number of rows and share of the outputs, 8 %
 // rms: what a workgroup costs and 32 rows through a chunk of either stage, and what a compute unit reads and writes 12 and 14 ns per KB.
+// Ranks above 128, where a chunk's products and its barrier cost more, fitted by themselves: 312 shapes of 64 to 16384 rows, 5 % rms.
 double plan_linear_two(i64 M, i64 K, i64 N, i64 r, int groups, int &rows, int &osplit)
 {
     double best = 1e30;
     const int RB = lt_blocks(r), chunks = (int)((N + 127) / 128);
-    for (int mb = 1; mb <= 4; mb *= 2) {
+    for (int mb = 1; mb <= lt_most(r); mb *= 2) {
         const i64 tiles = (M + 32 * mb - 1) / (32 * mb);
-        const int KC = RB == 4 && mb == 4 ? 64 : 128;
+        const int KC = RB == 8 || (RB == 4 && mb == 4) ? 64 : 128;
         const double steps = (double)((K + KC - 1) / KC);
         for (int os = 1; os <= chunks && os <= 8; os *= 2) {
             const int per = (chunks + os - 1) / os;
             const i64 rounds = (tiles * os * groups + 255) / 256;
             const double full = tiles * os * groups < 256 ? tiles * os * groups / 256.0 : 1;
             const double kb1 = K * (r + 32.0 * mb) / 512, kb2 = per * 128.0 * (r + 32 * mb) / 512;
-            const double t = 3.49 + rounds * (0.77 + 0.0392 * steps * mb + 0.0044 * per + 0.0452 * per * mb + 0.0121 * kb1 + 0.0137 * kb2 +
+            const double wide = 2.53 + rounds * (2.6 + steps * (0.319 + 0.205 * mb * KC / 128) + per * (0.25 + 0.035 * mb) + 0.0026 * kb1 + 0.0119 * kb2 +
+                                                 0.0024 * full * (kb1 + kb2));
+            const double t = RB > 4 ? wide : 3.49 + rounds * (0.77 + 0.0392 * steps * mb + 0.0044 * per + 0.0452 * per * mb + 0.0121 * kb1 + 0.0137 * kb2 +
                                               0.0049 * full * (kb1 + kb2) + (r % 8 ? 0.33 * (steps + per) : 0));
             if (t < best) best = t, rows = 32 * mb, osplit = os;
         }
@@ -417,21 +454,35 @@ static int lt_launch(hipStream_t s, const char *name, const LinTwoArgs &a)
     if (even && a.mask) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false, true>), grid, dim3(F::NT), s, a);
     else if (even && a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, true, false>), grid, dim3(F::NT), s, a);
     else if (even) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, true, false, false>), grid, dim3(F::NT), s, a);
-    else if (a.mask) return PF_ERR_UNSUPPORTED; // (backward takes ranks in whole pieces)
-    else if (a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, true, false>), grid, dim3(F::NT), s, a);
-    else PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, false, false>), grid, dim3(F::NT), s, a);
+    else if (a.mask || RB > 4) return PF_ERR_UNSUPPORTED; // (backward and ranks above 128 take ranks in whole pieces)
+    else if constexpr (RB <= 4) {
+        if (a.add) PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, true, false>), grid, dim3(F::NT), s, a);
+        else PF_LAUNCH(st, name, (linear_two_kernel<RB, MB, false, false, false>), grid, dim3(F::NT), s, a);
+    }
     return st;
 }
 template <int RB>
 static int lt_rows(hipStream_t s, const char *name, const LinTwoArgs &a, int rows)
 {
+    if constexpr (RB > 4) {
+        if constexpr (RB < 8)
+            if (rows == 64) return lt_launch<RB, 2>(s, name, a);
+        return rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
+    }
     if (rows == 128 && a.add && a.mask) rows = 64; // (both arrays' pieces beside the sums of 128 rows do not fit the registers)
-    return rows == 128 ? lt_launch<RB, 4>(s, name, a) : rows == 64 ? lt_launch<RB, 2>(s, name, a) : rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
+    if constexpr (RB <= 4) return rows == 128 ? lt_launch<RB, 4>(s, name, a) : rows == 64 ? lt_launch<RB, 2>(s, name, a) : rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
 }
 int launch_linear_two(hipStream_t s, const char *name, const LinTwoArgs &a, int rows)
 {
     if (!linear_two_supported(a.M, a.K, a.N, a.r) || a.osplit < 1 || a.osplit > (a.N + 127) / 128) return PF_ERR_UNSUPPORTED;
-    return lt_blocks(a.r) == 1 ? lt_rows<1>(s, name, a, rows) : lt_blocks(a.r) == 2 ? lt_rows<2>(s, name, a, rows) : lt_rows<4>(s, name, a, rows);
+    switch (lt_blocks(a.r)) {
+    case 1: return lt_rows<1>(s, name, a, rows);
+    case 2: return lt_rows<2>(s, name, a, rows);
+    case 4: return lt_rows<4>(s, name, a, rows);
+    case 5: return lt_rows<5>(s, name, a, rows);
+    case 6: return lt_rows<6>(s, name, a, rows);
+    default: return lt_rows<8>(s, name, a, rows);
+    }
 }
 
 } // namespace pf

@@ -72,6 +72,40 @@ def test_mask(two, M, K, N, r):
                 assert float((Y[kept].double() - want[kept].double()).norm()) <= 4e-3 * float(want.double().norm())  # one rounding to bf16
 
 
+@pytest.mark.parametrize("M,K,N,r,G", [(1, 136, 136, 136, 1), (33, 264, 392, 160, 2), (130, 1032, 648, 168, 1), (70, 192, 128, 192, 3), (97, 520, 264, 200, 1),
+                                       (200, 256, 1048, 256, 2)])
+def test_wide_ranks(two, M, K, N, r, G):
+    """Ranks above 128, first and last of five, six and eight blocks; tolerances as above (and nothing of LDS beyond the rank is seen)."""
+    g = torch.Generator(device="cuda").manual_seed(6)
+    n = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, V, U = n(M, K).bfloat16(), (n(G, K, r) * K ** -0.5).bfloat16(), (n(G, N, r) * r ** -0.5).bfloat16()
+    bias, add, mask = n(G, N).bfloat16(), n(M, N).bfloat16(), n(M, N).bfloat16()
+    p = lambda t: ctypes.c_void_p(None if t is None else t.data_ptr())
+    for rows in (32, 64, 128):
+        for osplit in {1, (N + 127) // 128}:
+            for ep in (False, True):
+                Y, T = (torch.full((G, M, w), float("nan"), dtype=torch.bfloat16, device="cuda") for w in (N, r))
+                one = ep and G == 1
+                args = [X, V, U, bias if ep else None, add if one else None]
+                st = two.linear_two(ctypes.c_longlong(M), K, N, r, G, rows, osplit, *map(p, args), int(ep and not one), p(Y), p(T), p(mask if one else None),
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+                assert (st == 0) == (rows <= (64 if r <= 192 else 32))
+                if st != 0:
+                    continue
+                want = T.float() @ U.float().transpose(1, 2).contiguous()
+                if ep:
+                    want = want + bias.float()[:, None]
+                    want = (want[0] + add.float())[None] * (mask.float() > 0) if one else want.clamp_min(0)
+                for got, ref in ((T, X.float() @ V.float()), (Y, want)):
+                    err = (got.double() - ref.double()).norm() / ref.double().norm().clamp_min(1e-30)
+                    assert err <= 4e-3, (rows, osplit, ep, err)
+
+
+@pytest.mark.parametrize("M,cols,r", [(64, (136, 264), 136), (333, (392, 160), 192), (1030, (200, 640), 200), (577, (256, 256), 256)])
+def test_wide_gradients(two, M, cols, r):
+    test_gradients(two, M, cols, r)
+
+
 @pytest.mark.parametrize("M,cols,r", [(64, (8, 8), 8), (65, (136, 120), 40), (1000, (264, 72), 64), (700, (128, 640), 128), (1030, (1032, 8), 24),
                                       (577, (256, 128), 96)])
 def test_gradients(two, M, cols, r):
@@ -114,6 +148,11 @@ def test_backward(shape):
         assert {"linear_bwd_data_two", "linear_grads"} <= _launches(pf, call)
         for x, ref in zip(got, (want,) + grads):  # (a share of 2^-8 per rounding to bf16; dT and T may round either way here)
             assert float((x.double() - ref.double()).norm() / ref.double().norm()) <= 4e-3
+
+
+@pytest.mark.parametrize("shape", [(8192, 640, 640, 160), (8000, 2048, 320, 200)])
+def test_wide_backward(shape):
+    test_backward(shape)
 
 
 @pytest.mark.parametrize("wanted", [(1, 1, 1), (1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 0, 1), (0, 1, 1), (0, 0, 0)])
