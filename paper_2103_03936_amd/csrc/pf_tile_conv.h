@@ -50,7 +50,6 @@ tile_conv_kernel(TileArgs by_value)
     const TileAt t = find_tile<CFG>(a);
     if (!t.live) return;
     const TileProb &p = a.p[t.prob];
-    const auto put = [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, t.ks, t.zb, t.m0 + m, t.n0 + n, v); };
     const int kbeg = t.ks * p.kper, nch = (min(p.K, kbeg + p.kper) - kbeg + BK - 1) / BK; // (not TILE_WG)
     constexpr bool STRIDED = GATHER && !WG; // (a strided input is the right operand of launches without weight gradients only)
     if (p.type == TILE_CONV || (STRIDED && p.type == TILE_CONVG)) {
@@ -78,14 +77,14 @@ tile_conv_kernel(TileArgs by_value)
                 }
             }
         }
-        tile_pieces<CT, CFG>(smem, tid, put);
+        put_planes<CT, CFG>(p, t.ks, t.zb, t.m0, t.n0, smem, tid);
     } else if (p.type == TILE_CONVT) {
         AS la;
         BP lb;
         la.init(p.A, p.lda, p.M, p.K, t.m0, kbeg, tid, p.ascale);
         lb.init(p.pb, t.n0, kbeg, tid, tile_tables);
         tile_product<CT, CFG>(la, lb, nch, smem, tid);
-        tile_pieces<CT, CFG>(smem, tid, put);
+        put_planes<CT, CFG>(p, t.ks, t.zb, t.m0, t.n0, smem, tid);
     } else if (p.type == TILE_PACK) {
         pack_filters<CT>(p, t.index, tid);
     } else if constexpr (WG) {

@@ -6,16 +6,29 @@
 
 namespace pf {
 
-// One 16-byte piece of the output: V neighbouring columns n .. n + V - 1 of row m (n a multiple of V).
+template <typename CT>
+__device__ __forceinline__ float tile_float(typename TileEl<CT>::elem x)
+{
+    if constexpr (sizeof(CT) == 4) return x;
+    else return bf16_bits_to_float(x);
+}
+template <typename CT>
+__device__ __forceinline__ typename TileEl<CT>::elem tile_elem(float x)
+{
+    if constexpr (sizeof(CT) == 4) return x;
+    else return float_to_bf16_bits(x);
+}
+
+// One 16-byte piece of a row-major output: V neighbouring columns n .. n + V - 1 of row m (n a multiple of V).
 template <typename CT, int V>
 __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int m, int n, float *v)
 {
     typedef typename TileEl<CT>::elem elem;
     const TileOut &o = p.o;
     if (m >= p.M || n >= p.N) return;
+    const int nv = min(V, p.N - n);
     if (o.f32) {
         float *c = (float *)o.C + ks * o.split_stride + zb * p.sc + (i64)m * o.ld + n;
-        const int nv = min(V, p.N - n);
         if (nv == V && !o.accumulate) {
 #pragma unroll
             for (int e = 0; e < V; e += 4) stg16(c + e, floats_piece<float>(v + e));
@@ -25,31 +38,10 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
         }
         return;
     }
-    i64 at;
-    int nv;
-    int pos = 0;
-    if (o.HC > 0) {
-        const int cn = n / V, img = cn / o.HC;
-        pos = (cn - img * o.HC) * V;
-        nv = min(V, o.HW - pos);
-        if (img >= o.N) return;
-        if (o.s > 1) {
-            at = ((i64)img * o.CH + m) * ((i64)o.H * o.W);
-        } else {
-            at = ((i64)img * o.CH + m) * o.HW + pos;
-        }
-    } else {
-        at = zb * p.sc + (i64)m * o.ld + n;
-        nv = min(V, p.N - n);
-    }
+    const i64 at = zb * p.sc + (i64)m * o.ld + n;
     elem *c = (elem *)o.C;
     const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask, *bias = o.bias ? (const elem *)o.bias + zb * p.sbias : nullptr;
-    const float sc = o.scale ? o.scale[m] : 1.f, sh = o.shift ? o.shift[m] : 0.f;
-    if (o.scale || o.shift) {
-#pragma unroll
-        for (int e = 0; e < V; ++e) v[e] = v[e] * sc + sh;
-    }
-    if (nv == V && !(o.s > 1)) {
+    if (nv == V) {
         float f[8];
         if (bias) {
             piece_floats<CT>(ldg16(bias + n), f);
@@ -73,34 +65,132 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
         stg16(c + at, floats_piece<CT>(v));
         return;
     }
-    int y = 0, x = 0;
-    if (o.s > 1) y = pos / o.gW, x = pos - y * o.gW;
 #pragma unroll
     for (int e = 0; e < V; ++e) {
         if (e < nv) {
-            i64 i = at + e;
-            bool in = true;
-            if (o.s > 1) {
-                const int yy = y * o.s + o.ph, xx = x * o.s + o.pw;
-                in = yy < o.H && xx < o.W;
-                i = at + (i64)yy * o.W + xx;
-                if (++x == o.gW) x = 0, ++y;
+            float t = v[e];
+            if (bias) t += tile_float<CT>(bias[n + e]);
+            if (add) t += tile_float<CT>(add[at + e]);
+            if (o.relu) t = fmaxf(t, 0.f);
+            if (mask) t = tile_float<CT>(mask[at + e]) > 0.f ? t : 0.f;
+            c[at + e] = tile_elem<CT>(t);
+        }
+    }
+}
+
+// A tile of planes with its epilogue (the sums over k of a split product: row-major).  A thread's pieces lie in the same columns of several rows.  What is added to up to four
+// of them, scales and masks them is requested before the first is used: piece by piece, and element by element in planes that are no whole
+// pieces, it was a chain of up to 24 waits, 4 to 5 us of a launch of 12.  A piece that would end past the array is pulled back inside and shifted
+// into place, as the operands' are.
+template <typename CT, class CFG>
+__device__ __forceinline__ void put_planes(const TileProb &p, int ks, int zb, int m0, int n0, const unsigned char *smem, int tid)
+{
+    typedef typename TileEl<CT>::elem elem;
+    constexpr int V = TileEl<CT>::V, CPR = CFG::BN / V, NT = TILE_THREADS * CFG::DEEP, ALL = CFG::BM * CPR, P = (ALL + NT - 1) / NT;
+    constexpr int PER = P < 4 ? P : 4;
+    static_assert(NT % CPR == 0 && P % PER == 0, "a thread's pieces are whole rounds, in the same columns of every row");
+    const TileOut &o = p.o;
+    if (o.HC == 0) {
+        tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, zb, m0 + m, n0 + n, v); });
+        return;
+    }
+    const int n = n0 + tid % CPR * V, row0 = m0 + tid / CPR;
+    if (n >= p.N || (ALL < NT && tid >= ALL)) return;
+    elem *c = (elem *)o.C;
+    const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask;
+    const int cn = n / V, img = cn / o.HC, pos = (cn - img * o.HC) * V, nv = min(V, o.HW - pos);
+    if (img >= o.N) return;
+    const i64 step = o.s > 1 ? (i64)o.H * o.W : o.HW, total = (i64)o.N * o.CH * step; // from row to row, and to the array's end
+    const i64 at0 = (i64)img * o.CH * step + (o.s > 1 ? 0 : pos);
+    const auto sums = [&](int j, float *v) __attribute__((always_inline)) {
+        constexpr int PITCH = CFG::BN + 4;
+        const float *Cs = (const float *)smem + (tid / CPR + NT / CPR * j) * PITCH + tid % CPR * V;
+#pragma unroll
+        for (int e = 0; e < V; e += 4) {
+            f32x4_t t = *(const f32x4_t *)&Cs[e];
+#pragma unroll
+            for (int w = 1; w < CFG::WK; ++w) t += *(const f32x4_t *)&Cs[w * CFG::BM * PITCH + e];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) v[e + x] = t[x];
+        }
+    };
+    if (o.s > 1) { // every second pixel (no scale)
+        int off[V]; // from the channel's first pixel; -1: none
+        int y = pos / o.gW, x = pos - y * o.gW;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const int yy = y * o.s + o.ph, xx = x * o.s + o.pw;
+            off[e] = e < nv && yy < o.H && xx < o.W ? yy * o.W + xx : -1;
+            if (++x == o.gW) x = 0, ++y;
+        }
+        for (int j = 0; j < P; ++j) {
+            const int m = row0 + NT / CPR * j;
+            if (m >= p.M) break;
+            const i64 at = at0 + m * step;
+            elem fa[V], fm[V];
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const i64 i = at + max(off[e], 0);
+                if (add) fa[e] = add[i];
+                if (mask) fm[e] = mask[i];
             }
-            if (in) {
-                union {
-                    uint32_t w[4];
-                    elem e[V];
-                } u;
-                float t = v[e];
-                if (bias) t += sizeof(elem) == 4 ? ((const float *)bias)[n + e] : bf16_bits_to_float((uint16_t)bias[n + e]);
-                if (add) t += sizeof(elem) == 4 ? ((const float *)add)[i] : bf16_bits_to_float((uint16_t)add[i]);
-                if (o.relu) t = fmaxf(t, 0.f);
-                if (mask)
-                    t = (sizeof(elem) == 4 ? ((const float *)mask)[i] : bf16_bits_to_float((uint16_t)mask[i])) > 0.f ? t
-                                                                                                                   : 0.f;
-                if (sizeof(elem) == 4) u.w[0] = __float_as_uint(t);
-                else u.w[0] = float_to_bf16_bits(t);
-                c[i] = u.e[0];
+            float v[V];
+            sums(j, v);
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                if (add) v[e] += tile_float<CT>(fa[e]);
+                if (o.relu) v[e] = fmaxf(v[e], 0.f);
+                if (mask) v[e] = tile_float<CT>(fm[e]) > 0.f ? v[e] : 0.f;
+                if (off[e] >= 0) c[at + off[e]] = tile_elem<CT>(v[e]);
+            }
+        }
+        return;
+    }
+#pragma unroll 1
+    for (int j0 = 0; j0 < P; j0 += PER) {
+        uint4 ra[PER], rm[PER];
+        float sc[PER], sh[PER];
+        i64 at[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int m = min(row0 + NT / CPR * (j0 + u), p.M - 1);
+            at[u] = at0 + m * step;
+            const i64 from = min(at[u], total - V);
+            if (add) ra[u] = ldg16(add + from);
+            if (mask) rm[u] = ldg16(mask + from);
+            if (o.scale) sc[u] = o.scale[m];
+            if (o.shift) sh[u] = o.shift[m];
+        }
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (row0 + NT / CPR * (j0 + u) >= p.M) break;
+            const int back = (int)(at[u] - min(at[u], total - V));
+            float v[V], f[8];
+            sums(j0 + u, v);
+            if (o.scale || o.shift) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = v[e] * (o.scale ? sc[u] : 1.f) + (o.shift ? sh[u] : 0.f);
+            }
+            if (add) {
+                piece_floats<CT>(back ? piece_shift<sizeof(elem)>(ra[u], back) : ra[u], f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] += f[e];
+            }
+            if (o.relu) {
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = fmaxf(v[e], 0.f);
+            }
+            if (mask) {
+                piece_floats<CT>(back ? piece_shift<sizeof(elem)>(rm[u], back) : rm[u], f);
+#pragma unroll
+                for (int e = 0; e < V; ++e) v[e] = f[e] > 0.f ? v[e] : 0.f;
+            }
+            if (nv == V) {
+                stg16(c + at[u], floats_piece<CT>(v));
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    if (e < nv) c[at[u] + e] = tile_elem<CT>(v[e]);
             }
         }
     }
@@ -185,8 +275,7 @@ template <typename CT, class CFG, class L>
 __device__ __forceinline__ void finish(const TileProb &p, int ks, int zb, int m0, int n0, L &l, int r0, int nr, bool sums,
                                        unsigned char *smem, int tid)
 {
-    constexpr int V = TileEl<CT>::V;
-    tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, V>(p, ks, zb, m0 + m, n0 + n, v); });
+    tile_pieces<CT, CFG>(smem, tid, [&](int m, int n, float *v) { put_piece<CT, TileEl<CT>::V>(p, ks, zb, m0 + m, n0 + n, v); });
     if (sums) {
         __syncthreads();
         float *out = p.o.sums + ks * p.o.sums_stride + zb * p.ssums;

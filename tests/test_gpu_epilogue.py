@@ -186,3 +186,31 @@ def test_epilogue_validation():
     assert need > pf.lib.pf_lowrank_conv_bwd_workspace_bytes(ctypes.byref(c))
     assert pf.lib.pf_lowrank_conv_bwd_ep(ctypes.byref(c), fake, fake, fake, fake, fake, None, None, None, 0, fake, fake, fake,
                                          None, 0, fake, ctypes.c_size_t(need - 1), None) == 4
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 133, 3, 3, 131, 1, 1), (3, 136, 5, 5, 140, 3, 1), (2, 130, 6, 8, 132, 3, 2), (2, 134, 7, 5, 129, 3, 2), (3, 132, 5, 3, 130, 1, 2)])
+def test_epilogue_on_ragged_planes(shape, dtype):
+    """Tiled products (a rank above 128) into planes that are no whole pieces, the array's last one among them, with all that an epilogue
+    has.  Float: sums of up to 1200 products, 2^-24 each in a random direction; bf16: one rounding of the output (2^-8 at most) and of T or dT."""
+    import paper_2103_03936_amd as pf
+    N, C, H, W, Cout, k, s = shape
+    r, pad = 132, k // 2
+    g = torch.Generator().manual_seed(11)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    n = lambda *sh: torch.randn(*sh, generator=g)
+    X, Uk, Vp = n(N, C, H, W).to(dt), (n(r, C, k, k) * (C * k * k) ** -0.5).to(dt), (n(Cout, r) * r ** -0.5).to(dt)
+    T = torch.nn.functional.conv2d(X.double(), Uk.double(), stride=s, padding=pad)
+    scale, shift = torch.rand(Cout, generator=g) + 0.5, n(Cout)
+    R, dZ, A = n(N, Cout, *T.shape[2:]).to(dt), n(N, Cout, *T.shape[2:]).to(dt), n(N, C, H, W).to(dt)
+    c = lambda t: t.cuda()
+    Y, Tg = pf.pf_lowrank_conv_fwd_ep(c(X), c(Uk), c(Vp), c(scale), c(shift), c(R), act="relu", stride=s, pad=pad)
+    got = pf.pf_lowrank_conv_bwd_ep(c(X), c(Uk), c(Vp), c(scale), c(dZ), T_saved=Tg, dX_add=c(A), x_is_relu=True, stride=s, pad=pad)
+    ch = lambda v: v.double()[None, :, None, None]
+    want = (torch.einsum("or,nrhw->nohw", Vp.double(), Tg.cpu().double()) * ch(scale) + ch(shift) + R.double()).clamp_min(0)
+    dT = torch.einsum("or,nohw->nrhw", (Vp.double() * scale.double()[:, None]), dZ.double())
+    dX = torch.nn.grad.conv2d_input(X.shape, Uk.double(), dT.to(dt).double(), stride=s, padding=pad) + A.double()
+    dX = torch.where(X.double() > 0, dX, torch.zeros_like(dX))
+    tol = 1e-6 if dtype == "f32" else 6e-3
+    for a, b in ((Tg, T), (Y, want), (got[0], dX)):
+        assert float((a.cpu().double() - b).norm() / b.norm()) <= tol
