@@ -16,8 +16,8 @@ struct LstmRunLayer {
     float *dh0, *dc0, *dz, *dTh, *dTx;
 };
 struct LstmRecurrence {
-    size_t (*floats)(const LstmGeom &g, bool bwd); // workspace (0: no device takes the call)
-    bool (*fits)(const LstmGeom &g, bool bwd);     // this device can hold the launch's workgroups at once
+    size_t (*floats)(const LstmGeom &g, bool bwd); // workspace that a call should have for it (0: none)
+    bool (*fits)(const LstmGeom &g, bool bwd, size_t room); // this device can hold the launch's workgroups at once, and `room` floats do
     // ws: 256-byte aligned; dh_top: gradient of the top layer's outputs, backward only
     int (*run)(const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, bool bwd, float *ws, hipStream_t s);
 };

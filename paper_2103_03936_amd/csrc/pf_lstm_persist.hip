@@ -341,7 +341,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
     __shared__ __attribute__((aligned(16))) float red[LP_WAVES * (NT > TN ? NT : TN) * RB * 64];
     __shared__ int ok;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), wg = blockIdx.x;
-    const int T = a.T, B = a.B, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
+    const int T = a.T, B = a.B, BT = a.BT, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
     LpSync sync = {a.sync, wg, &ok};
     unsigned *flags = a.sync + LP_BAR, *failed = a.sync + LP_FAILED;
     const bool in2 = wg < a.n2;
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
             int k, m;
             lp_element<RB>(at.o, k, m);
             const int q = k / rp, cc = k - q * rp;
-            const float v = a.l[0].Tx[((i64)at.row * B + min(m, B - 1)) * gr + q * r + min(cc, r - 1)];
+            const float v = a.l[0].Tx[((i64)at.row * BT + min(m, B - 1)) * gr + q * r + min(cc, r - 1)];
             lp_share(lp_xt(a, 0, 1, at.row) + at.o, cc < r ? v : 0.f);
         }
         sync.arrive(a.n2);
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
                                                              (tpath ? lp_xh(a, tl - 1, t + 1) : lp_xh(a, tl, t)) + tg0 * RB * 128, 0, tng);
                 lp_exchange<1>(red, acc);
                 if ((lost = !ok)) break;
-                lp_put_T<TN, 8, RB>(a, red, lp_xt(a, tl, tpath, t), (tpath ? a.l[tl].Tx : a.l[tl].Th) + (i64)t * B * gr, tcol, tncol);
+                lp_put_T<TN, 8, RB>(a, red, lp_xt(a, tl, tpath, t), (tpath ? a.l[tl].Tx : a.l[tl].Th) + (i64)t * BT * gr, tcol, tncol);
             }
             lp_publish(flags, lp_flag(1, cols.task), slot + 1);
         }
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_fwd_kernel(LpArgs by_value)
             lp_publish(flags, lp_flag(2, units.task), slot + 1); // the others need h only
             if (active && kept) {
                 const LstmRunLayer &y = a.l[zl];
-                const i64 idx = (i64)t * B * h + (i64)em * h + un, base = ((i64)t * B + em) * 4 * h + un;
+                const i64 idx = (i64)t * BT * h + (i64)em * h + un, base = ((i64)t * BT + em) * 4 * h + un;
                 y.h_all[idx] = hv;
                 y.c_all[idx] = cv;
 #pragma unroll
@@ -485,7 +485,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
     __shared__ __attribute__((aligned(16))) float red[LP_WAVES * (NT > TN ? NT : TN) * RB * 64];
     __shared__ int ok;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), wg = blockIdx.x;
-    const int T = a.T, B = a.B, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
+    const int T = a.T, B = a.B, BT = a.BT, h = a.h, r = a.r, gr = a.gr, L = a.L, hp = a.hp, rp = a.rp, G = G4 ? 4 : 1;
     unsigned *flags = a.sync + LP_BAR, *failed = a.sync + LP_FAILED;
     if (tid == 0) ok = 1; // (waits that give up clear it)
     __syncthreads();
@@ -547,12 +547,12 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                     int m, un;
                     element(it, m, un);
                     const bool in = m < B && un < h && t >= 0;
-                    const i64 idx = (i64)min(m, B - 1) * h + min(un, h - 1), at = (i64)max(t, 0) * B * h + idx;
-                    const i64 base = ((i64)max(t, 0) * B + min(m, B - 1)) * 4 * h + min(un, h - 1);
+                    const i64 idx = (i64)min(m, B - 1) * h + min(un, h - 1), at = (i64)max(t, 0) * BT * h + idx;
+                    const i64 base = ((i64)max(t, 0) * BT + min(m, B - 1)) * 4 * h + min(un, h - 1);
                     pa[it] = (in && zl == L - 1 ? a.dh_top[at] : 0.f) + (in && t == T - 1 && y.dhT ? y.dhT[idx] : 0.f);
 #pragma unroll
                     for (int g = 0; g < 4; ++g) pg[it][g] = in ? y.gates[base + (i64)g * h] : 0.f;
-                    pcp[it] = in ? (t > 0 ? y.c_all + (i64)(t - 1) * B * h : y.c0)[idx] : 0.f;
+                    pcp[it] = in ? (t > 0 ? y.c_all + (i64)(t - 1) * BT * h : y.c0)[idx] : 0.f;
                     pco[it] = in ? y.c_all[at] : 0.f;
                     if (t == T - 1) dcs[it] = in && y.dcT ? y.dcT[idx] : 0.f;
                 }
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                         if (m < B && un < h) {
                             if (t == 0) y.dc0[(i64)m * h + un] = dcv[it];
 #pragma unroll
-                            for (int g = 0; g < 4; ++g) y.dz[((i64)t * B + m) * 4 * h + (i64)g * h + un] = dv[it][g];
+                            for (int g = 0; g < 4; ++g) y.dz[((i64)t * BT + m) * 4 * h + (i64)g * h + un] = dv[it][g];
                         }
                     }
                 }
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
                 lp_exchange<TCB>(red, acc);
                 if ((lost = !ok)) break;
                 lp_put_T<TN, TW, RB>(a, red, lp_xt(a, tl, tpath, t) + (SL > 1 ? tq * rp * 4 * RB : 0),
-                                     SL > 1 ? nullptr : (tpath ? a.l[tl].dTx : a.l[tl].dTh) + (i64)t * B * gr, (G4 ? tq * rp : 0) + tcol, tncol);
+                                     SL > 1 ? nullptr : (tpath ? a.l[tl].dTx : a.l[tl].dTh) + (i64)t * BT * gr, (G4 ? tq * rp : 0) + tcol, tncol);
                 lp_publish(flags, lp_flag(2, cols.task), u + 1);
             }
         }
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(LP_NT) void lstm_run_bwd_kernel(LpArgs by_value)
             float v = x[0];
 #pragma unroll
             for (int sl = 1; sl < SL; ++sl) v += x[sl * nx];
-            (path ? a.l[l].dTx : a.l[l].dTh)[((i64)t * B + m) * gr + k] = v;
+            (path ? a.l[l].dTx : a.l[l].dTh)[((i64)t * BT + m) * gr + k] = v;
         }
     }
 }
@@ -658,12 +658,16 @@ static int lp_cus()
 // asked for before one is chosen).  A single step uses the factors once: 125 us as launches, 160 here (1216 units, batch 28).
 static size_t lp_floats(const LstmGeom &g, bool bwd)
 {
-    const LpPlan p = lp_plan(g, bwd, LP_MOST_CUS);
-    return g.T + g.L < 3 || p.NT == 0 ? 0 : p.floats;
+    LstmGeom some = g;
+    some.B = lp_rows_at_once(g, bwd, LP_MOST_CUS);
+    return g.T + g.L < 3 || some.B == 0 ? 0 : lp_plan(some, bwd, LP_MOST_CUS).floats;
 }
-static bool lp_fits(const LstmGeom &g, bool bwd)
+// (Halves with a pair per gate are no reason for a larger workspace: they are taken where they find room.)
+static size_t lp_wants(const LstmGeom &g, bool bwd) { return g.G != 1 && lp_rows_at_once(g, bwd, LP_MOST_CUS) != g.B ? 0 : lp_floats(g, bwd); }
+static bool lp_fits(const LstmGeom &g, bool bwd, size_t room)
 {
-    return lp_floats(g, bwd) > 0 && lp_plan(g, bwd, lp_cus()).NT > 0;
+    const size_t n = lp_floats(g, bwd);
+    return n > 0 && n <= room && lp_rows_at_once(g, bwd, lp_cus()) > 0;
 }
 
 static int lp_launch(void (*kernel)(LpArgs), const LpArgs &a, bool bwd, hipStream_t s)
@@ -703,17 +707,23 @@ static LpKernel lp_kernel(const LpPlan &p, int G, bool bwd)
 
 static int lp_run(const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, bool bwd, float *ws, hipStream_t s)
 {
-    const LpPlan p = lp_plan(g, bwd, lp_cus());
-    LpArgs a;
-    lp_fill(a, p, g, l, dh_top, ws);
-    int st = launch_zero_f32(s, (float *)a.sync, LP_SYNC);
-    if (st != PF_OK) return st;
-    return lp_launch(lp_kernel(p, g.G, bwd), a, bwd, s);
+    LstmGeom some = g;
+    const int rows = lp_rows_at_once(g, bwd, lp_cus());
+    for (int b0 = 0; b0 < g.B; b0 += rows) { // (one after the other: the workspace is theirs in turn)
+        some.B = g.B - b0 < rows ? g.B - b0 : rows;
+        const LpPlan p = lp_plan(some, bwd, lp_cus());
+        LpArgs a;
+        lp_fill(a, p, some, l, dh_top, ws, b0, g.B);
+        int st = launch_zero_f32(s, (float *)a.sync, LP_SYNC);
+        if (st == PF_OK) st = lp_launch(lp_kernel(p, g.G, bwd), a, bwd, s);
+        if (st != PF_OK) return st;
+    }
+    return PF_OK;
 }
 
 namespace {
 struct Install {
-    Install() { lstm_recurrence = LstmRecurrence{lp_floats, lp_fits, lp_run}; }
+    Install() { lstm_recurrence = LstmRecurrence{lp_wants, lp_fits, lp_run}; }
 } install;
 } // namespace
 

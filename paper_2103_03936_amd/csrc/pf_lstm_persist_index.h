@@ -23,6 +23,7 @@ struct LpArgs {
     unsigned *sync;
     i64 xh_step, xt_step; // floats from one step's copy to the next
     int T, B, h, r, G, gr, L;
+    int BT;               // rows of a step in the arrays, B or more: a launch may take some of them
     int hp, rp;           // h and r up to whole groups of 32 contraction indices
     int n1, n2, nwg;      // tasks (one per workgroup) of the two phases of a slot
     int nt1;              // 8-column tiles of a T / dT task
@@ -186,7 +187,7 @@ __host__ __device__ inline void lp_void_columns(const LpArgs &a, float *out, int
     for (int t = t0; t < t1; ++t)
         for (int e = tid; e < a.B * n; e += LP_NT) {
             const int m = e / n, c = col + e - m * n, q = c / a.rp, cc = c - q * a.rp;
-            if (q < a.G && cc < a.r) out[((i64)t * a.B + m) * a.gr + q * a.r + cc] = lp_nan();
+            if (q < a.G && cc < a.r) out[((i64)t * a.BT + m) * a.gr + q * a.r + cc] = lp_nan();
         }
 }
 // forward, in slot `slot`
@@ -199,7 +200,7 @@ __host__ __device__ inline void lp_void_fwd(const LpArgs &a, const LpColumns &c,
         for (int e = tid; e < a.B * z.n; e += LP_NT) {
             const int m = e / z.n, un = z.u0 + e - m * z.n;
             if (un >= a.h) continue;
-            const i64 row = (i64)t * a.B + m;
+            const i64 row = (i64)t * a.BT + m;
             y.h_all[row * a.h + un] = y.c_all[row * a.h + un] = lp_nan();
             for (int q = 0; q < 4; ++q) y.gates[(row * 4 + q) * a.h + un] = lp_nan();
         }
@@ -218,7 +219,7 @@ __host__ __device__ inline void lp_void_bwd(const LpArgs &a, const LpColumns &c,
         const int per = a.rp * 4 * RB; // (this workgroup's share of the sums, in any order)
         for (LpWalk at(per, wg * LP_NT + tid, a.n1 * LP_NT); at.row < (2 * a.L - 1) * a.T; at.next()) {
             const int pr = at.row / a.T, t = at.row - pr * a.T, l = lp_layer(pr), k = at.o / (4 * RB), m = at.o - k * (4 * RB);
-            if (k < a.r && m < a.B) (lp_path(pr) ? a.l[l].dTx : a.l[l].dTh)[((i64)t * a.B + m) * a.gr + k] = lp_nan();
+            if (k < a.r && m < a.B) (lp_path(pr) ? a.l[l].dTx : a.l[l].dTh)[((i64)t * a.BT + m) * a.gr + k] = lp_nan();
         }
     }
     if (!z.has || left(z.l) < 0) return;
@@ -229,7 +230,7 @@ __host__ __device__ inline void lp_void_bwd(const LpArgs &a, const LpColumns &c,
             if (un >= a.h) continue;
             if (t < 0) y.dh0[(i64)m * a.h + un] = y.dc0[(i64)m * a.h + un] = lp_nan();
             else
-                for (int q = 0; q < 4; ++q) y.dz[(((i64)t * a.B + m) * 4 + q) * a.h + un] = lp_nan();
+                for (int q = 0; q < 4; ++q) y.dz[(((i64)t * a.BT + m) * 4 + q) * a.h + un] = lp_nan();
         }
 }
 
@@ -291,11 +292,46 @@ static LpPlan lp_plan(const LstmGeom &g, bool bwd, int cus)
     return p;
 }
 
-static void lp_fill(LpArgs &a, const LpPlan &p, const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, float *ws)
+// Rows of a launch: all, or half of them, one launch after the other, where only the halves' row blocks fit beside the factors and that is
+// faster than the launches of a slot.  Whole calls, us, slots / halves: one pair per path, 896 units, three layers, batch 21, 36 steps 1960 /
+// 1277, 5 steps 415 / 361; 1500 units, two layers, batch 32, 4 steps 413 / 401, 2 steps 307 / 315.  A pair per gate: 700 units, three layers,
+// batch 21, 36 steps 2834 / 1650, 3 steps 422 / 396; two of 896, batch 32, 10 steps 778 / 741, 5 steps 460 / 502; two of 128, batch 32, 5 steps
+// 330 / 285, 3 steps 234 / 240; one layer of 1024, batch 32, 24 steps 1373 / 1221, 8 steps 500 / 534; two of 1280, batch 21, 8 steps 787 / 675,
+// batch 32 853 / 888; one of 1500, batch 32, 24 steps 1589 / 1773.
+static int lp_rows_at_once(const LstmGeom &g, bool bwd, int cus)
+{
+    if (lp_plan(g, bwd, cus).NT > 0) return g.B;
+    LstmGeom half = g;
+    half.B = (g.B + 1) / 2;
+    if (g.B < 2 || lp_plan(half, bwd, cus).NT == 0) return 0;
+    int least = 4; // steps
+    if (g.G != 1) least = g.h > 896 ? (g.L == 1 ? 16 : 8) : g.L == 1 ? 16 : g.L == 2 ? (g.h <= 512 ? 5 : 10) : 3;
+    if (g.T < least || (g.G != 1 && g.h > 896 && (g.L == 1 ? g.h > 1024 : g.h > 1280 || half.B > 12))) return 0;
+    return half.B;
+}
+
+// rows b0 .. b0 + g.B - 1 of arrays with BT of them
+static LstmRunLayer lp_rows(const LstmRunLayer &l, const LstmGeom &g, int b0)
+{
+    LstmRunLayer y = l;
+    const i64 h = (i64)b0 * g.h, gr = (i64)b0 * g.gr;
+    for (const float **p : {&y.h0, &y.c0, &y.dhT, &y.dcT})
+        if (*p) *p += h;
+    for (float **p : {&y.h_all, &y.c_all, &y.dh0, &y.dc0})
+        if (*p) *p += h;
+    for (float **p : {&y.gates, &y.dz})
+        if (*p) *p += 4 * h;
+    for (float **p : {&y.Tx, &y.Th, &y.dTh, &y.dTx})
+        if (*p) *p += gr;
+    return y;
+}
+
+static void lp_fill(LpArgs &a, const LpPlan &p, const LstmGeom &g, const LstmRunLayer *l, const float *dh_top, float *ws, int b0 = 0, int BT = 0)
 {
     a = {};
-    for (int q = 0; q < g.L; ++q) a.l[q] = l[q];
-    a.dh_top = dh_top;
+    a.BT = BT ? BT : g.B;
+    for (int q = 0; q < g.L; ++q) a.l[q] = lp_rows(l[q], g, b0);
+    a.dh_top = dh_top ? dh_top + (i64)b0 * g.h : nullptr;
     a.xh = ws;
     a.xt = a.xh + p.xh_step * g.L * (g.T + 1);
     a.sync = (unsigned *)(a.xt + p.xt_step * 2 * g.L * g.T);

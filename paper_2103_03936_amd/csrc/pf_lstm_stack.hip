@@ -876,7 +876,7 @@ static void run_layers(const StackGeom &g, const StackPtrs &p, LstmRunLayer *out
 }
 
 struct StackPlan {
-    size_t n_zx0, n_part, n_part2, n_dT, n_dz, n_pack_f, n_pack_b, n_run_f, n_run_b, fwd_bytes, bwd_bytes;
+    size_t n_zx0, n_part, n_part2, n_dT, n_dz, n_pack_f, n_pack_b, fwd_bytes, bwd_bytes;
 };
 
 // per-layer tensors of the backward pass
@@ -1108,10 +1108,10 @@ static int plan_stack(const StackGeom &g, StackPlan *out)
                   align_up(p.n_pack_b * sizeof(float));
     // (the one-launch recurrence: its exchange buffers instead of slices and copied factors)
     if (lstm_recurrence.run) {
-        p.n_run_f = lstm_recurrence.floats(run_geom(g), false);
-        p.n_run_b = lstm_recurrence.floats(run_geom(g), true);
-        p.fwd_bytes = std::max(p.fwd_bytes, align_up(p.n_part * sizeof(float)) + align_up(p.n_run_f * sizeof(float)));
-        p.bwd_bytes = std::max(p.bwd_bytes, kept + align_up(p.n_part * sizeof(float)) + align_up(p.n_run_b * sizeof(float)));
+        const size_t n_run_f = lstm_recurrence.floats(run_geom(g), false);
+        const size_t n_run_b = lstm_recurrence.floats(run_geom(g), true);
+        p.fwd_bytes = std::max(p.fwd_bytes, align_up(p.n_part * sizeof(float)) + align_up(n_run_f * sizeof(float)));
+        p.bwd_bytes = std::max(p.bwd_bytes, kept + align_up(p.n_part * sizeof(float)) + align_up(n_run_b * sizeof(float)));
     }
     *out = p;
     return PF_OK;
@@ -1186,8 +1186,9 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     const int h = g.h, r = g.r, gr = g.gr;
     const StackTall tall = plan_tall(g);
     const TileProb tx0 = tile_prob(TILE_NN, (int)Mt, gr, g.din, x, g.din, p.Vx[0], gr, nullptr, gr);
-    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), false)) {
-        float *part = ws.take<float>(pl.n_part), *run = ws.take<float>(pl.n_run_f);
+    const size_t room = (pl.fwd_bytes - align_up(pl.n_part * sizeof(float))) / sizeof(float);
+    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), false, room)) {
+        float *part = ws.take<float>(pl.n_part), *run = ws.take<float>(room);
         if (!ws.ok()) return PF_ERR_WORKSPACE;
         st = tall_mid(s, "lstm_stack_Tx0=X*Vx", tall.Tx, tx0, Mt * gr, p.Tx_all[0], part, nullptr);
         if (st != PF_OK) return st;
@@ -1299,8 +1300,10 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x, const 
         b.dTx_all[l] = ws.take<float>(pl.n_dT);
     }
     float *part = ws.take<float>(pl.n_part);
-    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), true)) {
-        float *run = ws.take<float>(pl.n_run_b);
+    const size_t kept = (size_t)L * (align_up(pl.n_dz * sizeof(float)) + 2 * align_up(pl.n_dT * sizeof(float)));
+    const size_t room = (pl.bwd_bytes - kept - align_up(pl.n_part * sizeof(float))) / sizeof(float);
+    if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), true, room)) {
+        float *run = ws.take<float>(room);
         if (!ws.ok()) return PF_ERR_WORKSPACE;
         LstmRunLayer layers[ST_MAX_LAYERS];
         run_layers(g, p, layers);

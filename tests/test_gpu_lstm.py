@@ -530,3 +530,12 @@ def test_layer_stack_few_rows(shape):
     import paper_2103_03936_amd as pf
     T, B, d, h, r, L, G = shape
     _check_stack_case(pf, T, B, d, h, r, L, G, True, 60, str(shape))
+
+
+@pytest.mark.parametrize("shape", [(4, 21, 12, 1100, 5, 2, 1), (5, 32, 8, 1400, 6, 3, 1), (6, 23, 40, 70, 12, 2, 4), (16, 30, 20, 640, 160, 1, 4),
+                                   (4, 22, 16, 300, 75, 3, 4)])
+def test_layer_stack_rows_in_two_launches(shape):
+    """Batches whose row blocks leave the registers no room for the factors: half the rows at a time, of both directions or one."""
+    import paper_2103_03936_amd as pf
+    T, B, d, h, r, L, G = shape
+    _check_stack_case(pf, T, B, d, h, r, L, G, True, 61, str(shape))
