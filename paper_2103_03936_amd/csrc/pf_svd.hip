@@ -16,7 +16,7 @@
 // So singular values far below the largest come out as exactly as without the preconditioner, down to 2^-92 of it or so (V carries
 // 2^-52 of the long columns into the short ones, and what A V rounds of that stays).
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
-// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.35 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.3
+// 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.30 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.3
 // (rounding to float tells the values apart); matrices of lower rank, whose noise takes sweeps either way, 576 x 64 of rank 8 1.67 and 1.22,
 // 2304 x 256 of rank 32 15.0 and 10.3, 1024 x 512 with 16 columns twice 17.2 and 7.8.  A matrix whose eigenvalues lie close without being
 // one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.46, 1024 x 256 8.9 / 9.3.  So does
@@ -70,20 +70,28 @@ __device__ __forceinline__ f64x2_t svd_frag(const double *M, int ld, int col, in
 }
 __device__ __forceinline__ double svd_masked(double v, bool in) { return in ? v : 0.0; }
 
-// Sum over the four wavefronts of a workgroup of a 32 x 32 tile: each has it as 2 x 2 MFMA tiles over its share of the contraction.
+// Sum over the wavefronts of a workgroup of a 32 x 32 tile: each has it as 2 x 2 MFMA tiles over its share of the contraction.
 // put(i, j, sum) for the elements of thread tid.
-template <class PUT>
+template <int WAVES, class PUT>
 __device__ __forceinline__ void svd_tile_out(const f64x4_t (&acc)[2][2], double (&part)[4][32][33], PUT put)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int q = 0; q < WAVES / 4; ++q) { // four at a time
+        if (wave / 4 == q) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) part[wave][16 * a + g + 4 * v][16 * b + c] = acc[a][b][v];
-    __syncthreads();
-    for (int e = tid; e < 1024; e += 256) {
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        double &sum = part[wave & 3][16 * a + g + 4 * v][16 * b + c];
+                        sum = q ? sum + acc[a][b][v] : acc[a][b][v];
+                    }
+        }
+        __syncthreads();
+    }
+    for (int e = tid; e < 1024; e += 64 * WAVES) {
         const int i = e >> 5, j = e & 31;
         put(i, j, (part[0][i][j] + part[1][i][j]) + (part[2][i][j] + part[3][i][j]));
     }
@@ -91,17 +99,15 @@ __device__ __forceinline__ void svd_tile_out(const f64x4_t (&acc)[2][2], double 
 
 constexpr int SVD_U = 4; // pieces of eight contraction indices that a wavefront has in flight
 
-// C = M^T M (symmetric, both halves written), one 32 x 32 tile per workgroup; the wavefronts split the rows, and SVD_U pieces are
+// C = M^T M (symmetric, both halves written), 32 x 32 tile ti, tj <= ti by a workgroup; the wavefronts split the rows, and SVD_U pieces are
 // requested while the SVD_U before are multiplied: a piece takes about a microsecond to arrive, its MFMAs 64 clocks each (2048 x 512:
 // 88 us with one at a time, 64 with SVD_U and a wait before they are multiplied, 36 so; the product of the two below 58 -> 38
-// us).  unless (nullable): nothing is done when it is 0.  place (nullable): -1 for columns that have an inner product other than
-// zero with another.
-__global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *unless,
-                                                        int *place)
+// us; with eight wavefronts, or columns that start in other channels of the L2, the same).  place
+// (nullable): -1 for columns that have an inner product other than zero with another.
+template <int WAVES, int U>
+__device__ __forceinline__ void svd_gram_tile(const double *M, double *C, int nr, int nc, int ld, int ldc, int ti, int tj, int *place,
+                                              double (&part)[4][32][33])
 {
-    if (unless && *unless == 0u) return;
-    const int ti = blockIdx.x, tj = blockIdx.y;
-    if (tj > ti) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
     f64x4_t acc[2][2];
 #pragma unroll
@@ -111,11 +117,11 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
     struct Pieces {
-        f64x2_t x[SVD_U][2], y[SVD_U][2];
+        f64x2_t x[U][2], y[U][2];
     };
     const auto fetch = [&](Pieces &p, int r) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < SVD_U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 p.x[u][a] = svd_frag(M, ld, 32 * ti + 16 * a + c, nc, r + 8 * u + 2 * g, nr);
@@ -125,7 +131,7 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
     };
     const auto multiply = [&](const Pieces &p, int r) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < SVD_U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const bool in = r + 8 * u + 2 * g + e < nr; // (columns past the last give sums that nobody stores)
@@ -139,19 +145,18 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
             }
         __builtin_amdgcn_sched_barrier(0);
     };
-    constexpr int STEP = 32 * SVD_U;
+    constexpr int STEP = 8 * WAVES * U;
     Pieces p0, p1;
-    fetch(p0, 8 * SVD_U * wave);
-    for (int r = 8 * SVD_U * wave; r < nr; r += 2 * STEP) {
+    fetch(p0, 8 * U * wave);
+    for (int r = 8 * U * wave; r < nr; r += 2 * STEP) {
         fetch(p1, r + STEP);
         multiply(p0, r);
         fetch(p0, r + 2 * STEP);
-        multiply(p1, r + STEP);
+        if (r + STEP < nr) multiply(p1, r + STEP);
     }
-    __shared__ double part[4][32][33];
     __shared__ int met[2][32];
     if (tid < 64) met[tid >> 5][tid & 31] = 0;
-    svd_tile_out(acc, part, [&](int i, int j, double s) {
+    svd_tile_out<WAVES>(acc, part, [&](int i, int j, double s) {
         const int gi = 32 * ti + i, gj = 32 * tj + j;
         if (gi < nc && gj < nc && (ti != tj || i >= j)) {
             C[(i64)gj * ldc + gi] = s;
@@ -163,6 +168,14 @@ __global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *
     __syncthreads();
     if (tid < 64 && met[tid >> 5][tid & 31]) place[32 * (tid < 32 ? ti : tj) + (tid & 31)] = -1;
 }
+// instead (nullable): nothing is done where it is set
+__global__ __launch_bounds__(256) void svd_gram_kernel(const double *M, double *C, int nr, int nc, int ld, int ldc, const unsigned *instead,
+                                                        int *place)
+{
+    __shared__ double part[4][32][33];
+    if ((instead && *instead) || blockIdx.y > blockIdx.x) return;
+    svd_gram_tile<4, SVD_U>(M, C, nr, nc, ld, ldc, blockIdx.x, blockIdx.y, place, part);
+}
 
 // The first-order rotation that takes the inner product g_ij of two columns out (0 where they count as orthogonal): with
 // K = (k_ij), k_ij = -k_ji, the columns of B (I + K) are orthogonal to second order.
@@ -173,37 +186,42 @@ __device__ __forceinline__ double svd_small_rotation(double g_ii, double g_jj, d
 // The largest row sum of |K| for which B (I + K) will do: I + K is orthogonal to its square, the rounding level.
 constexpr double SVD_COARSE = 3e-8;
 
-// Counts the pairs of columns whose Gram entry says that they are not orthogonal, and says whether K is too large.  One column
-// per workgroup.
-__global__ __launch_bounds__(256) void svd_check_kernel(const double *G, unsigned *violations, unsigned *coarse, int nc, int ld, double tol,
-                                                         const unsigned *unless)
+// Counts the pairs of columns whose Gram entry says that they are not orthogonal, and says whether K is too large.  Column j by a
+// workgroup, 256 threads of it (red: 256 doubles of LDS).
+__device__ __forceinline__ void svd_check_column(const double *G, unsigned *violations, unsigned *coarse, int j, int nc, int ld, double tol,
+                                                 double *red)
 {
-    if (unless && *unless == 0u) return;
-    const int j = blockIdx.x;
+    const int tid = threadIdx.x;
     const double gj = G[(i64)j * ld + j];
     int bad = 0;
     double sum = 0.0;
-    for (int i = threadIdx.x; i < nc; i += 256) {
+    for (int i = tid; tid < 256 && i < nc; i += 256) {
         if (i == j) continue;
         const double gi = G[(i64)i * ld + i], g = G[(i64)j * ld + i];
         if (svd_orthogonal(gi, gj, g, tol * tol)) continue;
         bad += i > j ? 1 : 0;
         sum += fabs(g / (gj - gi));
     }
-    __shared__ double red[256];
     __shared__ unsigned count;
-    if (threadIdx.x == 0) count = 0u;
-    red[threadIdx.x] = sum;
+    if (tid == 0) count = 0u;
+    if (tid < 256) red[tid] = sum;
     __syncthreads();
     if (bad) atomicAdd(&count, (unsigned)bad);
     for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        if (tid < s) red[tid] += red[tid + s];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         if (count) atomicAdd(violations, count);
-        if (!(red[0] <= SVD_COARSE)) *coarse = 1u;
+        if (!(red[0] <= SVD_COARSE)) __hip_atomic_store(coarse, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    __syncthreads();
+}
+__global__ __launch_bounds__(256) void svd_check_kernel(const double *G, SvdCtrl *ctrl, int nc, int ld, double tol)
+{
+    __shared__ double red[256];
+    if (ctrl->mixed) return;
+    svd_check_column(G, &ctrl->violations[0], &ctrl->coarse[0], blockIdx.x, nc, ld, tol, red);
 }
 
 // How far the columns behind the Gram matrix S may be from orthonormal for one more Newton step to make them so: the norm of
@@ -221,20 +239,18 @@ __global__ __launch_bounds__(256) void svd_mixed_kernel(const double *S, unsigne
 //   SVD_TIMES    right as it is (B = A V)
 //   SVD_NEWTON   right = 3/2 I - S / 2, S the Gram matrix of left's columns: the Newton step towards orthonormal columns; what
 //                rounding left in unit vectors (place) and in their rows goes
-//   SVD_CORRECT  right = I + K from the Gram matrix of left's columns, when a check found violations[0] pairs and K small; rows
-//                from split on go to out2
+//   SVD_CORRECT  right = I + K from the Gram matrix of left's columns; rows from split on go to out2
 enum { SVD_TIMES, SVD_NEWTON, SVD_CORRECT };
-template <int MODE>
-__global__ __launch_bounds__(256) void svd_product_kernel(const double *left, const double *right, double *out, double *out2, int nr, int nc,
-                                                           int ld, int ldr, int ldo, int ldo2, int split, double tol, const SvdCtrl *ctrl,
-                                                           const int *place)
+template <int MODE, int WAVES, int U>
+__device__ __forceinline__ void svd_product_tile(const double *left, const double *right, double *out, double *out2, int nr, int nc, int ld,
+                                                 int ldr, int ldo, int ldo2, int split, double tol, int units, const int *place, int ti, int tj,
+                                                 double (&part)[4][32][33])
 {
-    if (MODE == SVD_CORRECT && (ctrl->violations[0] == 0u || ctrl->coarse[0])) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const int j0 = blockIdx.y * 32, i0 = blockIdx.x * 32;
+    const int j0 = tj * 32, i0 = ti * 32;
     f64x4_t acc[2][2];
     double gj[2] = {1.0, 1.0};
-    const int unit = MODE == SVD_NEWTON ? place[min(i0 + (tid & 31), nc - 1)] : -1, units = MODE == SVD_NEWTON ? (int)ctrl->isolated : 0;
+    const int unit = MODE == SVD_NEWTON ? place[min(i0 + (tid & 31), nc - 1)] : -1;
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
         const int j = j0 + 16 * a + c;
@@ -245,11 +261,11 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0;
     }
     struct Pieces {
-        f64x2_t x[SVD_U][2], y[SVD_U][2], gk[SVD_U];
+        f64x2_t x[U][2], y[U][2], gk[U];
     };
     const auto fetch = [&](Pieces &p, int k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < SVD_U; ++u) {
+        for (int u = 0; u < U; ++u) {
             const int kk = k + 8 * u + 2 * g;
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
@@ -266,7 +282,7 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
     };
     const auto multiply = [&](const Pieces &p, int k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < SVD_U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int kk = k + 8 * u + 2 * g + e;
@@ -288,17 +304,16 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
             }
         __builtin_amdgcn_sched_barrier(0);
     };
-    constexpr int STEP = 32 * SVD_U;
+    constexpr int STEP = 8 * WAVES * U;
     Pieces p0, p1;
-    fetch(p0, 8 * SVD_U * wave);
-    for (int k = 8 * SVD_U * wave; k < nc; k += 2 * STEP) {
+    fetch(p0, 8 * U * wave);
+    for (int k = 8 * U * wave; k < nc; k += 2 * STEP) {
         fetch(p1, k + STEP);
         multiply(p0, k);
         fetch(p0, k + 2 * STEP);
-        multiply(p1, k + STEP);
+        if (k + STEP < nc) multiply(p1, k + STEP);
     }
-    __shared__ double part[4][32][33];
-    svd_tile_out(acc, part, [&](int jj, int ii, double s) {
+    svd_tile_out<WAVES>(acc, part, [&](int jj, int ii, double s) {
         const int j = j0 + jj, i = i0 + ii;
         if (j >= nc || i >= nr) return;
         if (MODE == SVD_NEWTON && (unit >= 0 || j < units)) s = unit == j ? 1.0 : 0.0; // (ii is tid & 31)
@@ -310,50 +325,55 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
     });
 }
 
-// the corrected columns back into BV
-__global__ __launch_bounds__(256) void svd_corrected_kernel(const double *B, const double *V, double *BV, int ldb, int split, int ldv,
-                                                             const SvdCtrl *ctrl)
+template <int MODE>
+__global__ __launch_bounds__(256) void svd_product_kernel(const double *left, const double *right, double *out, int nr, int nc, int ld, int ldr,
+                                                                 int ldo, const SvdCtrl *ctrl, const int *place)
 {
-    if (ctrl->violations[0] == 0u || ctrl->coarse[0]) return;
-    const int j = blockIdx.x;
-    for (int i = threadIdx.x; i < ldb; i += 256)
-        BV[(i64)j * ldb + i] = i < split ? B[(i64)j * split + i] : V[(i64)j * ldv + i - split];
+    __shared__ double part[4][32][33];
+    if (MODE == SVD_TIMES && ctrl->mixed) return;
+    svd_product_tile<MODE, 4, SVD_U>(left, right, out, nullptr, nr, nc, ld, ldr, ldo, 0, 0, 0.0, MODE == SVD_NEWTON ? (int)ctrl->isolated : 0, place,
+                                  blockIdx.x, blockIdx.y, part);
 }
 
 // L[:, j] /= |L[:, j]|, also into the V part of BV (rows v0 ..)
-__global__ __launch_bounds__(256) void svd_normalise_kernel(double *L, double *BV, int nc, int ldl, int ldb, int v0, const unsigned *unless)
+__device__ __forceinline__ void svd_normalise(double *L, double *BV, int j, int nc, int ldl, int ldb, int v0, double *red)
 {
-    if (unless && *unless == 0u) return;
-    double *a = L + (i64)blockIdx.x * ldl, *b = BV + (i64)blockIdx.x * ldb;
+    const int tid = threadIdx.x;
+    double *a = L + (i64)j * ldl, *b = BV + (i64)j * ldb;
     double acc = 0.0;
-    for (int i = threadIdx.x; i < nc; i += 256) acc += a[i] * a[i];
-    __shared__ double red[256];
-    red[threadIdx.x] = acc;
+    for (int i = tid; tid < 256 && i < nc; i += 256) acc += a[i] * a[i];
+    if (tid < 256) red[tid] = acc;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+        if (tid < s) red[tid] += red[tid + s];
         __syncthreads();
     }
     const double n = sqrt(red[0]), inv = n > 0.0 ? 1.0 / n : 0.0;
-    for (int i = threadIdx.x; i < nc; i += 256) {
+    for (int i = tid; i < nc; i += SVD_NT) {
         a[i] *= inv;
         b[v0 + i] = a[i];
     }
     // (the padding row between the two parts, and the one below)
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         for (int i = v0 + nc; i < ldb; ++i) b[i] = 0.0;
     }
+    __syncthreads();
 }
 
 // ------------------------------------------------------------------ grid barrier
 // Every workgroup of a cooperative launch is resident, so all of them arrive.  The wait is bounded all the same;
-// false: some workgroup gave up, and everyone leaves.
-__device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *failed, unsigned &generation, unsigned nwg)
+// false: some workgroup gave up, and everyone leaves.  patient: the others are sweeping, and polls 10 us apart
+// (of 124 waiting workgroups, at two a microsecond beside 132 sweeping ones, the barriers of these took a quarter longer).
+// shared: what others read was stored for them (agent scope), and has only to be complete.
+__device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *failed, unsigned &generation, unsigned nwg, bool patient = false, bool shared = false)
 {
     __shared__ int ok;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
     __syncthreads();
     if (threadIdx.x == 0) {
-        __threadfence(); // what this workgroup wrote is visible before it arrives
+        if (!shared) __threadfence(); // what this workgroup wrote is visible before it arrives
         generation += nwg;
         __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int good = 0;
@@ -363,7 +383,12 @@ __device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *fa
                 break;
             }
             if ((spin & 255) == 255 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            __builtin_amdgcn_s_sleep(1);
+            if (patient) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) __builtin_amdgcn_s_sleep(127);
+            } else {
+                __builtin_amdgcn_s_sleep(1);
+            }
         }
         if (!good) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence(); // and what the others wrote before they arrived is read afresh
@@ -519,7 +544,7 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
             const int cc = column(k);
-            if (cc < nc) M[(i64)cc * ld + row] = x[k];
+            if (cc < nc) __hip_atomic_store(&M[(i64)cc * ld + row], x[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
     return rotations;
@@ -529,13 +554,13 @@ __device__ __forceinline__ int svd_block_pair(double *M, int ld, int nc, int nr,
 // gave up.
 __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, int rows, double tol, SvdShort few, int most, unsigned *arrived,
                                            unsigned &generation, unsigned *rot, bool quick, SvdCtrl *ctrl, SvdShared &sh,
-                                           int *ran, const double *known = nullptr, int ldk = 0)
+                                           int *ran, unsigned nwg, const double *known = nullptr, int ldk = 0)
 {
     const int nbl = ((nc + SVD_B - 1) / SVD_B + 1) / 2 * 2, m1 = nbl - 1;
     int sweep = 0;
     for (; sweep < most; ++sweep) {
         for (int round = 0; round < m1; ++round) {
-            for (int k = blockIdx.x; k < nbl / 2; k += gridDim.x) {
+            for (int k = blockIdx.x; k < nbl / 2; k += nwg) {
                 int p = k == 0 ? m1 : (round + k) % m1, q = k == 0 ? round % m1 : (round - k + m1) % m1;
                 if (p > q) {
                     const int t = p;
@@ -543,13 +568,13 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
                     q = t;
                 }
                 bool large = false, held = false;
-                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, few, sh, large, held, known, ldk);
+                const int did = svd_block_pair(M, ld, nc, nr, rows, p, q, round == 0, tol, few, sh, large, held, sweep == 0 ? known : nullptr, ldk);
                 if (held && threadIdx.x == 0) __hip_atomic_store(&ctrl->held[sweep], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (did > 0 && (large || !quick) && threadIdx.x == 0)
                     __hip_atomic_fetch_add(&rot[sweep], (unsigned)did, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads(); // (the LDS tables are used again)
             }
-            if (!svd_grid_barrier(arrived, &ctrl->failed, generation, gridDim.x)) return false;
+            if (!svd_grid_barrier(arrived, &ctrl->failed, generation, nwg, false, true)) return false;
         }
         if (__hip_atomic_load(&rot[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
             if (few.low > 0.0 && __hip_atomic_load(&ctrl->held[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
@@ -564,22 +589,17 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
     return true;
 }
 
-// G (overwritten) -> L with G + shift I = L L^T, sixteen columns at a time; then one-sided Jacobi on L.
-__global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel,
-                                                                   double tol, const unsigned *unless)
+// G (overwritten) -> L with G + shift I = L L^T, sixteen columns at a time.
+// By workgroups 0 .. nwg - 1; false: a barrier gave up.
+__device__ __forceinline__ bool svd_factorize(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel, unsigned nwg, unsigned &generation, double *red)
 {
-    if (unless && *unless == 0u) return;
-    __shared__ SvdShared sh;
     __shared__ double d[16][17];
     __shared__ double shift_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, g = lane >> 4;
-    const unsigned nwg = gridDim.x;
-    unsigned generation = 0;
     // the shift: rounding level of the largest diagonal entry (read by every workgroup before anyone changes G)
     {
         double m = 0.0;
         for (int i = tid; i < nc; i += SVD_NT) m = fmax(m, G[(i64)i * ld + i]);
-        double *red = &sh.part[0][0][0];
         red[tid] = m;
         __syncthreads();
         if (tid == 0) {
@@ -589,7 +609,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, dou
         __syncthreads();
     }
     const double shift = shift_s;
-    if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
+    if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return false;
     for (int p0 = 0; p0 < nc; p0 += 16) {
         const int w = min(16, nc - p0);
         // the diagonal block, by every workgroup
@@ -630,7 +650,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, dou
         }
         for (i64 e = (i64)blockIdx.x * SVD_NT + tid; e < (i64)p0 * w; e += (i64)nwg * SVD_NT)
             L[(p0 + e / p0) * ld + e % p0] = 0.0; // above the diagonal block
-        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
+        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return false;
         // trailing blocks: G_ij -= X_i X_j^T, one 16 x 16 tile per wavefront
         const int n0 = p0 + 16, nt = n0 < nc ? (nc - n0 + 15) / 16 : 0;
         for (i64 t = (i64)blockIdx.x * (SVD_NT / 64) + wave; t < (i64)nt * nt; t += (i64)nwg * (SVD_NT / 64)) {
@@ -656,41 +676,134 @@ __global__ __launch_bounds__(SVD_NT) void svd_precondition_kernel(double *G, dou
                 if (i < nc && j < nc) G[(i64)j * ld + i] = acc[v];
             }
         }
-        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return;
+        if (!svd_grid_barrier(&ctrl->arrived[0], &ctrl->failed, generation, nwg)) return false;
     }
-    int ran = 0;
-    (void)svd_sweeps(L, ld, nc, nc, nc, tol, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran);
+    return true;
 }
 
-// One-sided Jacobi on B with V carried along, when a check found pairs to rotate.  First one sweep over the pairs of blocks that
-// have any (a preconditioned basis usually leaves few, by rounding: 2048 x 512 13.2 -> 11.9 ms, where a sweep over everything
-// and another that finds nothing followed); after the second check, sweeps over everything.
-__global__ __launch_bounds__(SVD_NT) void svd_finish_kernel(double *BV, const double *G, SvdCtrl *ctrl, int nr, int nc, int rows, int ld,
-                                                             int ldg, double tol, int first)
+// The preconditioner alone, for more columns than the eigenvectors take: in the kernel below its loops have fewer registers (2200 x 2100: 139 ms
+// a call, 115 so; 1024 x 256 with values down to 1e-6 of the largest, whose eigenvectors do not do, 5.62 in it and 5.46 in a launch of its own).
+__global__ __launch_bounds__(SVD_NT) void svd_jacobi_kernel(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel, double tol)
 {
     __shared__ SvdShared sh;
     unsigned generation = 0;
     int ran = 0;
+    if (svd_factorize(G, L, ctrl, nc, ld, rel, gridDim.x, generation, &sh.part[0][0][0]))
+        (void)svd_sweeps(L, ld, nc, nc, nc, tol, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl, sh, &ran, gridDim.x);
+}
+
+// What an ordinary call does not need, in one launch: a cooperative one costs 22 us around it even if it has nothing to do, and a launch
+// that leaves at once 2 to 5.  (Three of the first and six of the second took their places before: 2048 x 512 1356 -> 1302 us a call, 576 x 64
+// 266 -> 205, 320 x 240 604 -> 550.)  Jacobi as the preconditioner, where the eigenvectors do not do (ctrl->mixed) or were not formed, and B from it; the
+// correction B (I + K) or, where K is too large, one sweep over the pairs of blocks that have pairs to rotate (a preconditioned basis usually
+// leaves few, by rounding: 2048 x 512 13.2 -> 11.9 ms, where a sweep over everything and another that finds nothing followed); a second
+// check, and sweeps over everything.  The sweeps' workgroups are one per pair of blocks, the first `sweepers`; products are dealt to all.
+struct SvdRest {
+    double *At, *G, *L, *BV;
+    SvdCtrl *ctrl;
+    int nr, nc, lda, ldn, ldb, sweepers, jacobi, swept; // jacobi: whatever ctrl->mixed says; swept: L is there
+    double tol, tol_v, rel;
+};
+__global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
+{
+    SvdCtrl *ctrl = a.ctrl;
+    const int nr = a.nr, nc = a.nc, tiles = (nc + 31) / 32, wg = blockIdx.x, nwg = gridDim.x;
+    const bool jacobi = a.jacobi || ctrl->mixed;
+    unsigned found = ctrl->violations[0], coarse = ctrl->coarse[0], later = 0u;
     bool ok = ctrl->failed == 0u;
-    const unsigned found = first ? (ctrl->coarse[0] ? ctrl->violations[0] : 0u) : ctrl->violations[1]; // (else corrected already)
+    int ran = 0, before = 1; // sweeps; before them
     SvdShort few = {0.0, 0.0};
-    if (ok && found != 0u) {
-        double longest = 0.0;
-        for (int j = threadIdx.x; j < nc; j += SVD_NT) longest = fmax(longest, G[(i64)j * ldg + j]);
-        for (int s = 32; s > 0; s >>= 1) longest = fmax(longest, __shfl_xor(longest, s, 64));
-        if ((threadIdx.x & 63) == 0) sh.part[0][0][threadIdx.x >> 6] = longest;
-        __syncthreads();
+    if (ok && (jacobi || found)) {
+        __shared__ SvdShared sh;
+        __shared__ double part[4][32][33];
+        double *red = &part[0][0][0];
+        constexpr int W = SVD_NT / 64;
+        const bool sweeps = wg < a.sweepers;
+        const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2, crew = pairs < a.sweepers ? pairs : a.sweepers; // (B's: no more than have a pair)
+        unsigned everyone = 0;
+        const auto meet = [&](bool swept = false) { return svd_grid_barrier(&ctrl->everyone, &ctrl->failed, everyone, nwg, swept && !sweeps); };
+        const auto gram = [&](const double *M, int ld) {
+            for (int t = wg; t < tiles * tiles; t += nwg) {
+                if (t % tiles > t / tiles) continue;
+                svd_gram_tile<W, 1>(M, a.G, nr, nc, ld, a.ldn, t / tiles, t % tiles, (int *)nullptr, part);
+                __syncthreads(); // (the sums' LDS is used again)
+            }
+        };
+        const auto counted = [&](const unsigned *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        // Sweeps of L, of B where the first check found pairs, of B where the second did
+#pragma unroll 1
+        for (int stage = jacobi ? 0 : 1; ok && stage < 3; ++stage) {
+            const bool first = stage == 0;
+            if (first && !a.swept) {
+                gram(a.At, a.lda);
+                ok = meet();
+            }
+            const unsigned now = first ? 1u : stage == 1 ? found : later;
+            if (!ok || now == 0u) break;
+            // (half of all pairs or more: another check would only say that there are some left)
+            const bool many = stage == 1 && coarse && found > (unsigned)nc * (nc - 1) / 4u;
+            if (many) later = found, stage = 2;
+            if (stage != 1 || coarse) {
+                few = SvdShort{0.0, 0.0};
+                if (!first) {
+                    double longest = 0.0;
+                    for (int j = threadIdx.x; j < nc; j += SVD_NT) longest = fmax(longest, a.G[(i64)j * a.ldn + j]);
+                    for (int s = 32; s > 0; s >>= 1) longest = fmax(longest, __shfl_xor(longest, s, 64));
+                    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = longest;
+                    __syncthreads();
 #pragma unroll
-        for (int w = 0; w < SVD_NT / 64; ++w) longest = fmax(longest, sh.part[0][0][w]);
-        few = svd_short(longest);
-        __syncthreads();
-        ok = svd_sweeps(BV, ld, nc, nr, rows, tol, few, first ? 1 : SVD_MAX_SWEEPS - 1, &ctrl->arrived[first ? 1 : 2], generation,
-                        ctrl->rot[first ? 1 : 2], false, ctrl, sh, &ran, first ? G : nullptr, ldg);
+                    for (int w = 0; w < W; ++w) longest = fmax(longest, red[w]);
+                    __syncthreads();
+                    few = svd_short(longest);
+                }
+                unsigned generation = 0;
+                if (sweeps && first && !a.swept) // (a call of its own: what it has no use for goes)
+                    ok = svd_factorize(a.G, a.L, ctrl, nc, a.ldn, a.rel, a.sweepers, generation, red) &&
+                         svd_sweeps(a.L, a.ldn, nc, nc, nc, a.tol_v, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl,
+                                    sh, &ran, a.sweepers);
+                else if (!first && wg < crew)
+                    ok = svd_sweeps(a.BV, a.ldb, nc, nr, a.ldb, a.tol, few, stage == 1 ? 1 : SVD_MAX_SWEEPS - 1 + many, &ctrl->arrived[stage], generation,
+                                    ctrl->rot[stage], false, ctrl, sh, &ran, crew, stage == 1 || many ? a.G : nullptr, a.ldn);
+                before = many ? 0 : 1;
+                if (stage == 2) break;
+            } else { // (into At and L, and back)
+                const int down = (a.ldb + 31) / 32;
+                for (int t = wg; t < down * tiles; t += nwg) {
+                    svd_product_tile<SVD_CORRECT, W, 1>(a.BV, a.G, a.At, a.L, a.ldb, nc, a.ldb, a.ldn, a.lda, a.ldn, a.lda, a.tol, 0, nullptr, t % down,
+                                                     t / down, part);
+                    __syncthreads();
+                }
+                ok = meet();
+                for (int j = wg; ok && j < nc; j += nwg)
+                    for (int i = threadIdx.x; i < a.ldb; i += SVD_NT)
+                        a.BV[(i64)j * a.ldb + i] = i < a.lda ? a.At[(i64)j * a.lda + i] : a.L[(i64)j * a.ldn + i - a.lda];
+            }
+            ok = ok && meet(true);
+            if (first) {
+                for (int j = wg; ok && j < nc; j += nwg) svd_normalise(a.L, a.BV, j, nc, a.ldn, a.ldb, a.lda, red);
+                ok = ok && meet();
+                const int down = (a.lda + 31) / 32;
+                for (int t = wg; ok && t < down * tiles; t += nwg) {
+                    svd_product_tile<SVD_TIMES, W, 1>(a.At, a.BV + a.lda, a.BV, nullptr, a.lda, nc, a.lda, a.ldb, a.ldb, 0, 0, 0.0, 0, nullptr, t % down,
+                                                   t / down, part);
+                    __syncthreads();
+                }
+                ok = ok && meet();
+            }
+            if (ok) gram(a.BV, a.ldb);
+            ok = ok && meet();
+            for (int j = wg; ok && j < nc; j += nwg)
+                svd_check_column(a.G, &ctrl->violations[stage], &ctrl->coarse[stage], j, nc, a.ldn, a.tol, red);
+            ok = ok && meet();
+            if (first) found = counted(&ctrl->violations[0]), coarse = counted(&ctrl->coarse[0]);
+            else later = counted(&ctrl->violations[1]);
+            if (!first) few = SvdShort{0.0, 0.0};
+        }
     }
-    if (!first && blockIdx.x == 0 && threadIdx.x == 0) {
+    if (wg == 0 && threadIdx.x == 0) {
         // (a check that found nothing counts as one clean sweep)
-        ctrl->sweeps = !ok ? SVD_MAX_SWEEPS : ctrl->violations[0] == 0u ? 1 : found == 0u ? 2 : 1 + ran;
-        ctrl->last = !ok ? 1u : found == 0u ? 0u : ctrl->rot[2][ran - 1];
+        ctrl->sweeps = !ok ? SVD_MAX_SWEEPS : found == 0u ? 1 : later == 0u ? 2 : before + ran;
+        ctrl->last = !ok ? 1u : later == 0u ? 0u : ctrl->rot[2][ran - 1];
         ctrl->nil = few.nil;
     }
 }
@@ -803,55 +916,41 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void
     PF_LAUNCH(st, "svd_init", svd_init_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), s, (const float *)W, At, ctrl, rank,
               (int)d->n, nr, nc, p.lda, p.transposed);
     const dim3 gram((nc + 31) / 32, (nc + 31) / 32);
-    // one workgroup per pair of blocks (at least eight for the factorization), all of them resident
-    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2;
-    const int nwg = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
     double *V = BV + p.lda; // (leading dimension ldb, as B's)
     const dim3 square((nc + 31) / 32, (nc + 31) / 32);
+    const unsigned *none = nullptr;
     // V: eigenvectors of G made orthonormal; where they cannot be (ctrl->mixed), and for few or very many columns, by Jacobi
-    const bool eigen = svd_takes_eigenvectors(nc, cooperative_cus());
-    const unsigned *unless = eigen ? &ctrl->mixed : nullptr;
-    int *const place = rank; // (before the ranks are there)
-    PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn,
-              (const unsigned *)nullptr, eigen ? place : (int *)nullptr);
+    const int cus = cooperative_cus();
+    const bool eigen = svd_takes_eigenvectors(nc, cus);
     if (eigen) {
+        int *const place = rank; // (before the ranks are there)
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, none, place);
         if (st == PF_OK) st = launch_svd_eigenvectors(s, G, L, sig, BV, place, ctrl, nc, p.ldn);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nc, nc, p.ldn, p.ldn,
-                  (const unsigned *)nullptr, (int *)nullptr);
-        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)BV, (const double *)G, L,
-                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldn, 0, 0, 0.0, (const SvdCtrl *)ctrl, (const int *)place);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)L, G, nc, nc, p.ldn, p.ldn,
-                  (const unsigned *)nullptr, (int *)nullptr);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nc, nc, p.ldn, p.ldn, none, (int *)nullptr);
+        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)BV, (const double *)G, L, nc, nc, p.ldn,
+                  p.ldn, p.ldn, (const SvdCtrl *)ctrl, (const int *)place);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)L, G, nc, nc, p.ldn, p.ldn, none, (int *)nullptr);
         PF_LAUNCH(st, "svd_mixed", svd_mixed_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->mixed, nc, p.ldn);
-        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)L, (const double *)G, V,
-                  (double *)nullptr, nc, nc, p.ldn, p.ldn, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl, (const int *)place);
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, unless,
+        PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)L, (const double *)G, V, nc, nc, p.ldn,
+                  p.ldn, p.ldb, (const SvdCtrl *)ctrl, (const int *)place);
+        PF_LAUNCH(st, "svd_apply", svd_product_kernel<SVD_TIMES>, dim3((p.lda + 31) / 32, (nc + 31) / 32), dim3(256), s, (const double *)At,
+                  (const double *)V, BV, p.lda, nc, p.lda, p.ldb, p.ldb, (const SvdCtrl *)ctrl, (const int *)nullptr);
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, (const unsigned *)&ctrl->mixed,
                   (int *)nullptr);
+        PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3(nc), dim3(256), s, (const double *)G, ctrl, nc, p.ldn, svd_tolerance(nr));
     }
-    if (st == PF_OK)
-        st = launch_cooperative(s, "svd_precondition", svd_precondition_kernel, nwg, SVD_NT, G, L, ctrl, nc, p.ldn,
-                                16.0 * 2.220446049250313e-16 * (nc + 16), svd_tolerance_v(nc), unless);
-    PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda, unless);
-    PF_LAUNCH(st, "svd_apply", svd_product_kernel<SVD_TIMES>, dim3((p.lda + 31) / 32, (nc + 31) / 32), dim3(256), s, (const double *)At,
-              (const double *)V, BV, (double *)nullptr, p.lda, nc, p.lda, p.ldb, p.ldb, 0, 0, 0.0, (const SvdCtrl *)ctrl,
-              (const int *)nullptr);
-    for (int first = 1; first >= 0; --first) {
-        unless = first ? nullptr : &ctrl->violations[0];
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, unless,
-                  (int *)nullptr);
-        PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->violations[1 - first],
-                  &ctrl->coarse[1 - first], nc, p.ldn, svd_tolerance(nr), unless);
-        if (first) {
-            PF_LAUNCH(st, "svd_correct", svd_product_kernel<SVD_CORRECT>, dim3((p.ldb + 31) / 32, (nc + 31) / 32), dim3(256), s,
-                      (const double *)BV, (const double *)G, At, L, p.ldb, nc, p.ldb, p.ldn, p.lda, p.ldn, p.lda, svd_tolerance(nr),
-                      (const SvdCtrl *)ctrl, (const int *)nullptr);
-            PF_LAUNCH(st, "svd_corrected", svd_corrected_kernel, dim3(nc), dim3(256), s, (const double *)At, (const double *)L, BV, p.ldb,
-                      p.lda, p.ldn, (const SvdCtrl *)ctrl);
-        }
-        if (st == PF_OK)
-            st = launch_cooperative(s, "svd_finish", svd_finish_kernel, nwg, SVD_NT, BV, (const double *)G, ctrl, nr, nc, p.ldb, p.ldb, p.ldn,
-                                    svd_tolerance(nr), first);
+    // sweeps: one workgroup per pair of blocks (at least eight for the factorization); products: one per tile; all of them resident
+    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2, sweepers = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
+    const i64 tiles = (i64)((p.lda + 31) / 32) * ((nc + 31) / 32);
+    const int most = cus > 256 ? 256 : cus, wide = tiles < most ? (int)tiles : most;
+    const bool alone = !eigen && nc > SVD_EIGEN_MAX;
+    const double rel = 16.0 * 2.220446049250313e-16 * (nc + 16);
+    if (alone) {
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, none, (int *)nullptr);
+        if (st == PF_OK) st = launch_cooperative(s, "svd_jacobi", svd_jacobi_kernel, sweepers, SVD_NT, G, L, ctrl, nc, p.ldn, rel, svd_tolerance_v(nc));
     }
+    const SvdRest rest = {At, G, L, BV, ctrl, nr, nc, p.lda, p.ldn, p.ldb, sweepers, !eigen, alone, svd_tolerance(nr), svd_tolerance_v(nc), rel};
+    if (st == PF_OK) st = launch_cooperative(s, "svd_rest", svd_rest_kernel, eigen && wide > sweepers ? wide : sweepers, SVD_NT, rest);
     PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, ctrl, nr, p.ldb);
     PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 3) / 4), dim3(256), s, (const double *)sig, rank, nc);
     PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(nc), dim3(256), s, (const double *)BV, (const double *)sig,

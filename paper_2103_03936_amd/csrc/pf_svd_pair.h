@@ -12,7 +12,7 @@ typedef __attribute__((ext_vector_type(2))) double f64x2_t;
 
 // Device-side state of a call
 struct SvdCtrl {
-    unsigned arrived[3];    // grid barriers of the three cooperative launches
+    unsigned arrived[3];    // grid barriers: of the preconditioner's sweeps, of B's first and of B's others
     unsigned failed;        // a barrier's wait ran out
     unsigned broken;        // a singular value is not finite: the matrix was not
     unsigned isolated;      // columns of the matrix that are orthogonal to all others, to the bit (zero columns among them)
@@ -24,6 +24,8 @@ struct SvdCtrl {
     unsigned sweeps;        // sweeps over the pairs of B, a check that found nothing included
     unsigned last;          // pairs rotated in the last of them
     double nil;             // squared norm below which a column of B is zero
+    unsigned apart[64];     // (those who wait for the sweeps poll a line of their own)
+    unsigned everyone;      // a barrier of all workgroups
 };
 
 // What a call reports: sweeps, rotations of the last one, and whether its outputs are worth nothing because a barrier's wait

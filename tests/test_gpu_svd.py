@@ -335,3 +335,16 @@ def test_clustered_matrices(kind):
     assert np.linalg.norm(got - W) <= 2.0 ** -22 * np.linalg.norm(W.astype(np.float64))
     ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
     assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]
+
+
+@pytest.mark.parametrize("m,n", [(2049, 2049), (2100, 2056)])
+def test_more_columns_than_the_eigenvectors_take(m, n):
+    """Jacobi as the preconditioner in a launch of its own.  Bounds as for lower ranks."""
+    import paper_2103_03936_amd as pf
+    W = _matrix(m, n, 97)
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+    assert int(info[1]) == 0
+    w = torch.from_numpy(W).double()
+    assert float((U.double().cpu() @ V.double().cpu().T - w).norm()) <= 2.0 ** -22 * float(w.norm())
+    ref = torch.linalg.eigvalsh(w.T @ w).clamp_min(0).sqrt().flip(0)  # (to 2^-53 of the largest eigenvalue, 2^-26 of its root)
+    assert float((sigma.double().cpu() - ref).abs().max()) <= 2.0 ** -23 * float(ref[0])
