@@ -211,22 +211,34 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     if (tab > 28 * 1024) return;
     p.tiles = true;
     const i64 npx = (i64)g.N * HC * V;
-    p.sh_T = g.r <= 32 ? TS_32x64 : TS_64;
     p.sh_Y = g.Cout <= 32 ? TS_32x64 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
-    p.sh_dT = p.sh_T;
+    // Tiles that leave half the chip idle, splits and all: half as high, for a chunk of theirs takes half the time and they are twice as many.
+    // Both directions, us, 64 x 64 / 32 x 64, at most 128 of them: float 6 x 224 x 5 x 5, rank 39 60.0 / 54.4, 26 x 256 x 8 x 8, rank 64, stride 2
+    // 64.8 / 60.3, bf16 22 x 384 x 5 x 5, rank 80 56 / 53.5; with a full chip they are the slower ones (float 6 x 396 x 16 x 16, rank 99, T in
+    // 384 workgroups 110 / 118); bf16 T and dT from 64 on (36 x 343 x 12 x 12, rank 61, 81 tiles 45 / 46.4).
     // T and dT: too few tiles for the chip split their contraction (at least four chunks each)
-    const auto split_k = [&](i64 K) {
-        const i64 bm = g.r <= 32 ? 32 : 64, tiles = (g.r + bm - 1) / bm * ((npx + 63) / 64), chunks = (K + 8 * V - 1) / (8 * V);
+    const auto split_k = [&](i64 K, i64 bm, i64 &tiles) {
+        tiles = (g.r + bm - 1) / bm * ((npx + 63) / 64);
+        const i64 chunks = (K + 8 * V - 1) / (8 * V);
         i64 ks = tiles >= 200 ? 1 : 384 / tiles;
         if (ks > chunks / 4) ks = chunks / 4;
         if (ks > 16) ks = 16;
         return (int)(ks < 1 ? 1 : ks);
     };
-    p.ks_T = split_k((i64)g.C * kk);
-    p.ks_dT = split_k(g.Cout);
+    const auto mid = [&](i64 K, TileShape &shape, int &ks) {
+        i64 tiles = 0;
+        ks = split_k(K, 64, tiles);
+        shape = g.r <= 32 || tiles * ks <= (dtype == PF_BF16 ? 64 : 128) ? TS_32x64 : TS_64;
+        if (shape == TS_32x64) ks = split_k(K, 32, tiles);
+    };
+    mid((i64)g.C * kk, p.sh_T, p.ks_T);
+    mid(g.Cout, p.sh_dT, p.ks_dT);
+    if (p.sh_Y == TS_64 && (g.Cout + 63) / 64 * ((npx + 63) / 64) <= 128) p.sh_Y = TS_32x64;
     const size_t part_T = (size_t)(p.ks_T > p.ks_dT ? p.ks_T : p.ks_dT) * g.r * npx;
     p.n_part_T = p.ks_T > 1 || p.ks_dT > 1 ? part_T : 0;
-    p.sh_g = TS_64;
+    // dX in float, beside the gradients: 9 x 272 x 5 x 5 71 / 65, 4 x 448 x 13 x 13 92 / 83; 52 x 64 x 9 x 9, 134 tiles 50 / 57; bf16 3 x 320 x 12 x
+    // 12 48 / 51; the phases of stride 2 within 3 % either way.
+    p.sh_g = dtype == PF_F32 && g.s == 1 && (g.C + 63) / 64 * ((npx + 63) / 64) <= 96 ? TS_32x64 : TS_64;
     p.sh_w = g.r <= 32 ? TS_32x128 : TS_64;
     // both filter gradients in one launch: about two workgroups per compute unit, each at least four chunks long.  With at most 32
     // filters the gradients of both stages have the rank as their rows (dVp is formed transposed).

@@ -152,7 +152,14 @@ int launch_conv_t(hipStream_t s, const char *name, TileShape shape, TileShape wg
     typedef TileCfg<64, 64, 2, 2, 2> S64;
     typedef TileCfg<32, 128, 1, 4, 2> W32;
     switch (shape) {
-    case TS_32x64: return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, W32>(s, name, a); // (forward, or at most 32 channels)
+    case TS_32x64: {
+        bool grads = false;
+        for (int i = 0; i < a.n; ++i) grads = grads || a.p[i].type == TILE_WG || a.p[i].type == TILE_WGT;
+        if constexpr (sizeof(CT) == 4)
+            if (grads && wg == TS_64) return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, S64>(s, name, a);
+        if (grads && wg != TS_32x128) return PF_ERR_UNSUPPORTED;
+        return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, W32>(s, name, a);
+    }
     case TS_64: return wg == TS_32x128 ? launch_conv<CT, S64, W32>(s, name, a) : launch_conv<CT, S64, S64>(s, name, a);
     case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>, S64>(s, name, a);
     default: return PF_ERR_UNSUPPORTED;
