@@ -225,14 +225,22 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
         if (ks > 16) ks = 16;
         return (int)(ks < 1 ? 1 : ks);
     };
-    const auto mid = [&](i64 K, TileShape &shape, int &ks) {
+    const auto mid = [&](i64 K, bool taps, TileShape &shape, int &ks) {
         i64 tiles = 0;
         ks = split_k(K, 64, tiles);
         shape = g.r <= 32 || tiles * ks <= (dtype == PF_BF16 ? 64 : 128) ? TS_32x64 : TS_64;
         if (shape == TS_32x64) ks = split_k(K, 32, tiles);
+        // Short chains without a split, where it would cost more than it saves: a launch for the sums (4.3 us and their bytes) against chunks of
+        // 0.5 us in float, 0.3 in bf16, while a compute unit has one or two tiles.  Both directions, us, split / not: float 128 x 128 x 16 x 16 ->
+        // 256, rank 64, stride 2 105.7 / 102.0, 26 x 256 x 8 x 8 59.3 / 56.8, 75 x 512 x 18 x 7, rank 151, 1 x 1 138 / 131; bf16 12 x 464 x 4 x 4 51.8 /
+        // 49.8; but float 2 x 192 x 13 x 13 -> 448, 14 chunks 56.0 / 58.5.
+        const bool bf = dtype == PF_BF16;
+        const double chunks = (double)((K + 8 * V - 1) / (8 * V)), low = (double)((g.r + 31) / 32 * ((npx + 63) / 64)) / 256;
+        const double alone = chunks * (bf ? 0.3 : 0.5) * (low > 1 ? low : 1);
+        if (!taps && ks > 1 && low <= 2 && alone < 3.3 + ks * g.r * npx * 2.7e-6 + alone / ks) shape = TS_32x64, ks = 1;
     };
-    mid((i64)g.C * kk, p.sh_T, p.ks_T);
-    mid(g.Cout, p.sh_dT, p.ks_dT);
+    mid((i64)g.C * kk, kk > 1 || p.gather, p.sh_T, p.ks_T);
+    mid(g.Cout, false, p.sh_dT, p.ks_dT);
     if (p.sh_Y == TS_64 && (g.Cout + 63) / 64 * ((npx + 63) / 64) <= 128) p.sh_Y = TS_32x64;
     const size_t part_T = (size_t)(p.ks_T > p.ks_dT ? p.ks_T : p.ks_dT) * g.r * npx;
     p.n_part_T = p.ks_T > 1 || p.ks_dT > 1 ? part_T : 0;
