@@ -723,8 +723,14 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
     const int npx = g.N * vdT.HC * V, phases = g.s * g.s;
     TileArgs a = {}, b = {};
     if (dX) {
-        // the two phases of a row in one workgroup, where half a piece lies in a row of the grid and both phases are all of it
-        const bool rows = kk > 1 && g.s == 2 && g.H == 2 * g.Ho && g.W == 2 * g.Wo && g.Wo % (V / 2) == 0;
+        // The two phases of a row in one workgroup.  Where half a piece lies in a row of the grid and both phases are all of it, every piece
+        // leaves whole; elsewhere those do that hold no end of a row, as long as a row holds half a piece.  Half as many workgroups, each
+        // twice as long: with enough of them.  Both directions, us, phase by phase / so: bf16 161 x 128 x 18 x 18, 444 tiles a phase 127 / 102, 45 x 64 x
+        // 26 x 26, 124 tiles 62 / 48, 56 x 58 x 27 x 10, 63 tiles 66 / 61, 24 x 256 x 7 x 7, 24 tiles 44 / 49; rows of three cells, 225 x 384 x 5 x 5,
+        // 127 / 132; float 75 x 256 x 30 x 6, 228 tiles 93 / 82, 192 x 64 x 19 x 19 155 / 152, 24 x 192 x 15 x 15, 72 tiles 72 / 78.
+        const bool whole = g.H == 2 * g.Ho && g.W == 2 * g.Wo && g.Wo % (V / 2) == 0;
+        const bool many = g.Wo >= V / 2 && (i64)((g.C + 63) / 64) * ((npx + 63) / 64) >= (V == 8 ? 50 : 100);
+        const bool rows = kk > 1 && g.s == 2 && (whole || many);
         for (int f = 0; f < phases; ++f) {
             int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
             const int ni = phase_taps(g, f / g.s, ti, oi), nj = phase_taps(g, f % g.s, tj, oj), nt = ni * nj;

@@ -198,7 +198,8 @@ __device__ __forceinline__ void put_planes(const TileProb &p, int ks, int zb, in
 
 // Two tiles that are the even and the odd pixels of the same rows (a dX with stride 2, whose pixels x = 2 i and 2 i + 1 are reached by
 // different taps): the first one's sums stay in registers while the second is multiplied, and whole pieces of neighbouring pixels
-// leave.  Pixel by pixel, as elements 2 apart, the store and what is added and masks took 15 of the 24 us of a 64 x 64 tile.
+// leave.  Pixel by pixel, as elements 2 apart, the store and what is added and masks took 15 of the 24 us of a 64 x 64 tile.  Pieces that hold
+// the end of a row leave so all the same, both phases at once.
 template <typename CT, class CFG>
 struct PairOut {
     static constexpr bool TAKEN = CFG::BM == 64 && CFG::BN == 64; // (the shape of these products' tiles)
@@ -228,9 +229,42 @@ struct PairOut {
     {
         const TileOut &o = p.o;
         const int n = n0 + tid % CPR * W2, cell = o.HC * V, img = n / cell, pos = n - img * cell, y = pos / o.gW, x = pos - y * o.gW;
-        if (n >= p.N || img >= o.N || pos >= o.HW) return;
+        if (n >= p.N || img >= o.N || pos >= o.HW || 2 * y + o.ph >= o.H) return;
         elem *c = (elem *)o.C;
         const elem *add = (const elem *)o.add, *mask = (const elem *)o.mask;
+        if (x + W2 > o.gW || 2 * x + V > o.W) { // pixels of two rows, or past the last one of an odd width
+            int off[V]; // from the first pixel of the channel; -1: none
+#pragma unroll
+            for (int e = 0; e < V; ++e) {
+                const int cy = (pos + e / 2) / o.gW, yy = 2 * cy + o.ph, xx = 2 * (pos + e / 2 - cy * o.gW) + (e & 1);
+                off[e] = pos + e / 2 < o.HW && yy < o.H && xx < o.W ? yy * o.W + xx : -1;
+            }
+#pragma unroll 1
+            for (int j = 0; j < P; ++j) {
+                const int row = (tid + TILE_THREADS * j) / CPR;
+                if (m0 + row >= p.M) break;
+                const i64 ch = ((i64)img * o.CH + m0 + row) * ((i64)o.H * o.W);
+                elem fa[V], fm[V];
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    if (add) fa[e] = add[ch + max(off[e], 0)];
+                    if (mask) fm[e] = mask[ch + max(off[e], 0)];
+                }
+                float first[W2];
+#pragma unroll
+                for (int q = 0; q < P; ++q)
+#pragma unroll
+                    for (int e = 0; e < W2; ++e) first[e] = q == j ? c0[q][e] : q == 0 ? 0.f : first[e];
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    float v = e & 1 ? at(smem, row, tid % CPR * W2 + e / 2) : first[e / 2];
+                    if (add) v += tile_float<CT>(fa[e]);
+                    if (mask) v = tile_float<CT>(fm[e]) > 0.f ? v : 0.f;
+                    if (off[e] >= 0) c[ch + off[e]] = tile_elem<CT>(v);
+                }
+            }
+            return;
+        }
         constexpr int per = 4; // pieces whose operands are in flight together
         static_assert(P % per == 0 && TILE_THREADS % CPR == 0, "a thread's pieces are whole rounds, in the same pixels of every row");
 #pragma unroll

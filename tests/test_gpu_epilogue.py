@@ -214,3 +214,10 @@ def test_epilogue_on_ragged_planes(shape, dtype):
     tol = 1e-6 if dtype == "f32" else 6e-3
     for a, b in ((Tg, T), (Y, want), (got[0], dX)):
         assert float((a.cpu().double() - b).norm() / b.norm()) <= tol
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(80, 130, 9, 9, 129, 3, 2), (80, 130, 10, 7, 129, 3, 2), (80, 130, 9, 12, 129, 3, 2), (100, 130, 7, 20, 129, 3, 2)])
+def test_epilogue_on_rows_of_two_phases(shape, dtype):
+    """Enough tiles for both phases of a row in a workgroup: odd heights and widths, rows that are no whole pieces."""
+    test_epilogue_on_ragged_planes(shape, dtype)
