@@ -268,7 +268,7 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.t_U = tU, p.t_V = tV;
     p.ks_tU = split(tU, (i64)g.r * g.C * kk);
     p.ks_tV = split(tV, (i64)g.Cout * (g.r + 1));
-    p.n_pack = kk > 1 ? (size_t)g.r * g.C * kk : 0;
+    p.n_pack = kk > 1 || g.s > 1 ? (size_t)g.r * g.C * kk : 0;
     p.n_part_t = (size_t)p.ks_tU * g.r * g.C * kk + (size_t)p.ks_tV * ((size_t)g.Cout * g.r + g.Cout) + 320;
 }
 
@@ -729,8 +729,11 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
         // 26 x 26, 124 tiles 62 / 48, 56 x 58 x 27 x 10, 63 tiles 66 / 61, 24 x 256 x 7 x 7, 24 tiles 44 / 49; rows of three cells, 225 x 384 x 5 x 5,
         // 127 / 132; float 75 x 256 x 30 x 6, 228 tiles 93 / 82, 192 x 64 x 19 x 19 155 / 152, 24 x 192 x 15 x 15, 72 tiles 72 / 78.
         const bool whole = g.H == 2 * g.Ho && g.W == 2 * g.Wo && g.Wo % (V / 2) == 0;
-        const bool many = g.Wo >= V / 2 && (i64)((g.C + 63) / 64) * ((npx + 63) / 64) >= (V == 8 ? 50 : 100);
-        const bool rows = kk > 1 && g.s == 2 && (whole || many);
+        // Filters of one tap (three phases are zero, and what is added): bf16 192 x 64 x 15 x 25 78 / 55, 53 x 304 x 28 x 28 179 / 148, float 23 x 199 x 28
+        // x 28 90 / 68, 1 x 196 x 4 x 4, 4 tiles 38.7 / 40.3.
+        const i64 each = (i64)((g.C + 63) / 64) * ((npx + 63) / 64);
+        const bool many = g.Wo >= V / 2 && each >= (V == 8 ? 50 : 100);
+        const bool rows = g.s == 2 && ((whole && (kk > 1 || V == 8 || each >= 20)) || many), packed = kk > 1 || rows;
         for (int f = 0; f < phases; ++f) {
             int ti[TILE_MAX_TAPS], oi[TILE_MAX_TAPS], tj[TILE_MAX_TAPS], oj[TILE_MAX_TAPS];
             const int ni = phase_taps(g, f / g.s, ti, oi), nj = phase_taps(g, f % g.s, tj, oj), nt = ni * nj;
@@ -743,13 +746,13 @@ static int conv_bwd_tiles(const ConvGeom &g, const ConvPlan &p, const T *X, cons
                 pk.pb.dy[t] = (signed char)(ti[t / nj] * g.k + tj[t % nj]);
             }
             v.ntap = nt > 0 ? nt : 1;
-            if (kk > 1 && nt > 0) {
+            if (packed && nt > 0) {
                 pk.pb.ntap = nt;
                 pk.kper = kk;
                 tile_add(a, p.sh_dT, dt, pk, 1);
                 W = pack[f];
             }
-            TileProb q = kk > 1 ? tile_prob(TILE_CONV, g.C, npx, g.r * nt, W, g.r * nt, nullptr, 0, dX, 0)
+            TileProb q = packed ? tile_prob(TILE_CONV, g.C, npx, g.r * nt, W, g.r * nt, nullptr, 0, dX, 0)
                                 : tile_prob(TILE_CONVT, g.C, npx, nt > 0 ? g.r : 0, Uk, g.C, nullptr, 0, dX, 0);
             q.pb = v;
             out_planes(q.o, vdT, g.C);

@@ -217,7 +217,8 @@ def test_epilogue_on_ragged_planes(shape, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("shape", [(80, 130, 9, 9, 129, 3, 2), (80, 130, 10, 7, 129, 3, 2), (80, 130, 9, 12, 129, 3, 2), (100, 130, 7, 20, 129, 3, 2)])
+@pytest.mark.parametrize("shape", [(80, 130, 9, 9, 129, 3, 2), (80, 130, 10, 7, 129, 3, 2), (80, 130, 9, 12, 129, 3, 2), (100, 130, 7, 20, 129, 3, 2),
+                                   (3, 130, 8, 8, 129, 1, 2), (80, 130, 9, 9, 129, 1, 2), (80, 130, 12, 7, 129, 1, 2)])
 def test_epilogue_on_rows_of_two_phases(shape, dtype):
     """Enough tiles for both phases of a row in a workgroup: odd heights and widths, rows that are no whole pieces."""
     test_epilogue_on_ragged_planes(shape, dtype)
