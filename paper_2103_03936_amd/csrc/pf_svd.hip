@@ -35,7 +35,6 @@
 
 namespace pf {
 
-constexpr int SVD_B = 8; // columns per block
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 
 // A pair counts as orthogonal when |a_p . a_q| <= tol |a_p| |a_q|.  The inner product of two columns of `rows` doubles carries
@@ -361,11 +360,12 @@ __device__ __forceinline__ void svd_normalise(double *L, double *BV, int j, int 
 }
 
 // ------------------------------------------------------------------ grid barrier
-// Every workgroup of a cooperative launch is resident, so all of them arrive.  The wait is bounded all the same;
-// false: some workgroup gave up, and everyone leaves.  patient: the others are sweeping, and polls 10 us apart
-// (of 124 waiting workgroups, at two a microsecond beside 132 sweeping ones, the barriers of these took a quarter longer).
+// Every workgroup of a cooperative launch is resident, so all of them arrive.  The wait is bounded all the same (SvdPatience);
+// false: some workgroup gave up, and everyone leaves.  sweeping (nullable): the others are sweeping, this counter is that of their barrier,
+// and polls are 10 us apart (of 124 waiting workgroups, at two a microsecond beside 132 sweeping ones, the barriers of these took a quarter longer).
 // shared: what others read was stored for them (agent scope), and has only to be complete.
-__device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *failed, unsigned &generation, unsigned nwg, bool patient = false, bool shared = false)
+__device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *failed, unsigned &generation, unsigned nwg, const unsigned *sweeping = nullptr,
+                                                 bool shared = false)
 {
     __shared__ int ok;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -376,20 +376,22 @@ __device__ __forceinline__ bool svd_grid_barrier(unsigned *arrived, unsigned *fa
         if (!shared) __threadfence(); // what this workgroup wrote is visible before it arrives
         generation += nwg;
         __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        int good = 0;
-        for (int spin = 0; spin < 4000000; ++spin) {
-            if ((int)(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - generation) >= 0) {
-                good = 1;
-                break;
-            }
-            if ((spin & 255) == 255 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (patient) {
+        SvdPatience patience;
+        bool good, others = true;
+        do {
+            good = (int)(__hip_atomic_load(arrived, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - generation) >= 0;
+            if (good) break;
+            if (sweeping) {
 #pragma unroll
                 for (int i = 0; i < 3; ++i) __builtin_amdgcn_s_sleep(127);
             } else {
                 __builtin_amdgcn_s_sleep(1);
             }
-        }
+        } while (patience.goes_on([&] {
+                     others = __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+                     return sweeping ? __hip_atomic_load(sweeping, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                 }) &&
+                 others);
         if (!good) __hip_atomic_store(failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __threadfence(); // and what the others wrote before they arrived is read afresh
         ok = good;
@@ -574,7 +576,7 @@ __device__ __forceinline__ bool svd_sweeps(double *M, int ld, int nc, int nr, in
                     __hip_atomic_fetch_add(&rot[sweep], (unsigned)did, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads(); // (the LDS tables are used again)
             }
-            if (!svd_grid_barrier(arrived, &ctrl->failed, generation, nwg, false, true)) return false;
+            if (!svd_grid_barrier(arrived, &ctrl->failed, generation, nwg, nullptr, true)) return false;
         }
         if (__hip_atomic_load(&rot[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
             if (few.low > 0.0 && __hip_atomic_load(&ctrl->held[sweep], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
@@ -718,10 +720,8 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
         __shared__ double part[4][32][33];
         double *red = &part[0][0][0];
         constexpr int W = SVD_NT / 64;
-        const bool sweeps = wg < a.sweepers;
-        const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2, crew = pairs < a.sweepers ? pairs : a.sweepers; // (B's: no more than have a pair)
         unsigned everyone = 0;
-        const auto meet = [&](bool swept = false) { return svd_grid_barrier(&ctrl->everyone, &ctrl->failed, everyone, nwg, swept && !sweeps); };
+        const auto meet = [&](const unsigned *sweeping = nullptr) { return svd_grid_barrier(&ctrl->everyone, &ctrl->failed, everyone, nwg, sweeping); };
         const auto gram = [&](const double *M, int ld) {
             for (int t = wg; t < tiles * tiles; t += nwg) {
                 if (t % tiles > t / tiles) continue;
@@ -743,7 +743,9 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
             // (half of all pairs or more: another check would only say that there are some left)
             const bool many = stage == 1 && coarse && found > (unsigned)nc * (nc - 1) / 4u;
             if (many) later = found, stage = 2;
-            if (stage != 1 || coarse) {
+            const int crew = svd_crew(stage, nc, a.sweepers);
+            const bool swept = stage != 1 || coarse;
+            if (swept) {
                 few = SvdShort{0.0, 0.0};
                 if (!first) {
                     double longest = 0.0;
@@ -757,7 +759,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
                     few = svd_short(longest);
                 }
                 unsigned generation = 0;
-                if (sweeps && first && !a.swept) // (a call of its own: what it has no use for goes)
+                if (wg < crew && first && !a.swept) // (a call of its own: what it has no use for goes)
                     ok = svd_factorize(a.G, a.L, ctrl, nc, a.ldn, a.rel, a.sweepers, generation, red) &&
                          svd_sweeps(a.L, a.ldn, nc, nc, nc, a.tol_v, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl,
                                     sh, &ran, a.sweepers);
@@ -778,7 +780,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
                     for (int i = threadIdx.x; i < a.ldb; i += SVD_NT)
                         a.BV[(i64)j * a.ldb + i] = i < a.lda ? a.At[(i64)j * a.lda + i] : a.L[(i64)j * a.ldn + i - a.lda];
             }
-            ok = ok && meet(true);
+            ok = ok && meet(swept && wg >= crew ? &ctrl->arrived[stage] : nullptr);
             if (first) {
                 for (int j = wg; ok && j < nc; j += nwg) svd_normalise(a.L, a.BV, j, nc, a.ldn, a.ldb, a.lda, red);
                 ok = ok && meet();

@@ -28,6 +28,34 @@ struct SvdCtrl {
     unsigned everyone;      // a barrier of all workgroups
 };
 
+// How long a workgroup polls for others before it gives up: SVD_POLLS times, counted afresh whenever those it waits for have got on.  (Two
+// seconds at two polls a microsecond, far more than any round or product takes.  The sweeps of one stage may take longer: ten and more of
+// seven rounds, 30 ms each for four million rows of 64 columns.)
+constexpr int SVD_POLLS = 4000000;
+struct SvdPatience {
+    int polls = 0;
+    unsigned seen = 0;
+    // after a poll in vain: whether to go on; progress(): a counter that moves while the others do, asked for every 256 polls
+    template <class PROGRESS>
+    __host__ __device__ __forceinline__ bool goes_on(PROGRESS progress)
+    {
+        if (++polls % 256 == 0) {
+            const unsigned now = progress();
+            if (now != seen) seen = now, polls = 0;
+        }
+        return polls < SVD_POLLS;
+    }
+};
+
+// Workgroups that sweep in a stage: the preconditioner's factorization and sweeps are by all that there are for it, those of B by one for each
+// pair of blocks.  The others wait for them.
+constexpr int SVD_B = 8; // columns of a block
+__host__ __device__ __forceinline__ int svd_crew(int stage, int nc, int sweepers)
+{
+    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2;
+    return stage > 0 && pairs < sweepers ? pairs : sweepers;
+}
+
 // What a call reports: sweeps, rotations of the last one, and whether its outputs are worth nothing because a barrier's wait
 // ran out (they are NaN then, for callers that do not ask for the report).
 struct SvdOutcome {

@@ -18,6 +18,25 @@ void emu_rotation(double alpha, double beta, double gamma, double *cs)
 }
 int emu_before(double a, int i, double b, int j) { return svd_before(a, i, b, j); }
 int emu_takes_eigenvectors(int n, int cus) { return svd_takes_eigenvectors(n, cus); }
+// Polls of a workgroup that waits while others take `rounds` rounds of `each` polls: all of them, or those after which it gave up
+long long emu_polls(int rounds, int each)
+{
+    SvdPatience p;
+    long long n = 0;
+    for (; n < (long long)rounds * each; ++n)
+        if (!p.goes_on([&] { return (unsigned)(n / each); })) break;
+    return n;
+}
+// ... of one that waits while others take `rounds` rounds and then none
+long long emu_polls_then_stuck(int rounds, int each, long long most)
+{
+    SvdPatience p;
+    long long n = 0;
+    for (; n < most; ++n)
+        if (!p.goes_on([&] { return (unsigned)(n / each < rounds ? n / each : rounds); })) break;
+    return n;
+}
+int emu_crew(int stage, int nc, int sweepers) { return svd_crew(stage, nc, sweepers); }
 void emu_outcome(unsigned failed, unsigned broken, unsigned sweeps, unsigned last, int nc, int *out)
 {
     SvdCtrl c = {};

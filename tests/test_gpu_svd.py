@@ -348,3 +348,16 @@ def test_more_columns_than_the_eigenvectors_take(m, n):
     assert float((U.double().cpu() @ V.double().cpu().T - w).norm()) <= 2.0 ** -22 * float(w.norm())
     ref = torch.linalg.eigvalsh(w.T @ w).clamp_min(0).sqrt().flip(0)  # (to 2^-53 of the largest eigenvalue, 2^-26 of its root)
     assert float((sigma.double().cpu() - ref).abs().max()) <= 2.0 ** -23 * float(ref[0])
+
+
+@pytest.mark.parametrize("m,n", [(20000, 16), (20000, 40), (9000, 100)])
+def test_tall_matrices_of_lower_rank(m, n):
+    """Workgroups without a pair of columns wait while few sweep for long: preconditioner and B.  Bounds as for lower ranks."""
+    import paper_2103_03936_amd as pf
+    W = _lower_rank("product", m, n, 99)
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+    assert int(info[1]) == 0 and int(info[0]) > 2
+    w = torch.from_numpy(W).double()
+    assert float((U.double().cpu() @ V.double().cpu().T - w).norm()) <= 2.0 ** -22 * float(w.norm())
+    ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]

@@ -23,6 +23,8 @@ def emu(tmp_path_factory):
     lib.emu_orthogonal.argtypes = [d, d, d, d]
     lib.emu_orthogonal_short.argtypes = [d, d, d, d, d, ctypes.c_int]
     lib.emu_rotation.argtypes = [d, d, d, ctypes.c_void_p]
+    lib.emu_polls.restype = lib.emu_polls_then_stuck.restype = ctypes.c_longlong
+    lib.emu_polls_then_stuck.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_longlong]
     lib.emu_before.argtypes = [d, ctypes.c_int, d, ctypes.c_int]
     return lib
 
@@ -106,3 +108,26 @@ def test_workgroups_that_wait_for_one_another_are_all_resident(emu):
         assert emu.emu_takes_eigenvectors(n, workgroups) and emu.emu_takes_eigenvectors(n, 304)
         assert workgroups == 0 or not emu.emu_takes_eigenvectors(n, workgroups - 1)
     assert not emu.emu_takes_eigenvectors(16, 256) and not emu.emu_takes_eigenvectors(2049, 304)
+
+
+@pytest.mark.parametrize("rounds,each", [(280, 60000), (2, 3999999), (40, 1000000), (280, 40)])
+def test_who_waits_for_sweeps_outlasts_them(emu, rounds, each):
+    """A stage of sweeps is many rounds (ten sweeps of 64 columns: 70 and more), each of them well within the limit of a wait but not all
+    together: 70 rounds of 30 ms at two polls a microsecond are 4.2 million polls."""
+    assert emu.emu_polls(rounds, each) == rounds * each
+
+
+@pytest.mark.parametrize("rounds", [0, 1, 3])
+def test_a_wait_ends_without_progress(emu, rounds):
+    """Rounds of a thousand polls, then nothing: given up within the limit, counted from the last round seen."""
+    limit = 4000000
+    got = emu.emu_polls_then_stuck(rounds, 1000, 2 * limit)
+    assert abs(got - limit - rounds * 1000) <= 1256
+
+
+def test_workgroups_that_have_no_pair_wait(emu):
+    """Of eight workgroups the preconditioner has all; B of 64 columns has four pairs of blocks, of 112 seven, of 113 eight."""
+    for nc, crew in ((1, 1), (16, 1), (17, 2), (64, 4), (112, 7), (113, 8), (128, 8), (129, 9)):
+        sweepers = max(8, crew)
+        assert emu.emu_crew(0, nc, sweepers) == sweepers
+        assert emu.emu_crew(1, nc, sweepers) == emu.emu_crew(2, nc, sweepers) == crew
