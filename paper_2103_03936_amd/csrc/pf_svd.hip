@@ -151,7 +151,7 @@ __device__ __forceinline__ void svd_gram_tile(const double *M, double *C, int nr
         fetch(p1, r + STEP);
         multiply(p0, r);
         fetch(p0, r + 2 * STEP);
-        if (r + STEP < nr) multiply(p1, r + STEP);
+        multiply(p1, r + STEP); // (past the last row: zeros.  A condition here cost a wait: 65536 x 16 1605 us a call, 1568 without)
     }
     __shared__ int met[2][32];
     if (tid < 64) met[tid >> 5][tid & 31] = 0;
@@ -334,7 +334,8 @@ __global__ __launch_bounds__(256) void svd_product_kernel(const double *left, co
                                   blockIdx.x, blockIdx.y, part);
 }
 
-// L[:, j] /= |L[:, j]|, also into the V part of BV (rows v0 ..)
+// L[:, j] /= |L[:, j]|, also into the V part of BV (rows v0 ..), by NT threads
+template <int NT>
 __device__ __forceinline__ void svd_normalise(double *L, double *BV, int j, int nc, int ldl, int ldb, int v0, double *red)
 {
     const int tid = threadIdx.x;
@@ -348,7 +349,7 @@ __device__ __forceinline__ void svd_normalise(double *L, double *BV, int j, int 
         __syncthreads();
     }
     const double n = sqrt(red[0]), inv = n > 0.0 ? 1.0 / n : 0.0;
-    for (int i = tid; i < nc; i += SVD_NT) {
+    for (int i = tid; i < nc; i += NT) {
         a[i] *= inv;
         b[v0 + i] = a[i];
     }
@@ -357,6 +358,11 @@ __device__ __forceinline__ void svd_normalise(double *L, double *BV, int j, int 
         for (int i = v0 + nc; i < ldb; ++i) b[i] = 0.0;
     }
     __syncthreads();
+}
+__global__ __launch_bounds__(256) void svd_normalise_kernel(double *L, double *BV, int nc, int ldl, int ldb, int v0)
+{
+    __shared__ double red[256];
+    svd_normalise<256>(L, BV, blockIdx.x, nc, ldl, ldb, v0, red);
 }
 
 // ------------------------------------------------------------------ grid barrier
@@ -684,7 +690,8 @@ __device__ __forceinline__ bool svd_factorize(double *G, double *L, SvdCtrl *ctr
 }
 
 // The preconditioner alone, for more columns than the eigenvectors take: in the kernel below its loops have fewer registers (2200 x 2100: 139 ms
-// a call, 115 so; 1024 x 256 with values down to 1e-6 of the largest, whose eigenvectors do not do, 5.62 in it and 5.46 in a launch of its own).
+// a call, 115 so; 1024 x 256 with values down to 1e-6 of the largest, whose eigenvectors do not do, 5.53 in it and 5.43 in launches of their own).
+// And for few columns of many rows, whose products then have launches over the whole chip instead of eight workgroups.
 __global__ __launch_bounds__(SVD_NT) void svd_jacobi_kernel(double *G, double *L, SvdCtrl *ctrl, int nc, int ld, double rel, double tol)
 {
     __shared__ SvdShared sh;
@@ -703,7 +710,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_jacobi_kernel(double *G, double *L
 struct SvdRest {
     double *At, *G, *L, *BV;
     SvdCtrl *ctrl;
-    int nr, nc, lda, ldn, ldb, sweepers, jacobi, swept; // jacobi: whatever ctrl->mixed says; swept: L is there
+    int nr, nc, lda, ldn, ldb, sweepers, jacobi; // jacobi: there is no B yet, whatever ctrl->mixed says
     double tol, tol_v, rel;
 };
 __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
@@ -734,7 +741,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
 #pragma unroll 1
         for (int stage = jacobi ? 0 : 1; ok && stage < 3; ++stage) {
             const bool first = stage == 0;
-            if (first && !a.swept) {
+            if (first) {
                 gram(a.At, a.lda);
                 ok = meet();
             }
@@ -759,11 +766,11 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
                     few = svd_short(longest);
                 }
                 unsigned generation = 0;
-                if (wg < crew && first && !a.swept) // (a call of its own: what it has no use for goes)
+                if (wg < crew && first) // (a call of its own: what it has no use for goes)
                     ok = svd_factorize(a.G, a.L, ctrl, nc, a.ldn, a.rel, a.sweepers, generation, red) &&
                          svd_sweeps(a.L, a.ldn, nc, nc, nc, a.tol_v, SvdShort{0.0, 0.0}, SVD_MAX_SWEEPS, &ctrl->arrived[0], generation, ctrl->rot[0], true, ctrl,
                                     sh, &ran, a.sweepers);
-                else if (!first && wg < crew)
+                else if (wg < crew)
                     ok = svd_sweeps(a.BV, a.ldb, nc, nr, a.ldb, a.tol, few, stage == 1 ? 1 : SVD_MAX_SWEEPS - 1 + many, &ctrl->arrived[stage], generation,
                                     ctrl->rot[stage], false, ctrl, sh, &ran, crew, stage == 1 || many ? a.G : nullptr, a.ldn);
                 before = many ? 0 : 1;
@@ -782,7 +789,7 @@ __global__ __launch_bounds__(SVD_NT) void svd_rest_kernel(SvdRest a)
             }
             ok = ok && meet(swept && wg >= crew ? &ctrl->arrived[stage] : nullptr);
             if (first) {
-                for (int j = wg; ok && j < nc; j += nwg) svd_normalise(a.L, a.BV, j, nc, a.ldn, a.ldb, a.lda, red);
+                for (int j = wg; ok && j < nc; j += nwg) svd_normalise<SVD_NT>(a.L, a.BV, j, nc, a.ldn, a.ldb, a.lda, red);
                 ok = ok && meet();
                 const int down = (a.lda + 31) / 32;
                 for (int t = wg; ok && t < down * tiles; t += nwg) {
@@ -935,24 +942,30 @@ int pf_svd_split(const pf_svd_desc *d, const void *W, void *U, void *V_out, void
         PF_LAUNCH(st, "svd_mixed", svd_mixed_kernel, dim3(nc), dim3(256), s, (const double *)G, &ctrl->mixed, nc, p.ldn);
         PF_LAUNCH(st, "svd_newton", svd_product_kernel<SVD_NEWTON>, square, dim3(256), s, (const double *)L, (const double *)G, V, nc, nc, p.ldn,
                   p.ldn, p.ldb, (const SvdCtrl *)ctrl, (const int *)place);
+    }
+    // sweeps: one workgroup per pair of blocks (at least eight for the factorization); products: one per tile; all of them resident
+    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2, sweepers = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
+    const i64 tiles = (i64)((p.lda + 31) / 32) * ((nc + 31) / 32);
+    const int most = cus > 256 ? 256 : cus, wide = tiles < most ? (int)tiles : most;
+    const double rel = 16.0 * 2.220446049250313e-16 * (nc + 16);
+    // Few columns, us a call, Jacobi and products in the kernel below / in launches of their own: 1024 x 16 185 / 193, 2048 x 16 204 / 205, 4608 x 16 283 /
+    // 272, 16384 x 16 597 / 517, 65536 x 16 1920 / 1568, 1048576 x 16 29.2 / 23.2 ms.
+    const bool jacobi = !eigen && (nc > SVD_EIGEN_MAX || nr > 2048);
+    if (jacobi) {
+        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, none, (int *)nullptr);
+        if (st == PF_OK)
+            st = launch_cooperative(s, "svd_jacobi", svd_jacobi_kernel, sweepers, SVD_NT, G, L, ctrl, nc, p.ldn, rel, svd_tolerance_v(nc));
+        PF_LAUNCH(st, "svd_normalise", svd_normalise_kernel, dim3(nc), dim3(256), s, L, BV, nc, p.ldn, p.ldb, p.lda);
+    }
+    if (eigen || jacobi) {
         PF_LAUNCH(st, "svd_apply", svd_product_kernel<SVD_TIMES>, dim3((p.lda + 31) / 32, (nc + 31) / 32), dim3(256), s, (const double *)At,
                   (const double *)V, BV, p.lda, nc, p.lda, p.ldb, p.ldb, (const SvdCtrl *)ctrl, (const int *)nullptr);
         PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)BV, G, nr, nc, p.ldb, p.ldn, (const unsigned *)&ctrl->mixed,
                   (int *)nullptr);
         PF_LAUNCH(st, "svd_check", svd_check_kernel, dim3(nc), dim3(256), s, (const double *)G, ctrl, nc, p.ldn, svd_tolerance(nr));
     }
-    // sweeps: one workgroup per pair of blocks (at least eight for the factorization); products: one per tile; all of them resident
-    const int pairs = ((nc + SVD_B - 1) / SVD_B + 1) / 2, sweepers = pairs < 8 ? 8 : pairs > 256 ? 256 : pairs;
-    const i64 tiles = (i64)((p.lda + 31) / 32) * ((nc + 31) / 32);
-    const int most = cus > 256 ? 256 : cus, wide = tiles < most ? (int)tiles : most;
-    const bool alone = !eigen && nc > SVD_EIGEN_MAX;
-    const double rel = 16.0 * 2.220446049250313e-16 * (nc + 16);
-    if (alone) {
-        PF_LAUNCH(st, "svd_gram", svd_gram_kernel, gram, dim3(256), s, (const double *)At, G, nr, nc, p.lda, p.ldn, none, (int *)nullptr);
-        if (st == PF_OK) st = launch_cooperative(s, "svd_jacobi", svd_jacobi_kernel, sweepers, SVD_NT, G, L, ctrl, nc, p.ldn, rel, svd_tolerance_v(nc));
-    }
-    const SvdRest rest = {At, G, L, BV, ctrl, nr, nc, p.lda, p.ldn, p.ldb, sweepers, !eigen, alone, svd_tolerance(nr), svd_tolerance_v(nc), rel};
-    if (st == PF_OK) st = launch_cooperative(s, "svd_rest", svd_rest_kernel, eigen && wide > sweepers ? wide : sweepers, SVD_NT, rest);
+    const SvdRest rest = {At, G, L, BV, ctrl, nr, nc, p.lda, p.ldn, p.ldb, sweepers, !eigen && !jacobi, svd_tolerance(nr), svd_tolerance_v(nc), rel};
+    if (st == PF_OK) st = launch_cooperative(s, "svd_rest", svd_rest_kernel, (eigen || jacobi) && wide > sweepers ? wide : sweepers, SVD_NT, rest);
     PF_LAUNCH(st, "svd_sigma", svd_sigma_kernel, dim3(nc), dim3(256), s, (const double *)BV, sig, ctrl, nr, p.ldb);
     PF_LAUNCH(st, "svd_rank", svd_rank_kernel, dim3((nc + 3) / 4), dim3(256), s, (const double *)sig, rank, nc);
     PF_LAUNCH(st, "svd_emit", svd_emit_kernel, dim3(nc), dim3(256), s, (const double *)BV, (const double *)sig,

@@ -361,3 +361,17 @@ def test_tall_matrices_of_lower_rank(m, n):
     assert float((U.double().cpu() @ V.double().cpu().T - w).norm()) <= 2.0 ** -22 * float(w.norm())
     ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
     assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]
+
+
+@pytest.mark.parametrize("n", [1, 5, 16])
+@pytest.mark.parametrize("m", [2048, 2049, 30001])
+def test_few_columns_of_many_rows(m, n):
+    """Both sides of the rows from which Jacobi's preconditioner and the products have launches of their own.  Bounds as above."""
+    import paper_2103_03936_amd as pf
+    W = _matrix(m, n, 101)
+    U, V, sigma, info = pf.pf_svd_split(to_gpu(W), n, return_info=True)
+    assert int(info[1]) == 0 and int(info[0]) <= 2
+    w = torch.from_numpy(W).double()
+    assert float((U.double().cpu() @ V.double().cpu().T - w).norm()) <= 2.0 ** -22 * float(w.norm())
+    ref = np.linalg.svd(W.astype(np.float64), compute_uv=False)
+    assert np.max(np.abs(sigma.double().cpu().numpy() - ref)) <= 2.0 ** -23 * ref[0]
