@@ -8,7 +8,7 @@
 #include "pf_linear_two.h"
 #include "pf_skinny.h"
 #include "pf_linear_small.h"
-#include "pf_tile_host.h"
+#include "pf_tile_plans.h"
 
 #include <math.h>
 #include "pf_conv_wgrad.h"
@@ -129,14 +129,7 @@ int linear_bwd_entry(const pf_linear_desc *d, const void *X, const void *V, cons
 
 // ---------------------------------------------------------- workspace plan
 // The tiled products' part of a plan, for G layers of this shape that share their input (side by side in every launch).
-struct LinearTiles {
-    bool ok;               // every dimension holds a 16-byte piece
-    TilePlan T, dT, Y;     // tile shapes and splits of the intermediates and the output
-    bool T_sliced, dT_sliced; // their readers take the partial sums (float) and add them up
-    TileGroup grads;       // dX, dU and dV in one launch
-    size_t n_mid, n_part_T, n_part_g, fwd_bytes, bwd_bytes; // elements of T, partial sums (floats)
-};
-static LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
+LinearTiles make_linear_tiles(const pf_linear_desc *d, int G)
 {
     LinearTiles p = {};
     const i64 piece = d->dtype == PF_BF16 ? 8 : 4;

@@ -3,7 +3,7 @@
 // the any-shape path composes the guarded tile GEMM with two pointwise kernels.
 #include "pf_gemm.h"
 #include "pf_skinny.h"
-#include "pf_tile_host.h"
+#include "pf_tile_plans.h"
 
 namespace pf {
 
@@ -266,16 +266,9 @@ __global__ __launch_bounds__(256) void lstm_slices_pointwise_fwd_kernel(const fl
 // pays.  Products too small for the chip split their contraction; slices of T and dT are added by the tiles that read them, others by
 // one more launch.  Forward and backward, us, nine launches with streaming kernels for up to 32 rows before / now: 10 rows, 128 units
 // 39.8 / 22.1, 512 units 42.1 / 28.7 (a pair per gate 31.2), 1500 units 62.0 / 55; 64 rows, 512 units 39.5 / 30.5.
-struct LstmTilePlan {
-    TileGroup z, dxh, grads;
-    MidGroup T, dT;
-    TileGroup last; // dx, dh_prev and all gradients in one launch
-    bool one;       // ... where that is faster than two
-    size_t n_T, n_dT, n_dxh, fwd_bytes, bwd_bytes; // partial sums, floats
-};
 static bool lstm_tiles_ok(const pf_lstm_desc *d) { return d->B > 0 && d->d_in >= 4 && d->h >= 4 && d->r >= 4; }
 
-static LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
+LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
 {
     LstmTilePlan p;
     const i64 B = d->B, h = d->h, r = d->r, G = d->groups, gr = G * r, din = d->d_in, rows = (B + 31) / 32 * 32;
@@ -454,7 +447,7 @@ static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
 
 // Backward with a factor pair per gate and large factors at few rows: 1360 units and 10 rows 37 us here, 45 on the tiled products, at 20
 // rows 41 / 45; 896 units 29 / 27.  (Every extent of the sliced products holds one 16-byte load: see launch_skinny_gemm.)
-static bool lstm_skinny_pays(const pf_lstm_desc *d)
+bool lstm_skinny_pays(const pf_lstm_desc *d)
 {
     const double weights = (double)d->groups * d->r * (d->d_in + d->h) + 8.0 * d->h * d->r;
     return d->B > 0 && d->B <= SK_MAX_ROWS && d->d_in >= 4 && d->h >= 4 && d->r >= 4 && d->groups == 4 && weights >= 5e6;

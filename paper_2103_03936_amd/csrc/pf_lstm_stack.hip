@@ -22,7 +22,7 @@
 #include "pf_gemm.h"
 #include "pf_lstm_persist.h"
 #include "pf_skinny.h"
-#include "pf_tile_host.h"
+#include "pf_tile_plans.h"
 #include "pf_common.h"
 
 namespace pf {
@@ -574,31 +574,25 @@ static int check_stack_desc(const pf_lstm_stack_desc *d, StackGeom *g)
     return PF_OK;
 }
 
-// The products over all rows T B at once, on the tiled kernels (pf_tile.h): Tx = X Vx of the first layer (and, step by step, zx = Tx Ux^T)
-// before the recurrence, dTx = dz Ux and dx = dTx Vx^T after it.  The streaming kernels passed over the factors once for every 32 rows and
-// needed a launch for their slices: 700 rows, 1500 units, one pair for all gates 148 us in twelve launches, 90 in five; 4 x 32 rows, 640
-// units, a pair per gate: 294 -> 257 for the call, zx alone 63 -> 8.
-struct StackTall {
-    TilePlan Tx, zx, dx;
-    MidPlan dTx;
-    size_t n_part; // partial sums, floats
-};
-static StackTall make_tall(const StackGeom &g)
+// (On the tiled kernels.  The streaming kernels passed over the factors once for every 32 rows and needed a launch for their slices: 700 rows, 1500
+// units, one pair for all gates 148 us in twelve launches, 90 in five; 4 x 32 rows, 640 units, a pair per gate: 294 -> 257 for the call, zx
+// alone 63 -> 8.)
+StackTall make_tall(i64 rows, i64 din, i64 h, i64 r, int G)
 {
     StackTall t;
-    const i64 Mt = (i64)g.T * g.B, K = g.G == 1 ? 4 * g.h : g.h;
-    t.Tx = plan_tiles(PF_F32, Mt, g.gr, g.din, 16);
-    t.zx = plan_tiles(PF_F32, Mt, 4 * (i64)g.h, g.r, 1);
-    t.dx = plan_tiles(PF_F32, Mt, g.din, g.gr, 1);
-    t.dTx = plan_mid(PF_F32, Mt, g.gr, K, 16, t.dx.shape, (Mt + 31) / 32 * ((g.din + 31) / 32) * 128 * g.gr, 128 * g.gr);
+    const i64 K = G == 1 ? 4 * h : h, gr = G * r;
+    t.Tx = plan_tiles(PF_F32, rows, gr, din, 16);
+    t.zx = plan_tiles(PF_F32, rows, 4 * h, r, 1);
+    t.dx = plan_tiles(PF_F32, rows, din, gr, 1);
+    t.dTx = plan_mid(PF_F32, rows, gr, K, 16, t.dx.shape, (rows + 31) / 32 * ((din + 31) / 32) * 128 * gr, 128 * gr);
     const int ks = t.Tx.ksplit > t.dTx.t.ksplit ? t.Tx.ksplit : t.dTx.t.ksplit;
-    t.n_part = ks > 1 ? (size_t)(ks * Mt * g.gr) + 64 : 0;
+    t.n_part = ks > 1 ? (size_t)(ks * rows * gr) + 64 : 0;
     return t;
 }
 static const StackTall &plan_tall(const StackGeom &g)
 {
     static thread_local PlanCache<PlanKey<5>, StackTall> cache;
-    return cache.get(PlanKey<5>{{(i64)g.T * g.B, g.din, g.h, g.r, g.G}}, [&] { return make_tall(g); });
+    return cache.get(PlanKey<5>{{(i64)g.T * g.B, g.din, g.h, g.r, g.G}}, [&] { return make_tall((i64)g.T * g.B, g.din, g.h, g.r, g.G); });
 }
 // out [Mt][gr] = q, a product of that shape; slices (nullable): how many partial sums at `part` it stays in
 static int tall_mid(hipStream_t s, const char *name, const TilePlan &t, TileProb q, i64 count, float *out, float *part, int *slices)

@@ -1,6 +1,6 @@
 // The host side of the tiled products (test infrastructure, CPU only).  Built by tests/test_host_tiles.py against the library; nothing
 // in the product loads it.
-#include "pf_tile_host.h"
+#include "pf_tile_plans.h"
 
 using namespace pf;
 
@@ -28,12 +28,27 @@ int emu_plan(int dtype, long long M, long long N, long long K, int max_split, in
 // slices of the intermediate T (backward: dT) of a layer [M][in] -> r -> out that its readers add up, 1: none
 int emu_slices(int dtype, long long M, long long in, long long out, long long r, int backward)
 {
-    const TileNeed need[3] = {{M, in, r, false}, {out, r, M, true, true}, {in, r, M, true, true}};
-    const TileShape reader = backward ? plan_tile_group(dtype, need, 3).shape : plan_tiles(dtype, M, out, r, 1).shape;
-    const long long rows = (M + 31) / 32 * 32, ins = (in + 31) / 32, outs = (out + 31) / 32;
-    const MidPlan p = backward ? plan_mid(dtype, M, r, out, 16, reader, 8 * ins * rows * r, 128 * (M > r ? M : r))
-                               : plan_mid(dtype, M, r, in, 16, reader, 4 * outs * rows * r, 128 * r);
-    return p.sliced ? p.t.ksplit : 1;
+    pf_linear_desc d = {};
+    d.M = M, d.in = in, d.out = out, d.r = r, d.dtype = dtype;
+    const LinearTiles p = make_linear_tiles(&d, 1);
+    return backward ? (p.dT_sliced ? p.dT.ksplit : 1) : p.T_sliced ? p.T.ksplit : 1;
+}
+// the same of an LSTM cell's T and dT, and whether dx and dh_prev go with the gradients (*one) or all of it backward is on the streaming
+// kernels (*skinny)
+int emu_cell_slices(long long B, long long din, long long h, long long r, int groups, int backward, int *one, int *skinny)
+{
+    pf_lstm_desc d = {};
+    d.B = B, d.d_in = din, d.h = h, d.r = r, d.groups = groups;
+    const LstmTilePlan p = make_lstm_tile_plan(&d);
+    *one = p.one, *skinny = lstm_skinny_pays(&d);
+    const MidGroup &m = backward ? p.dT : p.T;
+    return m.sliced ? m.g.ksplit[0] : 1;
+}
+// ... and of dTx over all rows of a stack
+int emu_tall_slices(long long rows, long long din, long long h, long long r, int groups)
+{
+    const StackTall t = make_tall(rows, din, h, r, groups);
+    return t.dTx.sliced ? t.dTx.t.ksplit : 1;
 }
 // the same for the gradients of a layer [M][in] -> r -> out in one launch (dX, dU, dV)
 int emu_gradients(int dtype, long long M, long long in, long long out, long long r, int *split)

@@ -73,3 +73,23 @@ def test_padded_gradients_stay_on_smaller_tiles(emu, M, n_in, n_out):
 def test_slices_that_the_gpu_tests_count_on(emu, dtype, shape, forward, backward):
     M, n_in, n_out, r = (ctypes.c_longlong(v) for v in shape)
     assert (emu.emu_slices(dtype, M, n_in, n_out, r, 0), emu.emu_slices(dtype, M, n_in, n_out, r, 1)) == (forward, backward)
+
+
+@pytest.mark.parametrize("shape,groups,forward,backward,one,streaming", [
+    ((1, 515, 260, 65), 1, 3, 4, 1, 0), ((1, 515, 260, 65), 4, 3, 3, 1, 0), ((20, 700, 516, 129), 1, 4, 1, 1, 0), ((20, 700, 516, 129), 4, 4, 3, 1, 0),
+    ((33, 1030, 900, 225), 1, 3, 1, 1, 0), ((33, 1030, 900, 225), 4, 2, 2, 1, 0), ((3, 1302, 1360, 341), 4, 2, 1, 0, 1),
+    ((64, 70, 1500, 375), 4, 2, 1, 0, 0)])
+def test_cell_slices_that_the_gpu_tests_count_on(emu, shape, groups, forward, backward, one, streaming):
+    """test_gpu_tiles.test_lstm_cell_slices: slices of T and dT, dx and dh_prev beside the gradients or not, streaming kernels backward."""
+    B, d, h, r = (ctypes.c_longlong(v) for v in shape)
+    a, b = ctypes.c_int(), ctypes.c_int()
+    assert emu.emu_cell_slices(B, d, h, r, groups, 0, ctypes.byref(a), ctypes.byref(b)) == forward
+    assert emu.emu_cell_slices(B, d, h, r, groups, 1, ctypes.byref(a), ctypes.byref(b)) == backward
+    assert (a.value, b.value) == (one, streaming)
+
+
+@pytest.mark.parametrize("rows,d,h,r,groups,slices", [(1, 260, 9, 4, 1, 2), (2, 1030, 70, 33, 4, 1), (15, 36, 40, 10, 4, 2), (35, 515, 129, 31, 1, 4)])
+def test_stack_slices_that_the_gpu_tests_count_on(emu, rows, d, h, r, groups, slices):
+    """test_gpu_lstm.test_layer_stack_few_rows"""
+    i64 = ctypes.c_longlong
+    assert emu.emu_tall_slices(i64(rows), i64(d), i64(h), i64(r), groups) == slices
