@@ -283,13 +283,21 @@ LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
     if (split.cost < p.dxh.cost) p.dxh = split;
     p.grads = plan_tile_group(PF_F32, last + 2, 4);
     p.last = plan_tile_group(PF_F32, last, 6);
-    // (not where the long contractions of dx and dh_prev alone fill the time on the gradients' larger tiles: 64 rows, 1500 units, a pair per
-    // gate 86.8 us in two launches, 91.9 in one; 128 rows 131 / 121, 512 units 42.6 / 38.1, 1500 units with one pair at 64 rows 74.7 / 70.4)
-    const bool long_k = p.last.shape == TS_64 && p.last.cost <= 1.01 * (4100 + 1200.0 * ((gr + 31) / 32));
-    p.one = p.last.cost < p.dxh.cost + p.grads.cost && !long_k;
     const TileNeed dT[2] = {{B, gr, G == 4 ? h : 4 * h, true}, {B, gr, G == 4 ? h : 4 * h, true}};
-    p.dT = plan_mid_group(PF_F32, dT, 2, p.one ? p.last.shape : p.dxh.shape, 4 * rows * gr * ((din + 31) / 32 + (h + 31) / 32) * (p.one ? 2 : 1),
-                          128 * (p.one && B > gr ? B : gr));
+    const auto mid = [&](bool one) {
+        return plan_mid_group(PF_F32, dT, 2, one ? p.last.shape : p.dxh.shape, 4 * rows * gr * ((din + 31) / 32 + (h + 31) / 32) * (one ? 2 : 1),
+                              128 * (one && B > gr ? B : gr));
+    };
+    const MidGroup dT1 = mid(true), dT2 = mid(false);
+    // One launch or two, each with the dT that its readers can take.  The tiles of dx and dh_prev are few and contract over all ranks: beside
+    // the gradients' they are the longer for it.  (A launch costs 2000 clocks more than the 3000 that its plan has.)
+    // Backward, us, one / two, factors in the caches: a pair per gate, 64 rows, 1500 units 91.9 / 86.8, 87 rows, 576 -> 1280 units 51.0 / 47.0, 188
+    // rows, 448 units, rank 168 34.5 / 32.3, 200 rows, 448 -> 384 units 22.2 / 25.6; one pair, 7 rows, 768 units 19.7 / 21.6, 23 rows, 640 units
+    // 18.0 / 20.1.  Over 550 cells of 1 to 256 rows 0.2 % from the faster one (geometric mean), six more than a
+    // twentieth slower, three of which the streaming kernels take; out of the caches alike.
+    const double chain = tile_chain_cost(PF_F32, p.last.shape, last, 6, 2), all = p.last.cost > chain ? p.last.cost : chain;
+    p.one = all + dT1.g.cost < p.dxh.cost + p.grads.cost + dT2.g.cost + 2000;
+    p.dT = p.one ? dT1 : dT2;
     p.n_T = (size_t)((p.T.g.ksplit[0] + p.T.g.ksplit[1]) * B * gr) + 64;
     p.n_dT = (size_t)((p.dT.g.ksplit[0] + p.dT.g.ksplit[1]) * B * gr) + 64;
     p.n_dxh = (size_t)(p.dxh.ksplit[0] * B * din + p.dxh.ksplit[1] * B * h) + 64;

@@ -138,6 +138,21 @@ TileGroup plan_tile_group(int dtype, const TileNeed *need, int n)
     return best;
 }
 
+// A chain's compute unit has a workgroup of the others beside it while there are any left; until then, at two to a compute unit, a chunk of
+// it takes twice `work` instead of `one`.
+double tile_chain_cost(int dtype, TileShape shape, const TileNeed *need, int n, int chains)
+{
+    const ChunkCost cc = chunk_cost(dtype == PF_BF16, shape);
+    const i64 bm = SHAPES[shape].bm, bn = SHAPES[shape].bn, bk = dtype == PF_BF16 ? 64 : 32;
+    double longest = 0, rest = 0;
+    for (int i = 0; i < n; ++i) {
+        const double tiles = (double)(((need[i].M + bm - 1) / bm) * ((need[i].N + bn - 1) / bn)), chunks = (double)((need[i].K + bk - 1) / bk);
+        if (i >= chains) rest += tiles * (chunks * cc.work + cc.tile);
+        else if (chunks * cc.one + cc.tile > longest) longest = chunks * cc.one + cc.tile;
+    }
+    return 3000 + longest + (1 - cc.one / (2 * cc.work)) * rest / 256;
+}
+
 // (a workgroup of the readers brings its slices in at 50 bytes a clock; bf16 at 25, for its own intermediate is half of one of them)
 MidGroup plan_mid_group(int dtype, const TileNeed *need, int n, TileShape reader, i64 all, i64 most)
 {

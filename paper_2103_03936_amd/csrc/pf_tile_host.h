@@ -87,6 +87,9 @@ struct TileGroup {
     double cost;
 };
 TileGroup plan_tile_group(int dtype, const TileNeed *need, int n);
+// Clocks of a launch of tiles of that shape whose first `chains` products are few tiles with a long contraction and the others many with a
+// short one, all unsplit
+double tile_chain_cost(int dtype, TileShape shape, const TileNeed *need, int n, int chains);
 
 // The same for intermediates whose readers can take their partial sums instead (TileProb::aslices, bslices): `all` bytes of them go into
 // the readers' workgroups, `most` into one.  sliced: they are to do so.

@@ -93,3 +93,13 @@ def test_stack_slices_that_the_gpu_tests_count_on(emu, rows, d, h, r, groups, sl
     """test_gpu_lstm.test_layer_stack_few_rows"""
     i64 = ctypes.c_longlong
     assert emu.emu_tall_slices(i64(rows), i64(d), i64(h), i64(r), groups) == slices
+
+
+@pytest.mark.parametrize("shape,groups,one", [((7, 768, 768, 192), 1, 1), ((23, 640, 640, 160), 1, 1), ((200, 448, 384, 96), 4, 1),
+                                              ((64, 1500, 1500, 375), 4, 0), ((87, 576, 1280, 320), 4, 0), ((188, 448, 448, 168), 4, 0)])
+def test_cells_whose_gradients_go_with_dx(emu, shape, groups, one):
+    """The faster of one launch and two, by a twentieth and more of the call."""
+    B, d, h, r = (ctypes.c_longlong(v) for v in shape)
+    got, streaming = ctypes.c_int(), ctypes.c_int()
+    emu.emu_cell_slices(B, d, h, r, groups, 1, ctypes.byref(got), ctypes.byref(streaming))
+    assert got.value == one
