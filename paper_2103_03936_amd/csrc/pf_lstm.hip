@@ -296,7 +296,9 @@ LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)
     // 18.0 / 20.1.  Over 550 cells of 1 to 256 rows 0.2 % from the faster one (geometric mean), six more than a
     // twentieth slower, three of which the streaming kernels take; out of the caches alike.
     const double chain = tile_chain_cost(PF_F32, p.last.shape, last, 6, 2), all = p.last.cost > chain ? p.last.cost : chain;
-    p.one = all + dT1.g.cost < p.dxh.cost + p.grads.cost + dT2.g.cost + 2000;
+    const double in_one = all + dT1.g.cost, in_two = p.dxh.cost + p.grads.cost + dT2.g.cost + 2000;
+    p.one = in_one < in_two;
+    p.bwd = p.one ? in_one : in_two;
     p.dT = p.one ? dT1 : dT2;
     p.n_T = (size_t)((p.T.g.ksplit[0] + p.T.g.ksplit[1]) * B * gr) + 64;
     p.n_dT = (size_t)((p.dT.g.ksplit[0] + p.dT.g.ksplit[1]) * B * gr) + 64;
@@ -449,16 +451,25 @@ static int lstm_bwd_tiles(const pf_lstm_desc *d, const float *x, const float *h_
     return launch_tiles_linear(s, p.one ? "lstm_dxh,grads" : "lstm_grads", PF_F32, shape, c);
 }
 
-// ------------------------------------------------------------------ backward, few rows and large factors
+// ------------------------------------------------------------------ backward, few rows
 // Every product streams its factor once from all compute units (pf_skinny.h); slice sums of dx and dh_prev ride along with the gradient
 // updates.
 
-// Backward with a factor pair per gate and large factors at few rows: 1360 units and 10 rows 37 us here, 45 on the tiled products, at 20
-// rows 41 / 45; 896 units 29 / 27.  (Every extent of the sliced products holds one 16-byte load: see launch_skinny_gemm.)
+// Both ways in microseconds, fitted to 300 cells of 1 to 32 rows and 128 to 1500 units (3 and 4 % rms; the means of factors in the caches and out
+// of them).  Backward, us, here / tiled products, in the caches and out of them: a pair per gate, 2 rows, 1024 units 25.3 / 32.7 and 28.9 / 36.3, 20 rows 30.7
+// / 33.0 and 34.0 / 36.4, 4 rows, 1296 units 34.6 / 43.1 and 40.7 / 46.3, 22 rows, 960 units 31.3 / 26.6 and 34.0 / 30.7; one pair, 4 rows, 1024 units, rank
+// 453 28.0 / 34.2 and 32.0 / 36.7, 24 rows, 1216 units 32.7 / 27.9 and 35.6 / 30.0.  300 other cells: 0.4 % behind the
+// faster one (geometric mean), two of them a twentieth or more in the caches, five out of them, 7 % at most.  Smaller layers: 10 rows, 512 units
+// 20.9 / 13.4.
+// (Every extent of the sliced products holds one 16-byte load: see launch_skinny_gemm.)
 bool lstm_skinny_pays(const pf_lstm_desc *d)
 {
-    const double weights = (double)d->groups * d->r * (d->d_in + d->h) + 8.0 * d->h * d->r;
-    return d->B > 0 && d->B <= SK_MAX_ROWS && d->d_in >= 4 && d->h >= 4 && d->r >= 4 && d->groups == 4 && weights >= 5e6;
+    if (!lstm_tiles_ok(d) || d->B > SK_MAX_ROWS) return false;
+    const LstmTilePlan &p = plan_lstm_tiles(d);
+    const double B = (double)d->B, m = 1e-6 * ((double)d->groups * d->r * (d->d_in + d->h) + 8.0 * d->h * d->r); // millions of weights
+    const double here = 19.3 + 2.26 * m + B * (0.18 + 0.031 * m);
+    const double tiles = 7 + p.bwd / 1617 - 0.33 * m + (d->r % 4 ? 0.67 : 0) - (p.one ? 2.8 : 0);
+    return here < 0.98 * tiles;
 }
 
 // The two launches with sliced contractions.  Each builder fills the problem list, places the slice sums

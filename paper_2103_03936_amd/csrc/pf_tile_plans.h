@@ -22,6 +22,7 @@ struct LstmTilePlan {
     MidGroup T, dT;
     TileGroup last; // dx, dh_prev and all gradients in one launch
     bool one;       // ... where that is faster than two
+    double bwd;     // clocks of the backward products
     size_t n_T, n_dT, n_dxh, fwd_bytes, bwd_bytes; // partial sums, floats
 };
 LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d);

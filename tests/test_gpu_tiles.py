@@ -68,6 +68,12 @@ def test_lstm_cell_slices(shape, groups):
     test_gpu_lstm._cell(*shape, groups, seed=27)
 
 
+@pytest.mark.parametrize("shape,groups", [((4, 1024, 1024, 453), 1), ((1, 515, 1400, 402), 1), ((3, 130, 1033, 290), 4), ((17, 1100, 1499, 391), 4)])
+def test_lstm_cell_streamed(shape, groups):
+    """Few rows whose factors backward are streamed, one pair and a pair per gate (tests/test_host_tiles.py: these are)."""
+    test_gpu_lstm._cell(*shape, groups, seed=28)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape", [(33, 9, 10, 8, 2), (20, 24, 1500, 16, 3), (700, 130, 41, 24, 4), (6100, 264, 130, 128, 3),
                                    (6100, 264, 330, 128, 3), (6100, 380, 378, 128, 3)])

@@ -103,3 +103,16 @@ def test_cells_whose_gradients_go_with_dx(emu, shape, groups, one):
     got, streaming = ctypes.c_int(), ctypes.c_int()
     emu.emu_cell_slices(B, d, h, r, groups, 1, ctypes.byref(got), ctypes.byref(streaming))
     assert got.value == one
+
+
+@pytest.mark.parametrize("shape,groups,streaming", [((2, 1024, 1024, 256), 4, 1), ((4, 1296, 1296, 324), 4, 1), ((2, 448, 1152, 288), 4, 1), ((4, 1024, 1024, 453), 1, 1),
+                                                    ((22, 960, 960, 240), 4, 0), ((24, 1216, 1216, 304), 1, 0), ((10, 512, 512, 128), 1, 0),
+                                                    ((1, 515, 1400, 402), 1, 1), ((3, 130, 1033, 290), 4, 1), ((17, 1100, 1499, 391), 4, 1),
+                                                    ((33, 1500, 1500, 375), 4, 0), ((1, 3, 1500, 375), 4, 0)])
+def test_cells_whose_factors_are_streamed(emu, shape, groups, streaming):
+    """Backward, the faster of the streaming kernels and the tiled products by a tenth and more of the call, factors in the caches or not;
+    those of test_gpu_tiles.test_lstm_cell_streamed; neither more rows than the streaming kernels take nor rows shorter than a 16-byte load."""
+    B, d, h, r = (ctypes.c_longlong(v) for v in shape)
+    one, got = ctypes.c_int(), ctypes.c_int()
+    emu.emu_cell_slices(B, d, h, r, groups, 1, ctypes.byref(one), ctypes.byref(got))
+    assert got.value == streaming
