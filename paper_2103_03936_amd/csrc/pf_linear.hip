@@ -303,17 +303,24 @@ static int two_bwd_rows(i64 M, i64 in, i64 out, i64 r, int &split)
     return now < 0.95 * before ? rows : 0;
 }
 
-// Few rows in float: the streaming kernels read a factor at 8 rows at a time and take four or five launches a direction, the tiled products
-// two (their readers add the slices of T and dT) and pad to 32 rows.  Calls of 1 to 24 rows, us, streaming / tiled: forward 2048 -> 512 ->
-// 2048 15.7 / 15.0 at one row, 4000 -> 500 -> 4000 17.2 / 16.8, but 2000 -> 1000 -> 2000 16.8 / 20.0, at 8 rows 18.5 / 20.1, at 16 20.5 /
-// 20.2 (odd ranks cost the tiles unaligned pieces: 3712 -> 467 -> 1869 16.8 / 18.2 at one row); forward and backward 2048 -> 512 -> 2048 35.3 / 33.3, but 4096 -> 512 -> 2048 38.1 / 42.0, at 8 rows 40.7 / 42.9, at 16
-// 45.4 / 43.2; 4096 -> 2000 -> 4096 82.7 / 98.3 at 16 rows.  Smaller layers 448 -> 112 -> 768 29.3 / 22.5 at one row, 46.9 / 23.2 at 128.
-static void skinny_pays(const pf_linear_desc *d, bool &fwd, bool &bwd)
+// The streaming kernels read a factor at 8 rows at a time and take four or five launches a direction, the tiled products two (their readers
+// add the slices of T and dT) and pad to 32 rows; odd ranks cost these unaligned pieces, and a dX of few tiles is long on the gradients' larger
+// ones.  Both in microseconds, fitted to 1107 calls of 1 to 32 rows, layers of 0.4 to 11 million weights (2.7 % rms here, 4.7 and 4.1 % the tiles;
+// the means of factors in the caches and out of them).  us, here / tiled, in the caches and out of them:
+//   forward 1 row, 1472 -> 591 -> 1664 14.1 / 16.5 and 17.4 / 19.3, 9 rows, 2224 -> 970 -> 2816 19.0 / 22.3 and 21.9 / 23.5, 8 rows, 2816 -> 704 -> 3696
+//   19.1 / 17.7 and 21.4 / 19.3, 1 row, 2048 -> 512 -> 2048 14.5 / 13.6 and 17.5 / 16.7;
+//   backward 14 rows, 2848 -> 712 -> 4000 28.2 / 33.7 and 32.0 / 36.2, 1 row, 4000 -> 500 -> 4000 21.4 / 28.2 and 26.6 / 31.0, 6 rows, 2432 -> 608 -> 3136
+//   22.8 / 21.6 and 25.9 / 23.9, 16 rows, 2048 -> 512 -> 2048 22.4 / 17.5 and 25.1 / 19.9.
+// The rule is 0.2 % behind the faster one (geometric mean), none more than 12 %; none more than a tenth behind the streaming kernels.  Below
+// 0.8 million weights the tiles: 448 -> 112 -> 768 29.3 / 22.5 for both directions.
+void linear_skinny_pays(const pf_linear_desc *d, const LinearTiles &t, bool &fwd, bool &bwd)
 {
-    const double weights = (double)d->r * (d->in + d->out);
-    const bool any = d->dtype == PF_F32 && d->M > 0 && d->M <= SK_MAX_ROWS && d->in >= 4 && d->out >= 4 && d->r >= 4;
-    fwd = any && weights >= 2.5e6 && ((d->M <= 8 && d->r >= 700) || (d->M <= 2 && d->r >= 450 && d->r % 4));
-    bwd = any && weights >= (d->M <= 2 ? 2.5e6 : 2.8e6) + (d->M > 8 ? 0.35e6 * (d->M - 8) : 0);
+    const double m = 1e-6 * d->r * (d->in + d->out), M = (double)d->M, odd = d->r % 4 ? 1 : 0; // m: millions of weights
+    fwd = bwd = false;
+    if (d->dtype != PF_F32 || d->M <= 0 || d->M > SK_MAX_ROWS || !t.ok || m < 0.8) return;
+    fwd = 14.25 + 0.96 * m + M * (0.129 + 0.016 * m) < 2.87 + (t.T.cost + t.Y.cost) / 1796 + 0.97 * odd;
+    const double tiles = 0.56 + t.grads.cost / (t.grads.shape == TS_64 ? 1871 : 3042) + t.dT.cost / 1018 + odd * (0.32 + 0.0025 * d->r);
+    bwd = 15.46 + 2.2 * m + M * (0.187 + 0.0218 * m) < 0.98 * tiles;
 }
 
 static LinearPlan make_linear_plan(const pf_linear_desc *d)
@@ -340,7 +347,10 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
         p.lg = plan_linear_grad(d->M, d->in, d->out, d->r);
         p.n_lg = (size_t)p.lg.splits * (d->r * (d->in + d->out) + d->out) + 128;
     }
-    skinny_pays(d, p.skinny_fwd, p.skinny_bwd);
+    p.t = make_linear_tiles(d, 1);
+    if (p.t.fwd_bytes > p.fwd_bytes) p.fwd_bytes = p.t.fwd_bytes;
+    if (p.t.bwd_bytes > p.bwd_bytes) p.bwd_bytes = p.t.bwd_bytes;
+    linear_skinny_pays(d, p.t, p.skinny_fwd, p.skinny_bwd);
     p.n_part_sk = 0;
     if (p.skinny_fwd || p.skinny_bwd) {
         SkinnyArgs a;
@@ -356,9 +366,6 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
         if (fwd > p.fwd_bytes) p.fwd_bytes = fwd;
         if (bwd > p.bwd_bytes) p.bwd_bytes = bwd;
     }
-    p.t = make_linear_tiles(d, 1);
-    if (p.t.fwd_bytes > p.fwd_bytes) p.fwd_bytes = p.t.fwd_bytes;
-    if (p.t.bwd_bytes > p.bwd_bytes) p.bwd_bytes = p.t.bwd_bytes;
     const bool small = d->dtype == PF_F32 && linear_small_supported(d->M, d->in, d->out, d->r);
     // (wide layers are faster on the tiled products: 4096 -> 128 -> 4096 forward 17.3 / 15.5 us at 128 rows, 12.7 / 13.7 at one; forward and
     // backward together 39.9 / 33.1 at 64 rows, 256 -> 64 -> 4096 28.4 / 25.7 at 128; 2048 -> 128 -> 512 21.4 / 23.9 at 64)

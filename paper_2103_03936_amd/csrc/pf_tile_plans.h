@@ -15,6 +15,8 @@ struct LinearTiles {
     size_t n_mid, n_part_T, n_part_g, fwd_bytes, bwd_bytes; // elements of T, partial sums (floats)
 };
 LinearTiles make_linear_tiles(const pf_linear_desc *d, int G);
+// Few rows in float: the streaming kernels of pf_skinny.h instead, for each direction
+void linear_skinny_pays(const pf_linear_desc *d, const LinearTiles &t, bool &fwd, bool &bwd);
 
 // One step of an LSTM layer
 struct LstmTilePlan {

@@ -33,7 +33,16 @@ int emu_slices(int dtype, long long M, long long in, long long out, long long r,
     const LinearTiles p = make_linear_tiles(&d, 1);
     return backward ? (p.dT_sliced ? p.dT.ksplit : 1) : p.T_sliced ? p.T.ksplit : 1;
 }
-// the same of an LSTM cell's T and dT, and whether dx and dh_prev go with the gradients (*one) or all of it backward is on the streaming
+// whether the streaming kernels take a layer in float, forward (1) and backward (2)
+int emu_streamed(long long M, long long in, long long out, long long r)
+{
+    pf_linear_desc d = {};
+    d.M = M, d.in = in, d.out = out, d.r = r, d.dtype = PF_F32;
+    bool fwd, bwd;
+    linear_skinny_pays(&d, make_linear_tiles(&d, 1), fwd, bwd);
+    return fwd + 2 * bwd;
+}
+// slices of an LSTM cell's T (backward: dT), and whether dx and dh_prev go with the gradients (*one) or all of it backward is on the streaming
 // kernels (*skinny)
 int emu_cell_slices(long long B, long long din, long long h, long long r, int groups, int backward, int *one, int *skinny)
 {

@@ -60,6 +60,12 @@ def test_lstm_cell(shape, groups):
     test_gpu_lstm._cell(*shape, groups, seed=23)
 
 
+@pytest.mark.parametrize("shape", [(9, 2224, 2816, 970), (1, 2051, 1030, 515), (32, 4001, 4098, 1029)])
+def test_linear_streamed(shape):
+    """Few rows in float whose factors are streamed in one direction or both (tests/test_host_tiles.py: these are)."""
+    test_gpu_linear._run(*shape, dtype="f32", bias=True, saved_T=shape[0] != 1, seed=29)
+
+
 @pytest.mark.parametrize("groups", [1, 4])
 @pytest.mark.parametrize("shape", [(1, 515, 260, 65), (20, 700, 516, 129), (33, 1030, 900, 225), (3, 1302, 1360, 341), (64, 70, 1500, 375)])
 def test_lstm_cell_slices(shape, groups):

@@ -116,3 +116,13 @@ def test_cells_whose_factors_are_streamed(emu, shape, groups, streaming):
     one, got = ctypes.c_int(), ctypes.c_int()
     emu.emu_cell_slices(B, d, h, r, groups, 1, ctypes.byref(one), ctypes.byref(got))
     assert got.value == streaming
+
+
+@pytest.mark.parametrize("shape,streamed", [((9, 2224, 2816, 970), 3), ((14, 2848, 4000, 712), 2), ((1, 4000, 4000, 500), 2),
+                                            ((8, 2816, 3696, 704), 2), ((1, 2048, 2048, 512), 0), ((6, 2432, 3136, 608), 0), ((16, 2048, 2048, 512), 0),
+                                            ((1, 2051, 1030, 515), 1), ((32, 4001, 4098, 1029), 2),
+                                            ((32, 4096, 4096, 512), 0), ((33, 4096, 4096, 2000), 0), ((1, 448, 768, 112), 0), ((1, 3, 4096, 1000), 0)])
+def test_layers_whose_factors_are_streamed(emu, shape, streamed):
+    """Forward (1) and backward (2), the faster of the streaming kernels and the tiled products by a twentieth and more, factors in the caches or
+    not; neither more rows than the streaming kernels take nor rows shorter than a 16-byte load."""
+    assert emu.emu_streamed(*(ctypes.c_longlong(v) for v in shape)) == streamed
