@@ -355,10 +355,10 @@ static LinearPlan make_linear_plan(const pf_linear_desc *d)
     if (p.skinny_fwd || p.skinny_bwd) {
         SkinnyArgs a;
         const int M = (int)d->M, in = (int)d->in, out = (int)d->out, r = (int)d->r;
-        const size_t n1 = skinny_rows(M, nullptr, in, nullptr, r, in, r, nullptr, a);   // T = X V
-        const size_t n2 = skinny_rows(M, nullptr, r, nullptr, r, r, out, nullptr, a);   // Y = T U^T
-        const size_t n3 = skinny_rows(M, nullptr, out, nullptr, r, out, r, nullptr, a); // dT = dY U
-        const size_t n4 = skinny_rows(M, nullptr, r, nullptr, r, r, in, nullptr, a);    // dX = dT V^T
+        const size_t n1 = skinny_one(M, nullptr, in, nullptr, r, in, r, nullptr, a);   // T = X V
+        const size_t n2 = skinny_one(M, nullptr, r, nullptr, r, r, out, nullptr, a);   // Y = T U^T
+        const size_t n3 = skinny_one(M, nullptr, out, nullptr, r, out, r, nullptr, a); // dT = dY U
+        const size_t n4 = skinny_one(M, nullptr, r, nullptr, r, r, in, nullptr, a);    // dX = dT V^T
         const size_t f = n1 > n2 ? n1 : n2, b = n3 > n4 ? n3 : n4;
         p.n_part_sk = f > b ? f : b;
         const size_t fwd = align_up(p.n_T * sizeof(float)) + align_up(p.n_part_sk * sizeof(float));
@@ -827,11 +827,11 @@ static int linear_T_skinny(const pf_linear_desc *d, const float *X, const float 
 {
     const int M = (int)d->M, in = (int)d->in, r = (int)d->r;
     SkinnyArgs a;
-    skinny_rows(M, X, in, V, r, in, r, part, a);
+    skinny_one(M, X, in, V, r, in, r, part, a);
     int st = launch_skinny_gemm(s, "linear_T=X*V", a, false);
     if (st != PF_OK) return st;
     SliceSumArgs ss = {};
-    ss.s[ss.nseg++] = skinny_rows_seg(a, M, T, a.p[0].N, nullptr);
+    ss.s[ss.nseg++] = slice_seg(a.p[0], T, r, r);
     return launch_slice_sum(s, ss);
 }
 
@@ -845,11 +845,11 @@ static int linear_fwd_skinny(const pf_linear_desc *d, const LinearPlan &p, const
     int st = linear_T_skinny(d, X, V, T, part, s);
     if (st != PF_OK) return st;
     SkinnyArgs a;
-    skinny_rows(M, T, r, U, r, r, out, part, a);
+    skinny_one(M, T, r, U, r, r, out, part, a);
     st = launch_skinny_gemm(s, "linear_Y=T*Ut", a, true);
     if (st != PF_OK) return st;
     SliceSumArgs ss = {};
-    ss.s[ss.nseg++] = skinny_rows_seg(a, M, Y, a.p[0].N, d->has_bias ? bias : nullptr);
+    ss.s[ss.nseg++] = slice_seg(a.p[0], Y, out, out, d->has_bias ? bias : nullptr);
     return launch_slice_sum(s, ss);
 }
 
@@ -868,19 +868,19 @@ static int linear_bwd_skinny(const pf_linear_desc *d, const LinearPlan &p, const
     }
     const float *T = T_saved ? T_saved : Tws;
     SkinnyArgs a;
-    skinny_rows(M, dY, out, U, r, out, r, part, a);
+    skinny_one(M, dY, out, U, r, out, r, part, a);
     st = launch_skinny_gemm(s, "linear_dT=dY*U", a, false);
     if (st != PF_OK) return st;
     SliceSumArgs ss = {};
-    ss.s[ss.nseg++] = skinny_rows_seg(a, M, dT, a.p[0].N, nullptr);
+    ss.s[ss.nseg++] = slice_seg(a.p[0], dT, r, r);
     st = launch_slice_sum(s, ss);
     if (st != PF_OK) return st;
     ss = SliceSumArgs{};
     if (dX) {
-        skinny_rows(M, dT, r, V, r, r, in, part, a);
+        skinny_one(M, dT, r, V, r, r, in, part, a);
         st = launch_skinny_gemm(s, "linear_dX=dT*Vt", a, true);
         if (st != PF_OK) return st;
-        ss.s[ss.nseg++] = skinny_rows_seg(a, M, dX, a.p[0].N, nullptr);
+        ss.s[ss.nseg++] = slice_seg(a.p[0], dX, in, in);
     }
     // factor gradients are rank-M updates; the slice sums of dX ride along
     RankArgs ra = {};

@@ -105,12 +105,12 @@ inline SkinnyProb skinny_prob(int M, const float *A, i64 lda, const float *W, i6
     return p;
 }
 
-// the slice sums of problem p into out[m * ldo + n], n < N
-inline SliceSumSeg slice_seg(const SkinnyProb &p, float *out, i64 ldo, int N)
+// the slice sums of problem p into out[m * ldo + n], n < N (+ bias[n])
+inline SliceSumSeg slice_seg(const SkinnyProb &p, float *out, i64 ldo, int N, const float *bias = nullptr)
 {
     SliceSumSeg s;
     s.P = p.P;
-    s.bias = nullptr;
+    s.bias = bias;
     s.M = p.M;
     s.out = out;
     s.pcount = p.pcount;
@@ -121,27 +121,16 @@ inline SliceSumSeg slice_seg(const SkinnyProb &p, float *out, i64 ldo, int N)
     return s;
 }
 
-// Row blocks of up to 32 rows of one product C[M x N] = A[M x K] W become the problems of one launch
-// (M <= 32 * SK_MAX_PROB).  Places the slice sums from `part` on (NULL: size only) and returns the floats they take.
-inline size_t skinny_rows(int M, const float *A, i64 lda, const float *W, i64 ldw, int K, int N, float *part,
-                          SkinnyArgs &a)
+// One product C[M x N] = A[M x K] W (M <= 32) as the only problem of a launch.  Places the slice sums at `part` (NULL: size only) and returns
+// the floats they take.
+inline size_t skinny_one(int M, const float *A, i64 lda, const float *W, i64 ldw, int K, int N, float *part, SkinnyArgs &a)
 {
     a = SkinnyArgs{};
-    const i64 pc = (i64)M * N;
-    for (int m0 = 0; m0 < M; m0 += SK_MAX_ROWS)
-        a.p[a.nprob++] = skinny_prob(M - m0 < SK_MAX_ROWS ? M - m0 : SK_MAX_ROWS, A ? A + (i64)m0 * lda : nullptr, lda,
-                                     W, ldw, K, N, N, pc);
+    a.nprob = 1;
+    a.p[0] = skinny_prob(M, A, lda, W, ldw, K, N, N, (i64)M * N);
     skinny_plan(a);
-    for (int q = 0; q < a.nprob; ++q) a.p[q].P = part ? part + (i64)SK_MAX_ROWS * q * N : nullptr;
-    return (size_t)(a.p[0].ksplit * pc); // every block has the same K and N, hence the same slicing
-}
-// all row blocks of such a product summed in one segment: out[m * ldo + n] (+ bias[n])
-inline SliceSumSeg skinny_rows_seg(const SkinnyArgs &a, int M, float *out, i64 ldo, const float *bias)
-{
-    SliceSumSeg sg = slice_seg(a.p[0], out, ldo, a.p[0].N);
-    sg.M = M;
-    sg.bias = bias;
-    return sg;
+    a.p[0].P = part;
+    return (size_t)(a.p[0].ksplit * a.p[0].pcount);
 }
 
 // out[i * ldo + j] (+)= sum_b A[b * lda + i] * Bm[b * ldb + j], b < M: the weight gradients of a cell are
@@ -150,15 +139,14 @@ struct RankProb {
     const float *A, *Bm;
     float *out;
     i64 lda, ldb, ldo;
-    int M, I, J, wg0, jt; // M = rows summed over; jt = column tiles
+    int I, J, wg0, jt; // jt = column tiles
 };
 constexpr int RK_MAX_PROB = 12;
 struct RankArgs {
     RankProb p[RK_MAX_PROB];
-    int nprob, M, accumulate, nwg; // M: rows of a problem added without a count of its own
+    int nprob, M, accumulate, nwg; // M: rows summed over
 };
-void rank_add(RankArgs &a, const float *A, i64 lda, const float *Bm, i64 ldb, float *out, i64 ldo, int I, int J,
-              int M = -1);
+void rank_add(RankArgs &a, const float *A, i64 lda, const float *Bm, i64 ldb, float *out, i64 ldo, int I, int J);
 // seg: optional slice sums done by extra workgroups of the same launch (nseg == 0: none)
 int launch_rank_update(hipStream_t s, const char *name, const RankArgs &a, const SliceSumArgs &seg);
 

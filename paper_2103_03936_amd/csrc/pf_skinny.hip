@@ -374,43 +374,40 @@ __global__ __launch_bounds__(256) void rank_update_kernel(RankArgs a, SliceSumAr
         for (int f = 0; f < 4; ++f) acc[e][f] = old[f];
     }
 
-    for (int b0 = 0; b0 < pb.M; b0 += SK_MAX_ROWS) {
-        const int nb = min(SK_MAX_ROWS, pb.M - b0);
-        if (b0) __syncthreads();
-        // 16-byte pieces, all of a thread's requests in flight together (rows are only 4-byte aligned)
-        if (tid < nb * (RK_TI / 4)) {
-            const int b = tid / (RK_TI / 4), i4 = 4 * (tid % (RK_TI / 4));
-            const int left = I - (i0 + i4);
-            *(f32x4_t *)&As[b][i4] = ld4n(pb.A + (i64)(b0 + b) * pb.lda + (left > 0 ? i0 + i4 : 0), left);
+    const int nb = a.M;
+    // 16-byte pieces, all of a thread's requests in flight together (rows are only 4-byte aligned)
+    if (tid < nb * (RK_TI / 4)) {
+        const int b = tid / (RK_TI / 4), i4 = 4 * (tid % (RK_TI / 4));
+        const int left = I - (i0 + i4);
+        *(f32x4_t *)&As[b][i4] = ld4n(pb.A + (i64)b * pb.lda + (left > 0 ? i0 + i4 : 0), left);
+    }
+    f32x4_t bv[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = tid + 256 * q, b = e / (RK_TJ / 4), j4 = 4 * (e % (RK_TJ / 4));
+        const int left = J - (j0 + j4);
+        bv[q] = f32x4_t{1.f, 1.f, 1.f, 1.f};
+        if (e < nb * (RK_TJ / 4) && pb.Bm) bv[q] = ld4n(pb.Bm + (i64)b * pb.ldb + (left > 0 ? j0 + j4 : 0), left);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = tid + 256 * q, b = e / (RK_TJ / 4), j4 = 4 * (e % (RK_TJ / 4));
+        const int left = J - (j0 + j4);
+        if (e < nb * (RK_TJ / 4)) {
+            f32x4_t v = bv[q];
+#pragma unroll
+            for (int f = 0; f < 4; ++f) v[f] = f < left ? v[f] : 0.f; // past J: zero (also for the ones column)
+            *(f32x4_t *)&Bs[b][j4] = v;
         }
-        f32x4_t bv[4];
+    }
+    __syncthreads();
+    for (int b = 0; b < nb; ++b) {
+        const f32x4_t av = *(const f32x4_t *)&As[b][4 * ti];
+        const f32x4_t bv = *(const f32x4_t *)&Bs[b][4 * tj];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q, b = e / (RK_TJ / 4), j4 = 4 * (e % (RK_TJ / 4));
-            const int left = J - (j0 + j4);
-            bv[q] = f32x4_t{1.f, 1.f, 1.f, 1.f};
-            if (e < nb * (RK_TJ / 4) && pb.Bm) bv[q] = ld4n(pb.Bm + (i64)(b0 + b) * pb.ldb + (left > 0 ? j0 + j4 : 0), left);
-        }
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int e = tid + 256 * q, b = e / (RK_TJ / 4), j4 = 4 * (e % (RK_TJ / 4));
-            const int left = J - (j0 + j4);
-            if (e < nb * (RK_TJ / 4)) {
-                f32x4_t v = bv[q];
-#pragma unroll
-                for (int f = 0; f < 4; ++f) v[f] = f < left ? v[f] : 0.f; // past J: zero (also for the ones column)
-                *(f32x4_t *)&Bs[b][j4] = v;
-            }
-        }
-        __syncthreads();
-        for (int b = 0; b < nb; ++b) {
-            const f32x4_t av = *(const f32x4_t *)&As[b][4 * ti];
-            const f32x4_t bv = *(const f32x4_t *)&Bs[b][4 * tj];
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int f = 0; f < 4; ++f) acc[e][f] += av[e] * bv[f];
-        }
+            for (int f = 0; f < 4; ++f) acc[e][f] += av[e] * bv[f];
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -430,7 +427,7 @@ __global__ __launch_bounds__(256) void rank_update_kernel(RankArgs a, SliceSumAr
     }
 }
 
-void rank_add(RankArgs &a, const float *A, i64 lda, const float *Bm, i64 ldb, float *out, i64 ldo, int I, int J, int M)
+void rank_add(RankArgs &a, const float *A, i64 lda, const float *Bm, i64 ldb, float *out, i64 ldo, int I, int J)
 {
     if (!out || a.nprob >= RK_MAX_PROB) return;
     RankProb &p = a.p[a.nprob];
@@ -440,7 +437,6 @@ void rank_add(RankArgs &a, const float *A, i64 lda, const float *Bm, i64 ldb, fl
     p.lda = lda;
     p.ldb = ldb;
     p.ldo = ldo;
-    p.M = M >= 0 ? M : a.M;
     p.I = I;
     p.J = J;
     p.jt = (J + RK_TJ - 1) / RK_TJ;
@@ -454,6 +450,7 @@ int launch_rank_update(hipStream_t s, const char *name, const RankArgs &a, const
     int st = PF_OK;
     const int nsb = seg.nseg > 0 ? slice_sum_blocks(seg) : 0;
     if (a.nwg + nsb <= 0) return st;
+    if (a.M > SK_MAX_ROWS) return PF_ERR_UNSUPPORTED;
     PF_LAUNCH(st, name, rank_update_kernel, dim3(a.nwg + nsb), dim3(256), s, a, seg, nsb);
     return st;
 }

@@ -119,7 +119,9 @@ tile_conv_kernel(TileArgs by_value)
     }
 }
 
-template <typename CT, class CFG, class CFGW>
+// FORMS: which of the kernel's four forms a launch of these shapes can be, a bit each (strided input or paired pixels, weight gradients)
+enum { CONV_PLAIN = 1, CONV_WG = 2, CONV_GATHER = 4, CONV_GATHER_WG = 8, CONV_ALL = 15 };
+template <typename CT, class CFG, class CFGW, int FORMS>
 static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
 {
     typedef LoadPixMC<CT, CFG::BN, false> BP;
@@ -137,31 +139,36 @@ static int launch_conv(hipStream_t s, const char *name, const TileArgs &a)
     }
     tab = (tab + 15) / 16 * 16;
 #define PF_TILE_CONV(G, W)                                                                                              \
-    if (gather == G && wg == W)                                                                                         \
-        PF_LAUNCH_LDS(st, name, (tile_conv_kernel<CT, CFG, CFGW, G, W>), dim3(a.blocks), dim3(TILE_THREADS), tab, s, a);
+    if constexpr (FORMS >> (2 * G + W) & 1)                                                                             \
+        if (gather == G && wg == W) {                                                                                   \
+            PF_LAUNCH_LDS(st, name, (tile_conv_kernel<CT, CFG, CFGW, G, W>), dim3(a.blocks), dim3(TILE_THREADS), tab, s, a); \
+            return st;                                                                                                  \
+        }
     PF_TILE_CONV(false, false)
     PF_TILE_CONV(false, true)
     PF_TILE_CONV(true, false)
     PF_TILE_CONV(true, true)
 #undef PF_TILE_CONV
-    return st;
+    return PF_ERR_UNSUPPORTED;
 }
 template <typename CT>
 int launch_conv_t(hipStream_t s, const char *name, TileShape shape, TileShape wg, const TileArgs &a)
 {
     typedef TileCfg<64, 64, 2, 2, 2> S64;
+    typedef TileCfg<32, 64, 1, 2, 4> S32;
     typedef TileCfg<32, 128, 1, 4, 2> W32;
+    // (half-height tiles beside weight gradients are those of dX in float with unit stride; the widest have Y alone)
+    constexpr int BESIDE = sizeof(CT) == 4 ? CONV_WG : 0;
     switch (shape) {
     case TS_32x64: {
         bool grads = false;
         for (int i = 0; i < a.n; ++i) grads = grads || a.p[i].type == TILE_WG || a.p[i].type == TILE_WGT;
-        if constexpr (sizeof(CT) == 4)
-            if (grads && wg == TS_64) return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, S64>(s, name, a);
+        if (grads && wg == TS_64) return launch_conv<CT, S32, S64, BESIDE>(s, name, a);
         if (grads && wg != TS_32x128) return PF_ERR_UNSUPPORTED;
-        return launch_conv<CT, TileCfg<32, 64, 1, 2, 4>, W32>(s, name, a);
+        return launch_conv<CT, S32, W32, CONV_PLAIN | CONV_GATHER | BESIDE>(s, name, a);
     }
-    case TS_64: return wg == TS_32x128 ? launch_conv<CT, S64, W32>(s, name, a) : launch_conv<CT, S64, S64>(s, name, a);
-    case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>, S64>(s, name, a);
+    case TS_64: return wg == TS_32x128 ? launch_conv<CT, S64, W32, CONV_ALL>(s, name, a) : launch_conv<CT, S64, S64, CONV_ALL>(s, name, a);
+    case TS_128x64: return launch_conv<CT, TileCfg<128, 64, 2, 2, 2>, S64, CONV_PLAIN>(s, name, a);
     default: return PF_ERR_UNSUPPORTED;
     }
 }

@@ -217,7 +217,7 @@ int emu_rank_update_kernel(dim3 grid, const RankArgs &a, const SliceSumArgs &seg
     if (tiles != a.nwg || (int)grid.x != a.nwg + nsb) { g_err = "rank update: grid"; return PF_ERR_LAUNCH; }
     for (int q = 0; q < a.nprob; ++q) {
         const RankProb &p = a.p[q];
-        for (int b = 0; b < p.M; ++b) {
+        for (int b = 0; b < a.M; ++b) {
             CHK(p.A + (i64)b * p.lda, p.I, "rank A");
             if (p.Bm) CHK(p.Bm + (i64)b * p.ldb, p.J, "rank B");
         }
@@ -225,7 +225,7 @@ int emu_rank_update_kernel(dim3 grid, const RankArgs &a, const SliceSumArgs &seg
             CHK(p.out + (i64)i * p.ldo, p.J, "rank out");
             for (int j = 0; j < p.J; ++j) {
                 double acc = a.accumulate ? p.out[(i64)i * p.ldo + j] : 0.0;
-                for (int b = 0; b < p.M; ++b) acc += (double)p.A[(i64)b * p.lda + i] * (p.Bm ? p.Bm[(i64)b * p.ldb + j] : 1.0f);
+                for (int b = 0; b < a.M; ++b) acc += (double)p.A[(i64)b * p.lda + i] * (p.Bm ? p.Bm[(i64)b * p.ldb + j] : 1.0f);
                 p.out[(i64)i * p.ldo + j] = (float)acc;
             }
         }
