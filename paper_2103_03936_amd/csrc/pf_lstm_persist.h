@@ -23,5 +23,7 @@ struct LstmRecurrence {
 };
 // Members are null where the kernels are not part of the build (host-only builds of the launch schedule).
 extern LstmRecurrence lstm_recurrence;
+// floats that the workspace of a call has for it
+size_t lstm_stack_room(const pf_lstm_stack_desc *d, bool bwd);
 
 } // namespace pf

@@ -654,16 +654,6 @@ static int lp_cus()
     return n < LP_MOST_CUS ? n : LP_MOST_CUS;
 }
 
-// Whether the largest device could take the call, and what it needs there: sizes do not depend on the device (a workspace may be
-// asked for before one is chosen).  A single step uses the factors once: 125 us as launches, 160 here (1216 units, batch 28).
-static size_t lp_floats(const LstmGeom &g, bool bwd)
-{
-    LstmGeom some = g;
-    some.B = lp_rows_at_once(g, bwd, LP_MOST_CUS);
-    return g.T + g.L < 3 || some.B == 0 ? 0 : lp_plan(some, bwd, LP_MOST_CUS).floats;
-}
-// (Halves with a pair per gate are no reason for a larger workspace: they are taken where they find room.)
-static size_t lp_wants(const LstmGeom &g, bool bwd) { return g.G != 1 && lp_rows_at_once(g, bwd, LP_MOST_CUS) != g.B ? 0 : lp_floats(g, bwd); }
 static bool lp_fits(const LstmGeom &g, bool bwd, size_t room)
 {
     const size_t n = lp_floats(g, bwd);

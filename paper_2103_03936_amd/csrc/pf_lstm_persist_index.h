@@ -292,24 +292,42 @@ static LpPlan lp_plan(const LstmGeom &g, bool bwd, int cus)
     return p;
 }
 
+// What the launches of a slot take beyond two launches of the recurrence with half the rows each, us a call.  A slot is 9.6 us of launches and their
+// gaps, 3.5 more a layer and half for every million weights that it reads, less what two exchanges over the chip take, which grow with the row
+// blocks and units; a second cooperative launch and its start are 58.  Backward with one pair for all gates the launches of a slot are fewer, and slices
+// of dT are summed at the end.  Fitted to 1218 calls of 21 to 32 rows.  us, slots / halves: one pair, three layers of 704 units, batch 24, 34 steps
+// forward 968 / 546, two of 1152, batch 30, 4 steps 179 / 188, three of 1378, batch 29, 4 steps backward 319 / 459, of 1365, batch 23, 37 steps 1877 / 1371; a
+// pair per gate, three layers of 128 units, batch 27, 57 steps forward 1727 / 670, of 960, 55 steps 2465 / 1486, backward 2758 / 1899, two of 1392,
+// batch 22, 51 steps forward 2069 / 1400, one of 1216, batch 26 1274 / 1501, two of 832, batch 32, 8 steps backward 317 / 346.  The rule is 0.2 % behind the
+// faster way (geometric mean), one call in 58 by more than a twentieth, 14 % at most.
+static double lp_halves_gain(const LstmGeom &g, bool bwd)
+{
+    const int first = (g.B + 1) / 2, blocks = lp_row_blocks(first) + lp_row_blocks(g.B - first), slots = g.T + g.L - 1;
+    const double weights = 1e-6 * g.L * (2.0 * g.gr * g.h + 8.0 * g.h * g.r);
+    const double all = -58 + slots * (9.63 + 3.49 * g.L + 0.49 * weights - 0.53 * blocks - 8.42e-3 * g.h + (g.G == 1 ? 3.05 : 0));
+    return bwd && g.G == 1 ? all - 26 - 7.5 * blocks + slots * (11.7 - 2.05 * blocks) : all;
+}
 // Rows of a launch: all, or half of them, one launch after the other, where only the halves' row blocks fit beside the factors and that is
-// faster than the launches of a slot.  Whole calls, us, slots / halves: one pair per path, 896 units, three layers, batch 21, 36 steps 1960 /
-// 1277, 5 steps 415 / 361; 1500 units, two layers, batch 32, 4 steps 413 / 401, 2 steps 307 / 315.  A pair per gate: 700 units, three layers,
-// batch 21, 36 steps 2834 / 1650, 3 steps 422 / 396; two of 896, batch 32, 10 steps 778 / 741, 5 steps 460 / 502; two of 128, batch 32, 5 steps
-// 330 / 285, 3 steps 234 / 240; one layer of 1024, batch 32, 24 steps 1373 / 1221, 8 steps 500 / 534; two of 1280, batch 21, 8 steps 787 / 675,
-// batch 32 853 / 888; one of 1500, batch 32, 24 steps 1589 / 1773.
+// the faster way.
 static int lp_rows_at_once(const LstmGeom &g, bool bwd, int cus)
 {
     if (lp_plan(g, bwd, cus).NT > 0) return g.B;
     LstmGeom half = g;
     half.B = (g.B + 1) / 2;
-    if (g.B < 2 || lp_plan(half, bwd, cus).NT == 0) return 0;
-    int least = 4; // steps
-    if (g.G != 1) least = g.h > 896 ? (g.L == 1 ? 16 : 8) : g.L == 1 ? 16 : g.L == 2 ? (g.h <= 512 ? 5 : 10) : 3;
-    if (g.T < least || (g.G != 1 && g.h > 896 && (g.L == 1 ? g.h > 1024 : g.h > 1280 || half.B > 12))) return 0;
-    return half.B;
+    return g.B > 1 && lp_plan(half, bwd, cus).NT > 0 && lp_halves_gain(g, bwd) > 0 ? half.B : 0;
 }
 
+// Whether the largest device could take the call, and what it needs there: sizes do not depend on the device (a workspace may be
+// asked for before one is chosen).  A single step uses the factors once: 125 us as launches, 160 here (1216 units, batch 28).
+static size_t lp_floats(const LstmGeom &g, bool bwd)
+{
+    LstmGeom some = g;
+    some.B = lp_rows_at_once(g, bwd, LP_MOST_CUS);
+    return g.T + g.L < 3 || some.B == 0 ? 0 : lp_plan(some, bwd, LP_MOST_CUS).floats;
+}
+// (Halves with a pair per gate are no reason for a larger workspace than that of the launches of a slot: they are taken where their exchange buffers,
+// which hold every step, fit into it, so for shorter sequences or larger layers, whose slices and copied factors are more.)
+static size_t lp_wants(const LstmGeom &g, bool bwd) { return g.G != 1 && lp_rows_at_once(g, bwd, LP_MOST_CUS) != g.B ? 0 : lp_floats(g, bwd); }
 // rows b0 .. b0 + g.B - 1 of arrays with BT of them
 static LstmRunLayer lp_rows(const LstmRunLayer &l, const LstmGeom &g, int b0)
 {

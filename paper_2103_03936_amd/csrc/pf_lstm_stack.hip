@@ -1058,6 +1058,12 @@ static int stack_bwd_slot(const StackGeom &g, const StackPtrs &p, const StackPac
     return st_slice_sums(s, last, "lstm_stack_dh0_sum");
 }
 
+// what a backward call keeps of all steps
+static size_t stack_kept(const StackGeom &g, const StackPlan &p)
+{
+    return (size_t)g.L * (align_up(p.n_dz * sizeof(float)) + 2 * align_up(p.n_dT * sizeof(float)));
+}
+
 static int plan_stack(const StackGeom &g, StackPlan *out)
 {
     StackPlan p = {};
@@ -1097,7 +1103,7 @@ static int plan_stack(const StackGeom &g, StackPlan *out)
     p.n_pack_f = stack_pack(g, none, false, nullptr, nullptr, true, nullptr, nullptr);
     p.n_pack_b = stack_pack(g, none, true, nullptr, nullptr, true, nullptr, nullptr);
     p.fwd_bytes = align_up(p.n_zx0 * sizeof(float)) + align_up(p.n_part * sizeof(float)) + align_up(p.n_pack_f * sizeof(float));
-    const size_t kept = (size_t)g.L * (align_up(p.n_dz * sizeof(float)) + 2 * align_up(p.n_dT * sizeof(float)));
+    const size_t kept = stack_kept(g, p);
     p.bwd_bytes = kept + align_up(p.n_part * sizeof(float)) + align_up(p.n_part2 * sizeof(float)) +
                   align_up(p.n_pack_b * sizeof(float));
     // (the one-launch recurrence: its exchange buffers instead of slices and copied factors)
@@ -1109,6 +1115,18 @@ static int plan_stack(const StackGeom &g, StackPlan *out)
     }
     *out = p;
     return PF_OK;
+}
+
+static size_t stack_room(const StackGeom &g, const StackPlan &p, bool bwd)
+{
+    const size_t beside = align_up(p.n_part * sizeof(float));
+    return (bwd ? p.bwd_bytes - stack_kept(g, p) - beside : p.fwd_bytes - beside) / sizeof(float);
+}
+size_t lstm_stack_room(const pf_lstm_stack_desc *d, bool bwd)
+{
+    StackGeom g;
+    StackPlan p;
+    return check_stack_desc(d, &g) == PF_OK && d->T * d->B > 0 && plan_stack(g, &p) == PF_OK ? stack_room(g, p, bwd) : 0;
 }
 
 } // namespace pf
@@ -1180,7 +1198,7 @@ int pf_lowrank_lstm_stack_fwd(const pf_lstm_stack_desc *d, const void *x, const 
     const int h = g.h, r = g.r, gr = g.gr;
     const StackTall tall = plan_tall(g);
     const TileProb tx0 = tile_prob(TILE_NN, (int)Mt, gr, g.din, x, g.din, p.Vx[0], gr, nullptr, gr);
-    const size_t room = (pl.fwd_bytes - align_up(pl.n_part * sizeof(float))) / sizeof(float);
+    const size_t room = stack_room(g, pl, false);
     if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), false, room)) {
         float *part = ws.take<float>(pl.n_part), *run = ws.take<float>(room);
         if (!ws.ok()) return PF_ERR_WORKSPACE;
@@ -1294,8 +1312,7 @@ int pf_lowrank_lstm_stack_bwd(const pf_lstm_stack_desc *d, const void *x, const 
         b.dTx_all[l] = ws.take<float>(pl.n_dT);
     }
     float *part = ws.take<float>(pl.n_part);
-    const size_t kept = (size_t)L * (align_up(pl.n_dz * sizeof(float)) + 2 * align_up(pl.n_dT * sizeof(float)));
-    const size_t room = (pl.bwd_bytes - kept - align_up(pl.n_part * sizeof(float))) / sizeof(float);
+    const size_t room = stack_room(g, pl, true);
     if (lstm_recurrence.run && lstm_recurrence.fits(run_geom(g), true, room)) {
         float *run = ws.take<float>(room);
         if (!ws.ok()) return PF_ERR_WORKSPACE;

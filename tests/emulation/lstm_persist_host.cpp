@@ -21,17 +21,30 @@ int emu_walk(int n, int first, int step, int rows, long long *count, long long *
     return 1;
 }
 
-// Every workgroup of a run gives up in slot `slot`: the outputs that are not what they should be (the steps that the slot
-// and those after it write are NaN, the ones before are untouched, nothing outside is written), or -1: no such launch.
-int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot)
+// Rows of a launch on a device of 256 compute units (0: not taken); `fits`: and whether the exchange buffers find room in the workspace that
+// a call asks for
+int emu_rows(int T, int B, int d, int h, int r, int G, int L, int bwd, int *fits)
+{
+    const LstmGeom g = {T, B, h, r, G, G * r, L};
+    pf_lstm_stack_desc s = {};
+    s.T = T, s.B = B, s.d_in = d, s.h = h, s.r = r, s.groups = G, s.layers = L;
+    const size_t n = lp_floats(g, bwd);
+    *fits = n > 0 && n <= lstm_stack_room(&s, bwd);
+    return lp_rows_at_once(g, bwd, 256);
+}
+
+// Every workgroup of a run of rows b0 .. b0 + B - 1 of BT gives up in slot `slot`: the outputs that are not what they should be (the steps
+// that the slot and those after it write are NaN, the ones before and the other rows are untouched, nothing outside is written), or -1: no
+// such launch.
+int emu_void_rows(int T, int B, int h, int r, int G, int L, int bwd, int slot, int b0, int BT)
 {
     const LstmGeom g = {T, B, h, r, G, G * r, L};
     const LpPlan p = lp_plan(g, bwd, 256);
     if (p.NT == 0) return -1;
-    const int pad = 4096, TB = T * B, gr = G * r;
+    const int pad = 4096, TB = T * BT, gr = G * r;
     struct Array {
         std::vector<float> v;
-        int rows; // per step
+        int rows, width; // elements per step, per row
         bool used;
     };
     std::vector<Array> arrays((size_t)L * 10);
@@ -41,14 +54,15 @@ int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot)
         const int width[10] = {h, h, 4 * h, gr, gr, 4 * h, gr, gr, h, h};
         for (int i = 0; i < 10; ++i) {
             Array &a = arrays[(size_t)q * 10 + i];
-            a.rows = B * width[i];
-            a.v.assign((size_t)(i < 8 ? TB : B) * width[i] + 2 * pad, 0.f);
+            a.width = width[i];
+            a.rows = BT * width[i];
+            a.v.assign((size_t)(i < 8 ? TB : BT) * width[i] + 2 * pad, 0.f);
             a.used = (i >= 5) == (bwd != 0) && !((i == 4 || i == 7) && q == 0); // (the first layer's Tx is an input, its dTx a later product)
             *out[i] = a.v.data() + pad;
         }
     }
     LpArgs a;
-    lp_fill(a, p, g, l, nullptr, nullptr);
+    lp_fill(a, p, g, l, nullptr, nullptr, b0, BT);
     for (int wg = 0; wg < p.nwg; ++wg)
         for (int tid = 0; tid < LP_NT; ++tid) {
             if (bwd)
@@ -65,8 +79,8 @@ int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot)
             const int left = T - (slot - (L - 1 - q)); // backward: steps below this one
             for (size_t e = 0; e < b.v.size(); ++e) {
                 const bool in = e >= (size_t)pad && e < pad + n;
-                const int t = in ? (int)((e - pad) / b.rows) : 0;
-                bool want = in && b.used;
+                const int t = in ? (int)((e - pad) / b.rows) : 0, row = in ? (int)((e - pad) % b.rows) / b.width : 0;
+                bool want = in && b.used && row >= b0 && row < b0 + B;
                 if (i < 5) want = want && t >= slot - q;
                 else if (i >= 8) want = want && left >= 0;
                 else if (!((i == 6 || i == 7) && p.SL > 1)) want = want && t < left; // (sums over slices are written at the end)
@@ -75,6 +89,8 @@ int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot)
         }
     return wrong;
 }
+
+int emu_void(int T, int B, int h, int r, int G, int L, int bwd, int slot) { return emu_void_rows(T, B, h, r, G, L, bwd, slot, 0, B); }
 
 // The tasks that every wavefront waits for against those whose results it reads: how many wavefronts differ, -1: no such launch.
 int emu_watch(int T, int B, int h, int r, int G, int L, int bwd)

@@ -539,3 +539,13 @@ def test_layer_stack_rows_in_two_launches(shape):
     import paper_2103_03936_amd as pf
     T, B, d, h, r, L, G = shape
     _check_stack_case(pf, T, B, d, h, r, L, G, True, 61, str(shape))
+
+
+@pytest.mark.parametrize("shape", [(9, 23, 12, 1100, 30, 3, 1), (30, 21, 8, 1400, 20, 3, 1), (6, 23, 40, 70, 12, 2, 4), (24, 30, 20, 640, 160, 1, 4),
+                                   (9, 25, 12, 700, 40, 3, 4), (9, 29, 12, 1200, 40, 3, 4), (14, 31, 20, 260, 30, 2, 4)])
+def test_layer_stack_halves(shape):
+    """Half the rows at a time, of both directions or one (tests/test_host_lstm_persist.py: which): odd batches, one to five row blocks, one to
+    three tiles of a task."""
+    import paper_2103_03936_amd as pf
+    T, B, d, h, r, L, G = shape
+    _check_stack_case(pf, T, B, d, h, r, L, G, True, 62, str(shape))
