@@ -292,20 +292,21 @@ static LpPlan lp_plan(const LstmGeom &g, bool bwd, int cus)
     return p;
 }
 
-// What the launches of a slot take beyond two launches of the recurrence with half the rows each, us a call.  A slot is 9.6 us of launches and their
-// gaps, 3.5 more a layer and half for every million weights that it reads, less what two exchanges over the chip take, which grow with the row
-// blocks and units; a second cooperative launch and its start are 58.  Backward with one pair for all gates the launches of a slot are fewer, and slices
-// of dT are summed at the end.  Fitted to 1218 calls of 21 to 32 rows.  us, slots / halves: one pair, three layers of 704 units, batch 24, 34 steps
-// forward 968 / 546, two of 1152, batch 30, 4 steps 179 / 188, three of 1378, batch 29, 4 steps backward 319 / 459, of 1365, batch 23, 37 steps 1877 / 1371; a
-// pair per gate, three layers of 128 units, batch 27, 57 steps forward 1727 / 670, of 960, 55 steps 2465 / 1486, backward 2758 / 1899, two of 1392,
-// batch 22, 51 steps forward 2069 / 1400, one of 1216, batch 26 1274 / 1501, two of 832, batch 32, 8 steps backward 317 / 346.  The rule is 0.2 % behind the
-// faster way (geometric mean), one call in 58 by more than a twentieth, 14 % at most.
+// What the launches of a slot take beyond two launches of the recurrence with half the rows each, us a call.  A slot is 7.1 us of launches and their
+// gaps, 3.7 more a layer and half for every million weights that it reads, less what two exchanges over the chip take, which grow with the row
+// blocks, units and, with a pair per gate, the columns of T; a second cooperative launch and its start are 59.  Backward with one pair for all gates the
+// launches of a slot are fewer, and slices of dT are summed at the end.  Fitted to 1218 calls of 21 to 32 rows.  us, slots / halves:
+//   one pair, three layers of 704 units, batch 24, 34 steps forward 968 / 546, two of 1152, batch 30, 4 steps 179 / 188, three of 1378, batch 29, 4 steps
+//   backward 319 / 459, of 1365, batch 23, 37 steps 1877 / 1371;
+//   a pair per gate, three layers of 128 units, batch 27, 57 steps forward 1727 / 670, of 960, 55 steps 2465 / 1486, backward 2758 / 1899, two of 1392,
+//   batch 22, 51 steps forward 2069 / 1400, one of 1216, batch 26 1274 / 1501, backward 1433 / 1338, two of 832, batch 32, 8 steps backward 317 / 346.
+// The rule is 0.2 % behind the faster way (geometric mean), one call in 70 by more than a twentieth, 15 % at most.
 static double lp_halves_gain(const LstmGeom &g, bool bwd)
 {
     const int first = (g.B + 1) / 2, blocks = lp_row_blocks(first) + lp_row_blocks(g.B - first), slots = g.T + g.L - 1;
     const double weights = 1e-6 * g.L * (2.0 * g.gr * g.h + 8.0 * g.h * g.r);
-    const double all = -58 + slots * (9.63 + 3.49 * g.L + 0.49 * weights - 0.53 * blocks - 8.42e-3 * g.h + (g.G == 1 ? 3.05 : 0));
-    return bwd && g.G == 1 ? all - 26 - 7.5 * blocks + slots * (11.7 - 2.05 * blocks) : all;
+    const double all = -59 + slots * (7.12 + 3.73 * g.L + 0.5 * weights - 0.185 * blocks - 3.52e-3 * g.h - (g.G == 1 ? 2.89 : 3.1e-3 * g.r * blocks));
+    return bwd && g.G == 1 ? all - 25.4 - 7.4 * blocks + slots * (12.3 - 2.4 * blocks) : all;
 }
 // Rows of a launch: all, or half of them, one launch after the other, where only the halves' row blocks fit beside the factors and that is
 // the faster way.
