@@ -212,10 +212,6 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
     p.tiles = true;
     const i64 npx = (i64)g.N * HC * V;
     p.sh_Y = g.Cout <= 32 ? TS_32x64 : g.Cout >= 128 && (g.Cout + 127) / 128 * ((npx + 63) / 64) >= 512 ? TS_128x64 : TS_64;
-    // Tiles that leave half the chip idle, splits and all: half as high, for a chunk of theirs takes half the time and they are twice as many.
-    // Both directions, us, 64 x 64 / 32 x 64, at most 128 of them: float 6 x 224 x 5 x 5, rank 39 60.0 / 54.4, 26 x 256 x 8 x 8, rank 64, stride 2
-    // 64.8 / 60.3, bf16 22 x 384 x 5 x 5, rank 80 56 / 53.5; with a full chip they are the slower ones (float 6 x 396 x 16 x 16, rank 99, T in
-    // 384 workgroups 110 / 118); bf16 T and dT from 64 on (36 x 343 x 12 x 12, rank 61, 81 tiles 45 / 46.4).
     // T and dT: too few tiles for the chip split their contraction (at least four chunks each)
     const auto split_k = [&](i64 K, i64 bm, i64 &tiles) {
         tiles = (g.r + bm - 1) / bm * ((npx + 63) / 64);
@@ -225,6 +221,10 @@ static void plan_conv_tiles(const ConvGeom &g, int dtype, ConvPlan &p)
         if (ks > 16) ks = 16;
         return (int)(ks < 1 ? 1 : ks);
     };
+    // Tiles that leave half the chip idle, splits and all: half as high, for a chunk of theirs takes half the time and they are twice as many.
+    // Both directions, us, 64 x 64 / 32 x 64, at most 128 of them: float 6 x 224 x 5 x 5, rank 39 60.0 / 54.4, 26 x 256 x 8 x 8, rank 64, stride 2
+    // 64.8 / 60.3, bf16 22 x 384 x 5 x 5, rank 80 56 / 53.5; with a full chip they are the slower ones (float 6 x 396 x 16 x 16, rank 99, T in
+    // 384 workgroups 110 / 118); bf16 T and dT from 64 on (36 x 343 x 12 x 12, rank 61, 81 tiles 45 / 46.4).
     const auto mid = [&](i64 K, bool taps, TileShape &shape, int &ks) {
         i64 tiles = 0;
         ks = split_k(K, 64, tiles);

@@ -231,11 +231,11 @@ static bool chain_shared_fwd_pays(i64 M, i64 in) { return M <= 8192 && (in <= 51
 // a plain call and one with residual and ReLU, fitted to 785 shapes (7 and 10 % rms: ranks above 64, four blocks wide, cost it more than the
 // plan says, most of all where they are not whole pieces and are fitted in registers: 7 x 576 -> 67 -> 2824 10.6 / 12.9 us, 1313 x 1104
 // -> 83 -> 2016 16.0 / 19.3); at rank 128 and widths in multiples of 256 those of the chain kernel, fitted to 130 shapes.  Over the 785
-// shapes 1.42 times as fast where it is taken, three of a thousand calls more than 5 % slower; over 60 of the others 1.14 (8192 x 512 -> 128 -> 512 three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by
-// both); few rows and inputs up to 1024 wide stay with the row kernel (423 x 512 -> 512: 6.6 against 7.3).
+// shapes 1.42 times as fast where it is taken, three of a thousand calls more than 5 % slower; over 60 of the others 1.14 (8192 x 512 -> 128 -> 512
+// three times 25.4 -> 19.0 us, 8192 x 2048 -> 512 with residual 24.6 -> 18.9, 512 -> 2048 18.6 by both); few rows and inputs up to 1024 wide stay
+// with the row kernel (423 x 512 -> 512: 6.6 against 7.3).
 // Ranks from 136 to 256: tiled products fitted by themselves to 330 shapes of 64 to 19000 rows (7 % rms).  Taken for 128 of them, 1.31 times as
-// fast, none more than a tenth slower (8192 x 640 -> 160 -> 2560 37.4 / 20.8 us, tiled / two-stage; 13797 x 448 -> 176 -> 3584 68.7 / 36.9; with
-// few rows the tiles spread better: 1000 x 768 -> 192 -> 3072 12.4 / 14.9).
+// fast, none more than a tenth slower (8192 x 640 -> 160 -> 2560 37.4 / 20.8 us, tiled / two-stage; 13797 x 448 -> 176 -> 3584 68.7 / 36.9; with few rows the tiles spread better: 1000 x 768 -> 192 -> 3072 12.4 / 14.9).
 static int two_fwd_rows(i64 M, i64 in, i64 out, i64 r, int G, int &split)
 {
     if (!linear_two_supported(M, in, out, r) || rows_fwd_pays(M, in, out, r, G)) return 0;

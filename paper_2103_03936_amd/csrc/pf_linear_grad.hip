@@ -9,11 +9,13 @@ namespace pf {
 // much a compute unit has in flight towards memory, so three chunks of 64 rows (96 KB at rank 128) are in registers behind the two in
 // LDS, through descriptors (BufSrc) and without a condition, so that a wait is for the oldest of them alone.  A chunk takes 2000 clocks
 // where 240 workgroups load 9.2 TB/s, 5 of them from HBM (16384 x 2048 and x 512, rank 128: 27.6 us; 8192 18.3, of which 9 are launch, first
-// load and 16 MB of partial sums).  Ranks above 128 are six or eight blocks (FLAT: the ranks' chunk dealt out over its run of memory).  8192 rows, 512 -> 2048 and 2048 -> 512: 22.0 on the kernel of pf_linear_wgrad.hip with two tiles in flight.
+// load and 16 MB of partial sums).  Ranks above 128 are six or eight blocks (FLAT: the ranks' chunk dealt out over its run of memory).  8192 rows,
+// 512 -> 2048 and 2048 -> 512: 22.0 on the kernel of pf_linear_wgrad.hip with two tiles in flight.
 template <int RB>
 struct LinGradCfg {
     static constexpr int NT = 512, KC = 64, R = 32 * RB, RING = 3;
-    static constexpr int WM = 2, WN = RB > 1 ? RB / 2 : 1 /* (three of them: two wavefronts without ranks) */, WK = 8 / (WM * WN), NB = RB > 1 ? 2 : 1, STEPS = KC / 16; // 64 columns by 64 ranks
+    // 64 columns by 64 ranks; of three wavefronts across the ranks two without any
+    static constexpr int WM = 2, WN = RB > 1 ? RB / 2 : 1, WK = 8 / (WM * WN), NB = RB > 1 ? 2 : 1, STEPS = KC / 16;
     static constexpr int AP = 128 + 8, BP = R + 8, ABYTES = KC * AP * 2, BBYTES = KC * BP * 2, BUF = ABYTES + BBYTES;
     static constexpr int ACH = KC * 16 / NT, BPIECES = KC * RB * 4, BCH = BPIECES / NT > 0 ? BPIECES / NT : 1; // pieces per thread
     static constexpr bool FLAT = RB > 4; // the ranks' chunk, one run of memory, is dealt out piece by piece

@@ -410,7 +410,8 @@ static int lt_most(i64 r) { return r <= 128 ? 4 : r <= 192 ? 2 : 1; } // blocks 
 bool linear_two_supported(i64 M, i64 K, i64 N, i64 r)
 {
     const i64 lim = 1LL << 30;
-    return M >= 1 && K >= 8 && N >= 8 && K % 8 == 0 && N % 8 == 0 && r >= 8 && (r <= 128 || (r <= 256 && r % 8 == 0)) && M * K < lim && M * N < lim && K * r < lim && N * r < lim;
+    return M >= 1 && K >= 8 && N >= 8 && K % 8 == 0 && N % 8 == 0 && r >= 8 && (r <= 128 || (r <= 256 && r % 8 == 0)) && M * K < lim &&
+           M * N < lim && K * r < lim && N * r < lim;
 }
 
 // Fitted to times of 130 shapes (1 to 16384 rows, 128 to 4096 wide, ranks 8 to 128) with every number of rows and share of the outputs, 8 %
@@ -470,7 +471,11 @@ static int lt_rows(hipStream_t s, const char *name, const LinTwoArgs &a, int row
         return rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
     }
     if (rows == 128 && a.add && a.mask) rows = 64; // (both arrays' pieces beside the sums of 128 rows do not fit the registers)
-    if constexpr (RB <= 4) return rows == 128 ? lt_launch<RB, 4>(s, name, a) : rows == 64 ? lt_launch<RB, 2>(s, name, a) : rows == 32 ? lt_launch<RB, 1>(s, name, a) : PF_ERR_UNSUPPORTED;
+    if constexpr (RB <= 4)
+        return rows == 128  ? lt_launch<RB, 4>(s, name, a)
+               : rows == 64 ? lt_launch<RB, 2>(s, name, a)
+               : rows == 32 ? lt_launch<RB, 1>(s, name, a)
+                            : PF_ERR_UNSUPPORTED;
 }
 int launch_linear_two(hipStream_t s, const char *name, const LinTwoArgs &a, int rows)
 {

@@ -264,8 +264,8 @@ __global__ __launch_bounds__(256) void lstm_slices_pointwise_fwd_kernel(const fl
 // The products of a step on the tiled kernels (pf_tile.h), both paths (and the four gate blocks) side by side: forward
 // T; z as two slices; gates.  Backward gate derivatives; dT; dx and dh_prev; all parameter gradients, the last two in one launch where that
 // pays.  Products too small for the chip split their contraction; slices of T and dT are added by the tiles that read them, others by
-// one more launch.  Forward and backward, us, nine launches with streaming kernels for up to 32 rows before / now: 10 rows, 128 units
-// 39.8 / 22.1, 512 units 42.1 / 28.7 (a pair per gate 31.2), 1500 units 62.0 / 55; 64 rows, 512 units 39.5 / 30.5.
+// one more launch.  Forward and backward, us, factors in the caches, nine launches with streaming kernels for up to 32 rows before / now: 10 rows, 128
+// units 36.4 / 19.2, 512 units 38.7 / 25.5 (a pair per gate 38.7 / 28.2), 1500 units, backward streamed, 61.1 / 55.9; 64 rows, 512 units 34.7 / 27.2.
 static bool lstm_tiles_ok(const pf_lstm_desc *d) { return d->B > 0 && d->d_in >= 4 && d->h >= 4 && d->r >= 4; }
 
 LstmTilePlan make_lstm_tile_plan(const pf_lstm_desc *d)

@@ -17,19 +17,19 @@
 // 2^-52 of the long columns into the short ones, and what A V rounds of that stays).
 // Singular values = column norms of B, sorted by counting; the r largest triplets are scaled and written out.
 // 2048 x 512: 11.7 ms with Jacobi's preconditioner, 1.30 with the eigenvectors; 1024 x 512 with orthonormal columns 15.5 and 1.3
-// (rounding to float tells the values apart); matrices of lower rank, whose noise takes sweeps either way, 576 x 64 of rank 8 1.67 and 1.22,
-// 2304 x 256 of rank 32 15.0 and 10.3, 1024 x 512 with 16 columns twice 17.2 and 7.8.  A matrix whose eigenvalues lie close without being
-// one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.46, 1024 x 256 8.9 / 9.3.  So does
+// (rounding to float tells the values apart); matrices of lower rank, whose noise takes sweeps either way, 576 x 64 of rank 8 1.67 and 1.19,
+// 2304 x 256 of rank 32 15.0 and 10.4, 1024 x 512 with 16 columns twice 17.2 and 7.8.  A matrix whose eigenvalues lie close without being
+// one (graded down to the rounding of G) pays for both: 300 x 60 with values down to 1e-9 1.29 / 1.43, 1024 x 256 8.9 / 9.2.  So does
 // one in two blocks that share no row and no column, the first of lower rank and the other 1e-9 of it, whose columns the noise gets
 // among: 1024 x 256 12.4 / 18.0 (1e-6 of it: 12.1 / 8.6).
 //
 // A pair of eight-column blocks is a workgroup's unit: Gram matrix of the 16 columns on the matrix unit, rotations of
 // every column of one block against every column of the other (in a sweep's first round also within the blocks) found on
-// that 16 x 16 matrix in LDS by one wavefront and applied to the rows, one row per thread.  Pairs of blocks are dealt into rounds by round-robin; the rounds of all sweeps run in ONE cooperative
-// kernel with a grid barrier between them, because the number of sweeps is known on the device only: a launch per
-// round has to be enqueued for the most sweeps that may be needed, at 2.8 us each (2048 x 512: 12264 launches, 84 ms).
-// A barrier's wait is bounded: after about a second without the others a workgroup gives up; the call then reports no
-// convergence and its outputs are NaN.
+// that 16 x 16 matrix in LDS by one wavefront and applied to the rows, one row per thread.  Pairs of blocks are dealt into rounds by round-robin;
+// the rounds of all sweeps run in ONE cooperative kernel with a grid barrier between them, because the number of sweeps is known on the device only:
+// a launch per round has to be enqueued for the most sweeps that may be needed, at 2.8 us each (2048 x 512: 12264 launches, 84 ms).
+// A barrier's wait is bounded: after about two seconds in which those it waits for have not got on a workgroup gives up; the call then
+// reports no convergence and its outputs are NaN.
 #include "pf_gemm.h"
 #include "pf_svd_eigen.h"
 

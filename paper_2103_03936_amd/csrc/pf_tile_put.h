@@ -78,10 +78,10 @@ __device__ __forceinline__ void put_piece(const TileProb &p, int ks, int zb, int
     }
 }
 
-// A tile of planes with its epilogue (the sums over k of a split product: row-major).  A thread's pieces lie in the same columns of several rows.  What is added to up to four
-// of them, scales and masks them is requested before the first is used: piece by piece, and element by element in planes that are no whole
-// pieces, it was a chain of up to 24 waits, 4 to 5 us of a launch of 12.  A piece that would end past the array is pulled back inside and shifted
-// into place, as the operands' are.
+// A tile of planes with its epilogue (the sums over k of a split product: row-major).  A thread's pieces lie in the same columns of several rows.
+// What is added to up to four of them, scales and masks them is requested before the first is used: piece by piece, and element by element in planes
+// that are no whole pieces, it was a chain of up to 24 waits, 4 to 5 us of a launch of 12.  A piece that would end past the array is pulled back
+// inside and shifted into place, as the operands' are.
 template <typename CT, class CFG>
 __device__ __forceinline__ void put_planes(const TileProb &p, int ks, int zb, int m0, int n0, const unsigned char *smem, int tid)
 {
