@@ -807,7 +807,9 @@ def run_workload(args, torch, pf, workloads, name, lstm_groups=1):
             step_s = kernels[dom]["avg_us"] * 1e-6 * per_step  # time this kernel takes per step, all layers
             bound = "mfma" if kflops / kbytes >= peak * 1e12 / (HBM_GBS * 1e9) else "hbm"
             roofline.update({"bound": bound, "launches_per_step": per_step, "algorithmic_flops_per_step": kflops,
-                             "algorithmic_bytes_per_step": kbytes, "traffic": measured_traffic(wl.name, dom)})
+                             "algorithmic_bytes_per_step": kbytes,
+                             # (counters were taken with one factor pair per path)
+                             "traffic": measured_traffic(wl.name, dom) if getattr(wl, "groups", 1) == 1 else None})
             if bound == "mfma":
                 roofline.update({"achieved": kflops / step_s / 1e12, "peak": peak, "unit": "TFLOP/s",
                                  "frac": kflops / step_s / 1e12 / peak})
